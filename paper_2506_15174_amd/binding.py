@@ -5,12 +5,14 @@ library (host inspector in C++, executor in HIP for gfx950).  There is no
 Python or CPU fallback: if the library is missing, loading fails.
 """
 import ctypes
+import importlib.util
 import os
 
 import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "lib", "libspmm_cdna4.so")
+TORCH_EXT_PATH = os.path.join(HERE, "lib", "_spmm_torch.so")
 
 SPMM_OK = 0
 SPMM_ERR_INVALID_ARG = 1
@@ -58,17 +60,19 @@ class SpmmError(RuntimeError):
 
 
 _lib = None
+_execute_tensors = None  # the native tensor-level entry (csrc/spmm_torch.cpp)
 
 
 def load():
-    """Load the shared library (raises if it has not been built)."""
-    global _lib
+    """Load the shared library and the tensor-level entry (raises if they have not been built)."""
+    global _lib, _execute_tensors
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise RuntimeError(
-            "HIP library %s is missing: run `python -m paper_2506_15174_amd.build` "
-            "(there is no fallback path)" % LIB_PATH)
+    for path in (LIB_PATH, TORCH_EXT_PATH):
+        if not os.path.exists(path):
+            raise RuntimeError(
+                "HIP library %s is missing: run `python -m paper_2506_15174_amd.build` "
+                "(there is no fallback path)" % path)
     # PyTorch ships its own copy of the HIP runtime (same soname as the system
     # one).  The tensors and streams handed to spmm_execute belong to that copy,
     # so it must be the one already resident when this library is mapped.
@@ -94,6 +98,10 @@ def load():
     lib.spmm_plan_get_array.argtypes = [vp, i32, vp, i64, ctypes.POINTER(i64)]
     lib.spmm_status_string.restype = ctypes.c_char_p
     lib.spmm_status_string.argtypes = [ctypes.c_int]
+    spec = importlib.util.spec_from_file_location("_spmm_torch", TORCH_EXT_PATH)
+    ext = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(ext)
+    _execute_tensors = ext.execute
     _lib = lib
     return lib
 
@@ -114,8 +122,9 @@ def _ptr(arr):
 class Plan:
     """Owner of one spmm_plan_t*.  Same calls as the C ABI, numpy/torch marshalled."""
 
-    def __init__(self, handle):
+    def __init__(self, handle, M, K):
         self._h = handle
+        self._address, self._M, self._K = handle.value, M, K
         self._info = None
 
     @property
@@ -164,26 +173,15 @@ class Plan:
         tensor (M x N); allocated when omitted.  Runs on `stream` or on torch's
         current stream.  Returns C.
         """
-        import torch
-        if not (B.is_cuda and B.dtype == torch.float32 and B.is_contiguous() and B.dim() == 2):
-            raise ValueError("B must be a contiguous 2-D float32 device tensor")
-        info = self._info or self.describe()
-        if B.shape[0] != info["K"]:
-            raise ValueError("B has %d rows, A has %d columns" % (B.shape[0], info["K"]))
-        N = B.shape[1]
-        if C is None:
-            C = torch.empty((info["M"], N), dtype=torch.float32, device=B.device)
-        if not (C.is_cuda and C.dtype == torch.float32 and C.is_contiguous()
-                and tuple(C.shape) == (info["M"], N)):
-            raise ValueError("C must be a contiguous float32 device tensor of shape (M, N)")
-        s = stream if stream is not None else torch.cuda.current_stream(B.device)
-        self.execute_raw(B.data_ptr() or None, N, C.data_ptr() or None, s.cuda_stream or None)
+        C = _execute_tensors(self._address, self._M, self._K, B, C, stream)
+        if type(C) is int:
+            raise SpmmError(C, "spmm_execute")
         return C
 
     def destroy(self):
         if self._h is not None:
             _check(load().spmm_plan_destroy(self._h), "spmm_plan_destroy")
-            self._h = None
+            self._h, self._address = None, 0
 
     def __del__(self):
         try:
@@ -212,4 +210,4 @@ def plan_create(M, K, row_ptr, col_idx, vals, group_nnz=0, group_panels=0, host_
         st = lib.spmm_plan_create(ctypes.byref(handle), int(M), int(K), _ptr(row_ptr),
                                   _ptr(col_idx), _ptr(vals))
     _check(st, "spmm_plan_create")
-    return Plan(handle)
+    return Plan(handle, int(M), int(K))

@@ -12,6 +12,9 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB_DIR = os.path.join(HERE, "lib")
 LIB_PATH = os.path.join(LIB_DIR, "libspmm_cdna4.so")
+# the tensor-level entry (spmm_torch.cpp): a Python extension module beside the library
+TORCH_EXT_SOURCE = "spmm_torch.cpp"
+TORCH_EXT_PATH = os.path.join(LIB_DIR, "_spmm_torch.so")
 
 SOURCES = ["spmm_kernels.hip", "spmm_plan.cpp", "spmm_api.cpp"]
 HEADERS = ["spmm_format.h", "spmm_kernels.h", "spmm_plan.h"]
@@ -28,10 +31,10 @@ def _hipcc():
 
 
 def is_stale():
-    if not os.path.exists(LIB_PATH):
+    if not os.path.exists(LIB_PATH) or not os.path.exists(TORCH_EXT_PATH):
         return True
-    t = os.path.getmtime(LIB_PATH)
-    deps = [os.path.join(CSRC, f) for f in SOURCES + HEADERS]
+    t = min(os.path.getmtime(LIB_PATH), os.path.getmtime(TORCH_EXT_PATH))
+    deps = [os.path.join(CSRC, f) for f in SOURCES + HEADERS + [TORCH_EXT_SOURCE]]
     deps.append(os.path.join(os.path.dirname(HERE), "include", "spmm.h"))
     return any(os.path.getmtime(d) > t for d in deps)
 
@@ -105,7 +108,26 @@ def build(verbose=False):
         objects.append(obj)
     _run([hipcc, "-shared", "-fPIC"] + objects +
          ["-L", os.path.join(ROCM, "lib"), "-lamdhip64", "-pthread", "-o", LIB_PATH], verbose)
+    build_torch_extension(verbose)
     return LIB_PATH
+
+
+def build_torch_extension(verbose=False):
+    """Compile the tensor-level entry (host code: plain C++ against torch's headers), linked
+    to the library beside it.  torch's own copy of the HIP runtime is the one in the process
+    (see binding.load), so no runtime is named here."""
+    import sysconfig
+    import torch
+    root = os.path.dirname(torch.__file__)
+    _run([shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+          "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+          "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(ROCM, "include"),
+          os.path.join(CSRC, TORCH_EXT_SOURCE), "-o", TORCH_EXT_PATH,
+          "-L", LIB_DIR, "-lspmm_cdna4", "-Wl,-rpath,$ORIGIN",
+          "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath," + os.path.join(root, "lib")],
+         verbose)
+    return TORCH_EXT_PATH
 
 
 if __name__ == "__main__":
