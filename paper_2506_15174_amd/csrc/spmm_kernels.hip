@@ -316,17 +316,33 @@ constexpr int waves_per_simd(int S, int UFI, int UFKT, bool WIDE)
     return WIDE ? (narrow > 4 ? narrow - 2 : 2) : narrow;
 }
 
+// Arguments of a launch as one structure: the runtime copies a kernel's arguments one by one,
+// about 60 ns each, and the host's share of a launch is what paces the shortest products
+// (fourteen separate arguments 3.5 us per launch of an empty kernel, one structure 2.65 us).
+struct chunk_args {
+    const uint32_t *stream, *wins, *items, *rowmap;
+    const float *B;
+    float *C, *cross_sums;
+    uint32_t b_bytes, col_mask, n_cross_slots;
+    int32_t ldn, ldc, width, tile_cols;
+};
+
 // PROBE instances request and await every B row exactly as the product does but skip the
 // value reads and the multiply-adds (C becomes all zeros): the time of such a launch is the
 // on-chip gather ceiling of the plan's own index stream.
 template <int UFI, int S, int VW, int D, bool WIDE, int UFKT = UFK, bool PROBE = false>
 __global__ __launch_bounds__(64 * WAVES_PER_WG, (waves_per_simd(S, UFI, UFKT, WIDE))) void
-spmm_chunks_kernel(const uint32_t *__restrict__ stream_g,
-                   const uint32_t *__restrict__ wins_g, const uint32_t *__restrict__ items_g,
-                   const uint32_t *__restrict__ rowmap_g, const float *__restrict__ B_all, uint32_t b_bytes_all,
-                   float *__restrict__ C_all, int32_t ldn, int32_t ldc, int32_t width_all, int32_t tile_cols, uint32_t col_mask,
-                   float *__restrict__ cross_sums, uint32_t n_cross_slots)
+spmm_chunks_kernel(const chunk_args args)
 {
+    const uint32_t *__restrict__ stream_g = args.stream;
+    const uint32_t *__restrict__ wins_g = args.wins;
+    const uint32_t *__restrict__ items_g = args.items;
+    const uint32_t *__restrict__ rowmap_g = args.rowmap;
+    const float *__restrict__ B_all = args.B;
+    float *__restrict__ C_all = args.C;
+    float *__restrict__ cross_sums = args.cross_sums;
+    const uint32_t b_bytes_all = args.b_bytes, col_mask = args.col_mask, n_cross_slots = args.n_cross_slots;
+    const int32_t ldn = args.ldn, ldc = args.ldc, width_all = args.width, tile_cols = args.tile_cols;
     // blockIdx.y: the column tile this workgroup computes (tiles of tile_cols columns of
     // the width_all columns of this launch; the last one may be narrower).  Workgroups
     // are started tile by tile, so a tile begins while the previous one drains.
@@ -632,9 +648,10 @@ spmm_kslice_combine_kernel(const float *__restrict__ sums, int32_t k_slices, uin
 template <int U, int S, int VW, int D, bool WIDE, int UFKT = UFK, bool PROBE = false>
 void launch_instance(const spmm_launch_args &a, void *stream)
 {
+    const chunk_args args{a.stream, a.wins, a.items, a.rowmap, a.B, a.C, a.cross_sums, a.b_bytes, a.col_mask, a.n_cross_slots,
+                          a.ldn, a.ldc, a.width, a.tile_cols};
     hipLaunchKernelGGL((spmm_chunks_kernel<U, S, VW, D, WIDE, UFKT, PROBE>), dim3((unsigned)a.n_blocks, (unsigned)a.n_tiles),
-                       dim3(64 * WAVES_PER_WG), a.lds_pad, (hipStream_t)stream, a.stream, a.wins, a.items, a.rowmap,
-                       a.B, a.b_bytes, a.C, a.ldn, a.ldc, a.width, a.tile_cols, a.col_mask, a.cross_sums, a.n_cross_slots);
+                       dim3(64 * WAVES_PER_WG), a.lds_pad, (hipStream_t)stream, args);
 }
 
 // One (height, slices) pair at the pipeline depth asked for.  DMAX is the depth the
