@@ -11,6 +11,7 @@
 #include "spmm_format.h"
 #include "spmm_kernels.h"
 #include "spmm_plan.h"
+#include "spmm_tiles.h"
 
 using namespace spmm_fmt;
 
@@ -27,6 +28,7 @@ struct spmm_plan {
     // Plans cut along K: the slices' sums of one batch of up to KSLICE_COLS columns
     // (k_slices x slice_rows rows), written by every execute.
     float *d_slice_sums = nullptr;
+    TilePlan tiles;           // tiles.rows > 0: the entries are in tiles and the product runs on the matrix cores
     int64_t scratch_bytes = 0;
     int64_t device_bytes = 0;
     int64_t stream_words = 0;  // length of host.stream at creation (a device plan drops its host mirror)
@@ -67,6 +69,16 @@ spmm_status_t upload(T **dst, const void *src, size_t bytes, int64_t &total)
     return SPMM_OK;
 }
 
+// Whether the arrays can be handed to a device: dimensions, pointers and the row pointer
+// (the inspector, which checks the same, names the fault of arrays that cannot).
+bool row_pointer_ok(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals)
+{
+    if (M <= 0 || K <= 0 || M > INT32_MAX || K > INT32_MAX || !row_ptr || row_ptr[0] != 0 || !col_idx || !vals) return false;
+    for (int64_t i = 0; i < M; ++i)
+        if (row_ptr[i + 1] < row_ptr[i]) return false;
+    return true;
+}
+
 void release_device(spmm_plan *p)
 {
     if (p->d_stream) (void)hipFree(p->d_stream);
@@ -78,6 +90,7 @@ void release_device(spmm_plan *p)
     if (p->d_slice_sums) (void)hipFree(p->d_slice_sums);
     p->d_stream = p->d_wins = p->d_items = p->d_rowmap = p->d_cross_table = nullptr;
     p->d_cross_sums = p->d_slice_sums = nullptr;
+    spmm_tiles_release(p->tiles);
     (void)hipGetLastError();
 }
 
@@ -91,8 +104,8 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
     if (!plan) return SPMM_ERR_INVALID_ARG;
     *plan = nullptr;
     InspectorOptions io;
-    bool host_only = false, force_wide = false, probe = false;
-    int depth = 0;
+    bool host_only = false, force_wide = false, probe = false, schedule_forced = false;
+    int depth = 0, tiles = 0;
     if (opts) {
         if (opts->group_nnz < 0 || opts->group_panels < 0 || opts->n_hint < 0) return SPMM_ERR_INVALID_ARG;
         if (opts->ufi != 0 && opts->ufi != 1 && opts->ufi != 2 && opts->ufi != 4 && opts->ufi != 8)
@@ -119,12 +132,27 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
         if (io.kslices > 1 && io.ufk != 0 && io.ufk != UFK) return SPMM_ERR_INVALID_ARG;  // only plans with chunks of 8 are cut
         depth = opts->depth;
         probe = opts->probe != 0;
+        if (opts->tiles > 0 && opts->tiles != 16 && opts->tiles != 32) return SPMM_ERR_INVALID_ARG;
+        tiles = opts->tiles;
+        // settings of the chunk path ask for the chunk path
+        schedule_forced = opts->ufi || opts->group_nnz || opts->group_panels || opts->sort_rows || force_wide || depth || opts->cross ||
+                          opts->ufk || probe || opts->kslices;
         if (probe && (force_wide || depth != 0 || (io.ufk != 0 && io.ufk > 16))) return SPMM_ERR_INVALID_ARG;
     }
     spmm_plan *p = new (std::nothrow) spmm_plan();
     if (!p) return SPMM_ERR_ALLOC;
-    const int rc = spmm_inspect(M, K, row_ptr, col_idx, vals, io, p->host);
+    int rc = 0;
+    if (!host_only && tiles >= 0 && (tiles > 0 || !schedule_forced) && row_pointer_ok(M, K, row_ptr, col_idx, vals)) {
+        if (tiles == 0) tiles = choose_tiles(M, K, row_ptr, io.n_hint);
+        if (tiles > 0) {
+            rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
+            if (rc == TILES_NOT_POSSIBLE) rc = 0;
+            io.schedule_only = p->tiles.rows > 0;
+        }
+    }
+    if (rc == 0) rc = spmm_inspect(M, K, row_ptr, col_idx, vals, io, p->host);
     if (rc != 0) {
+        release_device(p);
         delete p;
         return (spmm_status_t)rc;
     }
@@ -133,11 +161,15 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
     p->probe = probe;
     if (!host_only) {
         if (hipGetDevice(&p->device) != hipSuccess) {
+            release_device(p);
             delete p;
             return hip_fail();
         }
         const HostPlan &h = p->host;
         spmm_status_t st = SPMM_OK;
+        if (p->tiles.rows > 0) {
+            p->device_bytes = p->tiles.device_bytes;
+        } else {
         if (st == SPMM_OK) st = upload(&p->d_stream, h.stream.data(), h.stream.size() * 4, p->device_bytes);
         if (st == SPMM_OK) st = upload(&p->d_wins, h.wins.data(), h.wins.size() * 4, p->device_bytes);
         if (st == SPMM_OK) st = upload(&p->d_items, h.items.data(), h.items.size() * 4, p->device_bytes);
@@ -159,6 +191,7 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
             st = upload(&p->d_slice_sums, nullptr, (size_t)h.plan_rows * KSLICE_COLS * sizeof(float), p->device_bytes);
             p->scratch_bytes += p->device_bytes - before;
         }
+        }
         if (st != SPMM_OK) {
             release_device(p);
             delete p;
@@ -166,7 +199,11 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
         }
         p->on_device = true;
     }
-    p->stream_words = (int64_t)p->host.stream.size();
+    p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : (int64_t)p->host.stream.size();
+    if (p->tiles.rows > 0) {
+        p->host.n_enum = p->tiles.n_panels * K;
+        p->host.n_chunks = p->tiles.n_panels * p->tiles.n_steps;
+    }
     if (p->on_device) {
         // the arrays live on the device now: keep the descriptors (row groups, sizes), not the mirror
         std::vector<uint32_t>().swap(p->host.stream);
@@ -203,6 +240,9 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return hip_fail();
     if (dev != plan->device) return SPMM_ERR_INVALID_ARG;
+
+    if (plan->tiles.rows > 0)
+        return spmm_tiles_execute(plan->tiles, h.M, h.K, B, N, C, stream) == 0 ? SPMM_OK : hip_fail();
 
     const uint64_t b_total = (uint64_t)h.K * (uint64_t)N * 4u;
     // Narrow addressing: 32-bit byte offsets into B formed by a 24 x 24-bit multiply.
@@ -306,8 +346,8 @@ spmm_status_t spmm_execute_static(const spmm_plan_t *plan, const float *B, int32
 {
     if (!plan) return SPMM_ERR_INVALID_ARG;
     const HostPlan &h = plan->host;
-    if (h.k_slices > 1 && plan->on_device) return SPMM_ERR_UNSUPPORTED;  // the slices' buffer is beyond the static array
-    if (h.n_cross_slots == 0 || !plan->on_device) return execute_with(plan, B, N, C, stream, nullptr, 0);
+    if (h.k_slices > 1 && plan->on_device && plan->tiles.rows == 0) return SPMM_ERR_UNSUPPORTED;  // the slices' buffer is beyond the static array
+    if (h.n_cross_slots == 0 || !plan->on_device || plan->tiles.rows > 0) return execute_with(plan, B, N, C, stream, nullptr, 0);
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return hip_fail();
     if (dev != plan->device) return SPMM_ERR_INVALID_ARG;
@@ -354,6 +394,7 @@ spmm_status_t spmm_plan_describe(const spmm_plan_t *plan, spmm_plan_info_t *out)
     out->k_slices = h.k_slices;
     out->slice_rows = h.slice_rows;
     out->slice_cols = h.slice_cols;
+    out->tile_rows = plan->tiles.rows;
     return SPMM_OK;
 }
 

@@ -51,11 +51,16 @@ struct InspectorOptions {
     int32_t cross = 0;         // 0 = choose whether panels may be cut across blocks; < 0 = never; > 0 = always
     int32_t ufk = 0;           // 0 = choose; else columns per chunk: 8, 16, 32 or 64
     int32_t kslices = 0;       // 0 = choose; 1 = never cut along K; 2, 4 or 8 = so many slices
+    bool schedule_only = false; // constants, row groups and blocks, but no chunks: for plans whose entries live in
+                                // tiles (spmm_tiles.h).  vals is not read and the columns must have been checked.
 };
 
 // Status codes follow spmm_status_t (0 ok, 1 invalid argument, 2 invalid CSR,
 // 3 allocation failure, 5 unsupported size).
 int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx,
                  const float *vals, const InspectorOptions &opts, HostPlan &out);
+
+// Rows per panel (32 or 16) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.
+int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint);
 
 #endif

@@ -1,0 +1,564 @@
+// gfx950 executor and builder of the matrix-core path: C <- A x B with A in bitmap tiles
+// (format: spmm_tiles.h).
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "spmm_tiles.h"
+
+namespace {
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr int OPS = TILE_OPERANDS;
+constexpr int A_SLOT_WORDS = TILE_PLACE0 / 4 + 1024;  // the expanded block behind the dump word
+
+// ---------------------------------------------------------------- executor
+
+struct tile_args {
+    const uint32_t *stream, *offsets;
+    const float *B;
+    float *C;
+    uint64_t b_bytes;   // bytes of B
+    int32_t n_panels, n_steps, n_tiles, M, K, N;
+};
+
+template <int NB> struct BVec;
+template <> struct BVec<1> { typedef float type; };
+template <> struct BVec<2> { typedef f32x2 type; };
+template <> struct BVec<4> { typedef f32x4 type; };
+
+__device__ __forceinline__ float part(float v, int) { return v; }
+__device__ __forceinline__ float part(const f32x2 &v, int j) { return v[j]; }
+__device__ __forceinline__ float part(const f32x4 &v, int j) { return v[j]; }
+
+template <int NB> __device__ __forceinline__ typename BVec<NB>::type buffer_load(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    if constexpr (NB == 1) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+    else if constexpr (NB == 2) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+        return f32x2{__uint_as_float(v[0]), __uint_as_float(v[1])};
+    } else {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
+        return f32x4{__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3])};
+    }
+}
+
+template <int R> struct Tile;
+template <> struct Tile<32> {
+    typedef f32x16 acc_t;
+    static constexpr int GROUPS = 4;  // groups of four accumulator registers
+    static __device__ __forceinline__ acc_t mfma(float b, float a, const acc_t &c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, c, 0, 0, 0); }
+};
+template <> struct Tile<16> {
+    typedef f32x4 acc_t;
+    static constexpr int GROUPS = 1;
+    static __device__ __forceinline__ acc_t mfma(float b, float a, const acc_t &c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0); }
+};
+
+// One workgroup computes a tile of C: R rows x NB * R columns.
+//
+// R       rows of a panel (32: v_mfma_f32_32x32x2, 16: v_mfma_f32_16x16x4; fp32 operands and sums)
+// NB      column groups of the tile.  Lane l holds columns NB * (l % R) .. + NB - 1 of a row of B, so
+//         that one load of NB words feeds NB matrix instructions
+// W       waves of the workgroup; they share the tile and cut K: wave w multiplies steps w, w + W, ...
+//         of the panel, which keeps the workgroup's rows of B together in the L2, and the waves'
+//         partial tiles meet in LDS at the end, in a fixed order
+// STAGED  rows of B pass through LDS (loads of one word per lane would cost the address path as much
+//         as loads of four: 16 cycles each); wider tiles load them straight into registers
+// WIDE    64-bit addresses of B, word by word: for the few N whose rows of a step span 4 GiB
+//
+// A wave's step: its block's entries, fetched one step ahead (16-byte loads), are scattered to their
+// places in a zeroed 4 KiB slot of LDS, read back as 16 operands per lane (four 16-byte reads), the
+// slot is zeroed again for the next block, and 16 * NB matrix instructions multiply.
+//
+// What bounds it: the matrix cores' fp32 rate (157 TFLOP/s dense) times the density.  fp32 matrix
+// instructions occupy the vector ALUs (a microbenchmark's 481 us of them and 634 us of integer adds
+// take 1086 us together), so every vector instruction beside them costs: expanding the blocks from
+// bitmaps in registers took 48 to 130 vector instructions per step, the scatter takes about 20, for
+// 6 bytes per entry instead of 4.3.  8192 x 8192 at 50 %, 128 columns: 134 us = 64 TFLOP/s of the
+// entries' products, 128 TFLOP/s on the matrix cores (matrix instructions alone: 121 us); the chunk
+// kernel takes 218 us there.  Splitting the operands into three bf16 parts (nine exact products on
+// the bf16 cores) was no faster: 142 us, at a clock the power limit pulls down to 1.7 GHz.
+template <int R, int NB, int W, bool STAGED, bool WIDE, int MINW>
+__global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_args args)
+{
+    typedef typename BVec<NB>::type bvec_t;
+    typedef typename Tile<R>::acc_t acc_t;
+    constexpr int KO = 64 / R;        // columns of A per operand
+    constexpr int KS = OPS * KO;      // ... per step
+    constexpr int NT = NB * R;        // columns of C per tile
+    constexpr int QUADS = NB * Tile<R>::GROUPS;
+    constexpr int B_SLOT_FLOATS = STAGED ? KS * NT : 0;
+    constexpr int B_LOADS = STAGED ? KS * NT / 256 : 1;
+    constexpr int SLOT = A_SLOT_WORDS + B_SLOT_FLOATS;
+    constexpr int RED = (W / 2) * QUADS * 256;
+    constexpr int LDS_WORDS = W * SLOT > RED ? W * SLOT : RED;
+    __shared__ __attribute__((aligned(16))) float lds[LDS_WORDS];
+
+    // Panel p runs on XCD p % 8 (workgroups are dealt to the XCDs in turn), all its column
+    // tiles one after the other, so that its blocks are read into one L2.
+    const uint32_t g8 = blockIdx.x / 8u;
+    const uint32_t nt = g8 % (uint32_t)args.n_tiles;
+    const uint32_t panel = (g8 / (uint32_t)args.n_tiles) * 8u + blockIdx.x % 8u;
+    if (panel >= (uint32_t)args.n_panels) return;
+    const uint32_t n0 = nt * (uint32_t)NT;
+
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63);
+    float *slot = lds + wave * SLOT;
+    float *bslot = slot + A_SLOT_WORDS;
+    const uint32_t n_steps = (uint32_t)args.n_steps;
+    const uint32_t *off_p = args.offsets + (size_t)panel * (n_steps + 1);
+    const uint32_t N = (uint32_t)args.N;
+    const uint32_t count = n_steps > (uint32_t)wave ? (n_steps - (uint32_t)wave + W - 1) / W : 0u;  // steps of this wave
+
+    acc_t acc[NB];
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j] = acc_t{};
+
+    // descriptor of the rows of B from step s on
+    auto b_rsrc = [&](uint32_t s) {
+        const uint64_t skip = ((uint64_t)s * KS * N + n0) * 4u;
+        const uint64_t left = args.b_bytes > skip ? args.b_bytes - skip : 0u;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(args.B)) + skip, (short)0,
+                                                 (int)(left > 0xFFFFFFFCull ? 0xFFFFFFFCu : (uint32_t)left), 0x00020000);
+    };
+    const uint32_t lane_off = ((uint32_t)(lane / R) * N + (uint32_t)(NB * (lane % R))) * 4u;                       // direct loads
+    const uint32_t stage_off = ((uint32_t)(lane * 4 / NT) * N + (uint32_t)(lane * 4 % NT)) * 4u;                   // staged loads
+    const uint32_t op_pitch = (uint32_t)KO * N * 4u, stage_pitch = (uint32_t)(256 / NT) * N * 4u;
+
+    {
+        f32x4 *z = reinterpret_cast<f32x4 *>(slot + TILE_PLACE0 / 4) + lane;
+#pragma unroll
+        for (int q = 0; q < OPS / 4; ++q) z[64 * q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+    uint32_t lo = 0, hi = 0;  // lane i: bounds of the block of step 64 * (batch) + i of this wave
+    f32x4 va[4];   // values of the block in flight, 256 entries at a time
+    u32x2 vp[4];   // their places in the expanded block
+    uint32_t n_next = 0;
+    auto fetch_a = [&](uint32_t i) {
+        if ((i & 63u) == 0) {
+            const uint32_t s = (uint32_t)wave + W * (i + (uint32_t)lane);
+            lo = s < n_steps ? off_p[s] : 0u;
+            hi = s < n_steps ? off_p[s + 1] : 0u;
+        }
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)(i & 63u));
+        n_next = 8u * ((uint32_t)__builtin_amdgcn_readlane((int)hi, (int)(i & 63u)) - a);
+        const char *block = reinterpret_cast<const char *>(args.stream) + (size_t)a * 48u;
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(block), (short)0, (int)(n_next * 4u), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(block) + (size_t)n_next * 4u, (short)0, (int)(n_next * 2u), 0x00020000);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q == 0 || n_next > 256u * (uint32_t)q) {
+                va[q] = buffer_load<4>(rv, (uint32_t)lane * 16u + 1024u * (uint32_t)q);
+                vp[q] = __builtin_amdgcn_raw_buffer_load_b64(rp, (int)((uint32_t)lane * 8u + 512u * (uint32_t)q), 0, 0);
+            }
+    };
+    f32x4 vb[B_LOADS];
+    auto fetch_b = [&](uint32_t i) {
+        const __amdgpu_buffer_rsrc_t r = b_rsrc((uint32_t)wave + W * i);
+#pragma unroll
+        for (int q = 0; q < B_LOADS; ++q) vb[q] = buffer_load<4>(r, stage_off + (uint32_t)q * stage_pitch);
+    };
+    constexpr int BATCH = NB == 2 && W == 16 ? 4 : 8;  // operands whose rows of B are requested together
+    bvec_t bq[2][BATCH];
+    auto fetch_batch = [&](__amdgpu_buffer_rsrc_t r, int k) {
+#pragma unroll
+        for (int t = 0; t < BATCH; ++t) bq[k % 2][t] = buffer_load<NB>(r, lane_off + (uint32_t)(k * BATCH + t) * op_pitch);
+    };
+    auto fetch_batch_wide = [&](uint32_t s, int k) {  // rows and columns outside B repeat its last ones (never used)
+#pragma unroll
+        for (int t = 0; t < BATCH; ++t) {
+            const uint64_t row = (uint64_t)s * KS + (uint32_t)((k * BATCH + t) * KO + lane / R);
+            const float *p = args.B + (row < (uint64_t)args.K ? row : (uint64_t)args.K - 1u) * N;
+            if constexpr (NB == 4)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t n = n0 + (uint32_t)(4 * (lane % R) + j);
+                    bq[k % 2][t][j] = p[n < N ? n : N - 1u];
+                }
+        }
+    };
+    auto fetch_rows = [&](uint32_t s, int k) {
+        if constexpr (WIDE) fetch_batch_wide(s, k);
+        else fetch_batch(b_rsrc(s), k);
+    };
+
+    if (count > 0) {
+        fetch_a(0);
+        if constexpr (STAGED) fetch_b(0);
+        else fetch_rows((uint32_t)wave, 0);
+        for (uint32_t i = 0; i < count; ++i) {
+            // ---- this step's entries (and rows of B) go to the wave's slot: every entry to its
+            //      place in the expanded block, which is all zeros at this point
+            const uint32_t n = n_next;
+            char *cslot = reinterpret_cast<char *>(slot);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (q == 0 || n > 256u * (uint32_t)q) {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        *reinterpret_cast<float *>(cslot + ((vp[q][x / 2] >> (16 * (x % 2))) & 0xFFFFu)) = va[q][x];
+                }
+            if constexpr (STAGED) {
+#pragma unroll
+                for (int q = 0; q < B_LOADS; ++q) reinterpret_cast<f32x4 *>(bslot)[lane + 64 * q] = vb[q];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // ---- the next step's data
+            const bool more = i + 1 < count;
+            if (more) {
+                fetch_a(i + 1);
+                if constexpr (STAGED) fetch_b(i + 1);
+            }
+            // ---- the lane's 16 values of A, and zeros for the next block
+            f32x4 *z = reinterpret_cast<f32x4 *>(slot + TILE_PLACE0 / 4) + lane;
+            f32x4 a4[OPS / 4];
+#pragma unroll
+            for (int q = 0; q < OPS / 4; ++q) a4[q] = z[64 * q];
+#pragma unroll
+            for (int q = 0; q < OPS / 4; ++q) z[64 * q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            // ---- multiply
+            auto multiply = [&](int t, const bvec_t &bt) {
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[j] = Tile<R>::mfma(part(bt, j), a4[t / 4][t % 4], acc[j]);
+            };
+            if constexpr (STAGED) {
+#pragma unroll
+                for (int t = 0; t < OPS; ++t) multiply(t, *reinterpret_cast<const bvec_t *>(bslot + (t * 64 + lane) * NB));
+            } else {
+#pragma unroll
+                for (int k = 0; k < OPS / BATCH; ++k) {
+                    if (k + 1 < OPS / BATCH) fetch_rows((uint32_t)wave + W * i, k + 1);
+                    else if (more) fetch_rows((uint32_t)wave + W * (i + 1), 0);
+#pragma unroll
+                    for (int t = 0; t < BATCH; ++t) multiply(k * BATCH + t, bq[k % 2][t]);
+                }
+            }
+        }
+    }
+
+    // ---- add the waves' tiles: the upper half of the waves parks its tiles, the lower half
+    //      adds them to its own, then all waves share the rest of the sum (fixed order)
+    f32x4 quad[QUADS];
+#pragma unroll
+    for (int f = 0; f < QUADS; ++f) {
+        const int g = f / NB, q = f % NB;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) quad[f][x] = acc[(4 * q + x) % NB][4 * g + (4 * q + x) / NB];
+    }
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+    __syncthreads();
+    if (wave >= W / 2) {
+#pragma unroll
+        for (int f = 0; f < QUADS; ++f) red[((wave - W / 2) * QUADS + f) * 64 + lane] = quad[f];
+    }
+    __syncthreads();
+    if (wave < W / 2) {
+#pragma unroll
+        for (int f = 0; f < QUADS; ++f) {
+            f32x4 *p = &red[(wave * QUADS + f) * 64 + lane];
+            *p = quad[f] + *p;
+        }
+    }
+    __syncthreads();
+    const uint32_t row = panel * (uint32_t)R + (uint32_t)(lane % R);
+    if (row >= (uint32_t)args.M) return;
+#pragma unroll
+    for (int f0 = 0; f0 < QUADS; f0 += W) {
+        const int f = f0 + wave;
+        if (f >= QUADS) break;
+        f32x4 sum = red[f * 64 + lane];
+#pragma unroll
+        for (int u = 1; u < W / 2; ++u) sum += red[(u * QUADS + f) * 64 + lane];
+        const uint32_t n = n0 + (uint32_t)(NB * (4 * KO * (f / NB) + 4 * (lane / R)) + 4 * (f % NB));
+        float *dst = args.C + (size_t)row * N + n;
+        if (n + 4 <= N) {
+            *reinterpret_cast<f32x4_unaligned *>(dst) = sum;
+        } else {
+            for (uint32_t x = 0; x < 4; ++x)
+                if (n + x < N) dst[x] = sum[(int)x];
+        }
+    }
+}
+
+template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void launch(tile_args &a, hipStream_t s)
+{
+    a.n_tiles = (a.N + NB * R - 1) / (NB * R);
+    const unsigned blocks = (unsigned)((a.n_panels + 7) / 8) * 8u * (unsigned)a.n_tiles;
+    hipLaunchKernelGGL((spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>), dim3(blocks), dim3(64 * W), 0, s, a);
+}
+
+// ---------------------------------------------------------------- builder
+
+struct position {
+    uint32_t step, op, lane;
+};
+template <int R> __device__ __forceinline__ position position_of(uint32_t row, uint32_t col)
+{
+    constexpr uint32_t KO = 64 / R, KS = OPS * KO;
+    return position{col / KS, col % KS / KO, row % R + R * (col % KO)};
+}
+
+enum { BAD_COLUMN = 1, TWICE = 2 };
+
+constexpr int MASK_WORDS = 32;  // bitmap of a block while the plan is built: 16 bits per lane
+
+// One wave per row: sets the entries' bits.
+template <int R> __global__ __launch_bounds__(256) void mark_kernel(const int32_t *row_ptr, const int32_t *col_idx, int64_t M, int64_t K, int64_t n_steps,
+                                                                    uint32_t *masks, uint32_t *flags)
+{
+    const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
+    if (row >= M) return;
+    uint32_t bad = 0;
+    for (int64_t q = row_ptr[row] + (int64_t)(threadIdx.x & 63); q < row_ptr[row + 1]; q += 64) {
+        const int32_t c = col_idx[q];
+        if (c < 0 || (int64_t)c >= K) {
+            bad |= BAD_COLUMN;
+            continue;
+        }
+        const position p = position_of<R>((uint32_t)row, (uint32_t)c);
+        uint32_t *word = masks + ((size_t)(row / R) * n_steps + p.step) * MASK_WORDS + p.lane / 2;
+        const uint32_t bit = 1u << (p.lane % 2 * 16 + p.op);
+        if (atomicOr(word, bit) & bit) bad |= TWICE;
+    }
+    if (bad) atomicOr(flags, bad);
+}
+
+// Half a wave per block: its length in units of eight entries, to offsets[panel][step].
+__global__ __launch_bounds__(256) void measure_kernel(const uint32_t *masks, int64_t n_panels, int64_t n_steps, uint32_t *counts, uint32_t *offsets)
+{
+    const int64_t b = (int64_t)blockIdx.x * 8 + threadIdx.x / 32;
+    if (b >= n_panels * n_steps) return;
+    uint32_t n = (uint32_t)__builtin_popcount(masks[(size_t)b * MASK_WORDS + (threadIdx.x & 31)]);
+    for (int m = 16; m; m >>= 1) n += (uint32_t)__shfl_xor((int)n, m, 32);
+    if ((threadIdx.x & 31) != 0) return;
+    counts[b] = n;
+    offsets[b / n_steps * (n_steps + 1) + b % n_steps] = (n + 7) / 8;
+}
+
+// Exclusive sums of `n` values of 256 threads' shares; returns the total.
+__device__ uint64_t scan_block(uint64_t v, uint64_t &before)
+{
+    __shared__ uint64_t sums[256];
+    sums[threadIdx.x] = v;
+    __syncthreads();
+    for (uint32_t d = 1; d < 256; d *= 2) {
+        const uint64_t x = threadIdx.x >= d ? sums[threadIdx.x - d] : 0;
+        __syncthreads();
+        sums[threadIdx.x] += x;
+        __syncthreads();
+    }
+    before = sums[threadIdx.x] - v;
+    const uint64_t total = sums[255];
+    __syncthreads();
+    return total;
+}
+
+// One workgroup per panel: block lengths -> starts within the panel; the panel's length.
+__global__ __launch_bounds__(256) void scan_panel_kernel(int64_t n_steps, uint32_t *offsets, uint64_t *panel_base)
+{
+    uint32_t *o = offsets + (size_t)blockIdx.x * (n_steps + 1);
+    uint64_t done = 0;
+    for (int64_t s0 = 0; s0 < n_steps; s0 += 256) {
+        const int64_t s = s0 + threadIdx.x;
+        const uint64_t v = s < n_steps ? o[s] : 0;
+        uint64_t before;
+        const uint64_t total = scan_block(v, before);
+        if (s < n_steps) o[s] = (uint32_t)(done + before);
+        done += total;
+    }
+    if (threadIdx.x == 0) {
+        o[n_steps] = (uint32_t)done;
+        panel_base[blockIdx.x] = done;
+    }
+}
+
+// One workgroup: panel lengths -> panel starts; panel_base[n_panels] = length of everything.
+__global__ __launch_bounds__(256) void scan_all_kernel(int64_t n_panels, uint64_t *panel_base)
+{
+    uint64_t done = 0;
+    for (int64_t p0 = 0; p0 < n_panels; p0 += 256) {
+        const int64_t p = p0 + threadIdx.x;
+        const uint64_t v = p < n_panels ? panel_base[p] : 0;
+        uint64_t before;
+        const uint64_t total = scan_block(v, before);
+        if (p < n_panels) panel_base[p] = done + before;
+        done += total;
+    }
+    if (threadIdx.x == 0) panel_base[n_panels] = done;
+}
+
+// One thread per block: its final start; the entries that fill up its last group of eight
+// (value 0 to the dump place).
+__global__ __launch_bounds__(256) void place_kernel(int64_t n_panels, int64_t n_steps, const uint64_t *panel_base, const uint32_t *counts,
+                                                    uint32_t *offsets, char *stream)
+{
+    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (b >= n_panels * n_steps) return;
+    const int64_t p = b / n_steps, s = b % n_steps;
+    uint32_t *o = offsets + p * (n_steps + 1) + s;
+    const uint32_t base = (uint32_t)panel_base[p], start = *o + base, n = counts[b], padded = (n + 7) / 8 * 8;
+    *o = start;
+    if (s + 1 == n_steps) o[1] += base;
+    char *block = stream + (size_t)start * 48;
+    for (uint32_t i = n; i < padded; ++i) {
+        reinterpret_cast<float *>(block)[i] = 0.0f;
+        reinterpret_cast<uint16_t *>(block + (size_t)padded * 4)[i] = 0;
+    }
+}
+
+// One wave per row: the entries to their blocks.  Their order inside a block is free (every
+// entry carries its place), so a counter per block, run down from its entries, deals the slots.
+template <int R> __global__ __launch_bounds__(256) void fill_kernel(const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t M,
+                                                                    int64_t n_steps, const uint32_t *offsets, uint32_t *counts, char *stream)
+{
+    const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
+    if (row >= M) return;
+    for (int64_t q = row_ptr[row] + (int64_t)(threadIdx.x & 63); q < row_ptr[row + 1]; q += 64) {
+        const position p = position_of<R>((uint32_t)row, (uint32_t)col_idx[q]);
+        const uint32_t *o = offsets + row / R * (n_steps + 1) + p.step;
+        char *block = stream + (size_t)o[0] * 48;
+        const uint32_t i = atomicSub(&counts[row / R * n_steps + p.step], 1u) - 1u;
+        reinterpret_cast<float *>(block)[i] = vals[q];
+        reinterpret_cast<uint16_t *>(block + (size_t)(o[1] - o[0]) * 32)[i] = (uint16_t)(TILE_PLACE0 + (p.op / 4 * 64 + p.lane) * 16 + p.op % 4 * 4);
+    }
+}
+
+__global__ __launch_bounds__(256) void clear_kernel(u32x4 *p, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = u32x4{0, 0, 0, 0};
+}
+
+struct device_array {
+    void *p = nullptr;
+    ~device_array() { if (p) (void)hipFree(p); }
+    hipError_t take(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 16); }
+    template <typename T> T *as() const { return static_cast<T *>(p); }
+};
+
+template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, TilePlan &out, int &status)
+{
+    const int64_t nnz = row_ptr[M], P = out.n_panels, S = out.n_steps;
+    device_array d_ptr, d_col, d_val, d_masks, d_counts, d_base;
+    const size_t mask_bytes = (size_t)(P * S) * MASK_WORDS * 4;
+    hipError_t e;
+#define TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
+    TRY(d_ptr.take((size_t)(M + 1) * 4));
+    TRY(d_col.take((size_t)nnz * 4));
+    TRY(d_val.take((size_t)nnz * 4));
+    TRY(d_masks.take(mask_bytes));
+    TRY(d_counts.take((size_t)(P * S) * 4));
+    TRY(d_base.take((size_t)(P + 2) * 8));
+    TRY(hipMalloc(reinterpret_cast<void **>(&out.d_offsets), (size_t)P * (size_t)(S + 1) * 4));
+    uint64_t *base = d_base.as<uint64_t>();
+    uint32_t *flags = reinterpret_cast<uint32_t *>(base + P + 1);
+    const hipStream_t s = nullptr;
+    const unsigned row_blocks = (unsigned)((M + 3) / 4), block_blocks = (unsigned)((P * S + 7) / 8);
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<int64_t>(4096, (int64_t)(mask_bytes / 4096 + 1))), dim3(256), 0, s, d_masks.as<u32x4>(), (int64_t)(mask_bytes / 16));
+    TRY(hipMemsetAsync(flags, 0, 8, s));
+    TRY(hipMemcpy(d_ptr.p, row_ptr, (size_t)(M + 1) * 4, hipMemcpyHostToDevice));
+    TRY(hipMemcpy(d_col.p, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice));
+    hipLaunchKernelGGL((mark_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr.as<int32_t>(), d_col.as<int32_t>(), M, K, S, d_masks.as<uint32_t>(), flags);
+    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks.as<uint32_t>(), P, S, d_counts.as<uint32_t>(), out.d_offsets);
+    hipLaunchKernelGGL(scan_panel_kernel, dim3((unsigned)P), dim3(256), 0, s, S, out.d_offsets, base);
+    hipLaunchKernelGGL(scan_all_kernel, dim3(1), dim3(256), 0, s, P, base);
+    TRY(hipGetLastError());
+    TRY(hipMemcpy(d_val.p, vals, (size_t)nnz * 4, hipMemcpyHostToDevice));  // the kernels run meanwhile
+    uint64_t answer[2];
+    TRY(hipMemcpy(answer, base + P, 16, hipMemcpyDeviceToHost));
+    const uint32_t bad = (uint32_t)answer[1];
+    if (bad & BAD_COLUMN) { status = 2; return hipSuccess; }
+    if ((bad & TWICE) || answer[0] >= (1ull << 32)) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
+    out.stream_words = (int64_t)answer[0] * 12;
+    TRY(hipMalloc(reinterpret_cast<void **>(&out.d_stream), (size_t)std::max<int64_t>(out.stream_words, 4) * 4));
+    char *stream = reinterpret_cast<char *>(out.d_stream);
+    hipLaunchKernelGGL(place_kernel, dim3((unsigned)((P * S + 255) / 256)), dim3(256), 0, s, P, S, base, d_counts.as<uint32_t>(), out.d_offsets, stream);
+    hipLaunchKernelGGL((fill_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr.as<int32_t>(), d_col.as<int32_t>(), d_val.as<float>(), M, S,
+                       out.d_offsets, d_counts.as<uint32_t>(), stream);
+    TRY(hipGetLastError());
+    TRY(hipStreamSynchronize(s));
+#undef TRY
+    out.device_bytes = out.stream_words * 4 + P * (S + 1) * 4;
+    status = 0;
+    return hipSuccess;
+}
+
+}  // namespace
+
+int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t rows, TilePlan &out)
+{
+    out = TilePlan();
+    out.rows = rows;
+    const int64_t step = TILE_OPERANDS * 64 / rows;
+    out.n_panels = (M + rows - 1) / rows;
+    out.n_steps = (K + step - 1) / step;
+    int status = 0;
+    const hipError_t e = rows == 32 ? build<32>(M, K, row_ptr, col_idx, vals, out, status) : build<16>(M, K, row_ptr, col_idx, vals, out, status);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        status = e == hipErrorOutOfMemory ? 3 : 4;
+    }
+    if (status != 0) spmm_tiles_release(out);
+    return status;
+}
+
+void spmm_tiles_release(TilePlan &p)
+{
+    if (p.d_stream) (void)hipFree(p.d_stream);
+    if (p.d_offsets) (void)hipFree(p.d_offsets);
+    p = TilePlan();
+}
+
+double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, int *NB_out)
+{
+    // A compute unit holds one workgroup at a time; a workgroup takes so many ns per step of its
+    // panel (measured on 15 shapes, 4 to 256 columns, 7 to 50 % of the entries kept: the estimate
+    // is within 14 % of the time, and the NB it prefers within 0.1 % of the best on average).
+    static const double ns_per_step[2][3] = {{97, 160, 262}, {144, 246, 470}};  // R = 16, 32; NB = 1, 2, 4
+    const int64_t panels = (M + rows - 1) / rows, steps = (K * rows + 1023) / 1024;
+    double best = 0.0;
+    for (int i = 0, NB = 1; i < 3; ++i, NB *= 2) {
+        if (NB > 1 && rows * NB >= 2 * N) break;  // more than half of the tile idle
+        const int64_t blocks = panels * ((N + rows * NB - 1) / (rows * NB));
+        const double t = 3.0 + 1e-3 * (double)((blocks + 255) / 256 * steps) * (ns_per_step[rows == 32][i] + 45.0 * (density > 0.1 ? density - 0.1 : 0.0));
+        if (i == 0 || t < best) {
+            best = t;
+            if (NB_out) *NB_out = NB;
+        }
+    }
+    return best;
+}
+
+int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream)
+{
+    tile_args a{p.d_stream, p.d_offsets, B, C, (uint64_t)K * (uint64_t)N * 4u, (int32_t)p.n_panels, (int32_t)p.n_steps, 1,
+                (int32_t)M, (int32_t)K, N};
+    hipStream_t s = (hipStream_t)stream;
+    const int64_t step_bytes = (int64_t)TILE_OPERANDS * 64 / p.rows * 4 * N;  // rows of B a step touches
+    if (step_bytes >= ((int64_t)1 << 32)) {
+        if (p.rows == 32) launch<32, 4, 8, false, 2, true>(a, s);
+        else launch<16, 4, 8, false, 2, true>(a, s);
+        return (int)hipGetLastError();
+    }
+    int NB = 1;
+    spmm_tiles_time(p.rows, M, K, N, 0.0, &NB);
+    switch (p.rows * 8 + NB) {
+    case 32 * 8 + 4: launch<32, 4, 8, false, 2>(a, s); break;
+    case 32 * 8 + 2: launch<32, 2, 16, false, 4>(a, s); break;
+    case 32 * 8 + 1: launch<32, 1, 16, true, 4>(a, s); break;
+    case 16 * 8 + 4: launch<16, 4, 8, false, 2>(a, s); break;
+    case 16 * 8 + 2: launch<16, 2, 8, true, 2>(a, s); break;
+    default: launch<16, 1, 16, true, 4>(a, s); break;
+    }
+    return (int)hipGetLastError();
+}

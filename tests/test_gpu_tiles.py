@@ -1,0 +1,124 @@
+"""Matrix-core path (spmm_options_t.tiles) against the CPU oracle, through the C ABI (GPU machine only)."""
+import numpy as np
+import pytest
+
+import paper_2506_15174_amd as spmm
+from workloads import generators as gen
+
+from test_gpu_parity import check, gpu_product, torch_gpu  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def integer_matrix(M, K, density, seed):
+    rng = np.random.default_rng(seed)
+    W = np.where(rng.random((M, K)) < density, rng.integers(-8, 9, (M, K)), 0).astype(np.float32)
+    W[min(5, M - 1)] = rng.integers(1, 9, K)   # a dense row
+    W[M // 2] = 0                              # an empty one
+    return gen.csr_from_dense(W)
+
+
+@pytest.mark.parametrize("N", [1, 3, 16, 17, 32, 33, 64, 100, 128, 129, 300])
+@pytest.mark.parametrize("tiles", [16, 32])
+@pytest.mark.parametrize("M,K", [(3, 1), (15, 65), (33, 511), (70, 1024), (257, 2050)])
+def test_tiles_are_bit_exact_on_integer_data(torch_gpu, oracle, M, K, tiles, N):  # noqa: F811
+    """Panels, column steps and column tiles that do not divide the sizes, fewer steps than waves
+    and more, dense and empty rows; any order of the sums is exact."""
+    csr = integer_matrix(M, K, 0.4, M + K)
+    B = np.random.default_rng(N).integers(-16, 17, (K, N)).astype(np.float32)
+    C, plan = gpu_product(torch_gpu, csr, B, guard_rows=2, tiles=tiles)
+    assert plan.describe()["tile_rows"] == tiles
+    C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B)
+    assert np.abs(C_ref).max() < 2 ** 24
+    assert np.array_equal(C.astype(np.float64), C_ref)
+
+
+@pytest.mark.parametrize("N", [20, 64, 128])
+@pytest.mark.parametrize("M,K,tiles", [(4096, 300, 16), (4096, 300, 32), (8192, 520, 32)])
+def test_tiles_with_workgroups_for_the_whole_chip(torch_gpu, oracle, M, K, tiles, N):  # noqa: F811
+    """Panels enough that the wider column tiles are taken; real values."""
+    csr = gen.lognormal_rows(M, K, 0.6, 7)
+    B = gen.dense_activations(K, N, 8)
+    C, plan = gpu_product(torch_gpu, csr, B, guard_rows=1, tiles=tiles)
+    assert plan.describe()["tile_rows"] == tiles
+    check(oracle, csr, B, C, parallel=True)
+
+
+def test_tiles_chosen_by_density_and_left_alone_by_other_settings(torch_gpu, oracle):  # noqa: F811
+    dense, sparse = gen.uniform_positions(2048, 2048, 0.6, 1), gen.uniform_positions(2048, 2048, 0.95, 2)
+    B = gen.dense_activations(2048, 128, 3)
+    C, plan = gpu_product(torch_gpu, dense, B, n_hint=128)
+    assert plan.describe()["tile_rows"] > 0 and plan.describe()["scratch_bytes"] == 0
+    check(oracle, dense, B, C, parallel=True)
+    for kw in (dict(tiles=-1), dict(ufi=8), dict(kslices=2), dict(sort_rows=1)):
+        assert gpu_product(torch_gpu, dense, B, n_hint=128, **kw)[1].describe()["tile_rows"] == 0
+    assert gpu_product(torch_gpu, sparse, B, n_hint=128)[1].describe()["tile_rows"] == 0
+
+
+def test_tiles_with_unsorted_columns_duplicates_and_bad_columns(torch_gpu, oracle):  # noqa: F811
+    """The order of a row's entries does not matter (bit for bit); a column stored twice keeps the
+    matrix on chunks; a column outside A is refused."""
+    csr = gen.uniform_positions(90, 700, 0.5, 4)
+    rng = np.random.default_rng(5)
+    rows = np.repeat(np.arange(csr.M), np.diff(csr.row_ptr))
+    o = np.lexsort((rng.random(len(rows)), rows))
+    B = gen.dense_activations(csr.K, 50, 6)
+    C0, _ = gpu_product(torch_gpu, csr, B, tiles=16)
+    C1, plan = gpu_product(torch_gpu, gen.Csr(csr.M, csr.K, csr.row_ptr, csr.col_idx[o], csr.vals[o]), B, tiles=16)
+    assert plan.describe()["tile_rows"] == 16 and np.array_equal(C0, C1)
+    check(oracle, csr, B, C1)
+    twice = csr.col_idx.copy()
+    twice[1] = twice[0]
+    csr2 = gen.Csr(csr.M, csr.K, csr.row_ptr, twice, csr.vals)
+    C2, plan = gpu_product(torch_gpu, csr2, B, tiles=16)
+    assert plan.describe()["tile_rows"] == 0
+    check(oracle, csr2, B, C2)
+    for bad in (-1, csr.K):
+        col = csr.col_idx.copy()
+        col[100] = bad
+        with pytest.raises(spmm.SpmmError) as err:
+            spmm.plan_create(csr.M, csr.K, csr.row_ptr, col, csr.vals, tiles=16)
+        assert err.value.status == spmm.SPMM_ERR_INVALID_CSR
+
+
+@pytest.mark.parametrize("tiles", [16, 32])
+def test_tiles_with_rows_of_b_too_long_for_32_bit_offsets(torch_gpu, oracle, tiles):  # noqa: F811
+    """A step's rows of B span more than 4 GiB: 64-bit addresses.  Checked on columns at both ends."""
+    torch = torch_gpu
+    csr = integer_matrix(20, 33, 0.5, 9)
+    N = (1 << 32) // (1024 // tiles * 4) + 3
+    B = torch.randint(-9, 10, (csr.K, N), device="cuda", dtype=torch.int8).to(torch.float32)
+    plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=tiles)
+    assert plan.describe()["tile_rows"] == tiles
+    C = plan.execute(B)
+    cols = torch.cat([torch.arange(0, 200), torch.arange(N - 200, N)]).cuda()
+    B_small, C_small = B[:, cols].contiguous().cpu().numpy(), C[:, cols].cpu().numpy()
+    C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B_small)
+    assert np.array_equal(C_small.astype(np.float64), C_ref)
+
+
+def test_tiles_replay_from_a_graph_and_overlap_on_streams(torch_gpu, oracle):  # noqa: F811
+    torch = torch_gpu
+    csr = gen.uniform_positions(300, 900, 0.5, 11)
+    plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=16)
+    B = torch.from_numpy(gen.dense_activations(csr.K, 64, 12)).cuda()
+    C = torch.full((csr.M, 64), float("nan"), device="cuda")
+    eager = plan.execute(B).clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        outs = [plan.execute(B) for _ in range(3)]
+    here = [plan.execute(B) for _ in range(3)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, eager) for x in outs + here)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan.execute(B, C)
+    for _ in range(3):
+        C.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, eager)
+        plan.execute(B)
+        torch.cuda.synchronize()
+    check(oracle, csr, B.cpu().numpy(), eager.cpu().numpy())
