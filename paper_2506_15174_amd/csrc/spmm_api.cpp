@@ -206,7 +206,7 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
     }
     if (p->on_device) {
         // the arrays live on the device now: keep the descriptors (row groups, sizes), not the mirror
-        std::vector<uint32_t>().swap(p->host.stream);
+        raw_words().swap(p->host.stream);
         std::vector<uint32_t>().swap(p->host.hdr);
         std::vector<uint32_t>().swap(p->host.wins);
         std::vector<uint32_t>().swap(p->host.items);
@@ -423,19 +423,24 @@ spmm_status_t spmm_plan_get_array(const spmm_plan_t *plan, int32_t which, uint32
         if (n) std::memcpy(out, h.rowmap.data(), (size_t)n * 4);
         return SPMM_OK;
     }
-    const std::vector<uint32_t> *v = nullptr;
+    const uint32_t *words = nullptr;
+    size_t count = 0;
+    auto take = [&](const auto &v) {
+        words = v.data();
+        count = v.size();
+    };
     switch (which) {
-    case SPMM_ARRAY_HDR: v = &h.hdr; break;
-    case SPMM_ARRAY_STREAM: v = &h.stream; break;
-    case SPMM_ARRAY_WINS: v = &h.wins; break;
-    case SPMM_ARRAY_ITEMS: v = &h.items; break;
-    case SPMM_ARRAY_CROSS: v = &h.cross; break;
+    case SPMM_ARRAY_HDR: take(h.hdr); break;
+    case SPMM_ARRAY_STREAM: take(h.stream); break;
+    case SPMM_ARRAY_WINS: take(h.wins); break;
+    case SPMM_ARRAY_ITEMS: take(h.items); break;
+    case SPMM_ARRAY_CROSS: take(h.cross); break;
     default: return SPMM_ERR_INVALID_ARG;
     }
-    if (n_words) *n_words = (int64_t)v->size();
+    if (n_words) *n_words = (int64_t)count;
     if (!out) return SPMM_OK;
-    if (cap_words < (int64_t)v->size()) return SPMM_ERR_INVALID_ARG;
-    if (!v->empty()) std::memcpy(out, v->data(), v->size() * 4);
+    if (cap_words < (int64_t)count) return SPMM_ERR_INVALID_ARG;
+    if (count) std::memcpy(out, words, count * 4);
     return SPMM_OK;
 }
 

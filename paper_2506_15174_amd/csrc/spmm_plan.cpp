@@ -427,15 +427,37 @@ std::vector<Group> make_groups(const int32_t *row_ptr, int64_t M, int ufi, int64
     return groups;
 }
 
-// Threads the enumeration may use: one per 2 M entries, at most 16 and at most what
-// the machine has, unless the caller names a count.
+// Threads the inspector may use: one per 2^16 entries (about 2 ms of one thread's work, against
+// some 50 us to start a thread: 512 x 2048 at 80 % 6.6 -> 2.9 ms on four threads, 4096 x 4096 at
+// 90 % 106 -> 23 ms on eight), at most 16 and at most what the machine has, unless the caller
+// names a count.
 int worker_count(int64_t nnz, int32_t asked)
 {
     if (asked >= 1) return std::min(asked, 64);
-    int64_t n = std::min<int64_t>(16, std::max<int64_t>(1, nnz / (2 << 20)));
+    int64_t n = std::min<int64_t>(16, std::max<int64_t>(1, nnz >> 16));
     const unsigned hw = std::thread::hardware_concurrency();
     if (hw > 0) n = std::min<int64_t>(n, hw);
     return (int)n;
+}
+
+// Runs job(first row, last row, share) over `threads` contiguous shares of the rows with about
+// equally many entries each.  The jobs must not throw.
+template <typename F> void over_rows(const int32_t *row_ptr, int64_t M, int threads, F job)
+{
+    auto bound = [&](int t) -> int64_t {
+        if (t >= threads) return M;
+        return std::lower_bound(row_ptr, row_ptr + M, (int32_t)((int64_t)row_ptr[M] * t / threads)) - row_ptr;
+    };
+    std::vector<std::thread> others;
+    for (int t = 1; t < threads; ++t) {
+        try {
+            others.emplace_back([=, &job] { job(bound(t), bound(t + 1), t); });
+        } catch (const std::system_error &) {
+            job(bound(t), bound(t + 1), t);  // no thread to be had
+        }
+    }
+    job(bound(0), bound(1), 0);
+    for (std::thread &o : others) o.join();
 }
 
 // Cuts the groups (creation order) into at most `want` contiguous ranges of about
@@ -491,10 +513,18 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
         if (row_ptr[i + 1] < row_ptr[i]) return ST_INVALID_CSR;
     const int64_t nnz = row_ptr[M];
     if (nnz > 0 && (!col_idx || !vals)) return ST_INVALID_ARG;
-    for (int64_t p = 0; p < nnz && !opts.schedule_only; ++p)
-        if (col_idx[p] < 0 || (int64_t)col_idx[p] >= K) return ST_INVALID_CSR;
 
     try {
+        const int threads = worker_count(nnz, opts.threads);
+        if (!opts.schedule_only) {
+            std::vector<char> bad((size_t)threads, 0);
+            over_rows(row_ptr, M, threads, [&](int64_t r0, int64_t r1, int t) {
+                uint32_t worst = 0;  // a negative column is the largest of all
+                for (int64_t q = row_ptr[r0]; q < row_ptr[r1]; ++q) worst = std::max(worst, (uint32_t)col_idx[q]);
+                bad[(size_t)t] = row_ptr[r1] > row_ptr[r0] && (int64_t)worst >= K;
+            });
+            if (std::count(bad.begin(), bad.end(), 0) != (ptrdiff_t)bad.size()) return ST_INVALID_CSR;
+        }
         out = HostPlan();
         out.M = M;
         out.K = K;
@@ -522,13 +552,16 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
         out.plan_rows = MP;
         if (NS > 1) {
             // the longest row of a slice
-            max_row = 0;
-            int64_t in_slice[8];
-            for (int64_t i = 0; i < M; ++i) {
-                std::fill(in_slice, in_slice + NS, (int64_t)0);
-                for (int64_t q = row_ptr[i]; q < row_ptr[i + 1]; ++q) in_slice[(int64_t)col_idx[q] / KS] += 1;
-                max_row = std::max(max_row, *std::max_element(in_slice, in_slice + NS));
-            }
+            std::vector<int64_t> longest((size_t)threads, 0);
+            over_rows(row_ptr, M, threads, [&](int64_t r0, int64_t r1, int t) {
+                int64_t in_slice[8];
+                for (int64_t i = r0; i < r1; ++i) {
+                    std::fill(in_slice, in_slice + NS, (int64_t)0);
+                    for (int64_t q = row_ptr[i]; q < row_ptr[i + 1]; ++q) in_slice[(uint32_t)col_idx[q] / (uint32_t)KS] += 1;
+                    longest[(size_t)t] = std::max(longest[(size_t)t], *std::max_element(in_slice, in_slice + NS));
+                }
+            });
+            max_row = *std::max_element(longest.begin(), longest.end());
             // A slice's panels are lighter by the number of slices: where the tallest panel of
             // its longest rows is no longer the tail of the launch, no panel needs to be cut
             // across workgroups (the 16384 x 16384 matrix above, four slices, eight rows:
@@ -569,16 +602,22 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
         };
         if (sorted || NS > 1) {
             own_ptr.assign((size_t)MP + 1, 0);
-            for (int64_t i = 0; i < MS; ++i) {
-                const int64_t m = mrow(i);
-                if (m < 0) continue;
-                if (NS == 1) {
-                    own_ptr[(size_t)i + 1] = row_ptr[m + 1] - row_ptr[m];
-                } else {
-                    for (int64_t q = row_ptr[m]; q < row_ptr[m + 1]; ++q)
-                        own_ptr[(size_t)((int64_t)col_idx[q] / KS * MS + i) + 1] += 1;
-                }
+            std::vector<int32_t> place;  // of a matrix row in a slice
+            if (sorted) {
+                place.resize((size_t)M);
+                for (int64_t i = 0; i < M; ++i) place[row_order[(size_t)i]] = (int32_t)i;
             }
+            over_rows(row_ptr, M, threads, [&](int64_t r0, int64_t r1, int) {
+                for (int64_t m = r0; m < r1; ++m) {
+                    const int64_t i = sorted ? place[(size_t)m] : m;
+                    if (NS == 1) {
+                        own_ptr[(size_t)i + 1] = row_ptr[m + 1] - row_ptr[m];
+                    } else {
+                        for (int64_t q = row_ptr[m]; q < row_ptr[m + 1]; ++q)
+                            own_ptr[(size_t)((int64_t)((uint32_t)col_idx[q] / (uint32_t)KS) * MS + i) + 1] += 1;
+                    }
+                }
+            });
             for (int64_t i = 0; i < MP; ++i) own_ptr[(size_t)i + 1] += own_ptr[(size_t)i];
             if (sorted) {
                 out.rowmap.resize((size_t)MP);
@@ -756,7 +795,7 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
                 gi = g_last + 1;
             }
         };
-        std::vector<int64_t> cuts = opts.schedule_only ? std::vector<int64_t>{0, 0} : range_cuts(groups, worker_count(nnz, opts.threads));
+        std::vector<int64_t> cuts = opts.schedule_only ? std::vector<int64_t>{0, 0} : range_cuts(groups, threads);
         const size_t n_ranges = cuts.size() - 1;
         std::vector<Emitter> parts(n_ranges);
         for (size_t t = 0; t < n_ranges; ++t) {
@@ -1048,9 +1087,10 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
         }
         out.wins.push_back(0u);  // look-ahead slot
         // the windows' words, contiguous runs of placed groups per thread
-        out.stream.resize((size_t)stream_at + STREAM_TAIL_PAD, 0u);
+        out.stream.resize((size_t)stream_at + STREAM_TAIL_PAD);
+        std::fill(out.stream.end() - STREAM_TAIL_PAD, out.stream.end(), 0u);
         {
-            const int want = worker_count(nnz, opts.threads);
+            const int want = opts.schedule_only ? 1 : threads;
             const size_t n_placed = placed.size();
             std::vector<size_t> from{0};
             for (int t = 1; t < want; ++t) {

@@ -4,7 +4,17 @@
 #define SPMM_PLAN_H
 
 #include <stdint.h>
+#include <memory>
+#include <new>
 #include <vector>
+
+// Words whose growth leaves them as they are (every one is written before it is read).
+template <typename T> struct leave_as_is : std::allocator<T> {
+    template <typename U> struct rebind { typedef leave_as_is<U> other; };
+    template <typename U> void construct(U *) noexcept {}
+    template <typename U, typename A> void construct(U *p, A &&a) { ::new ((void *)p) U(static_cast<A &&>(a)); }
+};
+typedef std::vector<uint32_t, leave_as_is<uint32_t>> raw_words;
 
 struct HostPlan {
     int64_t M = 0, K = 0, nnz = 0;
@@ -20,7 +30,8 @@ struct HostPlan {
     int64_t n_blocks = 0;      // workgroups of one launch
     // Chunk headers, chunk records and staging windows (already padded for the
     // kernels' look-ahead), launch order.
-    std::vector<uint32_t> hdr, stream, wins;
+    std::vector<uint32_t> hdr, wins;
+    raw_words stream;
     int64_t n_chunks = 0;      // real chunks (without the padding)
     int64_t n_enum = 0;        // enumerated columns (real column slots)
     int64_t n_split = 0;       // groups that are pieces of split panels
