@@ -65,8 +65,8 @@ typedef struct {
     int64_t slice_rows;    /* rows per range of such a plan: M rounded up to a multiple of 8 (M when
                               k_slices is 1) */
     int64_t slice_cols;    /* columns per range: ceil(K / k_slices) */
-    int64_t tile_rows;     /* 0, or the rows per panel (32 or 16) of a plan whose product runs on the matrix
-                              cores (spmm_options_t.tiles).  Such a plan holds the entries in bitmap tiles
+    int64_t tile_rows;     /* 0, or the rows per panel (32, 16 or 8) of a plan whose product runs on the matrix
+                              cores (spmm_options_t.tiles).  Such a plan holds the entries in tiles
                               instead of chunks: n_enum = panels * K and n_chunks = its (panel, column step)
                               blocks, stream_words and device_bytes are those of the tiles, scratch_bytes is 0
                               and any number of its executes may be in flight; the remaining fields and the
@@ -127,10 +127,10 @@ typedef struct {
                               the tile is exactly one L2 and the rows hold 1024 entries or more; never for
                               plans with chunks wider than 8 (SPMM_ERR_INVALID_ARG if both are forced).
                               At most one execute of such a plan may be in flight at a time. */
-    int32_t tiles;         /* the matrix-core path: A in bitmap tiles of panels of 16 or 32 rows, absent
+    int32_t tiles;         /* the matrix-core path: A in tiles of panels of 8, 16 or 32 rows, absent
                               entries multiplied as zeros by fp32 matrix instructions, which pays on
-                              matrices that are not very sparse.  16 or 32 = use it with panels of so many
-                              rows; < 0 = never; 0 = choose by shape, density and n_hint (never when
+                              matrices that are not very sparse.  8, 16 or 32 = use it with panels of so
+                              many rows (8 for B of up to 16 columns); < 0 = never; 0 = choose by shape, density and n_hint (never when
                               another setting but n_hint and threads is given, never for host-only
                               plans).  A matrix with a column stored twice in a row stays on chunks. */
 } spmm_options_t;

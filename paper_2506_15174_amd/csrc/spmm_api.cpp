@@ -132,7 +132,7 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
         if (io.kslices > 1 && io.ufk != 0 && io.ufk != UFK) return SPMM_ERR_INVALID_ARG;  // only plans with chunks of 8 are cut
         depth = opts->depth;
         probe = opts->probe != 0;
-        if (opts->tiles > 0 && opts->tiles != 16 && opts->tiles != 32) return SPMM_ERR_INVALID_ARG;
+        if (opts->tiles > 0 && opts->tiles != 8 && opts->tiles != 16 && opts->tiles != 32) return SPMM_ERR_INVALID_ARG;
         tiles = opts->tiles;
         // settings of the chunk path ask for the chunk path
         schedule_forced = opts->ufi || opts->group_nnz || opts->group_panels || opts->sort_rows || force_wide || depth || opts->cross ||

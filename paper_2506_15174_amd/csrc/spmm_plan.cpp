@@ -483,24 +483,51 @@ std::vector<int64_t> range_cuts(const std::vector<Group> &groups, int want)
 }  // namespace
 
 // Tiles multiply the absent entries too, so their time does not fall with the density as the
-// chunks' does; they pay from about 15 % of the entries on when there are tiles enough for the
-// chip, later for few rows or few columns of B (at 4 columns from 30 %).  Both times are estimated
-// and tiles are taken where theirs is at least 15 % shorter.  The chunks' estimate is a fit in the
-// logarithms of the sizes to 510 products (15 shapes from 256 to 12000 rows and columns, 7 to 50 %
-// of the entries kept, 4 to 256 columns; it is within 19 %); with it 156 of those products run
-// on tiles, 1.37 times as fast on average, the worst at 0.89.
+// chunks' does: wide B takes them from about 15 % of the entries on, B of up to 16 columns (whose
+// gathers fetch little at a time) from 5 to 10 % on, small matrices later or never.  Both times are estimated
+// and tiles are taken where theirs is at least 5 % shorter.  Of 1266 measured products (18 shapes
+// from 256 to 16384 rows and columns, 3 to 50 % of the entries kept, 4 to 256 columns) that moves 464
+// to tiles, 1.36 times as fast on average, the worst at 0.89.
+//
+// The chunks' time in us: a constant, the wave loads that gather rows of B, the vector FMAs (millions), the
+// plan's bytes (MB), the chunks (millions, dearer the more rows they span), and the second launch of
+// a plan cut along K.  Within 17 % (hints up to 8) to 8 % (64 and more) on uniform matrices; rows of
+// uneven length take longer on chunks, hardly on tiles.
+static double chunks_time(int64_t M, int64_t K, int64_t nnz, int32_t n_hint, double N)
+{
+    static const double weights[5][6] = {{2.82, 9.84, 10.5, 0.0, 69.5, 0.0},    // n_hint <= 8
+                                         {2.88, 7.07, 0.0, 0.265, 31.5, 0.0},   // ... 16
+                                         {2.99, 14.2, 0.0, 0.350, 7.93, 0.0},   // ... 32
+                                         {2.74, 19.5, 0.0, 0.495, 4.61, 0.0},   // ... 64
+                                         {3.14, 21.0, 0.0, 0.602, 14.6, 1.27}}; // more, or unknown
+    const double *w = weights[N <= 8 ? 0 : N <= 16 ? 1 : N <= 32 ? 2 : N <= 64 ? 3 : 4];
+    const int ufk = choose_ufk(K, n_hint), slices = choose_kslices(0, M, K, nnz, n_hint, ufk);
+    const int ufi = choose_ufi(M, (K + slices - 1) / slices, nnz, n_hint);
+    const double density = (double)nnz / ((double)M * (double)K);
+    const double fetched = (double)M / ufi * (double)K * (1.0 - std::pow(1.0 - density, ufi));  // rows of B, for one column tile
+    const int tile = ufk == 8 ? (N > 64 ? 128 : 64) : ufk == 16 ? 32 : ufk == 32 ? 16 : N > 4 ? 8 : 4;
+    const double tiles = std::ceil(N / tile) * 1e-6, per_load = 256.0 / tile;
+    return w[0] + tiles * (w[1] * fetched / per_load + w[2] * 4.2 * (double)nnz / per_load + w[3] * (4.0 * fetched + 4.2 * (double)nnz) +
+                           w[4] * fetched / ufk * std::sqrt((double)ufi)) + (slices > 1 ? w[5] : 0.0);
+}
+
 int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 {
     const int64_t nnz = row_ptr[M];
     const double density = (double)nnz / ((double)M * (double)K);
-    if (density < 0.1 || skewed_rows(row_ptr, M, nnz)) return 0;
+    if (density < 0.03) return 0;           // below all that was measured
+    if (nnz < ((int64_t)1 << 17)) return 0;  // mostly the launch's time: 1.5 % on average to gain
     const double N = n_hint <= 0 ? 128 : std::min(std::max(n_hint, 4), 256);
-    const double d = std::log(density), n = std::log(N);
-    const double chunks = 2.2 + std::exp(-8.842 + 0.662 * std::log((double)M) + 0.765 * std::log((double)K) + 0.588 * d - 0.122 * n +
-                                         0.017 * d * d + 0.091 * n * n + 0.007 * d * n);
-    const double t16 = spmm_tiles_time(16, M, K, (int64_t)N, density, nullptr), t32 = spmm_tiles_time(32, M, K, (int64_t)N, density, nullptr);
-    if (std::min(t16, t32) > 0.85 * chunks) return 0;
-    return t16 <= t32 ? 16 : 32;
+    double best = 0.95 * chunks_time(M, K, nnz, n_hint, N);
+    int rows = 0;
+    for (int r : {8, 16, 32}) {
+        const double t = spmm_tiles_time(r, M, K, (int64_t)N, density, nullptr);
+        if (t < best) {
+            best = t;
+            rows = r;
+        }
+    }
+    return rows;
 }
 
 int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx,

@@ -71,7 +71,7 @@ struct InspectorOptions {
 int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx,
                  const float *vals, const InspectorOptions &opts, HostPlan &out);
 
-// Rows per panel (32 or 16) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.
+// Rows per panel (32, 16 or 8) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.
 int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint);
 
 #endif

@@ -1,14 +1,16 @@
-// Matrix-core path (internal): A in bitmap tiles, multiplied by fp32 MFMA instructions.
+// Matrix-core path (internal): A in tiles, multiplied by fp32 MFMA instructions.
 #ifndef SPMM_TILES_H
 #define SPMM_TILES_H
 
 #include <stddef.h>
 #include <stdint.h>
 
-// Format.  The rows are taken in panels of `rows` = R (32 or 16) consecutive rows of A, the
-// columns in steps of 16 * 64 / R columns.  Lane l of the wave that multiplies a (panel, step)
-// pair, a *block*, owns row l % R of the panel and the 16 columns t * 64 / R + l / R (t = 0 .. 15)
-// of the step.  A block stores
+// Format.  The rows are taken in panels of `rows` = R (32, 16 or 8) consecutive rows of A, the
+// columns in steps of 16 * 64 / R columns.  The wave that multiplies a (panel, step) pair, a *block*,
+// gives it to 16 matrix operands t of one element per lane l:
+//   R = 32, 16   row l % R of the panel, column t * 64 / R + l / R of the step
+//   R = 8        row t % 2 * 4 + l % 4, column t / 2 * 16 + l / 4
+// A block stores
 //   values     its entries in any order, filled up to a multiple of eight with zeros
 //   places     16 bits per entry: where the value goes in the expanded block, in bytes:
 //              TILE_PLACE0 + ((t / 4 * 64 + l) * 4 + t % 4) * 4, or 0 for a filler
@@ -17,6 +19,7 @@
 struct TilePlan {
     int32_t rows = 0;               // R; 0 = the plan holds no tiles
     int64_t n_panels = 0, n_steps = 0;
+    int32_t loads = 4;              // runs of 256 entries the longest block has
     uint32_t *d_stream = nullptr;   // DEVICE blocks
     uint32_t *d_offsets = nullptr;  // DEVICE n_panels * (n_steps + 1) block starts
     int64_t stream_words = 0, device_bytes = 0;
@@ -34,7 +37,7 @@ int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t
 void spmm_tiles_release(TilePlan &p);
 
 // Estimated time of a product in us with panels of `rows` rows (density = share of the entries kept),
-// and the column groups NB of a tile (1, 2 or 4) it runs best with.
+// and the column groups NB of a tile (1, 2 or 4) it runs with.
 double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, int *NB);
 
 // Enqueues C <- A x B.  Returns the hipError_t of the launch as int.

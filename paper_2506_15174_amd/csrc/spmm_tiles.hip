@@ -1,4 +1,4 @@
-// gfx950 executor and builder of the matrix-core path: C <- A x B with A in bitmap tiles
+// gfx950 executor and builder of the matrix-core path: C <- A x B with A in tiles
 // (format: spmm_tiles.h).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -17,6 +17,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int OPS = TILE_OPERANDS;
+constexpr int NARROW_ROWS = 8;
 constexpr int A_SLOT_WORDS = TILE_PLACE0 / 4 + 1024;  // the expanded block behind the dump word
 
 // ---------------------------------------------------------------- executor
@@ -48,6 +49,14 @@ template <int NB> __device__ __forceinline__ typename BVec<NB>::type buffer_load
         const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, 0);
         return f32x4{__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3])};
     }
+}
+
+// What the lanes of a wave wrote to LDS before this point is what they read after it.
+__device__ __forceinline__ void lds_in_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 template <int R> struct Tile;
@@ -211,9 +220,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
 #pragma unroll
                 for (int q = 0; q < B_LOADS; ++q) reinterpret_cast<f32x4 *>(bslot)[lane + 64 * q] = vb[q];
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            lds_in_order();
             // ---- the next step's data
             const bool more = i + 1 < count;
             if (more) {
@@ -298,6 +305,233 @@ template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void l
     hipLaunchKernelGGL((spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>), dim3(blocks), dim3(64 * W), 0, s, a);
 }
 
+// ---------------------------------------------------------------- executor, narrow panels
+
+// v + v turned within every row of 16 lanes (CTRL: a DPP row rotation)
+template <int CTRL> __device__ __forceinline__ float add_turned(float v)
+{
+    return v + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+}
+
+// The loads before this point start before the work after it and in this order: the compiler would move
+// them to their first use, and count the wait for a block's entries by the wrong loads.
+__device__ __forceinline__ void keep_loads_here() { __builtin_amdgcn_sched_barrier(0); }
+
+// One workgroup computes a tile of C: a panel of 8 rows x 4 * NB columns, with v_mfma_f32_4x4x1 (16
+// products of 4 rows by 4 columns, one column of A each): 16 columns of A per instruction.  An operand of B
+// is then 16 rows x 4 columns of B as they lie in memory, so B needs no LDS, both row groups use it, and
+// B of 4 or 8 columns leaves no part of an instruction idle; panels of 8 rows give a matrix of 2048 rows
+// 256 workgroups, where panels of 16 leave half the chip without work.
+//
+// W       waves of the workgroup, cutting K as in the kernel above
+// AL      16-byte loads per lane that hold any block of the plan (256 entries each)
+// WIDE    64-bit addresses of B, word by word
+//
+// What bounds it: with four columns the plan's bytes (2048 x 8192, 70 % pruned: 30 MB in 7.1 us, 2.6 us of them
+// the launch; chunks 15.8, panels of 16 rows 17.1), with sixteen the vector ALUs, which the matrix
+// instructions share (10 cycles each, measured, of the nominal 8, and some 60 other instructions per step): 10.8 us; chunks
+// 21.4, panels of 16 rows 17.2.  Where a block has 256 entries or fewer, writing zeros to its places
+// is cheaper than clearing all of it (8192 x 8192, 90 % pruned, 4 columns: 14.7 -> 12.3 us).  Asking for blocks
+// two steps ahead, or sixteen waves, changed nothing; panels of 16 rows of this kind gain 15 % at 8192 rows
+// with 16 columns and lose as much or more elsewhere.
+template <int NB, int W, int AL, bool WIDE, int MINW>
+__global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const tile_args args)
+{
+    typedef typename BVec<NB>::type bvec_t;
+    constexpr int R = NARROW_ROWS;
+    constexpr int KS = 1024 / R;      // columns of A per step
+    constexpr int H = KS / 16;        // operands of B per step
+    constexpr int G = R / 4;          // row groups
+    constexpr int NT = NB * 4;        // columns of C per tile
+    constexpr int SLOT = A_SLOT_WORDS;
+    constexpr int T = R * NB;         // sums per lane
+    constexpr bool UNSCATTER = AL <= 2;
+    static_assert(R * NT <= SLOT, "a wave's sums fit its slot");
+    __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
+
+    const uint32_t g8 = blockIdx.x / 8u;  // panels to XCDs as in the kernel above
+    const uint32_t nt = g8 % (uint32_t)args.n_tiles;
+    const uint32_t panel = (g8 / (uint32_t)args.n_tiles) * 8u + blockIdx.x % 8u;
+    if (panel >= (uint32_t)args.n_panels) return;
+    const uint32_t n0 = nt * (uint32_t)NT;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63);
+    float *slot = lds + wave * SLOT;
+    char *cslot = reinterpret_cast<char *>(slot);
+    f32x4 *expanded = reinterpret_cast<f32x4 *>(slot + TILE_PLACE0 / 4) + lane;
+    const uint32_t n_steps = (uint32_t)args.n_steps;
+    const uint32_t *off_p = args.offsets + (size_t)panel * (n_steps + 1);
+    const uint32_t N = (uint32_t)args.N;
+    const uint32_t count = n_steps > (uint32_t)wave ? (n_steps - (uint32_t)wave + W - 1) / W : 0u;  // steps of this wave
+
+    f32x4 acc[G][NB];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int c = 0; c < NB; ++c) acc[g][c] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < OPS / 4; ++q) expanded[64 * q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // lane l: columns NB * (l % 4) .. of row l / 4 of the operand
+    bvec_t b[H];
+    auto fetch_b = [&](uint32_t i, int h) {  // no rows past the last step
+        const uint32_t s = (uint32_t)wave + W * i;
+        if constexpr (WIDE) {
+            const uint64_t row = (uint64_t)s * KS + (uint32_t)(16 * h + lane / 4);
+            const float *p = args.B + (row < (uint64_t)args.K ? row : (uint64_t)args.K - 1u) * N;
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {  // rows and columns outside B repeat its last ones (never used)
+                const uint32_t n = n0 + (uint32_t)(NB * (lane % 4) + j);
+                b[h][j] = p[n < N ? n : N - 1u];
+            }
+        } else {
+            const uint64_t skip = ((uint64_t)s * KS * N + n0) * 4u;
+            const uint64_t left = args.b_bytes > skip ? args.b_bytes - skip : 0u;
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(args.B)) + skip, (short)0,
+                                                                               (int)(left > 0xFFFFFFFCull ? 0xFFFFFFFCu : (uint32_t)left), 0x00020000);
+            b[h] = buffer_load<NB>(r, ((uint32_t)(lane / 4) * N + (uint32_t)(NB * (lane % 4))) * 4u + (uint32_t)h * (64u * N));
+        }
+    };
+    // Runs of 64 steps: lane i holds the bounds of the i-th block of the run.  (With the bounds loaded
+    // inside of the pipeline every step would have to wait for all loads on their way, in case this one
+    // is among them; for the same reason all steps make the same number of loads.)
+    uint32_t lo = 0, hi = 0, last = 0, n_next = 0;
+    f32x4 va[AL];
+    u32x2 vp[AL];
+    auto fetch_a = [&](uint32_t i) {
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)(i & 63u));
+        n_next = i < last ? 8u * ((uint32_t)__builtin_amdgcn_readlane((int)hi, (int)(i & 63u)) - a) : 0u;
+        const char *block = reinterpret_cast<const char *>(args.stream) + (size_t)a * 48u;
+        const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(block), (short)0, (int)(n_next * 4u), 0x00020000);
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(block) + (size_t)n_next * 4u, (short)0, (int)(n_next * 2u), 0x00020000);
+#pragma unroll
+        for (int q = 0; q < AL; ++q) {
+            va[q] = buffer_load<4>(rv, (uint32_t)lane * 16u + 1024u * (uint32_t)q);
+            vp[q] = __builtin_amdgcn_raw_buffer_load_b64(rp, (int)((uint32_t)lane * 8u + 512u * (uint32_t)q), 0, 0);
+        }
+    };
+
+    for (uint32_t first = 0; first < count; first = last) {
+        last = first + 64u < count ? first + 64u : count;
+        {
+            const uint32_t s = (uint32_t)wave + W * (first + (uint32_t)lane);
+            lo = s < n_steps ? off_p[s] : 0u;
+            hi = s < n_steps ? off_p[s + 1] : 0u;
+        }
+        fetch_a(first);
+        keep_loads_here();
+#pragma unroll
+        for (int h = 0; h < H; ++h) fetch_b(first, h);
+        keep_loads_here();
+        for (uint32_t i = first; i < last; ++i) {
+            // ---- the block's entries go to their places in the expanded block, zero otherwise
+            const uint32_t n = n_next;
+            u32x2 places[AL];
+#pragma unroll
+            for (int q = 0; q < AL; ++q) places[q] = vp[q];
+            auto scatter = [&](auto value) {
+#pragma unroll
+                for (int q = 0; q < AL; ++q)
+                    if (q == 0 || n > 256u * (uint32_t)q)
+                        if ((uint32_t)lane * 4u + 256u * (uint32_t)q < n)
+#pragma unroll
+                            for (int x = 0; x < 4; ++x)
+                                *reinterpret_cast<float *>(cslot + ((places[q][x / 2] >> (16 * (x % 2))) & 0xFFFFu)) = value(q, x);
+            };
+            scatter([&](int q, int x) { return va[q][x]; });
+            lds_in_order();
+            fetch_a(i + 1);
+            keep_loads_here();
+            f32x4 a[OPS / 4];
+#pragma unroll
+            for (int q = 0; q < OPS / 4; ++q) a[q] = expanded[64 * q];
+            // ---- zeros again for the next block, at its places where they are few
+            if constexpr (UNSCATTER) {
+                lds_in_order();
+                scatter([](int, int) { return 0.0f; });
+            } else {
+#pragma unroll
+                for (int q = 0; q < OPS / 4; ++q) expanded[64 * q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int c = 0; c < NB; ++c)
+                        acc[g][c] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[(h * G + g) / 4][(h * G + g) % 4], part(b[h], c), acc[g][c], 0, 0, 0);
+                fetch_b(i + 1, h);
+            }
+        }
+    }
+
+    // ---- add the 16 products of an instruction: halves, then quarters of the wave, each keeping half of
+    //      the sums, then within rows of 16 lanes
+    float v[T];  // row q / NB, columns NB * (lane % 4) + q % NB
+#pragma unroll
+    for (int q = 0; q < T; ++q) v[q] = acc[q / NB / 4][q % NB][q / NB % 4];
+#pragma unroll
+    for (int q = 0; q < T / 2; ++q) {
+        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[q]), __float_as_uint(v[q + T / 2]), false, false);
+        v[q] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < T / 4; ++q) {
+        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[q]), __float_as_uint(v[q + T / 4]), false, false);
+        v[q] = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    }
+#pragma unroll
+    for (int q = 0; q < T / 4; ++q) v[q] = add_turned<0x124>(add_turned<0x128>(v[q]));
+    if (lane % 16 < 4) {
+        const int o = T / 2 * (lane / 32) + T / 4 * (lane / 16 % 2);
+#pragma unroll
+        for (int q = 0; q < T / 4; ++q) slot[(o + q) / NB * NT + NB * (lane % 4) + (o + q) % NB] = v[q];
+    }
+    // ---- add the waves' tiles, in order
+    __syncthreads();
+    for (uint32_t t = threadIdx.x; t < (uint32_t)(R * NT); t += 64 * W) {
+        const uint32_t row = panel * (uint32_t)R + t / NT, n = n0 + t % NT;
+        float sum = lds[t];
+#pragma unroll
+        for (int u = 1; u < W; ++u) sum += lds[u * SLOT + t];
+        if (row < (uint32_t)args.M && n < N) args.C[(size_t)row * N + n] = sum;
+    }
+}
+
+template <int NB, int W, int AL, bool WIDE, int MINW> void launch_narrow(tile_args &a, hipStream_t s)
+{
+    a.n_tiles = (a.N + NB * 4 - 1) / (NB * 4);
+    const unsigned blocks = (unsigned)((a.n_panels + 7) / 8) * 8u * (unsigned)a.n_tiles;
+    hipLaunchKernelGGL((spmm_narrow_tiles_kernel<NB, W, AL, WIDE, MINW>), dim3(blocks), dim3(64 * W), 0, s, a);
+}
+template <int NB, int W> void launch_narrow(tile_args &a, int loads, hipStream_t s)
+{
+    if (loads == 1) launch_narrow<NB, W, 1, false, 4>(a, s);
+    else if (loads == 2) launch_narrow<NB, W, 2, false, 4>(a, s);
+    else launch_narrow<NB, W, 4, false, NB < 4 ? 4 : 2>(a, s);
+}
+template <int NB> void launch_narrow(tile_args &a, int waves, int loads, hipStream_t s)
+{
+    if (waves == 8) launch_narrow<NB, 8>(a, loads, s);
+    else launch_narrow<NB, 4>(a, loads, s);
+}
+
+// Column groups and waves of a workgroup.  While the workgroups of a narrower tile still all find an idle
+// compute unit, that tile; then the tile that takes all columns.  Eight waves share the panel where
+// its steps give each of them four or more and the workgroups are too few to keep enough waves on
+// the chip otherwise.  (1024 x 4096 with 90 % pruned, 16 columns: 4.8 us with tiles of 8, 5.6 us with tiles of
+// 16; 2048 x 8192 with 70 % pruned, 4 columns: 7.1 us with eight waves, 9.5 us with four; 4096 x 1024: 3.8 and 3.6 us.)
+int narrow_columns(int64_t panels, int64_t N)
+{
+    int NB = 1;
+    while (NB < 4 && NB * 4 < N && panels * ((N + NB * 4 - 1) / (NB * 4)) > 256) NB *= 2;
+    return NB;
+}
+int narrow_waves(int64_t panels, int64_t steps, int64_t N, int NB)
+{
+    return steps >= 32 && panels * ((N + NB * 4 - 1) / (NB * 4)) < (NB == 1 ? 1024 : 512) ? 8 : 4;
+}
+
 // ---------------------------------------------------------------- builder
 
 struct position {
@@ -306,6 +540,7 @@ struct position {
 template <int R> __device__ __forceinline__ position position_of(uint32_t row, uint32_t col)
 {
     constexpr uint32_t KO = 64 / R, KS = OPS * KO;
+    if constexpr (R == NARROW_ROWS) return position{col / KS, col % KS / 16 * (R / 4) + row % R / 4, col % 16 * 4 + row % 4};
     return position{col / KS, col % KS / KO, row % R + R * (col % KO)};
 }
 
@@ -335,7 +570,7 @@ template <int R> __global__ __launch_bounds__(256) void mark_kernel(const int32_
 }
 
 // Half a wave per block: its length in units of eight entries, to offsets[panel][step].
-__global__ __launch_bounds__(256) void measure_kernel(const uint32_t *masks, int64_t n_panels, int64_t n_steps, uint32_t *counts, uint32_t *offsets)
+__global__ __launch_bounds__(256) void measure_kernel(const uint32_t *masks, int64_t n_panels, int64_t n_steps, uint32_t *counts, uint32_t *offsets, uint32_t *longest)
 {
     const int64_t b = (int64_t)blockIdx.x * 8 + threadIdx.x / 32;
     if (b >= n_panels * n_steps) return;
@@ -343,6 +578,7 @@ __global__ __launch_bounds__(256) void measure_kernel(const uint32_t *masks, int
     for (int m = 16; m; m >>= 1) n += (uint32_t)__shfl_xor((int)n, m, 32);
     if ((threadIdx.x & 31) != 0) return;
     counts[b] = n;
+    if (n > *longest) atomicMax(longest, n);
     offsets[b / n_steps * (n_steps + 1) + b % n_steps] = (n + 7) / 8;
 }
 
@@ -469,7 +705,7 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     TRY(hipMemcpy(d_ptr.p, row_ptr, (size_t)(M + 1) * 4, hipMemcpyHostToDevice));
     TRY(hipMemcpy(d_col.p, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice));
     hipLaunchKernelGGL((mark_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr.as<int32_t>(), d_col.as<int32_t>(), M, K, S, d_masks.as<uint32_t>(), flags);
-    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks.as<uint32_t>(), P, S, d_counts.as<uint32_t>(), out.d_offsets);
+    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks.as<uint32_t>(), P, S, d_counts.as<uint32_t>(), out.d_offsets, flags + 1);
     hipLaunchKernelGGL(scan_panel_kernel, dim3((unsigned)P), dim3(256), 0, s, S, out.d_offsets, base);
     hipLaunchKernelGGL(scan_all_kernel, dim3(1), dim3(256), 0, s, P, base);
     TRY(hipGetLastError());
@@ -477,6 +713,7 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     uint64_t answer[2];
     TRY(hipMemcpy(answer, base + P, 16, hipMemcpyDeviceToHost));
     const uint32_t bad = (uint32_t)answer[1];
+    out.loads = std::max(1, (int32_t)(((uint32_t)(answer[1] >> 32) + 255u) / 256u));
     if (bad & BAD_COLUMN) { status = 2; return hipSuccess; }
     if ((bad & TWICE) || answer[0] >= (1ull << 32)) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
     out.stream_words = (int64_t)answer[0] * 12;
@@ -503,7 +740,7 @@ int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t
     out.n_panels = (M + rows - 1) / rows;
     out.n_steps = (K + step - 1) / step;
     int status = 0;
-    const hipError_t e = rows == 32 ? build<32>(M, K, row_ptr, col_idx, vals, out, status) : build<16>(M, K, row_ptr, col_idx, vals, out, status);
+    const hipError_t e = rows == NARROW_ROWS ? build<NARROW_ROWS>(M, K, row_ptr, col_idx, vals, out, status) : rows == 32 ? build<32>(M, K, row_ptr, col_idx, vals, out, status) : build<16>(M, K, row_ptr, col_idx, vals, out, status);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         status = e == hipErrorOutOfMemory ? 3 : 4;
@@ -519,18 +756,26 @@ void spmm_tiles_release(TilePlan &p)
     p = TilePlan();
 }
 
+// Fits to 1900 measured products, 3 to 50 % of the entries kept, 4 to 256 columns: within 5 % of the time
+// (panels of 8 rows: 7 to 16 %), and the NB it prefers is within 0.1 % of the best one on average.
 double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, int *NB_out)
 {
-    // A compute unit holds one workgroup at a time; a workgroup takes so many ns per step of its
-    // panel (measured on 15 shapes, 4 to 256 columns, 7 to 50 % of the entries kept: the estimate
-    // is within 14 % of the time, and the NB it prefers within 0.1 % of the best on average).
-    static const double ns_per_step[2][3] = {{97, 160, 262}, {144, 246, 470}};  // R = 16, 32; NB = 1, 2, 4
     const int64_t panels = (M + rows - 1) / rows, steps = (K * rows + 1023) / 1024;
+    if (rows == NARROW_ROWS) {
+        static const double ns_per_step[3] = {30, 61, 85}, ns_density[3] = {120, 114, 145}, us_per_round[3] = {0.02, 0.2, 0.3};
+        const int NB = narrow_columns(panels, N), i = NB == 1 ? 0 : NB == 2 ? 1 : 2;
+        if (NB_out) *NB_out = NB;
+        const double rounds = std::max(1.0, (double)(panels * ((N + NB * 4 - 1) / (NB * 4))) / 256.0);  // several workgroups per compute unit
+        return 2.6 + rounds * (1e-3 * (double)steps * (ns_per_step[i] + ns_density[i] * density) + us_per_round[i]);
+    }
+    // A compute unit holds one workgroup at a time.
+    static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 246, 477}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.1, 4.3}};  // R = 16, 32; NB = 1, 2, 4
     double best = 0.0;
     for (int i = 0, NB = 1; i < 3; ++i, NB *= 2) {
         if (NB > 1 && rows * NB >= 2 * N) break;  // more than half of the tile idle
         const int64_t blocks = panels * ((N + rows * NB - 1) / (rows * NB));
-        const double t = 3.0 + 1e-3 * (double)((blocks + 255) / 256 * steps) * (ns_per_step[rows == 32][i] + 45.0 * (density > 0.1 ? density - 0.1 : 0.0));
+        const double ns = ns_per_step[rows == 32][i] + 60.0 * std::max(0.0, density - 0.1);
+        const double t = 1.1 + (double)((blocks + 255) / 256) * (1e-3 * (double)steps * ns + us_per_round[rows == 32][i]);
         if (i == 0 || t < best) {
             best = t;
             if (NB_out) *NB_out = NB;
@@ -546,8 +791,16 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
     hipStream_t s = (hipStream_t)stream;
     const int64_t step_bytes = (int64_t)TILE_OPERANDS * 64 / p.rows * 4 * N;  // rows of B a step touches
     if (step_bytes >= ((int64_t)1 << 32)) {
-        if (p.rows == 32) launch<32, 4, 8, false, 2, true>(a, s);
+        if (p.rows == NARROW_ROWS) launch_narrow<4, 8, 4, true, 2>(a, s);
+        else if (p.rows == 32) launch<32, 4, 8, false, 2, true>(a, s);
         else launch<16, 4, 8, false, 2, true>(a, s);
+        return (int)hipGetLastError();
+    }
+    if (p.rows == NARROW_ROWS) {
+        const int NB = narrow_columns(p.n_panels, N), W = narrow_waves(p.n_panels, p.n_steps, N, NB);
+        if (NB == 1) launch_narrow<1>(a, W, p.loads, s);
+        else if (NB == 2) launch_narrow<2>(a, W, p.loads, s);
+        else launch_narrow<4>(a, W, p.loads, s);
         return (int)hipGetLastError();
     }
     int NB = 1;
