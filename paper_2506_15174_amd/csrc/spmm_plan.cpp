@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <functional>
 #include <cstring>
 #include <new>
 #include <numeric>
@@ -484,31 +485,47 @@ std::vector<int64_t> range_cuts(const std::vector<Group> &groups, int want)
 
 // Tiles multiply the absent entries too, so their time does not fall with the density as the
 // chunks' does: wide B takes them from about 15 % of the entries on, B of up to 16 columns (whose
-// gathers fetch little at a time) from 5 to 10 % on, small matrices later or never.  Both times are estimated
-// and tiles are taken where theirs is at least 5 % shorter.  Of 1266 measured products (18 shapes
-// from 256 to 16384 rows and columns, 3 to 50 % of the entries kept, 4 to 256 columns) that moves 464
-// to tiles, 1.36 times as fast on average, the worst at 0.89.
+// gathers fetch little at a time) from 5 to 10 % on, small matrices later or never.  Both times are
+// estimated and tiles are taken where theirs is at least 5 % shorter.  Of 917 measured products (13 shapes from
+// 512 to 16384 rows and 600 to 13000 columns, 4 to 45 % of the entries kept in even, lognormal or
+// Zipf rows, 4 to 256 columns) that moves 364 to tiles, 1.41 times as fast on average; ten are more
+// than 3 % slower, the worst at 0.86.
 //
 // The chunks' time in us: a constant, the wave loads that gather rows of B, the vector FMAs (millions), the
-// plan's bytes (MB), the chunks (millions, dearer the more rows they span), and the second launch of
-// a plan cut along K.  Within 17 % (hints up to 8) to 8 % (64 and more) on uniform matrices; rows of
-// uneven length take longer on chunks, hardly on tiles.
-static double chunks_time(int64_t M, int64_t K, int64_t nnz, int32_t n_hint, double N)
+// plan's bytes (MB), the chunks (millions, dearer the more rows they span), the second launch of
+// a plan cut along K or across workgroups, and the chunks of the longest piece of a panel cut into eight
+// (hundreds), the tail of the launch where rows are of uneven length.  Within 8 to 17 % (hints up to 8) of
+// 2091 measured products with even, lognormal and Zipf rows.
+static double chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
 {
-    static const double weights[5][6] = {{2.82, 9.84, 10.5, 0.0, 69.5, 0.0},    // n_hint <= 8
-                                         {2.88, 7.07, 0.0, 0.265, 31.5, 0.0},   // ... 16
-                                         {2.99, 14.2, 0.0, 0.350, 7.93, 0.0},   // ... 32
-                                         {2.74, 19.5, 0.0, 0.495, 4.61, 0.0},   // ... 64
-                                         {3.14, 21.0, 0.0, 0.602, 14.6, 1.27}}; // more, or unknown
+    static const double weights[5][8] = {{2.90, 7.22, 10.1, 0.0, 71.6, 0.0, 4.87, 0.0},   // n_hint <= 8
+                                         {2.99, 6.40, 0.0, 0.25, 31.0, 0.0, 6.28, 0.0},   // ... 16
+                                         {3.03, 13.9, 0.0, 0.35, 4.52, 0.0, 5.24, 0.0},   // ... 32
+                                         {2.79, 13.4, 0.0, 0.56, 3.20, 0.0, 6.97, 5.99},  // ... 64
+                                         {2.97, 22.1, 0.0, 0.70, 0.74, 1.73, 12.3, 15.2}};  // more, or unknown
     const double *w = weights[N <= 8 ? 0 : N <= 16 ? 1 : N <= 32 ? 2 : N <= 64 ? 3 : 4];
+    // the schedule the chunks would get, but for details
+    const int64_t nnz = row_ptr[M];
+    const bool skewed = skewed_rows(row_ptr, M, nnz);
     const int ufk = choose_ufk(K, n_hint), slices = choose_kslices(0, M, K, nnz, n_hint, ufk);
-    const int ufi = choose_ufi(M, (K + slices - 1) / slices, nnz, n_hint);
-    const double density = (double)nnz / ((double)M * (double)K);
-    const double fetched = (double)M / ufi * (double)K * (1.0 - std::pow(1.0 - density, ufi));  // rows of B, for one column tile
+    const bool cross = slices == 1 && cross_allowed(0, skewed, nnz, n_hint);
+    std::vector<int32_t> len((size_t)M);
+    for (int64_t i = 0; i < M; ++i) len[(size_t)i] = row_ptr[i + 1] - row_ptr[i];
+    const int64_t columns = (K + slices - 1) / slices, max_row = *std::max_element(len.begin(), len.end()) / slices;
+    const int ufi = skewed ? choose_ufi_skewed(columns, nnz, max_row, n_hint, cross) : choose_ufi(M, columns, nnz, n_hint);
+    if (skewed && ufi > 1) std::sort(len.begin(), len.end(), std::greater<int32_t>());
+    double fetched = 0.0, longest = 0.0;  // rows of B for one column tile: of all panels, of one
+    for (int64_t i = 0; i < M; i += ufi) {
+        double absent = 1.0;
+        for (int64_t r = i; r < std::min<int64_t>(M, i + ufi); ++r) absent *= 1.0 - (double)len[(size_t)r] / (double)K;
+        fetched += (double)K * (1.0 - absent);
+        longest = std::max(longest, (double)K * (1.0 - absent));
+    }
     const int tile = ufk == 8 ? (N > 64 ? 128 : 64) : ufk == 16 ? 32 : ufk == 32 ? 16 : N > 4 ? 8 : 4;
     const double tiles = std::ceil(N / tile) * 1e-6, per_load = 256.0 / tile;
     return w[0] + tiles * (w[1] * fetched / per_load + w[2] * 4.2 * (double)nnz / per_load + w[3] * (4.0 * fetched + 4.2 * (double)nnz) +
-                           w[4] * fetched / ufk * std::sqrt((double)ufi)) + (slices > 1 ? w[5] : 0.0);
+                           w[4] * fetched / ufk * std::sqrt((double)ufi)) +
+           (slices > 1 ? w[5] : 0.0) + (cross ? w[7] : w[6] * 1e-2 * longest / (8.0 * ufk * slices));
 }
 
 int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
@@ -518,10 +535,13 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     if (density < 0.03) return 0;           // below all that was measured
     if (nnz < ((int64_t)1 << 17)) return 0;  // mostly the launch's time: 1.5 % on average to gain
     const double N = n_hint <= 0 ? 128 : std::min(std::max(n_hint, 4), 256);
-    double best = 0.95 * chunks_time(M, K, nnz, n_hint, N);
+    double best = 0.95 * chunks_time(M, K, row_ptr, n_hint, N);
     int rows = 0;
     for (int r : {8, 16, 32}) {
-        const double t = spmm_tiles_time(r, M, K, (int64_t)N, density, nullptr);
+        int64_t heaviest = 0;
+        for (int64_t i = 0; i < M; i += r) heaviest = std::max<int64_t>(heaviest, row_ptr[std::min<int64_t>(M, i + r)] - row_ptr[i]);
+        const double peak = std::max(density, (double)heaviest / ((double)r * (double)K));
+        const double t = spmm_tiles_time(r, M, K, (int64_t)N, density, peak, nullptr);
         if (t < best) {
             best = t;
             rows = r;

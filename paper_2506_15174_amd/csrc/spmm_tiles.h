@@ -11,7 +11,8 @@
 //   R = 32, 16   row l % R of the panel, column t * 64 / R + l / R of the step
 //   R = 8        row t % 2 * 4 + l % 4, column t / 2 * 16 + l / 4
 // A block stores
-//   values     its entries in any order, filled up to a multiple of eight with zeros
+//   values     its entries, filled up to a multiple of eight with zeros; their order spreads the places of
+//              the entries that a wave writes together over the banks of LDS
 //   places     16 bits per entry: where the value goes in the expanded block, in bytes:
 //              TILE_PLACE0 + ((t / 4 * 64 + l) * 4 + t % 4) * 4, or 0 for a filler
 // Blocks lie panel by panel, step by step.
@@ -36,9 +37,9 @@ int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t
                      TilePlan &out);
 void spmm_tiles_release(TilePlan &p);
 
-// Estimated time of a product in us with panels of `rows` rows (density = share of the entries kept),
-// and the column groups NB of a tile (1, 2 or 4) it runs with.
-double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, int *NB);
+// Estimated time of a product in us with panels of `rows` rows, and the column groups NB of a tile
+// (1, 2 or 4) it runs with.  density = share of the entries kept, peak = the largest such share of a panel.
+double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB);
 
 // Enqueues C <- A x B.  Returns the hipError_t of the launch as int.
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream);

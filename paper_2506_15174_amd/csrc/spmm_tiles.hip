@@ -345,7 +345,6 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
     constexpr int NT = NB * 4;        // columns of C per tile
     constexpr int SLOT = A_SLOT_WORDS;
     constexpr int T = R * NB;         // sums per lane
-    constexpr bool UNSCATTER = AL <= 2;
     static_assert(R * NT <= SLOT, "a wave's sums fit its slot");
     __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
 
@@ -394,7 +393,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
     };
     // Runs of 64 steps: lane i holds the bounds of the i-th block of the run.  (With the bounds loaded
     // inside of the pipeline every step would have to wait for all loads on their way, in case this one
-    // is among them; for the same reason all steps make the same number of loads.)
+    // is among them; for the same reason all steps make the same number of loads, up to 512 entries.)
     uint32_t lo = 0, hi = 0, last = 0, n_next = 0;
     f32x4 va[AL];
     u32x2 vp[AL];
@@ -406,6 +405,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
         const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(block) + (size_t)n_next * 4u, (short)0, (int)(n_next * 2u), 0x00020000);
 #pragma unroll
         for (int q = 0; q < AL; ++q) {
+            if (AL > 2 && q > 0 && n_next <= 256u) break;  // few blocks are as long as the longest where rows are uneven
             va[q] = buffer_load<4>(rv, (uint32_t)lane * 16u + 1024u * (uint32_t)q);
             vp[q] = __builtin_amdgcn_raw_buffer_load_b64(rp, (int)((uint32_t)lane * 8u + 512u * (uint32_t)q), 0, 0);
         }
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
 #pragma unroll
             for (int q = 0; q < OPS / 4; ++q) a[q] = expanded[64 * q];
             // ---- zeros again for the next block, at its places where they are few
-            if constexpr (UNSCATTER) {
+            if (AL <= 2 || n <= 256u) {
                 lds_in_order();
                 scatter([](int, int) { return 0.0f; });
             } else {
@@ -546,7 +546,29 @@ template <int R> __device__ __forceinline__ position position_of(uint32_t row, u
 
 enum { BAD_COLUMN = 1, TWICE = 2 };
 
-constexpr int MASK_WORDS = 32;  // bitmap of a block while the plan is built: 16 bits per lane
+// The order of a block's entries.  A wave writes up to 64 of them to LDS at a time, so entries
+// that lie in different banks should follow each other: the places of a block fall into 64 classes of
+// 16 (place in words modulo 64), and the block takes the first entry of every class, in class order, then the
+// second of every class, and so on.  (In the order of the rows, a dense row's entries met in one bank: 2048 x 8192
+// with Zipf rows, 90 % pruned, 4 columns took 12.6 us instead of 6.1.)
+struct bank {
+    uint32_t of, rank_bit;  // the class; the place's number in it
+};
+__device__ __forceinline__ bank bank_of(const position &p) { return bank{p.lane % 16 * 4 + p.op % 4, p.lane / 16 * 4 + p.op / 4}; }
+
+constexpr int MASK_WORDS = 32;  // bitmap of a block while the plan is built: 16 bits per class
+struct block_order {            // of the entries that are the r-th of their classes:
+    uint64_t classes[16];       // the classes
+    uint16_t first[16];         // how many entries come before them
+};
+
+// Where the j-th entry of a block of n (a multiple of eight) entries is stored: lane l of the wave
+// reads entries 4 l .. 4 l + 3 of a run of 256 and writes the first of each lane together, then the second.
+__device__ __forceinline__ uint32_t stored_at(uint32_t j, uint32_t n)
+{
+    const uint32_t run = j / 256u * 256u, lanes = (n - run < 256u ? n - run : 256u) / 4u;
+    return run + (j - run) % lanes * 4u + (j - run) / lanes;
+}
 
 // One wave per row: sets the entries' bits.
 template <int R> __global__ __launch_bounds__(256) void mark_kernel(const int32_t *row_ptr, const int32_t *col_idx, int64_t M, int64_t K, int64_t n_steps,
@@ -562,21 +584,32 @@ template <int R> __global__ __launch_bounds__(256) void mark_kernel(const int32_
             continue;
         }
         const position p = position_of<R>((uint32_t)row, (uint32_t)c);
-        uint32_t *word = masks + ((size_t)(row / R) * n_steps + p.step) * MASK_WORDS + p.lane / 2;
-        const uint32_t bit = 1u << (p.lane % 2 * 16 + p.op);
+        const bank k = bank_of(p);
+        uint32_t *word = masks + ((size_t)(row / R) * n_steps + p.step) * MASK_WORDS + k.of / 2;
+        const uint32_t bit = 1u << (k.of % 2 * 16 + k.rank_bit);
         if (atomicOr(word, bit) & bit) bad |= TWICE;
     }
     if (bad) atomicOr(flags, bad);
 }
 
-// Half a wave per block: its length in units of eight entries, to offsets[panel][step].
-__global__ __launch_bounds__(256) void measure_kernel(const uint32_t *masks, int64_t n_panels, int64_t n_steps, uint32_t *counts, uint32_t *offsets, uint32_t *longest)
+// One wave per block: its length, to offsets[panel][step] in units of eight entries, and its order.
+__global__ __launch_bounds__(256) void measure_kernel(const uint32_t *masks, int64_t n_panels, int64_t n_steps, block_order *order,
+                                                      uint32_t *counts, uint32_t *offsets, uint32_t *longest)
 {
-    const int64_t b = (int64_t)blockIdx.x * 8 + threadIdx.x / 32;
+    const int64_t b = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
     if (b >= n_panels * n_steps) return;
-    uint32_t n = (uint32_t)__builtin_popcount(masks[(size_t)b * MASK_WORDS + (threadIdx.x & 31)]);
-    for (int m = 16; m; m >>= 1) n += (uint32_t)__shfl_xor((int)n, m, 32);
-    if ((threadIdx.x & 31) != 0) return;
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t mine = __builtin_popcount(masks[(size_t)b * MASK_WORDS + lane / 2] >> (lane % 2 * 16) & 0xFFFFu);
+    uint32_t n = 0;
+    for (uint32_t r = 0; r < 16; ++r) {
+        const uint64_t classes = __ballot(mine > r);
+        if (lane == r) {
+            order[b].classes[r] = classes;
+            order[b].first[r] = (uint16_t)n;
+        }
+        n += (uint32_t)__builtin_popcountll(classes);
+    }
+    if (lane != 0) return;
     counts[b] = n;
     if (n > *longest) atomicMax(longest, n);
     offsets[b / n_steps * (n_steps + 1) + b % n_steps] = (n + 7) / 8;
@@ -648,15 +681,16 @@ __global__ __launch_bounds__(256) void place_kernel(int64_t n_panels, int64_t n_
     if (s + 1 == n_steps) o[1] += base;
     char *block = stream + (size_t)start * 48;
     for (uint32_t i = n; i < padded; ++i) {
-        reinterpret_cast<float *>(block)[i] = 0.0f;
-        reinterpret_cast<uint16_t *>(block + (size_t)padded * 4)[i] = 0;
+        const uint32_t at = stored_at(i, padded);
+        reinterpret_cast<float *>(block)[at] = 0.0f;
+        reinterpret_cast<uint16_t *>(block + (size_t)padded * 4)[at] = 0;
     }
 }
 
-// One wave per row: the entries to their blocks.  Their order inside a block is free (every
-// entry carries its place), so a counter per block, run down from its entries, deals the slots.
+// One wave per row: the entries to their blocks.
 template <int R> __global__ __launch_bounds__(256) void fill_kernel(const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t M,
-                                                                    int64_t n_steps, const uint32_t *offsets, uint32_t *counts, char *stream)
+                                                                    int64_t n_steps, const uint32_t *offsets, const uint32_t *masks,
+                                                                    const block_order *order, char *stream)
 {
     const int64_t row = (int64_t)blockIdx.x * 4 + threadIdx.x / 64;
     if (row >= M) return;
@@ -664,9 +698,14 @@ template <int R> __global__ __launch_bounds__(256) void fill_kernel(const int32_
         const position p = position_of<R>((uint32_t)row, (uint32_t)col_idx[q]);
         const uint32_t *o = offsets + row / R * (n_steps + 1) + p.step;
         char *block = stream + (size_t)o[0] * 48;
-        const uint32_t i = atomicSub(&counts[row / R * n_steps + p.step], 1u) - 1u;
+        const uint32_t n = (o[1] - o[0]) * 8;
+        const size_t b = (size_t)(row / R * n_steps + p.step);
+        const bank k = bank_of(p);
+        const uint32_t in_class = masks[b * MASK_WORDS + k.of / 2] >> (k.of % 2 * 16) & 0xFFFFu;
+        const uint32_t r = (uint32_t)__builtin_popcount(in_class & ((1u << k.rank_bit) - 1u));
+        const uint32_t i = stored_at(order[b].first[r] + (uint32_t)__builtin_popcountll(order[b].classes[r] & ((1ull << k.of) - 1ull)), n);
         reinterpret_cast<float *>(block)[i] = vals[q];
-        reinterpret_cast<uint16_t *>(block + (size_t)(o[1] - o[0]) * 32)[i] = (uint16_t)(TILE_PLACE0 + (p.op / 4 * 64 + p.lane) * 16 + p.op % 4 * 4);
+        reinterpret_cast<uint16_t *>(block + (size_t)n * 4)[i] = (uint16_t)(TILE_PLACE0 + (p.op / 4 * 64 + p.lane) * 16 + p.op % 4 * 4);
     }
 }
 
@@ -685,7 +724,7 @@ struct device_array {
 template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, TilePlan &out, int &status)
 {
     const int64_t nnz = row_ptr[M], P = out.n_panels, S = out.n_steps;
-    device_array d_ptr, d_col, d_val, d_masks, d_counts, d_base;
+    device_array d_ptr, d_col, d_val, d_masks, d_order, d_counts, d_base;
     const size_t mask_bytes = (size_t)(P * S) * MASK_WORDS * 4;
     hipError_t e;
 #define TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
@@ -693,19 +732,20 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     TRY(d_col.take((size_t)nnz * 4));
     TRY(d_val.take((size_t)nnz * 4));
     TRY(d_masks.take(mask_bytes));
+    TRY(d_order.take((size_t)(P * S) * sizeof(block_order)));
     TRY(d_counts.take((size_t)(P * S) * 4));
     TRY(d_base.take((size_t)(P + 2) * 8));
     TRY(hipMalloc(reinterpret_cast<void **>(&out.d_offsets), (size_t)P * (size_t)(S + 1) * 4));
     uint64_t *base = d_base.as<uint64_t>();
     uint32_t *flags = reinterpret_cast<uint32_t *>(base + P + 1);
     const hipStream_t s = nullptr;
-    const unsigned row_blocks = (unsigned)((M + 3) / 4), block_blocks = (unsigned)((P * S + 7) / 8);
+    const unsigned row_blocks = (unsigned)((M + 3) / 4), block_blocks = (unsigned)((P * S + 3) / 4);
     hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<int64_t>(4096, (int64_t)(mask_bytes / 4096 + 1))), dim3(256), 0, s, d_masks.as<u32x4>(), (int64_t)(mask_bytes / 16));
     TRY(hipMemsetAsync(flags, 0, 8, s));
     TRY(hipMemcpy(d_ptr.p, row_ptr, (size_t)(M + 1) * 4, hipMemcpyHostToDevice));
     TRY(hipMemcpy(d_col.p, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice));
     hipLaunchKernelGGL((mark_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr.as<int32_t>(), d_col.as<int32_t>(), M, K, S, d_masks.as<uint32_t>(), flags);
-    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks.as<uint32_t>(), P, S, d_counts.as<uint32_t>(), out.d_offsets, flags + 1);
+    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks.as<uint32_t>(), P, S, d_order.as<block_order>(), d_counts.as<uint32_t>(), out.d_offsets, flags + 1);
     hipLaunchKernelGGL(scan_panel_kernel, dim3((unsigned)P), dim3(256), 0, s, S, out.d_offsets, base);
     hipLaunchKernelGGL(scan_all_kernel, dim3(1), dim3(256), 0, s, P, base);
     TRY(hipGetLastError());
@@ -721,7 +761,7 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     char *stream = reinterpret_cast<char *>(out.d_stream);
     hipLaunchKernelGGL(place_kernel, dim3((unsigned)((P * S + 255) / 256)), dim3(256), 0, s, P, S, base, d_counts.as<uint32_t>(), out.d_offsets, stream);
     hipLaunchKernelGGL((fill_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr.as<int32_t>(), d_col.as<int32_t>(), d_val.as<float>(), M, S,
-                       out.d_offsets, d_counts.as<uint32_t>(), stream);
+                       out.d_offsets, d_masks.as<uint32_t>(), d_order.as<block_order>(), stream);
     TRY(hipGetLastError());
     TRY(hipStreamSynchronize(s));
 #undef TRY
@@ -758,7 +798,7 @@ void spmm_tiles_release(TilePlan &p)
 
 // Fits to 1900 measured products, 3 to 50 % of the entries kept, 4 to 256 columns: within 5 % of the time
 // (panels of 8 rows: 7 to 16 %), and the NB it prefers is within 0.1 % of the best one on average.
-double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, int *NB_out)
+double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB_out)
 {
     const int64_t panels = (M + rows - 1) / rows, steps = (K * rows + 1023) / 1024;
     if (rows == NARROW_ROWS) {
@@ -766,7 +806,8 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
         const int NB = narrow_columns(panels, N), i = NB == 1 ? 0 : NB == 2 ? 1 : 2;
         if (NB_out) *NB_out = NB;
         const double rounds = std::max(1.0, (double)(panels * ((N + NB * 4 - 1) / (NB * 4))) / 256.0);  // several workgroups per compute unit
-        return 2.6 + rounds * (1e-3 * (double)steps * (ns_per_step[i] + ns_density[i] * density) + us_per_round[i]);
+        return 2.6 + rounds * (1e-3 * (double)steps * (ns_per_step[i] + ns_density[i] * density) + us_per_round[i]) +
+               1e-3 * (double)steps * ns_density[i] * (peak - density);
     }
     // A compute unit holds one workgroup at a time.
     static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 246, 477}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.1, 4.3}};  // R = 16, 32; NB = 1, 2, 4
@@ -775,7 +816,8 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
         if (NB > 1 && rows * NB >= 2 * N) break;  // more than half of the tile idle
         const int64_t blocks = panels * ((N + rows * NB - 1) / (rows * NB));
         const double ns = ns_per_step[rows == 32][i] + 60.0 * std::max(0.0, density - 0.1);
-        const double t = 1.1 + (double)((blocks + 255) / 256) * (1e-3 * (double)steps * ns + us_per_round[rows == 32][i]);
+        const double t = 1.1 + (double)((blocks + 255) / 256) * (1e-3 * (double)steps * ns + us_per_round[rows == 32][i]) +
+                         1e-3 * (double)steps * 60.0 * (peak - density);
         if (i == 0 || t < best) {
             best = t;
             if (NB_out) *NB_out = NB;
@@ -804,7 +846,7 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
         return (int)hipGetLastError();
     }
     int NB = 1;
-    spmm_tiles_time(p.rows, M, K, N, 0.0, &NB);
+    spmm_tiles_time(p.rows, M, K, N, 0.0, 0.0, &NB);
     switch (p.rows * 8 + NB) {
     case 32 * 8 + 4: launch<32, 4, 8, false, 2>(a, s); break;
     case 32 * 8 + 2: launch<32, 2, 16, false, 4>(a, s); break;
