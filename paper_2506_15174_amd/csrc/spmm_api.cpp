@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstring>
 #include <new>
 #include <vector>
@@ -35,12 +36,42 @@ struct spmm_plan {
     bool force_wide = false;  // spmm_options_t.force_wide: 64-bit addressing kernels also on small inputs
     int depth = 0;            // spmm_options_t.depth: pipeline depth asked for (0 = per-instance default)
     bool probe = false;       // spmm_options_t.probe: loads-only launches (measurement)
+    uint32_t lds_pad = 0;     // extra LDS per workgroup that keeps a third one off a compute unit (hold_to_two)
 };
 
 namespace {
 
 // Columns a plan cut along K computes per pair of launches (the width of its slices' buffer).
 constexpr int32_t KSLICE_COLS = 128;
+
+// Whether to hold a compute unit to two workgroups.  The workgroups come heaviest first.  While all of
+// them fit the chip at once the device deals them out in turn, so with a few more than 512 the heaviest
+// units, which hold the first and the 257th, get the 513th as well; held to two per unit, those few wait
+// for the first one with room, a lightly loaded one.  (1024 x 4096 with lognormal rows, 90 % pruned, 64
+// columns, 559 workgroups: 9.9 -> 8.2 us.)  Fewer waves hide less latency, and those last workgroups start
+// late: of 300 measured plans the cap gains 9 % on average where the most loaded unit gets at least 14 % less
+// to do and a unit's mean load shrinks by 24 chunks or more, and loses elsewhere (even rows, little
+// work per row, more than 640 workgroups, three per unit).
+bool hold_to_two(const HostPlan &h)
+{
+    constexpr int64_t UNITS = 256;
+    const int64_t n = h.n_blocks;
+    if (n <= 2 * UNITS || n > 2 * UNITS + UNITS / 2) return false;
+    auto weight = [&](int64_t block) {
+        int64_t chunks = 0;
+        for (int w = 0; w < WAVES_PER_WG; ++w) chunks += h.items[(size_t)((block * WAVES_PER_WG + w) * ITEM_WORDS + IT_NCHUNKS)];
+        return chunks;
+    };
+    std::vector<int64_t> held((size_t)UNITS, 0);
+    for (int64_t b = 0; b < 2 * UNITS; ++b) held[(size_t)(b % UNITS)] += weight(b);
+    std::vector<int64_t> dealt = held;
+    for (int64_t b = 2 * UNITS; b < n; ++b) {
+        dealt[(size_t)(b % UNITS)] += weight(b);
+        *std::min_element(held.begin(), held.end()) += weight(b);
+    }
+    const double ratio = (double)*std::max_element(held.begin(), held.end()) / (double)std::max<int64_t>(1, *std::max_element(dealt.begin(), dealt.end()));
+    return ratio <= 0.86 && (double)h.n_chunks / UNITS * (1.0 - ratio) >= 24.0;
+}
 
 spmm_status_t hip_fail()
 {
@@ -186,6 +217,7 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
             size_t unused_bytes = 0;
             if (spmm_static_scratch(&unused, &unused_bytes) != 0) (void)hipGetLastError();
         }
+        if (h.k_slices == 1 && win_words(h.ufk) == WIN_WORDS && hold_to_two(h)) p->lds_pad = 48u << 10;  // 32 KiB and these: half of a unit's LDS
         if (st == SPMM_OK && h.k_slices > 1) {
             int64_t before = p->device_bytes;
             st = upload(&p->d_slice_sums, nullptr, (size_t)h.plan_rows * KSLICE_COLS * sizeof(float), p->device_bytes);
@@ -280,7 +312,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     const bool narrow_tiles = !sliced && (int64_t)h.K * 512 > ((int64_t)4 << 20) && (int64_t)h.K * 256 <= ((int64_t)4 << 20);
     // Such a tile fills the L2: two workgroups per CU instead of three keep the rows of B that
     // concurrently running waves sweep inside it (same matrix: 262 against 275 us).
-    a.lds_pad = narrow_tiles ? 24u << 10 : 0u;
+    const uint32_t tile_pad = narrow_tiles ? 24u << 10 : 0u;
     // Column tiles of one width share a launch (its workgroups start tile by tile, so a
     // tile begins while the previous one drains); a narrower rest takes a launch of its own.
     // Plans made for narrow B (chunks wider than 8 columns) run every N on their own narrow tiles.
@@ -326,6 +358,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
         a.width = cols;
         a.tile_cols = tile;
         a.n_tiles = n_tiles;
+        a.lds_pad = tile_pad == 0 && n_tiles == 1 ? plan->lds_pad : tile_pad;
         const uint64_t skipped = (uint64_t)j0 * 4u;
         a.b_bytes = wide || b_total <= skipped ? 0u : (uint32_t)(b_total - skipped);
         const int e = spmm_launch_chunks(a, h.ufi, h.ufk, slices, wide, plan->depth, stream);
