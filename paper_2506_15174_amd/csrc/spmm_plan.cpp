@@ -538,6 +538,7 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     double best = 0.95 * chunks_time(M, K, row_ptr, n_hint, N);
     int rows = 0;
     for (int r : {8, 16, 32}) {
+        if (r == 8 && N > 64) continue;  // its tiles are 16 columns wide: too small a part of every row of B
         int64_t heaviest = 0;
         for (int64_t i = 0; i < M; i += r) heaviest = std::max<int64_t>(heaviest, row_ptr[std::min<int64_t>(M, i + r)] - row_ptr[i]);
         const double peak = std::max(density, (double)heaviest / ((double)r * (double)K));

@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "spmm_tiles.h"
 
@@ -71,6 +72,13 @@ template <> struct Tile<16> {
     static __device__ __forceinline__ acc_t mfma(float b, float a, const acc_t &c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0); }
 };
 
+// The workgroup's place among the column tiles of all panels, panel by panel.  Workgroups are dealt to
+// the eight XCDs in turn: each XCD takes an eighth of these places, next to each other, so that a panel's
+// blocks are read into one L2 (but for the panels at the borders) and the XCDs have equally much to do
+// also when the panels are few (269 x 6139, 82 % pruned, 100 columns: with whole panels dealt to XCDs 16.5 us, now 12.5).
+__device__ __forceinline__ uint32_t place_in_matrix() { return blockIdx.x % 8u * (gridDim.x / 8u) + blockIdx.x / 8u; }
+unsigned grid_for(int64_t places) { return (unsigned)((places + 7) / 8) * 8u; }
+
 // One workgroup computes a tile of C: R rows x NB * R columns.
 //
 // R       rows of a panel (32: v_mfma_f32_32x32x2, 16: v_mfma_f32_16x16x4; fp32 operands and sums)
@@ -111,11 +119,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
     constexpr int LDS_WORDS = W * SLOT > RED ? W * SLOT : RED;
     __shared__ __attribute__((aligned(16))) float lds[LDS_WORDS];
 
-    // Panel p runs on XCD p % 8 (workgroups are dealt to the XCDs in turn), all its column
-    // tiles one after the other, so that its blocks are read into one L2.
-    const uint32_t g8 = blockIdx.x / 8u;
-    const uint32_t nt = g8 % (uint32_t)args.n_tiles;
-    const uint32_t panel = (g8 / (uint32_t)args.n_tiles) * 8u + blockIdx.x % 8u;
+    const uint32_t id = place_in_matrix(), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
     if (panel >= (uint32_t)args.n_panels) return;
     const uint32_t n0 = nt * (uint32_t)NT;
 
@@ -301,7 +305,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
 template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void launch(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (a.N + NB * R - 1) / (NB * R);
-    const unsigned blocks = (unsigned)((a.n_panels + 7) / 8) * 8u * (unsigned)a.n_tiles;
+    const unsigned blocks = grid_for((int64_t)a.n_panels * a.n_tiles);
     hipLaunchKernelGGL((spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>), dim3(blocks), dim3(64 * W), 0, s, a);
 }
 
@@ -348,9 +352,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
     static_assert(R * NT <= SLOT, "a wave's sums fit its slot");
     __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
 
-    const uint32_t g8 = blockIdx.x / 8u;  // panels to XCDs as in the kernel above
-    const uint32_t nt = g8 % (uint32_t)args.n_tiles;
-    const uint32_t panel = (g8 / (uint32_t)args.n_tiles) * 8u + blockIdx.x % 8u;
+    const uint32_t id = place_in_matrix(), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
     if (panel >= (uint32_t)args.n_panels) return;
     const uint32_t n0 = nt * (uint32_t)NT;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -501,7 +503,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
 template <int NB, int W, int AL, bool WIDE, int MINW> void launch_narrow(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (a.N + NB * 4 - 1) / (NB * 4);
-    const unsigned blocks = (unsigned)((a.n_panels + 7) / 8) * 8u * (unsigned)a.n_tiles;
+    const unsigned blocks = grid_for((int64_t)a.n_panels * a.n_tiles);
     hipLaunchKernelGGL((spmm_narrow_tiles_kernel<NB, W, AL, WIDE, MINW>), dim3(blocks), dim3(64 * W), 0, s, a);
 }
 template <int NB, int W> void launch_narrow(tile_args &a, int loads, hipStream_t s)
@@ -523,7 +525,7 @@ template <int NB> void launch_narrow(tile_args &a, int waves, int loads, hipStre
 // 16; 2048 x 8192 with 70 % pruned, 4 columns: 7.1 us with eight waves, 9.5 us with four; 4096 x 1024: 3.8 and 3.6 us.)
 int narrow_columns(int64_t panels, int64_t N)
 {
-    int NB = 1;
+    int NB = N <= 16 ? 1 : N <= 32 ? 2 : 4;  // a quarter of a row of B at least: of shorter parts the L1 fetches too much beside them
     while (NB < 4 && NB * 4 < N && panels * ((N + NB * 4 - 1) / (NB * 4)) > 256) NB *= 2;
     return NB;
 }
@@ -805,7 +807,9 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
         static const double ns_per_step[3] = {30, 61, 85}, ns_density[3] = {120, 114, 145}, us_per_round[3] = {0.02, 0.2, 0.3};
         const int NB = narrow_columns(panels, N), i = NB == 1 ? 0 : NB == 2 ? 1 : 2;
         if (NB_out) *NB_out = NB;
-        const double rounds = std::max(1.0, (double)(panels * ((N + NB * 4 - 1) / (NB * 4))) / 256.0);  // several workgroups per compute unit
+        // Several workgroups share a compute unit: a unit with one more than the others takes
+        // about half as much longer.
+        const double share = std::max(1.0, (double)(panels * ((N + NB * 4 - 1) / (NB * 4))) / 256.0), rounds = 0.5 * (share + std::ceil(share));
         return 2.6 + rounds * (1e-3 * (double)steps * (ns_per_step[i] + ns_density[i] * density) + us_per_round[i]) +
                1e-3 * (double)steps * ns_density[i] * (peak - density);
     }
