@@ -716,42 +716,51 @@ __global__ __launch_bounds__(256) void clear_kernel(u32x4 *p, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = u32x4{0, 0, 0, 0};
 }
 
-struct device_array {
-    void *p = nullptr;
-    ~device_array() { if (p) (void)hipFree(p); }
-    hipError_t take(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 16); }
-    template <typename T> T *as() const { return static_cast<T *>(p); }
+// The builder's device memory in one piece: an allocation and its release cost 10 to 100 us each.
+struct device_arrays {
+    char *base = nullptr;
+    size_t bytes = 0;
+    ~device_arrays() { if (base) (void)hipFree(base); }
+    size_t reserve(size_t n)
+    {
+        const size_t at = bytes;
+        bytes += (n + 255) & ~(size_t)255;
+        return at;
+    }
+    hipError_t take() { return hipMalloc(reinterpret_cast<void **>(&base), bytes); }
+    template <typename T> T *at(size_t offset) const { return reinterpret_cast<T *>(base + offset); }
 };
 
 template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, TilePlan &out, int &status)
 {
     const int64_t nnz = row_ptr[M], P = out.n_panels, S = out.n_steps;
-    device_array d_ptr, d_col, d_val, d_masks, d_order, d_counts, d_base;
     const size_t mask_bytes = (size_t)(P * S) * MASK_WORDS * 4;
     hipError_t e;
 #define TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-    TRY(d_ptr.take((size_t)(M + 1) * 4));
-    TRY(d_col.take((size_t)nnz * 4));
-    TRY(d_val.take((size_t)nnz * 4));
-    TRY(d_masks.take(mask_bytes));
-    TRY(d_order.take((size_t)(P * S) * sizeof(block_order)));
-    TRY(d_counts.take((size_t)(P * S) * 4));
-    TRY(d_base.take((size_t)(P + 2) * 8));
+    device_arrays memory;
+    const size_t at_ptr = memory.reserve((size_t)(M + 1) * 4), at_col = memory.reserve((size_t)nnz * 4), at_val = memory.reserve((size_t)nnz * 4),
+                 at_masks = memory.reserve(mask_bytes), at_order = memory.reserve((size_t)(P * S) * sizeof(block_order)),
+                 at_counts = memory.reserve((size_t)(P * S) * 4), at_base = memory.reserve((size_t)(P + 2) * 8);
+    TRY(memory.take());
+    int32_t *d_ptr = memory.at<int32_t>(at_ptr), *d_col = memory.at<int32_t>(at_col);
+    float *d_val = memory.at<float>(at_val);
+    uint32_t *d_masks = memory.at<uint32_t>(at_masks), *d_counts = memory.at<uint32_t>(at_counts);
+    block_order *d_order = memory.at<block_order>(at_order);
     TRY(hipMalloc(reinterpret_cast<void **>(&out.d_offsets), (size_t)P * (size_t)(S + 1) * 4));
-    uint64_t *base = d_base.as<uint64_t>();
+    uint64_t *base = memory.at<uint64_t>(at_base);
     uint32_t *flags = reinterpret_cast<uint32_t *>(base + P + 1);
     const hipStream_t s = nullptr;
     const unsigned row_blocks = (unsigned)((M + 3) / 4), block_blocks = (unsigned)((P * S + 3) / 4);
-    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<int64_t>(4096, (int64_t)(mask_bytes / 4096 + 1))), dim3(256), 0, s, d_masks.as<u32x4>(), (int64_t)(mask_bytes / 16));
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<int64_t>(4096, (int64_t)(mask_bytes / 4096 + 1))), dim3(256), 0, s, reinterpret_cast<u32x4 *>(d_masks), (int64_t)(mask_bytes / 16));
     TRY(hipMemsetAsync(flags, 0, 8, s));
-    TRY(hipMemcpy(d_ptr.p, row_ptr, (size_t)(M + 1) * 4, hipMemcpyHostToDevice));
-    TRY(hipMemcpy(d_col.p, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice));
-    hipLaunchKernelGGL((mark_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr.as<int32_t>(), d_col.as<int32_t>(), M, K, S, d_masks.as<uint32_t>(), flags);
-    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks.as<uint32_t>(), P, S, d_order.as<block_order>(), d_counts.as<uint32_t>(), out.d_offsets, flags + 1);
+    TRY(hipMemcpy(d_ptr, row_ptr, (size_t)(M + 1) * 4, hipMemcpyHostToDevice));
+    TRY(hipMemcpy(d_col, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice));
+    hipLaunchKernelGGL((mark_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr, d_col, M, K, S, d_masks, flags);
+    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks, P, S, d_order, d_counts, out.d_offsets, flags + 1);
     hipLaunchKernelGGL(scan_panel_kernel, dim3((unsigned)P), dim3(256), 0, s, S, out.d_offsets, base);
     hipLaunchKernelGGL(scan_all_kernel, dim3(1), dim3(256), 0, s, P, base);
     TRY(hipGetLastError());
-    TRY(hipMemcpy(d_val.p, vals, (size_t)nnz * 4, hipMemcpyHostToDevice));  // the kernels run meanwhile
+    TRY(hipMemcpy(d_val, vals, (size_t)nnz * 4, hipMemcpyHostToDevice));  // the kernels run meanwhile
     uint64_t answer[2];
     TRY(hipMemcpy(answer, base + P, 16, hipMemcpyDeviceToHost));
     const uint32_t bad = (uint32_t)answer[1];
@@ -761,9 +770,9 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     out.stream_words = (int64_t)answer[0] * 12;
     TRY(hipMalloc(reinterpret_cast<void **>(&out.d_stream), (size_t)std::max<int64_t>(out.stream_words, 4) * 4));
     char *stream = reinterpret_cast<char *>(out.d_stream);
-    hipLaunchKernelGGL(place_kernel, dim3((unsigned)((P * S + 255) / 256)), dim3(256), 0, s, P, S, base, d_counts.as<uint32_t>(), out.d_offsets, stream);
-    hipLaunchKernelGGL((fill_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr.as<int32_t>(), d_col.as<int32_t>(), d_val.as<float>(), M, S,
-                       out.d_offsets, d_masks.as<uint32_t>(), d_order.as<block_order>(), stream);
+    hipLaunchKernelGGL(place_kernel, dim3((unsigned)((P * S + 255) / 256)), dim3(256), 0, s, P, S, base, d_counts, out.d_offsets, stream);
+    hipLaunchKernelGGL((fill_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr, d_col, d_val, M, S,
+                       out.d_offsets, d_masks, d_order, stream);
     TRY(hipGetLastError());
     TRY(hipStreamSynchronize(s));
 #undef TRY
