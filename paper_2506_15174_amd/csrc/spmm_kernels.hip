@@ -684,15 +684,18 @@ template <int U, int D2, int D4, int D8> void launch_slices(const spmm_launch_ar
 }
 
 // Plans made for narrow B (chunks of 16, 32 or 64 columns): one instance per height and chunk
-// width pair, at the tuned depth, 32-bit addressing only.  slices: 8 (tile of 32 columns,
-// chunks of 16), 16 (16 columns, chunks of 32), 32 or 64 (8 or 4 columns, chunks of 64).
+// width pair, 32-bit addressing only.  slices: 8 (tile of 32 columns, chunks of 16), 16 (16
+// columns, chunks of 32), 32 or 64 (8 or 4 columns, chunks of 64).  Two chunks in flight: a wave
+// has five to thirty of these wide chunks, and every further one in flight lengthens the start of
+// its window (8192 x 8192, 98 % pruned, 32 columns: 9.5 us with four, 9.0 with three, 8.6 with two; 40 of
+// 48 plans of one to eight rows are fastest with two or, by less than 2 %, three).
 template <int U, int D> bool launch_narrow(const spmm_launch_args &a, int ufk, int slices, void *stream)
 {
     if (a.probe && ufk == 16 && slices == 8) launch_instance<U, 8, 4, D, false, 16, true>(a, stream);
     else if (ufk == 16 && slices == 8) launch_instance<U, 8, 4, D, false, 16>(a, stream);
-    else if (ufk == 32 && slices == 16) launch_instance<U, 16, 4, (D > 4 ? 4 : D), false, 32>(a, stream);
-    else if (ufk == 64 && slices == 32) launch_instance<U, 32, 4, (D > 4 ? 4 : D), false, 64>(a, stream);
-    else if (ufk == 64 && slices == 64) launch_instance<U, 64, 4, (D > 4 ? 4 : D), false, 64>(a, stream);
+    else if (ufk == 32 && slices == 16) launch_instance<U, 16, 4, D, false, 32>(a, stream);
+    else if (ufk == 64 && slices == 32) launch_instance<U, 32, 4, D, false, 64>(a, stream);
+    else if (ufk == 64 && slices == 64) launch_instance<U, 64, 4, D, false, 64>(a, stream);
     else return false;
     return true;
 }
@@ -713,10 +716,10 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
         bool ok = !wide;
         if (ok) {
             switch (ufi) {
-            case 8: ok = launch_narrow<8, 4>(a, ufk, slices, stream); break;
-            case 4: ok = launch_narrow<4, 3>(a, ufk, slices, stream); break;
-            case 2: ok = launch_narrow<2, 4>(a, ufk, slices, stream); break;
-            case 1: ok = launch_narrow<1, 4>(a, ufk, slices, stream); break;
+            case 8: ok = launch_narrow<8, 2>(a, ufk, slices, stream); break;
+            case 4: ok = launch_narrow<4, 2>(a, ufk, slices, stream); break;
+            case 2: ok = launch_narrow<2, 2>(a, ufk, slices, stream); break;
+            case 1: ok = launch_narrow<1, 2>(a, ufk, slices, stream); break;
             default: ok = false;
             }
         }

@@ -498,9 +498,9 @@ std::vector<int64_t> range_cuts(const std::vector<Group> &groups, int want)
 // 2091 measured products with even, lognormal and Zipf rows.
 static double chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
 {
-    static const double weights[5][8] = {{2.90, 7.22, 10.1, 0.0, 71.6, 0.0, 4.87, 0.0},   // n_hint <= 8
-                                         {2.99, 6.40, 0.0, 0.25, 31.0, 0.0, 6.28, 0.0},   // ... 16
-                                         {3.03, 13.9, 0.0, 0.35, 4.52, 0.0, 5.24, 0.0},   // ... 32
+    static const double weights[5][8] = {{2.90, 6.86, 9.60, 0.0, 68.0, 0.0, 4.63, 0.0},   // n_hint <= 8
+                                         {2.99, 6.08, 0.0, 0.24, 29.5, 0.0, 5.97, 0.0},   // ... 16
+                                         {3.03, 13.2, 0.0, 0.33, 4.30, 0.0, 4.98, 0.0},   // ... 32
                                          {2.79, 13.4, 0.0, 0.56, 3.20, 0.0, 6.97, 5.99},  // ... 64
                                          {2.97, 22.1, 0.0, 0.70, 0.74, 1.73, 12.3, 15.2}};  // more, or unknown
     const double *w = weights[N <= 8 ? 0 : N <= 16 ? 1 : N <= 32 ? 2 : N <= 64 ? 3 : 4];
