@@ -29,6 +29,7 @@ struct tile_args {
     float *C;
     uint64_t b_bytes;   // bytes of B
     int32_t n_panels, n_steps, n_tiles, M, K, N;
+    uint32_t first;     // the launch's first place among all column tiles of all panels
 };
 
 template <int NB> struct BVec;
@@ -76,8 +77,20 @@ template <> struct Tile<16> {
 // the eight XCDs in turn: each XCD takes an eighth of these places, next to each other, so that a panel's
 // blocks are read into one L2 (but for the panels at the borders) and the XCDs have equally much to do
 // also when the panels are few (269 x 6139, 82 % pruned, 100 columns: with whole panels dealt to XCDs 16.5 us, now 12.5).
-__device__ __forceinline__ uint32_t place_in_matrix() { return blockIdx.x % 8u * (gridDim.x / 8u) + blockIdx.x / 8u; }
-unsigned grid_for(int64_t places) { return (unsigned)((places + 7) / 8) * 8u; }
+__device__ __forceinline__ uint32_t place_in_matrix(uint32_t first) { return first + blockIdx.x % 8u * (gridDim.x / 8u) + blockIdx.x / 8u; }
+
+// Launches `kernel` for all column tiles of all panels.  HIP refuses a grid of 2^32 threads or more, which
+// a C of 8 GiB reaches on panels of 8 rows (32768 x 65536): the places are dealt to as many launches as
+// that takes.  (A C that fits the device's memory has fewer than 2^32 places.)
+template <typename F> void launch_places(F kernel, tile_args &a, unsigned threads, hipStream_t s)
+{
+    const int64_t places = (int64_t)a.n_panels * a.n_tiles, most = (((int64_t)1 << 32) - 1) / threads / 8 * 8;
+    for (int64_t first = 0; first < places; first += most) {
+        a.first = (uint32_t)first;
+        const unsigned blocks = (unsigned)((std::min(places - first, most) + 7) / 8) * 8u;
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, s, a);
+    }
+}
 
 // One workgroup computes a tile of C: R rows x NB * R columns.
 //
@@ -119,7 +132,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
     constexpr int LDS_WORDS = W * SLOT > RED ? W * SLOT : RED;
     __shared__ __attribute__((aligned(16))) float lds[LDS_WORDS];
 
-    const uint32_t id = place_in_matrix(), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
+    const uint32_t id = place_in_matrix(args.first), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
     if (panel >= (uint32_t)args.n_panels) return;
     const uint32_t n0 = nt * (uint32_t)NT;
 
@@ -305,8 +318,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
 template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void launch(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (a.N + NB * R - 1) / (NB * R);
-    const unsigned blocks = grid_for((int64_t)a.n_panels * a.n_tiles);
-    hipLaunchKernelGGL((spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>), dim3(blocks), dim3(64 * W), 0, s, a);
+    launch_places(spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>, a, 64 * W, s);
 }
 
 // ---------------------------------------------------------------- executor, narrow panels
@@ -352,7 +364,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
     static_assert(R * NT <= SLOT, "a wave's sums fit its slot");
     __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
 
-    const uint32_t id = place_in_matrix(), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
+    const uint32_t id = place_in_matrix(args.first), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
     if (panel >= (uint32_t)args.n_panels) return;
     const uint32_t n0 = nt * (uint32_t)NT;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -503,8 +515,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
 template <int NB, int W, int AL, bool WIDE, int MINW> void launch_narrow(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (a.N + NB * 4 - 1) / (NB * 4);
-    const unsigned blocks = grid_for((int64_t)a.n_panels * a.n_tiles);
-    hipLaunchKernelGGL((spmm_narrow_tiles_kernel<NB, W, AL, WIDE, MINW>), dim3(blocks), dim3(64 * W), 0, s, a);
+    launch_places(spmm_narrow_tiles_kernel<NB, W, AL, WIDE, MINW>, a, 64 * W, s);
 }
 template <int NB, int W> void launch_narrow(tile_args &a, int loads, hipStream_t s)
 {
@@ -842,7 +853,7 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream)
 {
     tile_args a{p.d_stream, p.d_offsets, B, C, (uint64_t)K * (uint64_t)N * 4u, (int32_t)p.n_panels, (int32_t)p.n_steps, 1,
-                (int32_t)M, (int32_t)K, N};
+                (int32_t)M, (int32_t)K, N, 0};
     hipStream_t s = (hipStream_t)stream;
     const int64_t step_bytes = (int64_t)TILE_OPERANDS * 64 / p.rows * 4 * N;  // rows of B a step touches
     if (step_bytes >= ((int64_t)1 << 32)) {

@@ -59,3 +59,24 @@ def test_rows_of_b_too_long_for_32_bit_offsets(torch_gpu, oracle):  # noqa: F811
     B_small, C_small = B[:, cols].contiguous().cpu().numpy(), C[:, cols].cpu().numpy()
     C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B_small)
     assert np.array_equal(C_small.astype(np.float64), C_ref)
+
+
+def test_more_workgroups_than_one_launch_takes(torch_gpu, oracle):  # noqa: F811
+    """C of 8 GiB on panels of 8 rows: 2^24 workgroups of 256 threads, one more launch than HIP takes at
+    once.  All of C is compared, a run of columns at a time."""
+    torch = torch_gpu
+    M, N = 32768, 65536
+    csr = integer_matrix(M, 16, 0.4, 31)
+    plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=8)
+    assert plan.describe()["tile_rows"] == 8
+    B = torch.randint(-9, 10, (csr.K, N), device="cuda").to(torch.float32)
+    C = torch.full((M, N), float("nan"), device="cuda")
+    plan.execute(B, C)
+    A = np.zeros((M, csr.K), np.float32)
+    A[np.repeat(np.arange(M), np.diff(csr.row_ptr)), csr.col_idx] = csr.vals
+    A = torch.from_numpy(A).cuda()
+    for j in range(0, N, 8192):   # small integers: every order of the sums is exact
+        assert torch.equal(C[:, j:j + 8192], A @ B[:, j:j + 8192].contiguous()), j
+    cols = np.r_[0:8, N - 8:N]
+    C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B[:, cols].contiguous().cpu().numpy())
+    assert np.array_equal(C[:, cols].cpu().numpy().astype(np.float64), C_ref)
