@@ -317,7 +317,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
 
 template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void launch(tile_args &a, hipStream_t s)
 {
-    a.n_tiles = (a.N + NB * R - 1) / (NB * R);
+    a.n_tiles = (int32_t)(((int64_t)a.N + NB * R - 1) / (NB * R));
     launch_places(spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>, a, 64 * W, s);
 }
 
@@ -514,7 +514,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
 
 template <int NB, int W, int AL, bool WIDE, int MINW> void launch_narrow(tile_args &a, hipStream_t s)
 {
-    a.n_tiles = (a.N + NB * 4 - 1) / (NB * 4);
+    a.n_tiles = (int32_t)(((int64_t)a.N + NB * 4 - 1) / (NB * 4));
     launch_places(spmm_narrow_tiles_kernel<NB, W, AL, WIDE, MINW>, a, 64 * W, s);
 }
 template <int NB, int W> void launch_narrow(tile_args &a, int loads, hipStream_t s)

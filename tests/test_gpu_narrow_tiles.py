@@ -80,3 +80,18 @@ def test_more_workgroups_than_one_launch_takes(torch_gpu, oracle):  # noqa: F811
     cols = np.r_[0:8, N - 8:N]
     C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B[:, cols].contiguous().cpu().numpy())
     assert np.array_equal(C[:, cols].cpu().numpy().astype(np.float64), C_ref)
+
+
+def test_as_many_columns_as_the_interface_counts(torch_gpu):  # noqa: F811
+    """N = 2^31 - 1: the number of column tiles is rounded up beyond 31 bits.  One row of A, so that
+    C is a sum of scaled rows of B; all of it is compared, a run of columns at a time."""
+    torch = torch_gpu
+    N = 2 ** 31 - 1
+    plan = spmm.plan_create(1, 2, np.array([0, 2]), np.array([0, 1]), np.array([3.0, -2.0]), tiles=8)
+    assert plan.describe()["tile_rows"] == 8
+    B = torch.empty((2, N), device="cuda")
+    for j in range(0, N, 1 << 28):
+        B[:, j:j + (1 << 28)] = torch.randint(-9, 10, B[:, j:j + (1 << 28)].shape, device="cuda", dtype=torch.int8)
+    C = plan.execute(B)
+    for j in range(0, N, 1 << 28):
+        assert torch.equal(C[0, j:j + (1 << 28)], 3 * B[0, j:j + (1 << 28)] - 2 * B[1, j:j + (1 << 28)]), j

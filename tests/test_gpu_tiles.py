@@ -122,3 +122,19 @@ def test_tiles_replay_from_a_graph_and_overlap_on_streams(torch_gpu, oracle):  #
         plan.execute(B)
         torch.cuda.synchronize()
     check(oracle, csr, B.cpu().numpy(), eager.cpu().numpy())
+
+
+@pytest.mark.parametrize("tiles", [16, 32])
+def test_as_many_columns_as_the_interface_counts(torch_gpu, tiles):  # noqa: F811
+    """N = 2^31 - 1: the number of column tiles is rounded up beyond 31 bits.  One row of A, so that
+    C is a sum of scaled rows of B; all of it is compared, a run of columns at a time."""
+    torch = torch_gpu
+    N = 2 ** 31 - 1
+    plan = spmm.plan_create(1, 2, np.array([0, 2]), np.array([0, 1]), np.array([3.0, -2.0]), tiles=tiles)
+    assert plan.describe()["tile_rows"] == tiles
+    B = torch.empty((2, N), device="cuda")
+    for j in range(0, N, 1 << 28):
+        B[:, j:j + (1 << 28)] = torch.randint(-9, 10, B[:, j:j + (1 << 28)].shape, device="cuda", dtype=torch.int8)
+    C = plan.execute(B)
+    for j in range(0, N, 1 << 28):
+        assert torch.equal(C[0, j:j + (1 << 28)], 3 * B[0, j:j + (1 << 28)] - 2 * B[1, j:j + (1 << 28)]), j
