@@ -31,7 +31,8 @@ constexpr int TILE_PLACE0 = 16;
 
 // Builds the tiles of A on the current device from host CSR arrays whose row pointer has been
 // checked; the columns are checked here.  Status codes follow spmm_status_t; TILES_NOT_POSSIBLE:
-// A cannot be stored this way (a column occurs twice in a row, more than 2^34 words of blocks).
+// A cannot be stored this way (a column occurs twice in a row, more than 2^34 words of blocks, or
+// 2^26 rows or blocks and more: the builder's launches).
 constexpr int TILES_NOT_POSSIBLE = -1;
 int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t rows,
                      TilePlan &out);

@@ -801,6 +801,13 @@ int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t
     const int64_t step = TILE_OPERANDS * 64 / rows;
     out.n_panels = (M + rows - 1) / rows;
     out.n_steps = (K + step - 1) / step;
+    // The builder runs a wave per row and per block and a workgroup per panel, 256 threads each; HIP takes
+    // fewer than 2^32 threads per launch.
+    constexpr int64_t MOST = ((int64_t)1 << 24) - 1;
+    if ((M + 3) / 4 > MOST || out.n_panels > MOST || (out.n_panels * out.n_steps + 3) / 4 > MOST) {
+        out = TilePlan();
+        return TILES_NOT_POSSIBLE;
+    }
     int status = 0;
     const hipError_t e = rows == NARROW_ROWS ? build<NARROW_ROWS>(M, K, row_ptr, col_idx, vals, out, status) : rows == 32 ? build<32>(M, K, row_ptr, col_idx, vals, out, status) : build<16>(M, K, row_ptr, col_idx, vals, out, status);
     if (e != hipSuccess) {

@@ -138,3 +138,18 @@ def test_as_many_columns_as_the_interface_counts(torch_gpu, tiles):  # noqa: F81
     C = plan.execute(B)
     for j in range(0, N, 1 << 28):
         assert torch.equal(C[0, j:j + (1 << 28)], 3 * B[0, j:j + (1 << 28)] - 2 * B[1, j:j + (1 << 28)]), j
+
+
+def test_more_rows_than_a_launch_of_the_builder_takes(torch_gpu):  # noqa: F811
+    """2^26 rows, one wave each, are one launch more than HIP takes: the matrix stays on chunks."""
+    torch = torch_gpu
+    M = (1 << 26) + 8
+    row_ptr = (np.arange(M + 1) + 63) // 64          # every 64th row has an entry
+    nnz = int(row_ptr[-1])
+    vals = (np.arange(nnz) % 64 - 31).astype(np.float32)
+    plan = spmm.plan_create(M, 1, row_ptr, np.zeros(nnz), vals, tiles=8)
+    assert plan.describe()["tile_rows"] == 0
+    C = plan.execute(torch.full((1, 1), 3.0, device="cuda"))
+    want = torch.zeros(M, device="cuda")
+    want[::64] = 3 * torch.from_numpy(vals).cuda()
+    assert torch.equal(C[:, 0], want)
