@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -110,30 +111,27 @@ bool row_pointer_ok(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t 
     return true;
 }
 
-void release_device(spmm_plan *p)
+struct plan_release {
+    void operator()(spmm_plan *p) const
+    {
+        bool held = p->tiles.rows > 0;
+        for (void *q : {(void *)p->d_stream, (void *)p->d_wins, (void *)p->d_items, (void *)p->d_rowmap, (void *)p->d_cross_sums,
+                        (void *)p->d_cross_table, (void *)p->d_slice_sums})
+            if (q) {
+                held = true;
+                (void)hipFree(q);
+            }
+        spmm_tiles_release(p->tiles);
+        if (held) (void)hipGetLastError();
+        delete p;
+    }
+};
+typedef std::unique_ptr<spmm_plan, plan_release> plan_owner;
+
+// spmm_plan_create_ex but for the exceptions of the host containers, which its caller turns into a status.
+spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx,
+                     const float *vals, const spmm_options_t *opts)
 {
-    if (p->d_stream) (void)hipFree(p->d_stream);
-    if (p->d_wins) (void)hipFree(p->d_wins);
-    if (p->d_items) (void)hipFree(p->d_items);
-    if (p->d_rowmap) (void)hipFree(p->d_rowmap);
-    if (p->d_cross_sums) (void)hipFree(p->d_cross_sums);
-    if (p->d_cross_table) (void)hipFree(p->d_cross_table);
-    if (p->d_slice_sums) (void)hipFree(p->d_slice_sums);
-    p->d_stream = p->d_wins = p->d_items = p->d_rowmap = p->d_cross_table = nullptr;
-    p->d_cross_sums = p->d_slice_sums = nullptr;
-    spmm_tiles_release(p->tiles);
-    (void)hipGetLastError();
-}
-
-}  // namespace
-
-extern "C" {
-
-spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, const int32_t *row_ptr,
-                                  const int32_t *col_idx, const float *vals, const spmm_options_t *opts)
-{
-    if (!plan) return SPMM_ERR_INVALID_ARG;
-    *plan = nullptr;
     InspectorOptions io;
     bool host_only = false, force_wide = false, probe = false, schedule_forced = false;
     int depth = 0, tiles = 0;
@@ -170,8 +168,8 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
                           opts->ufk || probe || opts->kslices;
         if (probe && (force_wide || depth != 0 || (io.ufk != 0 && io.ufk > 16))) return SPMM_ERR_INVALID_ARG;
     }
-    spmm_plan *p = new (std::nothrow) spmm_plan();
-    if (!p) return SPMM_ERR_ALLOC;
+    plan.reset(new spmm_plan());
+    spmm_plan *p = plan.get();
     int rc = 0;
     if (!host_only && tiles >= 0 && (tiles > 0 || !schedule_forced) && row_pointer_ok(M, K, row_ptr, col_idx, vals)) {
         if (tiles == 0) tiles = choose_tiles(M, K, row_ptr, io.n_hint);
@@ -182,20 +180,12 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
         }
     }
     if (rc == 0) rc = spmm_inspect(M, K, row_ptr, col_idx, vals, io, p->host);
-    if (rc != 0) {
-        release_device(p);
-        delete p;
-        return (spmm_status_t)rc;
-    }
+    if (rc != 0) return (spmm_status_t)rc;
     p->force_wide = force_wide;
     p->depth = depth;
     p->probe = probe;
     if (!host_only) {
-        if (hipGetDevice(&p->device) != hipSuccess) {
-            release_device(p);
-            delete p;
-            return hip_fail();
-        }
+        if (hipGetDevice(&p->device) != hipSuccess) return hip_fail();
         const HostPlan &h = p->host;
         spmm_status_t st = SPMM_OK;
         if (p->tiles.rows > 0) {
@@ -224,11 +214,7 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
             p->scratch_bytes += p->device_bytes - before;
         }
         }
-        if (st != SPMM_OK) {
-            release_device(p);
-            delete p;
-            return st;
-        }
+        if (st != SPMM_OK) return st;
         p->on_device = true;
     }
     p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : (int64_t)p->host.stream.size();
@@ -244,8 +230,28 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
         std::vector<uint32_t>().swap(p->host.items);
         // the row map stays: one bit of it (sorted or not) is part of the description
     }
-    *plan = p;
     return SPMM_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, const int32_t *row_ptr,
+                                  const int32_t *col_idx, const float *vals, const spmm_options_t *opts)
+{
+    if (!plan) return SPMM_ERR_INVALID_ARG;
+    *plan = nullptr;
+    try {
+        plan_owner made;  // gives back what it holds unless it is handed over
+        const spmm_status_t st = create(made, M, K, row_ptr, col_idx, vals, opts);
+        if (st == SPMM_OK) *plan = made.release();
+        return st;
+    } catch (const std::bad_alloc &) {
+        return SPMM_ERR_ALLOC;
+    } catch (...) {  // length errors of the containers and the like
+        return SPMM_ERR_UNSUPPORTED;
+    }
 }
 
 spmm_status_t spmm_plan_create(spmm_plan_t **plan, int64_t M, int64_t K, const int32_t *row_ptr,
@@ -397,8 +403,7 @@ spmm_status_t spmm_execute_static(const spmm_plan_t *plan, const float *B, int32
 spmm_status_t spmm_plan_destroy(spmm_plan_t *plan)
 {
     if (!plan) return SPMM_OK;
-    if (plan->on_device) release_device(plan);
-    delete plan;
+    plan_release()(plan);
     return SPMM_OK;
 }
 

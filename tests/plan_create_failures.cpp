@@ -1,0 +1,189 @@
+// Plan creation where memory runs out: run by tests/test_plan_create_failures.py, which compiles this file
+// together with the library's host sources.  The HIP runtime and the kernels' entry points are stand-ins in
+// host memory, so every allocation can be made to fail in turn, also those a plan makes on a device.
+#include <hip/hip_runtime_api.h>
+
+#include <atomic>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <new>
+#include <vector>
+
+#include "spmm.h"
+#include "spmm_kernels.h"
+#include "spmm_tiles.h"
+
+// ---- host memory: allocation number `fail_at` fails, and everything is counted
+
+static std::atomic<long> made{0}, fail_at{-1}, host_live{0};
+
+void *operator new(size_t n)
+{
+    if (fail_at >= 0 && made++ == fail_at) throw std::bad_alloc();
+    void *p = std::malloc(n ? n : 1);
+    if (!p) throw std::bad_alloc();
+    ++host_live;
+    return p;
+}
+void operator delete(void *p) noexcept
+{
+    if (!p) return;
+    --host_live;
+    std::free(p);
+}
+void operator delete(void *p, size_t) noexcept { operator delete(p); }
+
+// ---- device memory
+
+static long device_live = 0, device_made = 0, device_fail_at = -1;
+
+extern "C" {
+hipError_t hipMalloc(void **p, size_t n)
+{
+    if (device_made++ == device_fail_at) return hipErrorOutOfMemory;
+    *p = std::malloc(n);
+    ++device_live;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    --device_live;
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind)
+{
+    std::memcpy(dst, src, n);
+    return hipSuccess;
+}
+hipError_t hipMemset(void *p, int v, size_t n)
+{
+    std::memset(p, v, n);
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d)
+{
+    *d = 0;
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+}
+
+// ---- the device sources' entry points
+
+static int tiles_status = 0;      // what the builder of tiles answers
+static double tiles_time = 1e9;   // its estimate of a product's time
+
+int spmm_launch_chunks(const spmm_launch_args &, int, int, int, bool, int, void *) { return 0; }
+int spmm_static_scratch(float **, size_t *) { return 1; }
+int spmm_tiles_execute(const TilePlan &, int64_t, int64_t, const float *, int32_t, float *, void *) { return 0; }
+double spmm_tiles_time(int, int64_t, int64_t, int64_t, double, double, int *) { return tiles_time; }
+int spmm_tiles_build(int64_t, int64_t, const int32_t *, const int32_t *, const float *, int32_t rows, TilePlan &out)
+{
+    out = TilePlan();
+    if (tiles_status != 0) return tiles_status;
+    out.rows = rows;
+    return hipMalloc(reinterpret_cast<void **>(&out.d_stream), 64) == hipSuccess ? 0 : 3;
+}
+void spmm_tiles_release(TilePlan &p)
+{
+    if (p.d_stream) (void)hipFree(p.d_stream);
+    p = TilePlan();
+}
+
+// ---- inputs
+
+struct csr {
+    int64_t M, K;
+    std::vector<int32_t> row_ptr{0}, col_idx;
+    std::vector<float> vals;
+};
+
+// Every `step`-th column of a row; the first `heavy` rows hold four times as many entries.
+static csr matrix(int64_t M, int64_t K, int step, int heavy)
+{
+    csr a{M, K};
+    for (int64_t i = 0; i < M; ++i) {
+        const int s = i < heavy ? step / 4 : step;
+        for (int64_t c = i % s; c < K; c += s) {
+            a.col_idx.push_back((int32_t)c);
+            a.vals.push_back((float)(c % 7) - 3.0f);
+        }
+        a.row_ptr.push_back((int32_t)a.col_idx.size());
+    }
+    return a;
+}
+
+static spmm_status_t create(const csr &a, const spmm_options_t &o, spmm_plan_t **p)
+{
+    return spmm_plan_create_ex(p, a.M, a.K, a.row_ptr.data(), a.col_idx.data(), a.vals.data(), &o);
+}
+
+#define REQUIRE(x) do { if (!(x)) { std::printf("%s:%d: %s\n", __FILE__, __LINE__, #x); std::exit(1); } } while (0)
+
+// Lets allocation after allocation fail, host and device, until a creation comes through: each failure has to
+// be reported as one and leave nothing behind.
+static void fail_in_turn(const char *name, const csr &a, const spmm_options_t &o)
+{
+    spmm_plan_t *p = nullptr;
+    REQUIRE(create(a, o, &p) == SPMM_OK);
+    REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+    for (int on_device = 0; on_device < 2; ++on_device) {
+        long tried = 0, refused = 0;
+        for (long n = 0;; ++n) {
+            const long host_before = host_live, device_before = device_live;
+            p = nullptr;
+            made = 0;
+            device_made = 0;
+            fail_at = on_device ? -1 : n;
+            device_fail_at = on_device ? n : -1;
+            const spmm_status_t st = create(a, o, &p);
+            fail_at = -1;
+            device_fail_at = -1;
+            const bool reached = on_device ? device_made > n : made > n;
+            ++tried;
+            REQUIRE(st == SPMM_OK || (st == SPMM_ERR_ALLOC && p == nullptr && reached));
+            refused += st != SPMM_OK;
+            REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+            REQUIRE(host_live == host_before && device_live == device_before);
+            if (!reached) break;
+        }
+        std::printf("%s: %ld %s allocations made to fail, %ld creations refused\n", name, tried - 1, on_device ? "device" : "host", refused);
+    }
+}
+
+int main()
+{
+    spmm_options_t o;
+    const csr dense = matrix(300, 1000, 2, 0);
+    {   // the choice between chunks and tiles, one thread
+        std::memset(&o, 0, sizeof o);
+        o.threads = 1;
+        fail_in_turn("chunks", dense, o);
+        tiles_time = 0.0;
+        spmm_plan_t *p = nullptr;
+        spmm_plan_info_t info;
+        REQUIRE(create(dense, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.tile_rows > 0);
+        REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+        fail_in_turn("tiles", dense, o);
+        tiles_time = 1e9;
+    }
+    {   // a compute unit held to two workgroups (more than 512 of them)
+        const csr uneven = matrix(1090, 2048, 16, 40);
+        std::memset(&o, 0, sizeof o);
+        o.threads = 1;
+        o.n_hint = 64;
+        o.ufi = 1;
+        o.group_nnz = 32;
+        spmm_plan_t *p = nullptr;
+        spmm_plan_info_t info;
+        REQUIRE(create(uneven, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK);
+        std::printf("%lld workgroups\n", (long long)info.n_blocks);
+        REQUIRE(info.n_blocks > 512 && info.n_blocks <= 640);
+        REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+        fail_in_turn("held to two", uneven, o);
+    }
+    std::printf("ok\n");
+    return 0;
+}
