@@ -18,7 +18,6 @@
 #include <cstring>
 #include <new>
 #include <numeric>
-#include <system_error>
 #include <thread>
 
 #include "spmm_format.h"
@@ -453,8 +452,8 @@ template <typename F> void over_rows(const int32_t *row_ptr, int64_t M, int thre
     for (int t = 1; t < threads; ++t) {
         try {
             others.emplace_back([=, &job] { job(bound(t), bound(t + 1), t); });
-        } catch (const std::system_error &) {
-            job(bound(t), bound(t + 1), t);  // no thread to be had
+        } catch (...) {
+            job(bound(t), bound(t + 1), t);  // no thread or no memory for one to be had; the others still have to be joined
         }
     }
     job(bound(0), bound(1), 0);
@@ -873,8 +872,8 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
             for (size_t t = 0; t < n_ranges; ++t) {
                 try {
                     workers.emplace_back(job, t);
-                } catch (const std::system_error &) {
-                    job(t);  // no thread to be had: this one does the range itself
+                } catch (...) {
+                    job(t);  // no thread or no memory for one to be had: this one does the range itself
                 }
             }
             for (std::thread &w : workers) w.join();
@@ -1162,7 +1161,7 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
                 for (int t = 0; t < want; ++t) {
                     try {
                         workers.emplace_back(fill_range, from[(size_t)t], from[(size_t)t + 1]);
-                    } catch (const std::system_error &) {
+                    } catch (...) {
                         fill_range(from[(size_t)t], from[(size_t)t + 1]);
                     }
                 }

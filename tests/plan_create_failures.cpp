@@ -184,6 +184,14 @@ int main()
         REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
         fail_in_turn("held to two", uneven, o);
     }
+    {   // several threads: their handles and their states are allocations too
+        std::memset(&o, 0, sizeof o);
+        o.threads = 4;
+        fail_in_turn("four threads", dense, o);
+        o.kslices = 4;
+        o.sort_rows = 1;
+        fail_in_turn("four threads, column ranges", matrix(300, 1000, 8, 20), o);
+    }
     std::printf("ok\n");
     return 0;
 }
