@@ -132,8 +132,9 @@ typedef struct {
                               matrices that are not very sparse.  8, 16 or 32 = use it with panels of so
                               many rows (8 for B of up to 16 columns); < 0 = never; 0 = choose by shape, density and n_hint (never when
                               another setting but n_hint and threads is given, never for host-only
-                              plans).  A matrix with a column stored twice in a row or with 2^26 rows
-                              or more stays on chunks. */
+                              plans).  A matrix with a column stored twice in a row, with 2^26 rows or
+                              more, or whose tiles find no room on the device while they are built
+                              stays on chunks. */
 } spmm_options_t;
 
 /*

@@ -175,7 +175,8 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (tiles == 0) tiles = choose_tiles(M, K, row_ptr, io.n_hint);
         if (tiles > 0) {
             rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
-            if (rc == TILES_NOT_POSSIBLE) rc = 0;
+            // the chunk plan needs no memory beside its own, the builder of tiles a multiple of its result's
+            if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) rc = 0;
             io.schedule_only = p->tiles.rows > 0;
         }
     }

@@ -167,6 +167,19 @@ int main()
         REQUIRE(create(dense, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.tile_rows > 0);
         REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
         fail_in_turn("tiles", dense, o);
+        // no room for the tiles: chunks, also where tiles were asked for
+        tiles_status = SPMM_ERR_ALLOC;
+        for (int asked : {0, 16}) {
+            o.tiles = asked;
+            REQUIRE(create(dense, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK);
+            REQUIRE(info.tile_rows == 0 && info.device_bytes > 0 && info.stream_words > 0);
+            REQUIRE(spmm_plan_destroy(p) == SPMM_OK && device_live == 0);
+        }
+        for (int status : {SPMM_ERR_HIP, SPMM_ERR_INVALID_CSR}) {  // anything else is reported
+            tiles_status = status;
+            REQUIRE(create(dense, o, &p) == (spmm_status_t)status && p == nullptr && device_live == 0);
+        }
+        tiles_status = 0;
         tiles_time = 1e9;
     }
     {   // a compute unit held to two workgroups (more than 512 of them)
