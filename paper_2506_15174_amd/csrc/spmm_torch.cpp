@@ -13,9 +13,12 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <stdint.h>
+
+#include <exception>
 
 #include "../../include/spmm.h"
 
@@ -74,8 +77,8 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         if (args[4] == Py_None) return THPVariable_Wrap(std::move(made));
         Py_INCREF(args[4]);
         return args[4];
-    } catch (const std::exception &e) {  // e.g. no memory for the output
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {  // as torch's own functions report it, e.g. torch.OutOfMemoryError for the output
+        torch::translate_exception_to_python(std::current_exception());
         return nullptr;
     }
 }
