@@ -24,6 +24,13 @@
 
 namespace {
 
+// Lets other Python threads run: an allocation may have to free and wait, a launch waits while its queue is
+// full.  (Handing the interpreter over and back costs 0.05 us where no other thread wants it.)
+struct others_run {
+    PyThreadState *state = PyEval_SaveThread();
+    ~others_run() { PyEval_RestoreThread(state); }
+};
+
 // execute(plan address, M, K, B, C or None, stream or None) -> C, or the status code as int
 PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
 {
@@ -39,7 +46,7 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         return nullptr;
     }
     try {
-        const at::Tensor &B = THPVariable_Unpack(args[3]);
+        const at::Tensor B = THPVariable_Unpack(args[3]);  // kept alive while other threads run
         if (!(B.is_cuda() && B.scalar_type() == at::kFloat && B.is_contiguous() && B.dim() == 2)) {
             PyErr_SetString(PyExc_ValueError, "B must be a contiguous 2-D float32 device tensor");
             return nullptr;
@@ -53,13 +60,14 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             PyErr_SetString(PyExc_ValueError, "B has more columns than the library's 32-bit column count");
             return nullptr;
         }
-        at::Tensor made;
-        if (args[4] == Py_None) made = at::empty({M, N}, B.options().requires_grad(false));
-        const at::Tensor &C = args[4] == Py_None ? made : THPVariable_Unpack(args[4]);
-        if (!(C.is_cuda() && C.scalar_type() == at::kFloat && C.is_contiguous() && C.dim() == 2 && C.size(0) == M &&
-              C.size(1) == N)) {
-            PyErr_SetString(PyExc_ValueError, "C must be a contiguous float32 device tensor of shape (M, N)");
-            return nullptr;
+        const bool given = args[4] != Py_None;
+        if (given) {
+            const at::Tensor &C = THPVariable_Unpack(args[4]);
+            if (!(C.is_cuda() && C.scalar_type() == at::kFloat && C.is_contiguous() && C.dim() == 2 && C.size(0) == M &&
+                  C.size(1) == N)) {
+                PyErr_SetString(PyExc_ValueError, "C must be a contiguous float32 device tensor of shape (M, N)");
+                return nullptr;
+            }
         }
         void *stream;
         if (args[5] == Py_None) {
@@ -71,10 +79,15 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             Py_DECREF(s);
             if (PyErr_Occurred()) return nullptr;
         }
-        const spmm_status_t st =
-            spmm_execute(plan, static_cast<const float *>(B.const_data_ptr()), (int32_t)N, static_cast<float *>(C.data_ptr()), stream);
+        at::Tensor C = given ? THPVariable_Unpack(args[4]) : at::Tensor();
+        spmm_status_t st;
+        {
+            others_run free_to_run;
+            if (!given) C = at::empty({M, N}, B.options().requires_grad(false));
+            st = spmm_execute(plan, static_cast<const float *>(B.const_data_ptr()), (int32_t)N, static_cast<float *>(C.data_ptr()), stream);
+        }
         if (st != SPMM_OK) return PyLong_FromLong((long)st);
-        if (args[4] == Py_None) return THPVariable_Wrap(std::move(made));
+        if (!given) return THPVariable_Wrap(std::move(C));
         Py_INCREF(args[4]);
         return args[4];
     } catch (...) {  // as torch's own functions report it, e.g. torch.OutOfMemoryError for the output

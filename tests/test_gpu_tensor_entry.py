@@ -1,4 +1,8 @@
 """The native tensor-level entry behind Plan.execute (GPU machine only)."""
+import sys
+import threading
+import time
+
 import numpy as np
 import pytest
 
@@ -22,3 +26,37 @@ def test_no_memory_for_the_output_is_torchs_own_error(torch_gpu):  # noqa: F811
     with pytest.raises(torch.cuda.OutOfMemoryError):
         plan.execute(B)
     assert torch.equal(plan.execute(B[:, :4].contiguous()), torch.ones((1 << 20, 4), device="cuda"))
+
+
+def test_other_threads_run_during_a_call(torch_gpu):  # noqa: F811
+    """With the interpreter's own switching out of the way, another thread comes to run only where a call
+    lets go of the interpreter."""
+    torch = torch_gpu
+    plan = one_column_plan(256)
+    B = torch.ones((1, 32), device="cuda")
+    C = plan.execute(B)
+    ready, stop, turns = threading.Event(), threading.Event(), [0]
+
+    def other():
+        ready.set()
+        while not stop.is_set():
+            turns[0] += 1
+            time.sleep(0)   # hand the interpreter back
+
+    interval = sys.getswitchinterval()
+    thread = threading.Thread(target=other)
+    thread.start()
+    ready.wait()
+    sys.setswitchinterval(1000.0)
+    try:
+        ran = 0
+        for out in [C, None] * 2000:
+            before = turns[0]
+            plan.execute(B, out)
+            ran += turns[0] != before
+    finally:
+        sys.setswitchinterval(interval)
+        stop.set()
+        thread.join()
+        torch.cuda.synchronize()
+    assert ran > 0
