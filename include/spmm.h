@@ -159,6 +159,9 @@ typedef struct {
  * The three arrays are only read during the call; the caller may free them when
  * it returns.  The plan owns its device memory on the device that is current at
  * the time of the call.
+ * Uploads are ordered behind the work of the default stream; work on other streams
+ * goes on meanwhile and is not waited for.  When the call returns, every stream may
+ * execute the plan.
  */
 spmm_status_t spmm_plan_create(spmm_plan_t **plan, int64_t M, int64_t K,
                                const int32_t *row_ptr, const int32_t *col_idx,

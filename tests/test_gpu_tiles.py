@@ -153,3 +153,33 @@ def test_more_rows_than_a_launch_of_the_builder_takes(torch_gpu):  # noqa: F811
     want = torch.zeros(M, device="cuda")
     want[::64] = 3 * torch.from_numpy(vals).cuda()
     assert torch.equal(C[:, 0], want)
+
+
+def test_a_plan_is_created_while_another_stream_works(torch_gpu, oracle):  # noqa: F811
+    """Building tiles waits for the builder's own work only, and its working memory goes back to the device."""
+    torch = torch_gpu
+    csr = gen.uniform_positions(1024, 1024, 0.5, 13)
+    B = gen.dense_activations(csr.K, 64, 14)
+    C, plan = gpu_product(torch, csr, B, tiles=16)   # everything is loaded
+    plan.destroy()
+    start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    start.record()
+    torch.cuda._sleep(1000000)
+    end.record()
+    torch.cuda.synchronize()
+    cycles = int(1000000 * 200.0 / start.elapsed_time(end))   # 200 ms
+    side, done = torch.cuda.Stream(), torch.cuda.Event()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(1000)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        torch.cuda._sleep(cycles)
+        done.record()
+    plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=16)
+    assert not done.query(), "the creation waited for the other stream"
+    assert plan.describe()["tile_rows"] == 16
+    assert free - torch.cuda.mem_get_info()[0] <= plan.describe()["device_bytes"] + (4 << 20)
+    dC = plan.execute(torch.from_numpy(B).cuda())
+    assert np.array_equal(dC.cpu().numpy(), C)
+    check(oracle, csr, B, C)
+    side.synchronize()
