@@ -192,28 +192,25 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (p->tiles.rows > 0) {
             p->device_bytes = p->tiles.device_bytes;
         } else {
-        if (st == SPMM_OK) st = upload(&p->d_stream, h.stream.data(), h.stream.size() * 4, p->device_bytes);
-        if (st == SPMM_OK) st = upload(&p->d_wins, h.wins.data(), h.wins.size() * 4, p->device_bytes);
-        if (st == SPMM_OK) st = upload(&p->d_items, h.items.data(), h.items.size() * 4, p->device_bytes);
-        if (st == SPMM_OK) st = upload(&p->d_rowmap, h.rowmap.data(), h.rowmap.size() * 4, p->device_bytes);
-        if (st == SPMM_OK && h.n_cross_slots > 0) {
-            const size_t slots = (size_t)h.n_cross_slots * CROSS_MAX_TILES;
-            int64_t before = p->device_bytes;
-            st = upload(&p->d_cross_sums, nullptr, slots * (size_t)h.ufi * CROSS_ROW_FLOATS * sizeof(float), p->device_bytes);
-            p->scratch_bytes = p->device_bytes - before;
+            // Scratch first: hipMemset may return before it is done, the copies behind it do not.
+            if (h.n_cross_slots > 0) {
+                const size_t slots = (size_t)h.n_cross_slots * CROSS_MAX_TILES;
+                st = upload(&p->d_cross_sums, nullptr, slots * (size_t)h.ufi * CROSS_ROW_FLOATS * sizeof(float), p->device_bytes);
+                // set-up for spmm_execute_static: this device's address of the static scratch is looked up here,
+                // once, so that the entry point itself finds it ready (a failure only matters to that entry point)
+                float *unused = nullptr;
+                size_t unused_bytes = 0;
+                if (spmm_static_scratch(&unused, &unused_bytes) != 0) (void)hipGetLastError();
+            }
+            if (st == SPMM_OK && h.k_slices > 1)
+                st = upload(&p->d_slice_sums, nullptr, (size_t)h.plan_rows * KSLICE_COLS * sizeof(float), p->device_bytes);
+            p->scratch_bytes = p->device_bytes;
+            if (st == SPMM_OK) st = upload(&p->d_rowmap, h.rowmap.data(), h.rowmap.size() * 4, p->device_bytes);
             if (st == SPMM_OK) st = upload(&p->d_cross_table, h.cross.data(), h.cross.size() * 4, p->device_bytes);
-            // set-up for spmm_execute_static: this device's address of the static scratch is looked up here,
-            // once, so that the entry point itself finds it ready (a failure only matters to that entry point)
-            float *unused = nullptr;
-            size_t unused_bytes = 0;
-            if (spmm_static_scratch(&unused, &unused_bytes) != 0) (void)hipGetLastError();
-        }
-        if (h.k_slices == 1 && win_words(h.ufk) == WIN_WORDS && hold_to_two(h)) p->lds_pad = 48u << 10;  // 32 KiB and these: half of a unit's LDS
-        if (st == SPMM_OK && h.k_slices > 1) {
-            int64_t before = p->device_bytes;
-            st = upload(&p->d_slice_sums, nullptr, (size_t)h.plan_rows * KSLICE_COLS * sizeof(float), p->device_bytes);
-            p->scratch_bytes += p->device_bytes - before;
-        }
+            if (st == SPMM_OK) st = upload(&p->d_stream, h.stream.data(), h.stream.size() * 4, p->device_bytes);
+            if (st == SPMM_OK) st = upload(&p->d_wins, h.wins.data(), h.wins.size() * 4, p->device_bytes);
+            if (st == SPMM_OK) st = upload(&p->d_items, h.items.data(), h.items.size() * 4, p->device_bytes);
+            if (h.k_slices == 1 && win_words(h.ufk) == WIN_WORDS && hold_to_two(h)) p->lds_pad = 48u << 10;  // 32 KiB and these: half of a unit's LDS
         }
         if (st != SPMM_OK) return st;
         p->on_device = true;

@@ -37,6 +37,7 @@ void operator delete(void *p, size_t) noexcept { operator delete(p); }
 // ---- device memory
 
 static long device_live = 0, device_made = 0, device_fail_at = -1;
+static bool memset_pending = false;  // hipMemset may return early; copies from the host do not
 
 extern "C" {
 hipError_t hipMalloc(void **p, size_t n)
@@ -55,11 +56,13 @@ hipError_t hipFree(void *p)
 hipError_t hipMemcpy(void *dst, const void *src, size_t n, hipMemcpyKind)
 {
     std::memcpy(dst, src, n);
+    memset_pending = false;
     return hipSuccess;
 }
 hipError_t hipMemset(void *p, int v, size_t n)
 {
     std::memset(p, v, n);
+    memset_pending = true;
     return hipSuccess;
 }
 hipError_t hipGetDevice(int *d)
@@ -128,6 +131,7 @@ static void fail_in_turn(const char *name, const csr &a, const spmm_options_t &o
 {
     spmm_plan_t *p = nullptr;
     REQUIRE(create(a, o, &p) == SPMM_OK);
+    REQUIRE(!memset_pending);  // any stream may execute the plan now
     REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
     for (int on_device = 0; on_device < 2; ++on_device) {
         long tried = 0, refused = 0;
@@ -204,6 +208,10 @@ int main()
         o.kslices = 4;
         o.sort_rows = 1;
         fail_in_turn("four threads, column ranges", matrix(300, 1000, 8, 20), o);
+        o.kslices = 0;
+        o.cross = 1;
+        o.group_nnz = 16;
+        fail_in_turn("four threads, panels across workgroups", matrix(300, 1000, 8, 20), o);
     }
     std::printf("ok\n");
     return 0;
