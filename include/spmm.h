@@ -18,6 +18,7 @@
 #ifndef SPMM_CDNA4_H
 #define SPMM_CDNA4_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -35,6 +36,12 @@ typedef enum {
     SPMM_ERR_HIP = 4,         /* any other HIP runtime failure (sticky error cleared) */
     SPMM_ERR_UNSUPPORTED = 5  /* size outside the index range of the kernels */
 } spmm_status_t;
+
+/*
+ * The two structures below grow at their end only, and every call that takes one is told
+ * its caller's size of it (see spmm_plan_create_sized), so that a program keeps working with a
+ * library that knows more fields than its own header, or fewer.
+ */
 
 /* Schedule constants and sizes of a plan (all read-only facts). */
 typedef struct {
@@ -172,10 +179,22 @@ spmm_status_t spmm_plan_create(spmm_plan_t **plan, int64_t M, int64_t K,
  * Same, with explicit settings (opts may be NULL = all zero).  The settings are
  * the only way to steer the inspector: the library reads no environment
  * variable.
+ *
+ * opts_bytes is the caller's sizeof(spmm_options_t): fields that lie behind it are
+ * zero; of a larger structure than the library's own the rest must be zero
+ * (else SPMM_ERR_UNSUPPORTED).  spmm_plan_create_ex is this call with the size
+ * filled in.  (The function of that name, for programs compiled before it became a
+ * macro, reads the options up to and including kslices.)
  */
+spmm_status_t spmm_plan_create_sized(spmm_plan_t **plan, int64_t M, int64_t K,
+                                     const int32_t *row_ptr, const int32_t *col_idx,
+                                     const float *vals, const spmm_options_t *opts,
+                                     size_t opts_bytes);
 spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K,
                                   const int32_t *row_ptr, const int32_t *col_idx,
                                   const float *vals, const spmm_options_t *opts);
+#define spmm_plan_create_ex(plan, M, K, row_ptr, col_idx, vals, opts) \
+    spmm_plan_create_sized(plan, M, K, row_ptr, col_idx, vals, opts, sizeof(spmm_options_t))
 
 /*
  * Executor (paper Section 3.3 "Sparse Coarsen", Listings 5-7): C <- A x B.
@@ -241,8 +260,16 @@ spmm_status_t spmm_execute_static(const spmm_plan_t *plan, const float *B, int32
 /* Frees the plan and its device memory.  NULL is a no-op returning SPMM_OK. */
 spmm_status_t spmm_plan_destroy(spmm_plan_t *plan);
 
-/* Read-only introspection: schedule constants and sizes. */
+/*
+ * Read-only introspection: schedule constants and sizes.  out_bytes is the caller's
+ * sizeof(spmm_plan_info_t): so many bytes of *out are written, zeros where the library
+ * knows fewer fields.  spmm_plan_describe is this call with the size filled in.  (The
+ * function of that name, for programs compiled before it became a macro, writes the
+ * fields up to and including slice_cols.)
+ */
+spmm_status_t spmm_plan_describe_sized(const spmm_plan_t *plan, spmm_plan_info_t *out, size_t out_bytes);
 spmm_status_t spmm_plan_describe(const spmm_plan_t *plan, spmm_plan_info_t *out);
+#define spmm_plan_describe(plan, out) spmm_plan_describe_sized(plan, out, sizeof(spmm_plan_info_t))
 
 /*
  * Row groups in launch order, five int32 each:

@@ -23,8 +23,8 @@ SPMM_ERR_UNSUPPORTED = 5
 
 ARRAY_HDR, ARRAY_STREAM, ARRAY_WINS, ARRAY_ITEMS, ARRAY_ROWMAP, ARRAY_CROSS = 0, 1, 2, 3, 4, 5
 
-EXPORTS = ("spmm_plan_create", "spmm_plan_create_ex", "spmm_execute", "spmm_execute_static",
-           "spmm_plan_destroy", "spmm_plan_describe", "spmm_plan_get_groups",
+EXPORTS = ("spmm_plan_create", "spmm_plan_create_ex", "spmm_plan_create_sized", "spmm_execute", "spmm_execute_static",
+           "spmm_plan_destroy", "spmm_plan_describe", "spmm_plan_describe_sized", "spmm_plan_get_groups",
            "spmm_plan_get_array", "spmm_status_string")
 
 
@@ -82,17 +82,17 @@ def load():
     vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
     lib.spmm_plan_create.restype = ctypes.c_int
     lib.spmm_plan_create.argtypes = [ctypes.POINTER(vp), i64, i64, vp, vp, vp]
-    lib.spmm_plan_create_ex.restype = ctypes.c_int
-    lib.spmm_plan_create_ex.argtypes = [ctypes.POINTER(vp), i64, i64, vp, vp, vp,
-                                        ctypes.POINTER(Options)]
+    lib.spmm_plan_create_sized.restype = ctypes.c_int
+    lib.spmm_plan_create_sized.argtypes = [ctypes.POINTER(vp), i64, i64, vp, vp, vp,
+                                           ctypes.POINTER(Options), ctypes.c_size_t]
     lib.spmm_execute.restype = ctypes.c_int
     lib.spmm_execute.argtypes = [vp, vp, i32, vp, vp]
     lib.spmm_execute_static.restype = ctypes.c_int
     lib.spmm_execute_static.argtypes = [vp, vp, i32, vp, vp]
     lib.spmm_plan_destroy.restype = ctypes.c_int
     lib.spmm_plan_destroy.argtypes = [vp]
-    lib.spmm_plan_describe.restype = ctypes.c_int
-    lib.spmm_plan_describe.argtypes = [vp, ctypes.POINTER(PlanInfo)]
+    lib.spmm_plan_describe_sized.restype = ctypes.c_int
+    lib.spmm_plan_describe_sized.argtypes = [vp, ctypes.POINTER(PlanInfo), ctypes.c_size_t]
     lib.spmm_plan_get_groups.restype = ctypes.c_int
     lib.spmm_plan_get_groups.argtypes = [vp, vp, i64]
     lib.spmm_plan_get_array.restype = ctypes.c_int
@@ -135,7 +135,7 @@ class Plan:
     def describe(self):
         if self._info is None:  # a plan is immutable: ask once
             info = PlanInfo()
-            _check(load().spmm_plan_describe(self._h, ctypes.byref(info)), "spmm_plan_describe")
+            _check(load().spmm_plan_describe_sized(self._h, ctypes.byref(info), ctypes.sizeof(info)), "spmm_plan_describe")
             self._info = info.as_dict()
         return dict(self._info)
 
@@ -194,7 +194,7 @@ class Plan:
 def plan_create(M, K, row_ptr, col_idx, vals, group_nnz=0, group_panels=0, host_only=False, ufi=0,
                 n_hint=0, sort_rows=0, force_wide=False, threads=0, depth=0, cross=0, ufk=0, probe=False,
                 kslices=0, tiles=0):
-    """spmm_plan_create / spmm_plan_create_ex on numpy host arrays."""
+    """spmm_plan_create / spmm_plan_create_sized on numpy host arrays."""
     row_ptr = np.ascontiguousarray(row_ptr, dtype=np.int32)
     col_idx = np.ascontiguousarray(col_idx, dtype=np.int32)
     vals = np.ascontiguousarray(vals, dtype=np.float32)
@@ -205,8 +205,8 @@ def plan_create(M, K, row_ptr, col_idx, vals, group_nnz=0, group_panels=0, host_
         opts = Options(int(group_nnz), int(group_panels), 1 if host_only else 0, int(ufi), int(n_hint),
                        int(sort_rows), 1 if force_wide else 0, int(threads), int(depth), int(cross), int(ufk), 1 if probe else 0,
                        int(kslices), int(tiles))
-        st = lib.spmm_plan_create_ex(ctypes.byref(handle), int(M), int(K), _ptr(row_ptr),
-                                     _ptr(col_idx), _ptr(vals), ctypes.byref(opts))
+        st = lib.spmm_plan_create_sized(ctypes.byref(handle), int(M), int(K), _ptr(row_ptr),
+                                        _ptr(col_idx), _ptr(vals), ctypes.byref(opts), ctypes.sizeof(opts))
     else:
         st = lib.spmm_plan_create(ctypes.byref(handle), int(M), int(K), _ptr(row_ptr),
                                   _ptr(col_idx), _ptr(vals))

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <cstring>
 #include <memory>
 #include <new>
@@ -128,46 +129,44 @@ struct plan_release {
 };
 typedef std::unique_ptr<spmm_plan, plan_release> plan_owner;
 
-// spmm_plan_create_ex but for the exceptions of the host containers, which its caller turns into a status.
+// spmm_plan_create_sized but for the exceptions of the host containers, which its caller turns into a status.
 spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx,
-                     const float *vals, const spmm_options_t *opts)
+                     const float *vals, const spmm_options_t &opts)
 {
     InspectorOptions io;
     bool host_only = false, force_wide = false, probe = false, schedule_forced = false;
     int depth = 0, tiles = 0;
-    if (opts) {
-        if (opts->group_nnz < 0 || opts->group_panels < 0 || opts->n_hint < 0) return SPMM_ERR_INVALID_ARG;
-        if (opts->ufi != 0 && opts->ufi != 1 && opts->ufi != 2 && opts->ufi != 4 && opts->ufi != 8)
-            return SPMM_ERR_INVALID_ARG;
-        if (opts->threads < 0 || opts->threads > 64) return SPMM_ERR_INVALID_ARG;
-        if (opts->depth != 0 && opts->depth != 1 && opts->depth != 2 && opts->depth != 3 && opts->depth != 4 &&
-            opts->depth != 8)
-            return SPMM_ERR_INVALID_ARG;
-        io.ufi = opts->ufi;
-        io.group_nnz = opts->group_nnz;
-        io.group_panels = opts->group_panels;
-        host_only = opts->host_only != 0;
-        io.n_hint = opts->n_hint;
-        io.sort_rows = opts->sort_rows;
-        io.threads = opts->threads;
-        io.cross = opts->cross;
-        if (opts->kslices != 0 && opts->kslices != 1 && opts->kslices != 2 && opts->kslices != 4 && opts->kslices != 8)
-            return SPMM_ERR_INVALID_ARG;
-        io.kslices = opts->kslices;
-        if (opts->ufk != 0 && !valid_ufk(opts->ufk)) return SPMM_ERR_INVALID_ARG;
-        io.ufk = opts->ufk;
-        force_wide = opts->force_wide != 0;
-        if (force_wide) io.ufk = UFK;  // the 64-bit addressing kernels read chunks of 8 columns
-        if (io.kslices > 1 && io.ufk != 0 && io.ufk != UFK) return SPMM_ERR_INVALID_ARG;  // only plans with chunks of 8 are cut
-        depth = opts->depth;
-        probe = opts->probe != 0;
-        if (opts->tiles > 0 && opts->tiles != 8 && opts->tiles != 16 && opts->tiles != 32) return SPMM_ERR_INVALID_ARG;
-        tiles = opts->tiles;
-        // settings of the chunk path ask for the chunk path
-        schedule_forced = opts->ufi || opts->group_nnz || opts->group_panels || opts->sort_rows || force_wide || depth || opts->cross ||
-                          opts->ufk || probe || opts->kslices;
-        if (probe && (force_wide || depth != 0 || (io.ufk != 0 && io.ufk > 16))) return SPMM_ERR_INVALID_ARG;
-    }
+    if (opts.group_nnz < 0 || opts.group_panels < 0 || opts.n_hint < 0) return SPMM_ERR_INVALID_ARG;
+    if (opts.ufi != 0 && opts.ufi != 1 && opts.ufi != 2 && opts.ufi != 4 && opts.ufi != 8)
+        return SPMM_ERR_INVALID_ARG;
+    if (opts.threads < 0 || opts.threads > 64) return SPMM_ERR_INVALID_ARG;
+    if (opts.depth != 0 && opts.depth != 1 && opts.depth != 2 && opts.depth != 3 && opts.depth != 4 &&
+        opts.depth != 8)
+        return SPMM_ERR_INVALID_ARG;
+    io.ufi = opts.ufi;
+    io.group_nnz = opts.group_nnz;
+    io.group_panels = opts.group_panels;
+    host_only = opts.host_only != 0;
+    io.n_hint = opts.n_hint;
+    io.sort_rows = opts.sort_rows;
+    io.threads = opts.threads;
+    io.cross = opts.cross;
+    if (opts.kslices != 0 && opts.kslices != 1 && opts.kslices != 2 && opts.kslices != 4 && opts.kslices != 8)
+        return SPMM_ERR_INVALID_ARG;
+    io.kslices = opts.kslices;
+    if (opts.ufk != 0 && !valid_ufk(opts.ufk)) return SPMM_ERR_INVALID_ARG;
+    io.ufk = opts.ufk;
+    force_wide = opts.force_wide != 0;
+    if (force_wide) io.ufk = UFK;  // the 64-bit addressing kernels read chunks of 8 columns
+    if (io.kslices > 1 && io.ufk != 0 && io.ufk != UFK) return SPMM_ERR_INVALID_ARG;  // only plans with chunks of 8 are cut
+    depth = opts.depth;
+    probe = opts.probe != 0;
+    if (opts.tiles > 0 && opts.tiles != 8 && opts.tiles != 16 && opts.tiles != 32) return SPMM_ERR_INVALID_ARG;
+    tiles = opts.tiles;
+    // settings of the chunk path ask for the chunk path
+    schedule_forced = opts.ufi || opts.group_nnz || opts.group_panels || opts.sort_rows || force_wide || depth || opts.cross ||
+                      opts.ufk || probe || opts.kslices;
+    if (probe && (force_wide || depth != 0 || (io.ufk != 0 && io.ufk > 16))) return SPMM_ERR_INVALID_ARG;
     plan.reset(new spmm_plan());
     spmm_plan *p = plan.get();
     int rc = 0;
@@ -239,14 +238,22 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
 
 extern "C" {
 
-spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, const int32_t *row_ptr,
-                                  const int32_t *col_idx, const float *vals, const spmm_options_t *opts)
+spmm_status_t spmm_plan_create_sized(spmm_plan_t **plan, int64_t M, int64_t K, const int32_t *row_ptr,
+                                     const int32_t *col_idx, const float *vals, const spmm_options_t *opts,
+                                     size_t opts_bytes)
 {
     if (!plan) return SPMM_ERR_INVALID_ARG;
     *plan = nullptr;
+    spmm_options_t known;
+    std::memset(&known, 0, sizeof known);
+    if (opts) {
+        std::memcpy(&known, opts, std::min(opts_bytes, sizeof known));
+        for (size_t i = sizeof known; i < opts_bytes; ++i)
+            if (reinterpret_cast<const unsigned char *>(opts)[i]) return SPMM_ERR_UNSUPPORTED;
+    }
     try {
         plan_owner made;  // gives back what it holds unless it is handed over
-        const spmm_status_t st = create(made, M, K, row_ptr, col_idx, vals, opts);
+        const spmm_status_t st = create(made, M, K, row_ptr, col_idx, vals, known);
         if (st == SPMM_OK) *plan = made.release();
         return st;
     } catch (const std::bad_alloc &) {
@@ -259,7 +266,13 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K, cons
 spmm_status_t spmm_plan_create(spmm_plan_t **plan, int64_t M, int64_t K, const int32_t *row_ptr,
                                const int32_t *col_idx, const float *vals)
 {
-    return spmm_plan_create_ex(plan, M, K, row_ptr, col_idx, vals, nullptr);
+    return spmm_plan_create_sized(plan, M, K, row_ptr, col_idx, vals, nullptr, 0);
+}
+
+spmm_status_t(spmm_plan_create_ex)(spmm_plan_t **plan, int64_t M, int64_t K, const int32_t *row_ptr,
+                                   const int32_t *col_idx, const float *vals, const spmm_options_t *opts)
+{
+    return spmm_plan_create_sized(plan, M, K, row_ptr, col_idx, vals, opts, offsetof(spmm_options_t, tiles));
 }
 
 namespace {
@@ -409,33 +422,41 @@ spmm_status_t spmm_plan_destroy(spmm_plan_t *plan)
     return SPMM_OK;
 }
 
-spmm_status_t spmm_plan_describe(const spmm_plan_t *plan, spmm_plan_info_t *out)
+spmm_status_t spmm_plan_describe_sized(const spmm_plan_t *plan, spmm_plan_info_t *out, size_t out_bytes)
 {
     if (!plan || !out) return SPMM_ERR_INVALID_ARG;
     const HostPlan &h = plan->host;
-    std::memset(out, 0, sizeof(*out));
-    out->M = h.M;
-    out->K = h.K;
-    out->nnz = h.nnz;
-    out->ufi = h.ufi;
-    out->ufk = h.ufk;
-    out->group_nnz = h.group_nnz;
-    out->group_panels = h.group_panels;
-    out->n_groups = (int64_t)(h.groups.size() / 5);
-    out->n_blocks = h.n_blocks;
-    out->n_split = h.n_split;
-    out->n_enum = h.n_enum;
-    out->n_chunks = h.n_chunks;
-    out->stream_words = plan->stream_words;
-    out->device_bytes = plan->device_bytes;
-    out->sorted_rows = h.rowmap.empty() ? 0 : 1;
-    out->n_cross = h.n_cross;
-    out->scratch_bytes = plan->scratch_bytes;
-    out->k_slices = h.k_slices;
-    out->slice_rows = h.slice_rows;
-    out->slice_cols = h.slice_cols;
-    out->tile_rows = plan->tiles.rows;
+    spmm_plan_info_t info;
+    std::memset(&info, 0, sizeof info);
+    info.M = h.M;
+    info.K = h.K;
+    info.nnz = h.nnz;
+    info.ufi = h.ufi;
+    info.ufk = h.ufk;
+    info.group_nnz = h.group_nnz;
+    info.group_panels = h.group_panels;
+    info.n_groups = (int64_t)(h.groups.size() / 5);
+    info.n_blocks = h.n_blocks;
+    info.n_split = h.n_split;
+    info.n_enum = h.n_enum;
+    info.n_chunks = h.n_chunks;
+    info.stream_words = plan->stream_words;
+    info.device_bytes = plan->device_bytes;
+    info.sorted_rows = h.rowmap.empty() ? 0 : 1;
+    info.n_cross = h.n_cross;
+    info.scratch_bytes = plan->scratch_bytes;
+    info.k_slices = h.k_slices;
+    info.slice_rows = h.slice_rows;
+    info.slice_cols = h.slice_cols;
+    info.tile_rows = plan->tiles.rows;
+    std::memset(out, 0, out_bytes);
+    std::memcpy(out, &info, std::min(out_bytes, sizeof info));
     return SPMM_OK;
+}
+
+spmm_status_t(spmm_plan_describe)(const spmm_plan_t *plan, spmm_plan_info_t *out)
+{
+    return spmm_plan_describe_sized(plan, out, offsetof(spmm_plan_info_t, tile_rows));
 }
 
 spmm_status_t spmm_plan_get_groups(const spmm_plan_t *plan, int32_t *out, int64_t cap)
