@@ -75,10 +75,9 @@ typedef struct {
     int64_t tile_rows;     /* 0, or the rows per panel (32, 16 or 8) of a plan whose product runs on the matrix
                               cores (spmm_options_t.tiles).  Such a plan holds the entries in tiles
                               instead of chunks: n_enum = panels * K and n_chunks = its (panel, column step)
-                              blocks, stream_words and device_bytes are those of the tiles, scratch_bytes and
-                              n_cross are 0, k_slices is 1 and any number of its executes may be in flight;
-                              the remaining fields and the row groups are those of the chunk schedule that
-                              cross < 0 and kslices = 1 give the same matrix. */
+                              blocks, stream_words and device_bytes are those of the tiles, scratch_bytes is 0
+                              and any number of its executes may be in flight; the remaining fields and the
+                              row groups are those of the chunk schedule of the same matrix. */
 } spmm_plan_info_t;
 
 /* Optional inspector settings; zero in a field means "let the inspector choose". */

@@ -176,11 +176,7 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
             rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
             // the chunk plan needs no memory beside its own, the builder of tiles a multiple of its result's
             if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) rc = 0;
-            if (p->tiles.rows > 0) {  // a schedule of whole panels and columns: nothing of this plan meets in scratch memory
-                io.schedule_only = true;
-                io.cross = -1;
-                io.kslices = 1;
-            }
+            io.schedule_only = p->tiles.rows > 0;
         }
     }
     if (rc == 0) rc = spmm_inspect(M, K, row_ptr, col_idx, vals, io, p->host);

@@ -179,18 +179,6 @@ int main()
             REQUIRE(info.tile_rows == 0 && info.device_bytes > 0 && info.stream_words > 0);
             REQUIRE(spmm_plan_destroy(p) == SPMM_OK && device_live == 0);
         }
-        tiles_status = 0;
-        // tiles share no scratch, whatever the chunks of the matrix would do: any number of executes may overlap
-        const csr cut = matrix(512, 16384, 4, 0);
-        o.tiles = -1;
-        REQUIRE(create(cut, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.k_slices == 4);
-        REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
-        o.tiles = 0;
-        REQUIRE(create(cut, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.tile_rows > 0);
-        REQUIRE(info.k_slices == 1 && info.slice_rows == cut.M && info.slice_cols == cut.K && info.n_cross == 0);
-        REQUIRE(info.scratch_bytes == 0);
-        REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
-        o.tiles = 16;
         for (int status : {SPMM_ERR_HIP, SPMM_ERR_INVALID_CSR}) {  // anything else is reported
             tiles_status = status;
             REQUIRE(create(dense, o, &p) == (spmm_status_t)status && p == nullptr && device_live == 0);
