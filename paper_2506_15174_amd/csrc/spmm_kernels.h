@@ -56,7 +56,4 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
 // part of the loaded code object); later calls return the kept value.  Returns a hipError_t.
 int spmm_static_scratch(float **ptr, size_t *bytes);
 
-// The pipeline depth an instance is tuned for.
-int spmm_default_depth(int ufi, int slices);
-
 #endif

@@ -672,11 +672,15 @@ template <int U, int S, int VW, int DMAX, bool WIDE> void launch_depth(const spm
 
 // Pipeline depths per height (D2, D4, D8 for 2, 4, 8 slices): the shallowest that keeps the
 // loads flowing (see waves_per_simd); one column slot per slice (8 slices) needs more chunks
-// in flight for the same number of requests.
+// in flight for the same number of requests.  Single rows in two slices make four loads per chunk, and
+// up to 32 waves per compute unit keep the gather busy by themselves: looking a chunk ahead only costs work at
+// the ends of the short windows (4096 x 4096, 95 % pruned, 128 columns: 18.0 us with two in flight, 17.4 with
+// one; 22 even and uneven matrices 2 to 12 % faster).  A unit held to two workgroups (lds_pad) has not enough
+// waves for that and keeps two, and so do 64-bit addresses and a caller who asks for more.
 template <int U, int D2, int D4, int D8> void launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream)
 {
     switch (slices) {
-    case 2: wide ? launch_depth<U, 2, 4, D2, true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream); break;
+    case 2: wide ? launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream); break;
     case 4: wide ? launch_depth<U, 4, 4, D4, true>(a, depth, stream) : launch_depth<U, 4, 4, D4, false>(a, depth, stream); break;
     case 8: wide ? launch_depth<U, 8, 4, D8, true>(a, depth, stream) : launch_depth<U, 8, 4, D8, false>(a, depth, stream); break;
     default: wide ? launch_depth<U, 1, 1, 3, true>(a, depth, stream) : launch_depth<U, 1, 1, 3, false>(a, depth, stream); break;
@@ -702,16 +706,9 @@ template <int U, int D> bool launch_narrow(const spmm_launch_args &a, int ufk, i
 
 }  // namespace
 
-// The depth table (instances per height: 2, 4, 8 slices): kept in step with
-// spmm_default_depth below.
 int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, bool wide, int depth, void *stream)
 {
     if (a.n_blocks <= 0 || a.n_tiles <= 0) return 0;
-    // Single rows in two slices: four loads per chunk and up to 32 waves per compute unit keep the
-    // gather busy by themselves, and looking a chunk ahead only costs work at the ends of the short
-    // windows (4096 x 4096, 95 % pruned, 128 columns: 18.0 -> 17.4 us; 22 even and uneven matrices 2 to
-    // 12 % faster).  A unit held to two workgroups has not enough waves for that.
-    if (ufi == 1 && slices == 2 && depth == 0 && a.lds_pad == 0) depth = 1;
     if (ufk != UFK) {
         bool ok = !wide;
         if (ok) {
@@ -724,12 +721,14 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
             }
         }
         if (!ok) return (int)hipErrorInvalidValue;
+    } else if (ufi == 1 && slices == 2 && !wide && (depth > 1 || (depth == 0 && a.lds_pad > 0))) {
+        launch_depth<1, 2, 4, 2, false>(a, depth, stream);
     } else
     switch (ufi) {
     case 8: launch_slices<8, 2, 3, 4>(a, slices, wide, depth, stream); break;
     case 4: launch_slices<4, 2, 3, 4>(a, slices, wide, depth, stream); break;
     case 2: launch_slices<2, 2, 2, 6>(a, slices, wide, depth, stream); break;
-    case 1: launch_slices<1, 2, 2, 8>(a, slices, wide, depth, stream); break;
+    case 1: launch_slices<1, 1, 2, 8>(a, slices, wide, depth, stream); break;
     default: return (int)hipErrorInvalidValue;
     }
     if (a.n_cross > 0)
@@ -773,11 +772,4 @@ int spmm_static_scratch(float **ptr, size_t *bytes)
     *ptr = scratch_on_device[dev];
     *bytes = SPMM_STATIC_SCRATCH_BYTES;
     return 0;
-}
-
-int spmm_default_depth(int ufi, int slices)
-{
-    static const int table[4][3] = {{2, 2, 8}, {2, 2, 6}, {2, 3, 4}, {2, 3, 4}};  // rows: height 1, 2, 4, 8
-    const int u = ufi == 8 ? 3 : ufi == 4 ? 2 : ufi == 2 ? 1 : 0;
-    return slices == 2 ? table[u][0] : slices == 4 ? table[u][1] : slices == 8 ? table[u][2] : 3;
 }
