@@ -65,7 +65,8 @@ typedef struct {
                               workgroups' sums meet in scratch memory of the plan */
     int64_t scratch_bytes; /* scratch memory of the plan that executes write (part of device_bytes): the
                               sums of panels cut across workgroups and of plans cut along K; 0 when
-                              n_cross is 0 and k_slices is 1 */
+                              n_cross is 0 and k_slices is 1, and for plans on tiles.  Above 0: at most
+                              one execute of the plan may be in flight at a time */
     int64_t k_slices;      /* 1, or the number of column ranges of A (2, 4 or 8) the plan is cut into:
                               the plan then has k_slices * slice_rows rows, row s * slice_rows + i
                               holding the entries of row i whose columns lie in range s */
@@ -76,8 +77,9 @@ typedef struct {
                               cores (spmm_options_t.tiles).  Such a plan holds the entries in tiles
                               instead of chunks: n_enum = panels * K and n_chunks = its (panel, column step)
                               blocks, stream_words and device_bytes are those of the tiles, scratch_bytes is 0
-                              and any number of its executes may be in flight; the remaining fields and the
-                              row groups are those of the chunk schedule of the same matrix. */
+                              and any number of its executes may be in flight; the remaining fields (also
+                              n_cross and k_slices) and the row groups are those of the chunk schedule of the
+                              same matrix, which its product does not use. */
 } spmm_plan_info_t;
 
 /* Optional inspector settings; zero in a field means "let the inspector choose". */
@@ -97,7 +99,7 @@ typedef struct {
                               a quarter of the entries and the chosen panels are taller than one row */
     int32_t force_wide;    /* nonzero: spmm_execute uses the 64-bit addressing kernels also where B
                               is small enough for 32-bit offsets (lets small inputs exercise them) */
-    int32_t threads;       /* host threads of the inspector, 1..64 (0 = one per two million entries,
+    int32_t threads;       /* host threads of the inspector, 1..64 (0 = one per 2^16 entries,
                               at most 16 and at most the machine's; the plan does not depend on it) */
     int32_t depth;         /* chunks of B rows a wave keeps in flight (the software pipeline's depth,
                               the paper's unroll(k, UFk) axis of Figure 2): 1, 2, 3, 4 or 8;
@@ -133,7 +135,7 @@ typedef struct {
                               more and its rows at least 32 entries per range on average, and when
                               the tile is exactly one L2 and the rows hold 1024 entries or more; never for
                               plans with chunks wider than 8 (SPMM_ERR_INVALID_ARG if both are forced).
-                              At most one execute of such a plan may be in flight at a time. */
+                              At most one execute of such a plan may be in flight at a time (not on tiles). */
     int32_t tiles;         /* the matrix-core path: A in tiles of panels of 8, 16 or 32 rows, absent
                               entries multiplied as zeros by fp32 matrix instructions, which pays on
                               matrices that are not very sparse.  8, 16 or 32 = use it with panels of so
@@ -215,10 +217,10 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K,
  * allocates nothing and does not synchronise.  The plan is read-only during
  * execution (pieces of a split panel meet in on-chip memory, not in the plan),
  * so any number of executes of one plan may be in flight on any streams -- unless the
- * plan holds panels cut across workgroups (info.n_cross > 0): their sums meet in scratch
- * memory of the plan, so at most one execute of such a plan may be in flight at a time;
- * the same holds for a plan cut along K (info.k_slices > 1), whose ranges' sums meet in
- * scratch memory of the plan and are added by a last launch, 128 columns at a time.
+ * plan has scratch memory (info.scratch_bytes > 0), where the sums of panels cut across
+ * workgroups meet, or those of the ranges of a plan cut along K, which a last launch adds, 128
+ * columns at a time: at most one execute of such a plan may be in flight at a time.
+ * (A plan on tiles has none, whatever the n_cross and k_slices of its chunk schedule.)
  * Results are bit-identical from run to run.  B and C must be 4-byte aligned.
  * Every N runs on the kernels that handle four columns per lane (the last lane of
  * a row stores only the columns that exist; rows that are not 16-byte aligned cost
@@ -241,7 +243,8 @@ spmm_status_t spmm_execute(const spmm_plan_t *plan, const float *B, int32_t N,
  * One column tile of a launch needs 512 * ufi bytes per workgroup of a cut panel; the
  * call packs as many column tiles into a launch as the array holds and returns
  * SPMM_ERR_UNSUPPORTED, enqueuing nothing, when a single tile does not fit, and for
- * every plan cut along K (info.k_slices > 1: its sums need more than the array holds).
+ * every plan on chunks cut along K (info.k_slices > 1 with info.tile_rows == 0: its sums
+ * need more than the array holds).
  * All plans and all callers on one device share the array, which keeps the last call's
  * content (every launch overwrites what it reads, nothing needs clearing): calls that
  * overlap in time on one device race, also on different streams and for different plans.

@@ -171,6 +171,14 @@ int main()
         REQUIRE(create(dense, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.tile_rows > 0);
         REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
         fail_in_turn("tiles", dense, o);
+        // executes share scratch memory on chunks, not on tiles: scratch_bytes tells
+        const csr cut = matrix(512, 16384, 4, 0);
+        for (int asked : {-1, 0}) {
+            o.tiles = asked;
+            REQUIRE(create(cut, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.k_slices == 4);
+            REQUIRE((info.tile_rows > 0) == (asked == 0) && (info.scratch_bytes > 0) == (asked < 0));
+            REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+        }
         // no room for the tiles: chunks, also where tiles were asked for
         tiles_status = SPMM_ERR_ALLOC;
         for (int asked : {0, 16}) {
