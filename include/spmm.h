@@ -201,6 +201,10 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K,
  * Executor (paper Section 3.3 "Sparse Coarsen", Listings 5-7): C <- A x B.
  *
  *   B       DEVICE  const float[K*N], row-major, leading dimension N, finite values
+ *           (an infinity or NaN in row k makes elements of its column of C NaN also in
+ *           rows of A without an entry in column k: in rows whose entries share a chunk or
+ *           its padding with that column, and on tiles, which multiply absent entries as
+ *           zeros, in every row of C)
  *   N       columns of B and C, >= 1 (32, 64 and 128 have tuned kernels; every
  *           other N runs through masked column tiles of at most 128 columns; tiles
  *           of one width share a kernel launch, a narrower rest takes a launch of

@@ -183,3 +183,22 @@ def test_a_plan_is_created_while_another_stream_works(torch_gpu, oracle):  # noq
     assert np.array_equal(dC.cpu().numpy(), C)
     check(oracle, csr, B, C)
     side.synchronize()
+
+
+def test_how_far_a_value_outside_the_domain_reaches(torch_gpu):  # noqa: F811
+    """B is finite by contract.  An infinity in one row of it stays in its column of C on both paths, and on
+    single rows of chunks in the rows with an entry there (and in none that has no entry in its chunks)."""
+    torch = torch_gpu
+    csr = gen.uniform_positions(64, 256, 0.5, 15)
+    B = gen.dense_activations(csr.K, 32, 16)
+    k, j = 100, 7
+    B[k, j] = np.inf
+    dense = np.zeros((csr.M, csr.K), np.float32)
+    dense[np.repeat(np.arange(csr.M), np.diff(csr.row_ptr)), csr.col_idx] = csr.vals
+    holds = dense[:, k] != 0
+    for tiles in (-1, 8, 16, 32):
+        C, _ = gpu_product(torch, csr, B, tiles=tiles, ufi=1 if tiles < 0 else 0)
+        finite = np.isfinite(C)
+        assert finite[:, [c for c in range(32) if c != j]].all()
+        assert not finite[holds, j].any()
+        assert finite[~holds, j].all() if tiles < 0 else not finite[:, j].any()
