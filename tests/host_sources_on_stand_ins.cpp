@@ -1,9 +1,11 @@
-// Plan creation where memory runs out: run by tests/test_plan_create_failures.py, which compiles this file
-// together with the library's host sources.  The HIP runtime and the kernels' entry points are stand-ins in
-// host memory, so every allocation can be made to fail in turn, also those a plan makes on a device.
+// The library's host sources on stand-ins: tests/test_host_sources.py compiles them together with this file, in
+// which the HIP runtime and the kernels' entry points are stand-ins in host memory.
+//   failures   every allocation of a plan's creation is made to fail in turn, also those on the device
+//   launches   what spmm_execute hands to the launcher
 #include <hip/hip_runtime_api.h>
 
 #include <atomic>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -78,7 +80,13 @@ hipError_t hipGetLastError() { return hipSuccess; }
 static int tiles_status = 0;      // what the builder of tiles answers
 static double tiles_time = 1e9;   // its estimate of a product's time
 
-int spmm_launch_chunks(const spmm_launch_args &, int, int, int, bool, int, void *) { return 0; }
+static std::vector<spmm_launch_args> launched;
+
+int spmm_launch_chunks(const spmm_launch_args &a, int, int, int, bool, int, void *)
+{
+    launched.push_back(a);
+    return 0;
+}
 int spmm_static_scratch(float **, size_t *) { return 1; }
 int spmm_tiles_execute(const TilePlan &, int64_t, int64_t, const float *, int32_t, float *, void *) { return 0; }
 double spmm_tiles_time(int, int64_t, int64_t, int64_t, double, double, int *) { return tiles_time; }
@@ -157,7 +165,7 @@ static void fail_in_turn(const char *name, const csr &a, const spmm_options_t &o
     }
 }
 
-int main()
+static void failures()
 {
     spmm_options_t o;
     const csr dense = matrix(300, 1000, 2, 0);
@@ -221,6 +229,67 @@ int main()
         o.group_nnz = 16;
         fail_in_turn("four threads, panels across workgroups", matrix(300, 1000, 8, 20), o);
     }
+}
+
+// A matrix of 1024 rows for 64 columns of B whose row lengths spread by `sigma` (lognormal, mean a tenth of K).
+static csr spread(int64_t K, double sigma)
+{
+    csr a{1024, K};
+    uint64_t state = 12345;
+    auto uniform = [&] { return (double)((state = state * 6364136223846793005u + 1442695040888963407u) >> 11) / 9007199254740992.0; };
+    for (int64_t i = 0; i < a.M; ++i) {
+        double z = -6.0;
+        for (int k = 0; k < 12; ++k) z += uniform();
+        const double density = 0.1 * std::exp(sigma * z - 0.5 * sigma * sigma);
+        for (int64_t c = 0; c < K; ++c)
+            if (uniform() < density) {
+                a.col_idx.push_back((int32_t)c);
+                a.vals.push_back(1.0f);
+            }
+        a.row_ptr.push_back((int32_t)a.col_idx.size());
+    }
+    return a;
+}
+
+// spmm_execute's launches of a chunk plan of `a`, made for 64 columns, on N columns.
+static std::vector<spmm_launch_args> launches(const csr &a, int N, spmm_plan_info_t *info)
+{
+    static float word;  // B and C are only passed on
+    spmm_options_t o;
+    std::memset(&o, 0, sizeof o);
+    o.n_hint = 64;
+    o.tiles = -1;
+    spmm_plan_t *p = nullptr;
+    REQUIRE(create(a, o, &p) == SPMM_OK && spmm_plan_describe(p, info) == SPMM_OK);
+    launched.clear();
+    REQUIRE(spmm_execute(p, &word, N, &word, nullptr) == SPMM_OK);
+    REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+    return launched;
+}
+
+// Compute units are held to two workgroups (extra LDS) where a few more than 512 workgroups of uneven rows
+// would overload the units that get three; not for even rows, not for other numbers of workgroups, and not
+// where several column tiles share the launch.
+static void held_to_two()
+{
+    spmm_plan_info_t info;
+    for (int N : {64, 100, 128}) {
+        const std::vector<spmm_launch_args> uneven = launches(spread(4096, 0.5), N, &info);
+        REQUIRE(info.n_blocks > 512 && info.n_blocks <= 640);
+        REQUIRE(uneven.size() == 1 && uneven[0].n_tiles == 1 && uneven[0].lds_pad == 48u << 10);
+    }
+    const std::vector<spmm_launch_args> two_tiles = launches(spread(4096, 0.5), 256, &info);
+    REQUIRE(two_tiles.size() == 1 && two_tiles[0].n_tiles == 2 && two_tiles[0].lds_pad == 0);
+    REQUIRE(launches(spread(4096, 0.0), 64, &info)[0].lds_pad == 0);
+    REQUIRE(launches(spread(512, 0.5), 64, &info)[0].lds_pad == 0 && info.n_blocks <= 512);
+}
+
+int main(int argc, char **argv)
+{
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!std::strcmp(what, "failures")) failures();
+    else if (!std::strcmp(what, "launches")) held_to_two();
+    else return 2;
     std::printf("ok\n");
     return 0;
 }

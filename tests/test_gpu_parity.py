@@ -808,3 +808,15 @@ def test_many_short_rows_share_waves(torch_gpu, oracle):
     info = plan.describe()
     assert info["ufi"] == 1 and info["group_panels"] == 16 and info["n_groups"] < M // 8
     check(oracle, csr, B, C)
+
+
+@pytest.mark.parametrize("N", [64, 100, 128, 256])
+def test_plans_that_hold_compute_units_to_two_workgroups(torch_gpu, oracle, N):
+    """A few more than 512 workgroups of uneven rows (tests/test_host_sources.py pins when that takes place):
+    the launch asks for LDS that it does not use, and single rows look a chunk ahead; two column tiles do neither."""
+    csr = gen.lognormal_rows(1024, 4096, 0.9, 45)
+    B = gen.dense_activations(csr.K, N, 46)
+    C, plan = gpu_product(torch_gpu, csr, B, guard_rows=2, n_hint=64)
+    info = plan.describe()
+    assert info["tile_rows"] == 0 and info["ufi"] == 1 and 512 < info["n_blocks"] <= 640
+    check(oracle, csr, B, C)

@@ -202,3 +202,57 @@ def test_how_far_a_value_outside_the_domain_reaches(torch_gpu):  # noqa: F811
         assert finite[:, [c for c in range(32) if c != j]].all()
         assert not finite[holds, j].any()
         assert finite[~holds, j].all() if tiles < 0 else not finite[:, j].any()
+
+
+@pytest.mark.parametrize("N", [1, 4, 36, 128, 1000, 4099])
+@pytest.mark.parametrize("tiles,n_hint", [(8, 4), (8, 16), (16, 64), (32, 128)])
+def test_tile_plans_at_widths_far_from_their_hint(torch_gpu, oracle, tiles, n_hint, N):  # noqa: F811
+    """A plan stays valid for every N: fewer columns than a column group, and many column tiles (more
+    workgroups than the chip holds at once, in several XCD shares)."""
+    csr = integer_matrix(530, 700, 0.3, 17)
+    B = np.random.default_rng(N).integers(-16, 17, (csr.K, N)).astype(np.float32)
+    C, plan = gpu_product(torch_gpu, csr, B, guard_rows=2, tiles=tiles, n_hint=n_hint)
+    assert plan.describe()["tile_rows"] == tiles
+    C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B)
+    assert np.array_equal(C.astype(np.float64), C_ref)
+
+
+@pytest.mark.parametrize("tiles", [8, 16, 32])
+def test_tile_plans_with_operands_at_4_byte_offsets(torch_gpu, oracle, tiles):  # noqa: F811
+    """The interface asks for 4-byte alignment only; nothing beside C is written, through either entry point."""
+    torch = torch_gpu
+    csr = integer_matrix(75, 300, 0.4, 19)
+    plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=tiles)
+    for N in (4, 8, 16, 64, 130):
+        Bh = np.random.default_rng(N).integers(-16, 17, (csr.K, N)).astype(np.float32)
+        C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, Bh)
+        for offset in (1, 2, 3):
+            memory = torch.full((csr.K * N + 8,), float("nan"), device="cuda")
+            B = memory[offset:offset + csr.K * N].view(csr.K, N)
+            B.copy_(torch.from_numpy(Bh))
+            for run in (plan.execute_raw, plan.execute_static_raw):
+                out = torch.full((csr.M * N + 8,), float("nan"), device="cuda")
+                run(B.data_ptr(), N, out.data_ptr() + 4 * offset, None)
+                torch.cuda.synchronize()
+                host = out.cpu().numpy()
+                assert np.array_equal(host[offset:offset + csr.M * N].reshape(csr.M, N).astype(np.float64), C_ref)
+                assert np.isnan(host[:offset]).all() and np.isnan(host[offset + csr.M * N:]).all()
+    for bad in (1, 2):
+        with pytest.raises(spmm.SpmmError) as err:
+            plan.execute_raw(B.data_ptr() + bad, N, out.data_ptr(), None)
+        assert err.value.status == spmm.SPMM_ERR_INVALID_ARG
+
+
+def test_values_of_the_tiles_setting(torch_gpu):  # noqa: F811
+    csr = gen.uniform_positions(40, 60, 0.5, 21)
+    for bad in (1, 4, 12, 24, 33, 64, 2 ** 31 - 1):
+        with pytest.raises(spmm.SpmmError) as err:
+            spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=bad)
+        assert err.value.status == spmm.SPMM_ERR_INVALID_ARG
+    for off in (-1, -8, -2 ** 31):
+        assert spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=off).describe()["tile_rows"] == 0
+    host = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=16, host_only=True)
+    assert host.describe()["tile_rows"] == 0
+    empty = spmm.plan_create(40, 60, np.zeros(41), [], [], tiles=16)   # no entry at all
+    B = torch_gpu.ones((60, 8), device="cuda")
+    assert torch_gpu.equal(empty.execute(B), torch_gpu.zeros((40, 8), device="cuda"))
