@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path: fp32 CSR SpMM C = A x B on one MI355X.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload conv|stress|ffn|ffn-all|matrix|sweep|narrow|sparsity|ablation|tune]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload conv|stress|ffn|ffn-all|matrix|sweep|narrow|sparsity|ablation|tune|unhinted|paths]
 
 A step is one pass of the whole hot path (spmm_execute, every kernel it
 launches) over the workload's column counts, with the plan and all operands
@@ -29,7 +29,9 @@ feed-forward matrices), `sparsity` (the same for a 512 x 512 matrix from 50 to 9
 the sweep of the paper's Figure 9), `ablation` (the method's ingredients switched
 on one by one, the ladder of the paper's Figure 7) and `tune` (every panel height
 and three group budgets forced per matrix: what the closed schedule rule loses
-against the best candidate, and the plan's size against CSR and dense).
+against the best candidate, and the plan's size against CSR and dense), `unhinted` (what the
+bCols hint is worth) and `paths` (chunks against tiles of every panel height, with the two estimates
+between which a plan's path is chosen).
 """
 import argparse
 import json
@@ -44,6 +46,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 # 256 CUs x 4 SIMDs x 16 lanes x 2 flop x 2.4 GHz, no packed-fp32 forms
 FP32_VALU_PEAK_TFLOPS = 78.6
+# dense fp32 on the matrix cores
+FP32_MFMA_PEAK_TFLOPS = 157.3
 
 
 def bytes_min(M, K, nnz, N):
@@ -59,13 +63,13 @@ def build_workload(name, args=None):
                 % (M, K, 100 * args.sparsity, args.seed, args.bcols),
                 gen.magnitude_pruned(M, K, args.sparsity, args.seed), (args.bcols,))
     if name == "conv":
-        return ("conv1x1 512x2048 @80% magnitude-pruned N(0,1), bCols 32/64/128 (configs[1])",
+        return ("conv1x1 512x2048 @80% magnitude-pruned N(0,1), bCols 32/64/128",
                 gen.conv_layer(), (32, 64, 128))
     if name == "stress":
-        return ("stress 16384x16384 @95% Zipf(1.5) rows, 5% empty, bCols 128 (configs[3])",
+        return ("stress 16384x16384 @95% Zipf(1.5) rows, 5% empty, bCols 128",
                 gen.stress(), (128,))
     if name == "ffn":
-        return ("ffn 4096x1024 @70% lognormal rows, bCols 32/64/128 (configs[2])",
+        return ("ffn 4096x1024 @70% lognormal rows, bCols 32/64/128",
                 gen.ffn(0, 0), (32, 64, 128))
     raise SystemExit("unknown workload %r" % name)
 
@@ -227,6 +231,20 @@ def kernel_shape(N, ufi, K=0, ufk=8, k_slices=1):
     return "S=8,VW=4,D=%d" % depth[2]
 
 
+def tile_kernel(tile_rows):
+    """The kernel of a plan on tiles: panels of 32 and 16 rows share one, panels of 8 have their own."""
+    return "spmm_narrow_tiles_kernel" if tile_rows == 8 else "spmm_tiles_kernel<R=%d>" % tile_rows
+
+
+def schedule_of(info, keys):
+    """The named facts of a plan; on tiles those of the chunk schedule, which its product does not use, are None."""
+    on_tiles = info["tile_rows"] > 0
+    out = {k: None if on_tiles and k in CHUNK_FACTS else info[k] for k in keys}
+    out["tile_rows"] = info["tile_rows"]
+    return out
+
+
+CHUNK_FACTS = ("ufi", "ufk", "group_nnz", "group_panels", "n_groups", "n_blocks", "n_split", "sorted_rows", "n_cross", "k_slices")
 SPARSITY_SWEEP = (0.5, 0.6, 0.7, 0.8, 0.85, 0.9, 0.95, 0.98, 0.99)
 
 
@@ -249,8 +267,7 @@ def _measure_points(torch, np, spmm, gen, entries, cols, make_matrix, keep=None,
             _, med = time_execute(torch, plan, Bs[N], Cs[N], N)
             b = base.get(str(N), {})
             rows_out.append({"index": entry["index"], "M": csr.M, "K": csr.K, "sparsity": entry["sparsity"],
-                             "nnz": nnz, "N": N, "ufi": info["ufi"], "group_nnz": info["group_nnz"],
-                             "n_blocks": info["n_blocks"], "us": round(med * 1e3, 3),
+                             "nnz": nnz, "N": N, **schedule_of(info, ("ufi", "group_nnz", "n_blocks")), "us": round(med * 1e3, 3),
                              "gflops": round(2.0 * nnz * N / (med * 1e-3) / 1e9, 1),
                              "hbm_model_gbs": round(bytes_min(csr.M, csr.K, nnz, N) / (med * 1e-3) / 1e9, 1),
                              "hipsparse_us": b.get("hipsparse_best_us"), "rocblas_us": b.get("rocblas_sgemm_us")})
@@ -313,10 +330,10 @@ def run_sweep(args, cols=(32, 64, 128), narrow=False, ffn=False, square512=False
     out = {"metric": "fp32 CSR SpMM GFLOP/s (2*nnz*bCols)", "value": round(total_flops / total_s / 1e9, 2),
            "unit": "GFLOP/s", "n_gpus": 1, "steps": 1, "warmup": 10, "ms_per_step": round(total_s * 1e3, 4),
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
-           "config": {"workload": ("ffn: 8 feed-forward matrices (lognormal rows) x bCols 32/64/128 (configs[2])" if ffn else
+           "config": {"workload": ("ffn: 8 feed-forward matrices (lognormal rows) x bCols 32/64/128" if ffn else
                                    "sparsity sweep: 512 x 512 magnitude-pruned, 50 to 99 % pruned, bCols 64 and 4" if square512 else
                                    "narrow B: 30 magnitude-pruned matrices (M, K >= 1024) x bCols 4/8/16" if narrow else
-                                   "sweep: 48 magnitude-pruned matrices x bCols 32/64/128 (configs[4])"),
+                                   "sweep: 48 magnitude-pruned matrices x bCols 32/64/128"),
                       "wall_s": round(time.perf_counter() - t_start, 1)},
            "summary": summary, "points": rows_out}
     print(json.dumps(out))
@@ -365,7 +382,7 @@ COLD_WORKING_SET = 1 << 30      # bytes the rotating copies must exceed (four ti
 COLD_MAX_COPIES = 256
 
 
-def time_execute_cold(torch, csr, plan, B, N, samples=SAMPLES, inner=INNER):
+def time_execute_cold(torch, csr, plan, B, N, samples=SAMPLES, inner=INNER, plan_kw=None):
     """Cold-cache duration of one spmm_execute: independent copies of (plan, B, C), at
     least 1 GiB together or 256 of them, taken in turn by the shim's C loop, so that no
     call finds its plan, B or C in L2 or in the Infinity Cache.  Returns a dict, or None
@@ -379,7 +396,8 @@ def time_execute_cold(torch, csr, plan, B, N, samples=SAMPLES, inner=INNER):
     info = plan.describe()
     one = info["device_bytes"] + 4 * N * (csr.K + csr.M)
     copies = max(2, min(COLD_MAX_COPIES, -(-COLD_WORKING_SET // max(one, 1))))
-    plans = [plan] + [spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=N)
+    plans = [plan] + [spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals,
+                                      **(plan_kw if plan_kw is not None else {"n_hint": N}))
                       for _ in range(copies - 1)]
     Bs = [B] + [B.clone() for _ in range(copies - 1)]
     Cs = [torch.empty((csr.M, N), dtype=torch.float32, device="cuda") for _ in range(copies)]
@@ -426,15 +444,17 @@ def run_ablation(args):
                   schedule rule; still one chunk at a time (pipeline depth 1)
       +coarsen    the chunks of B rows of the next D - 1 steps in flight while one is
                   multiplied (the paper's unroll(k, UFk), Section 3.3.2)
-      full        the plan the inspector makes by itself: as +coarsen, and cut into column
-                  ranges bound to the XCDs' L2 caches where a tile of B fills or exceeds one
-                  (of these matrices only 8192 x 8192 at 50 to 80 % for 128 columns)"""
+      +ranges     as +coarsen, and cut into column ranges bound to the XCDs' L2 caches where a tile
+                  of B fills or exceeds one (of these matrices only 8192 x 8192 at 50 to 80 %
+                  for 128 columns)
+      full        the plan the inspector makes by itself: as +ranges, or tiles on the matrix
+                  cores where the estimates say that those are faster"""
     import torch
     import paper_2506_15174_amd as spmm
     from workloads import generators as gen
     torch.cuda.set_device(0)
     cols = (32, 64, 128)
-    rungs = ("rows", "+balance", "+enumerate", "+coarsen", "full")
+    rungs = ("rows", "+balance", "+enumerate", "+coarsen", "+ranges", "full")
     pts = []
     t_start = time.perf_counter()
     for entry in _ladder_matrices(gen):
@@ -448,9 +468,11 @@ def run_ablation(args):
                      "+balance": spmm.plan_create(*a, ufi=1, n_hint=N, depth=1, kslices=1),
                      "+enumerate": spmm.plan_create(*a, n_hint=N, depth=1, kslices=1),
                      "+coarsen": spmm.plan_create(*a, n_hint=N, kslices=1),
+                     "+ranges": spmm.plan_create(*a, n_hint=N, tiles=-1),
                      "full": spmm.plan_create(*a, n_hint=N)}
             row = {"M": csr.M, "K": csr.K, "sparsity": entry["sparsity"], "N": N,
-                   "ufi": plans["full"].describe()["ufi"], "k_slices": plans["full"].describe()["k_slices"]}
+                   "ufi": plans["+ranges"].describe()["ufi"], "k_slices": plans["+ranges"].describe()["k_slices"],
+                   "tile_rows": plans["full"].describe()["tile_rows"]}
             for r in rungs:
                 us = _time_plan(torch, plans[r], B, C, N)
                 row[r + "_us"] = round(us, 3)
@@ -510,7 +532,7 @@ def run_tune(args):
         for N in cols:
             B = torch.from_numpy(gen.activations_for(csr, N)).cuda()
             C = torch.empty((csr.M, N), dtype=torch.float32, device="cuda")
-            auto = spmm.plan_create(*a, n_hint=N)
+            auto = spmm.plan_create(*a, n_hint=N, tiles=-1)   # the schedule of chunks, whether or not it is the path taken
             ai = auto.describe()
             _time_plan(torch, auto, B, C, N, reps=3)          # clocks up before the first figure
             row = {"M": csr.M, "K": csr.K, "sparsity": entry["sparsity"], "N": N, "heldout": entry["heldout"],
@@ -579,8 +601,8 @@ def run_unhinted(args):
             t_p = _time_plan(torch, plain, B, C, N)
             hinted.destroy()
             pts.append({"M": csr.M, "K": csr.K, "sparsity": entry["sparsity"], "N": N, "hinted_us": round(t_h, 3),
-                        "unhinted_us": round(t_p, 3), "hinted": [hi["ufi"], hi["ufk"], hi["group_nnz"], hi["k_slices"]],
-                        "unhinted": [pi["ufi"], pi["ufk"], pi["group_nnz"], pi["k_slices"]],
+                        "unhinted_us": round(t_p, 3), "hinted": schedule_of(hi, ("ufi", "ufk", "group_nnz", "k_slices")),
+                        "unhinted": schedule_of(pi, ("ufi", "ufk", "group_nnz", "k_slices")),
                         "unhinted_over_hinted": round(t_p / t_h, 3)})
         plain.destroy()
     summary = {str(N): {"geomean_unhinted_over_hinted": round(_geomean([p["unhinted_over_hinted"] for p in pts if p["N"] == N]), 3),
@@ -590,6 +612,88 @@ def run_unhinted(args):
                       "higher_is_better": False, "dtype": "f32", "data": "synthetic",
                       "config": {"workload": "48 sweep matrices, one unhinted plan each, executed at bCols 32/64/128"},
                       "summary": summary, "points": pts}))
+
+
+PATH_SHAPES = ((512, 2048), (512, 13000), (768, 3072), (1024, 1024), (1024, 4096), (1536, 6144), (2048, 2048), (2048, 8192),
+               (3000, 2500), (4096, 600), (4096, 1024), (4096, 4096), (8192, 3000), (8192, 8192), (16384, 1024))
+PATH_DENSITIES = (0.04, 0.06, 0.08, 0.1, 0.13, 0.16, 0.2, 0.25, 0.3, 0.38, 0.45)
+PATH_WIDTHS = (4, 8, 16, 32, 64, 128, 200, 256)
+
+
+def run_paths(args):
+    """Chunks against tiles: random matrices of PATH_SHAPES, PATH_DENSITIES and three laws of row lengths (even,
+    lognormal, Zipf), each at four of PATH_WIDTHS; the hinted chunk plan, tiles of 8, 16 and 32 rows and
+    the plan that the inspector chooses, timed in turn, with the estimates the choice is made by.  args.steps
+    matrices are drawn."""
+    import ctypes
+    import random
+    import numpy as np
+    import torch
+    import paper_2506_15174_amd as spmm
+    from workloads import generators as gen
+    torch.cuda.set_device(0)
+    lib = spmm.load()
+    lib.spmm_chunks_time.restype = lib.spmm_tiles_time.restype = ctypes.c_double
+    i64, dbl = ctypes.c_int64, ctypes.c_double
+    rng = random.Random(args.seed)
+    t_start, pts = time.perf_counter(), []
+    laws = {"even": gen.uniform_positions, "lognormal": gen.lognormal_rows, "zipf": gen.zipf_rows}
+    for number in range(args.steps):
+        (M, K), law = PATH_SHAPES[number % len(PATH_SHAPES)], ("even", "lognormal", "zipf")[rng.randrange(3)]
+        density = PATH_DENSITIES[rng.randrange(len(PATH_DENSITIES))]
+        csr = laws[law](M, K, 1.0 - density, 8000 + number)
+        nnz = int(csr.row_ptr[-1])
+        row_ptr = np.ascontiguousarray(csr.row_ptr, np.int32)
+        a = (csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals)
+        for N in sorted(rng.sample(PATH_WIDTHS, 4)):
+            B = torch.from_numpy(gen.activations_for(csr, N)).cuda()
+            C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+            plans = {"chunks": spmm.plan_create(*a, n_hint=N, tiles=-1), "chosen": spmm.plan_create(*a, n_hint=N)}
+            for R in (8, 16, 32):
+                if R != 8 or N <= 64:
+                    plans[R] = spmm.plan_create(*a, n_hint=N, tiles=R)
+            us = {k: min(_time_plan(torch, p, B, C, N, reps=5) for _ in range(2)) for k, p in plans.items()}
+            estimate = {"chunks": lib.spmm_chunks_time(i64(M), i64(K), ctypes.c_void_p(row_ptr.ctypes.data), N, dbl(N))}
+            for R in (k for k in plans if k not in ("chunks", "chosen")):
+                heaviest = max(int(row_ptr[min(M, i + R)]) - int(row_ptr[i]) for i in range(0, M, R))
+                mean = nnz / (M * K)
+                estimate[R] = lib.spmm_tiles_time(R, i64(M), i64(K), i64(N), dbl(mean), dbl(max(mean, heaviest / (R * K))), None)
+            chosen = plans["chosen"].describe()["tile_rows"]
+            paths = {k: v for k, v in us.items() if k != "chosen"}
+            pts.append({"M": M, "K": K, "law": law, "density": round(nnz / (M * K), 4), "N": N, "chosen": chosen,
+                        "us": {str(k): round(v, 2) for k, v in us.items()},
+                        "estimate": {str(k): round(v, 2) for k, v in estimate.items()},
+                        "chosen_over_best": round(paths[chosen or "chunks"] / min(paths.values()), 3),
+                        "chosen_over_chunks": round(paths[chosen or "chunks"] / us["chunks"], 3)})
+            print(json.dumps(pts[-1]), file=sys.stderr, flush=True)
+            for p in plans.values():
+                p.destroy()
+
+    def fit(key, sel):
+        ratios = [p["estimate"][key] / p["us"][key] for p in sel if key in p["estimate"]]
+        if not ratios:
+            return None
+        return {"products": len(ratios), "rms_pct": round(100 * (sum((r - 1) ** 2 for r in ratios) / len(ratios)) ** 0.5, 1),
+                "min": round(min(ratios), 2), "max": round(max(ratios), 2)}
+
+    moved = [p for p in pts if p["chosen"]]
+    summary = {"products": len(pts), "on_tiles": len(moved),
+               "chosen_over_best": {"geomean": round(_geomean([p["chosen_over_best"] for p in pts]), 3),
+                                    "worst": max(p["chosen_over_best"] for p in pts)},
+               "tiles_over_chunks_where_chosen": {"geomean": round(_geomean([p["chosen_over_chunks"] for p in moved]), 3) if moved else None,
+                                                  "worst": max((p["chosen_over_chunks"] for p in moved), default=None),
+                                                  "slower_by_3_pct": sum(p["chosen_over_chunks"] > 1.03 for p in moved)},
+               "estimate_over_measured": {k: fit(k, pts) for k in ("chunks", "8", "16", "32")},
+               "estimate_over_measured_chunks_by_width": {str(N): fit("chunks", [p for p in pts if p["N"] == N]) for N in PATH_WIDTHS}}
+    if args.points_file:
+        with open(args.points_file, "w") as f:
+            json.dump(pts, f)
+    print(json.dumps({"metric": "time of the chosen path / time of the fastest path (geomean)",
+                      "value": summary["chosen_over_best"]["geomean"], "unit": "ratio", "n_gpus": 1, "higher_is_better": False,
+                      "dtype": "f32", "data": "synthetic",
+                      "config": {"workload": "%d random matrices x four widths, chunks and tiles" % args.steps, "seed": args.seed,
+                                 "wall_s": round(time.perf_counter() - t_start, 1)},
+                      "summary": summary}))
 
 
 def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, plan_kw=None):
@@ -602,16 +706,28 @@ def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, pla
     achieved = bmin / (avg_ms * 1e-3) / 1e9
     kernel_tflops = 2.0 * nnz * N / (avg_ms * 1e-3) / 1e12
     traffic, prov = measured_traffic(workload_key, N)
-    shape = kernel_shape(N, info["ufi"], csr.K, info["ufk"], info["k_slices"])
+    on_tiles = info["tile_rows"] > 0
+    if on_tiles:
+        kernel, launches = tile_kernel(info["tile_rows"]), 1
+    else:
+        shape = kernel_shape(N, info["ufi"], csr.K, info["ufk"], info["k_slices"])
+        kernel, launches = "spmm_chunks_kernel<UFI=%d,%s>" % (info["ufi"], shape), 1 + (info["n_cross"] > 0) + (info["k_slices"] > 1)
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic, "traffic_source": prov,
-                "kernel": "spmm_chunks_kernel<UFI=%d,%s> (bCols %d)" % (info["ufi"], shape, N),
+                "kernel": "%s (bCols %d)" % (kernel, N),
                 "cache_state": "hot",
                 "avg_launch_us": round(avg_ms * 1e3, 3), "median_launch_us": round(med_ms * 1e3, 3),
-                "launches_per_execute": 1 + (info["n_cross"] > 0) + (info["k_slices"] > 1), "algorithmic_bytes": bmin, "kernel_tflops": round(kernel_tflops, 3),
+                "launches_per_execute": launches, "algorithmic_bytes": bmin, "kernel_tflops": round(kernel_tflops, 3),
                 "frac_of_fp32_valu_peak": round(kernel_tflops / FP32_VALU_PEAK_TFLOPS, 5),
                 "traffic_gbs": round(traffic / (avg_ms * 1e-3) / 1e9, 2) if traffic else None,
                 "counters_pct": measured_counters(workload_key, N)}
+    if on_tiles:
+        # absent entries are multiplied as zeros: 1024 cells per block, one flop pair per cell and column
+        with_zeros = 2.0 * 1024 * info["n_chunks"] * N / (avg_ms * 1e-3) / 1e12
+        roofline["gather"] = None
+        roofline["matrix_cores"] = {"blocks": info["n_chunks"], "tflops_with_zeros": round(with_zeros, 3),
+                                    "peak": FP32_MFMA_PEAK_TFLOPS, "frac": round(with_zeros / FP32_MFMA_PEAK_TFLOPS, 4)}
+        return roofline
     # On-chip gather: each chunk of ufk enumerated columns costs ufk / S wave-wide loads of B
     # rows (S rows of B per load); the ceiling is the rate the gather microbenchmark
     # reaches on distinct rows of an L2-resident B.
@@ -669,7 +785,7 @@ def cpu_baseline(csr, cols, gen, skip=False):
 
 
 PLAN_KEYS = ("ufi", "ufk", "group_nnz", "group_panels", "n_groups", "n_blocks", "n_split", "n_enum", "n_chunks",
-             "device_bytes", "sorted_rows", "n_cross", "scratch_bytes", "k_slices")
+             "device_bytes", "sorted_rows", "n_cross", "scratch_bytes", "k_slices", "tile_rows")
 
 
 def run_headline(args):
@@ -724,8 +840,9 @@ def run_headline(args):
         if roofline.get("traffic"):
             roofline["traffic_gbs"] = round(roofline["traffic"] / (cold["mean_us"] * 1e-6) / 1e9, 2)
         g = roofline["gather"]
-        rate = g["wave_loads_per_launch"] / (cold["mean_us"] * 1e-6) / 1e9
-        roofline["gather"] = dict(g, g_wave_loads_per_s=round(rate, 2), frac=round(rate / GATHER_CEILING_GWLS, 4))
+        if g is not None:
+            rate = g["wave_loads_per_launch"] / (cold["mean_us"] * 1e-6) / 1e9
+            roofline["gather"] = dict(g, g_wave_loads_per_s=round(rate, 2), frac=round(rate / GATHER_CEILING_GWLS, 4))
     stress_base = {} if args.no_baselines else measure_baselines(torch, np, csr, (Ns,), {Ns: B}).get(str(Ns), {})
 
     # The timed steps: one pass over every product of the batch.  The products are independent
@@ -763,8 +880,8 @@ def run_headline(args):
     out = {"metric": "fp32 CSR SpMM GFLOP/s (2*nnz*bCols)", "value": round(value, 2), "unit": "GFLOP/s",
            "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per_step, 5),
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
-           "config": {"workload": "sweep: 48 magnitude-pruned matrices x bCols 32/64/128 (configs[4]) + stress "
-                                  "16384x16384 @95% Zipf(1.5) rows, 5% empty, bCols 128 (configs[3]); one step = "
+           "config": {"workload": "sweep: 48 magnitude-pruned matrices x bCols 32/64/128 + stress "
+                                  "16384x16384 @95% Zipf(1.5) rows, 5% empty, bCols 128; one step = "
                                   "all 145 products, issued over " + str(args.streams) + " stream(s)",
                       "products_per_step": len(resident), "flops_per_step": flops_step,
                       "streams": args.streams,
@@ -772,7 +889,7 @@ def run_headline(args):
                       "sweep_only": {"gflops_from_per_launch_medians": round(sweep_flops / sweep_s / 1e9, 2),
                                      "sum_of_launch_medians_ms": round(sweep_s * 1e3, 4)},
                       "stress": {"M": csr.M, "K": csr.K, "nnz": nnz, "bCols": Ns,
-                                 "plan": {k: info[k] for k in PLAN_KEYS}, "plan_create_s": round(plan_s, 4),
+                                 "plan": schedule_of(info, PLAN_KEYS), "plan_create_s": round(plan_s, 4),
                                  "row_stats": gen.row_stats(csr), "cold": cold,
                                  "hipsparse_best_us": stress_base.get("hipsparse_best_us"),
                                  "rocblas_sgemm_us": stress_base.get("rocblas_sgemm_us")},
@@ -798,8 +915,8 @@ def run_single(args):
     t0 = time.perf_counter()
     # one plan per column count: the schedule constants are chosen per bCols, as the
     # paper's tuner does (Section 3.5)
-    plans = {N: spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=N, ufi=args.ufi,
-                                 depth=args.depth, ufk=args.ufk, kslices=args.kslices) for N in cols}
+    forced = dict(ufi=args.ufi, depth=args.depth, ufk=args.ufk, kslices=args.kslices)
+    plans = {N: spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=N, **forced) for N in cols}
     plan_s = (time.perf_counter() - t0) / len(cols)
     infos = {N: plans[N].describe() for N in cols}
 
@@ -841,7 +958,7 @@ def run_single(args):
                             "hbm_model_gbs": round(bytes_min(csr.M, csr.K, nnz, N) / (m * 1e-3) / 1e9, 1)}
     # cold timings after every hot one: creating their copies leaves the GPU idle for a while
     for N in () if args.no_cold else cols:
-        cold = time_execute_cold(torch, csr, plans[N], Bs[N], N)
+        cold = time_execute_cold(torch, csr, plans[N], Bs[N], N, plan_kw=dict(forced, n_hint=N))
         if cold is not None:
             cold["hbm_model_gbs"] = round(bytes_min(csr.M, csr.K, nnz, N) / (cold["us"] * 1e-6) / 1e9, 1)
             cold["frac_of_hbm_peak"] = round(cold["hbm_model_gbs"] / HBM_PEAK_GBS, 5)
@@ -864,7 +981,7 @@ def run_single(args):
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
            "data": "synthetic",
            "config": {"workload": label, "M": csr.M, "K": csr.K, "nnz": nnz, "bCols": list(cols),
-                      "plans": {str(N): {k: infos[N][k] for k in PLAN_KEYS} for N in cols},
+                      "plans": {str(N): schedule_of(infos[N], PLAN_KEYS) for N in cols},
                       "plan_create_s": round(plan_s, 4), "row_stats": gen.row_stats(csr)},
            "roofline": roofline, "cpu_baseline": cpu, "per_bcols": per_cols, "baselines": baselines}
     print(json.dumps(out))
@@ -877,11 +994,11 @@ def main():
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--workload", default="headline",
                     help="headline (default: sweep + stress) | conv | stress | ffn | ffn-all | matrix | sweep | "
-                         "narrow | sparsity | ablation | tune | unhinted")
+                         "narrow | sparsity | ablation | tune | unhinted | paths (--steps matrices)")
     ap.add_argument("--shape", default="4096x4096", help="--workload matrix: rows x columns of A")
     ap.add_argument("--sparsity", type=float, default=0.5, help="--workload matrix: pruned share")
     ap.add_argument("--bcols", type=int, default=128, help="--workload matrix: columns of B")
-    ap.add_argument("--seed", type=int, default=11, help="--workload matrix: generator seed")
+    ap.add_argument("--seed", type=int, default=11, help="--workload matrix, paths: generator seed")
     ap.add_argument("--ufi", type=int, default=0, help="single workloads: force the rows per panel (1, 2, 4, 8)")
     ap.add_argument("--kslices", type=int, default=0,
                     help="single workloads: cut the plan into so many column ranges (1 = never, 0 = the rule)")
@@ -892,7 +1009,7 @@ def main():
     ap.add_argument("--streams", type=int, default=2,
                     help="headline: HIP streams the independent products of a step are issued over (1 = one after the other)")
     ap.add_argument("--cols", default="", help="tune: comma-separated column counts instead of 32,64,128")
-    ap.add_argument("--points-file", default="", help="headline: also write the per-point figures to this JSON file")
+    ap.add_argument("--points-file", default="", help="headline, paths: also write the per-point figures to this JSON file")
     ap.add_argument("--no-baselines", action="store_true")
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle timing")
     ap.add_argument("--no-cold", action="store_true",
@@ -912,8 +1029,9 @@ def main():
         return run_sweep(args, cols=(64, 4), square512=True)
     if args.workload == "ffn-all":
         return run_sweep(args, ffn=True)
-    if args.workload in ("sweep", "ablation", "tune", "unhinted"):
-        return {"sweep": run_sweep, "ablation": run_ablation, "tune": run_tune, "unhinted": run_unhinted}[args.workload](args)
+    if args.workload in ("sweep", "ablation", "tune", "unhinted", "paths"):
+        return {"sweep": run_sweep, "ablation": run_ablation, "tune": run_tune, "unhinted": run_unhinted,
+                "paths": run_paths}[args.workload](args)
     return run_single(args)
 
 

@@ -40,7 +40,7 @@ void spmm_tiles_release(TilePlan &p);
 
 // Estimated time of a product in us with panels of `rows` rows, and the column groups NB of a tile
 // (1, 2 or 4) it runs with.  density = share of the entries kept, peak = the largest such share of a panel.
-double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB);
+extern "C" double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB);
 
 // Enqueues C <- A x B.  Returns the hipError_t of the launch as int.
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream);

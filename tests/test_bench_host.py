@@ -85,3 +85,16 @@ def test_build_refuses_kernel_instances_that_spill():
         build.check_no_spills(ok.replace("lane]: 0", "lane]: 16"))
     with pytest.raises(RuntimeError, match="no resource remarks"):
         build.check_no_spills("")
+
+
+def test_facts_of_a_plan_on_tiles():
+    """Of a plan on tiles the benchmark prints the tiles' facts and none of the chunk schedule that it does not use."""
+    import paper_2506_15174_amd as spmm
+    info = spmm.plan_create(3, 4, [0, 2, 2, 3], [0, 3, 1], [1.0, 2.0, 3.0], host_only=True).describe()
+    assert bench.schedule_of(info, bench.PLAN_KEYS) == {k: info[k] for k in bench.PLAN_KEYS}
+    on_tiles = bench.schedule_of(dict(info, tile_rows=16), bench.PLAN_KEYS)
+    assert on_tiles["tile_rows"] == 16 and on_tiles["n_chunks"] == info["n_chunks"]
+    assert all(on_tiles[k] is None for k in ("ufi", "group_nnz", "n_blocks", "k_slices", "n_cross"))
+    assert bench.tile_kernel(32) == "spmm_tiles_kernel<R=32>" and bench.tile_kernel(8) == "spmm_narrow_tiles_kernel"
+    src = open(os.path.join(ROOT, "paper_2506_15174_amd", "csrc", "spmm_tiles.hip")).read()
+    assert "void spmm_tiles_kernel(" in src and "void spmm_narrow_tiles_kernel(" in src
