@@ -6,7 +6,9 @@
 //   3. the same with the executor's access shape: every slice of a wave reads a
 //      different row with 16-byte loads (rows of 512 / 256 / 128 bytes = 2 / 4 / 8 slices);
 //   4. what a small launch costs: one workgroup of 8 waves per CU, launched back to back,
-//      each wave following 0 to 4 dependent loads before it stores one word.
+//      each wave following 0 to 4 dependent loads before it stores one word;
+//   5. fp32 matrix instructions: what one occupies, alone and beside vector instructions of the
+//      same waves (both issue from the vector ALUs).
 // hipEvent timing, best of 5 launches.  Build and run:
 //   hipcc --offload-arch=gfx950 -O3 baselines/microbench_paths.hip -o microbench_paths && ./microbench_paths
 #include <hip/hip_runtime.h>
@@ -151,6 +153,63 @@ void run_gather(const char *what, const float *B, float *out, uint32_t K, int wa
     fflush(stdout);
 }
 
+// ---- 5. matrix instructions ---------------------------------------------------------------
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <int SHAPE> struct Mfma;  // 32: v_mfma_f32_32x32x2, 16: 16x16x4, 4: 4x4x1 (16 products of 4 x 4)
+template <> struct Mfma<32> {
+    typedef f32x16 acc_t;
+    static constexpr double FLOPS = 2.0 * 32 * 32 * 2;
+    static __device__ acc_t run(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+};
+template <> struct Mfma<16> {
+    typedef f32x4 acc_t;
+    static constexpr double FLOPS = 2.0 * 16 * 16 * 4;
+    static __device__ acc_t run(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+};
+template <> struct Mfma<4> {
+    typedef f32x4 acc_t;
+    static constexpr double FLOPS = 2.0 * 16 * 4 * 4;
+    static __device__ acc_t run(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); }
+};
+
+// Per round: 8 matrix instructions on four accumulators in turn (MATRIX) with ADDS integer adds beside each.
+template <int SHAPE, bool MATRIX, int ADDS> __global__ __launch_bounds__(256) void matrix_rounds(int rounds, float *out)
+{
+    typename Mfma<SHAPE>::acc_t acc[4] = {};
+    const float a = (float)(threadIdx.x & 7), b = 0.5f;
+    uint32_t x[4] = {threadIdx.x, 1u, 2u, 3u};
+    for (int r = 0; r < rounds; ++r) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if constexpr (MATRIX) acc[i % 4] = Mfma<SHAPE>::run(a, b, acc[i % 4]);
+#pragma unroll
+            for (int k = 0; k < ADDS; ++k) asm volatile("v_add_u32 %0, %0, %1" : "+v"(x[k % 4]) : "v"(x[(k + 1) % 4]));
+        }
+    }
+    out[(size_t)blockIdx.x * 256 + threadIdx.x] = acc[0][0] + acc[1][1] + acc[2][2] + acc[3][3] + (float)(x[0] ^ x[1] ^ x[2] ^ x[3]);
+}
+
+template <int SHAPE, bool MATRIX, int ADDS> void run_matrix(float *out, int waves_per_simd, int cus, double ghz)
+{
+    const int rounds = 4096, blocks = cus * waves_per_simd;  // a block is a wave on each SIMD of a compute unit
+    const float ms = best_ms([&] { hipLaunchKernelGGL((matrix_rounds<SHAPE, MATRIX, ADDS>), dim3(blocks), dim3(256), 0, 0, rounds, out); });
+    const double steps = 8.0 * rounds * waves_per_simd;  // per SIMD
+    printf("%-10s %2d adds beside each, %d waves per SIMD: %8.1f us, %6.2f cycles of %.1f GHz per step, %6.1f TFLOP/s\n",
+           !MATRIX ? "(adds only)" : SHAPE == 32 ? "32x32x2" : SHAPE == 16 ? "16x16x4" : "4x4x1", ADDS, waves_per_simd, ms * 1e3,
+           ms * 1e6 * ghz / steps, ghz, MATRIX ? Mfma<SHAPE>::FLOPS * 8.0 * rounds * blocks * 4 / ms / 1e9 : 0.0);
+    fflush(stdout);
+}
+
+template <int SHAPE> void run_shape(float *out, int cus, double ghz)
+{
+    for (int w : {1, 2, 4}) run_matrix<SHAPE, true, 0>(out, w, cus, ghz);
+    run_matrix<SHAPE, true, 4>(out, 4, cus, ghz);
+    run_matrix<SHAPE, true, 8>(out, 4, cus, ghz);
+    run_matrix<SHAPE, true, 16>(out, 4, cus, ghz);
+}
+
 int main()
 {
     hipDeviceProp_t prop;
@@ -209,5 +268,12 @@ int main()
         for (int groups : {cus / 4, cus / 2, 2 * cus, 4 * cus, 8 * cus}) run_chase<3>(table, n, out, groups);
         free(host);
     }
+    printf("-- matrix instructions\n");
+    run_shape<32>(fo, cus, ghz);
+    run_shape<16>(fo, cus, ghz);
+    run_shape<4>(fo, cus, ghz);
+    run_matrix<4, false, 4>(fo, 4, cus, ghz);
+    run_matrix<4, false, 8>(fo, 4, cus, ghz);
+    run_matrix<4, false, 16>(fo, 4, cus, ghz);
     return 0;
 }

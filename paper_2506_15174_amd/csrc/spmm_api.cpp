@@ -51,14 +51,16 @@ constexpr int32_t KSLICE_COLS = 128;
 // units, which hold the first and the 257th, get the 513th as well; held to two per unit, those few wait
 // for the first one with room, a lightly loaded one.  (1024 x 4096 with lognormal rows, 90 % pruned, 64
 // columns, 559 workgroups: 9.9 -> 8.2 us.)  Fewer waves hide less latency, and those last workgroups start
-// late: of 300 measured plans the cap gains 9 % on average where the most loaded unit gets at least 14 % less
-// to do and a unit's mean load shrinks by 24 chunks or more, and loses elsewhere (even rows, little
-// work per row, more than 640 workgroups, three per unit).
+// late, so the cap is for plans where the most loaded unit gets at least 14 % less to do and a unit's mean load
+// shrinks by 24 chunks or more.  Timed with and without it, 360 random plans of 513 to 768 workgroups: the 23
+// that this takes run 6 % faster on average (20 % to two of 10 and 13 % slower); the other plans of single rows,
+// held all the same, would be 3 % slower, and so would the ten of taller panels that it would take, whose
+// registers leave less room for a third workgroup to begin with.
 bool hold_to_two(const HostPlan &h)
 {
     constexpr int64_t UNITS = 256;
     const int64_t n = h.n_blocks;
-    if (n <= 2 * UNITS || n > 2 * UNITS + UNITS / 2) return false;
+    if (h.ufi != 1 || n <= 2 * UNITS || n > 2 * UNITS + UNITS / 2) return false;
     auto weight = [&](int64_t block) {
         int64_t chunks = 0;
         for (int w = 0; w < WAVES_PER_WG; ++w) chunks += h.items[(size_t)((block * WAVES_PER_WG + w) * ITEM_WORDS + IT_NCHUNKS)];

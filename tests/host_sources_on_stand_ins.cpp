@@ -231,16 +231,16 @@ static void failures()
     }
 }
 
-// A matrix of 1024 rows for 64 columns of B whose row lengths spread by `sigma` (lognormal, mean a tenth of K).
-static csr spread(int64_t K, double sigma)
+// A matrix whose row lengths spread by `sigma` (lognormal).
+static csr spread(int64_t K, double sigma, int64_t M = 1024, double mean = 0.1)
 {
-    csr a{1024, K};
+    csr a{M, K};
     uint64_t state = 12345;
     auto uniform = [&] { return (double)((state = state * 6364136223846793005u + 1442695040888963407u) >> 11) / 9007199254740992.0; };
     for (int64_t i = 0; i < a.M; ++i) {
         double z = -6.0;
         for (int k = 0; k < 12; ++k) z += uniform();
-        const double density = 0.1 * std::exp(sigma * z - 0.5 * sigma * sigma);
+        const double density = mean * std::exp(sigma * z - 0.5 * sigma * sigma);
         for (int64_t c = 0; c < K; ++c)
             if (uniform() < density) {
                 a.col_idx.push_back((int32_t)c);
@@ -268,19 +268,21 @@ static std::vector<spmm_launch_args> launches(const csr &a, int N, spmm_plan_inf
 }
 
 // Compute units are held to two workgroups (extra LDS) where a few more than 512 workgroups of uneven rows
-// would overload the units that get three; not for even rows, not for other numbers of workgroups, and not
-// where several column tiles share the launch.
+// would overload the units that get three; not for even rows or taller panels, not for other numbers of
+// workgroups, and not where several column tiles share the launch.
 static void held_to_two()
 {
     spmm_plan_info_t info;
     for (int N : {64, 100, 128}) {
         const std::vector<spmm_launch_args> uneven = launches(spread(4096, 0.5), N, &info);
-        REQUIRE(info.n_blocks > 512 && info.n_blocks <= 640);
+        REQUIRE(info.ufi == 1 && info.n_blocks > 512 && info.n_blocks <= 640);
         REQUIRE(uneven.size() == 1 && uneven[0].n_tiles == 1 && uneven[0].lds_pad == 48u << 10);
     }
     const std::vector<spmm_launch_args> two_tiles = launches(spread(4096, 0.5), 256, &info);
     REQUIRE(two_tiles.size() == 1 && two_tiles[0].n_tiles == 2 && two_tiles[0].lds_pad == 0);
     REQUIRE(launches(spread(4096, 0.0), 64, &info)[0].lds_pad == 0);
+    REQUIRE(launches(spread(1147, 0.5, 1230, 0.35), 64, &info)[0].lds_pad == 0);
+    REQUIRE(info.ufi == 2 && info.n_blocks > 512 && info.n_blocks <= 640);
     REQUIRE(launches(spread(512, 0.5), 64, &info)[0].lds_pad == 0 && info.n_blocks <= 512);
 }
 
