@@ -108,14 +108,13 @@ template <typename F> void launch_places(F kernel, tile_args &a, unsigned thread
 // places in a zeroed 4 KiB slot of LDS, read back as 16 operands per lane (four 16-byte reads), the
 // slot is zeroed again for the next block, and 16 * NB matrix instructions multiply.
 //
-// What bounds it: the matrix cores' fp32 rate (157 TFLOP/s dense) times the density.  fp32 matrix
-// instructions occupy the vector ALUs (a microbenchmark's 481 us of them and 634 us of integer adds
-// take 1086 us together), so every vector instruction beside them costs: expanding the blocks from
-// bitmaps in registers took 48 to 130 vector instructions per step, the scatter takes about 20, for
+// What bounds it: the matrix cores' fp32 rate (157 TFLOP/s dense, 156 measured) times the density.  fp32
+// matrix instructions issue from the vector ALUs (baselines/microbench_paths.hip: a 32x32x2 takes 64.6 cycles, 16
+// integer adds 44.5, both together 108.7), so every vector instruction beside them costs: expanding the
+// blocks from bitmaps in registers took 48 to 130 vector instructions per step, the scatter takes about 20, for
 // 6 bytes per entry instead of 4.3.  8192 x 8192 at 50 %, 128 columns: 134 us = 64 TFLOP/s of the
-// entries' products, 128 TFLOP/s on the matrix cores (matrix instructions alone: 121 us); the chunk
-// kernel takes 218 us there.  Splitting the operands into three bf16 parts (nine exact products on
-// the bf16 cores) was no faster: 142 us, at a clock the power limit pulls down to 1.7 GHz.
+// entries' products, 129 TFLOP/s on the matrix cores (110 us at their measured rate); the chunk
+// kernel takes 196 us there.
 template <int R, int NB, int W, bool STAGED, bool WIDE, int MINW>
 __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_args args)
 {
@@ -345,7 +344,7 @@ __device__ __forceinline__ void keep_loads_here() { __builtin_amdgcn_sched_barri
 //
 // What bounds it: with four columns the plan's bytes (2048 x 8192, 70 % pruned: 30 MB in 7.1 us, 2.6 us of them
 // the launch; chunks 15.8, panels of 16 rows 17.1), with sixteen the vector ALUs, which the matrix
-// instructions share (10 cycles each, measured, of the nominal 8, and some 60 other instructions per step): 10.8 us; chunks
+// instructions share (9 to 11 cycles each, measured, of the nominal 8, and some 60 other instructions per step): 10.8 us; chunks
 // 21.4, panels of 16 rows 17.2.  Where a block has 256 entries or fewer, writing zeros to its places
 // is cheaper than clearing all of it (8192 x 8192, 90 % pruned, 4 columns: 14.7 -> 12.3 us).  Asking for blocks
 // two steps ahead, or sixteen waves, changed nothing; panels of 16 rows of this kind gain 15 % at 8192 rows
@@ -841,8 +840,8 @@ void spmm_tiles_release(TilePlan &p)
     p = TilePlan();
 }
 
-// Fits to 1900 measured products, 3 to 50 % of the entries kept, 4 to 256 columns: within 5 % of the time
-// (panels of 8 rows: 7 to 16 %), and the NB it prefers is within 0.1 % of the best one on average.
+// Fitted; against 600 other products (bench.py --workload paths: 4 to 45 % of the entries kept, 4 to 256 columns)
+// the rms error is 4 % for panels of 16 rows, 3 % for 32 and 10 % for 8.
 double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB_out)
 {
     const int64_t panels = (M + rows - 1) / rows, steps = (K * rows + 1023) / 1024;
