@@ -139,7 +139,8 @@ typedef struct {
     int32_t tiles;         /* the matrix-core path: A in tiles of panels of 8, 16 or 32 rows, absent
                               entries multiplied as zeros by fp32 matrix instructions, which pays on
                               matrices that are not very sparse.  8, 16 or 32 = use it with panels of so
-                              many rows (8 for B of up to 16 columns); < 0 = never; 0 = choose by shape, density and n_hint (never when
+                              many rows; < 0 = never; 0 = choose by shape, density and n_hint (8 rows
+                              for hints of at most 64 columns only; never when
                               another setting but n_hint and threads is given, never for host-only
                               plans).  A matrix with a column stored twice in a row, with 2^26 rows or
                               more, or whose tiles find no room on the device while they are built
