@@ -111,10 +111,11 @@ template <typename F> void launch_places(F kernel, tile_args &a, unsigned thread
 // What bounds it: the matrix cores' fp32 rate (157 TFLOP/s dense, 156 measured) times the density.  fp32
 // matrix instructions issue from the vector ALUs (baselines/microbench_paths.hip: a 32x32x2 takes 64.6 cycles, 16
 // integer adds 44.5, both together 108.7), so every vector instruction beside them costs: expanding the
-// blocks from bitmaps in registers took 48 to 130 vector instructions per step, the scatter takes about 20, for
-// 6 bytes per entry instead of 4.3.  8192 x 8192 at 50 %, 128 columns: 134 us = 64 TFLOP/s of the
-// entries' products, 129 TFLOP/s on the matrix cores (110 us at their measured rate); the chunk
-// kernel takes 196 us there.
+// blocks from bitmaps in registers took 48 to 130 vector instructions per step, with the scatter a step has 30
+// in all beside its matrix instructions, for 6 bytes per entry instead of 4.3.  8192 x 8192 at 50 %, 128 columns:
+// 134 us = 64 TFLOP/s of the entries' products, 129 TFLOP/s on the matrix cores (busy 81 % of the time; 110 us at
+// their measured rate); the chunk kernel takes 196 us there.  4096 x 1024 at 30 %, 128 columns, is one round of 256
+// workgroups whose waves make two steps each: 12.3 us, matrix cores busy 55 %.
 template <int R, int NB, int W, bool STAGED, bool WIDE, int MINW>
 __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_args args)
 {
@@ -344,8 +345,8 @@ __device__ __forceinline__ void keep_loads_here() { __builtin_amdgcn_sched_barri
 //
 // What bounds it: with four columns the plan's bytes (2048 x 8192, 70 % pruned: 30 MB in 7.1 us, 2.6 us of them
 // the launch; chunks 15.8, panels of 16 rows 17.1), with sixteen the vector ALUs, which the matrix
-// instructions share (9 to 11 cycles each, measured, of the nominal 8, and some 60 other instructions per step): 10.8 us; chunks
-// 21.4, panels of 16 rows 17.2.  Where a block has 256 entries or fewer, writing zeros to its places
+// instructions share (9 to 11 cycles each, measured, of the nominal 8, and 30 to 40 others per step), and the vector L1 (busy
+// 57 %): 10.0 us; chunks 21.4, panels of 16 rows 17.2.  Where a block has 256 entries or fewer, writing zeros to its places
 // is cheaper than clearing all of it (8192 x 8192, 90 % pruned, 4 columns: 14.7 -> 12.3 us).  Asking for blocks
 // two steps ahead, or sixteen waves, changed nothing; panels of 16 rows of this kind gain 15 % at 8192 rows
 // with 16 columns and lose as much or more elsewhere.
