@@ -46,7 +46,7 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         return nullptr;
     }
     try {
-        const at::Tensor B = THPVariable_Unpack(args[3]);  // kept alive while other threads run
+        const at::Tensor &B = THPVariable_Unpack(args[3]);  // the caller's references keep B and C while other threads run
         if (!(B.is_cuda() && B.scalar_type() == at::kFloat && B.is_contiguous() && B.dim() == 2)) {
             PyErr_SetString(PyExc_ValueError, "B must be a contiguous 2-D float32 device tensor");
             return nullptr;
@@ -61,8 +61,9 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             return nullptr;
         }
         const bool given = args[4] != Py_None;
+        at::Tensor made;
+        const at::Tensor &C = given ? THPVariable_Unpack(args[4]) : made;
         if (given) {
-            const at::Tensor &C = THPVariable_Unpack(args[4]);
             if (!(C.is_cuda() && C.scalar_type() == at::kFloat && C.is_contiguous() && C.dim() == 2 && C.size(0) == M &&
                   C.size(1) == N)) {
                 PyErr_SetString(PyExc_ValueError, "C must be a contiguous float32 device tensor of shape (M, N)");
@@ -79,15 +80,14 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
             Py_DECREF(s);
             if (PyErr_Occurred()) return nullptr;
         }
-        at::Tensor C = given ? THPVariable_Unpack(args[4]) : at::Tensor();
         spmm_status_t st;
         {
             others_run free_to_run;
-            if (!given) C = at::empty({M, N}, B.options().requires_grad(false));
+            if (!given) made = at::empty({M, N}, B.options().requires_grad(false));
             st = spmm_execute(plan, static_cast<const float *>(B.const_data_ptr()), (int32_t)N, static_cast<float *>(C.data_ptr()), stream);
         }
         if (st != SPMM_OK) return PyLong_FromLong((long)st);
-        if (!given) return THPVariable_Wrap(std::move(C));
+        if (!given) return THPVariable_Wrap(std::move(made));
         Py_INCREF(args[4]);
         return args[4];
     } catch (...) {  // as torch's own functions report it, e.g. torch.OutOfMemoryError for the output
