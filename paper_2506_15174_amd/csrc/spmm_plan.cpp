@@ -496,7 +496,7 @@ std::vector<int64_t> range_cuts(const std::vector<Group> &groups, int want)
 // a plan cut along K or across workgroups, and the chunks of the longest piece of a panel cut into eight
 // (hundreds), the tail of the launch where rows are of uneven length.  Against those 600 products the rms error is
 // 12 % (10 to 15 % by width; 0.52 to 1.41 of the time).
-double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
+static double chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
 {
     static const double weights[5][8] = {{2.90, 6.86, 9.60, 0.0, 68.0, 0.0, 4.63, 0.0},   // n_hint <= 8
                                          {2.99, 6.08, 0.0, 0.24, 29.5, 0.0, 5.97, 0.0},   // ... 16
@@ -528,6 +528,15 @@ double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_
            (slices > 1 ? w[5] : 0.0) + (cross ? w[7] : w[6] * 1e-2 * longest / (8.0 * ufk * slices));
 }
 
+double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
+{
+    try {
+        return chunks_time(M, K, row_ptr, n_hint, N);
+    } catch (...) {  // no memory for the rows' lengths
+        return -1.0;
+    }
+}
+
 int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 {
     const int64_t nnz = row_ptr[M];
@@ -535,7 +544,7 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     if (density < 0.03) return 0;           // below all that was measured
     if (nnz < ((int64_t)1 << 17)) return 0;  // mostly the launch's time: 1.5 % on average to gain
     const double N = n_hint <= 0 ? 128 : std::min(std::max(n_hint, 4), 256);
-    double best = 0.95 * spmm_chunks_time(M, K, row_ptr, n_hint, N);
+    double best = 0.95 * chunks_time(M, K, row_ptr, n_hint, N);
     int rows = 0;
     for (int r : {8, 16, 32}) {
         if (r == 8 && N > 64) continue;  // its tiles are 16 columns wide: too small a part of every row of B

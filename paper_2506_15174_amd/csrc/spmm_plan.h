@@ -71,8 +71,8 @@ struct InspectorOptions {
 int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx,
                  const float *vals, const InspectorOptions &opts, HostPlan &out);
 
-// Estimated time in us of a product with N columns of B on the chunk plan made for n_hint columns.  (The linkage
-// is for bench.py, which sets the estimates beside measured times.)
+// Estimated time in us of a product with N columns of B on the chunk plan made for n_hint columns, for
+// bench.py, which sets it beside measured times; -1 where there is no memory for it.
 extern "C" double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N);
 
 // Rows per panel (32, 16 or 8) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.
