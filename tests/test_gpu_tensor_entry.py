@@ -1,4 +1,4 @@
-"""The native tensor-level entry behind Plan.execute (GPU machine only)."""
+"""The native tensor-level entry behind Plan.execute (needs the GPU)."""
 import sys
 import threading
 import time
