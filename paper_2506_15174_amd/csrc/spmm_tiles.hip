@@ -16,6 +16,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int OPS = TILE_OPERANDS;
 constexpr int NARROW_ROWS = 8;
@@ -66,6 +67,7 @@ template <> struct Tile<32> {
     typedef f32x16 acc_t;
     static constexpr int GROUPS = 4;  // groups of four accumulator registers
     static __device__ __forceinline__ acc_t mfma(float b, float a, const acc_t &c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, c, 0, 0, 0); }
+    static __device__ __forceinline__ acc_t mfma(const bf16x8 &b, const bf16x8 &a, const acc_t &c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0); }
 };
 template <> struct Tile<16> {
     typedef f32x4 acc_t;
@@ -92,6 +94,55 @@ template <typename F> void launch_places(F kernel, tile_args &a, unsigned thread
     }
 }
 
+// Adds the waves' tiles, in a fixed order, and stores the sum: the upper half of the waves parks its tiles in
+// LDS, the lower half adds them to its own, then all waves share the rest of the sum.
+template <int R, int NB, int W> __device__ __forceinline__ void store_sum_of_waves(const tile_args &args, const typename Tile<R>::acc_t (&acc)[NB], float *lds,
+                                                                                  uint32_t panel, uint32_t n0, int wave, int lane)
+{
+    constexpr int KO = 64 / R, QUADS = NB * Tile<R>::GROUPS;
+    const uint32_t N = (uint32_t)args.N;
+    f32x4 quad[QUADS];
+#pragma unroll
+    for (int f = 0; f < QUADS; ++f) {
+        const int g = f / NB, q = f % NB;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) quad[f][x] = acc[(4 * q + x) % NB][4 * g + (4 * q + x) / NB];
+    }
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+    __syncthreads();
+    if (wave >= W / 2) {
+#pragma unroll
+        for (int f = 0; f < QUADS; ++f) red[((wave - W / 2) * QUADS + f) * 64 + lane] = quad[f];
+    }
+    __syncthreads();
+    if (wave < W / 2) {
+#pragma unroll
+        for (int f = 0; f < QUADS; ++f) {
+            f32x4 *p = &red[(wave * QUADS + f) * 64 + lane];
+            *p = quad[f] + *p;
+        }
+    }
+    __syncthreads();
+    const uint32_t row = panel * (uint32_t)R + (uint32_t)(lane % R);
+    if (row >= (uint32_t)args.M) return;
+#pragma unroll
+    for (int f0 = 0; f0 < QUADS; f0 += W) {
+        const int f = f0 + wave;
+        if (f >= QUADS) break;
+        f32x4 sum = red[f * 64 + lane];
+#pragma unroll
+        for (int u = 1; u < W / 2; ++u) sum += red[(u * QUADS + f) * 64 + lane];
+        const uint32_t n = n0 + (uint32_t)(NB * (4 * KO * (f / NB) + 4 * (lane / R)) + 4 * (f % NB));
+        float *dst = args.C + (size_t)row * N + n;
+        if (n + 4 <= N) {
+            *reinterpret_cast<f32x4_unaligned *>(dst) = sum;
+        } else {
+            for (uint32_t x = 0; x < 4; ++x)
+                if (n + x < N) dst[x] = sum[(int)x];
+        }
+    }
+}
+
 // One workgroup computes a tile of C: R rows x NB * R columns.
 //
 // R       rows of a panel (32: v_mfma_f32_32x32x2, 16: v_mfma_f32_16x16x4; fp32 operands and sums)
@@ -108,13 +159,13 @@ template <typename F> void launch_places(F kernel, tile_args &a, unsigned thread
 // places in a zeroed 4 KiB slot of LDS, read back as 16 operands per lane (four 16-byte reads), the
 // slot is zeroed again for the next block, and 16 * NB matrix instructions multiply.
 //
+// (32 rows x 128 columns: only WIDE; spmm_split_tiles_kernel below has the others.)
+//
 // What bounds it: the matrix cores' fp32 rate (157 TFLOP/s dense, 156 measured) times the density.  fp32
 // matrix instructions issue from the vector ALUs (baselines/microbench_paths.hip: a 32x32x2 takes 64.6 cycles, 16
 // integer adds 44.5, both together 108.7), so every vector instruction beside them costs: expanding the
 // blocks from bitmaps in registers took 48 to 130 vector instructions per step, with the scatter a step has 30
-// in all beside its matrix instructions, for 6 bytes per entry instead of 4.3.  8192 x 8192 at 50 %, 128 columns:
-// 134 us = 64 TFLOP/s of the entries' products, 129 TFLOP/s on the matrix cores (busy 81 % of the time; 110 us at
-// their measured rate); the chunk kernel takes 196 us there.  4096 x 1024 at 30 %, 128 columns, is one round of 256
+// in all beside its matrix instructions, for 6 bytes per entry instead of 4.3.  4096 x 1024 at 30 %, 128 columns, is one round of 256
 // workgroups whose waves make two steps each: 12.3 us, matrix cores busy 55 %.
 template <int R, int NB, int W, bool STAGED, bool WIDE, int MINW>
 __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_args args)
@@ -271,54 +322,252 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
         }
     }
 
-    // ---- add the waves' tiles: the upper half of the waves parks its tiles, the lower half
-    //      adds them to its own, then all waves share the rest of the sum (fixed order)
-    f32x4 quad[QUADS];
-#pragma unroll
-    for (int f = 0; f < QUADS; ++f) {
-        const int g = f / NB, q = f % NB;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) quad[f][x] = acc[(4 * q + x) % NB][4 * g + (4 * q + x) / NB];
-    }
-    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
-    __syncthreads();
-    if (wave >= W / 2) {
-#pragma unroll
-        for (int f = 0; f < QUADS; ++f) red[((wave - W / 2) * QUADS + f) * 64 + lane] = quad[f];
-    }
-    __syncthreads();
-    if (wave < W / 2) {
-#pragma unroll
-        for (int f = 0; f < QUADS; ++f) {
-            f32x4 *p = &red[(wave * QUADS + f) * 64 + lane];
-            *p = quad[f] + *p;
-        }
-    }
-    __syncthreads();
-    const uint32_t row = panel * (uint32_t)R + (uint32_t)(lane % R);
-    if (row >= (uint32_t)args.M) return;
-#pragma unroll
-    for (int f0 = 0; f0 < QUADS; f0 += W) {
-        const int f = f0 + wave;
-        if (f >= QUADS) break;
-        f32x4 sum = red[f * 64 + lane];
-#pragma unroll
-        for (int u = 1; u < W / 2; ++u) sum += red[(u * QUADS + f) * 64 + lane];
-        const uint32_t n = n0 + (uint32_t)(NB * (4 * KO * (f / NB) + 4 * (lane / R)) + 4 * (f % NB));
-        float *dst = args.C + (size_t)row * N + n;
-        if (n + 4 <= N) {
-            *reinterpret_cast<f32x4_unaligned *>(dst) = sum;
-        } else {
-            for (uint32_t x = 0; x < 4; ++x)
-                if (n + x < N) dst[x] = sum[(int)x];
-        }
-    }
+    store_sum_of_waves<R, NB, W>(args, acc, lds, panel, n0, wave, lane);
 }
 
 template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void launch(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (int32_t)(((int64_t)a.N + NB * R - 1) / (NB * R));
     launch_places(spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>, a, 64 * W, s);
+}
+
+// ---------------------------------------------------------------- executor, fp32 values in three bf16 parts
+
+// Eight values as h + m + l: the upper 16 bits, what is left rounded to bf16, and what is left of that.  A float
+// has 24 significant bits and the parts 8 each, so the sum is exact; only where the last part falls below the
+// smallest bf16 (values under 2^-101) is it not, and then `lost` gets a bit among its lower 16.
+struct parts {
+    bf16x8 h, m, l;
+};
+__device__ __forceinline__ parts in_parts(const float (&x)[8], uint32_t &lost)
+{
+    constexpr uint32_t UPPER = 0xFFFF0000u;
+    u32x4 h, m, l;
+    float r[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] = x[i] - __uint_as_float(__float_as_uint(x[i]) & UPPER);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        h[i] = __builtin_amdgcn_perm(__float_as_uint(x[2 * i + 1]), __float_as_uint(x[2 * i]), 0x07060302u);
+        // (a conversion of a vector would be done twice, once for each way its result is used)
+        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(m[i]) : "v"(r[2 * i]), "v"(r[2 * i + 1]));
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] -= __uint_as_float(i % 2 ? m[i / 2] & UPPER : m[i / 2] << 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        l[i] = __builtin_amdgcn_perm(__float_as_uint(r[2 * i + 1]), __float_as_uint(r[2 * i]), 0x07060302u);
+        lost |= __float_as_uint(r[2 * i]) | __float_as_uint(r[2 * i + 1]);
+    }
+    return parts{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+// What the parts are made of is not used after this point.  (The compiler would keep all terms of `lost` until the end.)
+__device__ __forceinline__ void parts_done(parts &p, uint32_t &lost) { asm volatile("" : "+v"(p.h), "+v"(p.m), "+v"(p.l), "+v"(lost)); }
+
+// N KiB from the start of `r` to `to`.  The load's last offset, a constant of the instruction, counts in both memories.
+template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, float *to, int lane)
+{
+    if constexpr (N > 1) load_to_lds<N - 1>(r, to, lane);
+    constexpr int Q = N - 1;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)(to + 1024 * (Q / 4)), 16, lane * 16 + 4096 * (Q / 4), 0,
+                                             1024 * (Q % 4), 0);
+}
+
+// The tile of 32 rows x 128 columns on the bf16 matrix instructions (v_mfma_f32_32x32x16, sixteen times the
+// products per cycle of the fp32 ones): every fp32 product is the sum of six products of parts,
+// h h + (h m + m h) + (m m + h l + l h), which the instructions multiply exactly and add in fp32.  The three that are left
+// out are below 2^-23 of the product, 2^-27 on average.  The sums of h h and of the five small ones are kept apart and added at the end: the large
+// sums are then rounded once per 16 columns of A, where the fp32 instructions round once per two.  8192 x 8192, 50 %
+// pruned, 128 columns: error of the result (2-norm, against 64 bits) 1.2e-7, with fp32 instructions 4.1e-7.
+//
+// Where a value has no exact parts or a sum is not finite the wave multiplies all of its steps again with fp32
+// instructions, so that the results of tiny, huge and non-finite values are those of the kernel above.
+//
+// AL      loads of 1 KiB that hold any block of the plan
+//
+// Blocks pass through LDS twice: as they are stored (buffer_load .. lds, two steps ahead, no registers), then
+// expanded as above.  Rows of B come straight to registers, half a step (16 rows) at a time and a step ahead,
+// and a column group of them is split right before its six instructions.
+//
+// What bounds it: 8192 x 8192, 50 % pruned, 128 columns take 123 us, with fp32 instructions 142; 16384 x 2048, 70 % pruned, 67
+// and 82.  The matrix cores are busy 39 % of the time; 11 vector instructions beside each of theirs (192 per 16 rows for B, which
+// every panel splits anew, 48 for A) overlap with it only in part, and the power limit holds the clock to 2 GHz.  Splitting B once, in a launch
+// of its own, leaves 2.6 vector instructions but moves 6 bytes per value, 19 TB/s through the L2s: 15 % faster, for a workspace that
+// spmm_execute does not have.  One wave per SIMD with everything interleaved is slower: a single wave issues an instruction every
+// 5 cycles only.
+template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_kernel(const tile_args args)
+{
+    constexpr int W = 8, R = 32, NB = 4, NT = NB * R, KO = 64 / R, KS = OPS * KO;
+    constexpr int RUNS = (AL * 1024 / 6 + 255) / 256;  // runs of 256 entries in a block
+    constexpr int STAGE_WORDS = 256 * AL, SLOT = A_SLOT_WORDS + 2 * STAGE_WORDS;
+    static_assert(RUNS * 256 * 4 <= STAGE_WORDS * 4 && W * SLOT >= W / 2 * NB * Tile<R>::GROUPS * 256, "reads of whole runs stay in the stage; the sums fit");
+    __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
+
+    const uint32_t id = place_in_matrix(args.first), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
+    if (panel >= (uint32_t)args.n_panels) return;
+    const uint32_t n0 = nt * (uint32_t)NT;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = (int)(threadIdx.x & 63);
+    float *slot = lds + wave * SLOT, *stages = slot + A_SLOT_WORDS;
+    f32x4 *expanded = reinterpret_cast<f32x4 *>(slot + TILE_PLACE0 / 4) + lane;
+    const uint32_t n_steps = (uint32_t)args.n_steps;
+    const uint32_t *off_p = args.offsets + (size_t)panel * (n_steps + 1);
+    const uint32_t N = (uint32_t)args.N;
+    const uint32_t count = n_steps > (uint32_t)wave ? (n_steps - (uint32_t)wave + W - 1) / W : 0u;  // steps of this wave
+
+    f32x16 acc[NB], cor[NB];  // sums of h h; of the other products
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j] = cor[j] = f32x16{};
+    uint32_t lost = 0;
+#pragma unroll
+    for (int q = 0; q < OPS / 4; ++q) expanded[64 * q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // Runs of 64 steps: lane i holds the bounds of the i-th block of the run.  (Loaded inside of the pipeline
+    // they would make every step wait for all loads on their way.)
+    uint32_t lo = 0, hi = 0, last = 0;
+    uint32_t n_in[2];  // entries of the blocks in the two stages
+    auto bounds = [&](uint32_t first) {
+        last = first + 64u < count ? first + 64u : count;
+        const uint32_t s = (uint32_t)wave + W * (first + (uint32_t)lane);
+        lo = s < n_steps ? off_p[s] : 0u;
+        hi = s < n_steps ? off_p[s + 1] : 0u;
+    };
+    // The compiler knows of these loads and of those of B and counts its waits by both: every step makes the
+    // same number of them, in this order (no load passes the empty asm).
+    auto fetch_a = [&](uint32_t i, int st) {  // nothing past the run
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)lo, (int)(i & 63u));
+        const uint32_t units = i < last ? (uint32_t)__builtin_amdgcn_readlane((int)hi, (int)(i & 63u)) - a : 0u;
+        n_in[st] = 8u * units;
+        const char *block = reinterpret_cast<const char *>(args.stream) + (size_t)a * 48u;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(block), (short)0, (int)(units * 48u), 0x00020000);
+        load_to_lds<AL>(r, stages + st * STAGE_WORDS, lane);
+        asm volatile("" ::: "memory");
+    };
+    // Every entry of the stage to its place in the expanded block, which is all zeros at this point; what lies
+    // behind the last one to the dump word.  All reads first: one wait for LDS and not one per run.
+    auto scatter = [&](int st) {
+        f32x4 v[RUNS];
+        u32x2 place[RUNS];
+        const uint32_t n = n_in[st];
+        const float *stage = stages + st * STAGE_WORDS;
+        const char *places = reinterpret_cast<const char *>(stage) + n * 4u;
+#pragma unroll
+        for (int q = 0; q < RUNS; ++q) {
+            v[q] = *reinterpret_cast<const f32x4 *>(stage + 4 * lane + 256 * q);
+            place[q] = *reinterpret_cast<const u32x2 *>(places + 8 * lane + 512 * q);
+        }
+        char *cslot = reinterpret_cast<char *>(slot);
+#pragma unroll
+        for (int q = 0; q < RUNS; ++q) {
+            const bool in = (uint32_t)lane * 4u + 256u * (uint32_t)q < n;
+            const u32x2 p = u32x2{in ? place[q][0] : 0u, in ? place[q][1] : 0u};
+#pragma unroll
+            for (int x = 0; x < 4; ++x) *reinterpret_cast<float *>(cslot + ((p[x / 2] >> (16 * (x % 2))) & 0xFFFFu)) = v[q][x];
+        }
+        lds_in_order();
+    };
+    // Rows of B from step s on
+    auto b_rsrc = [&](uint32_t s) {
+        const uint64_t skip = ((uint64_t)s * KS * N + n0) * 4u;
+        const uint64_t left = args.b_bytes > skip ? args.b_bytes - skip : 0u;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(args.B)) + skip, (short)0,
+                                                 (int)(left > 0xFFFFFFFCull ? 0xFFFFFFFCu : (uint32_t)left), 0x00020000);
+    };
+    const uint32_t lane_off = ((uint32_t)(lane / R) * N + (uint32_t)(NB * (lane % R))) * 4u, op_pitch = (uint32_t)KO * N * 4u;
+    f32x4 b[2][8];  // halves of a step
+    auto fetch_b = [&](uint32_t i, int half) {  // no rows past the last step
+        const __amdgpu_buffer_rsrc_t r = b_rsrc((uint32_t)wave + W * i);
+        uint32_t off = lane_off + (uint32_t)(8 * half) * op_pitch;
+        asm volatile("" : "+v"(off));  // one address register, not one per row
+#pragma unroll
+        for (int t = 0; t < 8; ++t, off += op_pitch) b[half][t] = buffer_load<4>(r, off);
+        asm volatile("" ::: "memory");
+    };
+    auto multiply_half = [&](uint32_t i, int half) {
+        float x[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) x[t] = expanded[64 * (2 * half + t / 4)][t % 4];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) expanded[64 * (2 * half + q)] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        parts a = in_parts(x, lost);
+        parts_done(a, lost);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) x[t] = b[half][t][j];
+            // not before this point: two groups of parts do not fit the registers
+            asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
+            parts p = in_parts(x, lost);
+            parts_done(p, lost);
+            if (j == NB - 1) fetch_b(i + 1, half);
+            cor[j] = Tile<R>::mfma(p.l, a.h, cor[j]);
+            cor[j] = Tile<R>::mfma(p.h, a.l, cor[j]);
+            cor[j] = Tile<R>::mfma(p.m, a.m, cor[j]);
+            cor[j] = Tile<R>::mfma(p.m, a.h, cor[j]);
+            cor[j] = Tile<R>::mfma(p.h, a.m, cor[j]);
+            acc[j] = Tile<R>::mfma(p.h, a.h, acc[j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    for (uint32_t first = 0; first < count; first = last) {
+        bounds(first);
+        fetch_a(first, 0);
+        fetch_a(first + 1, 1);
+        fetch_b(first, 0);
+        fetch_b(first, 1);
+        for (uint32_t i = first; i < last; i += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u == 1 && i + 1 >= last) break;
+                // the step's block has arrived: younger are the other stage's and 16 loads of B
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AL + 16) : "memory");
+                scatter(u);
+                fetch_a(i + (uint32_t)u + 2u, u);
+                multiply_half(i + (uint32_t)u, 0);
+                multiply_half(i + (uint32_t)u, 1);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no block on its way to the stages
+    }
+
+    float bad = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        acc[j] += cor[j];
+#pragma unroll
+        for (int x = 0; x < 16; ++x) bad = __builtin_fmaf(acc[j][x], 0.0f, bad);
+    }
+    if (__builtin_expect(__any((lost & 0xFFFFu) != 0 || bad != 0.0f), 0)) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[j] = f32x16{};
+#pragma unroll 1
+        for (uint32_t i = 0; i < count; ++i) {
+            if ((i & 63u) == 0) bounds(i);
+            fetch_a(i, 0);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            scatter(0);
+            const __amdgpu_buffer_rsrc_t r = b_rsrc((uint32_t)wave + W * i);
+#pragma unroll 1
+            for (int t = 0; t < OPS; ++t) {
+                float *e = reinterpret_cast<float *>(expanded + 64 * (t / 4)) + t % 4;
+                const float a = *e;
+                *e = 0.0f;
+                const f32x4 bt = buffer_load<4>(r, lane_off + (uint32_t)t * op_pitch);
+#pragma unroll
+                for (int j = 0; j < NB; ++j) acc[j] = Tile<R>::mfma(bt[j], a, acc[j]);
+            }
+            lds_in_order();
+        }
+    }
+    store_sum_of_waves<R, NB, W>(args, acc, lds, panel, n0, wave, lane);
+}
+
+template <int AL> void launch_split(tile_args &a, hipStream_t s)
+{
+    a.n_tiles = (int32_t)(((int64_t)a.N + 127) / 128);
+    launch_places(spmm_split_tiles_kernel<AL>, a, 512, s);
 }
 
 // ---------------------------------------------------------------- executor, narrow panels
@@ -857,14 +1106,16 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
                1e-3 * (double)steps * ns_density[i] * (peak - density);
     }
     // A compute unit holds one workgroup at a time.
-    static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 246, 477}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.1, 4.3}};  // R = 16, 32; NB = 1, 2, 4
+    // R = 16, 32; NB = 1, 2, 4 (the last one on bf16 instructions: 113 us for 8192 x 8192, 70 % pruned, 128 columns, 142 on fp32 ones)
+    static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 246, 365}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.1, 4.3}},
+                        ns_density[2][3] = {{60, 60, 60}, {60, 60, 150}};
     double best = 0.0;
     for (int i = 0, NB = 1; i < 3; ++i, NB *= 2) {
         if (NB > 1 && rows * NB >= 2 * N) break;  // more than half of the tile idle
         const int64_t blocks = panels * ((N + rows * NB - 1) / (rows * NB));
-        const double ns = ns_per_step[rows == 32][i] + 60.0 * std::max(0.0, density - 0.1);
+        const double more = ns_density[rows == 32][i], ns = ns_per_step[rows == 32][i] + more * std::max(0.0, density - 0.1);
         const double t = 1.1 + (double)((blocks + 255) / 256) * (1e-3 * (double)steps * ns + us_per_round[rows == 32][i]) +
-                         1e-3 * (double)steps * 60.0 * (peak - density);
+                         1e-3 * (double)steps * more * (peak - density);
         if (i == 0 || t < best) {
             best = t;
             if (NB_out) *NB_out = NB;
@@ -895,7 +1146,12 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
     int NB = 1;
     spmm_tiles_time(p.rows, M, K, N, 0.0, 0.0, &NB);
     switch (p.rows * 8 + NB) {
-    case 32 * 8 + 4: launch<32, 4, 8, false, 2>(a, s); break;
+    case 32 * 8 + 4:
+        if (p.loads == 1) launch_split<2>(a, s);
+        else if (p.loads == 2) launch_split<3>(a, s);
+        else if (p.loads == 3) launch_split<5>(a, s);
+        else launch_split<6>(a, s);
+        break;
     case 32 * 8 + 2: launch<32, 2, 16, false, 4>(a, s); break;
     case 32 * 8 + 1: launch<32, 1, 16, true, 4>(a, s); break;
     case 16 * 8 + 4: launch<16, 4, 8, false, 2>(a, s); break;

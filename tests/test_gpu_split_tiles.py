@@ -1,0 +1,103 @@
+"""Panels of 32 rows x 128 columns on bf16 matrix instructions (values in three parts) against the CPU oracle,
+through the C ABI (GPU machine only)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2506_15174_amd as spmm
+from workloads import generators as gen
+
+from test_gpu_parity import gpu_product, torch_gpu  # noqa: F401  (fixture)
+from test_gpu_tiles import integer_matrix
+
+pytestmark = pytest.mark.gpu
+
+WIDE = 128 * 128   # columns enough that one panel or two are multiplied in tiles of 128 columns
+
+
+def product(torch_gpu, csr, B):  # noqa: F811
+    """The product, of which the plan has to run in tiles of four column groups."""
+    lib, nb = spmm.load(), ctypes.c_int(0)
+    lib.spmm_tiles_time.restype = ctypes.c_double
+    lib.spmm_tiles_time(32, ctypes.c_int64(csr.M), ctypes.c_int64(csr.K), ctypes.c_int64(B.shape[1]), ctypes.c_double(0),
+                        ctypes.c_double(0), ctypes.byref(nb))
+    assert nb.value == 4
+    C, plan = gpu_product(torch_gpu, csr, B, guard_rows=2, tiles=32)
+    assert plan.describe()["tile_rows"] == 32
+    return C
+
+
+@pytest.mark.parametrize("M,K,N,density", [
+    (64, 1, WIDE, 0.5), (33, 31, WIDE - 1, 1.0), (40, 257, WIDE - 5, 0.2), (64, 300, WIDE, 0.45), (64, 520, WIDE - 124, 0.7),
+    (8192, 300, 100, 0.4), (8190, 545, 128, 1.0), (4090, 800, 200, 0.3), (9000, 64, 127, 0.6)])
+def test_bit_exact_on_integer_data(torch_gpu, oracle, M, K, N, density):  # noqa: F811
+    """Fewer steps than waves, odd and even numbers of them, rows, columns and steps cut short; blocks of one
+    to four runs of 256 entries."""
+    csr = integer_matrix(M, K, density, M + K)
+    B = np.random.default_rng(N).integers(-16, 17, (K, N)).astype(np.float32)
+    C = product(torch_gpu, csr, B)
+    C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B, parallel=True)
+    assert np.abs(C_ref).max() < 2 ** 24
+    assert np.array_equal(C.astype(np.float64), C_ref)
+
+
+def test_more_steps_than_a_run_of_bounds(torch_gpu):  # noqa: F811
+    """65 steps and more per wave.  Integer data, compared on the device in 64 bits."""
+    torch = torch_gpu
+    M, K, N = 32, 32 * 8 * 65 + 40, WIDE
+    csr = integer_matrix(M, K, 0.3, 3)
+    dense = torch.zeros((M, K), device="cuda", dtype=torch.float64)
+    rows = np.repeat(np.arange(M), np.diff(csr.row_ptr))
+    dense[torch.from_numpy(rows).cuda(), torch.from_numpy(csr.col_idx).cuda().long()] = torch.from_numpy(csr.vals).cuda().double()
+    B = torch.randint(-4, 5, (K, N), device="cuda", dtype=torch.int8).to(torch.float32)
+    plan = spmm.plan_create(M, K, csr.row_ptr, csr.col_idx, csr.vals, tiles=32)
+    C = plan.execute(B)
+    for j in range(0, N, 2048):
+        assert torch.equal(C[:, j:j + 2048].double(), dense @ B[:, j:j + 2048].double())
+
+
+def few_entries(M, K, seed, scale):
+    """Two entries in every row, one on its own in every eighth."""
+    rng = np.random.default_rng(seed)
+    W = np.zeros((M, K), np.float32)
+    for i in range(M):
+        n = 1 if i % 8 == 0 else 2
+        W[i, rng.choice(K, n, replace=False)] = (rng.standard_normal(n) * scale).astype(np.float32)
+    return gen.csr_from_dense(W)
+
+
+@pytest.mark.parametrize("a_scale,b_scale", [(1.0, 1.0), (1e-20, 1e10), (1.0, 1e-36), (1e-36, 1.0), (1e-39, 1.0), (1.0, 1e-39), (1e-10, 1e38),
+                                             (1e38, 1e-20)])
+def test_every_part_of_a_product_counts(torch_gpu, oracle, a_scale, b_scale):  # noqa: F811
+    """Sums of one or two products, so that nothing averages out.  Bound: a product's parts left out are below
+    2^-23 of it, and there are at most twelve fp32 roundings, all but two of sums below 2^-7 of the result's terms: 2^-21.
+    In the range of subnormal results add their spacing.  Values whose parts are not all normal (1e-36), subnormal ones and the largest."""
+    csr = few_entries(64, 90, 5, a_scale)
+    B = (np.random.default_rng(6).standard_normal((90, WIDE)) * b_scale).clip(-3.4e38, 3.4e38).astype(np.float32)
+    B[3, :64] = np.float32(3.4028235e38) * min(1.0, b_scale)   # the largest float rounds up to no bf16
+    C = product(torch_gpu, csr, B)
+    C_ref, S = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B, parallel=True)
+    fits = S < 3.4e38
+    assert fits.mean() > 0.5
+    assert (np.abs(C - C_ref)[fits] <= 2.0 ** -21 * S[fits] + 3 * 2.0 ** -149).all()
+
+
+def test_a_few_tiny_values_among_ordinary_ones(torch_gpu, oracle):  # noqa: F811
+    csr = few_entries(64, 300, 7, 1.0)
+    B = np.random.default_rng(8).standard_normal((300, WIDE)).astype(np.float32)
+    B[::7] *= np.float32(1e-37)
+    C = product(torch_gpu, csr, B)
+    C_ref, S = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B, parallel=True)
+    assert (np.abs(C - C_ref) <= 2.0 ** -21 * S + 3 * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_how_far_a_value_outside_the_domain_reaches(torch_gpu, value):  # noqa: F811
+    """As on the other tiles: its column of C and no other."""
+    csr = gen.uniform_positions(64, 256, 0.5, 15)
+    B = gen.dense_activations(csr.K, WIDE, 16)
+    B[100, 7] = value
+    C = product(torch_gpu, csr, B)
+    finite = np.isfinite(C)
+    assert not finite[:, 7].any() and np.delete(finite, 7, axis=1).all()
