@@ -914,6 +914,90 @@ __global__ __launch_bounds__(256) void scan_panel_kernel(int64_t n_steps, uint32
     }
 }
 
+// The three kernels above in one, for panels whose bitmaps fit LDS: a workgroup per panel sets the bits there,
+// orders the blocks and adds up their lengths.  (4096 x 4096, 80 % pruned, panels of 16 rows: the bits alone, an atomic
+// operation in global memory for every entry, took most of 150 us; the three together now take 22.)
+constexpr int64_t MOST_STEPS_IN_LDS = 1024;  // 128 KiB of bitmaps; one step per thread while the lengths are added
+template <int R> __global__ __launch_bounds__(1024) void panel_kernel(const int32_t *row_ptr, const int32_t *col_idx, int64_t M, int64_t K, int32_t n_steps,
+                                                                      uint32_t *masks, block_order *order, uint32_t *counts, uint32_t *offsets,
+                                                                      uint64_t *panel_base, uint32_t *flags, uint32_t *longest)
+{
+    extern __shared__ uint32_t bits[];
+    __shared__ uint32_t units[1024], sums[16];
+    constexpr int WAVES = 16, PER_ROW = R < WAVES ? WAVES / R : 1;  // waves per row
+    const int64_t panel = blockIdx.x;
+    const int wave = (int)(threadIdx.x / 64), lane = (int)(threadIdx.x & 63);
+    for (int32_t i = (int32_t)threadIdx.x; i < n_steps * MASK_WORDS; i += 1024) bits[i] = 0;
+    __syncthreads();
+    uint32_t bad = 0;
+    for (int r = wave / PER_ROW; r < R; r += WAVES / PER_ROW) {
+        const int64_t row = panel * R + r;
+        if (row >= M) break;
+        for (int64_t q = row_ptr[row] + (int64_t)(wave % PER_ROW * 64 + lane); q < row_ptr[row + 1]; q += 64 * PER_ROW) {
+            const int32_t c = col_idx[q];
+            if (c < 0 || (int64_t)c >= K) {
+                bad |= BAD_COLUMN;
+                continue;
+            }
+            const position p = position_of<R>((uint32_t)row, (uint32_t)c);
+            const bank k = bank_of(p);
+            const uint32_t bit = 1u << (k.of % 2 * 16 + k.rank_bit);
+            if (atomicOr(&bits[p.step * MASK_WORDS + k.of / 2], bit) & bit) bad |= TWICE;
+        }
+    }
+    if (bad) atomicOr(flags, bad);
+    __syncthreads();
+    uint32_t most = 0;
+    for (int32_t s = wave; s < n_steps; s += WAVES) {
+        const int64_t b = panel * n_steps + s;
+        const uint32_t mask = bits[s * MASK_WORDS + lane / 2], mine = __builtin_popcount(mask >> (lane % 2 * 16) & 0xFFFFu);
+        if (lane % 2 == 0) masks[(size_t)b * MASK_WORDS + lane / 2] = mask;
+        uint32_t n = 0;
+        uint64_t my_classes = 0;
+        uint32_t my_first = 0;
+#pragma unroll 4
+        for (int r = 0; r < 16; ++r) {
+            const uint64_t classes = __ballot(mine > (uint32_t)r);
+            if (lane == r) {
+                my_classes = classes;
+                my_first = n;
+            }
+            n += (uint32_t)__builtin_popcountll(classes);
+        }
+        if (lane < 16) {
+            order[b].classes[lane] = my_classes;
+            order[b].first[lane] = (uint16_t)my_first;
+        }
+        if (lane == 0) {
+            counts[b] = n;
+            units[s] = (n + 7) / 8;
+        }
+        most = n > most ? n : most;
+    }
+    if (lane == 0 && most > *longest) atomicMax(longest, most);
+    __syncthreads();
+    // thread s: the length of step s, then the sum up to it
+    const uint32_t mine = (int32_t)threadIdx.x < n_steps ? units[threadIdx.x] : 0u;
+    uint32_t sum = mine;
+    for (int d = 1; d < 64; d *= 2) {
+        const uint32_t below = __shfl_up(sum, d);
+        if (lane >= d) sum += below;
+    }
+    if (lane == 63) sums[wave] = sum;
+    __syncthreads();
+    uint32_t before = 0, total = 0;
+    for (int w = 0; w < WAVES; ++w) {
+        before += w < wave ? sums[w] : 0u;
+        total += sums[w];
+    }
+    uint32_t *o = offsets + (size_t)panel * ((size_t)n_steps + 1);
+    if ((int32_t)threadIdx.x < n_steps) o[threadIdx.x] = before + sum - mine;
+    if (threadIdx.x == 0) {
+        o[n_steps] = total;
+        panel_base[panel] = total;
+    }
+}
+
 // One workgroup: panel lengths -> panel starts; panel_base[n_panels] = length of everything.
 __global__ __launch_bounds__(256) void scan_all_kernel(int64_t n_panels, uint64_t *panel_base)
 {
@@ -1016,7 +1100,8 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     const size_t at_ptr = memory.reserve((size_t)(M + 1) * 4), at_col = memory.reserve((size_t)nnz * 4), at_val = memory.reserve((size_t)nnz * 4),
                  at_base = memory.reserve((size_t)(P + 2) * 8), at_masks = memory.reserve(mask_bytes),
                  at_order = memory.reserve((size_t)(P * S) * sizeof(block_order)), at_counts = memory.reserve((size_t)(P * S) * 4);
-    const size_t zeros = at_masks + mask_bytes - at_base;  // the panels' lengths, the flags behind them, the masks
+    // the panels' lengths, the flags behind them, the masks (which panel_kernel writes whole)
+    const size_t zeros = (S <= MOST_STEPS_IN_LDS ? at_masks : at_masks + mask_bytes) - at_base;
     TRY(memory.take());
     int32_t *d_ptr = memory.at<int32_t>(at_ptr), *d_col = memory.at<int32_t>(at_col);
     float *d_val = memory.at<float>(at_val);
@@ -1030,9 +1115,14 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<size_t>(4096, zeros / 4096 + 1)), dim3(256), 0, s, memory.at<u32x4>(at_base), (int64_t)(zeros / 16));
     TRY(hipMemcpyWithStream(d_ptr, row_ptr, (size_t)(M + 1) * 4, hipMemcpyHostToDevice, s));
     TRY(hipMemcpyWithStream(d_col, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL((mark_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr, d_col, M, K, S, d_masks, flags);
-    hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks, P, S, d_order, d_counts, out.d_offsets, flags + 1);
-    hipLaunchKernelGGL(scan_panel_kernel, dim3((unsigned)P), dim3(256), 0, s, S, out.d_offsets, base);
+    if (S <= MOST_STEPS_IN_LDS) {
+        hipLaunchKernelGGL((panel_kernel<R>), dim3((unsigned)P), dim3(1024), (unsigned)(S * MASK_WORDS * 4), s, d_ptr, d_col, M, K, (int32_t)S, d_masks, d_order,
+                           d_counts, out.d_offsets, base, flags, flags + 1);
+    } else {
+        hipLaunchKernelGGL((mark_kernel<R>), dim3(row_blocks), dim3(256), 0, s, d_ptr, d_col, M, K, S, d_masks, flags);
+        hipLaunchKernelGGL(measure_kernel, dim3(block_blocks), dim3(256), 0, s, d_masks, P, S, d_order, d_counts, out.d_offsets, flags + 1);
+        hipLaunchKernelGGL(scan_panel_kernel, dim3((unsigned)P), dim3(256), 0, s, S, out.d_offsets, base);
+    }
     hipLaunchKernelGGL(scan_all_kernel, dim3(1), dim3(256), 0, s, P, base);
     TRY(hipGetLastError());
     TRY(hipMemcpyWithStream(d_val, vals, (size_t)nnz * 4, hipMemcpyHostToDevice, s));  // the kernels run meanwhile
