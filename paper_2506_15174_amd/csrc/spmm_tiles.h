@@ -24,6 +24,7 @@ struct TilePlan {
     uint32_t *d_stream = nullptr;   // DEVICE blocks
     uint32_t *d_offsets = nullptr;  // DEVICE n_panels * (n_steps + 1) block starts
     int64_t stream_words = 0, device_bytes = 0;
+    bool built = false;             // whole
 };
 
 constexpr int TILE_OPERANDS = 16;
