@@ -166,14 +166,13 @@ template <int R, int NB, int W> __device__ __forceinline__ void store_sum_of_wav
 // places in a zeroed 4 KiB slot of LDS, read back as 16 operands per lane (four 16-byte reads), the
 // slot is zeroed again for the next block, and 16 * NB matrix instructions multiply.
 //
-// (32 rows x 128 columns: only WIDE; spmm_split_tiles_kernel below has the others.)
+// (32 rows x 128 columns: only WIDE; 32 x 64: only few steps; spmm_split_tiles_kernel below has the others.)
 //
 // What bounds it: the matrix cores' fp32 rate (157 TFLOP/s dense, 156 measured) times the density.  fp32
 // matrix instructions issue from the vector ALUs (baselines/microbench_paths.hip: a 32x32x2 takes 64.6 cycles, 16
 // integer adds 44.5, both together 108.7), so every vector instruction beside them costs: expanding the
 // blocks from bitmaps in registers took 48 to 130 vector instructions per step, with the scatter a step has 30
-// in all beside its matrix instructions, for 6 bytes per entry instead of 4.3.  4096 x 1024 at 30 %, 128 columns, is one round of 256
-// workgroups whose waves make two steps each: 12.3 us, matrix cores busy 55 %.
+// in all beside its matrix instructions, for 6 bytes per entry instead of 4.3.
 template <int R, int NB, int W, bool STAGED, bool WIDE, int MINW>
 __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_args args)
 {
@@ -380,7 +379,7 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
                                              1024 * (Q % 4), 0);
 }
 
-// The tile of 32 rows x 128 columns on the bf16 matrix instructions (v_mfma_f32_32x32x16, sixteen times the
+// Tiles of 32 rows x 128 or 64 columns on the bf16 matrix instructions (v_mfma_f32_32x32x16, sixteen times the
 // products per cycle of the fp32 ones): every fp32 product is the sum of six products of parts,
 // h h + (h m + m h) + (m m + h l + l h), which the instructions multiply exactly and add in fp32.  The three that are left
 // out are below 2^-23 of the product, 2^-27 on average.  The sums of h h and of the five small ones are kept apart and added at the end: the large
@@ -391,22 +390,34 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
 // instructions, so that the results of tiny, huge and non-finite values are those of the kernel above.
 //
 // AL      loads of 1 KiB that hold any block of the plan
+// NB      column groups of the tile, 4 or 2
 //
-// Blocks pass through LDS twice: as they are stored (buffer_load .. lds, two steps ahead, no registers), then
+// Blocks pass through LDS twice: as they are stored (buffer_load .. lds, one or two steps ahead, no registers), then
 // expanded as above.  Rows of B come straight to registers, half a step (16 rows) at a time and a step ahead,
 // and a column group of them is split right before its six instructions.
+//
+// 128 columns: 8 waves, two per SIMD, with 128 registers of sums.  64 columns: 12 waves with 64 (16 waves, four per
+// SIMD, spill; 8 are 3 % slower), and LDS for one step ahead.  4096 x 1024, 70 % pruned, 128 columns in tiles of 64:
+// 10.7 us, with fp32 instructions and 16 waves 12.6; 8192 x 8192, 90 % pruned, 64 columns: 67 and 78; 8192 x 2048, 50 %
+// pruned, 64 columns: 25 and 27.  At the first size 32 steps are three per wave at most.  Up to FEW_STEPS steps the fp32 kernel's
+// 16 waves make one each, and stay (4096 x 300: 7.6 and 8.0 us; 8192 x 512: 8.9 both).
 //
 // What bounds it: 8192 x 8192, 50 % pruned, 128 columns take 123 us, with fp32 instructions 142; 16384 x 2048, 70 % pruned, 67
 // and 82.  The matrix cores are busy 39 % of the time; 11 vector instructions beside each of theirs (192 per 16 rows for B, which
 // every panel splits anew, 48 for A) overlap with it only in part, and the power limit holds the clock to 2 GHz.  Splitting B once, in a launch
 // of its own, leaves 2.6 vector instructions but moves 6 bytes per value, 19 TB/s through the L2s: 15 % faster, for a workspace that
 // spmm_execute does not have.  One wave per SIMD with everything interleaved is slower: a single wave issues an instruction every
-// 5 cycles only.
-template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_kernel(const tile_args args)
+// 5 cycles only.  With two, the splitting of the next group placed between the matrix instructions (also over halves and steps)
+// takes 4 % fewer cycles and the same time: the clock falls by what the schedule gains.
+constexpr int FEW_STEPS = 16;
+constexpr int split_waves(int NB) { return NB == 4 ? 8 : 12; }
+template <int AL, int NB> __global__ __launch_bounds__(64 * split_waves(NB), split_waves(NB) / 4) void spmm_split_tiles_kernel(const tile_args args)
 {
-    constexpr int W = 8, R = 32, NB = 4, NT = NB * R, KO = 64 / R, KS = OPS * KO;
+    constexpr int W = split_waves(NB), R = 32, NT = NB * R, KO = 64 / R, KS = OPS * KO;
+    constexpr int STAGES = NB == 4 ? 2 : 1;            // blocks on their way to a wave
+    typedef typename BVec<NB>::type b_t;
     constexpr int RUNS = (AL * 1024 / 6 + 255) / 256;  // runs of 256 entries in a block
-    constexpr int STAGE_WORDS = 256 * AL, SLOT = A_SLOT_WORDS + 2 * STAGE_WORDS;
+    constexpr int STAGE_WORDS = 256 * AL, SLOT = A_SLOT_WORDS + STAGES * STAGE_WORDS;
     static_assert(RUNS * 256 * 4 <= STAGE_WORDS * 4 && W * SLOT >= W / 2 * NB * Tile<R>::GROUPS * 256, "reads of whole runs stay in the stage; the sums fit");
     __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
 
@@ -432,7 +443,7 @@ template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_ker
     // Runs of 64 steps: lane i holds the bounds of the i-th block of the run.  (Loaded inside of the pipeline
     // they would make every step wait for all loads on their way.)
     uint32_t lo = 0, hi = 0, last = 0;
-    uint32_t n_in[2];  // entries of the blocks in the two stages
+    uint32_t n_in[STAGES];  // entries of the blocks in the stages
     auto bounds = [&](uint32_t first) {
         last = first + 64u < count ? first + 64u : count;
         const uint32_t s = (uint32_t)wave + W * (first + (uint32_t)lane);
@@ -481,13 +492,13 @@ template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_ker
                                                  (int)(left > 0xFFFFFFFCull ? 0xFFFFFFFCu : (uint32_t)left), 0x00020000);
     };
     const uint32_t lane_off = ((uint32_t)(lane / R) * N + (uint32_t)(NB * (lane % R))) * 4u, op_pitch = (uint32_t)KO * N * 4u;
-    f32x4 b[2][8];  // halves of a step
+    b_t b[2][8];  // halves of a step
     auto fetch_b = [&](uint32_t i, int half) {  // no rows past the last step
         const __amdgpu_buffer_rsrc_t r = b_rsrc((uint32_t)wave + W * i);
         uint32_t off = lane_off + (uint32_t)(8 * half) * op_pitch;
         asm volatile("" : "+v"(off));  // one address register, not one per row
 #pragma unroll
-        for (int t = 0; t < 8; ++t, off += op_pitch) b[half][t] = buffer_load<4>(r, off);
+        for (int t = 0; t < 8; ++t, off += op_pitch) b[half][t] = buffer_load<NB>(r, off);
         asm volatile("" ::: "memory");
     };
     auto multiply_half = [&](uint32_t i, int half) {
@@ -502,7 +513,7 @@ template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_ker
         for (int j = 0; j < NB; ++j) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) x[t] = b[half][t][j];
+            for (int t = 0; t < 8; ++t) x[t] = part(b[half][t], j);
             // not before this point: two groups of parts do not fit the registers
             asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
             parts p = in_parts(x, lost);
@@ -521,17 +532,17 @@ template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_ker
     for (uint32_t first = 0; first < count; first = last) {
         bounds(first);
         fetch_a(first, 0);
-        fetch_a(first + 1, 1);
+        if (STAGES == 2) fetch_a(first + 1, 1);
         fetch_b(first, 0);
         fetch_b(first, 1);
-        for (uint32_t i = first; i < last; i += 2) {
+        for (uint32_t i = first; i < last; i += STAGES) {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
+            for (int u = 0; u < STAGES; ++u) {
                 if (u == 1 && i + 1 >= last) break;
                 // the step's block has arrived: younger are the other stage's and 16 loads of B
-                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(AL + 16) : "memory");
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 1) * AL + 16) : "memory");
                 scatter(u);
-                fetch_a(i + (uint32_t)u + 2u, u);
+                fetch_a(i + (uint32_t)(u + STAGES), u);
                 multiply_half(i + (uint32_t)u, 0);
                 multiply_half(i + (uint32_t)u, 1);
             }
@@ -561,9 +572,9 @@ template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_ker
                 float *e = reinterpret_cast<float *>(expanded + 64 * (t / 4)) + t % 4;
                 const float a = *e;
                 *e = 0.0f;
-                const f32x4 bt = buffer_load<4>(r, lane_off + (uint32_t)t * op_pitch);
+                const b_t bt = buffer_load<NB>(r, lane_off + (uint32_t)t * op_pitch);
 #pragma unroll
-                for (int j = 0; j < NB; ++j) acc[j] = Tile<R>::mfma(bt[j], a, acc[j]);
+                for (int j = 0; j < NB; ++j) acc[j] = Tile<R>::mfma(part(bt, j), a, acc[j]);
             }
             lds_in_order();
         }
@@ -571,10 +582,17 @@ template <int AL> __global__ __launch_bounds__(512, 2) void spmm_split_tiles_ker
     store_sum_of_waves<R, NB, W>(args, acc, lds, panel, n0, wave, lane);
 }
 
-template <int AL> void launch_split(tile_args &a, hipStream_t s)
+template <int AL, int NB> void launch_split(tile_args &a, hipStream_t s)
 {
-    a.n_tiles = (int32_t)(((int64_t)a.N + 127) / 128);
-    launch_places(spmm_split_tiles_kernel<AL>, a, 512, s);
+    a.n_tiles = (int32_t)(((int64_t)a.N + 32 * NB - 1) / (32 * NB));
+    launch_places(spmm_split_tiles_kernel<AL, NB>, a, 64 * split_waves(NB), s);
+}
+template <int NB> void launch_split(tile_args &a, int loads, hipStream_t s)
+{
+    if (loads == 1) launch_split<2, NB>(a, s);
+    else if (loads == 2) launch_split<3, NB>(a, s);
+    else if (loads == 3) launch_split<5, NB>(a, s);
+    else launch_split<6, NB>(a, s);
 }
 
 // ---------------------------------------------------------------- executor, narrow panels
@@ -1420,9 +1438,10 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
                1e-3 * (double)steps * ns_density[i] * (peak - density);
     }
     // A compute unit holds one workgroup at a time.
-    // R = 16, 32; NB = 1, 2, 4 (the last one on bf16 instructions: 113 us for 8192 x 8192, 70 % pruned, 128 columns, 142 on fp32 ones)
-    static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 246, 365}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.1, 4.3}},
-                        ns_density[2][3] = {{60, 60, 60}, {60, 60, 150}};
+    // R = 16, 32; NB = 1, 2, 4.  (R = 32 with NB = 2 and 4 on bf16 instructions: 8 and 16 % less per step than on fp32 ones.  With
+    // few steps NB = 2 runs on fp32 ones: 3 % more than estimated.)
+    static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 220, 365}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.1, 4.3}},
+                        ns_density[2][3] = {{60, 60, 60}, {60, 75, 150}};
     double best = 0.0;
     for (int i = 0, NB = 1; i < 3; ++i, NB *= 2) {
         if (NB > 1 && rows * NB >= 2 * N) break;  // more than half of the tile idle
@@ -1460,13 +1479,11 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
     int NB = 1;
     spmm_tiles_time(p.rows, M, K, N, 0.0, 0.0, &NB);
     switch (p.rows * 8 + NB) {
-    case 32 * 8 + 4:
-        if (p.loads == 1) launch_split<2>(a, s);
-        else if (p.loads == 2) launch_split<3>(a, s);
-        else if (p.loads == 3) launch_split<5>(a, s);
-        else launch_split<6>(a, s);
+    case 32 * 8 + 4: launch_split<4>(a, p.loads, s); break;
+    case 32 * 8 + 2:
+        if (p.n_steps <= FEW_STEPS) launch<32, 2, 16, false, 4>(a, s);
+        else launch_split<2>(a, p.loads, s);
         break;
-    case 32 * 8 + 2: launch<32, 2, 16, false, 4>(a, s); break;
     case 32 * 8 + 1: launch<32, 1, 16, true, 4>(a, s); break;
     case 16 * 8 + 4: launch<16, 4, 8, false, 2>(a, s); break;
     case 16 * 8 + 2: launch<16, 2, 8, true, 2>(a, s); break;

@@ -1,4 +1,4 @@
-"""Panels of 32 rows x 128 columns on bf16 matrix instructions (values in three parts) against the CPU oracle,
+"""Panels of 32 rows x 128 and 64 columns on bf16 matrix instructions (values in three parts) against the CPU oracle,
 through the C ABI (GPU machine only)."""
 import ctypes
 
@@ -16,13 +16,17 @@ pytestmark = pytest.mark.gpu
 WIDE = 128 * 128   # columns enough that one panel or two are multiplied in tiles of 128 columns
 
 
-def product(torch_gpu, csr, B):  # noqa: F811
-    """The product, of which the plan has to run in tiles of four column groups."""
+def column_groups(M, K, N):
     lib, nb = spmm.load(), ctypes.c_int(0)
     lib.spmm_tiles_time.restype = ctypes.c_double
-    lib.spmm_tiles_time(32, ctypes.c_int64(csr.M), ctypes.c_int64(csr.K), ctypes.c_int64(B.shape[1]), ctypes.c_double(0),
-                        ctypes.c_double(0), ctypes.byref(nb))
-    assert nb.value == 4
+    lib.spmm_tiles_time(32, ctypes.c_int64(M), ctypes.c_int64(K), ctypes.c_int64(N), ctypes.c_double(0), ctypes.c_double(0),
+                        ctypes.byref(nb))
+    return nb.value
+
+
+def product(torch_gpu, csr, B, groups=4):  # noqa: F811
+    """The product, of which the plan has to run in tiles of so many column groups."""
+    assert column_groups(csr.M, csr.K, B.shape[1]) == groups
     C, plan = gpu_product(torch_gpu, csr, B, guard_rows=2, tiles=32)
     assert plan.describe()["tile_rows"] == 32
     return C
@@ -42,10 +46,12 @@ def test_bit_exact_on_integer_data(torch_gpu, oracle, M, K, N, density):  # noqa
     assert np.array_equal(C.astype(np.float64), C_ref)
 
 
-def test_more_steps_than_a_run_of_bounds(torch_gpu):  # noqa: F811
+@pytest.mark.parametrize("M,waves,groups", [(64, 8, 4), (32, 12, 2)])
+def test_more_steps_than_a_run_of_bounds(torch_gpu, M, waves, groups):  # noqa: F811
     """65 steps and more per wave.  Integer data, compared on the device in 64 bits."""
     torch = torch_gpu
-    M, K, N = 32, 32 * 8 * 65 + 40, WIDE
+    K, N = 32 * waves * 65 + 40, WIDE
+    assert column_groups(M, K, N) == groups
     csr = integer_matrix(M, K, 0.3, 3)
     dense = torch.zeros((M, K), device="cuda", dtype=torch.float64)
     rows = np.repeat(np.arange(M), np.diff(csr.row_ptr))
@@ -55,6 +61,41 @@ def test_more_steps_than_a_run_of_bounds(torch_gpu):  # noqa: F811
     C = plan.execute(B)
     for j in range(0, N, 2048):
         assert torch.equal(C[:, j:j + 2048].double(), dense @ B[:, j:j + 2048].double())
+
+
+@pytest.mark.parametrize("M,K,N,density", [
+    (32, 512, WIDE, 0.5), (32, 513, WIDE, 0.45), (31, 545, WIDE - 1, 1.0), (20, 800, WIDE // 2 + 8, 0.2), (32, 1300, WIDE - 70, 0.7),
+    (8192, 600, 64, 0.3), (8190, 777, 63, 0.8), (4090, 800, 100, 0.6), (9000, 64, 50, 0.5)])
+def test_two_column_groups(torch_gpu, oracle, M, K, N, density):  # noqa: F811
+    """16 steps, which fp32 instructions multiply, and more: fewer than two per wave, remainders of waves, rows, columns
+    and steps; blocks of one to four runs of 256 entries."""
+    csr = integer_matrix(M, K, density, M + K)
+    B = np.random.default_rng(N).integers(-16, 17, (K, N)).astype(np.float32)
+    C = product(torch_gpu, csr, B, groups=2)
+    C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B, parallel=True)
+    assert np.abs(C_ref).max() < 2 ** 24
+    assert np.array_equal(C.astype(np.float64), C_ref)
+
+
+@pytest.mark.parametrize("a_scale,b_scale", [(1.0, 1.0), (1e-20, 1e10), (1.0, 1e-36), (1e-39, 1.0), (1e-10, 1e38), (1.0, None)])
+def test_two_column_groups_with_every_part(torch_gpu, oracle, a_scale, b_scale):  # noqa: F811
+    """The bounds of the two tests below, and a value outside the domain."""
+    csr = few_entries(32, 600, 5, a_scale)
+    B = np.random.default_rng(6).standard_normal((600, WIDE))
+    if b_scale is None:
+        B[::7] *= 1e-37
+        B[csr.col_idx[3], 7] = np.inf
+    else:
+        B = (B * b_scale).clip(-3.4e38, 3.4e38)
+    B = B.astype(np.float32)
+    C = product(torch_gpu, csr, B, groups=2)
+    C_ref, S = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, np.where(np.isinf(B), 0, B).astype(np.float32), parallel=True)
+    fits = S < 3.4e38
+    if b_scale is None:
+        assert not np.isfinite(C[:, 7]).all()
+        fits[:, 7] = False
+    assert fits.mean() > 0.5
+    assert (np.abs(C - C_ref)[fits] <= 2.0 ** -21 * S[fits] + 3 * 2.0 ** -149).all()
 
 
 def few_entries(M, K, seed, scale):
