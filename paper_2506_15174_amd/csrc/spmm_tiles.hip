@@ -1440,8 +1440,8 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
     // A compute unit holds one workgroup at a time.
     // R = 16, 32; NB = 1, 2, 4.  (R = 32 with NB = 2 and 4 on bf16 instructions: 8 and 16 % less per step than on fp32 ones.  With
     // few steps NB = 2 runs on fp32 ones: 3 % more than estimated.)
-    static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 220, 365}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.1, 4.3}},
-                        ns_density[2][3] = {{60, 60, 60}, {60, 75, 150}};
+    static const double ns_per_step[2][3] = {{99, 169, 275}, {146, 190, 345}}, us_per_round[2][3] = {{1.36, 1.61, 1.75}, {2.1, 3.6, 4.5}},
+                        ns_density[2][3] = {{60, 60, 60}, {60, 100, 130}};
     double best = 0.0;
     for (int i = 0, NB = 1; i < 3; ++i, NB *= 2) {
         if (NB > 1 && rows * NB >= 2 * N) break;  // more than half of the tile idle
