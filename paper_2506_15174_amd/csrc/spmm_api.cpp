@@ -38,6 +38,7 @@ struct spmm_plan {
     bool force_wide = false;  // spmm_options_t.force_wide: 64-bit addressing kernels also on small inputs
     int depth = 0;            // spmm_options_t.depth: pipeline depth asked for (0 = per-instance default)
     bool probe = false;       // spmm_options_t.probe: loads-only launches (measurement)
+    int32_t heavy = 0;        // the first blocks that are heavier than most (heavy_blocks)
     uint32_t lds_pad = 0;     // extra LDS per workgroup that keeps a third one off a compute unit (hold_to_two)
 };
 
@@ -45,6 +46,22 @@ namespace {
 
 // Columns a plan cut along K computes per pair of launches (the width of its slices' buffer).
 constexpr int32_t KSLICE_COLS = 128;
+
+int64_t block_weight(const HostPlan &h, int64_t block)
+{
+    int64_t chunks = 0;
+    for (int w = 0; w < WAVES_PER_WG; ++w) chunks += h.items[(size_t)((block * WAVES_PER_WG + w) * ITEM_WORDS + IT_NCHUNKS)];
+    return chunks;
+}
+
+// The blocks up to the last of the first 256 that is half as heavy again as the mean.  (They come heaviest first, but for
+// the order of split panels and whole ones.)
+int32_t heavy_blocks(const HostPlan &h)
+{
+    int64_t last = std::min<int64_t>(h.n_blocks, 256);
+    while (last > 0 && 2 * block_weight(h, last - 1) * h.n_blocks <= 3 * h.n_chunks) --last;
+    return (int32_t)last;
+}
 
 // Whether to hold a compute unit to two workgroups.  The workgroups come heaviest first.  While all of
 // them fit the chip at once the device deals them out in turn, so with a few more than 512 the heaviest
@@ -61,11 +78,7 @@ bool hold_to_two(const HostPlan &h)
     constexpr int64_t UNITS = 256;
     const int64_t n = h.n_blocks;
     if (h.ufi != 1 || n <= 2 * UNITS || n > 2 * UNITS + UNITS / 2) return false;
-    auto weight = [&](int64_t block) {
-        int64_t chunks = 0;
-        for (int w = 0; w < WAVES_PER_WG; ++w) chunks += h.items[(size_t)((block * WAVES_PER_WG + w) * ITEM_WORDS + IT_NCHUNKS)];
-        return chunks;
-    };
+    auto weight = [&](int64_t block) { return block_weight(h, block); };
     std::vector<int64_t> held((size_t)UNITS, 0);
     for (int64_t b = 0; b < 2 * UNITS; ++b) held[(size_t)(b % UNITS)] += weight(b);
     std::vector<int64_t> dealt = held;
@@ -211,6 +224,7 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
             if (st == SPMM_OK) st = upload(&p->d_stream, h.stream.data(), h.stream.size() * 4, p->device_bytes);
             if (st == SPMM_OK) st = upload(&p->d_wins, h.wins.data(), h.wins.size() * 4, p->device_bytes);
             if (st == SPMM_OK) st = upload(&p->d_items, h.items.data(), h.items.size() * 4, p->device_bytes);
+            p->heavy = heavy_blocks(h);
             if (h.k_slices == 1 && win_words(h.ufk) == WIN_WORDS && hold_to_two(h)) p->lds_pad = 48u << 10;  // 32 KiB and these: half of a unit's LDS
         }
         if (st != SPMM_OK) return st;
@@ -320,6 +334,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     a.cross_table = plan->d_cross_table;
     a.n_cross_slots = (uint32_t)h.n_cross_slots;
     a.n_cross = (int32_t)h.n_cross;
+    a.heavy = plan->heavy;
     a.probe = plan->probe;
     if (plan->probe && (wide || h.ufk > 16)) return SPMM_ERR_UNSUPPORTED;
     // the scratch of panels cut across workgroups holds so many column tiles of one launch
@@ -337,10 +352,10 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     // matrices in panels of several rows at 161, 188 and 192 columns: 13 % faster on average, 0.2 % slower at worst.  Single
     // rows share no load, and a row of B that begins inside of a cache line takes one line in three more than its
     // columns in tiles of 64, one in five in tiles of 128: with such rows they are up to 17 % slower from 2^19
-    // entries on and up to 40 % faster below, with whole lines 11 % faster on average (1.6 % slower at worst).
+    // entries on and up to 40 % faster below, with whole lines and blocks of even weight 11 % faster on average (9 % slower on Zipf rows).
     const bool three_tiles = !sliced && !wide && h.ufk == UFK && N > 160 && N <= 192 &&
-                             (h.ufi > 1 || N % 32 == 0 || h.nnz < ((int64_t)1 << 19));
-    // Column tiles of one width share a launch (its workgroups start tile by tile, so a
+                             (h.ufi > 1 || (N % 32 == 0 && plan->heavy == 0) || h.nnz < ((int64_t)1 << 19));
+    // Column tiles of one width share a launch (front_blocks: in which order; a
     // tile begins while the previous one drains); a narrower rest takes a launch of its own.
     // Plans made for narrow B (chunks wider than 8 columns) run every N on their own narrow tiles.
     if (h.ufk != UFK && wide) return SPMM_ERR_UNSUPPORTED;

@@ -18,10 +18,11 @@ struct spmm_launch_args {
     int32_t ldn;            // leading dimension of B (= N)
     int32_t ldc;            // leading dimension of what C points to
     int32_t width;          // columns of this launch: n_tiles tiles of tile_cols, the last maybe narrower
-    int32_t tile_cols;      // columns per tile (per blockIdx.y)
+    int32_t tile_cols;      // columns per tile
     int32_t n_tiles;        // column tiles of this launch (grid y)
     uint32_t col_mask;      // bits of a column word that hold the column index
     uint32_t lds_pad = 0;   // extra LDS bytes per workgroup (never touched): caps the workgroups per CU
+    int32_t heavy = 0;      // the plan's first blocks that are heavier than most (front_blocks)
     bool probe = false;     // launch the loads-only instance (32-bit addressing, tuned depth, chunks of 8 or 16)
     // Panels cut across workgroups (plans with n_cross > 0; else unused):
     float *cross_sums = nullptr;          // DEVICE n_tiles x n_cross_slots slots of ufi x 128 floats (scratch)
