@@ -137,7 +137,8 @@ typedef struct {
                               plans with chunks wider than 8 (SPMM_ERR_INVALID_ARG if both are forced).
                               At most one execute of such a plan may be in flight at a time (not on tiles). */
     int32_t tiles;         /* the matrix-core path: A in tiles of panels of 8, 16 or 32 rows, absent
-                              entries multiplied as zeros by fp32 matrix instructions, which pays on
+                              entries multiplied as zeros by matrix instructions (fp32, or bf16 on the
+                              three exact parts of every value), which pays on
                               matrices that are not very sparse.  8, 16 or 32 = use it with panels of so
                               many rows; < 0 = never; 0 = choose by shape, density and n_hint (8 rows
                               for hints of at most 64 columns only; never when

@@ -487,15 +487,15 @@ std::vector<int64_t> range_cuts(const std::vector<Group> &groups, int want)
 // gathers fetch little at a time) from 5 to 10 % on, small matrices later or never.  Both times are
 // estimated and tiles are taken where theirs is at least 5 % shorter.  Of 600 measured products
 // (bench.py --workload paths: 15 shapes of 512 to 16384 rows and 600 to 13000 columns, 4 to 45 % of the entries
-// kept in even, lognormal or Zipf rows, 4 to 256 columns) that moves 251 to tiles, 1.40 times as fast on
-// average; seven are more than 3 % slower, the worst by 15 %.  The path chosen takes 1.4 % longer than the fastest
+// kept in even, lognormal or Zipf rows, 4 to 256 columns) that moves 322 to tiles, 1.39 times as fast on
+// average; twenty are more than 3 % slower, the worst by 15 %.  The path chosen takes 1.5 % longer than the fastest
 // on average, 1.6 times as long at worst (uneven rows whose chunks' time is estimated too low).
 //
 // The chunks' time in us: a constant, the wave loads that gather rows of B, the vector FMAs (millions), the
 // plan's bytes (MB), the chunks (millions, dearer the more rows they span), the second launch of
 // a plan cut along K or across workgroups, and the chunks of the longest piece of a panel cut into eight
 // (hundreds), the tail of the launch where rows are of uneven length.  Against those 600 products the rms error is
-// 12 % (10 to 15 % by width; 0.52 to 1.41 of the time).
+// 13 % (0.53 to 1.41 of the time).
 static double chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
 {
     static const double weights[5][8] = {{2.90, 6.86, 9.60, 0.0, 68.0, 0.0, 4.63, 0.0},   // n_hint <= 8

@@ -1,4 +1,4 @@
-// Matrix-core path (internal): A in tiles, multiplied by fp32 MFMA instructions.
+// Matrix-core path (internal): A in tiles, multiplied by MFMA instructions (fp32, or bf16 on values in three parts).
 #ifndef SPMM_TILES_H
 #define SPMM_TILES_H
 
