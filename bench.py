@@ -48,6 +48,9 @@ HBM_PEAK_GBS = 8000.0
 FP32_VALU_PEAK_TFLOPS = 78.6
 # dense fp32 on the matrix cores
 FP32_MFMA_PEAK_TFLOPS = 157.3
+# dense bf16; six products of parts make one of fp32 values
+BF16_MFMA_PEAK_TFLOPS = 2500.0
+SPLIT_PRODUCTS = 6
 
 
 def bytes_min(M, K, nnz, N):
@@ -231,8 +234,23 @@ def kernel_shape(N, ufi, K=0, ufk=8, k_slices=1):
     return "S=8,VW=4,D=%d" % depth[2]
 
 
-def tile_kernel(tile_rows):
-    """The kernel of a plan on tiles: panels of 32 and 16 rows share one, panels of 8 have their own."""
+def split_groups(tile_rows, M, K, N):
+    """Column groups of spmm_split_tiles_kernel (4 or 2), the kernel of panels of 32 rows on 65 and more columns of a tile
+    or, with more than 16 steps of 32 columns of A, 33 and more; 0 where another kernel runs."""
+    if tile_rows != 32:
+        return 0
+    import ctypes
+    import paper_2506_15174_amd as spmm
+    groups, lib = ctypes.c_int(0), spmm.load()
+    lib.spmm_tiles_time.restype = ctypes.c_double
+    lib.spmm_tiles_time(32, ctypes.c_int64(M), ctypes.c_int64(K), ctypes.c_int64(N), ctypes.c_double(0), ctypes.c_double(0), ctypes.byref(groups))
+    return groups.value if groups.value == 4 or (groups.value == 2 and K > 512) else 0
+
+
+def tile_kernel(tile_rows, groups=0):
+    """The kernel of a plan on tiles: panels of 8 rows have their own, and panels of 32 on wide B (split_groups)."""
+    if groups:
+        return "spmm_split_tiles_kernel<NB=%d>" % groups
     return "spmm_narrow_tiles_kernel" if tile_rows == 8 else "spmm_tiles_kernel<R=%d>" % tile_rows
 
 
@@ -708,7 +726,8 @@ def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, pla
     traffic, prov = measured_traffic(workload_key, N)
     on_tiles = info["tile_rows"] > 0
     if on_tiles:
-        kernel, launches = tile_kernel(info["tile_rows"]), 1
+        groups = split_groups(info["tile_rows"], csr.M, csr.K, N)
+        kernel, launches = tile_kernel(info["tile_rows"], groups), 1
     else:
         shape = kernel_shape(N, info["ufi"], csr.K, info["ufk"], info["k_slices"])
         kernel, launches = "spmm_chunks_kernel<UFI=%d,%s>" % (info["ufi"], shape), 1 + (info["n_cross"] > 0) + (info["k_slices"] > 1)
@@ -725,8 +744,9 @@ def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, pla
         # absent entries are multiplied as zeros: 1024 cells per block, one flop pair per cell and column
         with_zeros = 2.0 * 1024 * info["n_chunks"] * N / (avg_ms * 1e-3) / 1e12
         roofline["gather"] = None
+        peak = BF16_MFMA_PEAK_TFLOPS / SPLIT_PRODUCTS if groups else FP32_MFMA_PEAK_TFLOPS
         roofline["matrix_cores"] = {"blocks": info["n_chunks"], "tflops_with_zeros": round(with_zeros, 3),
-                                    "peak": FP32_MFMA_PEAK_TFLOPS, "frac": round(with_zeros / FP32_MFMA_PEAK_TFLOPS, 4)}
+                                    "peak": round(peak, 1), "frac": round(with_zeros / peak, 4)}
         return roofline
     # On-chip gather: each chunk of ufk enumerated columns costs ufk / S wave-wide loads of B
     # rows (S rows of B per load); the ceiling is the rate the gather microbenchmark
