@@ -353,6 +353,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     // rows share no load, and a row of B that begins inside of a cache line takes one line in three more than its
     // columns in tiles of 64, one in five in tiles of 128: with such rows they are up to 17 % slower from 2^19
     // entries on and up to 40 % faster below, with whole lines and blocks of even weight 11 % faster on average (9 % slower on Zipf rows).
+    // 129 to 160 columns, 128 and a tile of 32, stay: as three tiles of 64 nineteen matrices are 4 % slower on average, up to 18 %.
     const bool three_tiles = !sliced && !wide && h.ufk == UFK && N > 160 && N <= 192 &&
                              (h.ufi > 1 || (N % 32 == 0 && plan->heavy == 0) || h.nnz < ((int64_t)1 << 19));
     // Column tiles of one width share a launch (front_blocks: in which order; a
