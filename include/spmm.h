@@ -138,7 +138,8 @@ typedef struct {
                               At most one execute of such a plan may be in flight at a time (not on tiles). */
     int32_t tiles;         /* the matrix-core path: A in tiles of panels of 8, 16 or 32 rows, absent
                               entries multiplied as zeros by matrix instructions (fp32, or bf16 on the
-                              three exact parts of every value), which pays on
+                              three exact parts of every value: six products of parts for one, what is
+                              left out is below 2^-24 of it), which pays on
                               matrices that are not very sparse.  8, 16 or 32 = use it with panels of so
                               many rows; < 0 = never; 0 = choose by shape, density and n_hint (8 rows
                               for hints of at most 64 columns only; never when

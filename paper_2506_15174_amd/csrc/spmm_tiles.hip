@@ -339,27 +339,31 @@ template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void l
 
 // ---------------------------------------------------------------- executor, fp32 values in three bf16 parts
 
-// Eight values as h + m + l: the upper 16 bits, what is left rounded to bf16, and what is left of that.  A float
-// has 24 significant bits and the parts 8 each, so the sum is exact; only where the last part falls below the
-// smallest bf16 (values under 2^-101) is it not, and then `lost` gets a bit among its lower 16.
+// Eight values as h + m + l: the value rounded to bf16, what is left rounded to bf16, and what is left of that.  A
+// float has 24 significant bits, a part 8 and a sign, and a value between 1 and 2 leaves at most 2^-8 and then 2^-17, a
+// multiple of 2^-23: the sum is exact.  Only where the last part falls below the smallest bf16 (values under
+// 2^-101) is it not, and then `lost` gets a bit among its lower 16; a value of 2^128 - 2^119 and more has an infinite h.
 struct parts {
     bf16x8 h, m, l;
 };
 __device__ __forceinline__ parts in_parts(const float (&x)[8], uint32_t &lost)
 {
-    constexpr uint32_t UPPER = 0xFFFF0000u;
     u32x4 h, m, l;
     float r[8];
+    auto rounded = [](float lower, float upper) {  // (a conversion of a vector would be done twice, once for each way its result is used)
+        uint32_t two;
+        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(two) : "v"(lower), "v"(upper));
+        return two;
+    };
+    auto value = [](const u32x4 &p, int i) { return __uint_as_float(i % 2 ? p[i / 2] & 0xFFFF0000u : p[i / 2] << 16); };
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = x[i] - __uint_as_float(__float_as_uint(x[i]) & UPPER);
+    for (int i = 0; i < 4; ++i) h[i] = rounded(x[2 * i], x[2 * i + 1]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        h[i] = __builtin_amdgcn_perm(__float_as_uint(x[2 * i + 1]), __float_as_uint(x[2 * i]), 0x07060302u);
-        // (a conversion of a vector would be done twice, once for each way its result is used)
-        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(m[i]) : "v"(r[2 * i]), "v"(r[2 * i + 1]));
-    }
+    for (int i = 0; i < 8; ++i) r[i] = x[i] - value(h, i);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] -= __uint_as_float(i % 2 ? m[i / 2] & UPPER : m[i / 2] << 16);
+    for (int i = 0; i < 4; ++i) m[i] = rounded(r[2 * i], r[2 * i + 1]);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) r[i] -= value(m, i);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         l[i] = __builtin_amdgcn_perm(__float_as_uint(r[2 * i + 1]), __float_as_uint(r[2 * i]), 0x07060302u);
@@ -382,9 +386,10 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
 // Tiles of 32 rows x 128 or 64 columns on the bf16 matrix instructions (v_mfma_f32_32x32x16, sixteen times the
 // products per cycle of the fp32 ones): every fp32 product is the sum of six products of parts,
 // h h + (h m + m h) + (m m + h l + l h), which the instructions multiply exactly and add in fp32.  The three that are left
-// out are below 2^-23 of the product, 2^-27 on average.  The sums of h h and of the five small ones are kept apart and added at the end: the large
-// sums are then rounded once per 16 columns of A, where the fp32 instructions round once per two.  8192 x 8192, 50 %
-// pruned, 128 columns: error of the result (2-norm, against 64 bits) 1.2e-7, with fp32 instructions 4.1e-7.
+// out are below 2^-24 of the product, 2^-28 on average.  The sums of h h and of the five small ones are kept apart and added at the end: the large
+// sums are then rounded once per 16 columns of A, where the fp32 instructions round once per two.  Error of the result (2-norm,
+// against 64 bits) and that of fp32 instructions in tiles of 16 rows: 8192 x 8192, 50 % pruned, 128 columns 1.5e-7 and 4.1e-7; 4096 x 600 with 64, 8, 2 and
+// 1 entries in every row 6.3e-8 and 7.6e-8, 5.32e-8 both, 3.65e-8 and 3.62e-8, 2.59e-8 and 2.53e-8.
 //
 // Where a value has no exact parts or a sum is not finite the wave multiplies all of its steps again with fp32
 // instructions, so that the results of tiny, huge and non-finite values are those of the kernel above.

@@ -112,7 +112,7 @@ def few_entries(M, K, seed, scale):
                                              (1e38, 1e-20)])
 def test_every_part_of_a_product_counts(torch_gpu, oracle, a_scale, b_scale):  # noqa: F811
     """Sums of one or two products, so that nothing averages out.  Bound: a product's parts left out are below
-    2^-23 of it, and there are at most twelve fp32 roundings, all but two of sums below 2^-7 of the result's terms: 2^-21.
+    2^-24 of it, and there are at most twelve fp32 roundings, all but two of sums below 2^-7 of the result's terms: 2^-21.
     In the range of subnormal results add their spacing.  Values whose parts are not all normal (1e-36), subnormal ones and the largest."""
     csr = few_entries(64, 90, 5, a_scale)
     B = (np.random.default_rng(6).standard_normal((90, WIDE)) * b_scale).clip(-3.4e38, 3.4e38).astype(np.float32)
@@ -122,6 +122,24 @@ def test_every_part_of_a_product_counts(torch_gpu, oracle, a_scale, b_scale):  #
     fits = S < 3.4e38
     assert fits.mean() > 0.5
     assert (np.abs(C - C_ref)[fits] <= 2.0 ** -21 * S[fits] + 3 * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("M,groups", [(64, 4), (32, 2)])
+def test_what_is_left_out_of_a_product(torch_gpu, oracle, M, groups):  # noqa: F811
+    """One product per element, of the values that lose most.  m is at most 2^-8 and l 2^-17 of a value's leading bit, so
+    m l + l m + l l are below 2^-24 of a product; adding the small sum rounds by 2^-24 once more, and its own five
+    roundings, of sums below 2^-7, by less than 2^-27.  (With h cut off instead of rounded the first square loses 2^-22.02.)"""
+    K, N = 600, WIDE
+    near = np.concatenate([1 + 2.0 ** -7 - 2.0 ** -16 - np.arange(1, 9) * 2.0 ** -23, 1 + 2.0 ** -8 - 2.0 ** -17 + np.arange(-8, 9) * 2.0 ** -23,
+                           1 + 2.0 ** -8 + 2.0 ** -17 + np.arange(-8, 9) * 2.0 ** -23, 1 + 3 * 2.0 ** -9 + np.arange(-8, 9) * 2.0 ** -23])
+    rng = np.random.default_rng(M)
+    W = np.zeros((M, K), np.float32)
+    W[np.arange(M), rng.choice(K, M, replace=False)] = rng.choice(near, M) * rng.choice([-1, 1], M) * 2.0 ** rng.integers(-20, 20, M)
+    csr = gen.csr_from_dense(W)
+    B = (rng.choice(near, (K, N)) * rng.choice([-1, 1], (K, N))).astype(np.float32)
+    C = product(torch_gpu, csr, B, groups)
+    C_ref, S = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B, parallel=True)
+    assert (np.abs(C - C_ref) <= (2.0 ** -23 + 2.0 ** -27) * S).all()
 
 
 def test_a_few_tiny_values_among_ordinary_ones(torch_gpu, oracle):  # noqa: F811
