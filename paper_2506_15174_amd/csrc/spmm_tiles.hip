@@ -394,7 +394,7 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
 // Where a value has no exact parts or a sum is not finite the wave multiplies all of its steps again with fp32
 // instructions, so that the results of tiny, huge and non-finite values are those of the kernel above.
 //
-// AL      loads of 1 KiB that hold any block of the plan
+// RUNS    runs of 256 entries that hold any block of the plan
 // NB      column groups of the tile, 4 or 2
 //
 // Blocks pass through LDS twice: as they are stored (buffer_load .. lds, one or two steps ahead, no registers), then
@@ -416,14 +416,14 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
 // takes 4 % fewer cycles and the same time: the clock falls by what the schedule gains.
 constexpr int FEW_STEPS = 16;
 constexpr int split_waves(int NB) { return NB == 4 ? 8 : 12; }
-template <int AL, int NB> __global__ __launch_bounds__(64 * split_waves(NB), split_waves(NB) / 4) void spmm_split_tiles_kernel(const tile_args args)
+template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), split_waves(NB) / 4) void spmm_split_tiles_kernel(const tile_args args)
 {
     constexpr int W = split_waves(NB), R = 32, NT = NB * R, KO = 64 / R, KS = OPS * KO;
     constexpr int STAGES = NB == 4 ? 2 : 1;            // blocks on their way to a wave
     typedef typename BVec<NB>::type b_t;
-    constexpr int RUNS = (AL * 1024 / 6 + 255) / 256;  // runs of 256 entries in a block
+    constexpr int AL = (RUNS * 256 * 6 + 1023) / 1024;  // loads of 1 KiB for one
     constexpr int STAGE_WORDS = 256 * AL, SLOT = A_SLOT_WORDS + STAGES * STAGE_WORDS;
-    static_assert(RUNS * 256 * 4 <= STAGE_WORDS * 4 && W * SLOT >= W / 2 * NB * Tile<R>::GROUPS * 256, "reads of whole runs stay in the stage; the sums fit");
+    static_assert(W * SLOT >= W / 2 * NB * Tile<R>::GROUPS * 256, "the sums fit");
     __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
 
     const uint32_t id = place_in_matrix(args.first), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
@@ -587,17 +587,17 @@ template <int AL, int NB> __global__ __launch_bounds__(64 * split_waves(NB), spl
     store_sum_of_waves<R, NB, W>(args, acc, lds, panel, n0, wave, lane);
 }
 
-template <int AL, int NB> void launch_split(tile_args &a, hipStream_t s)
+template <int RUNS, int NB> void launch_split(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (int32_t)(((int64_t)a.N + 32 * NB - 1) / (32 * NB));
-    launch_places(spmm_split_tiles_kernel<AL, NB>, a, 64 * split_waves(NB), s);
+    launch_places(spmm_split_tiles_kernel<RUNS, NB>, a, 64 * split_waves(NB), s);
 }
-template <int NB> void launch_split(tile_args &a, int loads, hipStream_t s)
+template <int NB> void launch_split(tile_args &a, int runs, hipStream_t s)
 {
-    if (loads == 1) launch_split<2, NB>(a, s);
-    else if (loads == 2) launch_split<3, NB>(a, s);
-    else if (loads == 3) launch_split<5, NB>(a, s);
-    else launch_split<6, NB>(a, s);
+    if (runs == 1) launch_split<1, NB>(a, s);
+    else if (runs == 2) launch_split<2, NB>(a, s);
+    else if (runs == 3) launch_split<3, NB>(a, s);
+    else launch_split<4, NB>(a, s);
 }
 
 // ---------------------------------------------------------------- executor, narrow panels
