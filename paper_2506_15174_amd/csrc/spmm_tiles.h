@@ -25,6 +25,8 @@ struct TilePlan {
     uint32_t *d_offsets = nullptr;  // DEVICE n_panels * (n_steps + 1) block starts
     int64_t stream_words = 0, device_bytes = 0;
     bool built = false;             // whole
+    bool exact_parts = false;       // R = 32: every value is the sum of three bf16 numbers
+    float largest = 0.0f;           // R = 32: size of the largest value
 };
 
 constexpr int TILE_OPERANDS = 16;

@@ -38,6 +38,7 @@ struct tile_args {
     uint64_t b_bytes;   // bytes of B
     int32_t n_panels, n_steps, n_tiles, M, K, N;
     uint32_t first;     // the launch's first place among all column tiles of all panels
+    float largest;      // size of A's largest value (spmm_split_tiles_kernel)
 };
 
 template <int NB> struct BVec;
@@ -101,13 +102,12 @@ template <typename F> void launch_places(F kernel, tile_args &a, unsigned thread
     }
 }
 
-// Adds the waves' tiles, in a fixed order, and stores the sum: the upper half of the waves parks its tiles in
-// LDS, the lower half adds them to its own, then all waves share the rest of the sum.
-template <int R, int NB, int W> __device__ __forceinline__ void store_sum_of_waves(const tile_args &args, const typename Tile<R>::acc_t (&acc)[NB], float *lds,
-                                                                                  uint32_t panel, uint32_t n0, int wave, int lane)
+// The sum of the waves' tiles, in a fixed order: the upper half of the waves parks its tiles in LDS, the lower half adds
+// them to its own, then all waves share the rest of the sum (store_sum).  `meanwhile` is called when all waves are there.
+template <int R, int NB, int W, typename F> __device__ __forceinline__ void add_halves(const typename Tile<R>::acc_t (&acc)[NB], float *lds, int wave, int lane,
+                                                                                      F meanwhile)
 {
-    constexpr int KO = 64 / R, QUADS = NB * Tile<R>::GROUPS;
-    const uint32_t N = (uint32_t)args.N;
+    constexpr int QUADS = NB * Tile<R>::GROUPS;
     f32x4 quad[QUADS];
 #pragma unroll
     for (int f = 0; f < QUADS; ++f) {
@@ -121,6 +121,7 @@ template <int R, int NB, int W> __device__ __forceinline__ void store_sum_of_wav
 #pragma unroll
         for (int f = 0; f < QUADS; ++f) red[((wave - W / 2) * QUADS + f) * 64 + lane] = quad[f];
     }
+    meanwhile();
     __syncthreads();
     if (wave < W / 2) {
 #pragma unroll
@@ -130,7 +131,14 @@ template <int R, int NB, int W> __device__ __forceinline__ void store_sum_of_wav
         }
     }
     __syncthreads();
-    const uint32_t row = panel * (uint32_t)R + (uint32_t)(lane % R);
+}
+// Calls `stored` with the first of every four columns and their sums.
+template <int R, int NB, int W, typename F> __device__ __forceinline__ void store_sum(const tile_args &args, const float *lds, uint32_t panel, uint32_t n0, int wave,
+                                                                                     int lane, F stored)
+{
+    constexpr int KO = 64 / R, QUADS = NB * Tile<R>::GROUPS;
+    const f32x4 *red = reinterpret_cast<const f32x4 *>(lds);
+    const uint32_t N = (uint32_t)args.N, row = panel * (uint32_t)R + (uint32_t)(lane % R);
     if (row >= (uint32_t)args.M) return;
 #pragma unroll
     for (int f0 = 0; f0 < QUADS; f0 += W) {
@@ -147,6 +155,7 @@ template <int R, int NB, int W> __device__ __forceinline__ void store_sum_of_wav
             for (uint32_t x = 0; x < 4; ++x)
                 if (n + x < N) dst[x] = sum[(int)x];
         }
+        stored(n, sum);
     }
 }
 
@@ -166,7 +175,7 @@ template <int R, int NB, int W> __device__ __forceinline__ void store_sum_of_wav
 // places in a zeroed 4 KiB slot of LDS, read back as 16 operands per lane (four 16-byte reads), the
 // slot is zeroed again for the next block, and 16 * NB matrix instructions multiply.
 //
-// (32 rows x 128 columns: only WIDE; 32 x 64: only few steps; spmm_split_tiles_kernel below has the others.)
+// (32 rows x 128 and 64 columns: WIDE, values of A without exact parts, few steps; spmm_split_tiles_kernel below has the others.)
 //
 // What bounds it: the matrix cores' fp32 rate (157 TFLOP/s dense, 156 measured) times the density.  fp32
 // matrix instructions issue from the vector ALUs (baselines/microbench_paths.hip: a 32x32x2 takes 64.6 cycles, 16
@@ -328,7 +337,8 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
         }
     }
 
-    store_sum_of_waves<R, NB, W>(args, acc, lds, panel, n0, wave, lane);
+    add_halves<R, NB, W>(acc, lds, wave, lane, [] {});
+    store_sum<R, NB, W>(args, lds, panel, n0, wave, lane, [](uint32_t, const f32x4 &) {});
 }
 
 template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void launch(tile_args &a, hipStream_t s)
@@ -342,11 +352,12 @@ template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void l
 // Eight values as h + m + l: the value rounded to bf16, what is left rounded to bf16, and what is left of that.  A
 // float has 24 significant bits, a part 8 and a sign, and a value between 1 and 2 leaves at most 2^-8 and then 2^-17, a
 // multiple of 2^-23: the sum is exact.  Only where the last part falls below the smallest bf16 (values under
-// 2^-101) is it not, and then `lost` gets a bit among its lower 16; a value of 2^128 - 2^119 and more has an infinite h.
+// 2^-110) is it not: less than 2^-133 is lost, and `lost`, if asked for, gets a bit among its lower 16.  A value of
+// 2^128 - 2^119 and more has an infinite h.
 struct parts {
     bf16x8 h, m, l;
 };
-__device__ __forceinline__ parts in_parts(const float (&x)[8], uint32_t &lost)
+template <bool LOST> __device__ __forceinline__ parts in_parts(const float (&x)[8], uint32_t &lost)
 {
     u32x4 h, m, l;
     float r[8];
@@ -367,7 +378,7 @@ __device__ __forceinline__ parts in_parts(const float (&x)[8], uint32_t &lost)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         l[i] = __builtin_amdgcn_perm(__float_as_uint(r[2 * i + 1]), __float_as_uint(r[2 * i]), 0x07060302u);
-        lost |= __float_as_uint(r[2 * i]) | __float_as_uint(r[2 * i + 1]);
+        if (LOST) lost |= __float_as_uint(r[2 * i]) | __float_as_uint(r[2 * i + 1]);
     }
     return parts{__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
 }
@@ -391,8 +402,11 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
 // against 64 bits) and that of fp32 instructions in tiles of 16 rows: 8192 x 8192, 50 % pruned, 128 columns 1.5e-7 and 4.1e-7; 4096 x 600 with 64, 8, 2 and
 // 1 entries in every row 6.3e-8 and 7.6e-8, 5.32e-8 both, 3.65e-8 and 3.62e-8, 2.59e-8 and 2.53e-8.
 //
-// Where a value has no exact parts or a sum is not finite the wave multiplies all of its steps again with fp32
-// instructions, so that the results of tiny, huge and non-finite values are those of the kernel above.
+// Where sums are not finite the workgroup multiplies again, with fp32 instructions, and gives what the kernel above gives.  Plans with values of A that have no exact parts run on that kernel (TilePlan::exact_parts).  Where values of B have
+// none, an element of C is off by at most 2^-133 x the largest value of A x K.  To an element 2^32 times as large that is
+// nothing; where one is smaller, of a row with entries and a column near such a value, the workgroup multiplies again too.
+// (8192 x 8192, 50 % pruned, 128 columns, 114 us: 113 with a tenth of B below 2^-110, 240 with a column of such values only or with
+// an infinite one, 134 with such a value in A; 4096 x 1024, 70 % pruned, in tiles of 64, 11.2 us: 11.4, 22 and 12.1.)
 //
 // RUNS    runs of 256 entries that hold any block of the plan
 // NB      column groups of the tile, 4 or 2
@@ -425,6 +439,11 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
     constexpr int STAGE_WORDS = 256 * AL, SLOT = A_SLOT_WORDS + STAGES * STAGE_WORDS;
     static_assert(W * SLOT >= W / 2 * NB * Tile<R>::GROUPS * 256, "the sums fit");
     __shared__ __attribute__((aligned(16))) float lds[W * SLOT];
+    struct loss {  // bit i: the wave lost bits of B's i-th group of columns; has entries in the panel's i-th row
+        uint32_t groups, rows, found;  // found: bits lost 1, sums that are not finite 2
+    };
+    __shared__ loss losses[W];
+    __shared__ uint32_t verdicts[W];
 
     const uint32_t id = place_in_matrix(args.first), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
     if (panel >= (uint32_t)args.n_panels) return;
@@ -441,9 +460,12 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
     f32x16 acc[NB], cor[NB];  // sums of h h; of the other products
 #pragma unroll
     for (int j = 0; j < NB; ++j) acc[j] = cor[j] = f32x16{};
-    uint32_t lost = 0;
+    uint32_t lost = 0, entries = 0;  // of the lane's columns of B; of its row of A
+    auto clear = [&] {
 #pragma unroll
-    for (int q = 0; q < OPS / 4; ++q) expanded[64 * q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int q = 0; q < OPS / 4; ++q) expanded[64 * q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    clear();
 
     // Runs of 64 steps: lane i holds the bounds of the i-th block of the run.  (Loaded inside of the pipeline
     // they would make every step wait for all loads on their way.)
@@ -498,22 +520,26 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
     };
     const uint32_t lane_off = ((uint32_t)(lane / R) * N + (uint32_t)(NB * (lane % R))) * 4u, op_pitch = (uint32_t)KO * N * 4u;
     b_t b[2][8];  // halves of a step
-    auto fetch_b = [&](uint32_t i, int half) {  // no rows past the last step
-        const __amdgpu_buffer_rsrc_t r = b_rsrc((uint32_t)wave + W * i);
+    auto fetch_b = [&](__amdgpu_buffer_rsrc_t r, int half) {  // no rows past the last step
         uint32_t off = lane_off + (uint32_t)(8 * half) * op_pitch;
         asm volatile("" : "+v"(off));  // one address register, not one per row
 #pragma unroll
         for (int t = 0; t < 8; ++t, off += op_pitch) b[half][t] = buffer_load<NB>(r, off);
         asm volatile("" ::: "memory");
     };
-    auto multiply_half = [&](uint32_t i, int half) {
-        float x[8];
+    auto values_of_a = [&](int half, float (&x)[8]) {
 #pragma unroll
         for (int t = 0; t < 8; ++t) x[t] = expanded[64 * (2 * half + t / 4)][t % 4];
 #pragma unroll
         for (int q = 0; q < 2; ++q) expanded[64 * (2 * half + q)] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        parts a = in_parts(x, lost);
-        parts_done(a, lost);
+    };
+    auto multiply_parts = [&](__amdgpu_buffer_rsrc_t next, int half) {
+        float x[8];
+        values_of_a(half, x);
+        parts a = in_parts<false>(x, entries);
+        const u32x4 h = __builtin_bit_cast(u32x4, a.h);
+        entries |= h[0] | h[1] | h[2] | h[3];
+        parts_done(a, entries);
 #pragma unroll
         for (int j = 0; j < NB; ++j) {
             __builtin_amdgcn_sched_barrier(0);
@@ -521,9 +547,9 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
             for (int t = 0; t < 8; ++t) x[t] = part(b[half][t], j);
             // not before this point: two groups of parts do not fit the registers
             asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]));
-            parts p = in_parts(x, lost);
+            parts p = in_parts<true>(x, lost);
             parts_done(p, lost);
-            if (j == NB - 1) fetch_b(i + 1, half);
+            if (j == NB - 1) fetch_b(next, half);
             cor[j] = Tile<R>::mfma(p.l, a.h, cor[j]);
             cor[j] = Tile<R>::mfma(p.h, a.l, cor[j]);
             cor[j] = Tile<R>::mfma(p.m, a.m, cor[j]);
@@ -533,58 +559,82 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-
-    for (uint32_t first = 0; first < count; first = last) {
-        bounds(first);
-        fetch_a(first, 0);
-        if (STAGES == 2) fetch_a(first + 1, 1);
-        fetch_b(first, 0);
-        fetch_b(first, 1);
-        for (uint32_t i = first; i < last; i += STAGES) {
+    auto multiply_whole = [&](__amdgpu_buffer_rsrc_t next, int half) {
+        float x[8];
+        values_of_a(half, x);
 #pragma unroll
-            for (int u = 0; u < STAGES; ++u) {
-                if (u == 1 && i + 1 >= last) break;
-                // the step's block has arrived: younger are the other stage's and 16 loads of B
-                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 1) * AL + 16) : "memory");
-                scatter(u);
-                fetch_a(i + (uint32_t)(u + STAGES), u);
-                multiply_half(i + (uint32_t)u, 0);
-                multiply_half(i + (uint32_t)u, 1);
+        for (int t = 0; t < 8; ++t)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[j] = Tile<R>::mfma(part(b[half][t], j), x[t], acc[j]);
+        fetch_b(next, half);
+    };
+    auto all_steps = [&](auto multiply_half) {
+        for (uint32_t first = 0; first < count; first = last) {
+            bounds(first);
+            fetch_a(first, 0);
+            if (STAGES == 2) fetch_a(first + 1, 1);
+            fetch_b(b_rsrc((uint32_t)wave + W * first), 0);
+            fetch_b(b_rsrc((uint32_t)wave + W * first), 1);
+            for (uint32_t i = first; i < last; i += STAGES) {
+#pragma unroll
+                for (int u = 0; u < STAGES; ++u) {
+                    if (u == 1 && i + 1 >= last) break;
+                    // the step's block has arrived: younger are the other stage's and 16 loads of B
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 1) * AL + 16) : "memory");
+                    scatter(u);
+                    fetch_a(i + (uint32_t)(u + STAGES), u);
+                    const __amdgpu_buffer_rsrc_t next = b_rsrc((uint32_t)wave + W * (i + (uint32_t)u + 1u));
+                    multiply_half(next, 0);
+                    multiply_half(next, 1);
+                }
             }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no block on its way to the stages
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no block on its way to the stages
-    }
+    };
+    all_steps(multiply_parts);
 
-    float bad = 0.0f;
+    float not_finite = 0.0f;
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         acc[j] += cor[j];
 #pragma unroll
-        for (int x = 0; x < 16; ++x) bad = __builtin_fmaf(acc[j][x], 0.0f, bad);
+        for (int x = 0; x < 16; ++x) not_finite = __builtin_fmaf(acc[j][x], 0.0f, not_finite);
     }
-    if (__builtin_expect(__any((lost & 0xFFFFu) != 0 || bad != 0.0f), 0)) {
-#pragma unroll
-        for (int j = 0; j < NB; ++j) acc[j] = f32x16{};
-#pragma unroll 1
-        for (uint32_t i = 0; i < count; ++i) {
-            if ((i & 63u) == 0) bounds(i);
-            fetch_a(i, 0);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            scatter(0);
-            const __amdgpu_buffer_rsrc_t r = b_rsrc((uint32_t)wave + W * i);
-#pragma unroll 1
-            for (int t = 0; t < OPS; ++t) {
-                float *e = reinterpret_cast<float *>(expanded + 64 * (t / 4)) + t % 4;
-                const float a = *e;
-                *e = 0.0f;
-                const b_t bt = buffer_load<NB>(r, lane_off + (uint32_t)t * op_pitch);
-#pragma unroll
-                for (int j = 0; j < NB; ++j) acc[j] = Tile<R>::mfma(part(bt, j), a, acc[j]);
-            }
-            lds_in_order();
+    const uint64_t lossy = __ballot((lost & 0xFFFFu) != 0), filled = __ballot(entries != 0), bad = __ballot(not_finite != 0.0f);
+    if (lane == 0) losses[wave] = loss{(uint32_t)(lossy | lossy >> 32), (uint32_t)(filled | filled >> 32), (uint32_t)(lossy != 0) + 2u * (uint32_t)(bad != 0)};
+    auto none = [](uint32_t, const f32x4 &) {};
+    const int one = lane < W ? lane : 0;
+    uint32_t found;
+    add_halves<R, NB, W>(acc, lds, wave, lane, [&] { found = losses[one].found; });
+    if (__builtin_expect(!__any(found != 0), 1)) {
+        store_sum<R, NB, W>(args, lds, panel, n0, wave, lane, none);
+        return;
+    }
+    if (!__any(found > 1)) {
+        uint32_t groups = 0, rows = 0;
+        for (int w = 0; w < W; ++w) {
+            groups |= losses[w].groups;
+            rows |= losses[w].rows;
         }
+        const float enough = args.largest * (float)args.K * 0x1p-101f;  // (infinite: no sum is)
+        const bool row = (rows >> (lane % R) & 1) != 0;
+        bool small = false;
+        store_sum<R, NB, W>(args, lds, panel, n0, wave, lane, [&](uint32_t n, const f32x4 &sum) {
+#pragma unroll
+            for (uint32_t x = 0; x < 4; ++x)
+                small |= row && (groups >> ((n + x - n0) / NB) & 1) != 0 && n + x < N && !(__builtin_fabsf(sum[(int)x]) > enough);
+        });
+        const bool any_small = __any(small);
+        if (lane == 0) verdicts[wave] = any_small;
+        __syncthreads();
+        if (!__any(verdicts[one] != 0)) return;
     }
-    store_sum_of_waves<R, NB, W>(args, acc, lds, panel, n0, wave, lane);
+    clear();
+#pragma unroll
+    for (int j = 0; j < NB; ++j) acc[j] = f32x16{};
+    all_steps(multiply_whole);
+    add_halves<R, NB, W>(acc, lds, wave, lane, [] {});
+    store_sum<R, NB, W>(args, lds, panel, n0, wave, lane, none);
 }
 
 template <int RUNS, int NB> void launch_split(tile_args &a, hipStream_t s)
@@ -838,6 +888,10 @@ template <int R> __device__ __forceinline__ position position_of(uint32_t row, u
 
 enum { BAD_COLUMN = 1, TWICE = 2 };
 
+// Sizes, as bits, between which a value is the sum of its parts (in_parts): 2^-110, the smallest whose last bit is a bf16, and
+// 2^128 - 2^119, which rounds to no bf16.
+constexpr uint32_t SMALLEST_IN_PARTS = (127u - 110u) << 23, LARGEST_IN_PARTS = 0x7F7F8000u;
+
 // The order of a block's entries.  A wave writes up to 64 of them to LDS at a time, so entries
 // that lie in different banks should follow each other: the places of a block fall into 64 classes of
 // 16 (place in words modulo 64), and the block takes the first entry of every class, in class order, then the
@@ -1025,6 +1079,27 @@ template <int R, typename Col> __global__ __launch_bounds__(1024) void panel_ker
     if (threadIdx.x == 0) {
         o[n_steps] = total;
         panel_base[panel] = total;
+    }
+}
+
+// The sizes of the values: range[0] = the largest, as bits; range[1] = 2^32 less the smallest that is not zero
+// (maxima on cleared memory).  Sizes order as their bits do, infinite and NaN ones last.
+__global__ __launch_bounds__(256) void range_kernel(const float *vals, int64_t nnz, uint32_t *range)
+{
+    uint32_t largest = 0, smallest = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * 256) {
+        const uint32_t size = __float_as_uint(vals[i]) & 0x7FFFFFFFu;
+        largest = size > largest ? size : largest;
+        smallest = 0u - size > smallest ? 0u - size : smallest;
+    }
+    for (int d = 32; d > 0; d /= 2) {
+        const uint32_t l = __shfl_xor(largest, d), s = __shfl_xor(smallest, d);
+        largest = l > largest ? l : largest;
+        smallest = s > smallest ? s : smallest;
+    }
+    if (threadIdx.x % 64 == 0) {
+        if (largest > range[0]) atomicMax(&range[0], largest);
+        if (smallest > range[1]) atomicMax(&range[1], smallest);
     }
 }
 
@@ -1324,9 +1399,9 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     uploader upload;  // (released before the memory)
     const bool staged = upload.begin(K, col_idx, vals, nnz, memory.stream), narrow = staged && upload.narrow_columns();
     const size_t at_ptr = memory.reserve((size_t)(M + 1) * 4), at_col = memory.reserve((size_t)nnz * 4), at_val = memory.reserve((size_t)nnz * 4),
-                 at_base = memory.reserve((size_t)(P + 2) * 8), at_masks = memory.reserve(mask_bytes),
+                 at_base = memory.reserve((size_t)(P + 3) * 8), at_masks = memory.reserve(mask_bytes),
                  at_order = memory.reserve((size_t)(P * S) * sizeof(block_order)), at_counts = memory.reserve((size_t)(P * S) * 4);
-    // the panels' lengths, the flags behind them, the masks (which panel_kernel writes whole)
+    // the panels' lengths, the flags and the values' sizes behind them, the masks (which panel_kernel writes whole)
     const size_t zeros = (S <= MOST_STEPS_IN_LDS ? at_masks : at_masks + mask_bytes) - at_base;
     TRY(memory.take());
     int32_t *d_ptr = memory.at<int32_t>(at_ptr), *d_col = memory.at<int32_t>(at_col);
@@ -1366,8 +1441,15 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
     } else {
         TRY(hipMemcpyWithStream(d_val, vals, (size_t)nnz * 4, hipMemcpyHostToDevice, s));  // the kernels run meanwhile
     }
-    uint64_t answer[2];
-    TRY(hipMemcpyWithStream(answer, base + P, 16, hipMemcpyDeviceToHost, s));
+    if (R == 32) {
+        hipLaunchKernelGGL(range_kernel, dim3((unsigned)std::min<int64_t>(512, nnz / 1024 + 1)), dim3(256), 0, s, d_val, nnz, flags + 2);
+        TRY(hipGetLastError());
+    }
+    uint64_t answer[3];
+    TRY(hipMemcpyWithStream(answer, base + P, 24, hipMemcpyDeviceToHost, s));
+    const uint32_t largest = (uint32_t)answer[2], smallest = 0u - (uint32_t)(answer[2] >> 32);
+    std::memcpy(&out.largest, &largest, 4);
+    out.exact_parts = largest < LARGEST_IN_PARTS && (smallest == 0 || smallest >= SMALLEST_IN_PARTS);
     const uint32_t bad = (uint32_t)answer[1];
     out.loads = std::max(1, (int32_t)(((uint32_t)(answer[1] >> 32) + 255u) / 256u));
     if (bad & BAD_COLUMN) { status = 2; return hipSuccess; }
@@ -1465,7 +1547,7 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream)
 {
     tile_args a{p.d_stream, p.d_offsets, B, C, (uint64_t)K * (uint64_t)N * 4u, (int32_t)p.n_panels, (int32_t)p.n_steps, 1,
-                (int32_t)M, (int32_t)K, N, 0};
+                (int32_t)M, (int32_t)K, N, 0, p.largest};
     hipStream_t s = (hipStream_t)stream;
     const int64_t step_bytes = (int64_t)TILE_OPERANDS * 64 / p.rows * 4 * N;  // rows of B a step touches
     if (step_bytes >= ((int64_t)1 << 32)) {
@@ -1484,9 +1566,12 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
     int NB = 1;
     spmm_tiles_time(p.rows, M, K, N, 0.0, 0.0, &NB);
     switch (p.rows * 8 + NB) {
-    case 32 * 8 + 4: launch_split<4>(a, p.loads, s); break;
+    case 32 * 8 + 4:
+        if (p.exact_parts) launch_split<4>(a, p.loads, s);
+        else launch<32, 4, 8, false, 2>(a, s);
+        break;
     case 32 * 8 + 2:
-        if (p.n_steps <= FEW_STEPS) launch<32, 2, 16, false, 4>(a, s);
+        if (p.n_steps <= FEW_STEPS || !p.exact_parts) launch<32, 2, 16, false, 4>(a, s);
         else launch_split<2>(a, p.loads, s);
         break;
     case 32 * 8 + 1: launch<32, 1, 16, true, 4>(a, s); break;

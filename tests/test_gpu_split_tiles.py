@@ -151,6 +151,67 @@ def test_a_few_tiny_values_among_ordinary_ones(torch_gpu, oracle):  # noqa: F811
     assert (np.abs(C - C_ref) <= 2.0 ** -21 * S + 3 * 2.0 ** -149).all()
 
 
+def with_tails(rng, K, N, share):
+    """Normal values, some so small that they are no sum of three bf16 numbers, subnormal ones among them."""
+    B = rng.standard_normal((K, N)).astype(np.float32)
+    tiny = rng.random((K, N)) < share
+    B[tiny] *= 10.0 ** rng.uniform(-44, -34, int(tiny.sum())).astype(np.float32)
+    return B
+
+
+@pytest.mark.parametrize("share", [0.01, 0.6, 1.0])
+@pytest.mark.parametrize("M,K,N,groups", [(64, 600, WIDE, 4), (57, 300, WIDE - 5, 4), (32, 1300, WIDE // 2 + 6, 2)])
+@pytest.mark.parametrize("tiny_in_a", [False, True])
+def test_tails(torch_gpu, oracle, M, K, N, groups, share, tiny_in_a):  # noqa: F811
+    """Whether a wave takes its first or its second result: columns with and without ordinary values, columns of zeros and tiny ones, rows
+    without entries (of the matrix, of a wave), columns past the last, and values of A that are no such sum.  Bound: 2^-24 of
+    what is left out of a product, and fewer than 120 roundings, one per 16 columns of A (two with fp32 instructions) and wave."""
+    rng = np.random.default_rng(K + N)
+    W = np.where(rng.random((M, K)) < 0.4, rng.standard_normal((M, K)), 0.0).astype(np.float32)
+    W[5] = 0
+    W[9, 1:] = 0
+    W[11, : K // 2] = 0
+    if tiny_in_a:
+        W[3, 7] = 1e-40
+        W[20, 50:60] = 3e-36
+    csr = gen.csr_from_dense(W)
+    B = with_tails(rng, K, N, share)
+    B[:, 3] = 0
+    B[:, 17] = np.where(np.arange(K) % 3 == 0, 1e-40, 0)
+    B[:, N - 1] = 2e-38
+    C = product(torch_gpu, csr, B, groups)
+    C_ref, S = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, B, parallel=True)
+    steps = (K + 31) // 32
+    assert (np.abs(C - C_ref) <= (steps * 16 + 40) * 2.0 ** -24 * S + steps * 16 * 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("M,K,sparsity,groups", [(8192, 2048, 0.5, 4), (4096, 4096, 0.5, 2), (4096, 1024, 0.97, 2)])
+def test_tails_take_no_second_pass(torch_gpu, M, K, sparsity, groups):  # noqa: F811
+    """Values that cannot change a result cost no time.  (With a second pass for each of them the product takes 2.7 times as long.)"""
+    torch = torch_gpu
+    csr = gen.uniform_positions(M, K, sparsity, 3)
+    plan = spmm.plan_create(csr.M, K, csr.row_ptr, csr.col_idx, csr.vals, tiles=32)
+    rng = np.random.default_rng(1)
+    ordinary, tails = (torch.from_numpy(with_tails(rng, K, 128, share)).cuda() for share in (0.0, 0.05))
+    C = torch.empty((csr.M, 128), device="cuda")
+
+    def fastest(B):
+        times = []
+        for _ in range(8):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            start.record()
+            for _ in range(20):
+                plan.execute(B, C)
+            end.record()
+            end.synchronize()
+            times.append(start.elapsed_time(end))
+        return min(times)
+
+    assert column_groups(M, K, 128) == groups
+    fastest(ordinary)
+    assert fastest(tails) < 1.5 * fastest(ordinary)
+
+
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
 def test_how_far_a_value_outside_the_domain_reaches(torch_gpu, value):  # noqa: F811
     """As on the other tiles: its column of C and no other."""
