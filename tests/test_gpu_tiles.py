@@ -163,6 +163,8 @@ def test_a_plan_is_created_while_another_stream_works(torch_gpu, oracle):  # noq
     C, plan = gpu_product(torch, csr, B, tiles=16)   # everything is loaded
     plan.destroy()
     start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    torch.cuda._sleep(1000)   # its first call also loads the kernel
+    torch.cuda.synchronize()
     start.record()
     torch.cuda._sleep(1000000)
     end.record()
