@@ -170,15 +170,20 @@ def test_a_plan_is_created_while_another_stream_works(torch_gpu, oracle):  # noq
     end.record()
     torch.cuda.synchronize()
     cycles = int(1000000 * 200.0 / start.elapsed_time(end))   # 200 ms
-    side, done = torch.cuda.Stream(), torch.cuda.Event()
-    with torch.cuda.stream(side):
-        torch.cuda._sleep(1000)
-        torch.cuda.synchronize()
-        free = torch.cuda.mem_get_info()[0]
-        torch.cuda._sleep(cycles)
-        done.record()
-    plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=16)
-    assert not done.query(), "the creation waited for the other stream"
+    for _ in range(8):   # a stream that shares the builder's hardware queue (one of four) holds it up whatever the library does
+        side, done = torch.cuda.Stream(), torch.cuda.Event()
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(1000)
+            torch.cuda.synchronize()
+            free = torch.cuda.mem_get_info()[0]
+            torch.cuda._sleep(cycles)
+            done.record()
+        plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, tiles=16)
+        waited = done.query()
+        if not waited:
+            break
+        plan.destroy()
+    assert not waited, "the creation waited for the other stream"
     assert plan.describe()["tile_rows"] == 16
     assert free - torch.cuda.mem_get_info()[0] <= plan.describe()["device_bytes"] + (4 << 20)
     dC = plan.execute(torch.from_numpy(B).cuda())
