@@ -1,4 +1,5 @@
 """Plans on tiles whose arrays go to the device through pinned memory (GPU machine only)."""
+import gc
 import threading
 
 import numpy as np
@@ -70,3 +71,39 @@ def test_creations_at_the_same_time(torch_gpu):  # noqa: F811
         t.join()
     for plan, (K, arrays) in zip(plans, cases):
         assert right(torch_gpu, plan, K, *arrays)
+
+
+def mapped():
+    """Bytes of this process's mappings of the device's memory: pinned memory and what the device has allocated."""
+    total = 0
+    with open("/proc/self/maps") as f:
+        for line in f:
+            if "/dev/dri/" in line:
+                first, last = line.split()[0].split("-")
+                total += int(last, 16) - int(first, 16)
+    return total
+
+
+def test_the_pinned_memory_is_given_back(torch_gpu):  # noqa: F811
+    """With the last plan on tiles, also right after it was made, and after a creation that failed; 6 MiB of it while there is one."""
+    K = 20000
+    row_ptr, col_idx, vals = matrix(SMALLEST + 5, K, 1)
+    outside = col_idx.copy()
+    outside[9] = K
+    small = spmm.plan_create(64, K, *matrix(4096, K, 2), tiles=32)   # what the library and the runtime set up once
+    del small
+    gc.collect()
+    torch_gpu.cuda.synchronize()
+    before = mapped()
+    with pytest.raises(spmm.SpmmError):
+        spmm.plan_create(64, K, row_ptr, outside, vals, tiles=32)
+    assert mapped() == before
+    for _ in range(2):
+        first = spmm.plan_create(64, K, row_ptr, col_idx, vals, tiles=32)
+        second = spmm.plan_create(64, K, row_ptr, col_idx, vals, tiles=32)
+        with_two = mapped()
+        del first
+        with_one = mapped()
+        del second
+        assert mapped() == before
+        assert with_one - before >= 6 << 20 and with_two > with_one
