@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstring>
 #include <mutex>
 #include <thread>
@@ -1297,7 +1298,7 @@ public:
                 const size_t oldest = usable.load() - staging_memory::PIECES;  // piece in the place that is wanted next
                 if (oldest < next && usable.load() < pieces.size()) {
                     const hipError_t e = hipEventQuery(copied[oldest % staging_memory::PIECES]);
-                    if (e == hipSuccess) usable.fetch_add(1);
+                    if (e == hipSuccess) one_more_usable();
                     else if (e != hipErrorNotReady) return e;
                     else (void)hipGetLastError();
                 }
@@ -1314,7 +1315,11 @@ public:
     void arrived() { next = 0; }                             // the stream has been waited for
     ~uploader()
     {
-        stop.store(true);
+        {
+            const std::lock_guard<std::mutex> hold(lock);
+            stop.store(true);
+        }
+        changed.notify_all();
         for (std::thread &t : helpers) t.join();
         if (pinned) {
             if (next > 0) (void)hipStreamSynchronize(stream);
@@ -1334,8 +1339,20 @@ private:
     char *place(size_t i) const { return pinned + i % staging_memory::PIECES * staging_memory::PIECE; }
     void help()
     {
-        while (!stop.load() && fill_piece.load() < pieces.size())
-            if (!fill_part()) std::this_thread::yield();
+        while (!stop.load()) {
+            if (fill_part()) continue;
+            std::unique_lock<std::mutex> hold(lock);
+            changed.wait(hold, [this] { return stop.load() || fill_piece.load() == pieces.size() || fill_piece.load() < usable.load(); });
+            if (fill_piece.load() == pieces.size()) return;
+        }
+    }
+    void one_more_usable()
+    {
+        {
+            const std::lock_guard<std::mutex> hold(lock);
+            usable.fetch_add(1);
+        }
+        changed.notify_all();
     }
     // Fills one part; false if there is none, or no place for it yet.
     bool fill_part()
@@ -1349,6 +1366,7 @@ private:
             if (next_part == parts(pieces[i])) {
                 next_part = 0;
                 fill_piece.store(i + 1);
+                if (i + 1 == pieces.size()) changed.notify_all();
             }
         }
         const piece &p = pieces[i];
@@ -1390,6 +1408,7 @@ private:
     std::vector<std::atomic<int>> left;  // parts of each piece that are still to be filled
     size_t column_pieces = 0, next = 0, next_part = 0;
     std::mutex lock;
+    std::condition_variable changed;  // fill_piece, usable or stop, for helpers that have nothing to fill
     std::atomic<size_t> fill_piece{0}, usable{staging_memory::PIECES};  // pieces below have a place in the memory
     std::atomic<bool> outside{false}, stop{false};
     std::vector<std::thread> helpers;
