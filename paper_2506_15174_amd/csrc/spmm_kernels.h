@@ -37,6 +37,47 @@ struct spmm_launch_args {
     int32_t ldc_out = 0;     // its leading dimension (= N)
 };
 
+// What a workgroup of a launch computes: the plan's block and the column tile.  Workgroups start in the order of x, then y.
+// The first `front` blocks of all tiles come first, block by block, then the others tile by tile.
+struct place {
+    uint32_t block, tile;
+};
+#ifdef __HIPCC__
+#define SPMM_DEVICE __device__ __forceinline__
+#else
+#define SPMM_DEVICE inline
+#endif
+template <typename args_t, typename at_t> SPMM_DEVICE place place_of(const args_t &args, const at_t &group)
+{
+    if (__builtin_expect(args.front == 0, 1)) return place{group.x, group.y};  // (one tile: without a taken branch)
+    const uint32_t at = group.y * args.n_blocks + group.x, front = args.front * args.n_tiles;
+    if (at < front) {
+        const uint32_t block = at / args.n_tiles;
+        return place{block, at - block * args.n_tiles};
+    }
+    const uint32_t rest = args.n_blocks - args.front, tile = (at - front) / rest;
+    return place{args.front + at - front - tile * rest, tile};
+}
+// Two, four and eight tiles of 64 or 128 columns: all blocks.  Workgroups go to the eight XCDs in turn, so that an
+// XCD's L2 sees the rows of one tile and fetches a half (a quarter, an eighth) of B, and the launch ends with the
+// lightest blocks of all tiles.  14 even and uneven matrices: 7 % faster at 256 columns, 11 % at 512 (at worst 2 % slower);
+// 6000 x 6000, 10 % lognormal, 256 columns 117 -> 95 us, 4096 x 4096, 5 % even, 32.4 -> 29.7.  Not where the last tile is less
+// than seven eighths of the others: its XCDs would be done early (3 to 8 % slower on even matrices at 200 to 230 columns).
+//
+// Other launches of uneven plans: taken tile by tile, the heaviest blocks of the second tile start when the first has
+// none left to hide them behind.  One block per compute unit comes first, of more or narrower tiles only those that are
+// heavier than most: 1024 x 4096, 6 % in Zipf rows, 200 columns 34.7 -> 22.0 us; 1024 x 4096, 10 % lognormal, 175 columns
+// (three tiles of 64) 22.1 -> 19.9.  14 matrices, 8 of them uneven, at 175 to 245 columns: 5 % faster on average; at 300 and 384 columns 3 %,
+// with one of 28 that is 6 % slower.  Tiles of 16 columns and less, which share the cache lines of B: none.
+inline uint32_t front_blocks(const spmm_launch_args &a)
+{
+    const int32_t T = a.n_tiles, last = a.width - (T - 1) * a.tile_cols;
+    if (T == 1 || a.tile_cols < 32) return 0;
+    if ((T == 2 || T == 4 || T == 8) && a.tile_cols >= 64 && 8 * last >= 7 * a.tile_cols) return (uint32_t)a.n_blocks;
+    const int32_t wanted = a.heavy > 0 && (a.tile_cols == 64 || (a.tile_cols > 64 && T == 2)) ? a.n_blocks : a.heavy;
+    return (uint32_t)(wanted < 256 / T ? wanted : 256 / T);
+}
+
 // Enqueues one launch of n_tiles column tiles (plus the small launches that add the sums of
 // panels cut across workgroups and of plans cut along K).  ufi = rows per panel of the plan (1, 2, 4, 8).
 // slices = 2 / 4 / 8: four columns per lane (16-byte loads and stores at 4-byte alignment;

@@ -2,6 +2,7 @@
 // which the HIP runtime and the kernels' entry points are stand-ins in host memory.
 //   failures   every allocation of a plan's creation is made to fail in turn, also those on the device
 //   launches   what spmm_execute hands to the launcher
+//   places     what the workgroups of a launch compute
 #include <hip/hip_runtime_api.h>
 
 #include <atomic>
@@ -286,11 +287,70 @@ static void held_to_two()
     REQUIRE(launches(spread(512, 0.5), 64, &info)[0].lds_pad == 0 && info.n_blocks <= 512);
 }
 
+struct launch_shape {
+    uint32_t n_blocks, n_tiles, front;
+};
+struct workgroup {
+    uint32_t x, y;
+};
+
+// Every block of every tile exactly once: the first `front` blocks of all tiles, block by block, then the others tile by tile.
+static void places_of(uint32_t n_blocks, uint32_t n_tiles, uint32_t front)
+{
+    uint32_t block = 0, tile = 0;  // expected
+    for (uint32_t y = 0; y < n_tiles; ++y)
+        for (uint32_t x = 0; x < n_blocks; ++x) {
+            const place p = place_of(launch_shape{n_blocks, n_tiles, front}, workgroup{x, y});
+            REQUIRE(p.block == block && p.tile == tile);
+            if (block < front) {
+                if (++tile == n_tiles) {
+                    tile = 0;
+                    ++block;
+                }
+            } else if (++block == n_blocks) {
+                block = front;
+                ++tile;
+            }
+        }
+    REQUIRE(front == n_blocks ? block == n_blocks : tile == n_tiles);
+}
+
+static void places()
+{
+    for (uint32_t n_blocks = 1; n_blocks <= 70; ++n_blocks)
+        for (uint32_t n_tiles = 1; n_tiles <= 20; ++n_tiles)
+            for (uint32_t front = 0; front <= n_blocks; ++front) places_of(n_blocks, n_tiles, front);
+    for (uint32_t front : {0u, 1u, 128u, 256u, 4999u, 5000u}) places_of(5000, 5, front);
+    // the largest launches: workgroups of 256 threads, fewer than 2^32 of these in a row of the grid
+    const uint32_t most = (1u << 24) - 1;
+    const launch_shape wide{most, 256, 1}, whole_front{most, 8, most};
+    const place first = place_of(wide, workgroup{0, 0}), last = place_of(wide, workgroup{most - 1, 255}), end = place_of(whole_front, workgroup{most - 1, 7});
+    REQUIRE(first.block == 0 && first.tile == 0 && last.block == most - 1 && last.tile == 255 && end.block == most - 1 && end.tile == 7);
+    // the rule's choices, at the edges of its widths, for plans of few and many, even and uneven blocks
+    uint32_t whole = 0, some = 0, none = 0;
+    for (int64_t M : {300, 1024, 3000})
+        for (double sigma : {0.0, 0.7}) {
+            const csr a = spread(700, sigma, M);
+            for (int N : {64, 128, 129, 160, 161, 176, 192, 200, 239, 240, 256, 300, 384, 495, 496, 512, 1008, 1024, 1100, 40000}) {
+                spmm_plan_info_t info;
+                for (const spmm_launch_args &l : launches(a, N, &info)) {
+                    const uint32_t front = front_blocks(l), n = (uint32_t)l.n_blocks;
+                    REQUIRE(front <= n && (front < n || l.n_tiles <= 256));
+                    places_of(n, (uint32_t)l.n_tiles, front);
+                    (front == 0 ? none : front == n ? whole : some) += 1;
+                }
+            }
+        }
+    std::printf("launches: %u tile by tile, %u some blocks first, %u block by block\n", none, some, whole);
+    REQUIRE(none > 0 && some > 0 && whole > 0);
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "failures")) failures();
     else if (!std::strcmp(what, "launches")) held_to_two();
+    else if (!std::strcmp(what, "places")) places();
     else return 2;
     std::printf("ok\n");
     return 0;

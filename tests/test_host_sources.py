@@ -32,3 +32,7 @@ def test_failed_allocations_are_a_status(program):
 
 def test_compute_units_held_to_two_workgroups(program):
     passes(program, "launches")
+
+
+def test_every_block_of_every_column_tile_once(program):
+    passes(program, "places")

@@ -91,3 +91,23 @@ def test_static_scratch_entry_point_runs_plans_without_cut_panels_and_refuses_ov
     assert lib.spmm_execute(heavy.handle, dB.data_ptr(), 8, dC.data_ptr(), None) == spmm.SPMM_OK
     torch.cuda.synchronize()
     assert torch.equal(dC, torch.full_like(dC, float(K)))
+
+
+@pytest.mark.parametrize("M,tiles_at_once", [(1800, 2), (3600, 1)])
+@pytest.mark.parametrize("N", [256, 512, 640])
+def test_several_column_tiles_in_launches_of_what_the_array_holds(M, tiles_at_once, N):
+    """The array holds fewer column tiles than the plan's own scratch (four), so the two entry points cut the same product into
+    different launches, each with its own order of the tiles' workgroups.  Small whole numbers: exact."""
+    import torch
+    spmm.load()
+    K = 520
+    row_ptr = (np.arange(M + 1, dtype=np.int64) * K).astype(np.int32)
+    col_idx = np.tile(np.arange(K, dtype=np.int32), M)
+    vals = np.random.default_rng(M).integers(-4, 5, M * K).astype(np.float32)
+    plan = spmm.plan_create(M, K, row_ptr, col_idx, vals, group_nnz=256, ufi=8, cross=1, sort_rows=-1)
+    info = plan.describe()
+    assert info["n_cross"] > 0 and (6 << 20) // (info["scratch_bytes"] // 4) == tiles_at_once
+    B = np.random.default_rng(N).integers(-4, 5, (K, N)).astype(np.float32)
+    C0, C1 = _both(torch, plan, B)
+    C_ref = vals.reshape(M, K).astype(np.float64) @ B.astype(np.float64)
+    assert np.array_equal(C0.astype(np.float64), C_ref) and np.array_equal(C1.astype(np.float64), C_ref)
