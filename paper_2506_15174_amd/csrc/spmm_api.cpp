@@ -348,12 +348,13 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     // rows of B that concurrently running waves sweep inside it (same matrix: 262 against 275 us).
     const uint32_t tile_pad = narrow_tiles ? 24u << 10 : 0u;
     // 161 to 192 columns are three tiles of 64 in one launch: as 128 and 64 the launch of the wide tile drains
-    // before that of the rest begins.  3001 x 2511, 85 % pruned, 192 columns: 40.0 against 28.9 us; 29 even and uneven
-    // matrices in panels of several rows at 161, 188 and 192 columns: 13 % faster on average, 0.2 % slower at worst.  Single
+    // before that of the rest begins.  24 even and uneven matrices at 161, 176, 188 and 192 columns: 13 to 18 % faster on
+    // average, 2 % slower at worst (24 others 12 to 17 and 6 %).  Single
     // rows share no load, and a row of B that begins inside of a cache line takes one line in three more than its
-    // columns in tiles of 64, one in five in tiles of 128: with such rows they are up to 17 % slower from 2^19
-    // entries on and up to 40 % faster below, with whole lines and blocks of even weight 11 % faster on average (9 % slower on Zipf rows).
-    // 129 to 160 columns, 128 and a tile of 32, stay: as three tiles of 64 nineteen matrices are 4 % slower on average, up to 18 %.
+    // columns in tiles of 64, one in five in tiles of 128: from 2^19 entries on even ones are up to 11 % slower then, uneven ones
+    // between 14 % faster and 9 % slower; below, up to twice as fast.
+    // 129 to 160 columns, 128 and a tile of 32, stay: as three tiles of 64 the 24 matrices are 5 % slower on average at 130 columns, 1 % at 144 and 3 % faster at 160
+    // (0.75 to 1.24 of the time).
     const bool three_tiles = !sliced && !wide && h.ufk == UFK && N > 160 && N <= 192 &&
                              (h.ufi > 1 || (N % 32 == 0 && plan->heavy == 0) || h.nnz < ((int64_t)1 << 19));
     // Column tiles of one width share a launch (front_blocks: in which order; a

@@ -60,15 +60,16 @@ template <typename args_t, typename at_t> SPMM_DEVICE place place_of(const args_
 }
 // Two, four and eight tiles of 64 or 128 columns: all blocks.  Workgroups go to the eight XCDs in turn, so that an
 // XCD's L2 sees the rows of one tile and fetches a half (a quarter, an eighth) of B, and the launch ends with the
-// lightest blocks of all tiles.  14 even and uneven matrices: 7 % faster at 256 columns, 11 % at 512 (at worst 2 % slower);
-// 6000 x 6000, 10 % lognormal, 256 columns 117 -> 95 us, 4096 x 4096, 5 % even, 32.4 -> 29.7.  Not where the last tile is less
-// than seven eighths of the others: its XCDs would be done early (3 to 8 % slower on even matrices at 200 to 230 columns).
+// lightest blocks of all tiles.  48 even and uneven matrices at 256 columns: 10 % faster on average, at worst 5 % slower; 24 at 512: 14 and 4 %.  4096 x 4096, 5 %
+// even, 256 columns 31.8 -> 29.5 us.  Not where the last tile is less
+// than seven eighths of the others: its XCDs would be done early (even matrices at 200 columns 5 % slower on average, up to 10 %).
 //
 // Other launches of uneven plans: taken tile by tile, the heaviest blocks of the second tile start when the first has
 // none left to hide them behind.  One block per compute unit comes first, of more or narrower tiles only those that are
-// heavier than most: 1024 x 4096, 6 % in Zipf rows, 200 columns 34.7 -> 22.0 us; 1024 x 4096, 10 % lognormal, 175 columns
-// (three tiles of 64) 22.1 -> 19.9.  14 matrices, 8 of them uneven, at 175 to 245 columns: 5 % faster on average; at 300 and 384 columns 3 %,
-// with one of 28 that is 6 % slower.  Tiles of 16 columns and less, which share the cache lines of B: none.
+// heavier than most: 1024 x 4096, 6 % in Zipf rows, 200 columns 33.9 -> 21.0 us; 1024 x 4096, 10 % lognormal, 25.1 -> 21.5.  The 48 at
+// 200 and 224 columns: 4 and 5 % faster on average, at 384 2 %; Zipf rows gain most and some of them lose (16384 x 2048, 3 % kept, 12 % at 200 columns,
+// 7 % at 384; 3000 x 4096, 5 % kept, 10 %).  Only the heavier blocks first at all widths: 2 % slower on average at 161 to 224 columns, 23 % at
+// worst.  Tiles of 16 columns and less, which share the cache lines of B: none.
 inline uint32_t front_blocks(const spmm_launch_args &a)
 {
     const int32_t T = a.n_tiles, last = a.width - (T - 1) * a.tile_cols;
