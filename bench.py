@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the hot path: fp32 CSR SpMM C = A x B on one MI355X.
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload conv|stress|ffn|ffn-all|matrix|sweep|narrow|sparsity|ablation|tune|unhinted|paths]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload conv|stress|ffn|ffn-all|matrix|sweep|narrow|sparsity|ablation|tune|unhinted|paths|parts]
 
 A step is one pass of the whole hot path (spmm_execute, every kernel it
 launches) over the workload's column counts, with the plan and all operands
@@ -30,8 +30,9 @@ the sweep of the paper's Figure 9), `ablation` (the method's ingredients switche
 on one by one, the ladder of the paper's Figure 7) and `tune` (every panel height
 and three group budgets forced per matrix: what the closed schedule rule loses
 against the best candidate, and the plan's size against CSR and dense), `unhinted` (what the
-bCols hint is worth) and `paths` (chunks against tiles of every panel height, with the two estimates
-between which a plan's path is chosen).
+bCols hint is worth), `paths` (chunks against tiles of every panel height, with the two estimates
+between which a plan's path is chosen) and `parts` (tiles on bf16 parts: error against 64 bits beside that of fp32
+instructions, and times where the operands hold tiny or infinite values).
 """
 import argparse
 import json
@@ -1007,6 +1008,79 @@ def run_single(args):
     print(json.dumps(out))
 
 
+# rows x columns, share of the entries kept (a whole number: entries of every row), columns of B
+PARTS_PRODUCTS = ((4096, 600, 1, 128), (4096, 600, 2, 128), (4096, 600, 4, 128), (4096, 600, 8, 128), (4096, 600, 16, 128), (4096, 600, 64, 128),
+                  (8192, 600, .3, 64), (8192, 2048, .15, 64), (8192, 8192, .5, 64), (4096, 1024, .3, 128), (3001, 2511, .15, 200),
+                  (4096, 4096, .1, 128), (2048, 2048, .9, 256), (16384, 2048, .3, 128), (8192, 8192, .5, 128), (8192, 8192, .1, 128),
+                  (2048, 16384, .3, 512), (16384, 260, .5, 250))
+
+
+def run_parts(args):
+    """Panels of 32 rows on bf16 parts.  Errors: products of normal values against 64 bits (2-norm of the difference over
+    that of the result), with the same product on panels of 16 rows (fp32 matrix instructions) and on
+    chunks (fp32 fused multiply-adds).  Times: two products with ordinary values, with values of B that have no exact parts
+    (a share of all values; a whole column) or are infinite, and with one such value in A."""
+    import numpy as np
+    import torch
+    import paper_2506_15174_amd as spmm
+    from workloads import generators as gen
+    torch.cuda.set_device(0)
+    errors, times = [], []
+    for M, K, kept, N in PARTS_PRODUCTS:
+        rng = np.random.default_rng(args.seed)
+        if isinstance(kept, int):
+            W = np.zeros((M, K), np.float32)
+            for i in range(M):
+                W[i, rng.choice(K, kept, replace=False)] = rng.standard_normal(kept)
+            csr = gen.csr_from_dense(W)
+        else:
+            csr = gen.uniform_positions(M, K, 1.0 - kept, args.seed)
+        B = torch.from_numpy(rng.standard_normal((K, N), dtype=np.float32)).cuda()
+        rows = torch.from_numpy(np.repeat(np.arange(M), np.diff(csr.row_ptr))).cuda()
+        dense = torch.zeros((M, K), dtype=torch.float64, device="cuda")
+        dense[rows, torch.from_numpy(csr.col_idx).cuda().long()] = torch.from_numpy(csr.vals).cuda().double()
+        exact = dense @ B.double()
+        point = {"M": M, "K": K, "kept": kept, "N": N}
+        for name, tiles in (("parts", 32), ("fp32_matrix", 16), ("chunks", -1)):
+            plan = spmm.plan_create(M, K, csr.row_ptr, csr.col_idx, csr.vals, tiles=tiles)
+            point[name] = float("%.3e" % float((plan.execute(B).double() - exact).norm() / exact.norm()))
+            plan.destroy()
+        point["parts_over_fp32_matrix"] = round(point["parts"] / point["fp32_matrix"], 3)
+        errors.append(point)
+        print(json.dumps(point), file=sys.stderr, flush=True)
+        del dense, exact
+    for M, K, kept, law, N in ((8192, 8192, .5, gen.uniform_positions, 128), (4096, 1024, .3, gen.lognormal_rows, 128)):
+        csr = law(M, K, 1.0 - kept, args.seed)
+        plain = torch.randn((K, N), device="cuda", generator=torch.Generator(device="cuda").manual_seed(args.seed))
+        C = torch.empty((M, N), device="cuda")
+        tiny_a = csr.vals.copy()
+        tiny_a[len(tiny_a) // 2] = 1e-37
+        plan, plan_a = (spmm.plan_create(M, K, csr.row_ptr, csr.col_idx, v, tiles=32) for v in (csr.vals, tiny_a))
+
+        def tails(share):
+            B = plain.clone()
+            B[torch.rand(B.shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)) < share] *= 1e-36
+            return B
+
+        one, column, infinite = plain.clone(), plain.clone(), plain.clone()
+        one[K // 3, 3] = 1e-35
+        column[:, 5] *= 1e-36
+        infinite[K // 3, 3] = float("inf")
+        cases = {"ordinary": (plan, plain), "one tiny value of B": (plan, one), "1 % of B tiny": (plan, tails(.01)), "10 % of B tiny": (plan, tails(.1)),
+                 "softmax of 20 B": (plan, torch.softmax(20 * plain, 0)), "one column of B tiny": (plan, column), "one infinite value of B": (plan, infinite),
+                 "one tiny value of A": (plan_a, plain)}
+        us = {k: [] for k in cases}
+        for turn in range(5):
+            for k in (list(cases) if turn % 2 == 0 else list(cases)[::-1]):
+                us[k].append(_time_plan(torch, cases[k][0], cases[k][1], C, N, reps=5))
+        times.append({"M": M, "K": K, "kept": kept, "N": N, "us": {k: round(sorted(v)[2], 2) for k, v in us.items()}})
+        print(json.dumps(times[-1]), file=sys.stderr, flush=True)
+    print(json.dumps({"metric": "error of bf16 parts / error of fp32 matrix instructions (2-norm against 64 bits, geomean)",
+                      "value": round(_geomean([p["parts_over_fp32_matrix"] for p in errors]), 3), "unit": "ratio", "n_gpus": 1,
+                      "higher_is_better": False, "dtype": "f32", "data": "synthetic",
+                      "config": {"workload": "%d products on panels of 32 rows" % len(errors), "seed": args.seed}, "errors": errors, "times": times}))
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -1014,11 +1088,11 @@ def main():
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--workload", default="headline",
                     help="headline (default: sweep + stress) | conv | stress | ffn | ffn-all | matrix | sweep | "
-                         "narrow | sparsity | ablation | tune | unhinted | paths (--steps matrices)")
+                         "narrow | sparsity | ablation | tune | unhinted | paths (--steps matrices) | parts")
     ap.add_argument("--shape", default="4096x4096", help="--workload matrix: rows x columns of A")
     ap.add_argument("--sparsity", type=float, default=0.5, help="--workload matrix: pruned share")
     ap.add_argument("--bcols", type=int, default=128, help="--workload matrix: columns of B")
-    ap.add_argument("--seed", type=int, default=11, help="--workload matrix, paths: generator seed")
+    ap.add_argument("--seed", type=int, default=11, help="--workload matrix, paths, parts: generator seed")
     ap.add_argument("--ufi", type=int, default=0, help="single workloads: force the rows per panel (1, 2, 4, 8)")
     ap.add_argument("--kslices", type=int, default=0,
                     help="single workloads: cut the plan into so many column ranges (1 = never, 0 = the rule)")
@@ -1049,9 +1123,9 @@ def main():
         return run_sweep(args, cols=(64, 4), square512=True)
     if args.workload == "ffn-all":
         return run_sweep(args, ffn=True)
-    if args.workload in ("sweep", "ablation", "tune", "unhinted", "paths"):
+    if args.workload in ("sweep", "ablation", "tune", "unhinted", "paths", "parts"):
         return {"sweep": run_sweep, "ablation": run_ablation, "tune": run_tune, "unhinted": run_unhinted,
-                "paths": run_paths}[args.workload](args)
+                "paths": run_paths, "parts": run_parts}[args.workload](args)
     return run_single(args)
 
 
