@@ -139,7 +139,9 @@ typedef struct {
     int32_t tiles;         /* the matrix-core path: A in tiles of panels of 8, 16 or 32 rows, absent
                               entries multiplied as zeros by matrix instructions (fp32, or bf16 on the
                               three exact parts of every value: six products of parts for one, what is
-                              left out is below 2^-24 of it), which pays on
+                              left out is below 2^-24 of it; a product is made a second time, in
+                              fp32 and in up to 2.2 times the time, where values of B below 2^-110
+                              could change a result or a sum is not finite), which pays on
                               matrices that are not very sparse.  8, 16 or 32 = use it with panels of so
                               many rows; < 0 = never; 0 = choose by shape, density and n_hint (8 rows
                               for hints of at most 64 columns only; never when

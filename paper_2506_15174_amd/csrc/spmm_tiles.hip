@@ -400,13 +400,13 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
 // out are below 2^-24 of the product, 2^-28 on average.  The sums of h h and of the five small ones are kept apart and added at the end: the large
 // sums are then rounded once per 16 columns of A, where the fp32 instructions round once per two.  Error of the result (2-norm,
 // against 64 bits) and that of fp32 instructions in tiles of 16 rows: 8192 x 8192, 50 % pruned, 128 columns 1.5e-7 and 4.1e-7; 4096 x 600 with 64, 8, 2 and
-// 1 entries in every row 6.3e-8 and 7.6e-8, 5.32e-8 both, 3.65e-8 and 3.62e-8, 2.59e-8 and 2.53e-8.
+// 1 entries in every row 6.3e-8 and 7.6e-8, 5.32e-8 and 5.33e-8, 3.63e-8 and 3.62e-8, 2.59e-8 and 2.52e-8.
 //
 // Where sums are not finite the workgroup multiplies again, with fp32 instructions, and gives what the kernel above gives.  Plans with values of A that have no exact parts run on that kernel (TilePlan::exact_parts).  Where values of B have
 // none, an element of C is off by at most 2^-133 x the largest value of A x K.  To an element 2^32 times as large that is
 // nothing; where one is smaller, of a row with entries and a column near such a value, the workgroup multiplies again too.
-// (8192 x 8192, 50 % pruned, 128 columns, 114 us: 113 with a tenth of B below 2^-110, 240 with a column of such values only or with
-// an infinite one, 134 with such a value in A; 4096 x 1024, 70 % pruned, in tiles of 64, 11.2 us: 11.4, 22 and 12.1.)
+// (8192 x 8192, 50 % pruned, 128 columns, 111 us: 111 with a tenth of B below 2^-110, 240 with a column of such values only or with
+// an infinite one, 134 with such a value in A; 4096 x 1024, 70 % pruned, in tiles of 64, 11.0 us: 11.2, 22 and 12.2.)
 //
 // RUNS    runs of 256 entries that hold any block of the plan
 // NB      column groups of the tile, 4 or 2
@@ -416,14 +416,13 @@ template <int N> __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsr
 // and a column group of them is split right before its six instructions.
 //
 // 128 columns: 8 waves, two per SIMD, with 128 registers of sums.  64 columns: 12 waves with 64 (16 waves, four per
-// SIMD, spill; 8 are 3 % slower), and LDS for one step ahead.  4096 x 1024, 70 % pruned, 128 columns in tiles of 64:
-// 10.7 us, with fp32 instructions and 16 waves 12.6; 8192 x 8192, 90 % pruned, 64 columns: 67 and 78; 8192 x 2048, 50 %
-// pruned, 64 columns: 25 and 27.  At the first size 32 steps are three per wave at most.  Up to FEW_STEPS steps the fp32 kernel's
+// SIMD, spill; 8 are 3 % slower), and LDS for one step ahead.  Back to back, C handed in, and with fp32 instructions: tiles of 128, 8192 x 8192, 50 % pruned,
+// 111 and 133 us, 16384 x 2048, 70 % pruned, 59 and 73; tiles of 64, 4096 x 1024, 70 % pruned, 128 columns, 11.0 and 12.2, 8192 x 8192, 90 % pruned,
+// 64 columns, 56 and 68, 8192 x 2048, 50 % pruned, 64 columns, 20 and 23.  At 4096 x 1024 32 steps are three per wave at most.  Up to FEW_STEPS steps the fp32 kernel's
 // 16 waves make one each, and stay (4096 x 300: 7.6 and 8.0 us; 8192 x 512: 8.9 both).
 //
-// What bounds it: 8192 x 8192, 50 % pruned, 128 columns take 123 us, with fp32 instructions 142; 16384 x 2048, 70 % pruned, 67
-// and 82.  The matrix cores are busy 39 % of the time; 11 vector instructions beside each of theirs (192 per 16 rows for B, which
-// every panel splits anew, 48 for A) overlap with it only in part, and the power limit holds the clock to 2 GHz.  Splitting B once, in a launch
+// What bounds it: on 8192 x 8192 the matrix cores are busy a good third of the time; 11 vector instructions beside each of theirs (192 per 16 rows for B, which
+// every panel splits anew, 44 for A) overlap with it only in part, and the power limit holds the clock to 2 GHz.  Splitting B once, in a launch
 // of its own, leaves 2.6 vector instructions but moves 6 bytes per value, 19 TB/s through the L2s: 15 % faster, for a workspace that
 // spmm_execute does not have.  One wave per SIMD with everything interleaved is slower: a single wave issues an instruction every
 // 5 cycles only.  With two, the splitting of the next group placed between the matrix instructions (also over halves and steps)

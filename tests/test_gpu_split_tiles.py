@@ -151,6 +151,28 @@ def test_a_few_tiny_values_among_ordinary_ones(torch_gpu, oracle):  # noqa: F811
     assert (np.abs(C - C_ref) <= 2.0 ** -21 * S + 3 * 2.0 ** -149).all()
 
 
+@pytest.mark.parametrize("M,groups", [(64, 4), (32, 2)])
+@pytest.mark.parametrize("exponents,power", [((-112, -108), 2.0 ** 40), ((126, 127), 2.0 ** -20)])
+@pytest.mark.parametrize("of_a", [False, True])
+def test_ends_of_the_range_of_parts(torch_gpu, M, groups, exponents, power, of_a):  # noqa: F811
+    """Values around 2^-110, below which the last part is no bf16, and around 2^128 - 2^119, from which the first is infinite, times a
+    power of two: every value is the sum of its parts or multiplied in fp32, so each product is exact."""
+    K, N = 600, WIDE
+    rng = np.random.default_rng(M)
+
+    def ends(shape):
+        mantissa = np.where(rng.random(shape) < 0.5, rng.integers(0, 1 << 23, shape), (1 << 23) - rng.choice([1, 2, 3, 1 << 14, (1 << 14) + 1, (1 << 15) + 1], shape))
+        return (np.ldexp(1 + mantissa * 2.0 ** -23, rng.integers(exponents[0], exponents[1] + 1, shape)) * rng.choice([-1, 1], shape)).astype(np.float32)
+
+    W = np.zeros((M, K), np.float32)
+    columns = rng.choice(K, M, replace=False)
+    W[np.arange(M), columns] = ends(M) if of_a else power
+    B = np.full((K, N), power, np.float32) if of_a else ends((K, N))
+    C = product(torch_gpu, gen.csr_from_dense(W), B, groups)
+    assert np.isfinite(C).all()
+    assert np.array_equal(C, W[np.arange(M), columns][:, None] * B[columns])
+
+
 def with_tails(rng, K, N, share):
     """Normal values, some so small that they are no sum of three bf16 numbers, subnormal ones among them."""
     B = rng.standard_normal((K, N)).astype(np.float32)
