@@ -1082,23 +1082,42 @@ template <int R, typename Col> __global__ __launch_bounds__(1024) void panel_ker
 }
 
 // The sizes of the values: range[0] = the largest, as bits; range[1] = 2^32 less the smallest that is not zero
-// (maxima on cleared memory).  Sizes order as their bits do, infinite and NaN ones last.
-__global__ __launch_bounds__(256) void range_kernel(const float *vals, int64_t nnz, uint32_t *range)
+// (maxima on cleared memory).  Sizes order as their bits do, infinite and NaN ones last.  Few workgroups and one pair of atomics
+// from each: two thousand pairs on one address held up a creation of 0.76 ms by 0.06.
+__global__ __launch_bounds__(1024) void range_kernel(const float *vals, int64_t nnz, uint32_t *range)
 {
+    __shared__ uint32_t of_wave[2][16];
     uint32_t largest = 0, smallest = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * 256) {
-        const uint32_t size = __float_as_uint(vals[i]) & 0x7FFFFFFFu;
+    auto take = [&](float v) {
+        const uint32_t size = __float_as_uint(v) & 0x7FFFFFFFu;
         largest = size > largest ? size : largest;
         smallest = 0u - size > smallest ? 0u - size : smallest;
+    };
+    const int64_t quads = nnz / 4, first = (int64_t)blockIdx.x * 1024 + threadIdx.x, all = (int64_t)gridDim.x * 1024;
+    for (int64_t i = first; i < quads; i += all) {
+        const f32x4 v = reinterpret_cast<const f32x4 *>(vals)[i];
+        for (int x = 0; x < 4; ++x) take(v[x]);
     }
-    for (int d = 32; d > 0; d /= 2) {
-        const uint32_t l = __shfl_xor(largest, d), s = __shfl_xor(smallest, d);
-        largest = l > largest ? l : largest;
-        smallest = s > smallest ? s : smallest;
-    }
+    for (int64_t i = 4 * quads + first; i < nnz; i += all) take(vals[i]);
+    auto over_lanes = [&](int lanes) {
+        for (int d = lanes / 2; d > 0; d /= 2) {
+            const uint32_t l = __shfl_xor(largest, d), s = __shfl_xor(smallest, d);
+            largest = l > largest ? l : largest;
+            smallest = s > smallest ? s : smallest;
+        }
+    };
+    over_lanes(64);
     if (threadIdx.x % 64 == 0) {
-        if (largest > range[0]) atomicMax(&range[0], largest);
-        if (smallest > range[1]) atomicMax(&range[1], smallest);
+        of_wave[0][threadIdx.x / 64] = largest;
+        of_wave[1][threadIdx.x / 64] = smallest;
+    }
+    __syncthreads();
+    largest = of_wave[0][threadIdx.x % 16];
+    smallest = of_wave[1][threadIdx.x % 16];
+    over_lanes(16);
+    if (threadIdx.x == 0) {
+        atomicMax(&range[0], largest);
+        atomicMax(&range[1], smallest);
     }
 }
 
@@ -1198,9 +1217,9 @@ struct workshop {
 // to 35.  Its first pages cost 0.1 ms per MiB once, and giving it back may wait for
 // all streams, which a creation must not.  So there is one piece of it for the process, lent to one creation at
 // a time (another one that runs meanwhile uploads from ordinary memory), and it goes back when the last plan on tiles
-// is released.  4096 x 4096, 80 % pruned (20 MB), plan and product: 0.89 ms where each plan is released before the next, 0.79 where one
-// lives, from ordinary memory 1.26; the first of a process (after a small plan) 1.9, from ordinary memory 2.25.  12 MiB in pieces of
-// 4: 0.84, 0.78 and 2.4; 4 MiB in pieces of 1: 0.96, 0.85 and 1.7.
+// is released.  4096 x 4096, 80 % pruned (20 MB), plan and product: 0.90 ms where each plan is released before the next (0.84 if the memory stayed), 0.80 where one
+// lives, from ordinary memory 1.26; the first of a process (after a small plan) 1.95, from ordinary memory 2.2.  12 MiB in pieces of
+// 4: 0.88, 0.77 and 2.35 (8192 x 4096, 30 % kept: 1.9 instead of 2.0); 4 MiB in pieces of 1: 0.96, 0.85 and 1.7.
 struct staging_memory {
     static constexpr size_t PIECE = 2u << 20, PIECES = 3;
     std::mutex lock;
@@ -1466,7 +1485,7 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
         TRY(hipMemcpyWithStream(d_val, vals, (size_t)nnz * 4, hipMemcpyHostToDevice, s));  // the kernels run meanwhile
     }
     if (R == 32) {
-        hipLaunchKernelGGL(range_kernel, dim3((unsigned)std::min<int64_t>(512, nnz / 1024 + 1)), dim3(256), 0, s, d_val, nnz, flags + 2);
+        hipLaunchKernelGGL(range_kernel, dim3((unsigned)std::min<int64_t>(128, nnz / 4096 + 1)), dim3(1024), 0, s, d_val, nnz, flags + 2);
         TRY(hipGetLastError());
     }
     uint64_t answer[3];
