@@ -21,7 +21,7 @@ MICROBENCH = os.path.join(HERE, "microbench_paths")
 
 
 def build_microbench():
-    """Compile the memory-path microbenchmark (a gfx950 executable; run it on the GPU machine)."""
+    """Compile the memory-path microbenchmark (a gfx950 executable; run it where there is a GPU)."""
     cmd = [os.path.join(ROCM, "bin", "hipcc"), "--offload-arch=gfx950", "-O3",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
            os.path.join(HERE, "microbench_paths.hip"), "-o", MICROBENCH]

@@ -1,7 +1,7 @@
 /* A plain C99 caller of the boundary (include/spmm.h) that runs the product on the
  * device: spmm_plan_create -> spmm_execute -> spmm_plan_destroy, with device memory
  * from the HIP runtime's C interface (declared by hand: no HIP header, no C++).
- * Built and run by tests/test_gpu_parity.py on the GPU machine.
+ * Built and run by tests/test_gpu_parity.py where there is a GPU.
  *
  * A = [ 1 0 0 2 ]     B[k][j] = 10 k + j (4 x 8)
  *     [ 0 0 0 0 ]

@@ -1,4 +1,4 @@
-"""Matrix-core path on panels of 8 rows (narrow B) against the CPU oracle, through the C ABI (GPU machine only)."""
+"""Matrix-core path on panels of 8 rows (narrow B) against the CPU oracle, through the C ABI (needs the GPU)."""
 import numpy as np
 import pytest
 

@@ -1,5 +1,5 @@
 """Parity of the HIP path with the CPU oracle, element by element, through the
-C ABI (GPU machine only: run with -m gpu).
+C ABI (needs the GPU: run with -m gpu).
 
 Bar (written out here): |C_gpu - C_ref| <= 1e-5 * S per element, where C_ref is
 the oracle's double-precision value and S = sum |A_ik| |B_kj| over the same

@@ -1,5 +1,5 @@
 """Panels of 32 rows x 128 and 64 columns on bf16 matrix instructions (values in three parts) against the CPU oracle,
-through the C ABI (GPU machine only)."""
+through the C ABI (needs the GPU)."""
 import ctypes
 
 import numpy as np

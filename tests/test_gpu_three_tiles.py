@@ -1,5 +1,5 @@
 """161 to 192 columns of B on the chunk kernels, three tiles of 64 columns in one launch, against the CPU oracle
-(GPU machine only)."""
+(needs the GPU)."""
 import numpy as np
 import pytest
 

@@ -1,4 +1,4 @@
-"""Building tiles with the bitmaps of a panel in LDS and, for more than 1024 steps, in global memory (GPU machine only)."""
+"""Building tiles with the bitmaps of a panel in LDS and, for more than 1024 steps, in global memory (needs the GPU)."""
 import numpy as np
 import pytest
 

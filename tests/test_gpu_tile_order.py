@@ -1,5 +1,5 @@
 """Order in which the workgroups of several column tiles start: every block of every tile exactly once, against the
-CPU oracle (GPU machine only)."""
+CPU oracle (needs the GPU)."""
 import numpy as np
 import pytest
 

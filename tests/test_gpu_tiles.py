@@ -1,4 +1,4 @@
-"""Matrix-core path (spmm_options_t.tiles) against the CPU oracle, through the C ABI (GPU machine only)."""
+"""Matrix-core path (spmm_options_t.tiles) against the CPU oracle, through the C ABI (needs the GPU)."""
 import numpy as np
 import pytest
 

@@ -1,4 +1,4 @@
-"""Plans on tiles whose arrays go to the device through pinned memory (GPU machine only)."""
+"""Plans on tiles whose arrays go to the device through pinned memory (needs the GPU)."""
 import gc
 import threading
 

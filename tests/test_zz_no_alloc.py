@@ -1,5 +1,5 @@
 """The allocation-free entry point spmm_execute_static against spmm_execute, through the
-C ABI (GPU machine only).
+C ABI (needs the GPU).
 
 Plans whose heavy panels are cut across workgroups park partial sums in scratch memory:
 spmm_execute uses memory the plan allocated, spmm_execute_static a device array that is
