@@ -256,10 +256,12 @@ def tile_kernel(tile_rows, groups=0):
 
 
 def schedule_of(info, keys):
-    """The named facts of a plan; on tiles those of the chunk schedule, which its product does not use, are None."""
-    on_tiles = info["tile_rows"] > 0
-    out = {k: None if on_tiles and k in CHUNK_FACTS else info[k] for k in keys}
+    """The named facts of a plan; on tiles and strips those of the chunk schedule, which its product does not use, are None."""
+    on_chunks = info["tile_rows"] == 0 and info.get("strip_units", 0) == 0
+    out = {k: None if not on_chunks and k in CHUNK_FACTS else info[k] for k in keys}
     out["tile_rows"] = info["tile_rows"]
+    if info.get("strip_units", 0):
+        out["strip_units"] = info["strip_units"]
     return out
 
 
@@ -725,8 +727,10 @@ def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, pla
     achieved = bmin / (avg_ms * 1e-3) / 1e9
     kernel_tflops = 2.0 * nnz * N / (avg_ms * 1e-3) / 1e12
     traffic, prov = measured_traffic(workload_key, N)
-    on_tiles = info["tile_rows"] > 0
-    if on_tiles:
+    on_tiles, on_strips = info["tile_rows"] > 0, info["strip_units"] > 0
+    if on_strips:
+        kernel, launches = "spmm_strips_kernel", 1
+    elif on_tiles:
         groups = split_groups(info["tile_rows"], csr.M, csr.K, N)
         kernel, launches = tile_kernel(info["tile_rows"], groups), 1
     else:
@@ -748,6 +752,10 @@ def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, pla
         peak = BF16_MFMA_PEAK_TFLOPS / SPLIT_PRODUCTS if groups else FP32_MFMA_PEAK_TFLOPS
         roofline["matrix_cores"] = {"blocks": info["n_chunks"], "tflops_with_zeros": round(with_zeros, 3),
                                     "peak": round(peak, 1), "frac": round(with_zeros / peak, 4)}
+        return roofline
+    if on_strips:
+        roofline["gather"] = None
+        roofline["strips"] = {"units": info["strip_units"], "steps": info["n_enum"] // 64, "lanes_filled": round(nnz / info["n_enum"], 4)}
         return roofline
     # On-chip gather: each chunk of ufk enumerated columns costs ufk / S wave-wide loads of B
     # rows (S rows of B per load); the ceiling is the rate the gather microbenchmark

@@ -80,6 +80,10 @@ typedef struct {
                               and any number of its executes may be in flight; the remaining fields (also
                               n_cross and k_slices) and the row groups are those of the chunk schedule of the
                               same matrix, which its product does not use. */
+    int64_t strip_units;   /* 0, or the units of 64 lanes of a plan whose product runs on strips of eight columns
+                              (spmm_options_t.strips): n_enum = lanes * steps and n_chunks = units * bands of columns of
+                              A, stream_words and device_bytes are those of the strips, scratch_bytes is 0 and any
+                              number of executes may be in flight; the remaining fields as with tile_rows. */
 } spmm_plan_info_t;
 
 /* Optional inspector settings; zero in a field means "let the inspector choose". */
@@ -149,6 +153,13 @@ typedef struct {
                               plans).  A matrix with a column stored twice in a row, with 2^26 rows or
                               more, or whose tiles find no room on the device while they are built
                               stays on chunks. */
+    int32_t strips;        /* the path that keeps eight columns of B at a time in a compute unit's LDS and gathers
+                              from there, one lane per part of a row (fp32 multiply-adds as on chunks).
+                              > 0 = use it (not together with other settings but n_hint and threads:
+                              SPMM_ERR_INVALID_ARG; tiles > 0 goes first); < 0 = never; 0 = choose by shape, row lengths and
+                              n_hint (never when another setting but n_hint and threads is given, tiles < 0 among them).
+                              A matrix with 2^28 rows or more or with a column stored millions of times
+                              in a row stays on chunks. */
 } spmm_options_t;
 
 /*
@@ -209,7 +220,7 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K,
  *           (an infinity or NaN in row k makes elements of its column of C NaN also in
  *           rows of A without an entry in column k: in rows whose entries share a chunk or
  *           its padding with that column, and on tiles, which multiply absent entries as
- *           zeros, in every row of C)
+ *           zeros, in every row of C; on strips in no others)
  *   N       columns of B and C, >= 1 (32, 64 and 128 have tuned kernels; every
  *           other N runs through masked column tiles of at most 128 columns; tiles
  *           of one width share a kernel launch, a narrower rest takes a launch of
@@ -229,7 +240,7 @@ spmm_status_t spmm_plan_create_ex(spmm_plan_t **plan, int64_t M, int64_t K,
  * plan has scratch memory (info.scratch_bytes > 0), where the sums of panels cut across
  * workgroups meet, or those of the ranges of a plan cut along K, which a last launch adds, 128
  * columns at a time: at most one execute of such a plan may be in flight at a time.
- * (A plan on tiles has none, whatever the n_cross and k_slices of its chunk schedule.)
+ * (A plan on tiles or strips has none, whatever the n_cross and k_slices of its chunk schedule.)
  * Results are bit-identical from run to run.  B and C must be 4-byte aligned.
  * Every N runs on the kernels that handle four columns per lane (the last lane of
  * a row stores only the columns that exist; rows that are not 16-byte aligned cost
@@ -252,7 +263,7 @@ spmm_status_t spmm_execute(const spmm_plan_t *plan, const float *B, int32_t N,
  * One column tile of a launch needs 512 * ufi bytes per workgroup of a cut panel; the
  * call packs as many column tiles into a launch as the array holds and returns
  * SPMM_ERR_UNSUPPORTED, enqueuing nothing, when a single tile does not fit, and for
- * every plan on chunks cut along K (info.k_slices > 1 with info.tile_rows == 0: its sums
+ * every plan on chunks cut along K (info.k_slices > 1 with info.tile_rows and info.strip_units 0: its sums
  * need more than the array holds).
  * All plans and all callers on one device share the array, which keeps the last call's
  * content (every launch overwrites what it reads, nothing needs clearing): calls that

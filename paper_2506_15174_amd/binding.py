@@ -42,7 +42,12 @@ class PlanInfo(ctypes.Structure):
                 ("tile_rows", ctypes.c_int64)]
 
     def as_dict(self):
-        return {name: int(getattr(self, name)) for name, _ in self._fields_}
+        return {name: int(getattr(self, name)) for cls in reversed(type(self).__mro__) for name, _ in vars(cls).get("_fields_", ())}
+
+
+class StripPlanInfo(PlanInfo):
+    """PlanInfo and the field behind it."""
+    _fields_ = [("strip_units", ctypes.c_int64)]
 
 
 class Options(ctypes.Structure):
@@ -52,6 +57,11 @@ class Options(ctypes.Structure):
                 ("force_wide", ctypes.c_int32), ("threads", ctypes.c_int32), ("depth", ctypes.c_int32),
                 ("cross", ctypes.c_int32), ("ufk", ctypes.c_int32), ("probe", ctypes.c_int32),
                 ("kslices", ctypes.c_int32), ("tiles", ctypes.c_int32)]
+
+
+class StripOptions(Options):
+    """Options and the field behind them."""
+    _fields_ = [("strips", ctypes.c_int32)]
 
 
 class SpmmError(RuntimeError):
@@ -134,7 +144,7 @@ class Plan:
 
     def describe(self):
         if self._info is None:  # a plan is immutable: ask once
-            info = PlanInfo()
+            info = StripPlanInfo()
             _check(load().spmm_plan_describe_sized(self._h, ctypes.byref(info), ctypes.sizeof(info)), "spmm_plan_describe")
             self._info = info.as_dict()
         return dict(self._info)
@@ -193,7 +203,7 @@ class Plan:
 
 def plan_create(M, K, row_ptr, col_idx, vals, group_nnz=0, group_panels=0, host_only=False, ufi=0,
                 n_hint=0, sort_rows=0, force_wide=False, threads=0, depth=0, cross=0, ufk=0, probe=False,
-                kslices=0, tiles=0):
+                kslices=0, tiles=0, strips=0):
     """spmm_plan_create / spmm_plan_create_sized on numpy host arrays."""
     row_ptr = np.ascontiguousarray(row_ptr, dtype=np.int32)
     col_idx = np.ascontiguousarray(col_idx, dtype=np.int32)
@@ -201,10 +211,10 @@ def plan_create(M, K, row_ptr, col_idx, vals, group_nnz=0, group_panels=0, host_
     handle = ctypes.c_void_p()
     lib = load()
     if group_nnz or group_panels or host_only or ufi or n_hint or sort_rows or force_wide or threads or depth \
-            or cross or ufk or probe or kslices or tiles:
-        opts = Options(int(group_nnz), int(group_panels), 1 if host_only else 0, int(ufi), int(n_hint),
-                       int(sort_rows), 1 if force_wide else 0, int(threads), int(depth), int(cross), int(ufk), 1 if probe else 0,
-                       int(kslices), int(tiles))
+            or cross or ufk or probe or kslices or tiles or strips:
+        opts = StripOptions(int(group_nnz), int(group_panels), 1 if host_only else 0, int(ufi), int(n_hint),
+                            int(sort_rows), 1 if force_wide else 0, int(threads), int(depth), int(cross), int(ufk), 1 if probe else 0,
+                            int(kslices), int(tiles), int(strips))
         st = lib.spmm_plan_create_sized(ctypes.byref(handle), int(M), int(K), _ptr(row_ptr),
                                         _ptr(col_idx), _ptr(vals), ctypes.byref(opts), ctypes.sizeof(opts))
     else:

@@ -16,8 +16,8 @@ LIB_PATH = os.path.join(LIB_DIR, "libspmm_cdna4.so")
 TORCH_EXT_SOURCE = "spmm_torch.cpp"
 TORCH_EXT_PATH = os.path.join(LIB_DIR, "_spmm_torch.so")
 
-SOURCES = ["spmm_kernels.hip", "spmm_tiles.hip", "spmm_plan.cpp", "spmm_api.cpp"]
-HEADERS = ["spmm_format.h", "spmm_kernels.h", "spmm_plan.h", "spmm_tiles.h"]
+SOURCES = ["spmm_kernels.hip", "spmm_tiles.hip", "spmm_strips.hip", "spmm_plan.cpp", "spmm_api.cpp"]
+HEADERS = ["spmm_format.h", "spmm_kernels.h", "spmm_plan.h", "spmm_tiles.h", "spmm_strips.h", "spmm_strips_build.h"]
 
 
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")

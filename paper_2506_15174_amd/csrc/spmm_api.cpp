@@ -14,6 +14,7 @@
 #include "spmm_format.h"
 #include "spmm_kernels.h"
 #include "spmm_plan.h"
+#include "spmm_strips_build.h"
 #include "spmm_tiles.h"
 
 using namespace spmm_fmt;
@@ -31,7 +32,10 @@ struct spmm_plan {
     // Plans cut along K: the slices' sums of one batch of up to KSLICE_COLS columns
     // (k_slices x slice_rows rows), written by every execute.
     float *d_slice_sums = nullptr;
-    TilePlan tiles;           // tiles.rows > 0: the entries are in tiles and the product runs on the matrix cores
+    // tiles.rows > 0: the entries are in tiles and the product runs on the matrix cores; tiles.strips.n_units > 0: they are in
+    // strips.  Otherwise they are in chunks.
+    TilePlan tiles;
+    bool on_chunks() const { return tiles.rows == 0 && tiles.strips.n_units == 0; }
     int64_t scratch_bytes = 0;
     int64_t device_bytes = 0;
     int64_t stream_words = 0;  // length of host.stream at creation (a device plan drops its host mirror)
@@ -131,8 +135,9 @@ struct plan_release {
     void operator()(spmm_plan *p) const
     {
         bool held = p->tiles.rows > 0;
+        const StripPlan &strips = p->tiles.strips;
         for (void *q : {(void *)p->d_stream, (void *)p->d_wins, (void *)p->d_items, (void *)p->d_rowmap, (void *)p->d_cross_sums,
-                        (void *)p->d_cross_table, (void *)p->d_slice_sums})
+                        (void *)p->d_cross_table, (void *)p->d_slice_sums, (void *)strips.d_stream, (void *)strips.d_units, (void *)strips.d_rows})
             if (q) {
                 held = true;
                 (void)hipFree(q);
@@ -185,14 +190,24 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
     plan.reset(new spmm_plan());
     spmm_plan *p = plan.get();
     int rc = 0;
+    strips::host strips;
+    bool use_strips = opts.strips > 0 && tiles <= 0;
+    if (use_strips && (schedule_forced || host_only)) return SPMM_ERR_INVALID_ARG;
     if (!host_only && tiles >= 0 && (tiles > 0 || !schedule_forced) && row_pointer_ok(M, K, row_ptr, col_idx, vals)) {
-        if (tiles == 0) tiles = choose_tiles(M, K, row_ptr, io.n_hint);
+        if (tiles == 0 && !use_strips) {
+            tiles = choose_tiles(M, K, row_ptr, io.n_hint);
+            use_strips = opts.strips == 0 && tiles == 0 && choose_strips(M, K, row_ptr, io.n_hint);
+        }
         if (tiles > 0) {
             rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
             // the chunk plan needs no memory beside its own, the builder of tiles a multiple of its result's
             if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) rc = 0;
             io.schedule_only = p->tiles.rows > 0;
         }
+    }
+    if (use_strips && row_pointer_ok(M, K, row_ptr, col_idx, vals) && row_ptr[M] > 0) {
+        rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, strips);
+        io.schedule_only = rc == 0 && strips.plan.n_units > 0;
     }
     if (rc == 0) rc = spmm_inspect(M, K, row_ptr, col_idx, vals, io, p->host);
     if (rc != 0) return (spmm_status_t)rc;
@@ -205,6 +220,11 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         spmm_status_t st = SPMM_OK;
         if (p->tiles.rows > 0) {
             p->device_bytes = p->tiles.device_bytes;
+        } else if (strips.plan.n_units > 0) {
+            StripPlan &to = p->tiles.strips = strips.plan;
+            st = upload(&to.d_stream, strips.stream.data(), strips.stream.size() * 4, p->device_bytes);
+            if (st == SPMM_OK) st = upload(&to.d_units, strips.units.data(), strips.units.size() * 4, p->device_bytes);
+            if (st == SPMM_OK) st = upload(&to.d_rows, strips.rows.data(), strips.rows.size() * 4, p->device_bytes);
         } else {
             // Scratch first: hipMemset may return before it is done, the copies behind it do not.
             if (h.n_cross_slots > 0) {
@@ -230,7 +250,11 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (st != SPMM_OK) return st;
         p->on_device = true;
     }
-    p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : (int64_t)p->host.stream.size();
+    p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : strips.plan.n_units > 0 ? (int64_t)strips.stream.size() : (int64_t)p->host.stream.size();
+    if (strips.plan.n_units > 0) {
+        p->host.n_enum = strips.plan.steps * 64;
+        p->host.n_chunks = strips.plan.n_units * strips.plan.bands;
+    }
     if (p->tiles.rows > 0) {
         p->host.n_enum = p->tiles.n_panels * K;
         p->host.n_chunks = p->tiles.n_panels * p->tiles.n_steps;
@@ -306,7 +330,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     if (hipGetDevice(&dev) != hipSuccess) return hip_fail();
     if (dev != plan->device) return SPMM_ERR_INVALID_ARG;
 
-    if (plan->tiles.rows > 0)
+    if (!plan->on_chunks())
         return spmm_tiles_execute(plan->tiles, h.M, h.K, B, N, C, stream) == 0 ? SPMM_OK : hip_fail();
 
     const uint64_t b_total = (uint64_t)h.K * (uint64_t)N * 4u;
@@ -423,8 +447,8 @@ spmm_status_t spmm_execute_static(const spmm_plan_t *plan, const float *B, int32
 {
     if (!plan) return SPMM_ERR_INVALID_ARG;
     const HostPlan &h = plan->host;
-    if (h.k_slices > 1 && plan->on_device && plan->tiles.rows == 0) return SPMM_ERR_UNSUPPORTED;  // the slices' buffer is beyond the static array
-    if (h.n_cross_slots == 0 || !plan->on_device || plan->tiles.rows > 0) return execute_with(plan, B, N, C, stream, nullptr, 0);
+    if (h.k_slices > 1 && plan->on_device && plan->on_chunks()) return SPMM_ERR_UNSUPPORTED;  // the slices' buffer is beyond the static array
+    if (h.n_cross_slots == 0 || !plan->on_device || !plan->on_chunks()) return execute_with(plan, B, N, C, stream, nullptr, 0);
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess) return hip_fail();
     if (dev != plan->device) return SPMM_ERR_INVALID_ARG;
@@ -472,6 +496,7 @@ spmm_status_t spmm_plan_describe_sized(const spmm_plan_t *plan, spmm_plan_info_t
     info.slice_rows = h.slice_rows;
     info.slice_cols = h.slice_cols;
     info.tile_rows = plan->tiles.rows;
+    info.strip_units = plan->tiles.strips.n_units;
     std::memset(out, 0, out_bytes);
     std::memcpy(out, &info, std::min(out_bytes, sizeof info));
     return SPMM_OK;

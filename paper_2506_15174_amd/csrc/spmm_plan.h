@@ -75,6 +75,15 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
 // bench.py, which sets it beside measured times; -1 where there is no memory for it.
 extern "C" double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N);
 
+// The entries of A in strips (spmm_strips_build.h), for products with n_hint columns.  Status codes as above; out.plan.n_units = 0:
+// A cannot be stored this way.
+namespace strips {
+struct host;
+}
+bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint);  // instead of chunks
+int spmm_strips_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t n_hint, int32_t threads,
+                      strips::host &out);
+
 // Rows per panel (32, 16 or 8) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.
 int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint);
 

@@ -1,0 +1,309 @@
+// Host builder of the strips path (format: spmm_strips.h).  Included by spmm_plan.cpp.
+#ifndef SPMM_STRIPS_BUILD_H
+#define SPMM_STRIPS_BUILD_H
+
+#include <algorithm>
+#include <cstdint>
+#include <cstring>
+#include <numeric>
+#include <vector>
+
+#include "spmm_plan.h"
+#include "spmm_strips.h"
+
+namespace strips {
+
+// Rows by length, longest first, stable.
+inline std::vector<uint32_t> by_length(int64_t M, const int32_t *row_ptr)
+{
+    int64_t longest = 0;
+    for (int64_t i = 0; i < M; ++i) longest = std::max<int64_t>(longest, row_ptr[i + 1] - row_ptr[i]);
+    std::vector<uint32_t> order((size_t)M);
+    if (longest < 8 * M + 4096) {  // counted
+        std::vector<uint32_t> place((size_t)longest + 2, 0);
+        for (int64_t i = 0; i < M; ++i) ++place[(size_t)(longest - (row_ptr[i + 1] - row_ptr[i])) + 1];
+        for (size_t k = 1; k < place.size(); ++k) place[k] += place[k - 1];
+        for (int64_t i = 0; i < M; ++i) order[place[(size_t)(longest - (row_ptr[i + 1] - row_ptr[i]))]++] = (uint32_t)i;
+    } else {
+        std::iota(order.begin(), order.end(), 0u);
+        std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return row_ptr[x + 1] - row_ptr[x] > row_ptr[y + 1] - row_ptr[y]; });
+    }
+    return order;
+}
+
+struct unit {
+    int64_t first;  // place of its first row in the order
+    int32_t parts_log2, steps;
+};
+constexpr int64_t steps_of(int64_t entries) { return (entries + STRIP_STEPS - 1) / STRIP_STEPS * STRIP_STEPS; }
+
+// The rows in units whose lanes have at most `most` entries, where a row in 64 parts allows that.
+inline std::vector<unit> units_of(int64_t M, const int32_t *row_ptr, const std::vector<uint32_t> &order, int64_t most)
+{
+    std::vector<unit> units;
+    for (int64_t at = 0; at < M;) {
+        const int64_t len = row_ptr[order[(size_t)at] + 1] - row_ptr[order[(size_t)at]];
+        int p = 0;
+        while (p < 6 && ((len + (1 << p) - 1) >> p) > most) ++p;
+        units.push_back(unit{at, p, (int32_t)steps_of((len + (1 << p) - 1) >> p)});
+        at += 64 >> p;
+    }
+    return units;
+}
+
+// Groups of units a launch for N columns wants: all compute units (256) with a workgroup each.
+inline int64_t wanted_groups(int64_t N) { return std::max<int64_t>(1, 256 / ((N + STRIP_COLS - 1) / STRIP_COLS)); }
+
+// The units for products with N columns: a quarter more than an equal share of the entries for every wave, so that most rows
+// keep to one number of parts; a strip in bands allows one unit per wave only, which more entries per lane bring about.
+inline std::vector<unit> units_for(int64_t M, const int32_t *row_ptr, const std::vector<uint32_t> &order, int64_t N, int32_t bands)
+{
+    const int64_t waves = STRIP_WAVES * wanted_groups(N);
+    int64_t most = std::max<int64_t>(8, steps_of((int64_t)row_ptr[M] * 5 / (4 * 64 * waves) + 1));
+    std::vector<unit> units = units_of(M, row_ptr, order, most);
+    for (int tries = 0; bands > 1 && (int64_t)units.size() > waves && tries < 8; ++tries) {
+        most += steps_of(most / 16 + 1);
+        units = units_of(M, row_ptr, order, most);
+    }
+    std::stable_sort(units.begin(), units.end(), [](const unit &x, const unit &y) { return x.steps > y.steps; });
+    return units;
+}
+
+inline void band_sizes(int64_t K, StripSizes &p)
+{
+    p.bands = (int32_t)((K + STRIP_MOST_ROWS - 1) / STRIP_MOST_ROWS);
+    p.band_rows = (int32_t)(((K + p.bands - 1) / p.bands + STRIP_BAND_ALIGN - 1) / STRIP_BAND_ALIGN * STRIP_BAND_ALIGN);
+}
+
+// Columns of B that a plan without a hint is made for.
+constexpr int64_t UNKNOWN_COLUMNS = 64;
+
+// The sizes a plan made for n_hint columns would have, but for what bands leave idle.
+inline StripSizes sizes(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
+{
+    StripSizes p;
+    band_sizes(K, p);
+    const std::vector<unit> units = units_for(M, row_ptr, by_length(M, row_ptr), n_hint > 0 ? n_hint : UNKNOWN_COLUMNS, p.bands);
+    p.n_units = (int64_t)units.size();
+    for (const unit &u : units) p.steps += u.steps;
+    p.longest = units.front().steps;
+    return p;
+}
+
+struct host {
+    StripPlan plan;  // without device memory
+    raw_words stream;
+    std::vector<uint32_t> units, rows;
+};
+
+// One thread's working memory.
+struct scratch {
+    std::vector<int32_t> order;
+    std::vector<uint16_t> columns;  // of the unit's entries in the band, lane by lane, by column modulo 8
+    std::vector<float> values;
+};
+
+// Orders and writes the entries of a unit in a band.  row_range(r, first, end): the r-th row's entries there, as places in `sorted`.
+template <typename Row> void fill(const unit &u, int64_t n_rows, Row row_range, const int32_t *col_idx, const float *vals, const int32_t *sorted, int32_t band_first,
+                                  uint32_t zero_row, int64_t groups, char *out, scratch &s)
+{
+    const int P = 1 << u.parts_log2;
+    int32_t start[65], count[64][8], left[64];
+    std::memset(count, 0, sizeof count);
+    std::memset(left, 0, sizeof left);
+    int64_t of_row[64][2];
+    int32_t total = 0;
+    for (int64_t r = 0; r < 64 / P; ++r) {
+        of_row[r][0] = of_row[r][1] = 0;
+        if (r < n_rows) row_range(r, of_row[r][0], of_row[r][1]);
+        const int64_t n = of_row[r][1] - of_row[r][0];
+        for (int x = 0; x < P; ++x) {
+            start[r * P + x] = total;
+            left[r * P + x] = (int32_t)((n + P - 1 - x) / P);
+            total += left[r * P + x];
+        }
+    }
+    s.columns.resize((size_t)total);
+    s.values.resize((size_t)total);
+    for (int64_t r = 0; r < 64 / P; ++r) {
+        // the row's entries class by class (column modulo 8), dealt to its lanes in turn
+        int32_t at[9] = {};
+        for (int64_t q = of_row[r][0]; q < of_row[r][1]; ++q) ++at[((col_idx[sorted[q]] - band_first) & 7) + 1];
+        for (int c = 1; c < 9; ++c) at[c] += at[c - 1];
+        for (int64_t q = of_row[r][0]; q < of_row[r][1]; ++q) {
+            const int32_t e = sorted[q], col = col_idx[e] - band_first, k = at[col & 7]++;
+            const int lane = (int)(r * P + (k & (P - 1)));
+            const size_t to = (size_t)(start[lane] + (k >> u.parts_log2));
+            s.columns[to] = (uint16_t)col;
+            s.values[to] = vals[e];
+            ++count[lane][col & 7];
+        }
+    }
+    const int32_t steps = (int32_t)(groups * STRIP_STEPS);
+    for (int cycle = 0; cycle < 4; ++cycle)
+        for (int odd = 0; odd < 2; ++odd) {
+            int lanes[8];
+            int32_t next[8][8];
+            uint32_t has[8];  // classes
+            for (int i = 0; i < 8; ++i) {
+                const int l = lanes[i] = strip_lane(cycle, i, odd);
+                int32_t to = start[l];
+                has[i] = 0;
+                for (int c = 0; c < 8; ++c) {
+                    next[i][c] = to;
+                    to += count[l][c];
+                    has[i] |= (uint32_t)(count[l][c] > 0) << c;
+                }
+            }
+            for (int32_t t = 0; t < steps; ++t) {
+                uint32_t used = 0, later = 0;
+                int take[8];
+                // every lane a class of its own, in turn
+                for (int i = 0; i < 8; ++i) {
+                    const int c = (t + i) & 7;
+                    take[i] = -1;
+                    if (has[i] >> c & 1) {
+                        take[i] = c;
+                        used |= 1u << c;
+                    } else {
+                        later |= 1u << i;
+                    }
+                }
+                for (; later; later &= later - 1) {
+                    const int i = __builtin_ctz(later), l = lanes[i];
+                    uint32_t can = has[i] & ~used;
+                    if (!can) {
+                        if (left[l] < steps - t) continue;  // it waits (or has none)
+                        can = has[i];                       // it collides
+                    }
+                    int best = -1;
+                    for (; can; can &= can - 1) {
+                        const int c = __builtin_ctz(can);
+                        if (best < 0 || count[l][c] > count[l][best]) best = c;
+                    }
+                    take[i] = best;
+                    used |= 1u << best;
+                }
+                char *group = out + (size_t)(t / STRIP_STEPS) * STRIP_GROUP_BYTES;
+                const int e = t % STRIP_STEPS;
+                for (int i = 0; i < 8; ++i) {
+                    const int l = lanes[i], c = take[i];
+                    uint16_t place = (uint16_t)zero_row;
+                    float value = 0.0f;
+                    if (c >= 0) {
+                        const size_t from = (size_t)next[i][c]++;
+                        place = s.columns[from];
+                        value = s.values[from];
+                        --left[l];
+                        if (--count[l][c] == 0) has[i] &= ~(1u << c);
+                    }
+                    std::memcpy(group + l * 16 + e * 4, &value, 4);
+                    std::memcpy(group + 1024 + l * 8 + e * 2, &place, 2);
+                }
+            }
+        }
+}
+
+constexpr int64_t MOST_GROUPS = 1 << 20;  // of a unit in a band (more take a column stored over and over in a row)
+
+// over(n, job): job(first, end) over shares of n units, on several threads.  The columns have been checked.  False if A cannot be
+// stored this way.
+template <typename Over> bool build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N, Over over, host &out)
+{
+    out = host();
+    if (M >= (int64_t)1 << STRIP_PARTS_SHIFT) return false;
+    StripPlan &p = out.plan;
+    band_sizes(K, p);
+    const std::vector<uint32_t> order = by_length(M, row_ptr);
+    const std::vector<unit> units = units_for(M, row_ptr, order, N, p.bands);
+    p.n_units = (int64_t)units.size();
+    const int64_t B = p.bands, R = p.band_rows;
+    out.rows.resize((size_t)p.n_units * 64, STRIP_NO_ROW);
+    out.units.resize((size_t)(p.n_units * B) * 2);
+    std::vector<int64_t> groups((size_t)(p.n_units * B) + 1, 0);
+    auto rows_of = [&](const unit &u) { return std::min<int64_t>(64 >> u.parts_log2, M - u.first); };
+    // Places of a row's entries in order of the columns (stable), or null where they are stored in that order.
+    auto canonical = [&](int64_t row, scratch &s) -> const int32_t * {
+        const int32_t a = row_ptr[row], b = row_ptr[row + 1];
+        bool sorted = true;
+        for (int32_t q = a + 1; q < b && sorted; ++q) sorted = col_idx[q] >= col_idx[q - 1];
+        if (sorted) return nullptr;
+        s.order.resize((size_t)(b - a));
+        std::iota(s.order.begin(), s.order.end(), a);
+        std::stable_sort(s.order.begin(), s.order.end(), [&](int32_t x, int32_t y) { return col_idx[x] < col_idx[y]; });
+        return s.order.data();
+    };
+    // ---- how many groups of steps every unit has in every band
+    over(p.n_units, [&](int64_t first, int64_t end) {
+        std::vector<int64_t> in_band((size_t)B);
+        for (int64_t i = first; i < end; ++i) {
+            const unit &u = units[(size_t)i];
+            for (int64_t r = 0; r < rows_of(u); ++r) {
+                const int64_t row = order[(size_t)(u.first + r)];
+                for (int x = 0; x < 1 << u.parts_log2; ++x) out.rows[(size_t)(i * 64 + (r << u.parts_log2) + x)] = (uint32_t)row | (uint32_t)u.parts_log2 << STRIP_PARTS_SHIFT;
+                if (B == 1) {
+                    in_band[0] = row_ptr[row + 1] - row_ptr[row];
+                } else {
+                    std::fill(in_band.begin(), in_band.end(), (int64_t)0);
+                    for (int32_t q = row_ptr[row]; q < row_ptr[row + 1]; ++q) ++in_band[(size_t)((uint32_t)col_idx[q] / (uint32_t)R)];
+                }
+                for (int64_t b = 0; b < B; ++b) {
+                    int64_t &g = groups[(size_t)(i * B + b) + 1];
+                    g = std::max(g, steps_of((in_band[(size_t)b] + (1 << u.parts_log2) - 1) >> u.parts_log2) / STRIP_STEPS);
+                }
+            }
+        }
+    });
+    if (*std::max_element(groups.begin(), groups.end()) > MOST_GROUPS) return false;
+    for (size_t k = 1; k < groups.size(); ++k) groups[k] += groups[k - 1];
+    if (groups.back() >= (int64_t)1 << 32) return false;
+    p.steps = groups.back() * STRIP_STEPS;
+    p.longest = units.front().steps;
+    for (int64_t s = 1; s <= StripPlan::KNOWN; ++s) {
+        int64_t g = 0;
+        strip_time(p, K, s * STRIP_COLS, &g);
+        p.groups[s] = (uint32_t)g;
+    }
+    for (int64_t k = 0; k < p.n_units * B; ++k) {
+        out.units[(size_t)k * 2] = (uint32_t)groups[(size_t)k];
+        out.units[(size_t)k * 2 + 1] = (uint32_t)(groups[(size_t)k + 1] - groups[(size_t)k]);
+    }
+    // ---- their entries
+    out.stream.resize((size_t)groups.back() * (STRIP_GROUP_BYTES / 4));
+    over(p.n_units, [&](int64_t first, int64_t end) {
+        scratch s;
+        std::vector<int32_t> sorted;      // the unit's rows in order of the columns
+        std::vector<int64_t> begin(65);   // their places there
+        for (int64_t i = first; i < end; ++i) {
+            const unit &u = units[(size_t)i];
+            const int64_t n = rows_of(u);
+            sorted.clear();
+            for (int64_t r = 0; r < n; ++r) {
+                const int64_t row = order[(size_t)(u.first + r)];
+                const int32_t *c = canonical(row, s);
+                begin[(size_t)r] = (int64_t)sorted.size();
+                if (c) sorted.insert(sorted.end(), c, c + (row_ptr[row + 1] - row_ptr[row]));
+                else
+                    for (int32_t q = row_ptr[row]; q < row_ptr[row + 1]; ++q) sorted.push_back(q);
+            }
+            begin[(size_t)n] = (int64_t)sorted.size();
+            for (int64_t b = 0; b < B; ++b) {
+                const int64_t band_first = b * R;
+                auto range = [&](int64_t r, int64_t &from, int64_t &to) {
+                    const auto lo = sorted.begin() + begin[(size_t)r], hi = sorted.begin() + begin[(size_t)r + 1];
+                    auto before = [&](int64_t col) { return std::partition_point(lo, hi, [&](int32_t e) { return (int64_t)col_idx[e] < col; }) - sorted.begin(); };
+                    from = B == 1 ? begin[(size_t)r] : before(band_first);
+                    to = B == 1 ? begin[(size_t)r + 1] : before(band_first + R);
+                };
+                const size_t k = (size_t)(i * B + b);
+                fill(u, n, range, col_idx, vals, sorted.data(), (int32_t)band_first, (uint32_t)R, groups[k + 1] - groups[k],
+                     reinterpret_cast<char *>(out.stream.data()) + (size_t)groups[k] * STRIP_GROUP_BYTES, s);
+            }
+        }
+    });
+    return true;
+}
+
+}  // namespace strips
+
+#endif

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "spmm_strips.h"
+
 // Format.  The rows are taken in panels of `rows` = R (32, 16 or 8) consecutive rows of A, the
 // columns in steps of 16 * 64 / R columns.  The wave that multiplies a (panel, step) pair, a *block*,
 // gives it to 16 matrix operands t of one element per lane l:
@@ -27,6 +29,7 @@ struct TilePlan {
     bool built = false;             // whole
     bool exact_parts = false;       // R = 32: every value is the sum of three bf16 numbers
     float largest = 0.0f;           // R = 32: size of the largest value
+    StripPlan strips;               // the entries are in strips instead (rows = 0)
 };
 
 constexpr int TILE_OPERANDS = 16;
@@ -45,7 +48,7 @@ void spmm_tiles_release(TilePlan &p);
 // (1, 2 or 4) it runs with.  density = share of the entries kept, peak = the largest such share of a panel.
 extern "C" double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB);
 
-// Enqueues C <- A x B.  Returns the hipError_t of the launch as int.
+// Enqueues C <- A x B, on tiles or on strips.  Returns the hipError_t of the launch as int.
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream);
 
 #endif

@@ -1589,6 +1589,7 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
 
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream)
 {
+    if (p.strips.n_units > 0) return spmm_strips_execute(p.strips, K, B, N, C, stream);
     tile_args a{p.d_stream, p.d_offsets, B, C, (uint64_t)K * (uint64_t)N * 4u, (int32_t)p.n_panels, (int32_t)p.n_steps, 1,
                 (int32_t)M, (int32_t)K, N, 0, p.largest};
     hipStream_t s = (hipStream_t)stream;

@@ -1,0 +1,112 @@
+"""The strips path (eight columns of B in LDS, one lane per part of a row) against the oracle, at the edges of its units, bands
+and strips.  Needs the GPU."""
+import numpy as np
+import pytest
+
+import paper_2506_15174_amd as spmm
+from workloads import generators as gen
+from test_gpu_parity import check, gpu_product, torch_gpu  # noqa: F401
+from test_gpu_tiles import integer_matrix
+
+pytestmark = pytest.mark.gpu
+
+
+def strips_of(csr, n_hint):
+    plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=n_hint, strips=1)
+    info = plan.describe()
+    assert info["strip_units"] > 0 and info["tile_rows"] == 0 and info["scratch_bytes"] == 0
+    return plan
+
+
+@pytest.mark.parametrize("N", [1, 7, 8, 9, 64, 130, 4099])
+@pytest.mark.parametrize("M,K,density,hint", [(2, 3, 0.9, 8), (2, 5000, 0.99, 200), (65, 100, 0.2, 16), (257, 5088, 0.1, 0), (257, 5089, 0.1, 64),
+                                              (70, 11000, 0.05, 128), (1500, 300, 0.02, 256)])
+def test_whole_numbers_are_exact(torch_gpu, oracle, M, K, density, hint, N):  # noqa: F811
+    """Rows in 1 to 64 parts, strips in one to three bands, few and many columns of B; B and C at every
+    offset that the interface allows, nothing beside C written, through both entry points."""
+    torch = torch_gpu
+    csr = integer_matrix(M, K, density, 5)
+    plan = strips_of(csr, hint)
+    Bh = np.random.default_rng(N).integers(-16, 17, (K, N)).astype(np.float32)
+    C_ref, _ = oracle.spmm(csr.row_ptr, csr.col_idx, csr.vals, Bh)
+    for offset, run in ((0, plan.execute_raw), (1, plan.execute_static_raw), (3, plan.execute_raw)):
+        memory = torch.full((K * N + 8,), float("nan"), device="cuda")
+        B = memory[offset:offset + K * N].view(K, N)
+        B.copy_(torch.from_numpy(Bh))
+        out = torch.full((M * N + 8,), float("nan"), device="cuda")
+        run(B.data_ptr(), N, out.data_ptr() + 4 * offset, None)
+        torch.cuda.synchronize()
+        host = out.cpu().numpy()
+        assert np.array_equal(host[offset:offset + M * N].reshape(M, N).astype(np.float64), C_ref)
+        assert np.isnan(host[:offset]).all() and np.isnan(host[offset + M * N:]).all()
+
+
+@pytest.mark.parametrize("make,M,K,sparsity,N", [(gen.uniform_positions, 4096, 4096, 0.95, 128), (gen.lognormal_rows, 3001, 2511, 0.85, 200),
+                                                 (gen.zipf_rows, 2000, 9000, 0.93, 60), (gen.zipf_rows, 3000, 700, 0.8, 33), (gen.lognormal_rows, 9000, 400, 0.7, 20)])
+def test_against_the_oracle(torch_gpu, oracle, make, M, K, sparsity, N):  # noqa: F811
+    csr = make(M, K, sparsity, 6)
+    B = gen.dense_activations(K, N, 7)
+    C, plan = gpu_product(torch_gpu, csr, B, guard_rows=2, n_hint=N, strips=1)
+    assert plan.describe()["strip_units"] > 0
+    check(oracle, csr, B, C, parallel=True)
+    C2, _ = gpu_product(torch_gpu, csr, B, n_hint=N, strips=1, threads=3)
+    assert np.array_equal(C, C2)
+
+
+def test_unsorted_columns_duplicates_empty_rows_and_bad_columns(torch_gpu, oracle):  # noqa: F811
+    """The order of a row's entries does not matter, bit for bit; duplicates are summed; a column outside A is refused."""
+    rng = np.random.default_rng(8)
+    csr = gen.lognormal_rows(300, 6000, 0.97, 9)
+    order = np.concatenate([rng.permutation(np.arange(a, b)) for a, b in zip(csr.row_ptr[:-1], csr.row_ptr[1:])])
+    B = gen.dense_activations(csr.K, 40, 10)
+    C0, _ = gpu_product(torch_gpu, csr, B, strips=1)
+    C1, _ = gpu_product(torch_gpu, gen.Csr(csr.M, csr.K, csr.row_ptr, csr.col_idx[order], csr.vals[order]), B, strips=1)
+    assert np.array_equal(C0, C1)
+    lens = rng.integers(0, 90, 200)
+    lens[::7] = 0
+    row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    csr = gen.Csr(200, 300, row_ptr, rng.integers(0, 300, row_ptr[-1]).astype(np.int32), rng.standard_normal(row_ptr[-1]).astype(np.float32))
+    C, _ = gpu_product(torch_gpu, csr, B[:300], guard_rows=1, strips=1)
+    check(oracle, csr, B[:300], C)
+    for bad in (-1, 300):
+        col = csr.col_idx.copy()
+        col[-1] = bad
+        with pytest.raises(spmm.SpmmError) as err:
+            spmm.plan_create(200, 300, row_ptr, col, csr.vals, strips=1)
+        assert err.value.status == spmm.SPMM_ERR_INVALID_CSR
+
+
+def test_a_value_outside_the_domain_reaches_only_rows_with_an_entry_there(torch_gpu):  # noqa: F811
+    csr = gen.uniform_positions(64, 256, 0.5, 15)
+    B = gen.dense_activations(csr.K, 32, 16)
+    B[100, 7] = np.inf
+    holds = np.zeros(csr.M, bool)
+    holds[np.repeat(np.arange(csr.M), np.diff(csr.row_ptr))[csr.col_idx == 100]] = True
+    C, _ = gpu_product(torch_gpu, csr, B, strips=1)
+    finite = np.isfinite(C)
+    assert not finite[holds, 7].any() and finite[~holds].all() and finite[:, [c for c in range(32) if c != 7]].all()
+
+
+def test_more_workgroups_than_a_launch_takes_and_addresses_beyond_32_bits(torch_gpu):  # noqa: F811
+    """33.6 million columns of B: 4.2 million strips (a launch takes 4.19 million workgroups of 1024 threads) and rows of 134 MB, of which 32
+    span more than 4 GiB."""
+    torch, N = torch_gpu, (1 << 25) + 9
+    plan = spmm.plan_create(2, 3, np.array([0, 2, 3]), np.array([0, 2, 1]), np.array([3.0, -2.0, 5.0]), strips=1)
+    assert plan.describe()["strip_units"] > 0
+    B = torch.randint(-9, 10, (3, N), device="cuda").float()
+    C = plan.execute(B)
+    assert torch.equal(C[0], 3 * B[0] - 2 * B[2]) and torch.equal(C[1], 5 * B[1])
+
+
+def test_when_strips_are_chosen(torch_gpu):  # noqa: F811
+    """Where chunks would gather slowly; never with another setting, never against one."""
+    csr = gen.uniform_positions(4096, 4096, 0.95, 1)
+    args = (csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals)
+    assert spmm.plan_create(*args, n_hint=128).describe()["strip_units"] > 0
+    for kw in (dict(tiles=-1), dict(strips=-1), dict(ufi=4), dict(kslices=2), dict(tiles=16)):
+        assert spmm.plan_create(*args, n_hint=128, **kw).describe()["strip_units"] == 0
+    for kw in (dict(ufi=4), dict(host_only=True), dict(force_wide=True)):
+        with pytest.raises(spmm.SpmmError) as err:
+            spmm.plan_create(*args, strips=1, **kw)
+        assert err.value.status == spmm.SPMM_ERR_INVALID_ARG
+    assert spmm.plan_create(40, 60, np.zeros(41), [], [], strips=1).describe()["strip_units"] == 0   # no entry at all
