@@ -573,9 +573,9 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     return rows;
 }
 
-// Strips take the place of chunks where they are estimated to be faster, without a hint at each of three widths.  Of 450 random
-// products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256 columns) that moves 145 from chunks, 1.61
-// times as fast on average, 0.97 at worst, with 0.7 of the error against 64 bits; 38 others would be 1.2 times as fast, half of them below 2^17
+// Strips take the place of chunks where they are estimated to be faster, without a hint at each of three widths.  Of 420 random
+// products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256 columns) that moves 145 from chunks, 1.60
+// times as fast on average, 0.96 at worst, with 0.7 of the error against 64 bits; 42 others would be 1.19 times as fast, 26 of them below 2^17
 // entries.  Not of tiles, which are
 // built on the device: 4096 x 4096, 20 % kept, 64 columns, plan and product 0.90 ms on tiles, 3.9 on strips.
 bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
@@ -583,12 +583,17 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     const int64_t nnz = row_ptr[M];
     // As for tiles mostly the launch's time; but chunks take two column tiles beyond 128 columns.
     if (nnz == 0 || (nnz < ((int64_t)1 << 17) && n_hint <= 128)) return false;
-    const StripSizes p = strips::sizes(M, K, row_ptr, n_hint);
-    const double hinted[] = {(double)std::min(std::max(n_hint, 4), 256)}, unknown[] = {16.0, 64.0, 200.0};
-    for (int i = 0; i < (n_hint > 0 ? 1 : 3); ++i) {
-        const double N = n_hint > 0 ? hinted[i] : unknown[i];
-        if (strip_time(p, K, (int64_t)N, nullptr) >= chunks_time(M, K, row_ptr, n_hint, N)) return false;
+    const int32_t hinted[] = {std::min(std::max(n_hint, 4), 256)}, unknown[] = {16, 64, 200};
+    const int widths = n_hint > 0 ? 1 : 3;
+    double chunks[3];
+    for (int i = 0; i < widths; ++i) {
+        const int32_t N = n_hint > 0 ? hinted[i] : unknown[i];
+        chunks[i] = chunks_time(M, K, row_ptr, n_hint, N);
+        if (strips::time_at_best(M, K, nnz, N) >= chunks[i]) return false;
     }
+    const StripSizes p = strips::sizes(M, K, row_ptr, n_hint);
+    for (int i = 0; i < widths; ++i)
+        if (strip_time(p, K, n_hint > 0 ? hinted[i] : unknown[i], nullptr) >= chunks[i]) return false;
     return true;
 }
 

@@ -37,7 +37,7 @@ struct StripSizes {
 };
 struct StripPlan : StripSizes {
     static constexpr int KNOWN = 64;
-    uint32_t groups[KNOWN + 1] = {};  // of units, for that many strips (strip_groups)
+    uint32_t groups[KNOWN + 1] = {};  // of units, for that many strips (strip_time)
     uint32_t *d_stream = nullptr;  // DEVICE groups
     uint32_t *d_units = nullptr;   // DEVICE per unit and band: first group, groups
     uint32_t *d_rows = nullptr;    // DEVICE per unit and lane: row | log2(P) << 28, or STRIP_NO_ROW
@@ -47,14 +47,14 @@ constexpr int STRIP_PARTS_SHIFT = 28;
 
 // Estimated time in us of a product with N columns of B, and the groups of units it runs with: a group is one workgroup
 // per strip, and of one to eight rounds of 256 workgroups those are taken that take least.  (A wave has one unit
-// at most where the strip comes in bands.)  Fitted to 450 products (256 to 16384 rows and columns, 2 to 50 % kept, 4 to 256 columns): rms error 7 %.
+// at most where the strip comes in bands.)  Fitted to 420 products (256 to 16384 rows and columns, 2 to 50 % kept, 4 to 256 columns): rms error 6.6 %.
 // A workgroup's time: the copy of its strip (by the lines of 128 bytes that it touches; more where B exceeds an L2), its units' steps or, where
 // those are few or uneven, its longest wave's, and the units' ends.
 inline double strip_time(const StripSizes &p, int64_t K, int64_t N, int64_t *groups_out)
 {
     const int64_t strips = (N + STRIP_COLS - 1) / STRIP_COLS, least = p.bands > 1 ? (p.n_units + STRIP_WAVES - 1) / STRIP_WAVES : 1;
     const double lines = std::min(1.0, (double)N / 32.0), beyond_l2 = std::min(1.0, std::max(0.0, 4e-6 / 4.2 * (double)K * (double)N - 0.75));
-    const double copy = 1e-3 * (double)p.bands * p.band_rows * lines * (0.87 + 0.48 * beyond_l2), mean = (double)p.steps / (double)p.n_units;
+    const double copy = 1e-3 * (double)p.bands * p.band_rows * lines * (0.91 + 0.4 * beyond_l2), mean = (double)p.steps / (double)p.n_units;
     double best = 0.0;
     int64_t last = 0;
     for (int64_t r = 1; r <= 8; ++r) {
@@ -62,8 +62,8 @@ inline double strip_time(const StripSizes &p, int64_t K, int64_t N, int64_t *gro
         if (groups == last) continue;
         last = groups;
         const double units = (double)p.n_units / (double)groups;
-        const double all = 5.8e-3 * mean * units, wave = 43e-3 * std::max((double)p.longest, mean * std::ceil(units / STRIP_WAVES));
-        const double us = (double)rounds * (2.83 + copy + 1.1 * (p.bands - 1) + std::cbrt(all * all * all + wave * wave * wave) + 0.05 * units);
+        const double all = 6.6e-3 * mean * units, wave = 40e-3 * std::max((double)p.longest, mean * std::ceil(units / STRIP_WAVES));
+        const double us = (double)rounds * (2.7 + copy + 0.96 * (p.bands - 1) + std::sqrt(std::sqrt(all * all * all * all + wave * wave * wave * wave)) + 0.04 * units);
         if (best == 0.0 || us < best) {
             best = us;
             if (groups_out) *groups_out = groups;

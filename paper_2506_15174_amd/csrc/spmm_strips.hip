@@ -11,6 +11,7 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
 
 struct strip_args {
@@ -26,11 +27,19 @@ struct strip_args {
     uint32_t n_units, n_groups, n_strips;
 };
 
-// v + v of another lane of the row of 16 (CTRL: a DPP permutation)
-template <int CTRL> __device__ __forceinline__ float add_other(float v)
+// v of lane l ^ 1, l ^ 2, l ^ 4 or l ^ 8
+template <int CTRL> __device__ __forceinline__ float moved(float v)
 {
-    return v + __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xf, 0xf, true));
 }
+template <int BIT> __device__ __forceinline__ float other(float v)
+{
+    if constexpr (BIT == 1) return moved<0xB1>(v);              // 1 0 3 2 of four lanes
+    if constexpr (BIT == 2) return moved<0x4E>(v);              // 2 3 0 1
+    if constexpr (BIT == 4) return moved<0x141>(moved<0x1B>(v));  // eight lanes mirrored, after four lanes mirrored
+    if constexpr (BIT == 8) return moved<0x128>(v);             // 16 lanes turned by eight
+}
+// v + v of lane l ^ 16 or l ^ 32
 __device__ __forceinline__ float add_row(float v)
 {
     const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -54,11 +63,15 @@ __device__ __forceinline__ float add_half(float v)
 //
 // Every 12 groups they go to a total (8192 x 8192, 50 % kept: error against 64 bits 4.1e-7 without, 1.9e-7 with a total every 6).
 //
-// What bounds it: LDS (two reads of 4.3 cycles per step and wave, 1.2 times that with the collisions that the
-// builder's order leaves) and the vector ALUs (8 multiply-adds and 3 others per step) about equally, 11 of the 17 cycles that a step takes, and
-// before them the copy of the strip: the vector L1 fetches a line of 128 bytes for 32, 2 cycles, so 4096 rows take 3.6 us.
-// Three plans in turn, on chunks and on strips: 4096 x 4096, 95 % pruned, 128 columns 17.4 and 14.3 us, 3001 x 2511, 85 % in lognormal
-// rows, 200 columns 37.4 and 20.8.  Back to back 8968 x 2473, 92 %, 96 columns 37 and 14, 2432 x 6741, 91 %, 112 columns 37 and 19.
+// What bounds it: LDS (two reads of 4.3 cycles per step and wave, 1.15 times that with the collisions that the builder's order
+// leaves), the vector ALUs (8 multiply-adds and 2 others per step) and the fetch of the entries (384 bytes per step) take about ten
+// cycles each of the 15 that a step and wave takes of a compute unit; and before them the copy of the strip: the vector L1
+// fetches a line of 128 bytes for 32, 2 cycles, so 4096 rows take 3.6 us.
+// Three plans in turn, on chunks and on strips: 4096 x 4096, 95 % pruned, 128 columns 17.4 and 13.0 us, 3001 x 2511, 85 % in lognormal
+// rows, 200 columns 37.4 and 17.4.  Back to back 8968 x 2473, 92 %, 96 columns 39 and 14.
+//
+// An accumulator's registers hold columns 1 0 3 2 of its four: a v_fmac of three registers that are all even or all odd takes 4.9
+// cycles, else 2.8, and those of LDS hold them in order (1 to 3 % of the product).
 template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, STRIP_WAVES / 4) void spmm_strips_kernel(const strip_args args)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -69,27 +82,28 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     const uint32_t group = (uint32_t)(place / args.n_strips), strip = (uint32_t)(place % args.n_strips);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
-    const uint32_t N = (uint32_t)args.N, col0 = strip * STRIP_COLS, band_rows = (uint32_t)args.band_rows;
-    const uint32_t half = (uint32_t)(lane & 1) * 16u;  // of its rows of the strip, which the lane reads first
+    constexpr int Q = STRIP_COLS / 4;  // fours of columns; the lane reads four i ^ turn of its rows as the i-th
+    const uint32_t turn = (uint32_t)lane % Q, N = (uint32_t)args.N, col0 = strip * STRIP_COLS, band_rows = (uint32_t)args.band_rows;
     const int bands = BANDS ? args.bands : 1;
 
-    if (threadIdx.x < 2) *reinterpret_cast<f32x4 *>(lds + band_rows * STRIP_ROW_BYTES + threadIdx.x * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (threadIdx.x < Q) *reinterpret_cast<f32x4 *>(lds + band_rows * STRIP_ROW_BYTES + threadIdx.x * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     auto copy_band = [&](uint32_t band) {
         const uint32_t row0 = band * band_rows, rows = min(band_rows, (uint32_t)args.K - row0);
         if constexpr (WIDE) {
-            for (uint32_t t = threadIdx.x; t < rows * 2; t += 64 * STRIP_WAVES) {
-                const float *p = args.B + (uint64_t)(row0 + t / 2) * N;
-                const uint32_t n = col0 + t % 2 * 4;
+            for (uint32_t t = threadIdx.x; t < rows * Q; t += 64 * STRIP_WAVES) {
+                const float *p = args.B + (uint64_t)(row0 + t / Q) * N;
+                const uint32_t n = col0 + t % Q * 4;
                 f32x4 x;
 #pragma unroll
                 for (uint32_t c = 0; c < 4; ++c) x[c] = n + c < N ? p[n + c] : 0.0f;
                 *reinterpret_cast<f32x4 *>(lds + t * 16) = x;
             }
         } else {
-            // 32 rows at a time, two lanes a row.  (Past the end of B zeros, past the end of a row what follows: columns that C does not have.)
-            const uint32_t off = (uint32_t)(lane / 2) * N * 4u + (uint32_t)(lane % 2) * 16u;
-            for (uint32_t op = (uint32_t)wave; op * 32 < rows; op += STRIP_WAVES) {
-                const uint64_t skip = ((uint64_t)(row0 + op * 32) * N + col0) * 4u, left = args.b_bytes - skip;
+            // 1024 bytes at a time, Q lanes a row.  (Past the end of B zeros, past the end of a row what follows: columns that C does not have.)
+            const uint32_t off = (uint32_t)(lane / Q) * N * 4u + (uint32_t)(lane % Q) * 16u;
+            constexpr uint32_t OP_ROWS = 64 / Q;
+            for (uint32_t op = (uint32_t)wave; op * OP_ROWS < rows; op += STRIP_WAVES) {
+                const uint64_t skip = ((uint64_t)(row0 + op * OP_ROWS) * N + col0) * 4u, left = args.b_bytes - skip;
                 const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(args.B)) + skip, (short)0,
                                                                                    (int)(left > 0xFFFFFFFCull ? 0xFFFFFFFCu : (uint32_t)left), 0x00020000);
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void *)(lds + op * 1024), 16, (int)off, 0, 0, 0);
@@ -102,15 +116,19 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     for (uint32_t unit = group + (uint32_t)wave * args.n_groups;; unit += STRIP_WAVES * args.n_groups) {
         const bool any = unit < args.n_units;
         if (!any && copied) break;
-        f32x4 acc[STRIP_STEPS][2], total[2] = {};  // of the last groups; of all before them
+        f32x4 acc[STRIP_STEPS][Q], total[Q] = {};  // of the last groups; of all before them
         auto collect = [&] {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) total[q] += (acc[0][q] + acc[1][q]) + (acc[2][q] + acc[3][q]);
+            for (int q = 0; q < Q; ++q) {
+                total[q] += (acc[0][q] + acc[1][q]) + (acc[2][q] + acc[3][q]);
 #pragma unroll
-            for (int e = 0; e < STRIP_STEPS; ++e) acc[e][0] = acc[e][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int e = 0; e < STRIP_STEPS; ++e) acc[e][q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
         };
 #pragma unroll
-        for (int e = 0; e < STRIP_STEPS; ++e) acc[e][0] = acc[e][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int e = 0; e < STRIP_STEPS; ++e)
+#pragma unroll
+            for (int q = 0; q < Q; ++q) acc[e][q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         for (int band = 0; band < bands; ++band) {
             const u32x2 d = any ? args.units[(size_t)unit * (uint32_t)bands + (uint32_t)band] : u32x2{0u, 0u};
             const uint32_t first = __builtin_amdgcn_readfirstlane(d[0]), groups = __builtin_amdgcn_readfirstlane(d[1]);
@@ -130,26 +148,28 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             }
             if (BANDS || !copied) __syncthreads();
             copied = true;
-            f32x4 x[2][2][2];  // rows of the strip: two steps each, read while the other two are multiplied
+            f32x4 x[2][2][Q];  // rows of the strip: two steps each, read while the other two are multiplied
             auto read = [&](int k, int h) {
-                const uint32_t two = places[k][h];
-                uint32_t at[2];
-                asm("v_mad_u32_u16 %0, %1, 32, %2" : "=v"(at[0]) : "v"(two), "v"(half));
-                asm("v_mad_u32_u16 %0, %1, 32, %2 op_sel:[1,0,0,0]" : "=v"(at[1]) : "v"(two), "v"(half));
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    x[h][e][0] = *reinterpret_cast<const f32x4 *>(lds + at[e]);
-                    x[h][e][1] = *reinterpret_cast<const f32x4 *>(lds + (at[e] ^ 16u));
+                    // (as an integer: the address of lds is 0, and to it the compiler would add)
+                    uint32_t at;
+                    if (e == 0) asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(turn * 16u));
+                    else asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(turn * 16u));
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) x[h][e][q] = *(const lds_f32x4 *)(size_t)(at ^ (uint32_t)q * 16u);
                 }
             };
             auto multiply = [&](int k, int h) {
 #pragma unroll
                 for (int e = 0; e < 2; ++e)
 #pragma unroll
-                    for (int q = 0; q < 2; ++q)
+                    for (int q = 0; q < Q; ++q)
 #pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            acc[2 * h + e][q][c] = __builtin_fmaf(values[k][2 * h + e], x[h][e][q][c], acc[2 * h + e][q][c]);
+                        for (int c = 0; c < 4; ++c) {
+                            f32x4 &to = acc[2 * h + e][q];
+                            to[c ^ 1] = __builtin_fmaf(values[k][2 * h + e], x[h][e][q][c], to[c ^ 1]);
+                        }
             };
             // The compiler would move the loads to their first use.
             auto keep_order = [] { __builtin_amdgcn_sched_barrier(0); };
@@ -167,41 +187,49 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
                     read((k + 1) % 3, 0);
                     keep_order();
                     multiply(k, 1);
+                    keep_order();
                 }
+                // (four registers in a row, not any four)
+#pragma unroll
+                for (int e = 0; e < STRIP_STEPS; ++e)
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(acc[e][q]));
                 if (g % 12 == 9) collect();
             }
         }
         if (!any) break;
         collect();
-        // ---- the sums of the four steps, of the parts of a row; two lanes of a row store four columns each
-        const bool odd = (lane & 1) != 0;
-        f32x4 sum[2] = {odd ? total[1] : total[0], odd ? total[0] : total[1]};  // columns 0 .. 3 and 4 .. 7
+        // ---- the sums of the parts of a row: lanes l and l ^ 1, then l and l ^ 2, each keep the fours that they read first (the other
+        // one has four i of the lane as i ^ 1, i ^ 2); from then on a lane has one four
+#pragma unroll
+        for (int q = 0; q < Q; ++q) total[q] = __builtin_shufflevector(total[q], total[q], 1, 0, 3, 2);
         const uint32_t word = args.rows[(size_t)unit * 64u + (uint32_t)lane], row = word & ((1u << STRIP_PARTS_SHIFT) - 1u);
         const uint32_t parts_log2 = __builtin_amdgcn_readfirstlane(word >> STRIP_PARTS_SHIFT);  // lane 0 has a row
-        auto all = [&](auto f) {
+        auto each = [&](int q, auto f) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) sum[q][c] = f(sum[q][c]);
+            for (int c = 0; c < 4; ++c) total[q][c] = f(total[q][c], c);
         };
-        // (each pair of lanes has equal sums after the first step, each four after the second: mirrored lanes serve)
-        if (parts_log2 > 0) all([](float v) { return add_other<0xB1>(v); });   // lanes 1 0 3 2
-        if (parts_log2 > 1) all([](float v) { return add_other<0x4E>(v); });   // lanes 2 3 0 1
-        if (parts_log2 > 2) all([](float v) { return add_other<0x141>(v); });  // the other four of eight
-        if (parts_log2 > 3) all([](float v) { return add_other<0x140>(v); });  // the other eight of 16
-        if (parts_log2 > 4) all([](float v) { return add_row(v); });
-        if (parts_log2 > 5) all([](float v) { return add_half(v); });
+        if (parts_log2 > 0) {
+#pragma unroll
+            for (int q = 0; q < Q; q += 2) each(q, [&](float v, int c) { return v + other<1>(total[q + 1][c]); });
+        }
+        if (parts_log2 > 1) each(0, [&](float v, int c) { return v + other<2>(total[Q > 2 ? 2 : 0][c]); });
+        if (parts_log2 > 2) each(0, [](float v, int) { return v + other<4>(v); });
+        if (parts_log2 > 3) each(0, [](float v, int) { return v + other<8>(v); });
+        if (parts_log2 > 4) each(0, [](float v, int) { return add_row(v); });
+        if (parts_log2 > 5) each(0, [](float v, int) { return add_half(v); });
         const uint32_t part = (uint32_t)lane & ((1u << parts_log2) - 1u);
-        if (word != STRIP_NO_ROW && part < 2) {
+        if (word != STRIP_NO_ROW && part < Q) {
             float *dst = args.C + (size_t)row * N + col0;
 #pragma unroll
-            for (uint32_t q = 0; q < 2; ++q) {
-                if (parts_log2 > 0 && part != q) continue;
-                if (col0 + 4 * q + 4 <= N) {
-                    *reinterpret_cast<f32x4_unaligned *>(dst + 4 * q) = sum[q];
+            for (int q = 0; q < Q; ++q) {
+                if (q & ((1 << parts_log2) - 1)) continue;
+                const uint32_t n = 4 * ((uint32_t)q ^ turn);
+                if (col0 + n + 4 <= N) {
+                    *reinterpret_cast<f32x4_unaligned *>(dst + n) = total[q];
                 } else {
                     for (uint32_t c = 0; c < 4; ++c)
-                        if (col0 + 4 * q + c < N) dst[4 * q + c] = sum[q][c];
+                        if (col0 + n + c < N) dst[n + c] = total[q][c];
                 }
             }
         }

@@ -51,24 +51,6 @@ inline std::vector<unit> units_of(int64_t M, const int32_t *row_ptr, const std::
     return units;
 }
 
-// Groups of units a launch for N columns wants: all compute units (256) with a workgroup each.
-inline int64_t wanted_groups(int64_t N) { return std::max<int64_t>(1, 256 / ((N + STRIP_COLS - 1) / STRIP_COLS)); }
-
-// The units for products with N columns: a quarter more than an equal share of the entries for every wave, so that most rows
-// keep to one number of parts; a strip in bands allows one unit per wave only, which more entries per lane bring about.
-inline std::vector<unit> units_for(int64_t M, const int32_t *row_ptr, const std::vector<uint32_t> &order, int64_t N, int32_t bands)
-{
-    const int64_t waves = STRIP_WAVES * wanted_groups(N);
-    int64_t most = std::max<int64_t>(8, steps_of((int64_t)row_ptr[M] * 5 / (4 * 64 * waves) + 1));
-    std::vector<unit> units = units_of(M, row_ptr, order, most);
-    for (int tries = 0; bands > 1 && (int64_t)units.size() > waves && tries < 8; ++tries) {
-        most += steps_of(most / 16 + 1);
-        units = units_of(M, row_ptr, order, most);
-    }
-    std::stable_sort(units.begin(), units.end(), [](const unit &x, const unit &y) { return x.steps > y.steps; });
-    return units;
-}
-
 inline void band_sizes(int64_t K, StripSizes &p)
 {
     p.bands = (int32_t)((K + STRIP_MOST_ROWS - 1) / STRIP_MOST_ROWS);
@@ -78,15 +60,62 @@ inline void band_sizes(int64_t K, StripSizes &p)
 // Columns of B that a plan without a hint is made for.
 constexpr int64_t UNKNOWN_COLUMNS = 64;
 
-// The sizes a plan made for n_hint columns would have, but for what bands leave idle.
-inline StripSizes sizes(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
+// The units, longest first, for products with N columns, and their sizes (in bands: but for what bands leave idle): lanes of 0.8 to
+// 1.6 equal shares of the entries, whichever is estimated to take least.  (A row's parts are a power of two, so some shares leave
+// some waves a second unit and others idle: 3001 x 2511, 85 % pruned, 200 columns 17.2 us with 1.25 for all, 15.7 so.)  A strip in bands
+// allows one unit per wave only, which more entries per lane bring about.
+inline std::vector<unit> units_for(int64_t M, int64_t K, const int32_t *row_ptr, const std::vector<uint32_t> &order, int64_t N, StripSizes &p)
+{
+    band_sizes(K, p);
+    const int64_t waves = STRIP_WAVES * std::max<int64_t>(1, 256 / ((N + STRIP_COLS - 1) / STRIP_COLS));  // with a workgroup on every compute unit
+    std::vector<unit> best;
+    int64_t best_most = 0;
+    double best_us = 0.0;
+    auto measure = [&](const std::vector<unit> &units, StripSizes &s) {
+        s.n_units = (int64_t)units.size();
+        s.steps = s.longest = 0;
+        for (const unit &u : units) {
+            s.steps += u.steps;
+            s.longest = std::max<int64_t>(s.longest, u.steps);
+        }
+    };
+    for (const int64_t tenths : {8, 10, 12, 14, 16}) {
+        int64_t most = std::max<int64_t>(8, steps_of((int64_t)row_ptr[M] * tenths / (10 * 64 * waves) + 1));
+        std::vector<unit> units = units_of(M, row_ptr, order, most);
+        for (int tries = 0; p.bands > 1 && (int64_t)units.size() > waves && tries < 8; ++tries) {
+            most += steps_of(most / 16 + 1);
+            units = units_of(M, row_ptr, order, most);
+        }
+        if (most == best_most) continue;
+        StripSizes s = p;
+        measure(units, s);
+        const double us = strip_time(s, K, N, nullptr);
+        if (best.empty() || us < best_us) {
+            best = units;
+            best_us = us;
+            best_most = most;
+        }
+    }
+    measure(best, p);
+    std::stable_sort(best.begin(), best.end(), [](const unit &x, const unit &y) { return x.steps > y.steps; });
+    return best;
+}
+
+// Estimated time in us if no lane were idle and every wave had a unit: at hand without a look at the rows.
+inline double time_at_best(int64_t M, int64_t K, int64_t entries, int64_t N)
 {
     StripSizes p;
     band_sizes(K, p);
-    const std::vector<unit> units = units_for(M, row_ptr, by_length(M, row_ptr), n_hint > 0 ? n_hint : UNKNOWN_COLUMNS, p.bands);
-    p.n_units = (int64_t)units.size();
-    for (const unit &u : units) p.steps += u.steps;
-    p.longest = units.front().steps;
+    p.n_units = std::max<int64_t>((M + 63) / 64, std::min<int64_t>(M, STRIP_WAVES * std::max<int64_t>(1, 256 / ((N + STRIP_COLS - 1) / STRIP_COLS))));
+    p.steps = (entries + 63) / 64;
+    return strip_time(p, K, N, nullptr);
+}
+
+// The sizes a plan made for n_hint columns would have.
+inline StripSizes sizes(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
+{
+    StripSizes p;
+    units_for(M, K, row_ptr, by_length(M, row_ptr), n_hint > 0 ? n_hint : UNKNOWN_COLUMNS, p);
     return p;
 }
 
@@ -140,7 +169,13 @@ template <typename Row> void fill(const unit &u, int64_t n_rows, Row row_range, 
         }
     }
     const int32_t steps = (int32_t)(groups * STRIP_STEPS);
-    for (int cycle = 0; cycle < 4; ++cycle)
+    for (int cycle = 0; cycle < 4; ++cycle) {
+        int32_t total[2][8] = {}, most = 0;  // entries of a class that the even (odd) lanes hold
+        for (int odd = 0; odd < 2; ++odd)
+            for (int i = 0; i < 8; ++i)
+                for (int c = 0; c < 8; ++c) most = std::max(most, total[odd][c] += count[strip_lane(cycle, i, odd)][c]);
+        // where one class holds more entries than there are steps, it has to collide that often: in the same steps for all classes, even and odd
+        const int32_t extra = std::max<int32_t>(0, most - steps);
         for (int odd = 0; odd < 2; ++odd) {
             int lanes[8];
             int32_t next[8][8];
@@ -155,34 +190,26 @@ template <typename Row> void fill(const unit &u, int64_t n_rows, Row row_range, 
                     has[i] |= (uint32_t)(count[l][c] > 0) << c;
                 }
             }
+            int32_t *sum = total[odd];
             for (int32_t t = 0; t < steps; ++t) {
-                uint32_t used = 0, later = 0;
+                const bool twice = extra >= steps || (int64_t)(t + 1) * extra / steps > (int64_t)t * extra / steps;
+                uint32_t once = 0, used = 0;
                 int take[8];
-                // every lane a class of its own, in turn
-                for (int i = 0; i < 8; ++i) {
-                    const int c = (t + i) & 7;
+                // the class of most entries that are left, of those that no other lane took (or only one, in some steps)
+                for (int k = 0; k < 8; ++k) {
+                    const int i = (t + k) & 7, l = lanes[i];
                     take[i] = -1;
-                    if (has[i] >> c & 1) {
-                        take[i] = c;
-                        used |= 1u << c;
-                    } else {
-                        later |= 1u << i;
-                    }
-                }
-                for (; later; later &= later - 1) {
-                    const int i = __builtin_ctz(later), l = lanes[i];
                     uint32_t can = has[i] & ~used;
                     if (!can) {
                         if (left[l] < steps - t) continue;  // it waits (or has none)
                         can = has[i];                       // it collides
                     }
-                    int best = -1;
-                    for (; can; can &= can - 1) {
-                        const int c = __builtin_ctz(can);
-                        if (best < 0 || count[l][c] > count[l][best]) best = c;
-                    }
+                    int32_t most_left = 0;
+                    for (int c = 0; c < 8; ++c) most_left = std::max(most_left, ((8 * count[l][c] + sum[c]) * 8 + c) & -(int32_t)(can >> c & 1));
+                    const int best = most_left & 7;
                     take[i] = best;
-                    used |= 1u << best;
+                    if (twice && !(once >> best & 1)) once |= 1u << best;
+                    else used |= 1u << best;
                 }
                 char *group = out + (size_t)(t / STRIP_STEPS) * STRIP_GROUP_BYTES;
                 const int e = t % STRIP_STEPS;
@@ -195,6 +222,7 @@ template <typename Row> void fill(const unit &u, int64_t n_rows, Row row_range, 
                         place = s.columns[from];
                         value = s.values[from];
                         --left[l];
+                        --sum[c];
                         if (--count[l][c] == 0) has[i] &= ~(1u << c);
                     }
                     std::memcpy(group + l * 16 + e * 4, &value, 4);
@@ -202,6 +230,7 @@ template <typename Row> void fill(const unit &u, int64_t n_rows, Row row_range, 
                 }
             }
         }
+    }
 }
 
 constexpr int64_t MOST_GROUPS = 1 << 20;  // of a unit in a band (more take a column stored over and over in a row)
@@ -213,10 +242,8 @@ template <typename Over> bool build(int64_t M, int64_t K, const int32_t *row_ptr
     out = host();
     if (M >= (int64_t)1 << STRIP_PARTS_SHIFT) return false;
     StripPlan &p = out.plan;
-    band_sizes(K, p);
     const std::vector<uint32_t> order = by_length(M, row_ptr);
-    const std::vector<unit> units = units_for(M, row_ptr, order, N, p.bands);
-    p.n_units = (int64_t)units.size();
+    const std::vector<unit> units = units_for(M, K, row_ptr, order, N, p);
     const int64_t B = p.bands, R = p.band_rows;
     out.rows.resize((size_t)p.n_units * 64, STRIP_NO_ROW);
     out.units.resize((size_t)(p.n_units * B) * 2);
@@ -258,7 +285,6 @@ template <typename Over> bool build(int64_t M, int64_t K, const int32_t *row_ptr
     for (size_t k = 1; k < groups.size(); ++k) groups[k] += groups[k - 1];
     if (groups.back() >= (int64_t)1 << 32) return false;
     p.steps = groups.back() * STRIP_STEPS;
-    p.longest = units.front().steps;
     for (int64_t s = 1; s <= StripPlan::KNOWN; ++s) {
         int64_t g = 0;
         strip_time(p, K, s * STRIP_COLS, &g);
