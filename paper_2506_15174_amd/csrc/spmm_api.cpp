@@ -135,13 +135,14 @@ struct plan_release {
     void operator()(spmm_plan *p) const
     {
         bool held = p->tiles.rows > 0;
-        const StripPlan &strips = p->tiles.strips;
+        StripPlan &strips = p->tiles.strips;
         for (void *q : {(void *)p->d_stream, (void *)p->d_wins, (void *)p->d_items, (void *)p->d_rowmap, (void *)p->d_cross_sums,
-                        (void *)p->d_cross_table, (void *)p->d_slice_sums, (void *)strips.d_stream, (void *)strips.d_units, (void *)strips.d_rows})
+                        (void *)p->d_cross_table, (void *)p->d_slice_sums, (void *)strips.d_units})
             if (q) {
                 held = true;
                 (void)hipFree(q);
             }
+        strips.d_units = nullptr;
         spmm_tiles_release(p->tiles);
         if (held) (void)hipGetLastError();
         delete p;
@@ -206,8 +207,13 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         }
     }
     if (use_strips && row_pointer_ok(M, K, row_ptr, col_idx, vals) && row_ptr[M] > 0) {
-        rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, strips);
-        io.schedule_only = rc == 0 && strips.plan.n_units > 0;
+        rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, -(io.n_hint > 0 ? io.n_hint : (int32_t)strips::UNKNOWN_COLUMNS), p->tiles);
+        if (rc == 0 && p->tiles.strips.n_units == 0) rc = TILES_NOT_POSSIBLE;
+        if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
+            spmm_tiles_release(p->tiles);
+            rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, strips);
+        }
+        io.schedule_only = rc == 0 && (strips.plan.n_units > 0 || p->tiles.strips.n_units > 0);
     }
     if (rc == 0) rc = spmm_inspect(M, K, row_ptr, col_idx, vals, io, p->host);
     if (rc != 0) return (spmm_status_t)rc;
@@ -218,13 +224,17 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (hipGetDevice(&p->device) != hipSuccess) return hip_fail();
         const HostPlan &h = p->host;
         spmm_status_t st = SPMM_OK;
-        if (p->tiles.rows > 0) {
+        if (p->tiles.rows > 0 || p->tiles.strips.n_units > 0) {
             p->device_bytes = p->tiles.device_bytes;
         } else if (strips.plan.n_units > 0) {
             StripPlan &to = p->tiles.strips = strips.plan;
-            st = upload(&to.d_stream, strips.stream.data(), strips.stream.size() * 4, p->device_bytes);
-            if (st == SPMM_OK) st = upload(&to.d_units, strips.units.data(), strips.units.size() * 4, p->device_bytes);
-            if (st == SPMM_OK) st = upload(&to.d_rows, strips.rows.data(), strips.rows.size() * 4, p->device_bytes);
+            const size_t front = strips::unit_words(to.n_units, to.bands);
+            std::vector<uint32_t> words(front + strips.stream.size());
+            std::copy(strips.units.begin(), strips.units.end(), words.begin());
+            std::copy(strips.rows.begin(), strips.rows.end(), words.begin() + (ptrdiff_t)strips.units.size());
+            std::copy(strips.stream.begin(), strips.stream.end(), words.begin() + (ptrdiff_t)front);
+            st = upload(&to.d_units, words.data(), words.size() * 4, p->device_bytes);
+            to.d_stream = to.d_units + front;
         } else {
             // Scratch first: hipMemset may return before it is done, the copies behind it do not.
             if (h.n_cross_slots > 0) {
@@ -250,10 +260,11 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (st != SPMM_OK) return st;
         p->on_device = true;
     }
-    p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : strips.plan.n_units > 0 ? (int64_t)strips.stream.size() : (int64_t)p->host.stream.size();
-    if (strips.plan.n_units > 0) {
-        p->host.n_enum = strips.plan.steps * 64;
-        p->host.n_chunks = strips.plan.n_units * strips.plan.bands;
+    const StripPlan &on_strips = p->tiles.strips;
+    p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : on_strips.n_units > 0 ? on_strips.steps / STRIP_STEPS * (STRIP_GROUP_BYTES / 4) : (int64_t)p->host.stream.size();
+    if (on_strips.n_units > 0) {
+        p->host.n_enum = on_strips.steps * 64;
+        p->host.n_chunks = on_strips.n_units * on_strips.bands;
     }
     if (p->tiles.rows > 0) {
         p->host.n_enum = p->tiles.n_panels * K;

@@ -576,8 +576,7 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 // Strips take the place of chunks where they are estimated to be faster, without a hint at each of three widths.  Of 420 random
 // products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256 columns) that moves 145 from chunks, 1.60
 // times as fast on average, 0.96 at worst, with 0.7 of the error against 64 bits; 42 others would be 1.19 times as fast, 26 of them below 2^17
-// entries.  Not of tiles, which are
-// built on the device: 4096 x 4096, 20 % kept, 64 columns, plan and product 0.90 ms on tiles, 3.9 on strips.
+// entries.
 bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 {
     const int64_t nnz = row_ptr[M];

@@ -38,9 +38,10 @@ struct StripSizes {
 struct StripPlan : StripSizes {
     static constexpr int KNOWN = 64;
     uint32_t groups[KNOWN + 1] = {};  // of units, for that many strips (strip_time)
-    uint32_t *d_stream = nullptr;  // DEVICE groups
-    uint32_t *d_units = nullptr;   // DEVICE per unit and band: first group, groups
-    uint32_t *d_rows = nullptr;    // DEVICE per unit and lane: row | log2(P) << 28, or STRIP_NO_ROW
+    uint32_t *d_stream = nullptr;  // DEVICE groups, in the same memory behind
+    // DEVICE per unit and band: first group, groups; behind them per unit and lane: row | log2(P) << 28, or STRIP_NO_ROW
+    uint32_t *d_units = nullptr;  // (as many words as strips::unit_words, a multiple of 256 bytes)
+    const uint32_t *d_rows() const { return d_units + n_units * bands * 2; }
 };
 constexpr uint32_t STRIP_NO_ROW = 0xFFFFFFFFu;
 constexpr int STRIP_PARTS_SHIFT = 28;

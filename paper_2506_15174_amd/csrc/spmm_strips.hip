@@ -3,8 +3,11 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <vector>
 
-#include "spmm_strips.h"
+#include "spmm_strips_build.h"
+#include "spmm_tiles.h"
+#include "spmm_upload.h"
 
 namespace {
 
@@ -236,6 +239,404 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     }
 }
 
+// ---------------------------------------------------------------- builder
+//
+// The same units, order and bytes as the builder on the host makes (spmm_strips_build.h says why that order): the rows' entries band by
+// band and class by class (class_kernel), then every unit in a band by a wave of its own, lane by lane what the host's loops do one
+// after the other (order_kernel).  Plan and product, 4096 x 4096, 80 % pruned, 64 columns (20 MB, of which the upload is
+// 0.5 ms): 0.85 ms, built on the host 7.1; 95 % pruned, 128 columns 0.59 and 3.6, on chunks 3.1.  Working memory is ten bytes an entry at most: with 16 its
+// allocation and release took 0.1 ms and 0.25 longer.
+
+struct build_args {
+    const int32_t *row_ptr;
+    const float *vals;
+    uint32_t *sorted;   // place in the band | number in the row << 16: the entries, a row's band by band and class by class
+    uint32_t *classes;  // per row and band: entries; how many before its classes 1 .. 7
+    uint32_t *flags;    // BAD_*
+    uint32_t *units;
+    uint32_t *rows;
+    const uint32_t *order;  // the rows, longest first
+    const u32x4 *list;      // the units
+    char *stream;
+    int64_t M;
+    uint32_t nnz;
+    int32_t K, bands, band_rows;
+};
+constexpr uint32_t NOTHING = ~0u;  // instead of an entry (its place is below the rows of a band)
+constexpr uint32_t BAD_COLUMN = 1, BAD_ORDER = 2, BAD_LENGTH = 4;
+
+// One wave per row.
+template <typename Col> __global__ __launch_bounds__(256) void class_kernel(const build_args args, const Col *col_idx)
+{
+    const int64_t row = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t lane = threadIdx.x & 63;
+    if (row >= args.M) return;
+    const int32_t first = args.row_ptr[row], end = args.row_ptr[row + 1];
+    uint32_t bad = 0;
+    for (int32_t band = 0, at = first; band < args.bands; ++band) {
+        int32_t stop = end;
+        if (band + 1 < args.bands) {  // the first entry beyond the band
+            int32_t low = at;
+            while (low < stop) {
+                const int32_t middle = low + (stop - low) / 2;
+                if ((int64_t)col_idx[middle] < (int64_t)(band + 1) * args.band_rows) low = middle + 1;
+                else stop = middle;
+            }
+        }
+        uint32_t n[8] = {};
+        for (uint32_t q0 = (uint32_t)at; q0 < (uint32_t)stop; q0 += 64) {
+            const uint32_t q = q0 + lane;
+            const bool in = q < (uint32_t)stop;
+            const int32_t c = in ? (int32_t)col_idx[q] : 0;
+            if (in && (uint32_t)c >= (uint32_t)args.K) bad |= BAD_COLUMN;
+            if (in && q > (uint32_t)first && (int32_t)col_idx[q - 1] > c) bad |= BAD_ORDER;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) n[k] += (uint32_t)__popcll(__ballot(in && (c & 7) == k));
+        }
+        uint32_t before[8];
+        before[0] = 0;
+#pragma unroll
+        for (int k = 1; k < 8; ++k) before[k] = before[k - 1] + n[k - 1];
+        if (lane < 8) {
+            uint32_t word = (uint32_t)(stop - at);
+#pragma unroll
+            for (int k = 1; k < 8; ++k) word = lane == (uint32_t)k ? before[k] : word;
+            args.classes[((size_t)row * (uint32_t)args.bands + (uint32_t)band) * 8 + lane] = word;
+        }
+        for (uint32_t q0 = (uint32_t)at; q0 < (uint32_t)stop; q0 += 64) {
+            const uint32_t q = q0 + lane;
+            const bool in = q < (uint32_t)stop;
+            const int32_t c = in ? (int32_t)col_idx[q] : 0;
+            uint32_t to = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const uint64_t them = __ballot(in && (c & 7) == k);
+                if ((c & 7) == k) to = before[k] + (uint32_t)__popcll(them & ((1ull << lane) - 1ull));
+                before[k] += (uint32_t)__popcll(them);
+            }
+            if (in) args.sorted[(size_t)at + to] = ((uint32_t)(c - band * args.band_rows) & 0xFFFFu) | (q - (uint32_t)first) << 16;
+        }
+        at = stop;
+    }
+    if (bad) atomicOr(args.flags, bad);
+}
+
+// One wave per unit: the rows of its lanes, and its groups, in bands as many as its rows need there.
+__global__ __launch_bounds__(64) void unit_kernel(const build_args args)
+{
+    const uint32_t unit = blockIdx.x, lane = threadIdx.x;
+    const u32x4 u = args.list[unit];  // first row in the order, log2 of the parts, first group, groups
+    const uint64_t at = (uint64_t)u[0] + (lane >> u[1]);
+    const uint32_t row = at < (uint64_t)args.M ? args.order[at] : STRIP_NO_ROW;
+    args.rows[(size_t)unit * 64 + lane] = row == STRIP_NO_ROW ? row : row | u[1] << STRIP_PARTS_SHIFT;
+    uint32_t *to = args.units + (size_t)unit * (uint32_t)args.bands * 2;
+    if (args.bands == 1) {
+        if (lane < 2) to[lane] = lane == 0 ? u[2] : u[3];
+        return;
+    }
+    for (int32_t band = 0; band < args.bands; ++band) {
+        uint32_t n = 0;
+        if (row != STRIP_NO_ROW) n = args.classes[((size_t)row * (uint32_t)args.bands + (uint32_t)band) * 8];
+        uint32_t groups = (((n + (1u << u[1]) - 1u) >> u[1]) + STRIP_STEPS - 1) / STRIP_STEPS;
+        for (int m = 1; m < 64; m *= 2) groups = max(groups, (uint32_t)__shfl_xor((int)groups, m));
+        if (lane == 0) {
+            to[band * 2 + 1] = groups;
+            if (groups > (uint32_t)strips::MOST_GROUPS) atomicOr(args.flags, BAD_LENGTH);
+        }
+    }
+}
+
+// One workgroup: where the groups of every unit in a band begin; how many there are.
+__global__ __launch_bounds__(1024) void begin_kernel(uint32_t *units, uint32_t n, uint64_t *total)
+{
+    __shared__ uint64_t sums[1024];
+    const uint32_t share = (n + 1023) / 1024, first = min(n, threadIdx.x * share), end = min(n, first + share);
+    uint64_t sum = 0;
+    for (uint32_t k = first; k < end; ++k) sum += units[(size_t)k * 2 + 1];
+    sums[threadIdx.x] = sum;
+    __syncthreads();
+    for (uint32_t m = 1; m < 1024; m *= 2) {
+        const uint64_t more = threadIdx.x >= m ? sums[threadIdx.x - m] : 0;
+        __syncthreads();
+        sums[threadIdx.x] += more;
+        __syncthreads();
+    }
+    uint64_t at = sums[threadIdx.x] - sum;
+    for (uint32_t k = first; k < end; ++k) {
+        units[(size_t)k * 2] = (uint32_t)at;
+        at += units[(size_t)k * 2 + 1];
+    }
+    if (threadIdx.x == 1023) *total = sums[1023];
+}
+
+// One wave per unit in a band.  Eight threads next to each other are the lanes that must not collide; what they propose goes around
+// between them as a bit of a byte per turn.  Bound by the chain of a step's 300 instructions: 4096 x 4096, 80 % pruned, 104 steps, 78 us (with
+// eight turns of one lane each and a shuffle 260).  The entries are loaded behind the choices, and written a group later.
+__global__ __launch_bounds__(64) void order_kernel(const build_args args)
+{
+    const uint32_t unit = blockIdx.x / (uint32_t)args.bands, band = blockIdx.x % (uint32_t)args.bands;
+    const uint32_t i = threadIdx.x & 7, set = threadIdx.x >> 3, j = 2 * i + (set & 1);
+    const uint32_t lane = (set >> 2) * 32 + ((set & 2 ? 0x7421u : 0x6530u) >> (j / 4 * 4) & 15u) * 4 + j % 4;  // strip_lane(set / 2, i, set % 2)
+    const uint32_t word = args.rows[(size_t)unit * 64 + lane], log2 = args.rows[(size_t)unit * 64] >> STRIP_PARTS_SHIFT, x = lane & ((1u << log2) - 1u);
+    const uint32_t first = args.units[(size_t)blockIdx.x * 2], groups = args.units[(size_t)blockIdx.x * 2 + 1];
+    uint32_t at[9] = {}, begin = 0, row_begin = 0;  // of the row's entries in the band: how many before a class; the first; the row's first
+    if (word != STRIP_NO_ROW) {
+        const uint32_t row = word & ((1u << STRIP_PARTS_SHIFT) - 1u);
+        const uint32_t *words = args.classes + (size_t)row * (uint32_t)args.bands * 8;
+        begin = row_begin = (uint32_t)args.row_ptr[row];
+        for (uint32_t b = 0; b < band; ++b) begin += words[b * 8];
+#pragma unroll
+        for (int c = 1; c < 8; ++c) at[c] = words[band * 8 + c];
+        at[8] = words[band * 8];
+    }
+    // the lane has those of them whose number modulo the row's parts is x
+    auto mine = [&](uint32_t n) { return (int32_t)((n + (1u << log2) - 1u - x) >> log2); };
+    int32_t next[8], count[8], most = 0;
+    uint32_t has = 0, rich = 0, above = 0;
+    auto sum_of_all = [](int32_t v) {  // over the eight
+        v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
+        return v + __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
+    };
+    auto of_all = [](uint32_t v) {
+        v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, true);
+        v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, true);
+        return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);
+    };
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        next[c] = mine(at[c]);
+        count[c] = mine(at[c + 1]) - next[c];
+        has |= (uint32_t)(count[c] > 0) << c;
+        const int32_t sum = sum_of_all(count[c]);
+        most = max(most, max(sum, __shfl_xor(sum, 8)));
+    }
+    int32_t left = mine(at[8]);
+    const int32_t steps = (int32_t)(groups * STRIP_STEPS), extra = max(0, most - steps);
+    int32_t part = 0;  // (t + 1) * extra modulo steps
+    auto weigh = [&] {  // once a group
+        const int32_t all = sum_of_all(left) / 8, own = left / 8;
+        rich = above = 0;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            rich |= (uint32_t)(count[c] > own) << c;
+            above |= (uint32_t)(sum_of_all(count[c]) > all) << c;
+        }
+    };
+    auto choose = [&](int32_t t) {  // place of the entry that the lane takes in step t
+        bool twice = extra >= steps;
+        if (!twice) {
+            part += extra;
+            twice = part >= steps;
+            part -= twice ? steps : 0;
+        }
+        const uint32_t turn = (i - (uint32_t)t) & 7u, from = (i + (uint32_t)t) & 7u, shift = (turn & 3u) * 8u;
+        const uint32_t before_low = turn < 4 ? (1u << shift) - 1u : ~0u, before_high = turn < 4 ? 0u : (1u << shift) - 1u;
+        const bool waits = left < steps - t;
+        uint32_t take = has >> from & 1u ? from : 8u;  // 8: none
+        uint32_t once = of_all(take < 8 ? 1u << from : 0u), two = 0;
+#pragma unroll
+        for (int last = 0; last < 2; ++last) {
+            const uint32_t can = has & ~(twice ? two : once);
+            const bool idle = take < 8 || (can == 0 && (!last || waits));
+            const uint32_t of = can ? can : has, both = of & rich & above, one = of & rich ? of & rich : of & above;
+            const uint32_t best = both ? both : one ? one : of;
+            const uint32_t choice = (uint32_t)__builtin_ctz(best << 8 | (best >> from << from) | 0x10000u) & 7u;
+            const uint32_t bit = idle ? 0u : 1u << (choice + shift);
+            const uint32_t low = of_all(turn < 4 ? bit : 0u), high = of_all(turn < 4 ? 0u : bit);  // a byte per turn
+            auto fold = [](uint32_t l, uint32_t h, uint32_t &once, uint32_t &two) {               // classes in a byte, in two
+                once = l | h;
+                two = l & h;
+                two |= two >> 16 | (once & once >> 16);
+                once |= once >> 16;
+                two = (two | two >> 8 | (once & once >> 8)) & 255u;
+                once = (once | once >> 8) & 255u;
+            };
+            uint32_t earlier, earlier_two, all, all_two;
+            fold(low & before_low, high & before_high, earlier, earlier_two);
+            fold(low, high, all, all_two);
+            const uint32_t full = twice ? two | (once & earlier) | earlier_two : once | earlier;
+            if (!idle && (!(full >> choice & 1u) || (last && !waits))) take = choice;
+            two |= (once & all) | all_two;
+            once |= all;
+        }
+        uint32_t k = 0;
+        const uint32_t bit = 1u << take;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int32_t is = (int32_t)(bit >> c & 1u);
+            k = is ? (uint32_t)next[c] : k;
+            next[c] += is;
+            count[c] -= is;
+            has &= ~((uint32_t)(count[c] == 0) << c);
+        }
+        left -= take < 8;
+        return take < 8 ? begin + x + (k << log2) : NOTHING;
+    };
+    // A group is chosen and its entries fetched; a group later their values are, and it is written two groups later.
+    uint32_t taken[2][STRIP_STEPS];  // entries
+    f32x4 values[2];
+    u32x2 places[2];
+    char *out = args.stream + (size_t)first * STRIP_GROUP_BYTES;
+    auto group = [&](uint32_t g, int b) {
+        weigh();
+#pragma unroll
+        for (int k = 0; k < STRIP_STEPS; ++k) {
+            const uint32_t from = choose((int32_t)(g * STRIP_STEPS) + k);
+            taken[b][k] = from == NOTHING ? NOTHING : args.sorted[from];
+        }
+    };
+    auto fetch = [&](int b) {
+        uint32_t place[STRIP_STEPS];
+#pragma unroll
+        for (int k = 0; k < STRIP_STEPS; ++k) {
+            const bool none = taken[b][k] == NOTHING;
+            place[k] = none ? (uint32_t)args.band_rows : taken[b][k] & 0xFFFFu;
+            values[b][k] = none ? 0.0f : args.vals[row_begin + (taken[b][k] >> 16)];
+        }
+        places[b] = u32x2{place[0] | place[1] << 16, place[2] | place[3] << 16};
+    };
+    auto store = [&](uint32_t g, int b) {
+        *reinterpret_cast<f32x4 *>(out + (size_t)g * STRIP_GROUP_BYTES + lane * 16) = values[b];
+        *reinterpret_cast<u32x2 *>(out + (size_t)g * STRIP_GROUP_BYTES + 1024 + lane * 8) = places[b];
+    };
+    uint32_t g = 0;
+    for (; g + 1 < groups; g += 2) {
+        group(g, 0);
+        if (g > 0) {
+            fetch(1);
+            store(g - 2, 0);
+        }
+        group(g + 1, 1);
+        fetch(0);
+        if (g > 0) store(g - 1, 1);
+    }
+    // what is left, at most three groups; g is even
+    if (g < groups) group(g, 0);
+    if (g > 0) {
+        fetch(1);
+        store(g - 2, 0);
+        store(g - 1, 1);
+    }
+    if (g < groups) {
+        fetch(0);
+        store(g, 0);
+    }
+}
+
+hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, TilePlan &out, int &status)
+{
+    const int64_t nnz = row_ptr[M];
+    hipError_t e;
+#define TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
+    StripPlan &p = out.strips;
+    builder::workshop memory;
+    builder::uploader upload;  // (released before the memory)
+    const bool staged = upload.begin(K, col_idx, vals, nnz, memory.stream), narrow = staged && upload.narrow_columns();
+    strips::band_sizes(K, p);
+    const int64_t bands = p.bands;
+    if (M > ((int64_t)1 << 26) - 8) { status = TILES_NOT_POSSIBLE; return hipSuccess; }  // 256 threads per four rows
+    // (a unit has a row at least; the columns, and when they have been read the values in their place)
+    const size_t at_words = memory.reserve((size_t)M * 24 + 1024), at_entries = memory.reserve((size_t)nnz * 4), at_sorted = memory.reserve((size_t)nnz * 4), at_classes = memory.reserve((size_t)(M * bands) * 32);
+    TRY(memory.take());
+    const hipStream_t s = memory.stream;
+    int32_t *d_col = memory.at<int32_t>(at_entries);
+    uint32_t *d_words = memory.at<uint32_t>(at_words);
+    uint64_t *answer = reinterpret_cast<uint64_t *>(d_words);  // groups, flags
+    const size_t front = ((size_t)M + 5 + 63) / 64 * 64, list = ((size_t)M + 3) / 4 * 4;
+    build_args a{reinterpret_cast<const int32_t *>(d_words + 4), memory.at<float>(at_entries), memory.at<uint32_t>(at_sorted), memory.at<uint32_t>(at_classes), d_words + 2, nullptr, nullptr,
+                 d_words + front, reinterpret_cast<const u32x4 *>(d_words + front + list), nullptr, M, (uint32_t)nnz, (int32_t)K, p.bands, p.band_rows};
+    std::vector<uint32_t> words((size_t)M + 5, 0u);  // groups, flags, the row pointer
+    std::copy(row_ptr, row_ptr + M + 1, words.begin() + 4);
+    TRY(upload.copy_words(words, d_words));
+    if (staged) {
+        TRY(upload.copy(0, reinterpret_cast<char *>(d_col)));
+        if (upload.column_outside()) { status = 2; return hipSuccess; }
+    } else {
+        TRY(hipMemcpyWithStream(d_col, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice, s));
+    }
+    if (narrow) hipLaunchKernelGGL(class_kernel<uint16_t>, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, s, a, reinterpret_cast<const uint16_t *>(d_col));
+    else hipLaunchKernelGGL(class_kernel<int32_t>, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, s, a, d_col);
+    TRY(hipGetLastError());
+    if (staged) TRY(upload.copy(1, memory.at<char>(at_entries)));
+    else TRY(hipMemcpyWithStream(d_col, vals, (size_t)nnz * 4, hipMemcpyHostToDevice, s));
+    // ---- while the last values travel: the rows' order, and the units in four words each (unit_kernel)
+    const std::vector<uint32_t> order = strips::by_length(M, row_ptr);
+    const std::vector<strips::unit> units = strips::units_for(M, K, row_ptr, order, N, p);
+    const int64_t n_units = (int64_t)units.size(), places = n_units * bands;
+    const size_t n_words = strips::unit_words(n_units, bands);
+    const int32_t longest = row_ptr[order[0] + 1] - row_ptr[order[0]];
+    // an entry's number in its row in 16 bits; blocks of 64 threads
+    if (longest > 65535 || places >= (int64_t)1 << 26) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
+    words.assign(list + (size_t)n_units * 4, 0u);
+    std::copy(order.begin(), order.end(), words.begin());
+    uint64_t groups = 0;
+    uint32_t *to = words.data() + list;
+    for (const strips::unit &u : units) {
+        const int64_t n = bands == 1 ? u.steps / STRIP_STEPS : 0;
+        for (uint64_t w : {(uint64_t)u.first, (uint64_t)u.parts_log2, groups, (uint64_t)n}) *to++ = (uint32_t)w;
+        groups += (uint64_t)n;
+    }
+    TRY(upload.copy_words(words, d_words + front));
+    // the plan's memory, once it is known how much; in bands the units wait in memory of their own
+    auto take_plan = [&]() -> hipError_t {
+        if (groups >= (1ull << 32)) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
+        const hipError_t failed = hipMalloc(reinterpret_cast<void **>(&p.d_units), n_words * 4 + (size_t)groups * STRIP_GROUP_BYTES);
+        if (failed != hipSuccess) return failed;
+        a.units = p.d_units;
+        p.d_stream = p.d_units + n_words;
+        a.stream = reinterpret_cast<char *>(p.d_stream);
+        return hipSuccess;
+    };
+    struct two_words {
+        uint32_t *p = nullptr;
+        hipStream_t s;
+        ~two_words()
+        {
+            if (p) (void)hipFreeAsync(p, s);
+        }
+    } waiting;
+    waiting.s = s;
+    if (bands == 1) {
+        TRY(take_plan());
+        if (status) return hipSuccess;
+    } else {
+        TRY(hipMallocAsync(reinterpret_cast<void **>(&waiting.p), n_words * 4, s));
+        a.units = waiting.p;
+    }
+    a.rows = a.units + places * 2;
+    hipLaunchKernelGGL(unit_kernel, dim3((unsigned)n_units), dim3(64), 0, s, a);
+    TRY(hipGetLastError());
+    uint64_t got[2];
+    if (bands > 1) {
+        hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1024), 0, s, a.units, (uint32_t)places, answer);
+        TRY(hipGetLastError());
+        TRY(hipMemcpyWithStream(got, answer, 16, hipMemcpyDeviceToHost, s));
+        groups = got[0];
+        if (got[1]) { status = got[1] & BAD_COLUMN ? 2 : TILES_NOT_POSSIBLE; return hipSuccess; }
+        TRY(take_plan());
+        if (status) return hipSuccess;
+        TRY(hipMemcpyAsync(a.units, waiting.p, n_words * 4, hipMemcpyDeviceToDevice, s));
+        a.rows = a.units + places * 2;
+    }
+    hipLaunchKernelGGL(order_kernel, dim3((unsigned)places), dim3(64), 0, s, a);
+    TRY(hipGetLastError());
+    TRY(hipMemcpyWithStream(got, answer, 16, hipMemcpyDeviceToHost, s));
+    if (got[1]) { status = got[1] & BAD_COLUMN ? 2 : TILES_NOT_POSSIBLE; return hipSuccess; }
+    TRY(memory.give_back());
+    TRY(hipStreamSynchronize(s));
+    upload.arrived();
+#undef TRY
+    p.n_units = n_units;
+    p.steps = (int64_t)groups * STRIP_STEPS;
+    strips::launches(p, K);
+    out.device_bytes = (int64_t)((size_t)groups * STRIP_GROUP_BYTES + n_words * 4);
+    out.built = true;
+    builder::staging.count_plan(1);
+    status = 0;
+    return hipSuccess;
+}
+
 }  // namespace
 
 int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N, float *C, void *stream)
@@ -244,7 +645,7 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
     int64_t groups = 0;
     if (strips <= StripPlan::KNOWN) groups = p.groups[strips];
     else strip_time(p, K, N, &groups);
-    strip_args a{reinterpret_cast<const char *>(p.d_stream), reinterpret_cast<const u32x2 *>(p.d_units), p.d_rows, B, C, (uint64_t)K * (uint64_t)N * 4u, 0, 0,
+    strip_args a{reinterpret_cast<const char *>(p.d_stream), reinterpret_cast<const u32x2 *>(p.d_units), p.d_rows(), B, C, (uint64_t)K * (uint64_t)N * 4u, 0, 0,
                  (int32_t)K, N, p.bands, p.band_rows, (uint32_t)p.n_units, (uint32_t)groups, (uint32_t)strips};
     a.n_places = (uint64_t)a.n_groups * a.n_strips;
     const bool wide = (uint64_t)N * 4u * 32u >= (1ull << 32);
@@ -258,4 +659,17 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * STRIP_WAVES), (unsigned)(p.band_rows + 1) * STRIP_ROW_BYTES, (hipStream_t)stream, a);
     }
     return (int)hipGetLastError();
+}
+
+int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, TilePlan &out)
+{
+    out = TilePlan();
+    int status = 0;
+    const hipError_t e = build(M, K, row_ptr, col_idx, vals, N, out, status);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        status = e == hipErrorOutOfMemory ? 3 : 4;
+    }
+    if (status != 0) spmm_tiles_release(out);
+    return status;
 }

@@ -1,4 +1,4 @@
-// Host builder of the strips path (format: spmm_strips.h).  Included by spmm_plan.cpp.
+// Host builder of the strips path (format: spmm_strips.h); the one on the device (spmm_strips.hip) takes its units.
 #ifndef SPMM_STRIPS_BUILD_H
 #define SPMM_STRIPS_BUILD_H
 
@@ -119,6 +119,18 @@ inline StripSizes sizes(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_
     return p;
 }
 
+// Words of the units and rows, in front of the groups.
+inline size_t unit_words(int64_t n_units, int64_t bands) { return ((size_t)(n_units * bands) * 2 + (size_t)n_units * 64 + 63) / 64 * 64; }
+
+inline void launches(StripPlan &p, int64_t K)
+{
+    for (int64_t s = 1; s <= StripPlan::KNOWN; ++s) {
+        int64_t g = 0;
+        strip_time(p, K, s * STRIP_COLS, &g);
+        p.groups[s] = (uint32_t)g;
+    }
+}
+
 struct host {
     StripPlan plan;  // without device memory
     raw_words stream;
@@ -191,25 +203,50 @@ template <typename Row> void fill(const unit &u, int64_t n_rows, Row row_range, 
                 }
             }
             int32_t *sum = total[odd];
+            uint32_t rich[8] = {}, above = 0;
             for (int32_t t = 0; t < steps; ++t) {
                 const bool twice = extra >= steps || (int64_t)(t + 1) * extra / steps > (int64_t)t * extra / steps;
-                uint32_t once = 0, used = 0;
-                int take[8];
-                // the class of most entries that are left, of those that no other lane took (or only one, in some steps)
-                for (int k = 0; k < 8; ++k) {
-                    const int i = (t + k) & 7, l = lanes[i];
-                    take[i] = -1;
-                    uint32_t can = has[i] & ~used;
-                    if (!can) {
-                        if (left[l] < steps - t) continue;  // it waits (or has none)
-                        can = has[i];                       // it collides
+                if (t % STRIP_STEPS == 0) {  // classes of which a lane, all lanes hold more than of others
+                    int32_t all = 0;
+                    for (int c = 0; c < 8; ++c) all += sum[c];
+                    above = 0;
+                    for (int c = 0; c < 8; ++c) above |= (uint32_t)(sum[c] > all / 8) << c;
+                    for (int i = 0; i < 8; ++i) {
+                        rich[i] = 0;
+                        for (int c = 0; c < 8; ++c) rich[i] |= (uint32_t)(count[lanes[i]][c] > left[lanes[i]] / 8) << c;
                     }
-                    int32_t most_left = 0;
-                    for (int c = 0; c < 8; ++c) most_left = std::max(most_left, ((8 * count[l][c] + sum[c]) * 8 + c) & -(int32_t)(can >> c & 1));
-                    const int best = most_left & 7;
-                    take[i] = best;
-                    if (twice && !(once >> best & 1)) once |= 1u << best;
-                    else used |= 1u << best;
+                }
+                // Lane i takes class t + i if it has one.  Of the others each proposes a class, of those that are left and that it holds more of
+                // if there is one, and of those that propose the same the first has it (in some steps: two have it); then once more.
+                uint32_t once = 0, two = 0;  // classes that a lane took; that two did
+                int take[8];
+                for (int i = 0; i < 8; ++i) {
+                    const int c = (t + i) & 7;
+                    take[i] = has[i] >> c & 1 ? c : -1;
+                    if (take[i] >= 0) once |= 1u << c;
+                }
+                for (const bool last : {false, true}) {
+                    const uint32_t full = twice ? two : once;
+                    for (int k = 0; k < 8; ++k) {
+                        const int i = (t + k) & 7, from = (t + i) & 7;
+                        if (take[i] >= 0) continue;
+                        const bool waits = left[lanes[i]] < steps - t;  // it can (or it has none)
+                        uint32_t can = has[i] & ~full;
+                        if (!can) {
+                            if (!last || waits) continue;
+                            can = has[i];  // it collides
+                        }
+                        for (const uint32_t best : {rich[i] & above, rich[i], above})
+                            if (can & best) {
+                                can &= best;
+                                break;
+                            }
+                        const int c = __builtin_ctz(can << 8 | (can >> from << from)) & 7;  // the first from t + i on, around
+                        if ((twice ? two : once) >> c & 1 && !(last && !waits)) continue;
+                        take[i] = c;
+                        two |= once & 1u << c;
+                        once |= 1u << c;
+                    }
                 }
                 char *group = out + (size_t)(t / STRIP_STEPS) * STRIP_GROUP_BYTES;
                 const int e = t % STRIP_STEPS;
@@ -285,11 +322,7 @@ template <typename Over> bool build(int64_t M, int64_t K, const int32_t *row_ptr
     for (size_t k = 1; k < groups.size(); ++k) groups[k] += groups[k - 1];
     if (groups.back() >= (int64_t)1 << 32) return false;
     p.steps = groups.back() * STRIP_STEPS;
-    for (int64_t s = 1; s <= StripPlan::KNOWN; ++s) {
-        int64_t g = 0;
-        strip_time(p, K, s * STRIP_COLS, &g);
-        p.groups[s] = (uint32_t)g;
-    }
+    launches(p, K);
     for (int64_t k = 0; k < p.n_units * B; ++k) {
         out.units[(size_t)k * 2] = (uint32_t)groups[(size_t)k];
         out.units[(size_t)k * 2 + 1] = (uint32_t)(groups[(size_t)k + 1] - groups[(size_t)k]);

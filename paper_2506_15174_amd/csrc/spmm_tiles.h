@@ -39,10 +39,13 @@ constexpr int TILE_PLACE0 = 16;
 // checked; the columns are checked here.  Status codes follow spmm_status_t; TILES_NOT_POSSIBLE:
 // A cannot be stored this way (a column occurs twice in a row, more than 2^34 words of blocks, or
 // 2^26 rows or blocks and more: the builder's launches).
+// rows < 0: strips for products with -rows columns (TILES_NOT_POSSIBLE: a row's columns are not in order, or more units than a
+// launch takes, or steps than a plan).
 constexpr int TILES_NOT_POSSIBLE = -1;
 int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t rows,
                      TilePlan &out);
 void spmm_tiles_release(TilePlan &p);
+int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, TilePlan &out);
 
 // Estimated time of a product in us with panels of `rows` rows, and the column groups NB of a tile
 // (1, 2 or 4) it runs with.  density = share of the entries kept, peak = the largest such share of a panel.

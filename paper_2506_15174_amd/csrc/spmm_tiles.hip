@@ -4,16 +4,12 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cmath>
-#include <condition_variable>
 #include <cstring>
-#include <mutex>
-#include <thread>
 #include <type_traits>
-#include <vector>
 
 #include "spmm_tiles.h"
+#include "spmm_upload.h"
 
 namespace {
 
@@ -1183,263 +1179,14 @@ __global__ __launch_bounds__(256) void clear_kernel(u32x4 *p, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = u32x4{0, 0, 0, 0};
 }
 
-// The builder's working memory, in one piece (an allocation and its release cost 10 to 100 us each), and the
-// stream it works on.  The memory is ordered by that stream: hipFree would wait for the work of all streams
-// (4096 x 4096, 80 % pruned, with 100 ms of matrix products on another stream: created after 100 ms, now
-// after 43, its kernels between theirs).  The calling thread's own stream waits for the null stream as every
-// copy does, and there is none to create: a new one costs 0.15 ms of 1.3.
-struct workshop {
-    const hipStream_t stream = hipStreamPerThread;
-    char *base = nullptr;
-    size_t bytes = 0;
-    ~workshop()
-    {
-        if (base && give_back() == hipSuccess) (void)hipStreamSynchronize(stream);
-    }
-    size_t reserve(size_t n)
-    {
-        const size_t at = bytes;
-        bytes += (n + 255) & ~(size_t)255;
-        return at;
-    }
-    hipError_t take() { return hipMallocAsync(reinterpret_cast<void **>(&base), bytes, stream); }
-    // The device has the memory back after the stream's next synchronisation.
-    hipError_t give_back()
-    {
-        char *p = base;
-        base = nullptr;
-        return hipFreeAsync(p, stream);
-    }
-    template <typename T> T *at(size_t offset) const { return reinterpret_cast<T *>(base + offset); }
-};
-
-// Pinned memory through which the builder uploads large matrices: the device reads it at 54 GB/s, ordinary memory at 28
-// to 35.  Its first pages cost 0.1 ms per MiB once, and giving it back may wait for
-// all streams, which a creation must not.  So there is one piece of it for the process, lent to one creation at
-// a time (another one that runs meanwhile uploads from ordinary memory), and it goes back when the last plan on tiles
-// is released.  4096 x 4096, 80 % pruned (20 MB), plan and product: 0.90 ms where each plan is released before the next (0.84 if the memory stayed), 0.80 where one
-// lives, from ordinary memory 1.26; the first of a process (after a small plan) 1.95, from ordinary memory 2.2.  12 MiB in pieces of
-// 4: 0.88, 0.77 and 2.35 (8192 x 4096, 30 % kept: 1.9 instead of 2.0); 4 MiB in pieces of 1: 0.96, 0.85 and 1.7.
-struct staging_memory {
-    static constexpr size_t PIECE = 2u << 20, PIECES = 3;
-    std::mutex lock;
-    char *memory = nullptr;
-    bool lent = false;
-    int64_t plans = 0;  // on tiles, alive
-    char *lend()
-    {
-        const std::lock_guard<std::mutex> hold(lock);
-        if (lent) return nullptr;
-        if (!memory && hipHostMalloc(reinterpret_cast<void **>(&memory), PIECE * PIECES, hipHostMallocPortable) != hipSuccess) {
-            (void)hipGetLastError();
-            memory = nullptr;
-        }
-        lent = memory != nullptr;
-        return memory;
-    }
-    void take_back()  // (a creation that made a plan has counted it)
-    {
-        const std::lock_guard<std::mutex> hold(lock);
-        lent = false;
-        release_unused();
-    }
-    void count_plan(int64_t by)
-    {
-        const std::lock_guard<std::mutex> hold(lock);
-        plans += by;
-        release_unused();
-    }
-
-private:
-    void release_unused()
-    {
-        if (plans > 0 || lent || !memory) return;
-        (void)hipHostFree(memory);
-        memory = nullptr;
-    }
-} staging;
-
-// Copies from pinned memory, between the builder's kernels.  (With hipMemcpyAsync, whose engines and the kernels wait for each other,
-// the creation below takes 0.2 ms longer.)
-__global__ __launch_bounds__(256) void pull_kernel(const u32x4 *from, u32x4 *to, uint32_t n)
-{
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) to[i] = from[i];
-}
-
-// The columns and values on their way to the device.  Four threads and the caller fill the pinned memory, columns as 16-bit
-// numbers where those hold them, and check the columns; each piece is copied when it is full, while the next ones
-// are filled.  (4096 x 4096, 80 % pruned: 20 MB; the plan is made in 0.7 ms, with 27 MB from ordinary memory in 1.1.)
-class uploader {
-public:
-    bool begin(int64_t K, const int32_t *col_idx, const float *vals, int64_t nnz, hipStream_t s)
-    {
-        if (nnz < (1 << 19)) return false;  // 4 MB: nothing to gain
-        size_t n_pieces = 0;
-        narrow = K <= 65536;
-        entry_bytes[0] = narrow ? 2 : 4;
-        for (int kind = 0; kind < 2; ++kind) {
-            const size_t most = staging_memory::PIECE / entry_bytes[kind];
-            for (size_t at = 0; at < (size_t)nnz; at += most) pieces.push_back(piece{kind, at, std::min(most, (size_t)nnz - at)});
-            if (kind == 0) column_pieces = pieces.size();
-        }
-        n_pieces = pieces.size();
-        left = std::vector<std::atomic<int>>(n_pieces);
-        for (size_t i = 0; i < n_pieces; ++i) left[i] = (int)parts(pieces[i]);
-        for (hipEvent_t &e : copied)
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-                (void)hipGetLastError();
-                e = nullptr;
-                return false;
-            }
-        pinned = staging.lend();
-        if (!pinned) return false;
-        stream = s;
-        columns = reinterpret_cast<const uint32_t *>(col_idx);
-        values = vals;
-        limit = (uint32_t)K;
-        for (int t = 0; t < 4; ++t) {
-            try {
-                helpers.emplace_back([this] { help(); });
-            } catch (...) {
-                break;  // the caller fills what is left
-            }
-        }
-        return true;
-    }
-    bool narrow_columns() const { return narrow; }
-    // Copies the columns (kind 0) or the values (1) to `to`, whose size is a multiple of 16 bytes.
-    hipError_t copy(int kind, char *to)
-    {
-        for (; next < (kind == 0 ? column_pieces : pieces.size()); ++next) {
-            const piece &p = pieces[next];
-            while (left[next].load(std::memory_order_acquire) > 0) {
-                const size_t oldest = usable.load() - staging_memory::PIECES;  // piece in the place that is wanted next
-                if (oldest < next && usable.load() < pieces.size()) {
-                    const hipError_t e = hipEventQuery(copied[oldest % staging_memory::PIECES]);
-                    if (e == hipSuccess) one_more_usable();
-                    else if (e != hipErrorNotReady) return e;
-                    else (void)hipGetLastError();
-                }
-                if (!fill_part()) std::this_thread::yield();
-            }
-            hipLaunchKernelGGL(pull_kernel, dim3(128), dim3(256), 0, stream, reinterpret_cast<const u32x4 *>(place(next)),
-                               reinterpret_cast<u32x4 *>(to + p.first * entry_bytes[kind]), (uint32_t)((p.count * entry_bytes[kind] + 15) / 16));
-            const hipError_t e = hipEventRecord(copied[next % staging_memory::PIECES], stream);
-            if (e != hipSuccess) return e;
-        }
-        return hipSuccess;
-    }
-    bool column_outside() const { return outside.load(); }  // after the columns' copies
-    void arrived() { next = 0; }                             // the stream has been waited for
-    ~uploader()
-    {
-        {
-            const std::lock_guard<std::mutex> hold(lock);
-            stop.store(true);
-        }
-        changed.notify_all();
-        for (std::thread &t : helpers) t.join();
-        if (pinned) {
-            if (next > 0) (void)hipStreamSynchronize(stream);
-            staging.take_back();
-        }
-        for (hipEvent_t e : copied)
-            if (e) (void)hipEventDestroy(e);
-    }
-
-private:
-    struct piece {
-        int kind;
-        size_t first, count;  // entries
-    };
-    static constexpr size_t PART = 32u << 10;  // entries that a thread takes at a time
-    static size_t parts(const piece &p) { return (p.count + PART - 1) / PART; }
-    char *place(size_t i) const { return pinned + i % staging_memory::PIECES * staging_memory::PIECE; }
-    void help()
-    {
-        while (!stop.load()) {
-            if (fill_part()) continue;
-            std::unique_lock<std::mutex> hold(lock);
-            changed.wait(hold, [this] { return stop.load() || fill_piece.load() == pieces.size() || fill_piece.load() < usable.load(); });
-            if (fill_piece.load() == pieces.size()) return;
-        }
-    }
-    void one_more_usable()
-    {
-        {
-            const std::lock_guard<std::mutex> hold(lock);
-            usable.fetch_add(1);
-        }
-        changed.notify_all();
-    }
-    // Fills one part; false if there is none, or no place for it yet.
-    bool fill_part()
-    {
-        size_t i, k;
-        {
-            const std::lock_guard<std::mutex> hold(lock);
-            i = fill_piece.load();
-            if (i == pieces.size() || i >= usable.load()) return false;
-            k = next_part++;
-            if (next_part == parts(pieces[i])) {
-                next_part = 0;
-                fill_piece.store(i + 1);
-                if (i + 1 == pieces.size()) changed.notify_all();
-            }
-        }
-        const piece &p = pieces[i];
-        const size_t at = k * PART, n = std::min(PART, p.count - at);
-        char *to = place(i) + at * entry_bytes[p.kind];
-        if (p.kind == 1) {
-            std::memcpy(to, values + p.first + at, n * 4);
-        } else {
-            const uint32_t *from = columns + p.first + at;
-            uint32_t beyond = 0;
-            if (narrow) {
-                uint16_t *out = reinterpret_cast<uint16_t *>(to);
-                for (size_t x = 0; x < n; ++x) {
-                    out[x] = (uint16_t)from[x];
-                    beyond |= (uint32_t)(from[x] >= limit);
-                }
-            } else {
-                uint32_t *out = reinterpret_cast<uint32_t *>(to);
-                for (size_t x = 0; x < n; ++x) {
-                    out[x] = from[x];
-                    beyond |= (uint32_t)(from[x] >= limit);
-                }
-            }
-            if (beyond) outside.store(true);
-        }
-        left[i].fetch_sub(1, std::memory_order_release);
-        return true;
-    }
-
-    char *pinned = nullptr;
-    hipStream_t stream = nullptr;
-    hipEvent_t copied[staging_memory::PIECES] = {};  // the copy from each place
-    const uint32_t *columns = nullptr;
-    const float *values = nullptr;
-    uint32_t limit = 0;
-    bool narrow = false;
-    size_t entry_bytes[2] = {4, 4};
-    std::vector<piece> pieces;
-    std::vector<std::atomic<int>> left;  // parts of each piece that are still to be filled
-    size_t column_pieces = 0, next = 0, next_part = 0;
-    std::mutex lock;
-    std::condition_variable changed;  // fill_piece, usable or stop, for helpers that have nothing to fill
-    std::atomic<size_t> fill_piece{0}, usable{staging_memory::PIECES};  // pieces below have a place in the memory
-    std::atomic<bool> outside{false}, stop{false};
-    std::vector<std::thread> helpers;
-};
-
 template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, TilePlan &out, int &status)
 {
     const int64_t nnz = row_ptr[M], P = out.n_panels, S = out.n_steps;
     const size_t mask_bytes = (size_t)(P * S) * MASK_WORDS * 4;
     hipError_t e;
 #define TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-    workshop memory;
-    uploader upload;  // (released before the memory)
+    builder::workshop memory;
+    builder::uploader upload;  // (released before the memory)
     const bool staged = upload.begin(K, col_idx, vals, nnz, memory.stream), narrow = staged && upload.narrow_columns();
     const size_t at_ptr = memory.reserve((size_t)(M + 1) * 4), at_col = memory.reserve((size_t)nnz * 4), at_val = memory.reserve((size_t)nnz * 4),
                  at_base = memory.reserve((size_t)(P + 3) * 8), at_masks = memory.reserve(mask_bytes),
@@ -1513,7 +1260,7 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
 #undef TRY
     out.device_bytes = out.stream_words * 4 + P * (S + 1) * 4;
     out.built = true;
-    staging.count_plan(1);
+    builder::staging.count_plan(1);
     status = 0;
     return hipSuccess;
 }
@@ -1523,6 +1270,7 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
 int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t rows, TilePlan &out)
 {
     out = TilePlan();
+    if (rows < 0) return spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, -rows, out);
     out.rows = rows;
     const int64_t step = TILE_OPERANDS * 64 / rows;
     out.n_panels = (M + rows - 1) / rows;
@@ -1548,7 +1296,8 @@ void spmm_tiles_release(TilePlan &p)
 {
     if (p.d_stream) (void)hipFree(p.d_stream);
     if (p.d_offsets) (void)hipFree(p.d_offsets);
-    if (p.built) staging.count_plan(-1);
+    if (p.strips.d_units) (void)hipFree(p.strips.d_units);
+    if (p.built) builder::staging.count_plan(-1);
     p = TilePlan();
 }
 

@@ -53,21 +53,32 @@ def test_against_the_oracle(torch_gpu, oracle, make, M, K, sparsity, N):  # noqa
     assert np.array_equal(C, C2)
 
 
-def test_unsorted_columns_duplicates_empty_rows_and_bad_columns(torch_gpu, oracle):  # noqa: F811
-    """The order of a row's entries does not matter, bit for bit; duplicates are summed; a column outside A is refused."""
+@pytest.mark.parametrize("make,M,K,sparsity,hint", [(gen.lognormal_rows, 300, 6000, 0.97, 40), (gen.zipf_rows, 1000, 700, 0.8, 0), (gen.zipf_rows, 5, 12000, 0.6, 8),
+                                                    (gen.uniform_positions, 3000, 1000, 0.75, 200), (gen.lognormal_rows, 700, 9001, 0.9, 16)])
+def test_the_builders_on_the_device_and_on_the_host_agree(torch_gpu, make, M, K, sparsity, hint):  # noqa: F811
+    """The order of a row's entries does not matter, bit for bit: where they are in order of the columns, the strips
+    are built on the device, else on the host."""
     rng = np.random.default_rng(8)
-    csr = gen.lognormal_rows(300, 6000, 0.97, 9)
+    csr = make(M, K, sparsity, 9)
     order = np.concatenate([rng.permutation(np.arange(a, b)) for a, b in zip(csr.row_ptr[:-1], csr.row_ptr[1:])])
-    B = gen.dense_activations(csr.K, 40, 10)
-    C0, _ = gpu_product(torch_gpu, csr, B, strips=1)
-    C1, _ = gpu_product(torch_gpu, gen.Csr(csr.M, csr.K, csr.row_ptr, csr.col_idx[order], csr.vals[order]), B, strips=1)
-    assert np.array_equal(C0, C1)
+    B = gen.dense_activations(K, 40, 10)
+    C0, one = gpu_product(torch_gpu, csr, B, strips=1, n_hint=hint)
+    C1, two = gpu_product(torch_gpu, gen.Csr(M, K, csr.row_ptr, csr.col_idx[order], csr.vals[order]), B, strips=1, n_hint=hint)
+    assert np.array_equal(C0, C1) and one.describe() == two.describe()
+
+
+def test_duplicates_empty_rows_and_bad_columns(torch_gpu, oracle):  # noqa: F811
+    """Duplicates are summed, in any order and side by side; a column outside A is refused."""
+    rng = np.random.default_rng(8)
+    B = gen.dense_activations(300, 40, 10)
     lens = rng.integers(0, 90, 200)
     lens[::7] = 0
     row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     csr = gen.Csr(200, 300, row_ptr, rng.integers(0, 300, row_ptr[-1]).astype(np.int32), rng.standard_normal(row_ptr[-1]).astype(np.float32))
-    C, _ = gpu_product(torch_gpu, csr, B[:300], guard_rows=1, strips=1)
-    check(oracle, csr, B[:300], C)
+    in_order = np.concatenate([np.sort(csr.col_idx[a:b]) for a, b in zip(row_ptr[:-1], row_ptr[1:])])
+    for a in (csr, gen.Csr(200, 300, row_ptr, in_order, csr.vals)):
+        C, _ = gpu_product(torch_gpu, a, B, guard_rows=1, strips=1)
+        check(oracle, a, B, C)
     for bad in (-1, 300):
         col = csr.col_idx.copy()
         col[-1] = bad
