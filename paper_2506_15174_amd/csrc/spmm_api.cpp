@@ -194,26 +194,34 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
     strips::host strips;
     bool use_strips = opts.strips > 0 && tiles <= 0;
     if (use_strips && (schedule_forced || host_only)) return SPMM_ERR_INVALID_ARG;
-    if (!host_only && tiles >= 0 && (tiles > 0 || !schedule_forced) && row_pointer_ok(M, K, row_ptr, col_idx, vals)) {
-        if (tiles == 0 && !use_strips) {
-            tiles = choose_tiles(M, K, row_ptr, io.n_hint);
-            use_strips = opts.strips == 0 && tiles == 0 && choose_strips(M, K, row_ptr, io.n_hint);
-        }
-        if (tiles > 0) {
-            rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
-            // the chunk plan needs no memory beside its own, the builder of tiles a multiple of its result's
-            if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) rc = 0;
-            io.schedule_only = p->tiles.rows > 0;
+    const bool checked = row_pointer_ok(M, K, row_ptr, col_idx, vals);
+    strips::start begun;
+    int32_t instead = 0;  // tiles that strips take the place of
+    if (!host_only && tiles == 0 && !use_strips && !schedule_forced && checked) {
+        tiles = choose_tiles(M, K, row_ptr, io.n_hint);
+        if (opts.strips == 0 && choose_strips(M, K, row_ptr, io.n_hint, tiles, begun)) {
+            if (begun.sizes.n_units > 0) p->tiles.begun = &begun;
+            use_strips = true;
+            instead = tiles;
+            tiles = 0;
         }
     }
-    if (use_strips && row_pointer_ok(M, K, row_ptr, col_idx, vals) && row_ptr[M] > 0) {
-        rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, -(io.n_hint > 0 ? io.n_hint : (int32_t)strips::UNKNOWN_COLUMNS), p->tiles);
+    if (use_strips && checked && row_ptr[M] > 0) {
+        rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, -(int32_t)strips::columns_for(io.n_hint), p->tiles);
         if (rc == 0 && p->tiles.strips.n_units == 0) rc = TILES_NOT_POSSIBLE;
         if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
             spmm_tiles_release(p->tiles);
-            rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, strips);
+            rc = 0;
+            if (instead > 0) tiles = instead;  // which the device builds from rows in any order
+            else rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, strips);
         }
         io.schedule_only = rc == 0 && (strips.plan.n_units > 0 || p->tiles.strips.n_units > 0);
+    }
+    if (rc == 0 && !host_only && tiles > 0 && checked) {
+        rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
+        // the chunk plan needs no memory beside its own, the builder of tiles a multiple of its result's
+        if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) rc = 0;
+        io.schedule_only = p->tiles.rows > 0;
     }
     if (rc == 0) rc = spmm_inspect(M, K, row_ptr, col_idx, vals, io, p->host);
     if (rc != 0) return (spmm_status_t)rc;

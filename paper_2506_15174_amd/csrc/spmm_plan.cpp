@@ -550,6 +550,15 @@ double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_
     }
 }
 
+// Estimated time in us on tiles of r rows, and the operands NB that one is wide.
+static double tiles_time(int r, int64_t M, int64_t K, const int32_t *row_ptr, int64_t N, int *NB)
+{
+    const double density = (double)row_ptr[M] / ((double)M * (double)K);
+    int64_t heaviest = 0;
+    for (int64_t i = 0; i < M; i += r) heaviest = std::max<int64_t>(heaviest, row_ptr[std::min<int64_t>(M, i + r)] - row_ptr[i]);
+    return spmm_tiles_time(r, M, K, N, density, std::max(density, (double)heaviest / ((double)r * (double)K)), NB);
+}
+
 int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 {
     const int64_t nnz = row_ptr[M];
@@ -561,10 +570,7 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     int rows = 0;
     for (int r : {8, 16, 32}) {
         if (r == 8 && N > 64) continue;  // its tiles are 16 columns wide: too small a part of every row of B
-        int64_t heaviest = 0;
-        for (int64_t i = 0; i < M; i += r) heaviest = std::max<int64_t>(heaviest, row_ptr[std::min<int64_t>(M, i + r)] - row_ptr[i]);
-        const double peak = std::max(density, (double)heaviest / ((double)r * (double)K));
-        const double t = spmm_tiles_time(r, M, K, (int64_t)N, density, peak, nullptr);
+        const double t = tiles_time(r, M, K, row_ptr, (int64_t)N, nullptr);
         if (t < best) {
             best = t;
             rows = r;
@@ -573,26 +579,43 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     return rows;
 }
 
-// Strips take the place of chunks where they are estimated to be faster, without a hint at each of three widths.  Of 420 random
-// products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256 columns) that moves 145 from chunks, 1.60
-// times as fast on average, 0.96 at worst, with 0.7 of the error against 64 bits; 42 others would be 1.19 times as fast, 26 of them below 2^17
-// entries.
-bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
+// Strips take the place of the chunks or the tiles (`rows` a panel) that would be chosen where they are estimated to be faster, without a hint
+// at each of three widths.  Of 1400 random products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256
+// columns, one in three without a hint):
+//   145 of 319 on chunks, 1.60 times as fast on average, 0.96 at worst, with 0.7 of the error against 64 bits; 42 others would be 1.19
+//       times as fast, 26 of them below 2^17 entries
+//   26 of 49 on 16 rows, and the 32 rows that are one operand wide, 1.4 times, 1.01 at worst, with 0.4 of the error
+//   4 of 33 tiles chosen without a hint, 1.5 times
+// Not tiles of 8 rows: with three plans in turn, B and A from beyond the L2s, 4096 x 4096, 80 % pruned, 4 columns take 5.8 us on tiles, 7.2 on strips, whose
+// copy of B is short of bytes in flight.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
+bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, int rows, strips::start &begun)
 {
     const int64_t nnz = row_ptr[M];
     // As for tiles mostly the launch's time; but chunks take two column tiles beyond 128 columns.
     if (nnz == 0 || (nnz < ((int64_t)1 << 17) && n_hint <= 128)) return false;
     const int32_t hinted[] = {std::min(std::max(n_hint, 4), 256)}, unknown[] = {16, 64, 200};
     const int widths = n_hint > 0 ? 1 : 3;
-    double chunks[3];
+    double others[3], margin = 10.0;
     for (int i = 0; i < widths; ++i) {
         const int32_t N = n_hint > 0 ? hinted[i] : unknown[i];
-        chunks[i] = chunks_time(M, K, row_ptr, n_hint, N);
-        if (strips::time_at_best(M, K, nnz, N) >= chunks[i]) return false;
+        if (rows > 0) {
+            int NB = 1;
+            others[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (n_hint > 0 ? 1.0 : 0.95);
+            if (rows == 8 || (rows == 32 && NB > 1)) return false;
+        } else {
+            others[i] = chunks_time(M, K, row_ptr, n_hint, N);
+        }
+        margin = std::min(margin, others[i] / strips::time_at_best(M, K, nnz, N));
     }
-    const StripSizes p = strips::sizes(M, K, row_ptr, n_hint);
+    if (margin <= 1.0) return false;
+    // Rows of about one length take 1.0 times what they take at best, 1.25 times in one product of a hundred: no need to look at the units,
+    // which the builder finds while the entries travel (0.05 ms of the 0.9 that plan and product of 4096 x 4096, 80 % pruned, take).
+    int64_t longest = 0;
+    for (int64_t i = 0; i < M; ++i) longest = std::max<int64_t>(longest, row_ptr[i + 1] - row_ptr[i]);
+    if (margin > 1.25 && longest * M <= 2 * nnz) return true;
+    begun = strips::begin(M, K, row_ptr, strips::columns_for(n_hint));
     for (int i = 0; i < widths; ++i)
-        if (strip_time(p, K, n_hint > 0 ? hinted[i] : unknown[i], nullptr) >= chunks[i]) return false;
+        if (strip_time(begun.sizes, K, n_hint > 0 ? hinted[i] : unknown[i], nullptr) >= others[i]) return false;
     return true;
 }
 
@@ -624,7 +647,7 @@ int spmm_strips_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_
         for (std::thread &o : others) o.join();
         if (failed) throw std::bad_alloc();
     };
-    if (!strips::build(M, K, row_ptr, col_idx, vals, n_hint > 0 ? n_hint : strips::UNKNOWN_COLUMNS, over, out)) out = strips::host();
+    if (!strips::build(M, K, row_ptr, col_idx, vals, strips::columns_for(n_hint), over, out)) out = strips::host();
     return ST_OK;
 }
 

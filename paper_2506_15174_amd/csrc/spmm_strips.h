@@ -36,7 +36,7 @@ struct StripSizes {
     int32_t bands = 1, band_rows = 0;
 };
 struct StripPlan : StripSizes {
-    static constexpr int KNOWN = 64;
+    static constexpr int KNOWN = 32;
     uint32_t groups[KNOWN + 1] = {};  // of units, for that many strips (strip_time)
     uint32_t *d_stream = nullptr;  // DEVICE groups, in the same memory behind
     // DEVICE per unit and band: first group, groups; behind them per unit and lane: row | log2(P) << 28, or STRIP_NO_ROW

@@ -244,7 +244,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
 // The same units, order and bytes as the builder on the host makes (spmm_strips_build.h says why that order): the rows' entries band by
 // band and class by class (class_kernel), then every unit in a band by a wave of its own, lane by lane what the host's loops do one
 // after the other (order_kernel).  Plan and product, 4096 x 4096, 80 % pruned, 64 columns (20 MB, of which the upload is
-// 0.5 ms): 0.85 ms, built on the host 7.1; 95 % pruned, 128 columns 0.59 and 3.6, on chunks 3.1.  Working memory is ten bytes an entry at most: with 16 its
+// 0.5 ms): 0.86 ms, on tiles 0.92, built on the host 7.1; 95 % pruned, 128 columns 0.58 and 3.6, on chunks 3.1.  Working memory is ten bytes an entry at most: with 16 its
 // allocation and release took 0.1 ms and 0.25 longer.
 
 struct build_args {
@@ -252,18 +252,19 @@ struct build_args {
     const float *vals;
     uint32_t *sorted;   // place in the band | number in the row << 16: the entries, a row's band by band and class by class
     uint32_t *classes;  // per row and band: entries; how many before its classes 1 .. 7
-    uint32_t *flags;    // BAD_*
+    uint32_t *flags;    // a word each for BAD_*, not zero where found
     uint32_t *units;
     uint32_t *rows;
     const uint32_t *order;  // the rows, longest first
     const u32x4 *list;      // the units
     char *stream;
     int64_t M;
-    uint32_t nnz;
+    uint32_t nnz, places;  // units in a band
     int32_t K, bands, band_rows;
+    builder::pull values;  // some of them, on their way beside the ordering
 };
 constexpr uint32_t NOTHING = ~0u;  // instead of an entry (its place is below the rows of a band)
-constexpr uint32_t BAD_COLUMN = 1, BAD_ORDER = 2, BAD_LENGTH = 4;
+constexpr int BAD_COLUMN = 0, BAD_ORDER = 1, BAD_LENGTH = 2;
 
 // One wave per row.
 template <typename Col> __global__ __launch_bounds__(256) void class_kernel(const build_args args, const Col *col_idx)
@@ -272,7 +273,7 @@ template <typename Col> __global__ __launch_bounds__(256) void class_kernel(cons
     const uint32_t lane = threadIdx.x & 63;
     if (row >= args.M) return;
     const int32_t first = args.row_ptr[row], end = args.row_ptr[row + 1];
-    uint32_t bad = 0;
+    bool outside = false, disorder = false;
     for (int32_t band = 0, at = first; band < args.bands; ++band) {
         int32_t stop = end;
         if (band + 1 < args.bands) {  // the first entry beyond the band
@@ -283,42 +284,61 @@ template <typename Col> __global__ __launch_bounds__(256) void class_kernel(cons
                 else stop = middle;
             }
         }
-        uint32_t n[8] = {};
-        for (uint32_t q0 = (uint32_t)at; q0 < (uint32_t)stop; q0 += 64) {
-            const uint32_t q = q0 + lane;
-            const bool in = q < (uint32_t)stop;
-            const int32_t c = in ? (int32_t)col_idx[q] : 0;
-            if (in && (uint32_t)c >= (uint32_t)args.K) bad |= BAD_COLUMN;
-            if (in && q > (uint32_t)first && (int32_t)col_idx[q - 1] > c) bad |= BAD_ORDER;
+        // Four loads at a time: one after the other they would take all of the kernel's time (25 us for the matrix above).
+        constexpr int AHEAD = 4;
+        int32_t c[AHEAD];
+        auto load = [&](uint32_t q0, bool check) {
 #pragma unroll
-            for (int k = 0; k < 8; ++k) n[k] += (uint32_t)__popcll(__ballot(in && (c & 7) == k));
-        }
-        uint32_t before[8];
-        before[0] = 0;
-#pragma unroll
-        for (int k = 1; k < 8; ++k) before[k] = before[k - 1] + n[k - 1];
-        if (lane < 8) {
-            uint32_t word = (uint32_t)(stop - at);
-#pragma unroll
-            for (int k = 1; k < 8; ++k) word = lane == (uint32_t)k ? before[k] : word;
-            args.classes[((size_t)row * (uint32_t)args.bands + (uint32_t)band) * 8 + lane] = word;
-        }
-        for (uint32_t q0 = (uint32_t)at; q0 < (uint32_t)stop; q0 += 64) {
-            const uint32_t q = q0 + lane;
-            const bool in = q < (uint32_t)stop;
-            const int32_t c = in ? (int32_t)col_idx[q] : 0;
-            uint32_t to = 0;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const uint64_t them = __ballot(in && (c & 7) == k);
-                if ((c & 7) == k) to = before[k] + (uint32_t)__popcll(them & ((1ull << lane) - 1ull));
-                before[k] += (uint32_t)__popcll(them);
+            for (int k = 0; k < AHEAD; ++k) {
+                const uint32_t q = q0 + 64u * k + lane;
+                c[k] = q < (uint32_t)stop ? (int32_t)col_idx[q] : 0;
+                if (check && q < (uint32_t)stop) {
+                    outside |= (uint32_t)c[k] >= (uint32_t)args.K;
+                    disorder |= q > (uint32_t)first && (int32_t)col_idx[q - 1] > c[k];
+                }
             }
-            if (in) args.sorted[(size_t)at + to] = ((uint32_t)(c - band * args.band_rows) & 0xFFFFu) | (q - (uint32_t)first) << 16;
+        };
+        // the lanes whose column is of class x
+        struct masks {
+            uint64_t in, bit[3];
+            __device__ uint64_t of(uint32_t x) const { return in & (x & 1 ? bit[0] : ~bit[0]) & (x & 2 ? bit[1] : ~bit[1]) & (x & 4 ? bit[2] : ~bit[2]); }
+        };
+        auto masks_of = [&](uint32_t q, int32_t column) {
+            masks m;
+            m.in = __ballot(q < (uint32_t)stop);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) m.bit[i] = __ballot((column >> i & 1) != 0);
+            return m;
+        };
+        const uint32_t mine = lane & 7;  // the class that the lane counts
+        uint32_t n = 0;
+        for (uint32_t q0 = (uint32_t)at; q0 < (uint32_t)stop; q0 += 64 * AHEAD) {
+            load(q0, true);
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) n += (uint32_t)__popcll(masks_of(q0 + 64u * k + lane, c[k]).of(mine));
+        }
+        uint32_t before = n;  // and then, how many come before it
+        for (uint32_t m = 1; m < 8; m *= 2) {
+            const uint32_t less = (uint32_t)__shfl_up((int)before, m);
+            if (mine >= m) before += less;
+        }
+        before -= n;
+        if (lane < 8) args.classes[((size_t)row * (uint32_t)args.bands + (uint32_t)band) * 8 + lane] = lane == 0 ? (uint32_t)(stop - at) : before;
+        for (uint32_t q0 = (uint32_t)at; q0 < (uint32_t)stop; q0 += 64 * AHEAD) {
+            load(q0, false);
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) {
+                const uint32_t q = q0 + 64u * k + lane;
+                const masks m = masks_of(q, c[k]);
+                const uint32_t to = (uint32_t)__shfl((int)before, c[k] & 7) + (uint32_t)__popcll(m.of((uint32_t)c[k] & 7u) & ((1ull << lane) - 1ull));
+                if (q < (uint32_t)stop) args.sorted[(size_t)at + to] = ((uint32_t)(c[k] - band * args.band_rows) & 0xFFFFu) | (q - (uint32_t)first) << 16;
+                before += (uint32_t)__popcll(m.of(mine));
+            }
         }
         at = stop;
     }
-    if (bad) atomicOr(args.flags, bad);
+    if (outside) args.flags[BAD_COLUMN] = 1;
+    if (disorder) args.flags[BAD_ORDER] = 1;
 }
 
 // One wave per unit: the rows of its lanes, and its groups, in bands as many as its rows need there.
@@ -341,7 +361,7 @@ __global__ __launch_bounds__(64) void unit_kernel(const build_args args)
         for (int m = 1; m < 64; m *= 2) groups = max(groups, (uint32_t)__shfl_xor((int)groups, m));
         if (lane == 0) {
             to[band * 2 + 1] = groups;
-            if (groups > (uint32_t)strips::MOST_GROUPS) atomicOr(args.flags, BAD_LENGTH);
+            if (groups > (uint32_t)strips::MOST_GROUPS) args.flags[BAD_LENGTH] = 1;
         }
     }
 }
@@ -371,19 +391,27 @@ __global__ __launch_bounds__(1024) void begin_kernel(uint32_t *units, uint32_t n
 
 // One wave per unit in a band.  Eight threads next to each other are the lanes that must not collide; what they propose goes around
 // between them as a bit of a byte per turn.  Bound by the chain of a step's 300 instructions: 4096 x 4096, 80 % pruned, 104 steps, 78 us (with
-// eight turns of one lane each and a shuffle 260).  The entries are loaded behind the choices, and written a group later.
-__global__ __launch_bounds__(64) void order_kernel(const build_args args)
+// eight turns of one lane each and a shuffle 260).  It writes places and, where the values will be, the entries: so it needs no values, and the
+// first workgroups copy a piece of those meanwhile (two of the three that the pinned memory holds would leave the next ones waiting).
+__global__ __launch_bounds__(256) void order_kernel(const build_args args)
 {
-    const uint32_t unit = blockIdx.x / (uint32_t)args.bands, band = blockIdx.x % (uint32_t)args.bands;
-    const uint32_t i = threadIdx.x & 7, set = threadIdx.x >> 3, j = 2 * i + (set & 1);
+    const uint32_t pulling = args.values.n ? builder::PULL_BLOCKS : 0u;
+    if (blockIdx.x < pulling) {
+        builder::run_pull(args.values, blockIdx.x);
+        return;
+    }
+    const uint32_t at_place = (blockIdx.x - pulling) * 4 + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (at_place >= args.places) return;
+    const uint32_t unit = at_place / (uint32_t)args.bands, band = at_place % (uint32_t)args.bands;
+    const uint32_t i = threadIdx.x & 7, set = threadIdx.x >> 3 & 7, j = 2 * i + (set & 1);
     const uint32_t lane = (set >> 2) * 32 + ((set & 2 ? 0x7421u : 0x6530u) >> (j / 4 * 4) & 15u) * 4 + j % 4;  // strip_lane(set / 2, i, set % 2)
     const uint32_t word = args.rows[(size_t)unit * 64 + lane], log2 = args.rows[(size_t)unit * 64] >> STRIP_PARTS_SHIFT, x = lane & ((1u << log2) - 1u);
-    const uint32_t first = args.units[(size_t)blockIdx.x * 2], groups = args.units[(size_t)blockIdx.x * 2 + 1];
-    uint32_t at[9] = {}, begin = 0, row_begin = 0;  // of the row's entries in the band: how many before a class; the first; the row's first
+    const uint32_t first = args.units[(size_t)at_place * 2], groups = args.units[(size_t)at_place * 2 + 1];
+    uint32_t at[9] = {}, begin = 0;  // of the row's entries in the band: how many before a class; the first
     if (word != STRIP_NO_ROW) {
         const uint32_t row = word & ((1u << STRIP_PARTS_SHIFT) - 1u);
         const uint32_t *words = args.classes + (size_t)row * (uint32_t)args.bands * 8;
-        begin = row_begin = (uint32_t)args.row_ptr[row];
+        begin = (uint32_t)args.row_ptr[row];
         for (uint32_t b = 0; b < band; ++b) begin += words[b * 8];
 #pragma unroll
         for (int c = 1; c < 8; ++c) at[c] = words[band * 8 + c];
@@ -473,58 +501,58 @@ __global__ __launch_bounds__(64) void order_kernel(const build_args args)
         left -= take < 8;
         return take < 8 ? begin + x + (k << log2) : NOTHING;
     };
-    // A group is chosen and its entries fetched; a group later their values are, and it is written two groups later.
-    uint32_t taken[2][STRIP_STEPS];  // entries
-    f32x4 values[2];
-    u32x2 places[2];
+    uint32_t taken[2][STRIP_STEPS];  // entries; written when the next group has been chosen
     char *out = args.stream + (size_t)first * STRIP_GROUP_BYTES;
-    auto group = [&](uint32_t g, int b) {
+    auto group = [&](uint32_t g, uint32_t (&e)[STRIP_STEPS]) {
         weigh();
 #pragma unroll
         for (int k = 0; k < STRIP_STEPS; ++k) {
             const uint32_t from = choose((int32_t)(g * STRIP_STEPS) + k);
-            taken[b][k] = from == NOTHING ? NOTHING : args.sorted[from];
+            e[k] = from == NOTHING ? NOTHING : args.sorted[from];
         }
     };
-    auto fetch = [&](int b) {
+    auto store = [&](uint32_t g, const uint32_t (&e)[STRIP_STEPS]) {
         uint32_t place[STRIP_STEPS];
 #pragma unroll
-        for (int k = 0; k < STRIP_STEPS; ++k) {
-            const bool none = taken[b][k] == NOTHING;
-            place[k] = none ? (uint32_t)args.band_rows : taken[b][k] & 0xFFFFu;
-            values[b][k] = none ? 0.0f : args.vals[row_begin + (taken[b][k] >> 16)];
-        }
-        places[b] = u32x2{place[0] | place[1] << 16, place[2] | place[3] << 16};
+        for (int k = 0; k < STRIP_STEPS; ++k) place[k] = e[k] == NOTHING ? (uint32_t)args.band_rows : e[k] & 0xFFFFu;
+        *reinterpret_cast<u32x4 *>(out + (size_t)g * STRIP_GROUP_BYTES + lane * 16) = u32x4{e[0], e[1], e[2], e[3]};
+        *reinterpret_cast<u32x2 *>(out + (size_t)g * STRIP_GROUP_BYTES + 1024 + lane * 8) = u32x2{place[0] | place[1] << 16, place[2] | place[3] << 16};
     };
-    auto store = [&](uint32_t g, int b) {
-        *reinterpret_cast<f32x4 *>(out + (size_t)g * STRIP_GROUP_BYTES + lane * 16) = values[b];
-        *reinterpret_cast<u32x2 *>(out + (size_t)g * STRIP_GROUP_BYTES + 1024 + lane * 8) = places[b];
-    };
-    uint32_t g = 0;
+    if (groups == 0) return;
+    group(0, taken[0]);
+    uint32_t g = 1;
     for (; g + 1 < groups; g += 2) {
-        group(g, 0);
-        if (g > 0) {
-            fetch(1);
-            store(g - 2, 0);
-        }
-        group(g + 1, 1);
-        fetch(0);
-        if (g > 0) store(g - 1, 1);
-    }
-    // what is left, at most three groups; g is even
-    if (g < groups) group(g, 0);
-    if (g > 0) {
-        fetch(1);
-        store(g - 2, 0);
-        store(g - 1, 1);
+        group(g, taken[1]);
+        store(g - 1, taken[0]);
+        group(g + 1, taken[0]);
+        store(g, taken[1]);
     }
     if (g < groups) {
-        fetch(0);
-        store(g, 0);
+        group(g, taken[1]);
+        store(g - 1, taken[0]);
+        store(g, taken[1]);
+    } else {
+        store(g - 1, taken[0]);
     }
 }
 
-hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, TilePlan &out, int &status)
+// Eight waves per unit in a band: the values in place of the entries.
+__global__ __launch_bounds__(512) void value_kernel(const build_args args)
+{
+    const uint32_t lane = threadIdx.x & 63, word = args.rows[(size_t)(blockIdx.x / (uint32_t)args.bands) * 64 + lane];
+    const uint32_t first = args.units[(size_t)blockIdx.x * 2], groups = args.units[(size_t)blockIdx.x * 2 + 1];
+    const float *vals = args.vals + (word == STRIP_NO_ROW ? 0 : args.row_ptr[word & ((1u << STRIP_PARTS_SHIFT) - 1u)]);
+    char *at = args.stream + (size_t)first * STRIP_GROUP_BYTES + lane * 16;
+    for (uint32_t g = threadIdx.x >> 6; g < groups; g += 8) {
+        const u32x4 e = *reinterpret_cast<const u32x4 *>(at + (size_t)g * STRIP_GROUP_BYTES);
+        f32x4 v;
+#pragma unroll
+        for (int k = 0; k < STRIP_STEPS; ++k) v[k] = e[k] == NOTHING ? 0.0f : vals[e[k] >> 16];
+        *reinterpret_cast<f32x4 *>(at + (size_t)g * STRIP_GROUP_BYTES) = v;
+    }
+}
+
+hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, const strips::start *begun, TilePlan &out, int &status)
 {
     const int64_t nnz = row_ptr[M];
     hipError_t e;
@@ -542,12 +570,34 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     const hipStream_t s = memory.stream;
     int32_t *d_col = memory.at<int32_t>(at_entries);
     uint32_t *d_words = memory.at<uint32_t>(at_words);
-    uint64_t *answer = reinterpret_cast<uint64_t *>(d_words);  // groups, flags
-    const size_t front = ((size_t)M + 5 + 63) / 64 * 64, list = ((size_t)M + 3) / 4 * 4;
-    build_args a{reinterpret_cast<const int32_t *>(d_words + 4), memory.at<float>(at_entries), memory.at<uint32_t>(at_sorted), memory.at<uint32_t>(at_classes), d_words + 2, nullptr, nullptr,
-                 d_words + front, reinterpret_cast<const u32x4 *>(d_words + front + list), nullptr, M, (uint32_t)nnz, (int32_t)K, p.bands, p.band_rows};
-    std::vector<uint32_t> words((size_t)M + 5, 0u);  // groups, flags, the row pointer
-    std::copy(row_ptr, row_ptr + M + 1, words.begin() + 4);
+    uint64_t *answer = reinterpret_cast<uint64_t *>(d_words) + 2;  // behind four words of flags: groups
+    const size_t front = ((size_t)M + 9 + 63) / 64 * 64, list = ((size_t)M + 3) / 4 * 4;
+    build_args a{reinterpret_cast<const int32_t *>(d_words + 8), memory.at<float>(at_entries), memory.at<uint32_t>(at_sorted), memory.at<uint32_t>(at_classes), staged ? upload.flags() : d_words, nullptr, nullptr,
+                 d_words + front, reinterpret_cast<const u32x4 *>(d_words + front + list), nullptr, M, (uint32_t)nnz, 0, (int32_t)K, p.bands, p.band_rows, {}};
+    // ---- while other threads fill the first pinned memory: the rows' order and the units
+    strips::start own;
+    if (!begun) own = strips::begin(M, K, row_ptr, N);
+    const strips::start &begin = begun ? *begun : own;
+    const std::vector<uint32_t> &order = begin.r.order;
+    const std::vector<strips::unit> &units = begin.units;
+    static_cast<StripSizes &>(p) = begin.sizes;
+    const int64_t n_units = (int64_t)units.size(), places = n_units * bands;
+    const size_t n_words = strips::unit_words(n_units, bands);
+    const uint32_t longest = begin.r.length[0];
+    // an entry's number in its row in 16 bits; blocks of 512 threads
+    if (longest > 65535 || places >= (int64_t)1 << 23) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
+    // flags, groups, the row pointer; the order; the units in four words each (unit_kernel)
+    std::vector<uint32_t> words(front + list + (size_t)n_units * 4, 0u);
+    std::copy(row_ptr, row_ptr + M + 1, words.begin() + 8);
+    std::copy(order.begin(), order.end(), words.begin() + (ptrdiff_t)front);
+    uint64_t groups = 0;
+    uint32_t *to = words.data() + front + list;
+    for (const strips::unit &u : units) {
+        const int64_t n = bands == 1 ? u.steps / STRIP_STEPS : 0;
+        for (uint64_t w : {(uint64_t)u.first, (uint64_t)u.parts_log2, groups, (uint64_t)n}) *to++ = (uint32_t)w;
+        groups += (uint64_t)n;
+    }
+    a.places = (uint32_t)places;
     TRY(upload.copy_words(words, d_words));
     if (staged) {
         TRY(upload.copy(0, reinterpret_cast<char *>(d_col)));
@@ -558,26 +608,7 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     if (narrow) hipLaunchKernelGGL(class_kernel<uint16_t>, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, s, a, reinterpret_cast<const uint16_t *>(d_col));
     else hipLaunchKernelGGL(class_kernel<int32_t>, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, s, a, d_col);
     TRY(hipGetLastError());
-    if (staged) TRY(upload.copy(1, memory.at<char>(at_entries)));
-    else TRY(hipMemcpyWithStream(d_col, vals, (size_t)nnz * 4, hipMemcpyHostToDevice, s));
-    // ---- while the last values travel: the rows' order, and the units in four words each (unit_kernel)
-    const std::vector<uint32_t> order = strips::by_length(M, row_ptr);
-    const std::vector<strips::unit> units = strips::units_for(M, K, row_ptr, order, N, p);
-    const int64_t n_units = (int64_t)units.size(), places = n_units * bands;
-    const size_t n_words = strips::unit_words(n_units, bands);
-    const int32_t longest = row_ptr[order[0] + 1] - row_ptr[order[0]];
-    // an entry's number in its row in 16 bits; blocks of 64 threads
-    if (longest > 65535 || places >= (int64_t)1 << 26) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
-    words.assign(list + (size_t)n_units * 4, 0u);
-    std::copy(order.begin(), order.end(), words.begin());
-    uint64_t groups = 0;
-    uint32_t *to = words.data() + list;
-    for (const strips::unit &u : units) {
-        const int64_t n = bands == 1 ? u.steps / STRIP_STEPS : 0;
-        for (uint64_t w : {(uint64_t)u.first, (uint64_t)u.parts_log2, groups, (uint64_t)n}) *to++ = (uint32_t)w;
-        groups += (uint64_t)n;
-    }
-    TRY(upload.copy_words(words, d_words + front));
+    TRY(upload.look());
     // the plan's memory, once it is known how much; in bands the units wait in memory of their own
     auto take_plan = [&]() -> hipError_t {
         if (groups >= (1ull << 32)) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
@@ -607,24 +638,35 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     a.rows = a.units + places * 2;
     hipLaunchKernelGGL(unit_kernel, dim3((unsigned)n_units), dim3(64), 0, s, a);
     TRY(hipGetLastError());
-    uint64_t got[2];
+    uint32_t got[6] = {};  // flags, groups
+    auto refused = [&] {
+        const uint32_t *flags = staged ? upload.flags() : got;
+        status = flags[BAD_COLUMN] ? 2 : flags[BAD_ORDER] || flags[BAD_LENGTH] ? TILES_NOT_POSSIBLE : 0;
+        return status != 0;
+    };
     if (bands > 1) {
         hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1024), 0, s, a.units, (uint32_t)places, answer);
         TRY(hipGetLastError());
-        TRY(hipMemcpyWithStream(got, answer, 16, hipMemcpyDeviceToHost, s));
-        groups = got[0];
-        if (got[1]) { status = got[1] & BAD_COLUMN ? 2 : TILES_NOT_POSSIBLE; return hipSuccess; }
+        TRY(hipMemcpyWithStream(got, d_words, sizeof got, hipMemcpyDeviceToHost, s));
+        if (refused()) return hipSuccess;
+        std::memcpy(&groups, got + 4, 8);
         TRY(take_plan());
         if (status) return hipSuccess;
         TRY(hipMemcpyAsync(a.units, waiting.p, n_words * 4, hipMemcpyDeviceToDevice, s));
         a.rows = a.units + places * 2;
     }
-    hipLaunchKernelGGL(order_kernel, dim3((unsigned)places), dim3(64), 0, s, a);
+    TRY(upload.next_values(memory.at<char>(at_entries), a.values));
+    hipLaunchKernelGGL(order_kernel, dim3((unsigned)((places + 3) / 4) + (a.values.n ? builder::PULL_BLOCKS : 0u)), dim3(256), 0, s, a);
     TRY(hipGetLastError());
-    TRY(hipMemcpyWithStream(got, answer, 16, hipMemcpyDeviceToHost, s));
-    if (got[1]) { status = got[1] & BAD_COLUMN ? 2 : TILES_NOT_POSSIBLE; return hipSuccess; }
+    TRY(upload.launched());
+    if (staged) TRY(upload.copy(1, memory.at<char>(at_entries)));
+    else TRY(hipMemcpyWithStream(d_col, vals, (size_t)nnz * 4, hipMemcpyHostToDevice, s));
+    hipLaunchKernelGGL(value_kernel, dim3((unsigned)places), dim3(512), 0, s, a);
+    TRY(hipGetLastError());
+    if (!staged) TRY(hipMemcpyWithStream(got, d_words, sizeof got, hipMemcpyDeviceToHost, s));
     TRY(memory.give_back());
     TRY(hipStreamSynchronize(s));
+    if (refused()) return hipSuccess;
     upload.arrived();
 #undef TRY
     p.n_units = n_units;
@@ -663,9 +705,10 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
 
 int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, TilePlan &out)
 {
+    const strips::start *begun = out.begun;
     out = TilePlan();
     int status = 0;
-    const hipError_t e = build(M, K, row_ptr, col_idx, vals, N, out, status);
+    const hipError_t e = build(M, K, row_ptr, col_idx, vals, N, begun, out, status);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         status = e == hipErrorOutOfMemory ? 3 : 4;

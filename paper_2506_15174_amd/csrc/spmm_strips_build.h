@@ -13,22 +13,32 @@
 
 namespace strips {
 
-// Rows by length, longest first, stable.
-inline std::vector<uint32_t> by_length(int64_t M, const int32_t *row_ptr)
+// Rows by length, longest first, stable; their lengths.
+struct rows {
+    std::vector<uint32_t> order, length;
+};
+inline rows by_length(int64_t M, const int32_t *row_ptr)
 {
     int64_t longest = 0;
     for (int64_t i = 0; i < M; ++i) longest = std::max<int64_t>(longest, row_ptr[i + 1] - row_ptr[i]);
-    std::vector<uint32_t> order((size_t)M);
+    rows r;
+    r.order.resize((size_t)M);
+    r.length.resize((size_t)M);
     if (longest < 8 * M + 4096) {  // counted
         std::vector<uint32_t> place((size_t)longest + 2, 0);
         for (int64_t i = 0; i < M; ++i) ++place[(size_t)(longest - (row_ptr[i + 1] - row_ptr[i])) + 1];
         for (size_t k = 1; k < place.size(); ++k) place[k] += place[k - 1];
-        for (int64_t i = 0; i < M; ++i) order[place[(size_t)(longest - (row_ptr[i + 1] - row_ptr[i]))]++] = (uint32_t)i;
+        for (int64_t i = 0; i < M; ++i) {
+            const uint32_t n = (uint32_t)(row_ptr[i + 1] - row_ptr[i]), at = place[(size_t)(longest - n)]++;
+            r.order[at] = (uint32_t)i;
+            r.length[at] = n;
+        }
     } else {
-        std::iota(order.begin(), order.end(), 0u);
-        std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return row_ptr[x + 1] - row_ptr[x] > row_ptr[y + 1] - row_ptr[y]; });
+        std::iota(r.order.begin(), r.order.end(), 0u);
+        std::stable_sort(r.order.begin(), r.order.end(), [&](uint32_t x, uint32_t y) { return row_ptr[x + 1] - row_ptr[x] > row_ptr[y + 1] - row_ptr[y]; });
+        for (int64_t i = 0; i < M; ++i) r.length[(size_t)i] = (uint32_t)(row_ptr[r.order[(size_t)i] + 1] - row_ptr[r.order[(size_t)i]]);
     }
-    return order;
+    return r;
 }
 
 struct unit {
@@ -38,17 +48,18 @@ struct unit {
 constexpr int64_t steps_of(int64_t entries) { return (entries + STRIP_STEPS - 1) / STRIP_STEPS * STRIP_STEPS; }
 
 // The rows in units whose lanes have at most `most` entries, where a row in 64 parts allows that.
-inline std::vector<unit> units_of(int64_t M, const int32_t *row_ptr, const std::vector<uint32_t> &order, int64_t most)
+inline void units_of(const rows &r, int64_t most, std::vector<unit> &units)
 {
-    std::vector<unit> units;
+    units.clear();
+    const int64_t M = (int64_t)r.length.size();
+    units.reserve((size_t)(M / 8 + 64));
+    int p = 6;
     for (int64_t at = 0; at < M;) {
-        const int64_t len = row_ptr[order[(size_t)at] + 1] - row_ptr[order[(size_t)at]];
-        int p = 0;
-        while (p < 6 && ((len + (1 << p) - 1) >> p) > most) ++p;
+        const int64_t len = r.length[(size_t)at];  // (no longer than those before)
+        while (p > 0 && ((len + (1 << (p - 1)) - 1) >> (p - 1)) <= most) --p;
         units.push_back(unit{at, p, (int32_t)steps_of((len + (1 << p) - 1) >> p)});
         at += 64 >> p;
     }
-    return units;
 }
 
 inline void band_sizes(int64_t K, StripSizes &p)
@@ -64,39 +75,37 @@ constexpr int64_t UNKNOWN_COLUMNS = 64;
 // 1.6 equal shares of the entries, whichever is estimated to take least.  (A row's parts are a power of two, so some shares leave
 // some waves a second unit and others idle: 3001 x 2511, 85 % pruned, 200 columns 17.2 us with 1.25 for all, 15.7 so.)  A strip in bands
 // allows one unit per wave only, which more entries per lane bring about.
-inline std::vector<unit> units_for(int64_t M, int64_t K, const int32_t *row_ptr, const std::vector<uint32_t> &order, int64_t N, StripSizes &p)
+inline std::vector<unit> units_for(int64_t K, const rows &r, int64_t entries, int64_t N, StripSizes &p)
 {
     band_sizes(K, p);
     const int64_t waves = STRIP_WAVES * std::max<int64_t>(1, 256 / ((N + STRIP_COLS - 1) / STRIP_COLS));  // with a workgroup on every compute unit
-    std::vector<unit> best;
-    int64_t best_most = 0;
+    std::vector<unit> best, units;
+    StripSizes best_sizes = p;
     double best_us = 0.0;
-    auto measure = [&](const std::vector<unit> &units, StripSizes &s) {
+    int64_t last_most = 0;
+    for (const int64_t tenths : {8, 10, 12, 14, 16}) {
+        int64_t most = std::max<int64_t>(8, steps_of(entries * tenths / (10 * 64 * waves) + 1));
+        units_of(r, most, units);
+        for (int tries = 0; p.bands > 1 && (int64_t)units.size() > waves && tries < 8; ++tries) {
+            most += steps_of(most / 16 + 1);
+            units_of(r, most, units);
+        }
+        if (most == last_most) continue;
+        last_most = most;
+        StripSizes s = p;
         s.n_units = (int64_t)units.size();
-        s.steps = s.longest = 0;
         for (const unit &u : units) {
             s.steps += u.steps;
             s.longest = std::max<int64_t>(s.longest, u.steps);
         }
-    };
-    for (const int64_t tenths : {8, 10, 12, 14, 16}) {
-        int64_t most = std::max<int64_t>(8, steps_of((int64_t)row_ptr[M] * tenths / (10 * 64 * waves) + 1));
-        std::vector<unit> units = units_of(M, row_ptr, order, most);
-        for (int tries = 0; p.bands > 1 && (int64_t)units.size() > waves && tries < 8; ++tries) {
-            most += steps_of(most / 16 + 1);
-            units = units_of(M, row_ptr, order, most);
-        }
-        if (most == best_most) continue;
-        StripSizes s = p;
-        measure(units, s);
         const double us = strip_time(s, K, N, nullptr);
         if (best.empty() || us < best_us) {
-            best = units;
+            best.swap(units);
             best_us = us;
-            best_most = most;
+            best_sizes = s;
         }
     }
-    measure(best, p);
+    p = best_sizes;
     std::stable_sort(best.begin(), best.end(), [](const unit &x, const unit &y) { return x.steps > y.steps; });
     return best;
 }
@@ -111,13 +120,20 @@ inline double time_at_best(int64_t M, int64_t K, int64_t entries, int64_t N)
     return strip_time(p, K, N, nullptr);
 }
 
-// The sizes a plan made for n_hint columns would have.
-inline StripSizes sizes(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
+// What a plan made for products with N columns begins with.
+struct start {
+    rows r;
+    std::vector<unit> units;
+    StripSizes sizes;
+};
+inline start begin(int64_t M, int64_t K, const int32_t *row_ptr, int64_t N)
 {
-    StripSizes p;
-    units_for(M, K, row_ptr, by_length(M, row_ptr), n_hint > 0 ? n_hint : UNKNOWN_COLUMNS, p);
-    return p;
+    start s;
+    s.r = by_length(M, row_ptr);
+    s.units = units_for(K, s.r, row_ptr[M], N, s.sizes);
+    return s;
 }
+inline int64_t columns_for(int32_t n_hint) { return n_hint > 0 ? n_hint : UNKNOWN_COLUMNS; }
 
 // Words of the units and rows, in front of the groups.
 inline size_t unit_words(int64_t n_units, int64_t bands) { return ((size_t)(n_units * bands) * 2 + (size_t)n_units * 64 + 63) / 64 * 64; }
@@ -279,8 +295,10 @@ template <typename Over> bool build(int64_t M, int64_t K, const int32_t *row_ptr
     out = host();
     if (M >= (int64_t)1 << STRIP_PARTS_SHIFT) return false;
     StripPlan &p = out.plan;
-    const std::vector<uint32_t> order = by_length(M, row_ptr);
-    const std::vector<unit> units = units_for(M, K, row_ptr, order, N, p);
+    const start s0 = begin(M, K, row_ptr, N);
+    const std::vector<uint32_t> &order = s0.r.order;
+    const std::vector<unit> &units = s0.units;
+    static_cast<StripSizes &>(p) = s0.sizes;
     const int64_t B = p.bands, R = p.band_rows;
     out.rows.resize((size_t)p.n_units * 64, STRIP_NO_ROW);
     out.units.resize((size_t)(p.n_units * B) * 2);

@@ -7,6 +7,10 @@
 
 #include "spmm_strips.h"
 
+namespace strips {
+struct start;
+}
+
 // Format.  The rows are taken in panels of `rows` = R (32, 16 or 8) consecutive rows of A, the
 // columns in steps of 16 * 64 / R columns.  The wave that multiplies a (panel, step) pair, a *block*,
 // gives it to 16 matrix operands t of one element per lane l:
@@ -30,6 +34,7 @@ struct TilePlan {
     bool exact_parts = false;       // R = 32: every value is the sum of three bf16 numbers
     float largest = 0.0f;           // R = 32: size of the largest value
     StripPlan strips;               // the entries are in strips instead (rows = 0)
+    const strips::start *begun = nullptr;  // for the builder of strips, if the caller has it
 };
 
 constexpr int TILE_OPERANDS = 16;

@@ -1269,8 +1269,8 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
 
 int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t rows, TilePlan &out)
 {
-    out = TilePlan();
     if (rows < 0) return spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, -rows, out);
+    out = TilePlan();
     out.rows = rows;
     const int64_t step = TILE_OPERANDS * 64 / rows;
     out.n_panels = (M + rows - 1) / rows;

@@ -95,6 +95,18 @@ private:
 };
 inline staging_memory staging;
 
+// A copy from pinned memory that a kernel makes beside its own work (n = 0: none).
+struct pull {
+    const upload_unit *from = nullptr;
+    upload_unit *to = nullptr;
+    uint32_t n = 0;
+};
+constexpr unsigned PULL_BLOCKS = 128;  // of 256 threads
+__device__ inline void run_pull(const pull &p, uint32_t block)
+{
+    for (uint32_t i = block * 256u + threadIdx.x; i < p.n; i += PULL_BLOCKS * 256u) p.to[i] = p.from[i];
+}
+
 // Copies from pinned memory, between a builder's kernels.  (With hipMemcpyAsync, whose engines and the kernels wait for each other,
 // the creation below takes 0.2 ms longer.)
 static __global__ __launch_bounds__(256) void pull_kernel(const upload_unit *from, upload_unit *to, uint32_t n)
@@ -130,16 +142,21 @@ public:
             }
         pinned = staging.lend();
         if (!pinned) return false;
+        std::memset(flags(), 0, 64);
         columns = reinterpret_cast<const uint32_t *>(col_idx);
         values = vals;
         limit = (uint32_t)K;
-        for (int t = 0; t < 4; ++t) {
+        // (a thread takes 15 us to start: the first one starts the others)
+        auto start = [this](int t, auto job) {
             try {
-                helpers.emplace_back([this] { help(); });
-            } catch (...) {
-                break;  // the caller fills what is left
+                helpers[t] = std::thread(job);
+            } catch (...) {  // the others and the caller fill what is left
             }
-        }
+        };
+        start(0, [this, start] {
+            for (int t = 1; t < HELPERS; ++t) start(t, [this] { help(); });
+            help();
+        });
         return true;
     }
     bool narrow_columns() const { return narrow; }
@@ -148,25 +165,43 @@ public:
     {
         for (; next < (kind == 0 ? column_pieces : pieces.size()); ++next) {
             const piece &p = pieces[next];
-            while (left[next].load(std::memory_order_acquire) > 0) {
-                const hipError_t e = look();
-                if (e != hipSuccess) return e;
-                if (!fill_part()) std::this_thread::yield();
-            }
+            hipError_t e = await_next();
+            if (e != hipSuccess) return e;
             hipLaunchKernelGGL(pull_kernel, dim3(128), dim3(256), 0, stream, reinterpret_cast<const upload_unit *>(place(next)),
                                reinterpret_cast<upload_unit *>(to + p.first * entry_bytes[kind]), (uint32_t)((p.count * entry_bytes[kind] + 15) / 16));
-            hipError_t e = hipEventRecord(copied[next % staging_memory::PIECES], stream);
+            e = hipEventRecord(copied[next % staging_memory::PIECES], stream);
+            launched_pieces = next + 1;
             if (e == hipSuccess) e = look();
             if (e != hipSuccess) return e;
         }
         return hipSuccess;
+    }
+    // The next piece of the values, when it is full, as a pull of the caller's, who says when that has been launched (none: n = 0).
+    hipError_t next_values(char *to, pull &out)
+    {
+        out = pull();
+        if (!pinned || next >= pieces.size() || pieces[next].kind != 1) return hipSuccess;
+        const hipError_t e = await_next();
+        if (e != hipSuccess) return e;
+        const piece &p = pieces[next];
+        out = pull{reinterpret_cast<const upload_unit *>(place(next)), reinterpret_cast<upload_unit *>(to + p.first * 4), (uint32_t)((p.count * 4 + 15) / 16)};
+        ++next;
+        return hipSuccess;
+    }
+    hipError_t launched()
+    {
+        for (; launched_pieces < next; ++launched_pieces) {
+            const hipError_t e = hipEventRecord(copied[launched_pieces % staging_memory::PIECES], stream);
+            if (e != hipSuccess) return e;
+        }
+        return look();
     }
     // Lets the helpers go on where copies have left room.
     hipError_t look()
     {
         while (pinned && usable.load() < pieces.size()) {
             const size_t oldest = usable.load() - staging_memory::PIECES;  // piece in the place that is wanted next
-            if (oldest >= next) break;
+            if (oldest >= launched_pieces) break;
             const hipError_t e = hipEventQuery(copied[oldest % staging_memory::PIECES]);
             if (e == hipErrorNotReady) {
                 (void)hipGetLastError();
@@ -181,13 +216,15 @@ public:
     hipError_t copy_words(const std::vector<uint32_t> &words, uint32_t *to)
     {
         const size_t bytes = (words.size() * 4 + 15) / 16 * 16;
-        if (!pinned || sent + bytes > staging_memory::WORDS) return hipMemcpyWithStream(to, words.data(), words.size() * 4, hipMemcpyHostToDevice, stream);
+        if (!pinned || sent + bytes > staging_memory::WORDS - 64) return hipMemcpyWithStream(to, words.data(), words.size() * 4, hipMemcpyHostToDevice, stream);
         char *from = pinned + staging_memory::PIECE * staging_memory::PIECES + sent;
         sent += bytes;
         std::copy(words.begin(), words.end(), reinterpret_cast<uint32_t *>(from));
         hipLaunchKernelGGL(pull_kernel, dim3(16), dim3(256), 0, stream, reinterpret_cast<const upload_unit *>(from), reinterpret_cast<upload_unit *>(to), (uint32_t)(bytes / 16));
         return hipGetLastError();
     }
+    // Words of pinned memory that a kernel may write, zero before; to be read when the stream has been waited for.
+    uint32_t *flags() { return reinterpret_cast<uint32_t *>(pinned + staging_memory::PIECE * staging_memory::PIECES + staging_memory::WORDS - 64); }
     bool column_outside() const { return outside.load(); }  // after the columns' copies
     void arrived()  // the stream has been waited for
     {
@@ -201,7 +238,8 @@ public:
             stop.store(true);
         }
         changed.notify_all();
-        for (std::thread &t : helpers) t.join();
+        for (std::thread &t : helpers)  // (the first one first)
+            if (t.joinable()) t.join();
         if (pinned) {
             if (next > 0 || sent > 0) (void)hipStreamSynchronize(stream);
             staging.take_back();
@@ -242,6 +280,16 @@ private:
             usable.fetch_add(1);
         }
         changed.notify_all();
+    }
+    // Fills with the others until the next piece is full.
+    hipError_t await_next()
+    {
+        while (left[next].load(std::memory_order_acquire) > 0) {
+            const hipError_t e = look();
+            if (e != hipSuccess) return e;
+            if (!fill_part()) std::this_thread::yield();
+        }
+        return hipSuccess;
     }
     // Fills one part; false if there is none, or no place for it yet.
     bool fill_part()
@@ -296,12 +344,13 @@ private:
     size_t entry_bytes[2] = {4, 4};
     std::vector<piece> pieces;
     std::vector<std::atomic<int>> left;  // parts of each piece that are still to be filled
-    size_t column_pieces = 0, next = 0, next_part = 0;
+    size_t column_pieces = 0, next = 0, next_part = 0, launched_pieces = 0;  // launched_pieces: whose event is recorded
     std::mutex lock;
     std::condition_variable changed;  // fill_piece, usable or stop, for helpers that have nothing to fill
     std::atomic<size_t> fill_piece{0}, usable{staging_memory::PIECES};  // pieces below have a place in the memory
     std::atomic<bool> outside{false}, stop{false};
-    std::vector<std::thread> helpers;
+    static constexpr int HELPERS = 4;
+    std::thread helpers[HELPERS];
 };
 
 }  // namespace builder

@@ -110,7 +110,7 @@ def test_more_workgroups_than_a_launch_takes_and_addresses_beyond_32_bits(torch_
 
 
 def test_when_strips_are_chosen(torch_gpu):  # noqa: F811
-    """Where chunks would gather slowly; never with another setting, never against one."""
+    """Where chunks would gather slowly and tiles would multiply too many zeros; never with another setting, never against one."""
     csr = gen.uniform_positions(4096, 4096, 0.95, 1)
     args = (csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals)
     assert spmm.plan_create(*args, n_hint=128).describe()["strip_units"] > 0
@@ -120,4 +120,13 @@ def test_when_strips_are_chosen(torch_gpu):  # noqa: F811
         with pytest.raises(spmm.SpmmError) as err:
             spmm.plan_create(*args, strips=1, **kw)
         assert err.value.status == spmm.SPMM_ERR_INVALID_ARG
+    # instead of tiles of 16 rows, but neither of 8 rows nor of the wide ones of 32; from rows out of order the tiles stay
+    csr = gen.uniform_positions(4096, 2048, 0.8, 2)
+    for n_hint, rows in ((64, 0), (4, 8)):
+        info = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=n_hint).describe()
+        assert info["tile_rows"] == rows and (info["strip_units"] > 0) == (rows == 0)
+    csr.col_idx[:2] = csr.col_idx[1::-1]
+    assert spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=64).describe()["tile_rows"] == 16
+    csr = gen.uniform_positions(2048, 4096, 0.5, 3)
+    assert spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=256).describe()["tile_rows"] == 32
     assert spmm.plan_create(40, 60, np.zeros(41), [], [], strips=1).describe()["strip_units"] == 0   # no entry at all
