@@ -125,7 +125,7 @@ def build_torch_extension(verbose=False):
           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(ROCM, "include"),
           os.path.join(CSRC, TORCH_EXT_SOURCE), "-o", TORCH_EXT_PATH,
           "-L", LIB_DIR, "-lspmm_cdna4", "-Wl,-rpath,$ORIGIN",
-          "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath," + os.path.join(root, "lib")],
+          "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip", "-Wl,-rpath," + os.path.join(root, "lib")],
          verbose)
     return TORCH_EXT_PATH
 

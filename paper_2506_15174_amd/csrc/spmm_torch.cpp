@@ -12,6 +12,13 @@
 #include <Python.h>
 
 #include <ATen/ATen.h>
+#include <ATen/Context.h>
+#include <ATen/EmptyTensor.h>
+#include <ATen/record_function.h>
+#include <ATen/hip/impl/HIPCachingAllocatorMasqueradingAsCUDA.h>
+#include <c10/core/impl/LocalDispatchKeySet.h>
+#include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -30,6 +37,20 @@ struct others_run {
     PyThreadState *state = PyEval_SaveThread();
     ~others_run() { PyEval_RestoreThread(state); }
 };
+
+// An output beside B.  On its way through the dispatcher at::empty takes 0.9 us of a small product's 4.5 (256 x 256, 32 columns: now 3.6).  Where
+// nothing may want to see or change that call (a dispatch mode, a functional transform, inference mode, a profiler, the fill of
+// deterministic mode) and the device is set, the tensor is made from the same allocator directly.
+at::Tensor output(const at::Tensor &B, int64_t M, int64_t N)
+{
+    const c10::impl::LocalDispatchKeySet local = c10::impl::tls_local_dispatch_key_set();
+    const bool plain = local.included_ == c10::default_included_set && local.excluded_ == c10::default_excluded_set &&
+                       !c10::impl::TorchDispatchModeTLS::any_modes_set() && !at::hasCallbacks() && !at::globalContext().deterministicAlgorithms() &&
+                       B.key_set().has(c10::DispatchKey::CUDA) && c10::hip::current_device() == B.device().index();
+    if (!plain) return at::empty({M, N}, B.options().requires_grad(false));
+    const int64_t sizes[2] = {M, N};
+    return at::Tensor(at::detail::empty_generic(sizes, c10::hip::HIPCachingAllocatorMasqueradingAsCUDA::get(), c10::DispatchKeySet(c10::DispatchKey::CUDA), at::kFloat, std::nullopt));
+}
 
 // execute(plan address, M, K, B, C or None, stream or None) -> C, or the status code as int
 PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
@@ -83,7 +104,7 @@ PyObject *execute(PyObject *, PyObject *const *args, Py_ssize_t nargs)
         spmm_status_t st;
         {
             others_run free_to_run;
-            if (!given) made = at::empty({M, N}, B.options().requires_grad(false));
+            if (!given) made = output(B, M, N);
             st = spmm_execute(plan, static_cast<const float *>(B.const_data_ptr()), (int32_t)N, static_cast<float *>(C.data_ptr()), stream);
         }
         if (st != SPMM_OK) return PyLong_FromLong((long)st);
