@@ -131,6 +131,16 @@ bool row_pointer_ok(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t 
     return true;
 }
 
+// Whether the first columns of 64 rows at even distances are in order: the builder of strips on the device refuses rows that are not, after
+// the upload (0.8 ms for 3.4 million entries).
+bool looks_in_order(int64_t M, const int32_t *row_ptr, const int32_t *col_idx)
+{
+    for (int64_t i = 0; i < M; i += (M + 63) / 64)
+        for (int64_t q = (int64_t)row_ptr[i] + 1; q < std::min<int64_t>(row_ptr[i + 1], (int64_t)row_ptr[i] + 16); ++q)
+            if (col_idx[q] < col_idx[q - 1]) return false;
+    return true;
+}
+
 struct plan_release {
     void operator()(spmm_plan *p) const
     {
@@ -207,7 +217,7 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         }
     }
     if (use_strips && checked && row_ptr[M] > 0) {
-        rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, -(int32_t)strips::columns_for(io.n_hint), p->tiles);
+        rc = looks_in_order(M, row_ptr, col_idx) ? spmm_tiles_build(M, K, row_ptr, col_idx, vals, -(int32_t)strips::columns_for(io.n_hint), p->tiles) : TILES_NOT_POSSIBLE;
         if (rc == 0 && p->tiles.strips.n_units == 0) rc = TILES_NOT_POSSIBLE;
         if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
             spmm_tiles_release(p->tiles);

@@ -580,11 +580,11 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 }
 
 // Strips take the place of the chunks or the tiles (`rows` a panel) that would be chosen where they are estimated to be faster, without a hint
-// at each of three widths.  Of 1400 random products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256
+// at each of three widths.  Of 1200 random products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256
 // columns, one in three without a hint):
 //   145 of 319 on chunks, 1.60 times as fast on average, 0.96 at worst, with 0.7 of the error against 64 bits; 42 others would be 1.19
 //       times as fast, 26 of them below 2^17 entries
-//   26 of 49 on 16 rows, and the 32 rows that are one operand wide, 1.4 times, 1.01 at worst, with 0.4 of the error
+//   28 of 49 on 16 rows, 1.34 times, 1.01 at worst, with 0.4 of the error, and 8 of 10 on 32 rows that are one operand wide
 //   4 of 33 tiles chosen without a hint, 1.5 times
 // Not tiles of 8 rows: with three plans in turn, B and A from beyond the L2s, 4096 x 4096, 80 % pruned, 4 columns take 5.8 us on tiles, 7.2 on strips, whose
 // copy of B is short of bytes in flight.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
