@@ -563,7 +563,8 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     const bool staged = upload.begin(K, col_idx, vals, nnz, memory.stream), narrow = staged && upload.narrow_columns();
     strips::band_sizes(K, p);
     const int64_t bands = p.bands;
-    if (M > ((int64_t)1 << 26) - 8) { status = TILES_NOT_POSSIBLE; return hipSuccess; }  // 256 threads per four rows
+    // 256 threads per four rows; 32 bytes of working memory per row and band
+    if (M > ((int64_t)1 << 26) - 8 || M * bands > (int64_t)1 << 26) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
     // (a unit has a row at least; the columns, and when they have been read the values in their place)
     const size_t at_words = memory.reserve((size_t)M * 24 + 1024), at_entries = memory.reserve((size_t)nnz * 4), at_sorted = memory.reserve((size_t)nnz * 4), at_classes = memory.reserve((size_t)(M * bands) * 32);
     TRY(memory.take());
