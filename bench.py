@@ -669,17 +669,19 @@ def run_paths(args):
         for N in sorted(rng.sample(PATH_WIDTHS, 4)):
             B = torch.from_numpy(gen.activations_for(csr, N)).cuda()
             C = torch.empty((M, N), dtype=torch.float32, device="cuda")
-            plans = {"chunks": spmm.plan_create(*a, n_hint=N, tiles=-1), "chosen": spmm.plan_create(*a, n_hint=N)}
+            plans = {"chunks": spmm.plan_create(*a, n_hint=N, tiles=-1), "strips": spmm.plan_create(*a, n_hint=N, strips=1),
+                     "chosen": spmm.plan_create(*a, n_hint=N)}
             for R in (8, 16, 32):
                 if R != 8 or N <= 64:
                     plans[R] = spmm.plan_create(*a, n_hint=N, tiles=R)
             us = {k: min(_time_plan(torch, p, B, C, N, reps=5) for _ in range(2)) for k, p in plans.items()}
             estimate = {"chunks": lib.spmm_chunks_time(i64(M), i64(K), ctypes.c_void_p(row_ptr.ctypes.data), N, dbl(N))}
-            for R in (k for k in plans if k not in ("chunks", "chosen")):
+            for R in (k for k in plans if k not in ("chunks", "strips", "chosen")):
                 heaviest = max(int(row_ptr[min(M, i + R)]) - int(row_ptr[i]) for i in range(0, M, R))
                 mean = nnz / (M * K)
                 estimate[R] = lib.spmm_tiles_time(R, i64(M), i64(K), i64(N), dbl(mean), dbl(max(mean, heaviest / (R * K))), None)
-            chosen = plans["chosen"].describe()["tile_rows"]
+            info = plans["chosen"].describe()
+            chosen = "strips" if info["strip_units"] else info["tile_rows"]
             paths = {k: v for k, v in us.items() if k != "chosen"}
             pts.append({"M": M, "K": K, "law": law, "density": round(nnz / (M * K), 4), "N": N, "chosen": chosen,
                         "us": {str(k): round(v, 2) for k, v in us.items()},
@@ -698,10 +700,10 @@ def run_paths(args):
                 "min": round(min(ratios), 2), "max": round(max(ratios), 2)}
 
     moved = [p for p in pts if p["chosen"]]
-    summary = {"products": len(pts), "on_tiles": len(moved),
+    summary = {"products": len(pts), "on_tiles": sum(p["chosen"] != "strips" for p in moved), "on_strips": sum(p["chosen"] == "strips" for p in moved),
                "chosen_over_best": {"geomean": round(_geomean([p["chosen_over_best"] for p in pts]), 3),
                                     "worst": max(p["chosen_over_best"] for p in pts)},
-               "tiles_over_chunks_where_chosen": {"geomean": round(_geomean([p["chosen_over_chunks"] for p in moved]), 3) if moved else None,
+               "tiles_or_strips_over_chunks_where_chosen": {"geomean": round(_geomean([p["chosen_over_chunks"] for p in moved]), 3) if moved else None,
                                                   "worst": max((p["chosen_over_chunks"] for p in moved), default=None),
                                                   "slower_by_3_pct": sum(p["chosen_over_chunks"] > 1.03 for p in moved)},
                "estimate_over_measured": {k: fit(k, pts) for k in ("chunks", "8", "16", "32")},

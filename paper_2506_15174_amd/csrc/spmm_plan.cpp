@@ -586,8 +586,10 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 //       times as fast, 26 of them below 2^17 entries
 //   28 of 49 on 16 rows, 1.34 times, 1.01 at worst, with 0.4 of the error, and 8 of 10 on 32 rows that are one operand wide
 //   4 of 33 tiles chosen without a hint, 1.5 times
-// Not tiles of 8 rows: with three plans in turn, B and A from beyond the L2s, 4096 x 4096, 80 % pruned, 4 columns take 5.8 us on tiles, 7.2 on strips, whose
-// copy of B is short of bytes in flight.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
+// Instead of tiles of 8 rows only from 1.54 times up, of chunks for up to 16 columns from 1.15 times: with three plans in turn, A and B from beyond the L2s,
+// narrow strips, whose copy of B is short of bytes in flight, take up to 1.3 times what is estimated (4096 x 4096, 80 % pruned, 4 columns 6.3 us on tiles, 7.3 on
+// strips; 2048 x 2048, 90 %, 8 columns 3.5 on chunks, 3.7 on strips), and chunks up to 0.85 times.  What still moves gains: 16384 x 1024, 75 %, 8 columns 10.8 -> 7.4 us,
+// 16000 x 700, 60 % in Zipf rows, 6 columns 10.8 -> 7.6, 9000 x 3000, 85 %, 10 columns 17.1 -> 7.9.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
 bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, int rows, strips::start &begun)
 {
     const int64_t nnz = row_ptr[M];
@@ -600,10 +602,10 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint,
         const int32_t N = n_hint > 0 ? hinted[i] : unknown[i];
         if (rows > 0) {
             int NB = 1;
-            others[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (n_hint > 0 ? 1.0 : 0.95);
-            if (rows == 8 || (rows == 32 && NB > 1)) return false;
+            others[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (rows == 8 ? 0.65 : n_hint > 0 ? 1.0 : 0.95);
+            if (rows == 32 && NB > 1) return false;
         } else {
-            others[i] = chunks_time(M, K, row_ptr, n_hint, N);
+            others[i] = chunks_time(M, K, row_ptr, n_hint, N) * (n_hint > 0 && N <= 16 ? 0.87 : 1.0);
         }
         margin = std::min(margin, others[i] / strips::time_at_best(M, K, nnz, N));
     }
