@@ -32,10 +32,11 @@ struct spmm_plan {
     // Plans cut along K: the slices' sums of one batch of up to KSLICE_COLS columns
     // (k_slices x slice_rows rows), written by every execute.
     float *d_slice_sums = nullptr;
-    // tiles.rows > 0: the entries are in tiles and the product runs on the matrix cores; tiles.strips.n_units > 0: they are in
+    // tiles.rows > 0: the entries are in tiles and the product runs on the matrix cores; strips.n_units > 0: they are in
     // strips.  Otherwise they are in chunks.
     TilePlan tiles;
-    bool on_chunks() const { return tiles.rows == 0 && tiles.strips.n_units == 0; }
+    StripPlan strips;
+    bool on_chunks() const { return tiles.rows == 0 && strips.n_units == 0; }
     int64_t scratch_bytes = 0;
     int64_t device_bytes = 0;
     int64_t stream_words = 0;  // length of host.stream at creation (a device plan drops its host mirror)
@@ -144,16 +145,15 @@ bool looks_in_order(int64_t M, const int32_t *row_ptr, const int32_t *col_idx)
 struct plan_release {
     void operator()(spmm_plan *p) const
     {
-        bool held = p->tiles.rows > 0;
-        StripPlan &strips = p->tiles.strips;
+        bool held = p->tiles.rows > 0 || p->strips.d_units;
         for (void *q : {(void *)p->d_stream, (void *)p->d_wins, (void *)p->d_items, (void *)p->d_rowmap, (void *)p->d_cross_sums,
-                        (void *)p->d_cross_table, (void *)p->d_slice_sums, (void *)strips.d_units})
+                        (void *)p->d_cross_table, (void *)p->d_slice_sums})
             if (q) {
                 held = true;
                 (void)hipFree(q);
             }
-        strips.d_units = nullptr;
         spmm_tiles_release(p->tiles);
+        spmm_strips_release(p->strips);
         if (held) (void)hipGetLastError();
         delete p;
     }
@@ -210,22 +210,19 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
     if (!host_only && tiles == 0 && !use_strips && !schedule_forced && checked) {
         tiles = choose_tiles(M, K, row_ptr, io.n_hint);
         if (opts.strips == 0 && choose_strips(M, K, row_ptr, io.n_hint, tiles, begun)) {
-            if (begun.sizes.n_units > 0) p->tiles.begun = &begun;
             use_strips = true;
             instead = tiles;
             tiles = 0;
         }
     }
     if (use_strips && checked && row_ptr[M] > 0) {
-        rc = looks_in_order(M, row_ptr, col_idx) ? spmm_tiles_build(M, K, row_ptr, col_idx, vals, -(int32_t)strips::columns_for(io.n_hint), p->tiles) : TILES_NOT_POSSIBLE;
-        if (rc == 0 && p->tiles.strips.n_units == 0) rc = TILES_NOT_POSSIBLE;
-        if (rc == TILES_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
-            spmm_tiles_release(p->tiles);
+        rc = looks_in_order(M, row_ptr, col_idx) ? spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, strips::columns_for(io.n_hint), begun, p->strips) : STRIPS_NOT_POSSIBLE;
+        if (rc == STRIPS_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
             rc = 0;
             if (instead > 0) tiles = instead;  // which the device builds from rows in any order
             else rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, strips);
         }
-        io.schedule_only = rc == 0 && (strips.plan.n_units > 0 || p->tiles.strips.n_units > 0);
+        io.schedule_only = rc == 0 && (strips.plan.n_units > 0 || p->strips.n_units > 0);
     }
     if (rc == 0 && !host_only && tiles > 0 && checked) {
         rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
@@ -242,10 +239,10 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (hipGetDevice(&p->device) != hipSuccess) return hip_fail();
         const HostPlan &h = p->host;
         spmm_status_t st = SPMM_OK;
-        if (p->tiles.rows > 0 || p->tiles.strips.n_units > 0) {
-            p->device_bytes = p->tiles.device_bytes;
+        if (!p->on_chunks()) {
+            p->device_bytes = p->tiles.device_bytes + p->strips.device_bytes;
         } else if (strips.plan.n_units > 0) {
-            StripPlan &to = p->tiles.strips = strips.plan;
+            StripPlan &to = p->strips = strips.plan;
             const size_t front = strips::unit_words(to.n_units, to.bands);
             std::vector<uint32_t> words(front + strips.stream.size());
             std::copy(strips.units.begin(), strips.units.end(), words.begin());
@@ -278,7 +275,7 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (st != SPMM_OK) return st;
         p->on_device = true;
     }
-    const StripPlan &on_strips = p->tiles.strips;
+    const StripPlan &on_strips = p->strips;
     p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : on_strips.n_units > 0 ? on_strips.steps / STRIP_STEPS * (STRIP_GROUP_BYTES / 4) : (int64_t)p->host.stream.size();
     if (on_strips.n_units > 0) {
         p->host.n_enum = on_strips.steps * 64;
@@ -359,8 +356,8 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     if (hipGetDevice(&dev) != hipSuccess) return hip_fail();
     if (dev != plan->device) return SPMM_ERR_INVALID_ARG;
 
-    if (!plan->on_chunks())
-        return spmm_tiles_execute(plan->tiles, h.M, h.K, B, N, C, stream) == 0 ? SPMM_OK : hip_fail();
+    if (plan->strips.n_units > 0) return spmm_strips_execute(plan->strips, h.K, B, N, C, stream) == 0 ? SPMM_OK : hip_fail();
+    if (plan->tiles.rows > 0) return spmm_tiles_execute(plan->tiles, h.M, h.K, B, N, C, stream) == 0 ? SPMM_OK : hip_fail();
 
     const uint64_t b_total = (uint64_t)h.K * (uint64_t)N * 4u;
     // Narrow addressing: 32-bit byte offsets into B formed by a 24 x 24-bit multiply.
@@ -525,7 +522,7 @@ spmm_status_t spmm_plan_describe_sized(const spmm_plan_t *plan, spmm_plan_info_t
     info.slice_rows = h.slice_rows;
     info.slice_cols = h.slice_cols;
     info.tile_rows = plan->tiles.rows;
-    info.strip_units = plan->tiles.strips.n_units;
+    info.strip_units = plan->strips.n_units;
     std::memset(out, 0, out_bytes);
     std::memcpy(out, &info, std::min(out_bytes, sizeof info));
     return SPMM_OK;

@@ -42,6 +42,8 @@ struct StripPlan : StripSizes {
     // DEVICE per unit and band: first group, groups; behind them per unit and lane: row | log2(P) << 28, or STRIP_NO_ROW
     uint32_t *d_units = nullptr;  // (as many words as strips::unit_words, a multiple of 256 bytes)
     const uint32_t *d_rows() const { return d_units + n_units * bands * 2; }
+    int64_t device_bytes = 0;
+    bool built_on_device = false;  // whole, by spmm_strips_build_on_device
 };
 constexpr uint32_t STRIP_NO_ROW = 0xFFFFFFFFu;
 constexpr int STRIP_PARTS_SHIFT = 28;
@@ -72,6 +74,18 @@ inline double strip_time(const StripSizes &p, int64_t K, int64_t N, int64_t *gro
     }
     return best;
 }
+
+namespace strips {
+struct start;
+}
+// Builds the strips of A on the current device from host CSR arrays whose row pointer has been checked; the columns are
+// checked here.  N: the columns that the plan is for; begun: what it begins with, made here if it is empty.  Status codes
+// follow spmm_status_t; STRIPS_NOT_POSSIBLE: a row's columns are not in order, a row has 65536 entries or more, or there are more
+// units than a launch takes, or steps than a plan.
+constexpr int STRIPS_NOT_POSSIBLE = -1;
+int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N,
+                                strips::start &begun, StripPlan &out);
+void spmm_strips_release(StripPlan &p);  // however it was built
 
 // Enqueues C <- A x B.  Returns the hipError_t of the launch as int.
 int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N, float *C, void *stream);

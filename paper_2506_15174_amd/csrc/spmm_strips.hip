@@ -6,7 +6,6 @@
 #include <vector>
 
 #include "spmm_strips_build.h"
-#include "spmm_tiles.h"
 #include "spmm_upload.h"
 
 namespace {
@@ -552,19 +551,18 @@ __global__ __launch_bounds__(512) void value_kernel(const build_args args)
     }
 }
 
-hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, const strips::start *begun, TilePlan &out, int &status)
+hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N, strips::start &begun, StripPlan &p, int &status)
 {
     const int64_t nnz = row_ptr[M];
     hipError_t e;
 #define TRY(x) do { e = (x); if (e != hipSuccess) return e; } while (0)
-    StripPlan &p = out.strips;
     builder::workshop memory;
     builder::uploader upload;  // (released before the memory)
     const bool staged = upload.begin(K, col_idx, vals, nnz, memory.stream), narrow = staged && upload.narrow_columns();
     strips::band_sizes(K, p);
     const int64_t bands = p.bands;
     // 256 threads per four rows; 32 bytes of working memory per row and band
-    if (M > ((int64_t)1 << 26) - 8 || M * bands > (int64_t)1 << 26) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
+    if (M > ((int64_t)1 << 26) - 8 || M * bands > (int64_t)1 << 26) { status = STRIPS_NOT_POSSIBLE; return hipSuccess; }
     // (a unit has a row at least; the columns, and when they have been read the values in their place)
     const size_t at_words = memory.reserve((size_t)M * 24 + 1024), at_entries = memory.reserve((size_t)nnz * 4), at_sorted = memory.reserve((size_t)nnz * 4), at_classes = memory.reserve((size_t)(M * bands) * 32);
     TRY(memory.take());
@@ -576,17 +574,15 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     build_args a{reinterpret_cast<const int32_t *>(d_words + 8), memory.at<float>(at_entries), memory.at<uint32_t>(at_sorted), memory.at<uint32_t>(at_classes), staged ? upload.flags() : d_words, nullptr, nullptr,
                  d_words + front, reinterpret_cast<const u32x4 *>(d_words + front + list), nullptr, M, (uint32_t)nnz, 0, (int32_t)K, p.bands, p.band_rows, {}};
     // ---- while other threads fill the first pinned memory: the rows' order and the units
-    strips::start own;
-    if (!begun) own = strips::begin(M, K, row_ptr, N);
-    const strips::start &begin = begun ? *begun : own;
-    const std::vector<uint32_t> &order = begin.r.order;
-    const std::vector<strips::unit> &units = begin.units;
-    static_cast<StripSizes &>(p) = begin.sizes;
+    if (begun.units.empty()) begun = strips::begin(M, K, row_ptr, N);
+    const std::vector<uint32_t> &order = begun.r.order;
+    const std::vector<strips::unit> &units = begun.units;
+    static_cast<StripSizes &>(p) = begun.sizes;
     const int64_t n_units = (int64_t)units.size(), places = n_units * bands;
     const size_t n_words = strips::unit_words(n_units, bands);
-    const uint32_t longest = begin.r.length[0];
+    const uint32_t longest = begun.r.length[0];
     // an entry's number in its row in 16 bits; blocks of 512 threads
-    if (longest > 65535 || places >= (int64_t)1 << 23) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
+    if (longest > 65535 || places >= (int64_t)1 << 23) { status = STRIPS_NOT_POSSIBLE; return hipSuccess; }
     // flags, groups, the row pointer; the order; the units in four words each (unit_kernel)
     std::vector<uint32_t> words(front + list + (size_t)n_units * 4, 0u);
     std::copy(row_ptr, row_ptr + M + 1, words.begin() + 8);
@@ -612,7 +608,7 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     TRY(upload.look());
     // the plan's memory, once it is known how much; in bands the units wait in memory of their own
     auto take_plan = [&]() -> hipError_t {
-        if (groups >= (1ull << 32)) { status = TILES_NOT_POSSIBLE; return hipSuccess; }
+        if (groups >= (1ull << 32)) { status = STRIPS_NOT_POSSIBLE; return hipSuccess; }
         const hipError_t failed = hipMalloc(reinterpret_cast<void **>(&p.d_units), n_words * 4 + (size_t)groups * STRIP_GROUP_BYTES);
         if (failed != hipSuccess) return failed;
         a.units = p.d_units;
@@ -642,7 +638,7 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     uint32_t got[6] = {};  // flags, groups
     auto refused = [&] {
         const uint32_t *flags = staged ? upload.flags() : got;
-        status = flags[BAD_COLUMN] ? 2 : flags[BAD_ORDER] || flags[BAD_LENGTH] ? TILES_NOT_POSSIBLE : 0;
+        status = flags[BAD_COLUMN] ? 2 : flags[BAD_ORDER] || flags[BAD_LENGTH] ? STRIPS_NOT_POSSIBLE : 0;
         return status != 0;
     };
     if (bands > 1) {
@@ -673,8 +669,8 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     p.n_units = n_units;
     p.steps = (int64_t)groups * STRIP_STEPS;
     strips::launches(p, K);
-    out.device_bytes = (int64_t)((size_t)groups * STRIP_GROUP_BYTES + n_words * 4);
-    out.built = true;
+    p.device_bytes = (int64_t)((size_t)groups * STRIP_GROUP_BYTES + n_words * 4);
+    p.built_on_device = true;
     builder::staging.count_plan(1);
     status = 0;
     return hipSuccess;
@@ -704,16 +700,22 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
     return (int)hipGetLastError();
 }
 
-int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, TilePlan &out)
+int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N, strips::start &begun, StripPlan &out)
 {
-    const strips::start *begun = out.begun;
-    out = TilePlan();
+    out = StripPlan();
     int status = 0;
     const hipError_t e = build(M, K, row_ptr, col_idx, vals, N, begun, out, status);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         status = e == hipErrorOutOfMemory ? 3 : 4;
     }
-    if (status != 0) spmm_tiles_release(out);
+    if (status != 0) spmm_strips_release(out);
     return status;
+}
+
+void spmm_strips_release(StripPlan &p)
+{
+    if (p.d_units) (void)hipFree(p.d_units);
+    if (p.built_on_device) builder::staging.count_plan(-1);
+    p = StripPlan();
 }

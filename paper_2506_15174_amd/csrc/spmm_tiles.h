@@ -5,12 +5,6 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include "spmm_strips.h"
-
-namespace strips {
-struct start;
-}
-
 // Format.  The rows are taken in panels of `rows` = R (32, 16 or 8) consecutive rows of A, the
 // columns in steps of 16 * 64 / R columns.  The wave that multiplies a (panel, step) pair, a *block*,
 // gives it to 16 matrix operands t of one element per lane l:
@@ -33,8 +27,6 @@ struct TilePlan {
     bool built = false;             // whole
     bool exact_parts = false;       // R = 32: every value is the sum of three bf16 numbers
     float largest = 0.0f;           // R = 32: size of the largest value
-    StripPlan strips;               // the entries are in strips instead (rows = 0)
-    const strips::start *begun = nullptr;  // for the builder of strips, if the caller has it
 };
 
 constexpr int TILE_OPERANDS = 16;
@@ -44,19 +36,16 @@ constexpr int TILE_PLACE0 = 16;
 // checked; the columns are checked here.  Status codes follow spmm_status_t; TILES_NOT_POSSIBLE:
 // A cannot be stored this way (a column occurs twice in a row, more than 2^34 words of blocks, or
 // 2^26 rows or blocks and more: the builder's launches).
-// rows < 0: strips for products with -rows columns (TILES_NOT_POSSIBLE: a row's columns are not in order, or more units than a
-// launch takes, or steps than a plan).
 constexpr int TILES_NOT_POSSIBLE = -1;
 int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t rows,
                      TilePlan &out);
 void spmm_tiles_release(TilePlan &p);
-int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t N, TilePlan &out);
 
 // Estimated time of a product in us with panels of `rows` rows, and the column groups NB of a tile
 // (1, 2 or 4) it runs with.  density = share of the entries kept, peak = the largest such share of a panel.
 extern "C" double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB);
 
-// Enqueues C <- A x B, on tiles or on strips.  Returns the hipError_t of the launch as int.
+// Enqueues C <- A x B.  Returns the hipError_t of the launch as int.
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream);
 
 #endif

@@ -1269,7 +1269,6 @@ template <int R> hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, 
 
 int spmm_tiles_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t rows, TilePlan &out)
 {
-    if (rows < 0) return spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, -rows, out);
     out = TilePlan();
     out.rows = rows;
     const int64_t step = TILE_OPERANDS * 64 / rows;
@@ -1296,7 +1295,6 @@ void spmm_tiles_release(TilePlan &p)
 {
     if (p.d_stream) (void)hipFree(p.d_stream);
     if (p.d_offsets) (void)hipFree(p.d_offsets);
-    if (p.strips.d_units) (void)hipFree(p.strips.d_units);
     if (p.built) builder::staging.count_plan(-1);
     p = TilePlan();
 }
@@ -1338,7 +1336,6 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
 
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream)
 {
-    if (p.strips.n_units > 0) return spmm_strips_execute(p.strips, K, B, N, C, stream);
     tile_args a{p.d_stream, p.d_offsets, B, C, (uint64_t)K * (uint64_t)N * 4u, (int32_t)p.n_panels, (int32_t)p.n_steps, 1,
                 (int32_t)M, (int32_t)K, N, 0, p.largest};
     hipStream_t s = (hipStream_t)stream;

@@ -15,6 +15,7 @@
 
 #include "spmm.h"
 #include "spmm_kernels.h"
+#include "spmm_strips.h"
 #include "spmm_tiles.h"
 
 // ---- host memory: allocation number `fail_at` fails, and everything is counted
@@ -102,6 +103,25 @@ void spmm_tiles_release(TilePlan &p)
 {
     if (p.d_stream) (void)hipFree(p.d_stream);
     p = TilePlan();
+}
+
+static int strips_status = STRIPS_NOT_POSSIBLE;  // what the builder of strips on the device answers
+static int strips_asked = 0;                     // how often
+
+int spmm_strips_build_on_device(int64_t, int64_t, const int32_t *, const int32_t *, const float *, int64_t, strips::start &, StripPlan &out)
+{
+    out = StripPlan();
+    ++strips_asked;
+    if (strips_status != 0) return strips_status;
+    out.n_units = 1;
+    out.device_bytes = 64;
+    return hipMalloc(reinterpret_cast<void **>(&out.d_units), 64) == hipSuccess ? 0 : 3;
+}
+int spmm_strips_execute(const StripPlan &, int64_t, const float *, int32_t, float *, void *) { return 0; }
+void spmm_strips_release(StripPlan &p)
+{
+    if (p.d_units) (void)hipFree(p.d_units);
+    p = StripPlan();
 }
 
 // ---- inputs
