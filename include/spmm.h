@@ -158,8 +158,8 @@ typedef struct {
                               > 0 = use it (not together with other settings but n_hint and threads:
                               SPMM_ERR_INVALID_ARG; tiles > 0 goes first); < 0 = never; 0 = choose by shape, row lengths and
                               n_hint (never when another setting but n_hint and threads is given, tiles < 0 among them).
-                              A matrix with 2^28 rows or more or with a column stored millions of times
-                              in a row stays on chunks. */
+                              A matrix with 2^28 rows or more, with a column stored millions of times in a
+                              row, or whose strips find no room on the host or the device stays on chunks. */
 } spmm_options_t;
 
 /*

@@ -142,6 +142,34 @@ bool looks_in_order(int64_t M, const int32_t *row_ptr, const int32_t *col_idx)
     return true;
 }
 
+// Strips that the host builds, from rows in any order.  SPMM_OK and no units: A cannot be stored this way, or there is no room for
+// it, on the host or on the device; chunks need less of both.
+spmm_status_t strips_from_host(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals,
+                               const InspectorOptions &io, StripPlan &out)
+{
+    strips::host made;
+    try {
+        const int rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, made);
+        if (rc != 0) return (spmm_status_t)rc;
+    } catch (const std::bad_alloc &) {
+        return SPMM_OK;
+    }
+    if (made.plan.n_units == 0) return SPMM_OK;
+    const size_t front = strips::unit_words(made.plan.n_units, made.plan.bands), bytes = (front + made.stream.size()) * 4;
+    void *memory = nullptr;
+    const hipError_t e = hipMalloc(&memory, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return e == hipErrorOutOfMemory ? SPMM_OK : SPMM_ERR_HIP;
+    }
+    out = made.plan;  // its owner releases the memory
+    out.d_units = static_cast<uint32_t *>(memory);
+    out.d_stream = out.d_units + front;
+    out.device_bytes = (int64_t)bytes;
+    auto copy = [](uint32_t *to, const auto &words) { return words.empty() || hipMemcpy(to, words.data(), words.size() * 4, hipMemcpyHostToDevice) == hipSuccess; };
+    return copy(out.d_units, made.units) && copy(out.d_units + made.units.size(), made.rows) && copy(out.d_stream, made.stream) ? SPMM_OK : hip_fail();
+}
+
 struct plan_release {
     void operator()(spmm_plan *p) const
     {
@@ -201,7 +229,6 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
     plan.reset(new spmm_plan());
     spmm_plan *p = plan.get();
     int rc = 0;
-    strips::host strips;
     bool use_strips = opts.strips > 0 && tiles <= 0;
     if (use_strips && (schedule_forced || host_only)) return SPMM_ERR_INVALID_ARG;
     const bool checked = row_pointer_ok(M, K, row_ptr, col_idx, vals);
@@ -220,9 +247,9 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (rc == STRIPS_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
             rc = 0;
             if (instead > 0) tiles = instead;  // which the device builds from rows in any order
-            else rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, strips);
+            else rc = strips_from_host(M, K, row_ptr, col_idx, vals, io, p->strips);
         }
-        io.schedule_only = rc == 0 && (strips.plan.n_units > 0 || p->strips.n_units > 0);
+        io.schedule_only = p->strips.n_units > 0;
     }
     if (rc == 0 && !host_only && tiles > 0 && checked) {
         rc = spmm_tiles_build(M, K, row_ptr, col_idx, vals, tiles, p->tiles);
@@ -241,15 +268,6 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         spmm_status_t st = SPMM_OK;
         if (!p->on_chunks()) {
             p->device_bytes = p->tiles.device_bytes + p->strips.device_bytes;
-        } else if (strips.plan.n_units > 0) {
-            StripPlan &to = p->strips = strips.plan;
-            const size_t front = strips::unit_words(to.n_units, to.bands);
-            std::vector<uint32_t> words(front + strips.stream.size());
-            std::copy(strips.units.begin(), strips.units.end(), words.begin());
-            std::copy(strips.rows.begin(), strips.rows.end(), words.begin() + (ptrdiff_t)strips.units.size());
-            std::copy(strips.stream.begin(), strips.stream.end(), words.begin() + (ptrdiff_t)front);
-            st = upload(&to.d_units, words.data(), words.size() * 4, p->device_bytes);
-            to.d_stream = to.d_units + front;
         } else {
             // Scratch first: hipMemset may return before it is done, the copies behind it do not.
             if (h.n_cross_slots > 0) {

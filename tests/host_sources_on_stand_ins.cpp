@@ -186,6 +186,8 @@ static void fail_in_turn(const char *name, const csr &a, const spmm_options_t &o
     }
 }
 
+static csr spread(int64_t K, double sigma, int64_t M = 1024, double mean = 0.1);
+
 static void failures()
 {
     spmm_options_t o;
@@ -223,6 +225,48 @@ static void failures()
         tiles_status = 0;
         tiles_time = 1e9;
     }
+    {   // no room for the strips, on the device or on the host: chunks, also where strips were asked for
+        std::memset(&o, 0, sizeof o);
+        o.threads = 1;
+        o.n_hint = 128;
+        spmm_plan_t *p = nullptr;
+        spmm_plan_info_t info;
+        for (int asked : {0, 1}) {
+            const csr a = spread(asked ? 400 : 4096, 0.0, asked ? 300 : 4096, 0.05);
+            o.strips = asked;
+            REQUIRE(create(a, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.strip_units > 0);
+            REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+            for (int status : {STRIPS_NOT_POSSIBLE, (int)SPMM_ERR_ALLOC}) {
+                strips_status = status;
+                device_made = 0;
+                device_fail_at = 0;  // the first allocation is that of the strips
+                const spmm_status_t st = create(a, o, &p);
+                device_fail_at = -1;
+                REQUIRE(st == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK);
+                REQUIRE(info.strip_units == 0 && info.tile_rows == 0 && info.device_bytes > 0 && info.stream_words > 0);
+                REQUIRE(spmm_plan_destroy(p) == SPMM_OK && device_live == 0);
+            }
+            for (int status : {SPMM_ERR_HIP, SPMM_ERR_INVALID_CSR}) {  // anything else is reported
+                strips_status = status;
+                REQUIRE(create(a, o, &p) == (spmm_status_t)status && p == nullptr && device_live == 0);
+            }
+            strips_status = STRIPS_NOT_POSSIBLE;
+        }
+        const csr a = spread(400, 0.0, 300, 0.05);
+        fail_in_turn("strips", a, o);
+        long on_chunks = 0;
+        for (long n = 0; on_chunks == 0; ++n) {
+            made = 0;
+            fail_at = n;
+            const spmm_status_t st = create(a, o, &p);
+            fail_at = -1;
+            REQUIRE(made > n);  // or no failure of the host's builder led to chunks
+            if (st != SPMM_OK) continue;
+            REQUIRE(spmm_plan_describe(p, &info) == SPMM_OK);
+            on_chunks += info.strip_units == 0;
+            REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+        }
+    }
     {   // a compute unit held to two workgroups (more than 512 of them)
         const csr uneven = matrix(1090, 2048, 16, 40);
         std::memset(&o, 0, sizeof o);
@@ -253,7 +297,7 @@ static void failures()
 }
 
 // A matrix whose row lengths spread by `sigma` (lognormal).
-static csr spread(int64_t K, double sigma, int64_t M = 1024, double mean = 0.1)
+static csr spread(int64_t K, double sigma, int64_t M, double mean)
 {
     csr a{M, K};
     uint64_t state = 12345;
