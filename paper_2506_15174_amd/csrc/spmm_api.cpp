@@ -145,11 +145,11 @@ bool looks_in_order(int64_t M, const int32_t *row_ptr, const int32_t *col_idx)
 // Strips that the host builds, from rows in any order.  SPMM_OK and no units: A cannot be stored this way, or there is no room for
 // it, on the host or on the device; chunks need less of both.
 spmm_status_t strips_from_host(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals,
-                               const InspectorOptions &io, StripPlan &out)
+                               const InspectorOptions &io, strips::start &begun, StripPlan &out)
 {
     strips::host made;
     try {
-        const int rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, made);
+        const int rc = spmm_strips_build(M, K, row_ptr, col_idx, vals, io.n_hint, io.threads, begun, made);
         if (rc != 0) return (spmm_status_t)rc;
     } catch (const std::bad_alloc &) {
         return SPMM_OK;
@@ -247,7 +247,7 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         if (rc == STRIPS_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
             rc = 0;
             if (instead > 0) tiles = instead;  // which the device builds from rows in any order
-            else rc = strips_from_host(M, K, row_ptr, col_idx, vals, io, p->strips);
+            else if (!begun.beaten) rc = strips_from_host(M, K, row_ptr, col_idx, vals, io, begun, p->strips);
         }
         io.schedule_only = p->strips.n_units > 0;
     }

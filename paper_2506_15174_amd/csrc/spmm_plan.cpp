@@ -596,18 +596,20 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint,
     // As for tiles mostly the launch's time; but chunks take two column tiles beyond 128 columns.
     if (nnz == 0 || (nnz < ((int64_t)1 << 17) && n_hint <= 128)) return false;
     const int32_t hinted[] = {std::min(std::max(n_hint, 4), 256)}, unknown[] = {16, 64, 200};
-    const int widths = n_hint > 0 ? 1 : 3;
-    double others[3], margin = 10.0;
-    for (int i = 0; i < widths; ++i) {
+    strips::rivals &others = begun.others;
+    others.n = n_hint > 0 ? 1 : 3;
+    double margin = 10.0;
+    for (int i = 0; i < others.n; ++i) {
         const int32_t N = n_hint > 0 ? hinted[i] : unknown[i];
+        others.N[i] = N;
         if (rows > 0) {
             int NB = 1;
-            others[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (rows == 8 ? 0.65 : n_hint > 0 ? 1.0 : 0.95);
+            others.us[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (rows == 8 ? 0.65 : n_hint > 0 ? 1.0 : 0.95);
             if (rows == 32 && NB > 1) return false;
         } else {
-            others[i] = chunks_time(M, K, row_ptr, n_hint, N) * (n_hint > 0 && N <= 16 ? 0.87 : 1.0);
+            others.us[i] = chunks_time(M, K, row_ptr, n_hint, N) * (n_hint > 0 && N <= 16 ? 0.87 : 1.0);
         }
-        margin = std::min(margin, others[i] / strips::time_at_best(M, K, nnz, N));
+        margin = std::min(margin, others.us[i] / strips::time_at_best(M, K, nnz, N));
     }
     if (margin <= 1.0) return false;
     // Rows of about one length take 1.0 times what they take at best, 1.25 times in one product of a hundred: no need to look at the units,
@@ -615,14 +617,12 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint,
     int64_t longest = 0;
     for (int64_t i = 0; i < M; ++i) longest = std::max<int64_t>(longest, row_ptr[i + 1] - row_ptr[i]);
     if (margin > 1.25 && longest * M <= 2 * nnz) return true;
-    begun = strips::begin(M, K, row_ptr, strips::columns_for(n_hint));
-    for (int i = 0; i < widths; ++i)
-        if (strip_time(begun.sizes, K, n_hint > 0 ? hinted[i] : unknown[i], nullptr) >= others[i]) return false;
-    return true;
+    strips::begin(M, K, row_ptr, strips::columns_for(n_hint), begun);
+    return !others.faster_than(begun.sizes, K);
 }
 
 int spmm_strips_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t n_hint, int32_t asked,
-                      strips::host &out)
+                      strips::start &begun, strips::host &out)
 {
     const int threads = worker_count(row_ptr[M], asked);
     if (!columns_ok(K, row_ptr, col_idx, M, threads)) return ST_INVALID_CSR;
@@ -649,7 +649,7 @@ int spmm_strips_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_
         for (std::thread &o : others) o.join();
         if (failed) throw std::bad_alloc();
     };
-    if (!strips::build(M, K, row_ptr, col_idx, vals, strips::columns_for(n_hint), over, out)) out = strips::host();
+    if (!strips::build(M, K, row_ptr, col_idx, vals, strips::columns_for(n_hint), over, begun, out)) out = strips::host();
     return ST_OK;
 }
 

@@ -84,7 +84,7 @@ struct start;
 // instead of chunks (rows = 0) or of tiles of so many rows; `begun`: what the plan begins with, if that has been looked at
 bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, int rows, strips::start &begun);
 int spmm_strips_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t n_hint, int32_t threads,
-                      strips::host &out);
+                      strips::start &begun, strips::host &out);
 
 // Rows per panel (32, 16 or 8) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.
 int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint);

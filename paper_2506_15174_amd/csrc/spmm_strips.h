@@ -32,7 +32,7 @@ inline int strip_lane(int c, int i, int odd)
 
 struct StripSizes {
     int64_t n_units = 0;            // 0 = the plan holds no strips
-    int64_t steps = 0, longest = 0;  // of all units, of one
+    int64_t steps = 0, longest = 0;  // of all units, of one (as the rows' lengths tell, until the entries in every band have been counted)
     int32_t bands = 1, band_rows = 0;
 };
 struct StripPlan : StripSizes {
@@ -80,8 +80,8 @@ struct start;
 }
 // Builds the strips of A on the current device from host CSR arrays whose row pointer has been checked; the columns are
 // checked here.  N: the columns that the plan is for; begun: what it begins with, made here if it is empty.  Status codes
-// follow spmm_status_t; STRIPS_NOT_POSSIBLE: a row's columns are not in order, a row has 65536 entries or more, or there are more
-// units than a launch takes, or steps than a plan.
+// follow spmm_status_t; STRIPS_NOT_POSSIBLE: a row's columns are not in order, a row has 65536 entries or more, there are more
+// units than a launch takes, or steps than a plan, or what the strips have to beat is faster (begun.beaten).
 constexpr int STRIPS_NOT_POSSIBLE = -1;
 int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N,
                                 strips::start &begun, StripPlan &out);

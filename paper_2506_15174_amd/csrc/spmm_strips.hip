@@ -365,10 +365,12 @@ __global__ __launch_bounds__(64) void unit_kernel(const build_args args)
     }
 }
 
-// One workgroup: where the groups of every unit in a band begin; how many there are.
-__global__ __launch_bounds__(1024) void begin_kernel(uint32_t *units, uint32_t n, uint64_t *total)
+// One workgroup: where the groups of every unit in a band begin; how many there are, and (behind) how many a unit has at most.
+__global__ __launch_bounds__(1024) void begin_kernel(uint32_t *units, uint32_t n, uint32_t bands, uint64_t *total)
 {
     __shared__ uint64_t sums[1024];
+    __shared__ uint32_t longest;
+    if (threadIdx.x == 0) longest = 0;
     const uint32_t share = (n + 1023) / 1024, first = min(n, threadIdx.x * share), end = min(n, first + share);
     uint64_t sum = 0;
     for (uint32_t k = first; k < end; ++k) sum += units[(size_t)k * 2 + 1];
@@ -385,7 +387,18 @@ __global__ __launch_bounds__(1024) void begin_kernel(uint32_t *units, uint32_t n
         units[(size_t)k * 2] = (uint32_t)at;
         at += units[(size_t)k * 2 + 1];
     }
-    if (threadIdx.x == 1023) *total = sums[1023];
+    uint32_t most = 0;
+    for (uint32_t k = threadIdx.x * bands; k < n; k += 1024 * bands) {
+        uint32_t of_unit = 0;
+        for (uint32_t b = 0; b < bands; ++b) of_unit += units[(size_t)(k + b) * 2 + 1];
+        most = max(most, of_unit);
+    }
+    atomicMax(&longest, most);
+    __syncthreads();
+    if (threadIdx.x == 1023) {
+        total[0] = sums[1023];
+        total[1] = longest;
+    }
 }
 
 // One wave per unit in a band.  Eight threads next to each other are the lanes that must not collide; what they propose goes around
@@ -569,12 +582,12 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     const hipStream_t s = memory.stream;
     int32_t *d_col = memory.at<int32_t>(at_entries);
     uint32_t *d_words = memory.at<uint32_t>(at_words);
-    uint64_t *answer = reinterpret_cast<uint64_t *>(d_words) + 2;  // behind four words of flags: groups
+    uint64_t *answer = reinterpret_cast<uint64_t *>(d_words) + 2;  // behind four words of flags: groups, those of the longest unit
     const size_t front = ((size_t)M + 9 + 63) / 64 * 64, list = ((size_t)M + 3) / 4 * 4;
     build_args a{reinterpret_cast<const int32_t *>(d_words + 8), memory.at<float>(at_entries), memory.at<uint32_t>(at_sorted), memory.at<uint32_t>(at_classes), staged ? upload.flags() : d_words, nullptr, nullptr,
                  d_words + front, reinterpret_cast<const u32x4 *>(d_words + front + list), nullptr, M, (uint32_t)nnz, 0, (int32_t)K, p.bands, p.band_rows, {}};
     // ---- while other threads fill the first pinned memory: the rows' order and the units
-    if (begun.units.empty()) begun = strips::begin(M, K, row_ptr, N);
+    strips::begin(M, K, row_ptr, N, begun);
     const std::vector<uint32_t> &order = begun.r.order;
     const std::vector<strips::unit> &units = begun.units;
     static_cast<StripSizes &>(p) = begun.sizes;
@@ -635,18 +648,22 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     a.rows = a.units + places * 2;
     hipLaunchKernelGGL(unit_kernel, dim3((unsigned)n_units), dim3(64), 0, s, a);
     TRY(hipGetLastError());
-    uint32_t got[6] = {};  // flags, groups
+    uint32_t got[8] = {};  // flags, groups, those of the longest unit
     auto refused = [&] {
         const uint32_t *flags = staged ? upload.flags() : got;
         status = flags[BAD_COLUMN] ? 2 : flags[BAD_ORDER] || flags[BAD_LENGTH] ? STRIPS_NOT_POSSIBLE : 0;
         return status != 0;
     };
     if (bands > 1) {
-        hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1024), 0, s, a.units, (uint32_t)places, answer);
+        hipLaunchKernelGGL(begin_kernel, dim3(1), dim3(1024), 0, s, a.units, (uint32_t)places, (uint32_t)bands, answer);
         TRY(hipGetLastError());
         TRY(hipMemcpyWithStream(got, d_words, sizeof got, hipMemcpyDeviceToHost, s));
         if (refused()) return hipSuccess;
         std::memcpy(&groups, got + 4, 8);
+        p.steps = (int64_t)groups * STRIP_STEPS;
+        p.longest = (int64_t)got[6] * STRIP_STEPS;
+        begun.beaten = begun.others.faster_than_counted(p, K);
+        if (begun.beaten) { status = STRIPS_NOT_POSSIBLE; return hipSuccess; }
         TRY(take_plan());
         if (status) return hipSuccess;
         TRY(hipMemcpyAsync(a.units, waiting.p, n_words * 4, hipMemcpyDeviceToDevice, s));

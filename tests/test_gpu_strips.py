@@ -133,6 +133,13 @@ def test_when_strips_are_chosen(torch_gpu):  # noqa: F811
         assert info["tile_rows"] == rows and (info["strip_units"] > 0) == (rows == 0)
     csr.col_idx[:2] = csr.col_idx[1::-1]
     assert spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=64).describe()["tile_rows"] == 16
+    # not where the rows' entries lie together, so that most lanes wait in most bands of columns
+    for apart in (True, False):
+        csr = gen.uniform_positions(2048, 16384 if apart else 4096, 0.9 if apart else 0.6, 4)
+        if not apart:
+            csr = gen.Csr(2048, 16384, csr.row_ptr, csr.col_idx + 4096 * np.repeat(np.arange(2048) * 7919 % 4, np.diff(csr.row_ptr)).astype(np.int32), csr.vals)
+        info = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=200).describe()
+        assert info["tile_rows"] == 0 and (info["strip_units"] > 0) == apart
     csr = gen.uniform_positions(2048, 4096, 0.5, 3)
     assert spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=256).describe()["tile_rows"] == 32
     assert spmm.plan_create(40, 60, np.zeros(41), [], [], strips=1).describe()["strip_units"] == 0   # no entry at all
