@@ -132,16 +132,6 @@ bool row_pointer_ok(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t 
     return true;
 }
 
-// Whether the first columns of 64 rows at even distances are in order: the builder of strips on the device refuses rows that are not, after
-// the upload (0.8 ms for 3.4 million entries).
-bool looks_in_order(int64_t M, const int32_t *row_ptr, const int32_t *col_idx)
-{
-    for (int64_t i = 0; i < M; i += (M + 63) / 64)
-        for (int64_t q = (int64_t)row_ptr[i] + 1; q < std::min<int64_t>(row_ptr[i + 1], (int64_t)row_ptr[i] + 16); ++q)
-            if (col_idx[q] < col_idx[q - 1]) return false;
-    return true;
-}
-
 // Strips that the host builds, from rows in any order.  SPMM_OK and no units: A cannot be stored this way, or there is no room for
 // it, on the host or on the device; chunks need less of both.
 spmm_status_t strips_from_host(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals,
@@ -236,14 +226,15 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
     int32_t instead = 0;  // tiles that strips take the place of
     if (!host_only && tiles == 0 && !use_strips && !schedule_forced && checked) {
         tiles = choose_tiles(M, K, row_ptr, io.n_hint);
-        if (opts.strips == 0 && choose_strips(M, K, row_ptr, io.n_hint, tiles, begun)) {
+        if (opts.strips == 0 && choose_strips(M, K, row_ptr, col_idx, io.n_hint, tiles, begun)) {
             use_strips = true;
             instead = tiles;
             tiles = 0;
         }
     }
     if (use_strips && checked && row_ptr[M] > 0) {
-        rc = looks_in_order(M, row_ptr, col_idx) ? spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, strips::columns_for(io.n_hint), begun, p->strips) : STRIPS_NOT_POSSIBLE;
+        if (opts.strips > 0) look_at_columns(M, row_ptr, col_idx, begun);
+        rc = begun.in_order ? spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, strips::columns_for(io.n_hint), begun, p->strips) : STRIPS_NOT_POSSIBLE;
         if (rc == STRIPS_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
             rc = 0;
             if (instead > 0) tiles = instead;  // which the device builds from rows in any order

@@ -579,6 +579,41 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
     return rows;
 }
 
+// What 64 rows at even distances show, in four runs of 16 entries each: whether the columns are in order, which the builder of strips on the
+// device asks for and finds out after the upload (0.8 ms for 3.4 million entries; rows out of order elsewhere still cost that), and
+// whether the lanes that read LDS together can read different banks, which they can where their columns differ modulo 8.  Of 64 entries
+// (shorter rows together) one such class holds 0.20 on average where the columns are anyhow, 0.32 where all are even, 0.55 where
+// all are multiples of four and all where they are multiples of eight.  4096 x 4096, 95 % pruned, 128 columns: 12.3, 14.2, 19.2 and 28.4 us on
+// strips, 17.1 on chunks; without the 6.1 us that a product without steps takes that is 0.65 + 0.36 times the reads of a bank.
+// Of 47 products whose columns are multiples of four or eight (or those and the row's number) 30 went to strips without this, 5 of them do with it,
+// which take 0.72 of the time; the others would take 1.27 times as long, 2.8 at worst.
+void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, strips::start &begun)
+{
+    constexpr int64_t ROWS = 64, RUNS = 4, RUN = 16;
+    int64_t of_class[8] = {}, seen = 0, blocks = 0;
+    double shares = 0.0;
+    begun.in_order = true;
+    for (int64_t i = 0; i < M; i += (M + ROWS - 1) / ROWS) {
+        const int64_t first = row_ptr[i], end = row_ptr[i + 1];
+        for (int64_t k = 0, from = first; k < RUNS && from < end; ++k) {
+            const int64_t to = end - first <= RUNS * RUN ? end : from + RUN;
+            for (int64_t q = from; q < to; ++q) {
+                if (q > first && col_idx[q] < col_idx[q - 1]) begun.in_order = false;
+                ++of_class[col_idx[q] & 7];
+            }
+            seen += to - from;
+            from = to == end ? end : first + (end - first - RUN) * (k + 1) / (RUNS - 1);
+        }
+        if (seen < RUNS * RUN) continue;
+        shares += (double)*std::max_element(of_class, of_class + 8) / (double)seen;
+        ++blocks;
+        std::fill(of_class, of_class + 8, (int64_t)0);
+        seen = 0;
+    }
+    const double share = blocks > 0 ? shares / (double)blocks : 0.0;
+    begun.others.crowding = share > 0.4 ? 0.65 + 0.36 * 8.0 * share : 1.0;
+}
+
 // Strips take the place of the chunks or the tiles (`rows` a panel) that would be chosen where they are estimated to be faster, without a hint
 // at each of three widths.  Of 1200 random products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256
 // columns, one in three without a hint):
@@ -590,7 +625,7 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
 // narrow strips, whose copy of B is short of bytes in flight, take up to 1.3 times what is estimated (4096 x 4096, 80 % pruned, 4 columns 6.3 us on tiles, 7.3 on
 // strips; 2048 x 2048, 90 %, 8 columns 3.5 on chunks, 3.7 on strips), and chunks up to 0.85 times.  What still moves gains: 16384 x 1024, 75 %, 8 columns 10.8 -> 7.4 us,
 // 16000 x 700, 60 % in Zipf rows, 6 columns 10.8 -> 7.6, 9000 x 3000, 85 %, 10 columns 17.1 -> 7.9.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
-bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, int rows, strips::start &begun)
+bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, strips::start &begun)
 {
     const int64_t nnz = row_ptr[M];
     // As for tiles mostly the launch's time; but chunks take two column tiles beyond 128 columns.
@@ -612,11 +647,13 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint,
         margin = std::min(margin, others.us[i] / strips::time_at_best(M, K, nnz, N));
     }
     if (margin <= 1.0) return false;
+    look_at_columns(M, row_ptr, col_idx, begun);
+    if (rows > 0 && !begun.in_order) return false;  // tiles are built on the device from rows in any order
     // Rows of about one length take 1.0 times what they take at best, 1.25 times in one product of a hundred: no need to look at the units,
     // which the builder finds while the entries travel (0.05 ms of the 0.9 that plan and product of 4096 x 4096, 80 % pruned, take).
     int64_t longest = 0;
     for (int64_t i = 0; i < M; ++i) longest = std::max<int64_t>(longest, row_ptr[i + 1] - row_ptr[i]);
-    if (margin > 1.25 && longest * M <= 2 * nnz) return true;
+    if (begun.others.crowding == 1.0 && margin > 1.25 && longest * M <= 2 * nnz) return true;
     strips::begin(M, K, row_ptr, strips::columns_for(n_hint), begun);
     return !others.faster_than(begun.sizes, K);
 }

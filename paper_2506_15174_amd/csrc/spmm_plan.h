@@ -81,8 +81,9 @@ namespace strips {
 struct host;
 struct start;
 }
-// instead of chunks (rows = 0) or of tiles of so many rows; `begun`: what the plan begins with, if that has been looked at
-bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, int rows, strips::start &begun);
+// instead of chunks (rows = 0) or of tiles of so many rows; `begun`: what the plan begins with, as far as it has been looked at
+bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, strips::start &begun);
+void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, strips::start &begun);
 int spmm_strips_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t n_hint, int32_t threads,
                       strips::start &begun, strips::host &out);
 

@@ -126,9 +126,12 @@ struct rivals {
     int n = 0;
     int64_t N[MOST] = {};
     double us[MOST] = {};
+    double crowding = 1.0;  // how much longer a step takes than the estimate says (look_at_columns)
     // Whether strips of these sizes are slower at one of the widths.
-    bool faster_than(const StripSizes &p, int64_t K) const
+    bool faster_than(StripSizes p, int64_t K) const
     {
+        p.steps = (int64_t)((double)p.steps * crowding);
+        p.longest = (int64_t)((double)p.longest * crowding);
         for (int i = 0; i < n; ++i)
             if (strip_time(p, K, N[i], nullptr) > us[i]) return true;
         return false;
@@ -152,6 +155,7 @@ struct start {
     std::vector<unit> units;  // none: not looked at yet
     StripSizes sizes;
     rivals others;
+    bool in_order = true;     // the columns of the rows that look_at_columns saw
     bool beaten = false;  // by them, when the strips in bands had been counted
 };
 inline void begin(int64_t M, int64_t K, const int32_t *row_ptr, int64_t N, start &s)

@@ -1,6 +1,7 @@
 // The library's host sources on stand-ins: tests/test_host_sources.py compiles them together with this file, in
 // which the HIP runtime and the kernels' entry points are stand-ins in host memory.
 //   failures   every allocation of a plan's creation is made to fail in turn, also those on the device
+//   choices    which matrices are left to chunks that strips would take by the lengths of their rows
 //   launches   what spmm_execute hands to the launcher
 //   places     what the workgroups of a launch compute
 #include <hip/hip_runtime_api.h>
@@ -316,6 +317,46 @@ static csr spread(int64_t K, double sigma, int64_t M, double mean)
     return a;
 }
 
+static bool on_strips(const csr &a, int n_hint, int strips = 0)
+{
+    spmm_options_t o;
+    std::memset(&o, 0, sizeof o);
+    o.n_hint = n_hint;
+    o.strips = strips;
+    o.threads = 8;
+    spmm_plan_t *p = nullptr;
+    spmm_plan_info_t info;
+    REQUIRE(create(a, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.tile_rows == 0);
+    REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+    return info.strip_units > 0;
+}
+
+// The matrix with its column c as column c * by + i % turn of row i.
+static csr stretched(csr a, int by, int turn = 1)
+{
+    a.K *= by;
+    for (int64_t i = 0; i < a.M; ++i)
+        for (int32_t q = a.row_ptr[(size_t)i]; q < a.row_ptr[(size_t)i + 1]; ++q) a.col_idx[(size_t)q] = a.col_idx[(size_t)q] * by + (int32_t)(i % turn);
+    return a;
+}
+
+// The builder on the device refuses everything here (STRIPS_NOT_POSSIBLE), so the host's makes the strips.
+static void choices()
+{
+    const csr even = spread(4096, 0.0, 4096, 0.05);
+    REQUIRE(on_strips(even, 128));
+    // columns of which many are the same modulo 8 collide in LDS
+    for (int by : {2, 4, 8}) {
+        const csr a = stretched(spread(4096 / by, 0.0, 4096, 0.05 * by), by);
+        REQUIRE(on_strips(a, 128) == (by == 2) && on_strips(a, 128, 1));
+    }
+    REQUIRE(!on_strips(stretched(spread(512, 0.0, 4096, 0.4), 8, 8), 128));
+    // ... but where chunks take twice as long as strips those may take half as long again
+    REQUIRE(on_strips(stretched(spread(628, 0.3, 3001, 0.6), 4), 200));
+    // short rows, eight entries on average, are looked at together
+    REQUIRE(on_strips(spread(512, 0.0, 32768, 0.016), 200) && !on_strips(stretched(spread(64, 0.0, 32768, 0.125), 8), 200));
+}
+
 // spmm_execute's launches of a chunk plan of `a`, made for 64 columns, on N columns.
 static std::vector<spmm_launch_args> launches(const csr &a, int N, spmm_plan_info_t *info)
 {
@@ -413,6 +454,7 @@ int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "failures")) failures();
+    else if (!std::strcmp(what, "choices")) choices();
     else if (!std::strcmp(what, "launches")) held_to_two();
     else if (!std::strcmp(what, "places")) places();
     else return 2;

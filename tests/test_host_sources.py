@@ -30,6 +30,10 @@ def test_failed_allocations_are_a_status(program):
     passes(program, "failures")
 
 
+def test_which_path_is_chosen(program):
+    passes(program, "choices")
+
+
 def test_compute_units_held_to_two_workgroups(program):
     passes(program, "launches")
 
