@@ -225,8 +225,9 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
     strips::start begun;
     int32_t instead = 0;  // tiles that strips take the place of
     if (!host_only && tiles == 0 && !use_strips && !schedule_forced && checked) {
-        tiles = choose_tiles(M, K, row_ptr, io.n_hint);
-        if (opts.strips == 0 && choose_strips(M, K, row_ptr, col_idx, io.n_hint, tiles, begun)) {
+        chunk_estimate chunks;
+        tiles = choose_tiles(M, K, row_ptr, io.n_hint, chunks);
+        if (opts.strips == 0 && choose_strips(M, K, row_ptr, col_idx, io.n_hint, tiles, chunks, begun)) {
             use_strips = true;
             instead = tiles;
             tiles = 0;

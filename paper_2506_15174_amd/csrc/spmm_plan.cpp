@@ -509,7 +509,7 @@ std::vector<int64_t> range_cuts(const std::vector<Group> &groups, int want)
 // a plan cut along K or across workgroups, and the chunks of the longest piece of a panel cut into eight
 // (hundreds), the tail of the launch where rows are of uneven length.  Against those 600 products the rms error is
 // 13 % (0.53 to 1.41 of the time).
-static double chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
+double chunk_estimate::time(double N) const
 {
     static const double weights[5][8] = {{2.90, 6.86, 9.60, 0.0, 68.0, 0.0, 4.63, 0.0},   // n_hint <= 8
                                          {2.99, 6.08, 0.0, 0.24, 29.5, 0.0, 5.97, 0.0},   // ... 16
@@ -517,34 +517,40 @@ static double chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t 
                                          {2.79, 13.4, 0.0, 0.56, 3.20, 0.0, 6.97, 5.99},  // ... 64
                                          {2.97, 22.1, 0.0, 0.70, 0.74, 1.73, 12.3, 15.2}};  // more, or unknown
     const double *w = weights[N <= 8 ? 0 : N <= 16 ? 1 : N <= 32 ? 2 : N <= 64 ? 3 : 4];
-    // the schedule the chunks would get, but for details
+    const int tile = ufk == 8 ? (N > 64 ? 128 : 64) : ufk == 16 ? 32 : ufk == 32 ? 16 : N > 4 ? 8 : 4;
+    const double tiles = std::ceil(N / tile) * 1e-6, per_load = 256.0 / tile;
+    return w[0] + tiles * (w[1] * fetched / per_load + w[2] * 4.2 * nnz / per_load + w[3] * (4.0 * fetched + 4.2 * nnz) + w[4] * fetched / ufk * std::sqrt((double)ufi)) +
+           (slices > 1 ? w[5] : 0.0) + (cross ? w[7] : w[6] * 1e-2 * longest / (8.0 * ufk * slices));
+}
+
+// The schedule that the chunks would get, but for details.
+static chunk_estimate look_at_chunks(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
+{
     const int64_t nnz = row_ptr[M];
     const bool skewed = skewed_rows(row_ptr, M, nnz);
-    const int ufk = choose_ufk(K, n_hint), slices = choose_kslices(0, M, K, nnz, n_hint, ufk);
-    const bool cross = slices == 1 && cross_allowed(0, skewed, nnz, n_hint);
+    chunk_estimate e;
+    e.nnz = (double)nnz;
+    e.ufk = choose_ufk(K, n_hint);
+    const int slices = e.slices = choose_kslices(0, M, K, nnz, n_hint, e.ufk);
+    const bool cross = e.cross = slices == 1 && cross_allowed(0, skewed, nnz, n_hint);
     std::vector<int32_t> len((size_t)M);
     for (int64_t i = 0; i < M; ++i) len[(size_t)i] = row_ptr[i + 1] - row_ptr[i];
     const int64_t columns = (K + slices - 1) / slices, max_row = *std::max_element(len.begin(), len.end()) / slices;
-    const int ufi = skewed ? choose_ufi_skewed(columns, nnz, max_row, n_hint, cross) : choose_ufi(M, columns, nnz, n_hint);
+    const int ufi = e.ufi = skewed ? choose_ufi_skewed(columns, nnz, max_row, n_hint, cross) : choose_ufi(M, columns, nnz, n_hint);
     if (skewed && ufi > 1) std::sort(len.begin(), len.end(), std::greater<int32_t>());
-    double fetched = 0.0, longest = 0.0;  // rows of B for one column tile: of all panels, of one
     for (int64_t i = 0; i < M; i += ufi) {
         double absent = 1.0;
         for (int64_t r = i; r < std::min<int64_t>(M, i + ufi); ++r) absent *= 1.0 - (double)len[(size_t)r] / (double)K;
-        fetched += (double)K * (1.0 - absent);
-        longest = std::max(longest, (double)K * (1.0 - absent));
+        e.fetched += (double)K * (1.0 - absent);
+        e.longest = std::max(e.longest, (double)K * (1.0 - absent));
     }
-    const int tile = ufk == 8 ? (N > 64 ? 128 : 64) : ufk == 16 ? 32 : ufk == 32 ? 16 : N > 4 ? 8 : 4;
-    const double tiles = std::ceil(N / tile) * 1e-6, per_load = 256.0 / tile;
-    return w[0] + tiles * (w[1] * fetched / per_load + w[2] * 4.2 * (double)nnz / per_load + w[3] * (4.0 * fetched + 4.2 * (double)nnz) +
-                           w[4] * fetched / ufk * std::sqrt((double)ufi)) +
-           (slices > 1 ? w[5] : 0.0) + (cross ? w[7] : w[6] * 1e-2 * longest / (8.0 * ufk * slices));
+    return e;
 }
 
 double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N)
 {
     try {
-        return chunks_time(M, K, row_ptr, n_hint, N);
+        return look_at_chunks(M, K, row_ptr, n_hint).time(N);
     } catch (...) {  // no memory for the rows' lengths
         return -1.0;
     }
@@ -559,14 +565,15 @@ static double tiles_time(int r, int64_t M, int64_t K, const int32_t *row_ptr, in
     return spmm_tiles_time(r, M, K, N, density, std::max(density, (double)heaviest / ((double)r * (double)K)), NB);
 }
 
-int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint)
+int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, chunk_estimate &chunks)
 {
     const int64_t nnz = row_ptr[M];
     const double density = (double)nnz / ((double)M * (double)K);
     if (density < 0.03) return 0;           // below all that was measured
     if (nnz < ((int64_t)1 << 17)) return 0;  // mostly the launch's time: 1.5 % on average to gain
     const double N = n_hint <= 0 ? 128 : std::min(std::max(n_hint, 4), 256);
-    double best = 0.95 * chunks_time(M, K, row_ptr, n_hint, N);
+    chunks = look_at_chunks(M, K, row_ptr, n_hint);
+    double best = 0.95 * chunks.time(N);
     int rows = 0;
     for (int r : {8, 16, 32}) {
         if (r == 8 && N > 64) continue;  // its tiles are 16 columns wide: too small a part of every row of B
@@ -625,7 +632,7 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 // narrow strips, whose copy of B is short of bytes in flight, take up to 1.3 times what is estimated (4096 x 4096, 80 % pruned, 4 columns 6.3 us on tiles, 7.3 on
 // strips; 2048 x 2048, 90 %, 8 columns 3.5 on chunks, 3.7 on strips), and chunks up to 0.85 times.  What still moves gains: 16384 x 1024, 75 %, 8 columns 10.8 -> 7.4 us,
 // 16000 x 700, 60 % in Zipf rows, 6 columns 10.8 -> 7.6, 9000 x 3000, 85 %, 10 columns 17.1 -> 7.9.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
-bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, strips::start &begun)
+bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, chunk_estimate chunks, strips::start &begun)
 {
     const int64_t nnz = row_ptr[M];
     // As for tiles mostly the launch's time; but chunks take two column tiles beyond 128 columns.
@@ -642,7 +649,8 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *
             others.us[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (rows == 8 ? 0.65 : n_hint > 0 ? 1.0 : 0.95);
             if (rows == 32 && NB > 1) return false;
         } else {
-            others.us[i] = chunks_time(M, K, row_ptr, n_hint, N) * (n_hint > 0 && N <= 16 ? 0.87 : 1.0);
+            if (chunks.ufk == 0) chunks = look_at_chunks(M, K, row_ptr, n_hint);
+            others.us[i] = chunks.time(N) * (n_hint > 0 && N <= 16 ? 0.87 : 1.0);
         }
         margin = std::min(margin, others.us[i] / strips::time_at_best(M, K, nnz, N));
     }

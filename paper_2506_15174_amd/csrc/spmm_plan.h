@@ -71,6 +71,14 @@ struct InspectorOptions {
 int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx,
                  const float *vals, const InspectorOptions &opts, HostPlan &out);
 
+// What the estimated time on chunks depends on beside the width; ufk = 0: not looked at yet (which takes a sort of uneven rows).
+struct chunk_estimate {
+    int ufk = 0, ufi = 1, slices = 1;
+    bool cross = false;
+    double nnz = 0.0, fetched = 0.0, longest = 0.0;  // entries; rows of B for one column tile: of all panels, of one
+    double time(double N) const;
+};
+
 // Estimated time in us of a product with N columns of B on the chunk plan made for n_hint columns, for
 // bench.py, which sets it beside measured times; -1 where there is no memory for it.
 extern "C" double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N);
@@ -82,12 +90,14 @@ struct host;
 struct start;
 }
 // instead of chunks (rows = 0) or of tiles of so many rows; `begun`: what the plan begins with, as far as it has been looked at
-bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, strips::start &begun);
+bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, chunk_estimate chunks,
+                   strips::start &begun);
 void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, strips::start &begun);
 int spmm_strips_build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int32_t n_hint, int32_t threads,
                       strips::start &begun, strips::host &out);
 
-// Rows per panel (32, 16 or 8) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.
-int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint);
+// Rows per panel (32, 16 or 8) of the matrix-core path (spmm_tiles.h), 0 = this matrix stays on chunks.  chunks: what that
+// took to find out, for choose_strips.
+int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, chunk_estimate &chunks);
 
 #endif
