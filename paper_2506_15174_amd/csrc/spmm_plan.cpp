@@ -516,7 +516,8 @@ double chunk_estimate::time(double N) const
                                          {3.03, 13.2, 0.0, 0.33, 4.30, 0.0, 4.98, 0.0},   // ... 32
                                          {2.79, 13.4, 0.0, 0.56, 3.20, 0.0, 6.97, 5.99},  // ... 64
                                          {2.97, 22.1, 0.0, 0.70, 0.74, 1.73, 12.3, 15.2}};  // more, or unknown
-    const double *w = weights[N <= 8 ? 0 : N <= 16 ? 1 : N <= 32 ? 2 : N <= 64 ? 3 : 4];
+    // (chunks of eight columns take what they take for 17 to 32 where B is narrower: the first two are of wider ones)
+    const double *w = weights[N <= 8 && ufk > 8 ? 0 : N <= 16 && ufk > 8 ? 1 : N <= 32 ? 2 : N <= 64 ? 3 : 4];
     const int tile = ufk == 8 ? (N > 64 ? 128 : 64) : ufk == 16 ? 32 : ufk == 32 ? 16 : N > 4 ? 8 : 4;
     const double tiles = std::ceil(N / tile) * 1e-6, per_load = 256.0 / tile;
     return w[0] + tiles * (w[1] * fetched / per_load + w[2] * 4.2 * nnz / per_load + w[3] * (4.0 * fetched + 4.2 * nnz) + w[4] * fetched / ufk * std::sqrt((double)ufi)) +
@@ -622,7 +623,7 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 }
 
 // Strips take the place of the chunks or the tiles (`rows` a panel) that would be chosen where they are estimated to be faster, without a hint
-// at each of three widths.  Of 1200 random products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256
+// at each of three widths, in bands also at the other two that chunks have tuned kernels for.  Of 1200 random products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256
 // columns, one in three without a hint):
 //   145 of 319 on chunks, 1.60 times as fast on average, 0.96 at worst, with 0.7 of the error against 64 bits; 42 others would be 1.19
 //       times as fast, 26 of them below 2^17 entries
@@ -632,14 +633,18 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 // narrow strips, whose copy of B is short of bytes in flight, take up to 1.3 times what is estimated (4096 x 4096, 80 % pruned, 4 columns 6.3 us on tiles, 7.3 on
 // strips; 2048 x 2048, 90 %, 8 columns 3.5 on chunks, 3.7 on strips), and chunks up to 0.85 times.  What still moves gains: 16384 x 1024, 75 %, 8 columns 10.8 -> 7.4 us,
 // 16000 x 700, 60 % in Zipf rows, 6 columns 10.8 -> 7.6, 9000 x 3000, 85 %, 10 columns 17.1 -> 7.9.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
+// Widths without a hint: of 120 products that move by 16, 64 and 200 columns 26 would be left by the estimates for 32 and 128 as well.  The 21 of one band
+// take 0.4 to 1.02 times as long on strips at any width from 4 to 256 columns (those of chunks of uneven rows are estimated too low); the five in bands
+// up to 1.22 at 32, 1.10 at 128 (6925 x 5876, 3.2 %, 32 columns; 2286 x 11700, 14 %, 128 columns).  Of 120 others judged so 117 move: on average 0.50
+// (200 columns) to 0.67 of the time (32), 1.04 at worst at any width up to 200; at 256, where chunks fill two column tiles, 0.65 and, in bands, 1.31 at worst.
 bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, chunk_estimate chunks, strips::start &begun)
 {
     const int64_t nnz = row_ptr[M];
     // As for tiles mostly the launch's time; but chunks take two column tiles beyond 128 columns.
     if (nnz == 0 || (nnz < ((int64_t)1 << 17) && n_hint <= 128)) return false;
-    const int32_t hinted[] = {std::min(std::max(n_hint, 4), 256)}, unknown[] = {16, 64, 200};
+    const int32_t hinted[] = {std::min(std::max(n_hint, 4), 256)}, unknown[] = {16, 64, 200, 32, 128};
     strips::rivals &others = begun.others;
-    others.n = n_hint > 0 ? 1 : 3;
+    others.n = n_hint > 0 ? 1 : K > STRIP_MOST_ROWS ? 5 : 3;
     double margin = 10.0;
     for (int i = 0; i < others.n; ++i) {
         const int32_t N = n_hint > 0 ? hinted[i] : unknown[i];

@@ -122,7 +122,7 @@ inline double time_at_best(int64_t M, int64_t K, int64_t entries, int64_t N)
 
 // What strips have to beat where they were not asked for: the times of what a plan would hold instead, at some widths of B.
 struct rivals {
-    static constexpr int MOST = 3;
+    static constexpr int MOST = 5;
     int n = 0;
     int64_t N[MOST] = {};
     double us[MOST] = {};
