@@ -63,7 +63,8 @@ __device__ __forceinline__ float add_half(float v)
 // lanes' banks differ; and a lane that owns a part of a row adds up by itself, without a cross-lane step per entry.  A lane holds
 // four sums per column, for the four steps of a group: chains of a quarter of its entries.
 //
-// Every 12 groups they go to a total (8192 x 8192, 50 % kept: error against 64 bits 4.1e-7 without, 1.9e-7 with a total every 6).
+// Every 12 groups, of whatever bands, they go to a total (error against 64 bits and time with and without: 8192 x 8192, 50 % kept, 128 columns 1.48e-7
+// and 4.08e-7, 218 and 211 us; 4096 x 16384, 5 %, 128 columns in four bands 0.94e-7 and 1.40e-7, 47.5 us both).
 //
 // What bounds it: LDS (two reads of 4.3 cycles per step and wave, 1.15 times that with the collisions that the builder's order
 // leaves), the vector ALUs (8 multiply-adds and 2 others per step) and the fetch of the entries (384 bytes per step) take about ten
@@ -119,6 +120,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
         const bool any = unit < args.n_units;
         if (!any && copied) break;
         f32x4 acc[STRIP_STEPS][Q], total[Q] = {};  // of the last groups; of all before them
+        int rounds = 0;                             // of up to three groups that are in acc, of all bands
         auto collect = [&] {
 #pragma unroll
             for (int q = 0; q < Q; ++q) {
@@ -196,7 +198,10 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
                 for (int e = 0; e < STRIP_STEPS; ++e)
 #pragma unroll
                     for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(acc[e][q]));
-                if (g % 12 == 9) collect();
+                if (++rounds == 4) {
+                    collect();
+                    rounds = 0;
+                }
             }
         }
         if (!any) break;

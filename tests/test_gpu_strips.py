@@ -93,6 +93,22 @@ def test_duplicates_empty_rows_and_bad_columns(torch_gpu, oracle):  # noqa: F811
         assert err.value.status == spmm.SPMM_ERR_INVALID_CSR
 
 
+def test_no_chain_of_additions_is_longer_than_twelve_groups(torch_gpu):  # noqa: F811
+    """A row of 2^24 and ones, two of a lane in each of 30 bands, a group each: the chain of the 2^24 loses every one that it meets.  It meets eleven
+    at most, and the sums of the parts of a row, rounded to even numbers, are off by one in each of six additions."""
+    torch, bands = torch_gpu, 30
+    K, in_band = bands * 5088, 128
+    col = np.concatenate([b * 5088 + np.arange(in_band) for b in range(bands)]).astype(np.int32)
+    for big in (0, 1, 77):
+        vals = np.ones(col.size, np.float32)
+        vals[big] = 2.0 ** 24
+        plan = spmm.plan_create(1, K, np.array([0, col.size]), col, vals, strips=1)
+        assert plan.describe()["n_chunks"] == bands and plan.describe()["n_enum"] == bands * 64 * 4
+        C = plan.execute(torch.ones((K, 8), device="cuda"))
+        off = (C.double() - (2.0 ** 24 + col.size - 1)).abs()
+        assert float(off.max()) <= 11 + 6
+
+
 def test_a_value_outside_the_domain_reaches_only_rows_with_an_entry_there(torch_gpu):  # noqa: F811
     csr = gen.uniform_positions(64, 256, 0.5, 15)
     B = gen.dense_activations(csr.K, 32, 16)
