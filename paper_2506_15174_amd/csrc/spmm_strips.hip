@@ -634,12 +634,15 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
         a.stream = reinterpret_cast<char *>(p.d_stream);
         return hipSuccess;
     };
-    struct two_words {
+    struct units_in_waiting {
         uint32_t *p = nullptr;
         hipStream_t s;
-        ~two_words()
+        ~units_in_waiting() { (void)give_back(); }
+        hipError_t give_back()
         {
-            if (p) (void)hipFreeAsync(p, s);
+            uint32_t *const q = p;
+            p = nullptr;
+            return q ? hipFreeAsync(q, s) : hipSuccess;
         }
     } waiting;
     waiting.s = s;
@@ -683,6 +686,7 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     hipLaunchKernelGGL(value_kernel, dim3((unsigned)places), dim3(512), 0, s, a);
     TRY(hipGetLastError());
     if (!staged) TRY(hipMemcpyWithStream(got, d_words, sizeof got, hipMemcpyDeviceToHost, s));
+    TRY(waiting.give_back());
     TRY(memory.give_back());
     TRY(hipStreamSynchronize(s));
     if (refused()) return hipSuccess;

@@ -93,6 +93,19 @@ def test_duplicates_empty_rows_and_bad_columns(torch_gpu, oracle):  # noqa: F811
         assert err.value.status == spmm.SPMM_ERR_INVALID_CSR
 
 
+@pytest.mark.parametrize("K", [4096, 16384])
+def test_what_the_builder_worked_with_is_given_back(torch_gpu, K):  # noqa: F811
+    """When the creation returns, not with the next synchronisation; with one band and with four."""
+    torch = torch_gpu
+    csr = gen.uniform_positions(8192, K, 0.96, 3)
+    strips_of(csr, 64)   # what the runtime sets up once
+    torch.cuda.synchronize()
+    plan = strips_of(csr, 64)
+    free = torch.cuda.mem_get_info()[0]
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free and plan.describe()["n_chunks"] == plan.describe()["strip_units"] * (1 if K == 4096 else 4)
+
+
 def test_no_chain_of_additions_is_longer_than_twelve_groups(torch_gpu):  # noqa: F811
     """A row of 2^24 and ones, two of a lane in each of 30 bands, a group each: the chain of the 2^24 loses every one that it meets.  It meets eleven
     at most, and the sums of the parts of a row, rounded to even numbers, are off by one in each of six additions."""
