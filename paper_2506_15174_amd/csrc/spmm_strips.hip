@@ -77,7 +77,7 @@ __device__ __forceinline__ float add_half(float v)
 // cycles, else 2.8, and those of LDS hold them in order (1 to 3 % of the product).
 template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, STRIP_WAVES / 4) void spmm_strips_kernel(const strip_args args)
 {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+    extern __shared__ __attribute__((aligned(32))) char lds[];  // (whole rows: the halves of one differ in a bit of the address)
     // Workgroups are dealt to the eight XCDs in turn: each takes an eighth of the places, next to each other, so that the strips of
     // a group, which read the same entries, share an L2.
     const uint64_t place = args.first + blockIdx.x % 8u * (gridDim.x / 8u) + blockIdx.x / 8u;
@@ -88,6 +88,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     constexpr int Q = STRIP_COLS / 4;  // fours of columns; the lane reads four i ^ turn of its rows as the i-th
     const uint32_t turn = (uint32_t)lane % Q, N = (uint32_t)args.N, col0 = strip * STRIP_COLS, band_rows = (uint32_t)args.band_rows;
     const int bands = BANDS ? args.bands : 1;
+    const uint32_t own = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)lds + turn * 16u;  // what the lane reads first of row 0
 
     if (threadIdx.x < Q) *reinterpret_cast<f32x4 *>(lds + band_rows * STRIP_ROW_BYTES + threadIdx.x * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     auto copy_band = [&](uint32_t band) {
@@ -156,10 +157,10 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             auto read = [&](int k, int h) {
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    // (as an integer: the address of lds is 0, and to it the compiler would add)
+                    // (as an integer, the strip's address in LDS in what is added anyway: to a pointer the compiler would add it once more)
                     uint32_t at;
-                    if (e == 0) asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(turn * 16u));
-                    else asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(turn * 16u));
+                    if (e == 0) asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(own));
+                    else asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(own));
 #pragma unroll
                     for (int q = 0; q < Q; ++q) x[h][e][q] = *(const lds_f32x4 *)(size_t)(at ^ (uint32_t)q * 16u);
                 }
