@@ -85,7 +85,8 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     const uint32_t group = (uint32_t)(place / args.n_strips), strip = (uint32_t)(place % args.n_strips);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
-    constexpr int Q = STRIP_COLS / 4;  // fours of columns; the lane reads four i ^ turn of its rows as the i-th
+    constexpr int Q = 2;  // fours of columns; the lane reads four i ^ turn of its rows as the i-th
+    static_assert(Q * 4 == STRIP_COLS, "the fours of a row change places with one bit");
     const uint32_t turn = (uint32_t)lane % Q, N = (uint32_t)args.N, col0 = strip * STRIP_COLS, band_rows = (uint32_t)args.band_rows;
     const int bands = BANDS ? args.bands : 1;
     const uint32_t own = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)lds + turn * 16u;  // what the lane reads first of row 0
@@ -207,25 +208,22 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
         }
         if (!any) break;
         collect();
-        // ---- the sums of the parts of a row: lanes l and l ^ 1, then l and l ^ 2, each keep the fours that they read first (the other
-        // one has four i of the lane as i ^ 1, i ^ 2); from then on a lane has one four
+        // ---- the sums of the parts of a row: lanes l and l ^ 1 each keep the four that they read first (the other
+        // one has it as its second); from then on a lane has one four
 #pragma unroll
         for (int q = 0; q < Q; ++q) total[q] = __builtin_shufflevector(total[q], total[q], 1, 0, 3, 2);
         const uint32_t word = args.rows[(size_t)unit * 64u + (uint32_t)lane], row = word & ((1u << STRIP_PARTS_SHIFT) - 1u);
         const uint32_t parts_log2 = __builtin_amdgcn_readfirstlane(word >> STRIP_PARTS_SHIFT);  // lane 0 has a row
-        auto each = [&](int q, auto f) {
+        auto each = [&](auto f) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) total[q][c] = f(total[q][c], c);
+            for (int c = 0; c < 4; ++c) total[0][c] = f(total[0][c], c);
         };
-        if (parts_log2 > 0) {
-#pragma unroll
-            for (int q = 0; q < Q; q += 2) each(q, [&](float v, int c) { return v + other<1>(total[q + 1][c]); });
-        }
-        if (parts_log2 > 1) each(0, [&](float v, int c) { return v + other<2>(total[Q > 2 ? 2 : 0][c]); });
-        if (parts_log2 > 2) each(0, [](float v, int) { return v + other<4>(v); });
-        if (parts_log2 > 3) each(0, [](float v, int) { return v + other<8>(v); });
-        if (parts_log2 > 4) each(0, [](float v, int) { return add_row(v); });
-        if (parts_log2 > 5) each(0, [](float v, int) { return add_half(v); });
+        if (parts_log2 > 0) each([&](float v, int c) { return v + other<1>(total[1][c]); });
+        if (parts_log2 > 1) each([](float v, int) { return v + other<2>(v); });
+        if (parts_log2 > 2) each([](float v, int) { return v + other<4>(v); });
+        if (parts_log2 > 3) each([](float v, int) { return v + other<8>(v); });
+        if (parts_log2 > 4) each([](float v, int) { return add_row(v); });
+        if (parts_log2 > 5) each([](float v, int) { return add_half(v); });
         const uint32_t part = (uint32_t)lane & ((1u << parts_log2) - 1u);
         if (word != STRIP_NO_ROW && part < Q) {
             float *dst = args.C + (size_t)row * N + col0;
@@ -249,8 +247,8 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
 // The same units, order and bytes as the builder on the host makes (spmm_strips_build.h says why that order): the rows' entries band by
 // band and class by class (class_kernel), then every unit in a band by a wave of its own, lane by lane what the host's loops do one
 // after the other (order_kernel).  Plan and product, 4096 x 4096, 80 % pruned, 64 columns (20 MB, of which the upload is
-// 0.5 ms): 0.86 ms, on tiles 0.92, built on the host 7.1; 95 % pruned, 128 columns 0.58 and 3.6, on chunks 3.1.  Working memory is ten bytes an entry at most: with 16 its
-// allocation and release took 0.1 ms and 0.25 longer.
+// 0.5 ms): 0.86 ms, on tiles 0.92, built on the host 7.1; 95 % pruned, 128 columns 0.58 and 3.6, on chunks 3.1.  Working memory: 8 bytes an entry, 24 a row and 32 per row and band, and the units
+// once more in bands; with 16 bytes an entry its allocation and release took 0.1 ms and 0.25 longer.
 
 struct build_args {
     const int32_t *row_ptr;
@@ -269,7 +267,7 @@ struct build_args {
     builder::pull values;  // some of them, on their way beside the ordering
 };
 constexpr uint32_t NOTHING = ~0u;  // instead of an entry (its place is below the rows of a band)
-constexpr int BAD_COLUMN = 0, BAD_ORDER = 1, BAD_LENGTH = 2;
+constexpr int BAD_COLUMN = 0, BAD_ORDER = 1;
 
 // One wave per row.
 template <typename Col> __global__ __launch_bounds__(256) void class_kernel(const build_args args, const Col *col_idx)
@@ -364,10 +362,7 @@ __global__ __launch_bounds__(64) void unit_kernel(const build_args args)
         if (row != STRIP_NO_ROW) n = args.classes[((size_t)row * (uint32_t)args.bands + (uint32_t)band) * 8];
         uint32_t groups = (((n + (1u << u[1]) - 1u) >> u[1]) + STRIP_STEPS - 1) / STRIP_STEPS;
         for (int m = 1; m < 64; m *= 2) groups = max(groups, (uint32_t)__shfl_xor((int)groups, m));
-        if (lane == 0) {
-            to[band * 2 + 1] = groups;
-            if (groups > (uint32_t)strips::MOST_GROUPS) args.flags[BAD_LENGTH] = 1;
-        }
+        if (lane == 0) to[band * 2 + 1] = groups;
     }
 }
 
@@ -600,7 +595,7 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     const int64_t n_units = (int64_t)units.size(), places = n_units * bands;
     const size_t n_words = strips::unit_words(n_units, bands);
     const uint32_t longest = begun.r.length[0];
-    // an entry's number in its row in 16 bits; blocks of 512 threads
+    // an entry's number in its row in 16 bits (so a unit has 2^14 groups in a band at most); blocks of 512 threads
     if (longest > 65535 || places >= (int64_t)1 << 23) { status = STRIPS_NOT_POSSIBLE; return hipSuccess; }
     // flags, groups, the row pointer; the order; the units in four words each (unit_kernel)
     std::vector<uint32_t> words(front + list + (size_t)n_units * 4, 0u);
@@ -660,7 +655,7 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     uint32_t got[8] = {};  // flags, groups, those of the longest unit
     auto refused = [&] {
         const uint32_t *flags = staged ? upload.flags() : got;
-        status = flags[BAD_COLUMN] ? 2 : flags[BAD_ORDER] || flags[BAD_LENGTH] ? STRIPS_NOT_POSSIBLE : 0;
+        status = flags[BAD_COLUMN] ? 2 : flags[BAD_ORDER] ? STRIPS_NOT_POSSIBLE : 0;
         return status != 0;
     };
     if (bands > 1) {
