@@ -589,6 +589,20 @@ spmm_status_t spmm_plan_get_array(const spmm_plan_t *plan, int32_t which, uint32
     return SPMM_OK;
 }
 
+// For the tests, which compare the strips of the two builders: the units, rows and groups of a plan on strips (as many words as
+// fit `cap`); how many words they are, or -1.
+int64_t spmm_strips_words(const spmm_plan_t *plan, uint32_t *out, int64_t cap, int32_t *built_on_device)
+{
+    if (!plan || !plan->on_device || plan->strips.n_units == 0) return -1;
+    const StripPlan &p = plan->strips;
+    const size_t front = (size_t)(p.n_units * (p.bands * 2 + 64)), behind = (size_t)(p.steps / STRIP_STEPS) * (STRIP_GROUP_BYTES / 4);
+    if (built_on_device) *built_on_device = p.built_on_device;
+    if (out && cap >= (int64_t)(front + behind) &&
+        (hipMemcpy(out, p.d_units, front * 4, hipMemcpyDeviceToHost) != hipSuccess || hipMemcpy(out + front, p.d_stream, behind * 4, hipMemcpyDeviceToHost) != hipSuccess))
+        return -1;
+    return (int64_t)(front + behind);
+}
+
 const char *spmm_status_string(spmm_status_t status)
 {
     switch (status) {

@@ -1,5 +1,7 @@
 """The strips path (eight columns of B in LDS, one lane per part of a row) against the oracle, at the edges of its units, bands
 and strips.  Needs the GPU."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -57,7 +59,7 @@ def test_against_the_oracle(torch_gpu, oracle, make, M, K, sparsity, N):  # noqa
                                                     (gen.uniform_positions, 3000, 1000, 0.75, 200), (gen.lognormal_rows, 700, 9001, 0.9, 16)])
 def test_the_builders_on_the_device_and_on_the_host_agree(torch_gpu, make, M, K, sparsity, hint):  # noqa: F811
     """The order of a row's entries does not matter, bit for bit: where they are in order of the columns, the strips
-    are built on the device, else on the host."""
+    are built on the device, else on the host; both make the same words."""
     rng = np.random.default_rng(8)
     csr = make(M, K, sparsity, 9)
     order = np.concatenate([rng.permutation(np.arange(a, b)) for a, b in zip(csr.row_ptr[:-1], csr.row_ptr[1:])])
@@ -65,12 +67,68 @@ def test_the_builders_on_the_device_and_on_the_host_agree(torch_gpu, make, M, K,
     C0, one = gpu_product(torch_gpu, csr, B, strips=1, n_hint=hint)
     C1, two = gpu_product(torch_gpu, gen.Csr(M, K, csr.row_ptr, csr.col_idx[order], csr.vals[order]), B, strips=1, n_hint=hint)
     assert np.array_equal(C0, C1) and one.describe() == two.describe()
+    same_strips(one, two)
     # out of order only at the end of a long row: the device finds it and the host builds
     end = csr.row_ptr[np.argmax(np.diff(csr.row_ptr)) + 1]
     order = np.arange(csr.row_ptr[-1])
     order[end - 2:end] = order[end - 2:end][::-1]
-    C2, _ = gpu_product(torch_gpu, gen.Csr(M, K, csr.row_ptr, csr.col_idx[order], csr.vals[order]), B, strips=1, n_hint=hint)
+    C2, three = gpu_product(torch_gpu, gen.Csr(M, K, csr.row_ptr, csr.col_idx[order], csr.vals[order]), B, strips=1, n_hint=hint)
     assert np.array_equal(C0, C2)
+    same_strips(one, three)
+
+
+def words(plan):
+    """The words of a plan on strips, and whether they were made on the device."""
+    lib = ctypes.CDLL(spmm.load()._name)
+    lib.spmm_strips_words.restype = ctypes.c_int64
+    on_device = ctypes.c_int32(-1)
+    n = lib.spmm_strips_words(plan.handle, None, ctypes.c_int64(0), ctypes.byref(on_device))
+    out = np.zeros(n, np.uint32)
+    assert n > 0 and lib.spmm_strips_words(plan.handle, ctypes.c_void_p(out.ctypes.data), ctypes.c_int64(n), None) == n
+    return out, on_device.value
+
+
+def same_strips(by_device, by_host):
+    (one, on_device), (two, on_host) = words(by_device), words(by_host)
+    assert (on_device, on_host) == (1, 0) and np.array_equal(one, two)
+
+
+def in_order(nnz, K, seed):
+    """64 rows, in all `nnz` entries, columns in order."""
+    rng = np.random.default_rng(seed)
+    lens = np.full(64, nnz // 64)
+    lens[:nnz - lens.sum()] += 1
+    row_ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col_idx = np.concatenate([np.sort(rng.permutation(K)[:n]) for n in lens]).astype(np.int32)
+    return row_ptr, col_idx, rng.integers(-8, 9, nnz).astype(np.float32)
+
+
+# columns of 16 bits and, from 65537 on, of 32; from ordinary memory and through pinned memory, in one piece or several
+@pytest.mark.parametrize("nnz,K", [((1 << 19) - 1, 70000), (1 << 19, 20000), ((1 << 19) + 1, 65536), ((1 << 19) + 1, 65537), (2200003, 65536), (3500001, 70000)])
+def test_large_matrices_reach_the_device_whole(torch_gpu, nnz, K):  # noqa: F811
+    torch = torch_gpu
+    row_ptr, col_idx, vals = in_order(nnz, K, nnz % 1000)
+    plan = spmm.plan_create(64, K, row_ptr, col_idx, vals, strips=1)
+    B = torch.randint(-4, 5, (K, 4), device="cuda", dtype=torch.int8).to(torch.float32)
+    rows = torch.from_numpy(np.repeat(np.arange(64), np.diff(row_ptr))).cuda()
+    terms = torch.from_numpy(vals).cuda().double()[:, None] * B[torch.from_numpy(col_idx).cuda().long()].double()
+    assert torch.equal(plan.execute(B).double(), torch.zeros((64, 4), device="cuda", dtype=torch.float64).index_add_(0, rows, terms))
+    order = np.concatenate([np.arange(a, b)[::-1] for a, b in zip(row_ptr[:-1], row_ptr[1:])])
+    same_strips(plan, spmm.plan_create(64, K, row_ptr, col_idx[order], vals[order], strips=1))
+
+
+@pytest.mark.parametrize("nnz,K", [(2200003, 40000), (2200003, 70000), (9000, 70000)])
+def test_columns_outside_are_found_on_the_device(torch_gpu, nnz, K):  # noqa: F811
+    """In the first, the middle and the last piece of the upload; in rows that are otherwise in order."""
+    row_ptr, col_idx, vals = in_order(nnz, K, 1)
+    for row in (0, 31, 63):
+        for at, outside in ((row_ptr[row], -1), (row_ptr[row + 1] - 1, K), (row_ptr[row + 1] - 1, 2 ** 31 - 1), (row_ptr[row], -65536), (row_ptr[row + 1] - 1, K + 65536)):
+            bad = col_idx.copy()
+            bad[at] = outside
+            with pytest.raises(spmm.SpmmError) as err:
+                spmm.plan_create(64, K, row_ptr, bad, vals, strips=1)
+            assert err.value.status == spmm.SPMM_ERR_INVALID_CSR
+    assert words(spmm.plan_create(64, K, row_ptr, col_idx, vals, strips=1))[1] == 1   # the memory was given back
 
 
 def test_duplicates_empty_rows_and_bad_columns(torch_gpu, oracle):  # noqa: F811
