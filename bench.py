@@ -642,8 +642,8 @@ PATH_WIDTHS = (4, 8, 16, 32, 64, 128, 200, 256)
 
 
 def run_paths(args):
-    """Chunks against tiles: random matrices of PATH_SHAPES, PATH_DENSITIES and three laws of row lengths (even,
-    lognormal, Zipf), each at four of PATH_WIDTHS; the hinted chunk plan, tiles of 8, 16 and 32 rows and
+    """Chunks, tiles and strips: random matrices of PATH_SHAPES, PATH_DENSITIES and three laws of row lengths (even,
+    lognormal, Zipf), each at four of PATH_WIDTHS; the hinted chunk plan, tiles of 8, 16 and 32 rows, strips and
     the plan that the inspector chooses, timed in turn, with the estimates the choice is made by.  args.steps
     matrices are drawn."""
     import ctypes
@@ -654,7 +654,7 @@ def run_paths(args):
     from workloads import generators as gen
     torch.cuda.set_device(0)
     lib = spmm.load()
-    lib.spmm_chunks_time.restype = lib.spmm_tiles_time.restype = ctypes.c_double
+    lib.spmm_chunks_time.restype = lib.spmm_tiles_time.restype = lib.spmm_strips_time.restype = ctypes.c_double
     i64, dbl = ctypes.c_int64, ctypes.c_double
     rng = random.Random(args.seed)
     t_start, pts = time.perf_counter(), []
@@ -675,7 +675,8 @@ def run_paths(args):
                 if R != 8 or N <= 64:
                     plans[R] = spmm.plan_create(*a, n_hint=N, tiles=R)
             us = {k: min(_time_plan(torch, p, B, C, N, reps=5) for _ in range(2)) for k, p in plans.items()}
-            estimate = {"chunks": lib.spmm_chunks_time(i64(M), i64(K), ctypes.c_void_p(row_ptr.ctypes.data), N, dbl(N))}
+            estimate = {"chunks": lib.spmm_chunks_time(i64(M), i64(K), ctypes.c_void_p(row_ptr.ctypes.data), N, dbl(N)),
+                        "strips": lib.spmm_strips_time(i64(M), i64(K), ctypes.c_void_p(row_ptr.ctypes.data), N, i64(N))}
             for R in (k for k in plans if k not in ("chunks", "strips", "chosen")):
                 heaviest = max(int(row_ptr[min(M, i + R)]) - int(row_ptr[i]) for i in range(0, M, R))
                 mean = nnz / (M * K)
@@ -706,7 +707,7 @@ def run_paths(args):
                "tiles_or_strips_over_chunks_where_chosen": {"geomean": round(_geomean([p["chosen_over_chunks"] for p in moved]), 3) if moved else None,
                                                   "worst": max((p["chosen_over_chunks"] for p in moved), default=None),
                                                   "slower_by_3_pct": sum(p["chosen_over_chunks"] > 1.03 for p in moved)},
-               "estimate_over_measured": {k: fit(k, pts) for k in ("chunks", "8", "16", "32")},
+               "estimate_over_measured": {k: fit(k, pts) for k in ("chunks", "8", "16", "32", "strips")},
                "estimate_over_measured_chunks_by_width": {str(N): fit("chunks", [p for p in pts if p["N"] == N]) for N in PATH_WIDTHS}}
     if args.points_file:
         with open(args.points_file, "w") as f:
@@ -714,7 +715,7 @@ def run_paths(args):
     print(json.dumps({"metric": "time of the chosen path / time of the fastest path (geomean)",
                       "value": summary["chosen_over_best"]["geomean"], "unit": "ratio", "n_gpus": 1, "higher_is_better": False,
                       "dtype": "f32", "data": "synthetic",
-                      "config": {"workload": "%d random matrices x four widths, chunks and tiles" % args.steps, "seed": args.seed,
+                      "config": {"workload": "%d random matrices x four widths, chunks, tiles and strips" % args.steps, "seed": args.seed,
                                  "wall_s": round(time.perf_counter() - t_start, 1)},
                       "summary": summary}))
 

@@ -557,6 +557,18 @@ double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_
     }
 }
 
+double spmm_strips_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, int64_t N)
+{
+    if (M == 0 || row_ptr[M] == 0) return 0.0;  // no strips
+    try {
+        strips::start s;
+        strips::begin(M, K, row_ptr, strips::columns_for(n_hint), s);
+        return strip_time(s.sizes, K, N, nullptr);
+    } catch (...) {
+        return -1.0;
+    }
+}
+
 // Estimated time in us on tiles of r rows, and the operands NB that one is wide.
 static double tiles_time(int r, int64_t M, int64_t K, const int32_t *row_ptr, int64_t N, int *NB)
 {

@@ -82,6 +82,8 @@ struct chunk_estimate {
 // Estimated time in us of a product with N columns of B on the chunk plan made for n_hint columns, for
 // bench.py, which sets it beside measured times; -1 where there is no memory for it.
 extern "C" double spmm_chunks_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, double N);
+// The same on strips, as the rows' lengths tell.
+extern "C" double spmm_strips_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, int64_t N);
 
 // The entries of A in strips (spmm_strips_build.h), for products with n_hint columns.  Status codes as above; out.plan.n_units = 0:
 // A cannot be stored this way.
