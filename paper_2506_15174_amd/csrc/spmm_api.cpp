@@ -235,7 +235,8 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
     }
     if (use_strips && checked && row_ptr[M] > 0) {
         if (opts.strips > 0) look_at_columns(M, row_ptr, col_idx, begun);
-        rc = begun.in_order ? spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, strips::columns_for(io.n_hint), begun, p->strips) : STRIPS_NOT_POSSIBLE;
+        rc = begun.in_order ? spmm_strips_build_on_device(M, K, row_ptr, col_idx, vals, strips::columns_for(io.n_hint), begun, p->strips)
+                            : STRIPS_NOT_POSSIBLE;
         if (rc == STRIPS_NOT_POSSIBLE || rc == SPMM_ERR_ALLOC) {
             rc = 0;
             if (instead > 0) tiles = instead;  // which the device builds from rows in any order
@@ -286,7 +287,9 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
         p->on_device = true;
     }
     const StripPlan &on_strips = p->strips;
-    p->stream_words = p->tiles.rows > 0 ? p->tiles.stream_words : on_strips.n_units > 0 ? on_strips.steps / STRIP_STEPS * (STRIP_GROUP_BYTES / 4) : (int64_t)p->host.stream.size();
+    p->stream_words = p->tiles.rows > 0          ? p->tiles.stream_words
+                      : on_strips.n_units > 0    ? on_strips.steps / STRIP_STEPS * (STRIP_GROUP_BYTES / 4)
+                                                 : (int64_t)p->host.stream.size();
     if (on_strips.n_units > 0) {
         p->host.n_enum = on_strips.steps * 64;
         p->host.n_chunks = on_strips.n_units * on_strips.bands;

@@ -599,14 +599,18 @@ int choose_tiles(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_hint, c
     return rows;
 }
 
-// What 64 rows at even distances show, in four runs of 16 entries each: whether the columns are in order, which the builder of strips on the
-// device asks for and finds out after the upload (0.8 ms for 3.4 million entries; rows out of order elsewhere still cost that), and
-// whether the lanes that read LDS together can read different banks, which they can where their columns differ modulo 8.  Of 64 entries
-// (shorter rows together) one such class holds 0.20 on average where the columns are anyhow, 0.32 where all are even, 0.55 where
-// all are multiples of four and all where they are multiples of eight.  4096 x 4096, 95 % pruned, 128 columns: 12.3, 14.2, 19.2 and 28.4 us on
-// strips, 17.1 on chunks; without the 6.1 us that a product without steps takes that is 0.65 + 0.36 times the reads of a bank.
-// Of 47 products whose columns are multiples of four or eight (or those and the row's number) 30 went to strips without this, 5 of them do with it,
-// which take 0.72 of the time; the others would take 1.27 times as long, 2.8 at worst.
+// What 64 rows at even distances show, in four runs of 16 entries each.
+// Whether the columns are in order, which the builder of strips on the device asks for.  Rows out of order elsewhere it finds
+// after the upload (0.8 ms for 3.4 million entries).
+// And whether the lanes that read LDS together can read different banks, which they can where their columns differ modulo 8.
+// Of 64 entries (shorter rows together) one such class holds a share of 0.20 on average where the columns are anyhow.
+// 4096 x 4096, 95 % pruned, 128 columns, 17.1 us on chunks:
+//   columns    anyhow  multiples of 2  of 4  of 8
+//   share        0.20        0.32      0.55  1
+//   strips, us   12.3        14.2      19.2  28.4
+// Without the 6.1 us that a product without steps takes that is 0.65 + 0.36 times the reads of a bank.
+// Of 47 products whose columns are multiples of four or eight (or those and the row's number) 30 went to strips without this.
+// 5 of them do with it and take 0.72 of the time; the others would take 1.27 times as long, 2.8 at worst.
 void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, strips::start &begun)
 {
     constexpr int64_t ROWS = 64, RUNS = 4, RUN = 16;
@@ -634,22 +638,34 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
     begun.others.crowding = share > 0.4 ? 0.65 + 0.36 * 8.0 * share : 1.0;
 }
 
-// Strips take the place of the chunks or the tiles (`rows` a panel) that would be chosen where they are estimated to be faster, without a hint
-// at each of three widths, in bands also at the other two that chunks have tuned kernels for.  Of 1200 random products (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows, 4 to 256
-// columns, one in three without a hint):
-//   145 of 319 on chunks, 1.60 times as fast on average, 0.96 at worst, with 0.7 of the error against 64 bits; 42 others would be 1.19
-//       times as fast, 26 of them below 2^17 entries
-//   28 of 49 on 16 rows, 1.34 times, 1.01 at worst, with 0.4 of the error, and 8 of 10 on 32 rows that are one operand wide
-//   4 of 33 tiles chosen without a hint, 1.5 times
-// Instead of tiles of 8 rows only from 1.54 times up, of chunks for up to 16 columns from 1.15 times: with three plans in turn, A and B from beyond the L2s,
-// narrow strips, whose copy of B is short of bytes in flight, take up to 1.3 times what is estimated (4096 x 4096, 80 % pruned, 4 columns 6.3 us on tiles, 7.3 on
-// strips; 2048 x 2048, 90 %, 8 columns 3.5 on chunks, 3.7 on strips), and chunks up to 0.85 times.  What still moves gains: 16384 x 1024, 75 %, 8 columns 10.8 -> 7.4 us,
-// 16000 x 700, 60 % in Zipf rows, 6 columns 10.8 -> 7.6, 9000 x 3000, 85 %, 10 columns 17.1 -> 7.9.  Not the wider tiles of 32 rows, though 28 would be 1.4 times as fast: those run on bf16 parts, and the strips' error is 1.2 times theirs, 1.57 at most.
-// Widths without a hint: of 120 products that move by 16, 64 and 200 columns 26 would be left by the estimates for 32 and 128 as well.  The 21 of one band
-// take 0.4 to 1.02 times as long on strips at any width from 4 to 256 columns (those of chunks of uneven rows are estimated too low); the five in bands
-// up to 1.22 at 32, 1.10 at 128 (6925 x 5876, 3.2 %, 32 columns; 2286 x 11700, 14 %, 128 columns).  Of 120 others judged so 117 move: on average 0.50
-// (200 columns) to 0.67 of the time (32), 1.04 at worst at any width up to 200; at 256, where chunks fill two column tiles, 0.65 and, in bands, 1.31 at worst.
-bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, chunk_estimate chunks, strips::start &begun)
+// Strips take the place of the chunks or the tiles (`rows` a panel) that would be chosen where they are estimated to be
+// faster.  Of 420 random products with a hint (256 to 16384 rows and columns, 2 to 50 % kept in even, lognormal or Zipf rows,
+// 4 to 256 columns), one plan back to back; errors against 64 bits, median and largest:
+//   instead of         of   move  times as fast (worst)  their error   left though more than 3 % faster
+//   chunks            310    127       1.66 (0.89)        0.78, 1.02    55, 1.21 times, 24 of them below 2^17 entries
+//   16 rows            44     27       1.29 (0.95)        0.44, 0.82     8, 1.09 times
+//   8 rows             37     11       1.48 (1.18)        0.77, 0.97    11, 1.17 times
+//   32 rows            29      5       1.33 (1.04)        0.70, 0.83    19, 1.47 times
+// Worst: 896 x 7936, 8 % kept, 100 columns, 14.2 us on chunks and 16.1 on strips in two bands.
+// Not the wider tiles of 32 rows: those run on bf16 parts, and the strips' error is 1.3 times theirs, 1.6 at most.
+//
+// Instead of tiles of 8 rows only from 1.54 times up, of chunks for up to 16 columns from 1.15 times: with three plans in turn,
+// A and B from beyond the L2s, narrow strips, whose copy of B is short of bytes in flight, take up to 1.3 times what is
+// estimated, and chunks down to 0.85 times.
+//   4096 x 4096, 80 % pruned, 4 columns    6.3 us on tiles, 7.3 on strips: stays
+//   2048 x 2048, 90 %, 8 columns           3.5 on chunks, 3.7 on strips: stays
+//   16384 x 1024, 75 %, 8 columns          10.8 -> 7.4
+//   9000 x 3000, 85 %, 10 columns          17.1 -> 7.9
+//
+// Without a hint they have to be faster at each of three widths, in bands also at the other two that chunks have tuned kernels
+// for.  Of 120 products that move by 16, 64 and 200 columns 26 would be left by the estimates for 32 and 128 as well.  The 21 of
+// one band take 0.4 to 1.02 times as long on strips at any width from 4 to 256 columns (the time on chunks of uneven rows is
+// estimated too low); the five in bands up to 1.22 at 32, 1.10 at 128 (6925 x 5876, 3.2 %, 32 columns; 2286 x 11700, 14 %, 128).
+// Of 120 others (all of 2^17 entries and more) 49 move, from chunks and tiles of 16 rows, and are faster at every width up to 200:
+// 1.02 times at least, on average 1.4 (32 columns) to 1.8 (200).  At 256, where chunks fill two column tiles, 1.4, three
+// of them in bands slower, 0.81 at worst.
+bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, chunk_estimate chunks,
+                   strips::start &begun)
 {
     const int64_t nnz = row_ptr[M];
     // As for tiles mostly the launch's time; but chunks take two column tiles beyond 128 columns.
@@ -674,8 +690,9 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *
     if (margin <= 1.0) return false;
     look_at_columns(M, row_ptr, col_idx, begun);
     if (rows > 0 && !begun.in_order) return false;  // tiles are built on the device from rows in any order
-    // Rows of about one length take 1.0 times what they take at best, 1.25 times in one product of a hundred: no need to look at the units,
-    // which the builder finds while the entries travel (0.05 ms of the 0.9 that plan and product of 4096 x 4096, 80 % pruned, take).
+    // Rows of about one length take 1.0 times what they take at best, 1.25 times in one product of a hundred: no need to look at the
+    // units, which the builder finds while the entries travel (0.05 ms of the 0.8 that plan and product of 4096 x 4096, 80 %
+    // pruned, take).
     int64_t longest = 0;
     for (int64_t i = 0; i < M; ++i) longest = std::max<int64_t>(longest, row_ptr[i + 1] - row_ptr[i]);
     if (begun.others.crowding == 1.0 && margin > 1.25 && longest * M <= 2 * nnz) return true;

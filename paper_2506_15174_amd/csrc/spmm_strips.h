@@ -23,7 +23,8 @@ constexpr int STRIP_LDS_BYTES = 160 * 1024, STRIP_BAND_ALIGN = 32;
 constexpr int STRIP_MOST_ROWS = (STRIP_LDS_BYTES / STRIP_ROW_BYTES - 1) / STRIP_BAND_ALIGN * STRIP_BAND_ALIGN;  // of a band, but for the row of zeros
 constexpr int STRIP_WAVES = 16;  // of a workgroup
 // Lane i (0 .. 7) of the even (odd = 0) or odd ones among the 16 lanes that cycle `c` (0 .. 3) of a 16-byte read serves: lanes
-// 0-3, 12-15, 20-23, 24-27, then 4-7, 8-11, 16-19, 28-31, then the same of the upper half (found by timing reads of which two lanes collide).
+// 0-3, 12-15, 20-23, 24-27, then 4-7, 8-11, 16-19, 28-31, then the same of the upper half (found by timing reads of which two
+// lanes collide).
 inline int strip_lane(int c, int i, int odd)
 {
     constexpr int quads[2][4] = {{0, 12, 20, 24}, {4, 8, 16, 28}};
@@ -32,7 +33,8 @@ inline int strip_lane(int c, int i, int odd)
 
 struct StripSizes {
     int64_t n_units = 0;            // 0 = the plan holds no strips
-    int64_t steps = 0, longest = 0;  // of all units, of one (as the rows' lengths tell, until the entries in every band have been counted)
+    // of all units, of one (as the rows' lengths tell, until the entries in every band have been counted)
+    int64_t steps = 0, longest = 0;
     int32_t bands = 1, band_rows = 0;
 };
 struct StripPlan : StripSizes {
@@ -50,9 +52,11 @@ constexpr int STRIP_PARTS_SHIFT = 28;
 
 // Estimated time in us of a product with N columns of B, and the groups of units it runs with: a group is one workgroup
 // per strip, and of one to eight rounds of 256 workgroups those are taken that take least.  (A wave has one unit
-// at most where the strip comes in bands.)  Fitted to 420 products (256 to 16384 rows and columns, 2 to 50 % kept, 4 to 256 columns): rms error 6.6 %.
-// A workgroup's time: the copy of its strip (by the lines of 128 bytes that it touches; more where B exceeds an L2), its units' steps or, where
-// those are few or uneven, its longest wave's, and the units' ends.
+// at most where the strip comes in bands.)
+// A workgroup's time: the copy of its strip (by the lines of 128 bytes that it touches; more where B exceeds an L2), its
+// units' steps or, where those are few or uneven, its longest wave's, and the units' ends.
+// Fitted to 420 products (256 to 16384 rows and columns, 2 to 50 % kept, 4 to 256 columns).  Of 420 others the rms error is
+// 8.7 % (0.57 to 1.27 of the time back to back): 14 % below 8 columns, 7.5 % in one band, 11 % in several.
 inline double strip_time(const StripSizes &p, int64_t K, int64_t N, int64_t *groups_out)
 {
     const int64_t strips = (N + STRIP_COLS - 1) / STRIP_COLS, least = p.bands > 1 ? (p.n_units + STRIP_WAVES - 1) / STRIP_WAVES : 1;

@@ -59,19 +59,24 @@ __device__ __forceinline__ float add_half(float v)
 // BANDS  the strip does not fit LDS: it comes in bands of columns of A, one after the other, and a wave has one unit at most
 // WIDE   64-bit addresses of B, word by word: for the few N whose 32 rows span 4 GiB
 //
-// Why: a gather of rows of B from the vector L1 moves 64 bytes per cycle and compute unit at most (16 cycles per wave load), reads of LDS 256 where the
-// lanes' banks differ; and a lane that owns a part of a row adds up by itself, without a cross-lane step per entry.  A lane holds
-// four sums per column, for the four steps of a group: chains of a quarter of its entries.
+// Why: a gather of rows of B from the vector L1 moves 64 bytes per cycle and compute unit at most (16 cycles per wave load),
+// reads of LDS 256 where the lanes' banks differ; and a lane that owns a part of a row adds up by itself, without a
+// cross-lane step per entry.  A lane holds four sums per column, for the four steps of a group: chains of a quarter of its
+// entries.
 //
-// Every 12 groups, of whatever bands, they go to a total (error against 64 bits and time with and without: 8192 x 8192, 50 % kept, 128 columns 1.48e-7
-// and 4.08e-7, 218 and 211 us; 4096 x 16384, 5 %, 128 columns in four bands 0.94e-7 and 1.40e-7, 47.5 us both).
+// Every 12 groups, of whatever bands, they go to a total.  Error against 64 bits and time with and without that, 128 columns:
+//   8192 x 8192, 50 % kept                    1.48e-7, 218 us;   4.08e-7, 211 us
+//   4096 x 16384, 5 % kept, in four bands     0.94e-7, 47.5 us;  1.40e-7, 47.5 us
 //
 // What bounds it: LDS (two reads of 4.3 cycles per step and wave, 1.15 times that with the collisions that the builder's order
-// leaves), the vector ALUs (8 multiply-adds and 2 others per step) and the fetch of the entries (384 bytes per step) take about ten
-// cycles each of the 15 that a step and wave takes of a compute unit; and before them the copy of the strip: the vector L1
-// fetches a line of 128 bytes for 32, 2 cycles, so 4096 rows take 3.6 us.
-// Three plans in turn, on chunks and on strips: 4096 x 4096, 95 % pruned, 128 columns 17.4 and 13.0 us, 3001 x 2511, 85 % in lognormal
-// rows, 200 columns 37.4 and 17.4.  Back to back 8968 x 2473, 92 %, 96 columns 39 and 14.
+// leaves), the vector ALUs (8 multiply-adds and 2 others per step) and the fetch of the entries (384 bytes per step) take
+// about ten cycles each of the 15 that a step and wave takes of a compute unit; and before them the copy of the strip: the
+// vector L1 fetches a line of 128 bytes for 32, 2 cycles, so 4096 rows take 3.6 us.
+//
+// Three plans in turn (and one back to back), on chunks and on strips:
+//   4096 x 4096, 95 % pruned, 128 columns                     17.6 (16.1) -> 13.1 us (11.2)
+//   3001 x 2511, 85 % in lognormal rows, 200 columns          37.4 (35.3) -> 17.8 (17.0)
+//   8968 x 2473, 92 %, 96 columns                             41.3 (39.2) -> 14.0 (13.2)
 //
 // An accumulator's registers hold columns 1 0 3 2 of its four: a v_fmac of three registers that are all even or all odd takes 4.9
 // cycles, else 2.8, and those of LDS hold them in order (1 to 3 % of the product).
@@ -104,7 +109,8 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
                 *reinterpret_cast<f32x4 *>(lds + t * 16) = x;
             }
         } else {
-            // 1024 bytes at a time, Q lanes a row.  (Past the end of B zeros, past the end of a row what follows: columns that C does not have.)
+            // 1024 bytes at a time, Q lanes a row.  (Past the end of B zeros, past the end of a row what follows: columns that C
+            // does not have.)
             const uint32_t off = (uint32_t)(lane / Q) * N * 4u + (uint32_t)(lane % Q) * 16u;
             constexpr uint32_t OP_ROWS = 64 / Q;
             for (uint32_t op = (uint32_t)wave; op * OP_ROWS < rows; op += STRIP_WAVES) {
@@ -158,7 +164,8 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             auto read = [&](int k, int h) {
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
-                    // (as an integer, the strip's address in LDS in what is added anyway: to a pointer the compiler would add it once more)
+                    // (as an integer, with the strip's address in LDS in what is added anyway: to a pointer the compiler would add
+                    // it once more)
                     uint32_t at;
                     if (e == 0) asm("v_mad_u32_u16 %0, %1, %2, %3" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(own));
                     else asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0]" : "=v"(at) : "v"(places[k][h]), "n"(STRIP_ROW_BYTES), "v"(own));
@@ -244,11 +251,14 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
 
 // ---------------------------------------------------------------- builder
 //
-// The same units, order and bytes as the builder on the host makes (spmm_strips_build.h says why that order): the rows' entries band by
-// band and class by class (class_kernel), then every unit in a band by a wave of its own, lane by lane what the host's loops do one
-// after the other (order_kernel).  Plan and product, 4096 x 4096, 80 % pruned, 64 columns (20 MB, of which the upload is
-// 0.5 ms): 0.86 ms, on tiles 0.92, built on the host 7.1; 95 % pruned, 128 columns 0.58 and 3.6, on chunks 3.1.  Working memory: 8 bytes an entry, 24 a row and 32 per row and band, and the units
-// once more in bands; with 16 bytes an entry its allocation and release took 0.1 ms and 0.25 longer.
+// The same units, order and bytes as the builder on the host makes (spmm_strips_build.h says why that order): the rows' entries
+// band by band and class by class (class_kernel), then every unit in a band by a wave of its own, lane by lane what the host's
+// loops do one after the other (order_kernel).  Plan and product in ms, each plan released before the next:
+//                                    strips   built on the host   tiles of 16 rows   chunks
+//   4096 x 4096, 80 %, 64 columns     0.79           5.7               0.87           10.1    (20 MB, of which the upload takes 0.5)
+//   4096 x 4096, 95 %, 128 columns    0.55           2.2               0.65            3.0
+// Working memory: 8 bytes an entry, 24 a row and 32 per row and band, and the units once more in bands; with 16 bytes an
+// entry its allocation and release took 0.1 ms and 0.25 longer.
 
 struct build_args {
     const int32_t *row_ptr;
@@ -402,10 +412,11 @@ __global__ __launch_bounds__(1024) void begin_kernel(uint32_t *units, uint32_t n
     }
 }
 
-// One wave per unit in a band.  Eight threads next to each other are the lanes that must not collide; what they propose goes around
-// between them as a bit of a byte per turn.  Bound by the chain of a step's 300 instructions: 4096 x 4096, 80 % pruned, 104 steps, 78 us (with
-// eight turns of one lane each and a shuffle 260).  It writes places and, where the values will be, the entries: so it needs no values, and the
-// first workgroups copy a piece of those meanwhile (two of the three that the pinned memory holds would leave the next ones waiting).
+// One wave per unit in a band.  Eight threads next to each other are the lanes that must not collide; what they propose goes
+// around between them as a bit of a byte per turn.  Bound by the chain of a step's 300 instructions: 4096 x 4096, 80 %
+// pruned, 104 steps, 78 us (with eight turns of one lane each and a shuffle 260).  It writes places and, where the values will
+// be, the entries: so it needs no values, and the first workgroups copy a piece of those meanwhile (two of the three that the
+// pinned memory holds would leave the next ones waiting).
 __global__ __launch_bounds__(256) void order_kernel(const build_args args)
 {
     const uint32_t pulling = args.values.n ? builder::PULL_BLOCKS : 0u;
@@ -565,7 +576,8 @@ __global__ __launch_bounds__(512) void value_kernel(const build_args args)
     }
 }
 
-hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N, strips::start &begun, StripPlan &p, int &status)
+hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N, strips::start &begun,
+                 StripPlan &p, int &status)
 {
     const int64_t nnz = row_ptr[M];
     hipError_t e;
@@ -578,15 +590,17 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     // 256 threads per four rows; 32 bytes of working memory per row and band
     if (M > ((int64_t)1 << 26) - 8 || M * bands > (int64_t)1 << 26) { status = STRIPS_NOT_POSSIBLE; return hipSuccess; }
     // (a unit has a row at least; the columns, and when they have been read the values in their place)
-    const size_t at_words = memory.reserve((size_t)M * 24 + 1024), at_entries = memory.reserve((size_t)nnz * 4), at_sorted = memory.reserve((size_t)nnz * 4), at_classes = memory.reserve((size_t)(M * bands) * 32);
+    const size_t at_words = memory.reserve((size_t)M * 24 + 1024), at_entries = memory.reserve((size_t)nnz * 4);
+    const size_t at_sorted = memory.reserve((size_t)nnz * 4), at_classes = memory.reserve((size_t)(M * bands) * 32);
     TRY(memory.take());
     const hipStream_t s = memory.stream;
     int32_t *d_col = memory.at<int32_t>(at_entries);
     uint32_t *d_words = memory.at<uint32_t>(at_words);
     uint64_t *answer = reinterpret_cast<uint64_t *>(d_words) + 2;  // behind four words of flags: groups, those of the longest unit
     const size_t front = ((size_t)M + 9 + 63) / 64 * 64, list = ((size_t)M + 3) / 4 * 4;
-    build_args a{reinterpret_cast<const int32_t *>(d_words + 8), memory.at<float>(at_entries), memory.at<uint32_t>(at_sorted), memory.at<uint32_t>(at_classes), staged ? upload.flags() : d_words, nullptr, nullptr,
-                 d_words + front, reinterpret_cast<const u32x4 *>(d_words + front + list), nullptr, M, (uint32_t)nnz, 0, (int32_t)K, p.bands, p.band_rows, {}};
+    build_args a{reinterpret_cast<const int32_t *>(d_words + 8), memory.at<float>(at_entries), memory.at<uint32_t>(at_sorted),
+                 memory.at<uint32_t>(at_classes), staged ? upload.flags() : d_words, nullptr, nullptr, d_words + front,
+                 reinterpret_cast<const u32x4 *>(d_words + front + list), nullptr, M, (uint32_t)nnz, 0, (int32_t)K, p.bands, p.band_rows, {}};
     // ---- while other threads fill the first pinned memory: the rows' order and the units
     strips::begin(M, K, row_ptr, N, begun);
     const std::vector<uint32_t> &order = begun.r.order;
@@ -722,7 +736,8 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
     return (int)hipGetLastError();
 }
 
-int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N, strips::start &begun, StripPlan &out)
+int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N,
+                                strips::start &begun, StripPlan &out)
 {
     out = StripPlan();
     int status = 0;

@@ -71,10 +71,11 @@ inline void band_sizes(int64_t K, StripSizes &p)
 // Columns of B that a plan without a hint is made for.
 constexpr int64_t UNKNOWN_COLUMNS = 64;
 
-// The units, longest first, for products with N columns, and their sizes (in bands: but for what bands leave idle): lanes of 0.8 to
-// 1.6 equal shares of the entries, whichever is estimated to take least.  (A row's parts are a power of two, so some shares leave
-// some waves a second unit and others idle: 3001 x 2511, 85 % pruned, 200 columns 17.2 us with 1.25 for all, 15.7 so.)  A strip in bands
-// allows one unit per wave only, which more entries per lane bring about.
+// The units, longest first, for products with N columns, and their sizes (in bands: but for what bands leave idle): lanes of
+// 0.8 to 1.6 equal shares of the entries, whichever is estimated to take least.  A row's parts are a power of two, so some
+// shares leave some waves a second unit and others idle: with 1.25 shares for all 8968 x 2473, 92 % pruned, 96 columns takes
+// 16.0 us instead of 14.0, 3001 x 2511, 85 %, 200 columns 18.4 instead of 17.8.  A strip in bands allows one unit per wave only,
+// which more entries per lane bring about.
 inline std::vector<unit> units_for(int64_t K, const rows &r, int64_t entries, int64_t N, StripSizes &p)
 {
     band_sizes(K, p);
@@ -136,11 +137,12 @@ struct rivals {
             if (strip_time(p, K, N[i], nullptr) > us[i]) return true;
         return false;
     }
-    // The same of strips in bands when their steps have been counted.  A unit's lanes wait in every band for the fullest one, which the
-    // rows' lengths do not tell: rows whose entries lie together leave most lanes idle in most bands.  150 products that the lengths alone move
-    // (5100 to 16384 columns, rows even, lognormal or within a half, a third or a quarter of the columns): the counted time is 1.00 of the
-    // measured one (rms 10 %), that of the others 0.90 of theirs.  From 1.1 times theirs on strips are left, 49 products, in which they
-    // take 1.12 times as long on average and up to 1.99 times; the 101 that stay take 0.73, 1.19 at worst.
+    // The same of strips in bands when their steps have been counted.  A unit's lanes wait in every band for the fullest one,
+    // which the rows' lengths do not tell: rows whose entries lie together leave most lanes idle in most bands.
+    // Of 150 products that the lengths alone move (5100 to 16384 columns, rows even, lognormal or within a half, a third or a
+    // quarter of the columns) the counted time is 1.00 of the measured one (rms 10 %), that of the others 0.90 of theirs.
+    // From 1.1 times theirs on strips are left: 49 products, in which they take 1.12 times as long on average and up to 1.99
+    // times; the 101 that stay take 0.73, 1.19 at worst.
     bool faster_than_counted(const StripSizes &p, int64_t K) const
     {
         rivals later = *this;
