@@ -493,7 +493,7 @@ def run_ablation(args):
                      "full": spmm.plan_create(*a, n_hint=N)}
             row = {"M": csr.M, "K": csr.K, "sparsity": entry["sparsity"], "N": N,
                    "ufi": plans["+ranges"].describe()["ufi"], "k_slices": plans["+ranges"].describe()["k_slices"],
-                   "tile_rows": plans["full"].describe()["tile_rows"]}
+                   **schedule_of(plans["full"].describe(), ())}
             for r in rungs:
                 us = _time_plan(torch, plans[r], B, C, N)
                 row[r + "_us"] = round(us, 3)

@@ -664,6 +664,10 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 // Of 120 others (all of 2^17 entries and more) 49 move, from chunks and tiles of 16 rows, and are faster at every width up to 200:
 // 1.02 times at least, on average 1.4 (32 columns) to 1.8 (200).  At 256, where chunks fill two column tiles, 1.4, three
 // of them in bands slower, 0.81 at worst.
+// Of 252 more that move in one band one takes more than 1.03 times as long at one of eleven widths (5140 x 3637, 3.4 %, 32
+// columns: 6.8 -> 7.3 us; the other 251 0.67 on average there), and so does 4096 x 4096, 95 % pruned: 7.0 -> 7.8 at 32
+// columns, 9.6 -> 9.0 at 64, 16.3 -> 11.5 at 128.  There chunks are estimated to take 8.7, so looking at 32 columns does not
+// tell; a line at 0.97 of the estimate would, but would leave 30 of the 252 that take 0.66 of the time at 32 columns.
 bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int32_t n_hint, int rows, chunk_estimate chunks,
                    strips::start &begun)
 {

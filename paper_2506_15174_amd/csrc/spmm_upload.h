@@ -52,9 +52,12 @@ struct workshop {
 // to 35.  Its first pages cost 0.1 ms per MiB once, and giving it back may wait for
 // all streams, which a creation must not.  So there is one piece of it for the process, lent to one creation at
 // a time (another one that runs meanwhile uploads from ordinary memory), and it goes back when the last plan on tiles or strips
-// is released.  4096 x 4096, 80 % pruned (20 MB), plan and product: 0.90 ms where each plan is released before the next (0.84 if the memory stayed), 0.80 where one
-// lives, from ordinary memory 1.26; the first of a process (after a small plan) 1.95, from ordinary memory 2.2.  12 MiB in pieces of
-// 4: 0.88, 0.77 and 2.35 (8192 x 4096, 30 % kept: 1.9 instead of 2.0); 4 MiB in pieces of 1: 0.96, 0.85 and 1.7.
+// is released.  4096 x 4096, 80 % pruned (20 MB), plan on tiles and product in ms:
+//                                 each plan released before the next   one lives    the first of a process (after a small plan)
+//   three pieces of 2 MiB           0.90 (0.84 if the memory stayed)     0.80        1.95
+//   three of 4                      0.88                                 0.77        2.35    (8192 x 4096, 30 %: 1.9 instead of 2.0)
+//   four of 1                       0.96                                 0.85        1.7
+//   from ordinary memory            1.26                                             2.2
 struct staging_memory {
     static constexpr size_t PIECE = 2u << 20, PIECES = 3, WORDS = 256u << 10;  // pieces of the entries; what else a builder sends
     std::mutex lock;
