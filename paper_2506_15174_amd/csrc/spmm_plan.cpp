@@ -563,7 +563,7 @@ double spmm_strips_time(int64_t M, int64_t K, const int32_t *row_ptr, int32_t n_
     try {
         strips::start s;
         strips::begin(M, K, row_ptr, strips::columns_for(n_hint), s);
-        return strip_estimate(s.sizes, K, N);
+        return strip_time(s.sizes, K, N, nullptr);
     } catch (...) {
         return -1.0;
     }
@@ -644,22 +644,17 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 //   instead of         of   move  times as fast (worst)  their error   left though more than 3 % faster
 //   chunks            310    127       1.66 (0.89)        0.78, 1.02    55, 1.21 times, 24 of them below 2^17 entries
 //   16 rows            44     27       1.29 (0.95)        0.44, 0.82     8, 1.09 times
+//   8 rows             37     11       1.48 (1.18)        0.77, 0.97    11, 1.17 times
 //   32 rows            29      5       1.33 (1.04)        0.70, 0.83    19, 1.47 times
 // Worst: 896 x 7936, 8 % kept, 100 columns, 14.2 us on chunks and 16.1 on strips in two bands.
 // Of 688 further products of 24 to 256 columns that move (183 of them in bands), three plans in turn, none takes more than 1.03
 // times as long; 0.65 on average.
 // Not the wider tiles of 32 rows: those run on bf16 parts, and the strips' error is 1.3 times theirs, 1.6 at most.
 //
-// Instead of tiles of 8 rows only from 1.25 times up, of chunks for up to 16 columns from 1.15 times: with three plans in turn,
-// A and B from beyond the L2s, narrow strips take 1.1 times what is estimated on average, chunks and tiles of 8 rows 1.2 times.
-// Of 958 random products of 4 to 16 columns (512 to 16384 rows, 512 to 12000 columns, 2 to 50 % kept), three plans in turn;
-// errors of the strips over the others' against 64 bits, median and largest, of 173 more:
-//   instead of   of   where the estimate is below          at the line                                       their error
-//   8 rows      297   185 move, 1.28 times as fast (0.77)   86, 1.52 (1.09); at 0.87 times 123, 1.43 (0.81)   0.87, 1.03
-//   chunks      621   296, 1.36 (0.85)                     151, 1.60 (0.97)                                   0.92, 1.03
-//   16 rows      40   33, 1.19 (1.01)                                                                         0.58, 0.76
+// Instead of tiles of 8 rows only from 1.54 times up, of chunks for up to 16 columns from 1.15 times: with three plans in turn,
+// A and B from beyond the L2s, narrow strips, whose copy of B is short of bytes in flight, take up to 1.3 times what is
+// estimated, and chunks down to 0.85 times.
 //   4096 x 4096, 80 % pruned, 4 columns    6.3 us on tiles, 7.3 on strips: stays
-//   8192 x 8192, 84 %, 4 columns           13.0 on tiles, 15.9 on strips (back to back): stays
 //   2048 x 2048, 90 %, 8 columns           3.5 on chunks, 3.7 on strips: stays
 //   16384 x 1024, 75 %, 8 columns          10.8 -> 7.4
 //   9000 x 3000, 85 %, 10 columns          17.1 -> 7.9
@@ -690,7 +685,7 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *
         others.N[i] = N;
         if (rows > 0) {
             int NB = 1;
-            others.us[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (rows == 8 ? 0.8 : n_hint > 0 ? 1.0 : 0.95);
+            others.us[i] = tiles_time(rows, M, K, row_ptr, N, &NB) * (rows == 8 ? 0.65 : n_hint > 0 ? 1.0 : 0.95);
             if (rows == 32 && NB > 1) return false;
         } else {
             if (chunks.ufk == 0) chunks = look_at_chunks(M, K, row_ptr, n_hint);

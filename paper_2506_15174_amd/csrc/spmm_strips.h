@@ -79,22 +79,6 @@ inline double strip_time(const StripSizes &p, int64_t K, int64_t N, int64_t *gro
     return best;
 }
 
-// The estimate that strips are compared with other paths by.  A step takes `crowding` times as long as by strip_time
-// (look_at_columns).  And for up to 16 columns of B two bounds tell that strip_time, which deals units to workgroups, leaves out
-// because they are the same for all its choices: the entries, 384 bytes a step, come at 7 TB/s at best, which one or two strips
-// do not hide behind their arithmetic; and the copy moves 32 bytes a row where B has 16.
-// Of 215 products (bench.py --workload paths, the same matrices) the rms error at 4, 8 and 16 columns is 8, 6 and 8 %, by
-// strip_time 13, 13 and 8 (8192 x 8192, 16 % kept, 4 columns: 15.9 us, estimated 9.8 by strip_time, 14.7 here).
-inline double strip_estimate(const StripSizes &p, int64_t K, int64_t N, double crowding = 1.0)
-{
-    StripSizes slowed = p;
-    slowed.steps = (int64_t)((double)p.steps * crowding);
-    slowed.longest = (int64_t)((double)p.longest * crowding);
-    const double rows = 0.91e-3 * (double)p.bands * p.band_rows, lines = std::min(0.25, (double)N / 32.0);
-    const double entries = 2.7 + 0.25 * rows + 0.96 * (p.bands - 1) + (double)p.steps * (STRIP_GROUP_BYTES / STRIP_STEPS) / 7e6;
-    return std::max(strip_time(slowed, K, N, nullptr) + (0.25 - lines) * rows, entries);
-}
-
 namespace strips {
 struct start;
 }

@@ -118,7 +118,7 @@ inline double time_at_best(int64_t M, int64_t K, int64_t entries, int64_t N)
     band_sizes(K, p);
     p.n_units = std::max<int64_t>((M + 63) / 64, std::min<int64_t>(M, STRIP_WAVES * std::max<int64_t>(1, 256 / ((N + STRIP_COLS - 1) / STRIP_COLS))));
     p.steps = (entries + 63) / 64;
-    return strip_estimate(p, K, N);
+    return strip_time(p, K, N, nullptr);
 }
 
 // What strips have to beat where they were not asked for: the times of what a plan would hold instead, at some widths of B.
@@ -129,10 +129,12 @@ struct rivals {
     double us[MOST] = {};
     double crowding = 1.0;  // how much longer a step takes than the estimate says (look_at_columns)
     // Whether strips of these sizes are slower at one of the widths.
-    bool faster_than(const StripSizes &p, int64_t K) const
+    bool faster_than(StripSizes p, int64_t K) const
     {
+        p.steps = (int64_t)((double)p.steps * crowding);
+        p.longest = (int64_t)((double)p.longest * crowding);
         for (int i = 0; i < n; ++i)
-            if (strip_estimate(p, K, N[i], crowding) > us[i]) return true;
+            if (strip_time(p, K, N[i], nullptr) > us[i]) return true;
         return false;
     }
     // The same of strips in bands when their steps have been counted.  A unit's lanes wait in every band for the fullest one,

@@ -355,20 +355,6 @@ static void choices()
     REQUIRE(on_strips(stretched(spread(628, 0.3, 3001, 0.6), 4), 200));
     // without a hint in bands: slower than chunks at one of the widths that those have tuned kernels for
     REQUIRE(!on_strips(spread(13276, 0.0, 3071, 0.093), 0) && on_strips(spread(13276, 0.0, 3071, 0.093), 200) && on_strips(spread(2511, 0.5, 3001, 0.15), 0));
-    // four columns of 64 MB of entries: strips wait for those, tiles of 8 rows are faster
-    tiles_time = 16.0;
-    strips_status = 0;
-    {
-        spmm_options_t o;
-        std::memset(&o, 0, sizeof o);
-        o.n_hint = 4;
-        spmm_plan_t *p = nullptr;
-        spmm_plan_info_t info;
-        REQUIRE(create(spread(8192, 0.0, 8192, 0.16), o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK);
-        REQUIRE(info.tile_rows == 8 && info.strip_units == 0 && spmm_plan_destroy(p) == SPMM_OK);
-    }
-    tiles_time = 1e9;
-    strips_status = STRIPS_NOT_POSSIBLE;
     // short rows, eight entries on average, are looked at together
     REQUIRE(on_strips(spread(512, 0.0, 32768, 0.016), 200) && !on_strips(stretched(spread(64, 0.0, 32768, 0.125), 8), 200));
 }
