@@ -658,6 +658,14 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 //   2048 x 2048, 90 %, 8 columns           3.5 on chunks, 3.7 on strips: stays
 //   16384 x 1024, 75 %, 8 columns          10.8 -> 7.4
 //   9000 x 3000, 85 %, 10 columns          17.1 -> 7.9
+// Of 958 random products of 4 to 16 columns (512 to 16384 rows, 512 to 12000 columns, 2 to 50 % kept), three plans in turn:
+//   instead of   of   move   times as fast (worst)
+//   8 rows      297     89   1.51 (1.08)
+//   chunks      621    170   1.57 (0.93)
+//   16 rows      40     33   1.19 (1.01)
+// With one plan back to back narrow strips can be slower (8192 x 8192, 84 %, 4 columns: 13.0 us on tiles, 15.9), which an
+// estimate with the entries' bytes at 7 TB/s as a bound sees.  But the others' times in turn are above their estimates as well:
+// of 17 products in 260 whose path that changed ten took 1.3 to 1.6 times as long in turn.
 //
 // Without a hint they have to be faster at each of three widths, in bands also at the other two that chunks have tuned kernels
 // for.  Of 120 products that move by 16, 64 and 200 columns 26 would be left by the estimates for 32 and 128 as well.  The 21 of
