@@ -660,8 +660,8 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 //   9000 x 3000, 85 %, 10 columns          17.1 -> 7.9
 // Of 958 random products of 4 to 16 columns (512 to 16384 rows, 512 to 12000 columns, 2 to 50 % kept), three plans in turn:
 //   instead of   of   move   times as fast (worst)
-//   8 rows      297     89   1.51 (1.08)
-//   chunks      621    170   1.57 (0.93)
+//   8 rows      297     89   1.51 (1.07)
+//   chunks      621    170   1.58 (0.94)
 //   16 rows      40     33   1.19 (1.01)
 // With one plan back to back narrow strips can be slower (8192 x 8192, 84 %, 4 columns: 13.0 us on tiles, 15.9), which an
 // estimate with the entries' bytes at 7 TB/s as a bound sees.  But the others' times in turn are above their estimates as well:
