@@ -668,12 +668,15 @@ void look_at_columns(int64_t M, const int32_t *row_ptr, const int32_t *col_idx, 
 // of 17 products in 260 whose path that changed ten took 1.3 to 1.6 times as long in turn.
 //
 // Without a hint they have to be faster at each of three widths, in bands also at the other two that chunks have tuned kernels
-// for.  Of 120 products that move by 16, 64 and 200 columns 26 would be left by the estimates for 32 and 128 as well.  The 21 of
-// one band take 0.4 to 1.02 times as long on strips at any width from 4 to 256 columns (the time on chunks of uneven rows is
-// estimated too low); the five in bands up to 1.22 at 32, 1.10 at 128 (6925 x 5876, 3.2 %, 32 columns; 2286 x 11700, 14 %, 128).
-// Of 120 others (all of 2^17 entries and more) 49 move, from chunks and tiles of 16 rows, and are faster at every width up to 200:
-// 1.02 times at least, on average 1.4 (32 columns) to 1.8 (200).  At 256, where chunks fill two column tiles, 1.4, three
-// of them in bands slower, 0.81 at worst.
+// for unless the rows are skewed.  Of 120 products that move by 16, 64 and 200 columns 26 would be left by the estimates for 32
+// and 128 as well.  The 21 of one band take 0.4 to 1.02 times as long on strips at any width from 4 to 256 columns (the time on
+// chunks of uneven rows is estimated too low); the five in bands up to 1.22 at 32, 1.10 at 128 (6925 x 5876, 3.2 %, 32 columns;
+// 2286 x 11700, 14 %, 128).
+// Of 109 others in bands, three plans in turn, the two widths would leave 30; time on strips, on average and at most:
+//                            16 columns    32            64            128           200           256
+//   18 of even rows, left     0.71, 0.90    0.92, 1.15    0.80, 0.96    0.97, 1.09    0.73, 0.88    1.03, 1.32
+//   12 of skewed, they stay   0.70, 0.77    0.90, 1.02    0.76, 0.82    0.73, 1.00    0.75, 0.85    1.15, 1.39
+//   79 that stay anyway       0.55, 0.84    0.70, 1.07    0.62, 0.81    0.72, 0.93    0.62, 0.87    0.80, 1.28
 // Of 252 more that move in one band one takes more than 1.03 times as long at one of eleven widths (5140 x 3637, 3.4 %, 32
 // columns: 6.8 -> 7.3 us; the other 251 0.67 on average there), and so does 4096 x 4096, 95 % pruned: 7.0 -> 7.8 at 32
 // columns, 9.6 -> 9.0 at 64, 16.3 -> 11.5 at 128.  There chunks are estimated to take 8.7, so looking at 32 columns does not
@@ -686,7 +689,7 @@ bool choose_strips(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *
     if (nnz == 0 || (nnz < ((int64_t)1 << 17) && n_hint <= 128)) return false;
     const int32_t hinted[] = {std::min(std::max(n_hint, 4), 256)}, unknown[] = {16, 64, 200, 32, 128};
     strips::rivals &others = begun.others;
-    others.n = n_hint > 0 ? 1 : K > STRIP_MOST_ROWS ? 5 : 3;
+    others.n = n_hint > 0 ? 1 : K > STRIP_MOST_ROWS && !skewed_rows(row_ptr, M, nnz) ? 5 : 3;
     double margin = 10.0;
     for (int i = 0; i < others.n; ++i) {
         const int32_t N = n_hint > 0 ? hinted[i] : unknown[i];

@@ -355,6 +355,8 @@ static void choices()
     REQUIRE(on_strips(stretched(spread(628, 0.3, 3001, 0.6), 4), 200));
     // without a hint in bands: slower than chunks at one of the widths that those have tuned kernels for
     REQUIRE(!on_strips(spread(13276, 0.0, 3071, 0.093), 0) && on_strips(spread(13276, 0.0, 3071, 0.093), 200) && on_strips(spread(2511, 0.5, 3001, 0.15), 0));
+    // ... which the estimates tell of rows that are not skewed only
+    REQUIRE(on_strips(spread(8330, 2.0, 2167, 0.05), 0));
     // short rows, eight entries on average, are looked at together
     REQUIRE(on_strips(spread(512, 0.0, 32768, 0.016), 200) && !on_strips(stretched(spread(64, 0.0, 32768, 0.125), 8), 200));
 }
