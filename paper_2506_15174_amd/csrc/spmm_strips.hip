@@ -15,6 +15,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 typedef float f32x4_unaligned __attribute__((ext_vector_type(4), aligned(4)));
+typedef const uint64_t __attribute__((address_space(4))) scalar_words;  // read through the scalar cache where the address is uniform
 
 struct strip_args {
     const char *stream;
@@ -78,6 +79,11 @@ __device__ __forceinline__ float add_half(float v)
 //   3001 x 2511, 85 % in lognormal rows, 200 columns          37.4 (35.3) -> 17.8 (17.0)
 //   8968 x 2473, 92 %, 96 columns                             41.3 (39.2) -> 14.0 (13.2)
 //
+// One back to back, with the entries' addresses read only when a unit or band begins, waits for all fetches once a round and the
+// waves in the order of their age, and as it is now: the second 17.4 -> 16.4 us, the third 13.1 -> 12.9, 8192 x 8192, 95 % in lognormal rows, 64
+// columns, in two bands 22.8 -> 21.7, 5376 x 14464, 89 %, 40 columns, in three 36.2 -> 33.9; up to 2 % longer where a wave has ten groups or fewer.
+// Four or six groups in registers are slower by 1 and 5 %, a third half of a group read ahead from LDS by 1 %.
+//
 // An accumulator's registers hold columns 1 0 3 2 of its four: a v_fmac of three registers that are all even or all odd takes 4.9
 // cycles, else 2.8, and those of LDS hold them in order (1 to 3 % of the product).
 template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, STRIP_WAVES / 4) void spmm_strips_kernel(const strip_args args)
@@ -90,6 +96,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     const uint32_t group = (uint32_t)(place / args.n_strips), strip = (uint32_t)(place % args.n_strips);
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
+    constexpr int AHEAD = 3;  // groups of a unit in registers: the one at work and the next two
     constexpr int Q = 2;  // fours of columns; the lane reads four i ^ turn of its rows as the i-th
     static_assert(Q * 4 == STRIP_COLS, "the fours of a row change places with one bit");
     const uint32_t turn = (uint32_t)lane % Q, N = (uint32_t)args.N, col0 = strip * STRIP_COLS, band_rows = (uint32_t)args.band_rows;
@@ -97,9 +104,12 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     const uint32_t own = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)lds + turn * 16u;  // what the lane reads first of row 0
 
     if (threadIdx.x < Q) *reinterpret_cast<f32x4 *>(lds + band_rows * STRIP_ROW_BYTES + threadIdx.x * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    auto copy_band = [&](uint32_t band) {
+    // (in two parts, the first EARLY operations of a wave and the others: the entries that it begins with are asked for between them)
+    constexpr uint32_t EARLY = 2;
+    auto copy_band = [&](uint32_t band, bool early) {
         const uint32_t row0 = band * band_rows, rows = min(band_rows, (uint32_t)args.K - row0);
         if constexpr (WIDE) {
+            if (early) return;
             for (uint32_t t = threadIdx.x; t < rows * Q; t += 64 * STRIP_WAVES) {
                 const float *p = args.B + (uint64_t)(row0 + t / Q) * N;
                 const uint32_t n = col0 + t % Q * 4;
@@ -113,7 +123,8 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             // does not have.)
             const uint32_t off = (uint32_t)(lane / Q) * N * 4u + (uint32_t)(lane % Q) * 16u;
             constexpr uint32_t OP_ROWS = 64 / Q;
-            for (uint32_t op = (uint32_t)wave; op * OP_ROWS < rows; op += STRIP_WAVES) {
+            const uint32_t begin = early ? 0u : EARLY * STRIP_WAVES, end = early ? EARLY * STRIP_WAVES : ~0u;
+            for (uint32_t op = begin + (uint32_t)wave; op < end && op * OP_ROWS < rows; op += STRIP_WAVES) {
                 const uint64_t skip = ((uint64_t)(row0 + op * OP_ROWS) * N + col0) * 4u, left = args.b_bytes - skip;
                 const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(args.B)) + skip, (short)0,
                                                                                    (int)(left > 0xFFFFFFFCull ? 0xFFFFFFFCu : (uint32_t)left), 0x00020000);
@@ -121,12 +132,25 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             }
         }
     };
-    copy_band(0);
+    // A unit's groups in a band (none where there is no unit), asked for when those before them are still to be multiplied.
+    struct run {
+        uint32_t first, groups;
+    };
+    auto groups_of = [&](uint32_t unit, uint32_t band) {
+        const bool is = unit < args.n_units;
+        const uint64_t d = ((scalar_words *)args.units)[(size_t)(is ? unit : 0u) * (uint32_t)bands + band];
+        return run{(uint32_t)d, is ? (uint32_t)(d >> 32) : 0u};
+    };
+    const uint32_t pitch = STRIP_WAVES * args.n_groups;
+    uint32_t unit = group + (uint32_t)wave * args.n_groups;
+    run next = groups_of(unit, 0);
+    copy_band(0, true);
     bool copied = false;  // the first band, and waited for
 
-    for (uint32_t unit = group + (uint32_t)wave * args.n_groups;; unit += STRIP_WAVES * args.n_groups) {
+    for (;; unit += pitch) {
         const bool any = unit < args.n_units;
         if (!any && copied) break;
+        uint32_t word = STRIP_NO_ROW;
         f32x4 acc[STRIP_STEPS][Q], total[Q] = {};  // of the last groups; of all before them
         int rounds = 0;                             // of up to three groups that are in acc, of all bands
         auto collect = [&] {
@@ -142,24 +166,35 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
 #pragma unroll
             for (int q = 0; q < Q; ++q) acc[e][q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         for (int band = 0; band < bands; ++band) {
-            const u32x2 d = any ? args.units[(size_t)unit * (uint32_t)bands + (uint32_t)band] : u32x2{0u, 0u};
-            const uint32_t first = __builtin_amdgcn_readfirstlane(d[0]), groups = __builtin_amdgcn_readfirstlane(d[1]);
+            const uint32_t first = next.first, groups = next.groups;
             const char *stream = args.stream + (size_t)first * STRIP_GROUP_BYTES;
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(stream), (short)0, (int)(groups * STRIP_GROUP_BYTES), 0x00020000);
-            f32x4 values[3];  // of the group at work and the next two
-            u32x2 places[3];
+            f32x4 values[AHEAD];
+            u32x2 places[AHEAD];
             auto fetch = [&](int k, uint32_t g) {  // nothing past the unit
                 values[k] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(r, lane * 16, (int)(g * STRIP_GROUP_BYTES), 0));
                 places[k] = __builtin_amdgcn_raw_buffer_load_b64(r, 1024 + lane * 8, (int)(g * STRIP_GROUP_BYTES), 0);
             };
+            // The compiler would move the loads to their first use.
+            auto keep_order = [] { __builtin_amdgcn_sched_barrier(0); };
+            keep_order();
             fetch(0, 0);
+            keep_order();
             fetch(1, 1);
+            keep_order();
+            next = band + 1 < bands ? groups_of(unit, (uint32_t)band + 1u) : groups_of(unit + pitch, 0u);
             if (BANDS && band > 0) {
                 __syncthreads();
-                copy_band((uint32_t)band);
+                copy_band((uint32_t)band, true);
             }
-            if (BANDS || !copied) __syncthreads();
+            if (BANDS || !copied) {
+                copy_band((uint32_t)band, false);
+                __syncthreads();
+            }
             copied = true;
+            if (!BANDS || band + 1 == bands) word = args.rows[(size_t)(any ? unit : 0u) * 64u + (uint32_t)lane];
+            // (waited for here: in the loop below its wait would be one for all reads of LDS)
+            asm volatile("" ::"s"(next.first), "s"(next.groups));
             f32x4 x[2][2][Q];  // rows of the strip: two steps each, read while the other two are multiplied
             auto read = [&](int k, int h) {
 #pragma unroll
@@ -184,33 +219,51 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
                             to[c ^ 1] = __builtin_fmaf(values[k][2 * h + e], x[h][e][q][c], to[c ^ 1]);
                         }
             };
-            // The compiler would move the loads to their first use.
-            auto keep_order = [] { __builtin_amdgcn_sched_barrier(0); };
-            read(0, 0);
-            for (uint32_t g = 0; g < groups; g += 3) {
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    if (k > 0 && g + (uint32_t)k >= groups) break;
-                    fetch((k + 2) % 3, g + (uint32_t)k + 2u);
-                    keep_order();
-                    read(k, 1);
-                    keep_order();
-                    multiply(k, 0);
-                    keep_order();
-                    read((k + 1) % 3, 0);
-                    keep_order();
-                    multiply(k, 1);
-                    keep_order();
-                }
+            auto work = [&](int k, bool more) {
+                read(k, 1);
+                keep_order();
+                multiply(k, 0);
+                keep_order();
+                if (more) read((k + 1) % AHEAD, 0);
+                keep_order();
+                multiply(k, 1);
+                keep_order();
+            };
+            auto round_ends = [&] {
                 // (four registers in a row, not any four)
 #pragma unroll
                 for (int e = 0; e < STRIP_STEPS; ++e)
 #pragma unroll
                     for (int q = 0; q < Q; ++q) asm volatile("" : "+v"(acc[e][q]));
-                if (++rounds == 4) {
+                if (++rounds == 12 / AHEAD) {
                     collect();
                     rounds = 0;
                 }
+            };
+            // Whole rounds first, then what is left of one: a loop that may be left inside of a round makes the compiler wait, at its
+            // top, for every fetch but the last.
+            __builtin_amdgcn_s_waitcnt(0x0F72);  // all but two loads (of which it would wait for the last in the loop)
+            read(0, 0);
+            uint32_t g = 0;
+            for (; g + AHEAD <= groups; g += AHEAD) {
+                // Of the four waves of a SIMD the one that started first would go first: 9.7, 10.1, 10.8 and 11.5 us at the end of equal units.
+                // The wave that has least behind it does.
+                if (g * 4u < groups) __builtin_amdgcn_s_setprio(3);
+                else if (g * 2u < groups) __builtin_amdgcn_s_setprio(2);
+                else if (g * 4u < groups * 3u) __builtin_amdgcn_s_setprio(1);
+                else __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+                for (int k = 0; k < AHEAD; ++k) {
+                    fetch((k + 2) % AHEAD, g + (uint32_t)k + 2u);
+                    keep_order();
+                    work(k, true);
+                }
+                round_ends();
+            }
+            if (g < groups) {
+                work(0, true);
+                if (g + 1 < groups) work(1, false);
+                round_ends();
             }
         }
         if (!any) break;
@@ -219,7 +272,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
         // one has it as its second); from then on a lane has one four
 #pragma unroll
         for (int q = 0; q < Q; ++q) total[q] = __builtin_shufflevector(total[q], total[q], 1, 0, 3, 2);
-        const uint32_t word = args.rows[(size_t)unit * 64u + (uint32_t)lane], row = word & ((1u << STRIP_PARTS_SHIFT) - 1u);
+        const uint32_t row = word & ((1u << STRIP_PARTS_SHIFT) - 1u);
         const uint32_t parts_log2 = __builtin_amdgcn_readfirstlane(word >> STRIP_PARTS_SHIFT);  // lane 0 has a row
         auto each = [&](auto f) {
 #pragma unroll
