@@ -80,8 +80,8 @@ __device__ __forceinline__ float add_half(float v)
 //   8968 x 2473, 92 %, 96 columns                             41.3 (39.2) -> 14.0 (13.2)
 //
 // One back to back, with the entries' addresses read only when a unit or band begins, waits for all fetches once a round and the
-// waves in the order of their age, and as it is now: the second 17.4 -> 16.4 us, the third 13.1 -> 12.9, 8192 x 8192, 95 % in lognormal rows, 64
-// columns, in two bands 22.8 -> 21.7, 5376 x 14464, 89 %, 40 columns, in three 36.2 -> 33.9; up to 2 % longer where a wave has ten groups or fewer.
+// waves in the order of their age, and as it is now: the second 18.5 -> 17.5 us, the third 14.5 -> 14.2, 8192 x 8192, 95 % in lognormal rows, 64
+// columns, in two bands 24.5 -> 23.6, 5376 x 14464, 89 %, 40 columns, in three 39.0 -> 37.2; 28 products 2 % on average, two of them 2 % slower.
 // Four or six groups in registers are slower by 1 and 5 %, a third half of a group read ahead from LDS by 1 %.
 //
 // An accumulator's registers hold columns 1 0 3 2 of its four: a v_fmac of three registers that are all even or all odd takes 4.9
@@ -104,12 +104,9 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     const uint32_t own = (uint32_t)(size_t)(__attribute__((address_space(3))) char *)lds + turn * 16u;  // what the lane reads first of row 0
 
     if (threadIdx.x < Q) *reinterpret_cast<f32x4 *>(lds + band_rows * STRIP_ROW_BYTES + threadIdx.x * 16) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    // (in two parts, the first EARLY operations of a wave and the others: the entries that it begins with are asked for between them)
-    constexpr uint32_t EARLY = 2;
-    auto copy_band = [&](uint32_t band, bool early) {
+    auto copy_band = [&](uint32_t band) {
         const uint32_t row0 = band * band_rows, rows = min(band_rows, (uint32_t)args.K - row0);
         if constexpr (WIDE) {
-            if (early) return;
             for (uint32_t t = threadIdx.x; t < rows * Q; t += 64 * STRIP_WAVES) {
                 const float *p = args.B + (uint64_t)(row0 + t / Q) * N;
                 const uint32_t n = col0 + t % Q * 4;
@@ -123,8 +120,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             // does not have.)
             const uint32_t off = (uint32_t)(lane / Q) * N * 4u + (uint32_t)(lane % Q) * 16u;
             constexpr uint32_t OP_ROWS = 64 / Q;
-            const uint32_t begin = early ? 0u : EARLY * STRIP_WAVES, end = early ? EARLY * STRIP_WAVES : ~0u;
-            for (uint32_t op = begin + (uint32_t)wave; op < end && op * OP_ROWS < rows; op += STRIP_WAVES) {
+            for (uint32_t op = (uint32_t)wave; op * OP_ROWS < rows; op += STRIP_WAVES) {
                 const uint64_t skip = ((uint64_t)(row0 + op * OP_ROWS) * N + col0) * 4u, left = args.b_bytes - skip;
                 const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(args.B)) + skip, (short)0,
                                                                                    (int)(left > 0xFFFFFFFCull ? 0xFFFFFFFCu : (uint32_t)left), 0x00020000);
@@ -144,7 +140,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
     const uint32_t pitch = STRIP_WAVES * args.n_groups;
     uint32_t unit = group + (uint32_t)wave * args.n_groups;
     run next = groups_of(unit, 0);
-    copy_band(0, true);
+    copy_band(0);
     bool copied = false;  // the first band, and waited for
 
     for (;; unit += pitch) {
@@ -185,11 +181,11 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             next = band + 1 < bands ? groups_of(unit, (uint32_t)band + 1u) : groups_of(unit + pitch, 0u);
             if (BANDS && band > 0) {
                 __syncthreads();
-                copy_band((uint32_t)band, true);
-            }
-            if (BANDS || !copied) {
-                copy_band((uint32_t)band, false);
+                copy_band((uint32_t)band);
                 __syncthreads();
+            } else if (!copied) {
+                // all loads but the four of the entries, which a barrier of the compiler's would wait for too
+                asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
             }
             copied = true;
             if (!BANDS || band + 1 == bands) word = args.rows[(size_t)(any ? unit : 0u) * 64u + (uint32_t)lane];
@@ -244,13 +240,14 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             // top, for every fetch but the last.
             __builtin_amdgcn_s_waitcnt(0x0F72);  // all but two loads (of which it would wait for the last in the loop)
             read(0, 0);
+            // Of the four waves of a SIMD the one that started first would go first: 9.7, 10.1, 10.8 and 11.5 us at the end of equal units.
+            // Of those at their last unit the one that has least of it behind it does, before them those that have another.
+            const uint32_t last = unit + pitch >= args.n_units ? groups : ~0u / 4u;
             uint32_t g = 0;
             for (; g + AHEAD <= groups; g += AHEAD) {
-                // Of the four waves of a SIMD the one that started first would go first: 9.7, 10.1, 10.8 and 11.5 us at the end of equal units.
-                // The wave that has least behind it does.
-                if (g * 4u < groups) __builtin_amdgcn_s_setprio(3);
-                else if (g * 2u < groups) __builtin_amdgcn_s_setprio(2);
-                else if (g * 4u < groups * 3u) __builtin_amdgcn_s_setprio(1);
+                if (g * 4u < last) __builtin_amdgcn_s_setprio(3);
+                else if (g * 2u < last) __builtin_amdgcn_s_setprio(2);
+                else if (g * 4u < last * 3u) __builtin_amdgcn_s_setprio(1);
                 else __builtin_amdgcn_s_setprio(0);
 #pragma unroll
                 for (int k = 0; k < AHEAD; ++k) {
