@@ -45,6 +45,7 @@ struct spmm_plan {
     bool probe = false;       // spmm_options_t.probe: loads-only launches (measurement)
     int32_t heavy = 0;        // the first blocks that are heavier than most (heavy_blocks)
     uint32_t lds_pad = 0;     // extra LDS per workgroup that keeps a third one off a compute unit (hold_to_two)
+    int32_t n_dealt = 0;      // blocks behind the plan's own in d_items, dealt to the compute units (deal_blocks)
 };
 
 namespace {
@@ -77,7 +78,7 @@ int32_t heavy_blocks(const HostPlan &h)
 // shrinks by 24 chunks or more.  Timed with and without it, 360 random plans of 513 to 768 workgroups: the 23
 // that this takes run 6 % faster on average (20 % to two of 10 and 13 % slower); the other plans of single rows,
 // held all the same, would be 3 % slower, and so would the ten of taller panels that it would take, whose
-// registers leave less room for a third workgroup to begin with.
+// registers leave less room for a third workgroup to begin with.  (A launch of dealt blocks does without.)
 bool hold_to_two(const HostPlan &h)
 {
     constexpr int64_t UNITS = 256;
@@ -93,6 +94,72 @@ bool hold_to_two(const HostPlan &h)
     }
     const double ratio = (double)*std::max_element(held.begin(), held.end()) / (double)std::max<int64_t>(1, *std::max_element(dealt.begin(), dealt.end()));
     return ratio <= 0.86 && (double)h.n_chunks / UNITS * (1.0 - ratio) >= 24.0;
+}
+
+// The blocks in the order in which compute units are loaded evenly; empty where the order they have does that.
+//
+// While all workgroups of a launch fit the chip the device deals them out in turn: block b goes to the unit of block
+// b - 256 (looked up for 512 to 1024 workgroups of this size), whatever they weigh.  The blocks come heaviest first, so the
+// first units get the heaviest of every round and, where the number of blocks is no multiple of 256, a block more.  Here every
+// block, heaviest first, goes to the unit that has least so far, at most `per_unit` to one; a unit's r-th block is at place
+// 256 r + unit, units with most blocks first, and idle blocks, which end at once, fill the places between.
+// A gather is bound by the unit's vector L1, so a unit's time is the sum of its blocks' chunks; a block's start and end
+// count as STARTING chunks.  A plan whose fullest unit gains less than 3 % keeps its order.
+//
+// In the plan's own order (the first and third held to two workgroups, hold_to_two) and dealt, lognormal rows:
+//   1024 x 4096, 90 % pruned, 64 columns, 560 blocks     8.8 -> 7.5 us
+//   1024 x 2048, 90 %, 64 columns, 286 blocks            6.5 -> 5.1
+//   1536 x 6144, 95 %, 64 columns, 646 blocks            9.7 -> 7.6
+//   700 x 5000, 90 %, 100 columns, 323 of two rows      14.7 -> 11.2
+//   2048 x 4096, 90 %, 32 columns, 932 blocks            8.2 -> 7.1
+//   5000 x 2000, 97 %, 128 columns, 704 blocks           9.0 -> 8.2
+// Twenty even, lognormal and Zipf matrices 8 % on average, none slower.  More blocks than the chip holds go to whichever unit is done first,
+// and several column tiles have an order of their own (front_blocks).
+std::vector<uint32_t> deal_blocks(const HostPlan &h, int per_unit)
+{
+    constexpr int64_t UNITS = 256, STARTING = 8;
+    const int64_t n = h.n_blocks;
+    if (n <= UNITS || n > UNITS * per_unit || h.k_slices > 1 || h.n_cross > 0) return {};
+    std::vector<std::pair<int64_t, int32_t>> blocks((size_t)n);
+    std::vector<int64_t> as_is((size_t)UNITS, 0);
+    for (int64_t b = 0; b < n; ++b) {
+        blocks[(size_t)b] = {block_weight(h, b) + STARTING, (int32_t)b};
+        as_is[(size_t)(b % UNITS)] += blocks[(size_t)b].first;
+    }
+    std::stable_sort(blocks.begin(), blocks.end(), [](const auto &x, const auto &y) { return x.first > y.first; });
+    struct unit {
+        int64_t load;
+        int32_t number;
+        bool operator<(const unit &u) const { return load != u.load ? load > u.load : number > u.number; }  // the least loaded on top
+    };
+    std::vector<unit> heap((size_t)UNITS);
+    std::vector<std::vector<int32_t>> of((size_t)UNITS);
+    for (int32_t u = 0; u < UNITS; ++u) heap[(size_t)u] = {0, u};
+    std::make_heap(heap.begin(), heap.end());
+    int64_t most = 0;
+    for (const auto &[weight, block] : blocks) {
+        std::pop_heap(heap.begin(), heap.end());
+        unit &u = heap.back();
+        of[(size_t)u.number].push_back(block);
+        u.load += weight;
+        most = std::max(most, u.load);
+        if ((int)of[(size_t)u.number].size() < per_unit) std::push_heap(heap.begin(), heap.end());
+        else heap.pop_back();
+    }
+    if (most * 100 > *std::max_element(as_is.begin(), as_is.end()) * 97) return {};
+    std::stable_sort(of.begin(), of.end(), [](const auto &x, const auto &y) { return x.size() > y.size(); });
+    const int64_t rounds = (int64_t)of[0].size();
+    int64_t last = 0;  // units with a block in the last round
+    while (last < UNITS && (int64_t)of[(size_t)last].size() == rounds) ++last;
+    constexpr size_t WORDS = (size_t)WAVES_PER_WG * ITEM_WORDS;
+    std::vector<uint32_t> items((size_t)((rounds - 1) * UNITS + last) * WORDS, 0u);
+    for (size_t at = 0; at < items.size(); at += WORDS) {
+        const size_t place = at / WORDS, round = place / (size_t)UNITS;
+        const std::vector<int32_t> &u = of[place % (size_t)UNITS];
+        if (round < u.size()) std::copy_n(h.items.begin() + (ptrdiff_t)((size_t)u[round] * WORDS), WORDS, items.begin() + (ptrdiff_t)at);
+        else for (size_t w = 0; w < (size_t)WAVES_PER_WG; ++w) items[at + w * ITEM_WORDS + IT_FLAGS] = FLAG_IDLE;
+    }
+    return items;
 }
 
 spmm_status_t hip_fail()
@@ -279,8 +346,14 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
             if (st == SPMM_OK) st = upload(&p->d_cross_table, h.cross.data(), h.cross.size() * 4, p->device_bytes);
             if (st == SPMM_OK) st = upload(&p->d_stream, h.stream.data(), h.stream.size() * 4, p->device_bytes);
             if (st == SPMM_OK) st = upload(&p->d_wins, h.wins.data(), h.wins.size() * 4, p->device_bytes);
-            if (st == SPMM_OK) st = upload(&p->d_items, h.items.data(), h.items.size() * 4, p->device_bytes);
             p->heavy = heavy_blocks(h);
+            // for the widest tile of as many columns as the plan is meant for
+            const int slices = h.ufk == 16 ? 8 : h.ufk == 32 ? 16 : h.ufk == 64 ? 32 : io.n_hint <= 0 || io.n_hint > 64 ? 2 : io.n_hint > 32 ? 4 : 8;
+            std::vector<uint32_t> dealt = deal_blocks(h, workgroups_per_unit(slices, h.ufi, h.ufk, false));
+            p->n_dealt = (int32_t)(dealt.size() / ((size_t)WAVES_PER_WG * ITEM_WORDS));
+            if (p->n_dealt > 0) dealt.insert(dealt.begin(), h.items.begin(), h.items.end());
+            const std::vector<uint32_t> &items = p->n_dealt > 0 ? dealt : h.items;
+            if (st == SPMM_OK) st = upload(&p->d_items, items.data(), items.size() * 4, p->device_bytes);
             if (h.k_slices == 1 && win_words(h.ufk) == WIN_WORDS && hold_to_two(h)) p->lds_pad = 48u << 10;  // 32 KiB and these: half of a unit's LDS
         }
         if (st != SPMM_OK) return st;
@@ -466,6 +539,9 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
         a.tile_cols = tile;
         a.n_tiles = n_tiles;
         a.lds_pad = tile_pad == 0 && n_tiles == 1 ? plan->lds_pad : tile_pad;
+        const bool dealt = n_tiles == 1 && tile_pad == 0 && plan->n_dealt <= 256 * workgroups_per_unit(slices, h.ufi, h.ufk, wide);
+        a.dealt = plan->d_items + (size_t)h.n_blocks * WAVES_PER_WG * ITEM_WORDS;
+        a.n_dealt = dealt ? plan->n_dealt : 0;
         const uint64_t skipped = (uint64_t)j0 * 4u;
         a.b_bytes = wide || b_total <= skipped ? 0u : (uint32_t)(b_total - skipped);
         const int e = spmm_launch_chunks(a, h.ufi, h.ufk, slices, wide, plan->depth, stream);

@@ -6,12 +6,56 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "spmm_format.h"
+
+// Waves per SIMD the register budget of an instance is sized for.  Narrow slices
+// keep few B rows in flight per wave and walk a long dependent chain per chunk
+// (header, row branches, LDS reads), so they need more resident waves to cover
+// it: 8 (64 VGPRs) with eight slices, 6 (80 VGPRs) with four, 4 (128 VGPRs)
+// with two.  The eight-row tile alone is 32 registers: 4 waves whatever the slices
+// (sized for 6, the eight-slice instance spilled 68 registers and ran 10-28 % slower).
+// Waves per SIMD an instance is compiled for (its register budget: 512 / waves).  Measured on
+// the pruned-layer shapes with every depth forced: past two or three chunks in flight a deeper
+// pipeline buys nothing (the memory path, not the number of requests a wave has outstanding,
+// paces the gather), while every further resident wave hides more of the chunk's dependent
+// chain (header, row branches, value reads).  So each instance takes the shallowest pipeline
+// that keeps the loads flowing and the occupancy its tile allows: eight-row tiles 4 waves
+// (6 on four slices), four-row tiles 4 waves on two slices and 8 otherwise, shorter tiles 6 to
+// 8.  Wider chunks (UFKT > 8) give a slice two column slots per chunk: 8 waves (6 with eight
+// rows); windows of 2048 words (UFKT >= 32) cap a compute unit at two workgroups.
+// Every budget is one the instance fits without spilling (the build checks it): a spilled
+// register could be the destination of a B row still in flight.  64-bit addressing costs a
+// register more per column slot, so those instances get the budget of two waves fewer.
+constexpr int waves_per_simd(int S, int UFI, int UFKT, bool WIDE)
+{
+    const int narrow = UFKT >= 32  ? 4
+                       : UFKT == 16 ? (UFI > 4 ? 6 : 8)
+                       : S == 1     ? 4
+                       : UFI == 8   ? (S == 2 ? 4 : 6)
+                       : UFI == 4   ? (S == 2 ? 4 : 8)
+                       : UFI == 2   ? (S == 2 ? 6 : 8)
+                                    : 8;
+    return WIDE ? (narrow > 4 ? narrow - 2 : 2) : narrow;
+}
+
+// Workgroups of an instance that share a compute unit: by its registers, and by 160 KiB of LDS.
+constexpr int workgroups_per_unit(int S, int UFI, int UFKT, bool WIDE)
+{
+    const int by_waves = waves_per_simd(S, UFI, UFKT, WIDE) * 4 / spmm_fmt::WAVES_PER_WG;
+    const int by_lds = 160 * 1024 / (spmm_fmt::WAVES_PER_WG * spmm_fmt::win_words(UFKT) * 4);
+    return by_waves < by_lds ? by_waves : by_lds;
+}
+
 struct spmm_launch_args {
     const uint32_t *stream; // DEVICE staging windows: headers, column indices, value bits
     const uint32_t *wins;   // DEVICE window table
     const uint32_t *items;  // DEVICE wave-slot descriptors, 16 per block
     const uint32_t *rowmap = nullptr; // DEVICE row of C per row of the plan, or null (same rows)
     int32_t n_blocks;       // workgroups to launch
+    // The same descriptors in the order in which compute units are loaded evenly, idle blocks among them (deal_blocks), for a
+    // launch of one column tile; it needs no lds_pad.  None: 0.
+    const uint32_t *dealt = nullptr;
+    int32_t n_dealt = 0;
     const float *B;         // DEVICE first column of the launch's first column tile
     uint32_t b_bytes;       // bytes of B reachable from that pointer (narrow addressing only)
     float *C;               // DEVICE first column of the launch's first column tile (of the slices' buffer when k_slices > 1)

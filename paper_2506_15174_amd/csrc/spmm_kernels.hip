@@ -280,42 +280,6 @@ template <int UFKT> __device__ __forceinline__ uint32_t value_block(uint32_t at,
     return w < limit ? w : limit;
 }
 
-// UFI   rows per panel (1, 2, 4, 8): height of the register tile
-// S     slices per wave (1, 2, 4, 8; 16, 32, 64 for narrow B); a slice has 64 / S lanes and UFKT / S column slots per chunk
-// UFKT  enumerated columns per chunk of the plan (8; 16, 32, 64 in plans made for narrow B)
-// VW    columns per lane (4 with 16-byte loads; 1 for the generic path, S == 1 only)
-// D     chunks of B rows in flight per wave
-// WIDE  64-bit addressing of B
-// Waves per SIMD the register budget of an instance is sized for.  Narrow slices
-// keep few B rows in flight per wave and walk a long dependent chain per chunk
-// (header, row branches, LDS reads), so they need more resident waves to cover
-// it: 8 (64 VGPRs) with eight slices, 6 (80 VGPRs) with four, 4 (128 VGPRs)
-// with two.  The eight-row tile alone is 32 registers: 4 waves whatever the slices
-// (sized for 6, the eight-slice instance spilled 68 registers and ran 10-28 % slower).
-// Waves per SIMD an instance is compiled for (its register budget: 512 / waves).  Measured on
-// the pruned-layer shapes with every depth forced: past two or three chunks in flight a deeper
-// pipeline buys nothing (the memory path, not the number of requests a wave has outstanding,
-// paces the gather), while every further resident wave hides more of the chunk's dependent
-// chain (header, row branches, value reads).  So each instance takes the shallowest pipeline
-// that keeps the loads flowing and the occupancy its tile allows: eight-row tiles 4 waves
-// (6 on four slices), four-row tiles 4 waves on two slices and 8 otherwise, shorter tiles 6 to
-// 8.  Wider chunks (UFKT > 8) give a slice two column slots per chunk: 6 waves (4 with eight
-// rows); windows of 2048 words (UFKT >= 32) cap a compute unit at two workgroups.
-// Every budget is one the instance fits without spilling (the build checks it): a spilled
-// register could be the destination of a B row still in flight.  64-bit addressing costs a
-// register more per column slot, so those instances get the budget of two waves fewer.
-constexpr int waves_per_simd(int S, int UFI, int UFKT, bool WIDE)
-{
-    const int narrow = UFKT >= 32  ? 4
-                       : UFKT == 16 ? (UFI > 4 ? 4 : 6)
-                       : S == 1     ? 4
-                       : UFI == 8   ? (S == 2 ? 4 : 6)
-                       : UFI == 4   ? (S == 2 ? 4 : 8)
-                       : UFI == 2   ? (S == 2 ? 6 : 8)
-                                    : 8;
-    return WIDE ? (narrow > 4 ? narrow - 2 : 2) : narrow;
-}
-
 // Arguments of a launch as one structure: the runtime copies a kernel's arguments one by one,
 // about 60 ns each, and the host's share of a launch is what paces the shortest products
 // (fourteen separate arguments 3.5 us per launch of an empty kernel, one structure 2.65 us).
@@ -328,6 +292,12 @@ struct chunk_args {
     uint32_t n_blocks, n_tiles, front;  // front: see place_of
 };
 
+// UFI   rows per panel (1, 2, 4, 8): height of the register tile
+// S     slices per wave (1, 2, 4, 8; 16, 32, 64 for narrow B); a slice has 64 / S lanes and UFKT / S column slots per chunk
+// UFKT  enumerated columns per chunk of the plan (8; 16, 32, 64 in plans made for narrow B)
+// VW    columns per lane (4 with 16-byte loads; 1 for the generic path, S == 1 only)
+// D     chunks of B rows in flight per wave
+// WIDE  64-bit addressing of B
 // PROBE instances request and await every B row exactly as the product does but skip the
 // value reads and the multiply-adds (C becomes all zeros): the time of such a launch is the
 // on-chip gather ceiling of the plan's own index stream.
@@ -710,6 +680,14 @@ template <int U, int D> bool launch_narrow(const spmm_launch_args &a, int ufk, i
 int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, bool wide, int depth, void *stream)
 {
     if (a.n_blocks <= 0 || a.n_tiles <= 0) return 0;
+    if (a.n_dealt > 0) {
+        spmm_launch_args dealt = a;
+        dealt.items = a.dealt;
+        dealt.n_blocks = a.n_dealt;
+        dealt.lds_pad = 0;
+        dealt.n_dealt = 0;
+        return spmm_launch_chunks(dealt, ufi, ufk, slices, wide, depth, stream);
+    }
     if (ufk != UFK) {
         bool ok = !wide;
         if (ok) {
