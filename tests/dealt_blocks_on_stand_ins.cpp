@@ -65,7 +65,7 @@ int main()
     REQUIRE(dealt(spread(4096, 0.5, 2048, 0.1), 32, 32));       // chunks of 16 columns
     REQUIRE(dealt(spread(5000, 0.5, 700, 0.1), 100, 100));      // panels of two rows
     REQUIRE(!dealt(uneven, 64, 256));                           // two column tiles
-    REQUIRE(!dealt(spread(4096, 0.0), 64, 64));                 // even rows
+    REQUIRE(!dealt(matrix(1024, 4096, 10, 0), 64, 64));          // rows of one length
     REQUIRE(!dealt(few, 64, 64));                               // a block per unit at most
     REQUIRE(!dealt(spread(4096, 0.5, 16384, 0.02), 64, 64));    // more than the chip holds
     std::printf("ok\n");
