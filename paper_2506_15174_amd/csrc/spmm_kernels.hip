@@ -50,6 +50,7 @@
 
 #include "spmm_format.h"
 #include "spmm_kernels.h"
+#include "spmm_launch.h"
 
 using namespace spmm_fmt;
 
@@ -617,19 +618,19 @@ spmm_kslice_combine_kernel(const float *__restrict__ sums, int32_t k_slices, uin
 }
 
 template <int U, int S, int VW, int D, bool WIDE, int UFKT = UFK, bool PROBE = false>
-void launch_instance(const spmm_launch_args &a, void *stream)
+hipError_t launch_instance(const spmm_launch_args &a, void *stream)
 {
     const chunk_args args{a.stream, a.wins, a.items, a.rowmap, a.B, a.C, a.cross_sums, a.b_bytes, a.col_mask, a.n_cross_slots,
                           a.ldn, a.ldc, a.width, a.tile_cols, (uint32_t)a.n_blocks, (uint32_t)a.n_tiles, front_blocks(a)};
-    hipLaunchKernelGGL((spmm_chunks_kernel<U, S, VW, D, WIDE, UFKT, PROBE>), dim3((unsigned)a.n_blocks, (unsigned)a.n_tiles),
-                       dim3(64 * WAVES_PER_WG), a.lds_pad, (hipStream_t)stream, args);
+    return launch_kernel(spmm_chunks_kernel<U, S, VW, D, WIDE, UFKT, PROBE>, dim3((unsigned)a.n_blocks, (unsigned)a.n_tiles), 64 * WAVES_PER_WG, a.lds_pad,
+                         (hipStream_t)stream, args);
 }
 
 // One (height, slices) pair at the pipeline depth asked for.  DMAX is the depth the
 // instance is tuned for (as deep as its register budget allows); a caller may ask for a
 // shallower pipeline (1, 2, 3, 4, 8: the loads-in-flight axis of the paper's Figure 2),
 // a deeper request runs at DMAX.  The 64-bit addressing kernels exist at DMAX only.
-template <int U, int S, int VW, int DMAX, bool WIDE> void launch_depth(const spmm_launch_args &a, int depth, void *stream)
+template <int U, int S, int VW, int DMAX, bool WIDE> hipError_t launch_depth(const spmm_launch_args &a, int depth, void *stream)
 {
     if constexpr (!WIDE) {
         if (a.probe) return launch_instance<U, S, VW, DMAX, WIDE, UFK, true>(a, stream);
@@ -638,7 +639,7 @@ template <int U, int S, int VW, int DMAX, bool WIDE> void launch_depth(const spm
         if (depth == 3 && DMAX > 3) return launch_instance<U, S, VW, (DMAX > 3 ? 3 : DMAX), WIDE>(a, stream);
         if (depth == 4 && DMAX > 4) return launch_instance<U, S, VW, (DMAX > 4 ? 4 : DMAX), WIDE>(a, stream);
     }
-    launch_instance<U, S, VW, DMAX, WIDE>(a, stream);
+    return launch_instance<U, S, VW, DMAX, WIDE>(a, stream);
 }
 
 // Pipeline depths per height (D2, D4, D8 for 2, 4, 8 slices): the shallowest that keeps the
@@ -648,13 +649,13 @@ template <int U, int S, int VW, int DMAX, bool WIDE> void launch_depth(const spm
 // the ends of the short windows (4096 x 4096, 95 % pruned, 128 columns: 18.0 us with two in flight, 17.4 with
 // one; 22 even and uneven matrices 2 to 12 % faster).  A unit held to two workgroups (lds_pad) has not enough
 // waves for that and keeps two, and so do 64-bit addresses and a caller who asks for more.
-template <int U, int D2, int D4, int D8> void launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream)
+template <int U, int D2, int D4, int D8> hipError_t launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream)
 {
     switch (slices) {
-    case 2: wide ? launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream); break;
-    case 4: wide ? launch_depth<U, 4, 4, D4, true>(a, depth, stream) : launch_depth<U, 4, 4, D4, false>(a, depth, stream); break;
-    case 8: wide ? launch_depth<U, 8, 4, D8, true>(a, depth, stream) : launch_depth<U, 8, 4, D8, false>(a, depth, stream); break;
-    default: wide ? launch_depth<U, 1, 1, 3, true>(a, depth, stream) : launch_depth<U, 1, 1, 3, false>(a, depth, stream); break;
+    case 2: return wide ? launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream);
+    case 4: return wide ? launch_depth<U, 4, 4, D4, true>(a, depth, stream) : launch_depth<U, 4, 4, D4, false>(a, depth, stream);
+    case 8: return wide ? launch_depth<U, 8, 4, D8, true>(a, depth, stream) : launch_depth<U, 8, 4, D8, false>(a, depth, stream);
+    default: return wide ? launch_depth<U, 1, 1, 3, true>(a, depth, stream) : launch_depth<U, 1, 1, 3, false>(a, depth, stream);
     }
 }
 
@@ -664,15 +665,14 @@ template <int U, int D2, int D4, int D8> void launch_slices(const spmm_launch_ar
 // has five to thirty of these wide chunks, and every further one in flight lengthens the start of
 // its window (8192 x 8192, 98 % pruned, 32 columns: 9.5 us with four, 9.0 with three, 8.6 with two; 40 of
 // 48 plans of one to eight rows are fastest with two or, by less than 2 %, three).
-template <int U, int D> bool launch_narrow(const spmm_launch_args &a, int ufk, int slices, void *stream)
+template <int U, int D> hipError_t launch_narrow(const spmm_launch_args &a, int ufk, int slices, void *stream)
 {
-    if (a.probe && ufk == 16 && slices == 8) launch_instance<U, 8, 4, D, false, 16, true>(a, stream);
-    else if (ufk == 16 && slices == 8) launch_instance<U, 8, 4, D, false, 16>(a, stream);
-    else if (ufk == 32 && slices == 16) launch_instance<U, 16, 4, D, false, 32>(a, stream);
-    else if (ufk == 64 && slices == 32) launch_instance<U, 32, 4, D, false, 64>(a, stream);
-    else if (ufk == 64 && slices == 64) launch_instance<U, 64, 4, D, false, 64>(a, stream);
-    else return false;
-    return true;
+    if (a.probe && ufk == 16 && slices == 8) return launch_instance<U, 8, 4, D, false, 16, true>(a, stream);
+    if (ufk == 16 && slices == 8) return launch_instance<U, 8, 4, D, false, 16>(a, stream);
+    if (ufk == 32 && slices == 16) return launch_instance<U, 16, 4, D, false, 32>(a, stream);
+    if (ufk == 64 && slices == 32) return launch_instance<U, 32, 4, D, false, 64>(a, stream);
+    if (ufk == 64 && slices == 64) return launch_instance<U, 64, 4, D, false, 64>(a, stream);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -688,39 +688,35 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
         dealt.n_dealt = 0;
         return spmm_launch_chunks(dealt, ufi, ufk, slices, wide, depth, stream);
     }
+    hipError_t e = hipErrorInvalidValue;
     if (ufk != UFK) {
-        bool ok = !wide;
-        if (ok) {
+        if (!wide) {
             switch (ufi) {
-            case 8: ok = launch_narrow<8, 2>(a, ufk, slices, stream); break;
-            case 4: ok = launch_narrow<4, 2>(a, ufk, slices, stream); break;
-            case 2: ok = launch_narrow<2, 2>(a, ufk, slices, stream); break;
-            case 1: ok = launch_narrow<1, 2>(a, ufk, slices, stream); break;
-            default: ok = false;
+            case 8: e = launch_narrow<8, 2>(a, ufk, slices, stream); break;
+            case 4: e = launch_narrow<4, 2>(a, ufk, slices, stream); break;
+            case 2: e = launch_narrow<2, 2>(a, ufk, slices, stream); break;
+            case 1: e = launch_narrow<1, 2>(a, ufk, slices, stream); break;
             }
         }
-        if (!ok) return (int)hipErrorInvalidValue;
     } else if (ufi == 1 && slices == 2 && !wide && (depth > 1 || (depth == 0 && a.lds_pad > 0))) {
-        launch_depth<1, 2, 4, 2, false>(a, depth, stream);
-    } else
-    switch (ufi) {
-    case 8: launch_slices<8, 2, 3, 4>(a, slices, wide, depth, stream); break;
-    case 4: launch_slices<4, 2, 3, 4>(a, slices, wide, depth, stream); break;
-    case 2: launch_slices<2, 2, 2, 6>(a, slices, wide, depth, stream); break;
-    case 1: launch_slices<1, 1, 2, 8>(a, slices, wide, depth, stream); break;
-    default: return (int)hipErrorInvalidValue;
+        e = launch_depth<1, 2, 4, 2, false>(a, depth, stream);
+    } else {
+        switch (ufi) {
+        case 8: e = launch_slices<8, 2, 3, 4>(a, slices, wide, depth, stream); break;
+        case 4: e = launch_slices<4, 2, 3, 4>(a, slices, wide, depth, stream); break;
+        case 2: e = launch_slices<2, 2, 2, 6>(a, slices, wide, depth, stream); break;
+        case 1: e = launch_slices<1, 1, 2, 8>(a, slices, wide, depth, stream); break;
+        }
     }
-    if (a.n_cross > 0)
-        hipLaunchKernelGGL(spmm_cross_combine_kernel, dim3((unsigned)a.n_cross, (unsigned)a.n_tiles), dim3(256), 0,
-                           (hipStream_t)stream, a.cross_table, a.cross_sums, a.n_cross_slots, (int32_t)ufi, a.C, a.ldc,
-                           a.width, a.tile_cols);
-    if (a.k_slices > 1) {
+    if (e == hipSuccess && a.n_cross > 0)
+        e = launch_kernel(spmm_cross_combine_kernel, dim3((unsigned)a.n_cross, (unsigned)a.n_tiles), 256, 0, (hipStream_t)stream, a.cross_table, a.cross_sums,
+                          a.n_cross_slots, (int32_t)ufi, a.C, a.ldc, a.width, a.tile_cols);
+    if (e == hipSuccess && a.k_slices > 1) {
         const uint64_t threads = (uint64_t)a.M * (uint64_t)((a.width + 3) / 4);
-        hipLaunchKernelGGL(spmm_kslice_combine_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0,
-                           (hipStream_t)stream, a.C, a.k_slices, (uint32_t)a.slice_rows, a.ldc, a.C_out, a.ldc_out,
-                           (uint32_t)a.M, a.width);
+        e = launch_kernel(spmm_kslice_combine_kernel, dim3((unsigned)((threads + 255) / 256)), 256, 0, (hipStream_t)stream, a.C, a.k_slices,
+                          (uint32_t)a.slice_rows, a.ldc, a.C_out, a.ldc_out, (uint32_t)a.M, a.width);
     }
-    return (int)hipGetLastError();
+    return (int)e;
 }
 
 // Scratch memory that exists without any allocation call: a device array of the library's

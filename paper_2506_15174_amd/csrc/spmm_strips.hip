@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "spmm_launch.h"
 #include "spmm_strips_build.h"
 #include "spmm_upload.h"
 
@@ -781,9 +782,10 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
     for (uint64_t first = 0; first < a.n_places; first += most) {
         a.first = first;
         const unsigned blocks = (unsigned)((std::min(a.n_places - first, most) + 7) / 8) * 8u;
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64 * STRIP_WAVES), (unsigned)(p.band_rows + 1) * STRIP_ROW_BYTES, (hipStream_t)stream, a);
+        const hipError_t e = launch_kernel(kernel, dim3(blocks), 64 * STRIP_WAVES, (unsigned)(p.band_rows + 1) * STRIP_ROW_BYTES, (hipStream_t)stream, a);
+        if (e != hipSuccess) return (int)e;
     }
-    return (int)hipGetLastError();
+    return (int)hipSuccess;
 }
 
 int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *col_idx, const float *vals, int64_t N,

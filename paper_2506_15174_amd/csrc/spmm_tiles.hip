@@ -8,6 +8,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "spmm_launch.h"
 #include "spmm_tiles.h"
 #include "spmm_upload.h"
 
@@ -104,14 +105,16 @@ __device__ __forceinline__ void first_if_behind(uint32_t done, uint32_t all)
 // Launches `kernel` for all column tiles of all panels.  HIP refuses a grid of 2^32 threads or more, which
 // a C of 8 GiB reaches on panels of 8 rows (32768 x 65536): the places are dealt to as many launches as
 // that takes.  (A C that fits the device's memory has fewer than 2^32 places.)
-template <typename F> void launch_places(F kernel, tile_args &a, unsigned threads, hipStream_t s)
+template <typename F> hipError_t launch_places(F kernel, tile_args &a, unsigned threads, hipStream_t s)
 {
     const int64_t places = (int64_t)a.n_panels * a.n_tiles, most = (((int64_t)1 << 32) - 1) / threads / 8 * 8;
     for (int64_t first = 0; first < places; first += most) {
         a.first = (uint32_t)first;
         const unsigned blocks = (unsigned)((std::min(places - first, most) + 7) / 8) * 8u;
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, s, a);
+        const hipError_t e = launch_kernel(kernel, dim3(blocks), threads, 0, s, a);
+        if (e != hipSuccess) return e;
     }
+    return hipSuccess;
 }
 
 // The sum of the waves' tiles, in a fixed order: the upper half of the waves parks its tiles in LDS, the lower half adds
@@ -354,10 +357,10 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
     store_sum<R, NB, W>(args, lds, panel, n0, wave, lane, [](uint32_t, const f32x4 &) {});
 }
 
-template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> void launch(tile_args &a, hipStream_t s)
+template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> hipError_t launch(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (int32_t)(((int64_t)a.N + NB * R - 1) / (NB * R));
-    launch_places(spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>, a, 64 * W, s);
+    return launch_places(spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>, a, 64 * W, s);
 }
 
 // ---------------------------------------------------------------- executor, fp32 values in three bf16 parts
@@ -650,17 +653,17 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
     store_sum<R, NB, W>(args, lds, panel, n0, wave, lane, none);
 }
 
-template <int RUNS, int NB> void launch_split(tile_args &a, hipStream_t s)
+template <int RUNS, int NB> hipError_t launch_split(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (int32_t)(((int64_t)a.N + 32 * NB - 1) / (32 * NB));
-    launch_places(spmm_split_tiles_kernel<RUNS, NB>, a, 64 * split_waves(NB), s);
+    return launch_places(spmm_split_tiles_kernel<RUNS, NB>, a, 64 * split_waves(NB), s);
 }
-template <int NB> void launch_split(tile_args &a, int runs, hipStream_t s)
+template <int NB> hipError_t launch_split(tile_args &a, int runs, hipStream_t s)
 {
-    if (runs == 1) launch_split<1, NB>(a, s);
-    else if (runs == 2) launch_split<2, NB>(a, s);
-    else if (runs == 3) launch_split<3, NB>(a, s);
-    else launch_split<4, NB>(a, s);
+    if (runs == 1) return launch_split<1, NB>(a, s);
+    if (runs == 2) return launch_split<2, NB>(a, s);
+    if (runs == 3) return launch_split<3, NB>(a, s);
+    return launch_split<4, NB>(a, s);
 }
 
 // ---------------------------------------------------------------- executor, narrow panels
@@ -854,21 +857,20 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_narrow_tiles_kernel(const t
     }
 }
 
-template <int NB, int W, int AL, bool WIDE, int MINW> void launch_narrow(tile_args &a, hipStream_t s)
+template <int NB, int W, int AL, bool WIDE, int MINW> hipError_t launch_narrow(tile_args &a, hipStream_t s)
 {
     a.n_tiles = (int32_t)(((int64_t)a.N + NB * 4 - 1) / (NB * 4));
-    launch_places(spmm_narrow_tiles_kernel<NB, W, AL, WIDE, MINW>, a, 64 * W, s);
+    return launch_places(spmm_narrow_tiles_kernel<NB, W, AL, WIDE, MINW>, a, 64 * W, s);
 }
-template <int NB, int W> void launch_narrow(tile_args &a, int loads, hipStream_t s)
+template <int NB, int W> hipError_t launch_narrow(tile_args &a, int loads, hipStream_t s)
 {
-    if (loads == 1) launch_narrow<NB, W, 1, false, 4>(a, s);
-    else if (loads == 2) launch_narrow<NB, W, 2, false, 4>(a, s);
-    else launch_narrow<NB, W, 4, false, NB < 4 ? 4 : 2>(a, s);
+    if (loads == 1) return launch_narrow<NB, W, 1, false, 4>(a, s);
+    if (loads == 2) return launch_narrow<NB, W, 2, false, 4>(a, s);
+    return launch_narrow<NB, W, 4, false, NB < 4 ? 4 : 2>(a, s);
 }
-template <int NB> void launch_narrow(tile_args &a, int waves, int loads, hipStream_t s)
+template <int NB> hipError_t launch_narrow(tile_args &a, int waves, int loads, hipStream_t s)
 {
-    if (waves == 8) launch_narrow<NB, 8>(a, loads, s);
-    else launch_narrow<NB, 4>(a, loads, s);
+    return waves == 8 ? launch_narrow<NB, 8>(a, loads, s) : launch_narrow<NB, 4>(a, loads, s);
 }
 
 // Column groups and waves of a workgroup.  While the workgroups of a narrower tile still all find an idle
@@ -1358,34 +1360,22 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
                 (int32_t)M, (int32_t)K, N, 0, p.largest};
     hipStream_t s = (hipStream_t)stream;
     const int64_t step_bytes = (int64_t)TILE_OPERANDS * 64 / p.rows * 4 * N;  // rows of B a step touches
-    if (step_bytes >= ((int64_t)1 << 32)) {
-        if (p.rows == NARROW_ROWS) launch_narrow<4, 8, 4, true, 2>(a, s);
-        else if (p.rows == 32) launch<32, 4, 8, false, 2, true>(a, s);
-        else launch<16, 4, 8, false, 2, true>(a, s);
-        return (int)hipGetLastError();
-    }
+    if (step_bytes >= ((int64_t)1 << 32))
+        return (int)(p.rows == NARROW_ROWS ? launch_narrow<4, 8, 4, true, 2>(a, s)
+                     : p.rows == 32        ? launch<32, 4, 8, false, 2, true>(a, s)
+                                           : launch<16, 4, 8, false, 2, true>(a, s));
     if (p.rows == NARROW_ROWS) {
         const int NB = narrow_columns(p.n_panels, N), W = narrow_waves(p.n_panels, p.n_steps, N, NB);
-        if (NB == 1) launch_narrow<1>(a, W, p.loads, s);
-        else if (NB == 2) launch_narrow<2>(a, W, p.loads, s);
-        else launch_narrow<4>(a, W, p.loads, s);
-        return (int)hipGetLastError();
+        return (int)(NB == 1 ? launch_narrow<1>(a, W, p.loads, s) : NB == 2 ? launch_narrow<2>(a, W, p.loads, s) : launch_narrow<4>(a, W, p.loads, s));
     }
     int NB = 1;
     spmm_tiles_time(p.rows, M, K, N, 0.0, 0.0, &NB);
     switch (p.rows * 8 + NB) {
-    case 32 * 8 + 4:
-        if (p.exact_parts) launch_split<4>(a, p.loads, s);
-        else launch<32, 4, 8, false, 2>(a, s);
-        break;
-    case 32 * 8 + 2:
-        if (p.n_steps <= FEW_STEPS || !p.exact_parts) launch<32, 2, 16, false, 4>(a, s);
-        else launch_split<2>(a, p.loads, s);
-        break;
-    case 32 * 8 + 1: launch<32, 1, 16, true, 4>(a, s); break;
-    case 16 * 8 + 4: launch<16, 4, 8, false, 2>(a, s); break;
-    case 16 * 8 + 2: launch<16, 2, 8, true, 2>(a, s); break;
-    default: launch<16, 1, 16, true, 4>(a, s); break;
+    case 32 * 8 + 4: return (int)(p.exact_parts ? launch_split<4>(a, p.loads, s) : launch<32, 4, 8, false, 2>(a, s));
+    case 32 * 8 + 2: return (int)(p.n_steps <= FEW_STEPS || !p.exact_parts ? launch<32, 2, 16, false, 4>(a, s) : launch_split<2>(a, p.loads, s));
+    case 32 * 8 + 1: return (int)launch<32, 1, 16, true, 4>(a, s);
+    case 16 * 8 + 4: return (int)launch<16, 4, 8, false, 2>(a, s);
+    case 16 * 8 + 2: return (int)launch<16, 2, 8, true, 2>(a, s);
+    default: return (int)launch<16, 1, 16, true, 4>(a, s);
     }
-    return (int)hipGetLastError();
 }
