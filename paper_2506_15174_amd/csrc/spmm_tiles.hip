@@ -88,14 +88,14 @@ __device__ __forceinline__ uint32_t place_in_matrix(uint32_t first) { return fir
 
 // Of the waves of a SIMD the one that started first would go first, and the workgroup waits for the last: at the end of equally many
 // steps 3.3, 4.2, 4.5 and 5.1 us (512 x 2048, 80 % pruned, 128 columns), and matrix and vector instructions of fewer and fewer waves beside each other
-// before it.  The wave with more steps left goes first, in four classes that get narrower towards the end.
+// before it.  The wave with more steps left goes first, in four classes that get narrower towards the end.  Steps left of as many as the
+// workgroup's busiest wave has: of a wave's own, one with its only step to come would be as urgent as one with two (8137 x 328, 66 %, 102 columns 9.4 -> 9.7 us).
 //   512 x 2048, 80 %, 128 columns       6.4 -> 6.1 us     8192 x 2048, 50 %, 64 columns     19.9 -> 19.1 us
 //   4096 x 1024, 70 %, 128 columns     11.3 -> 10.9       7872 x 2688, 87 %, 140 columns    58.6 -> 55.9
 //   4096 x 4096, 50 %, 128 columns     33.7 -> 32.3       8192 x 8192, 50 %, 128 columns   108.0 -> 105.5
-// Eighteen products 3 % on average, none slower; classes at equal distances 2 %.  (Panels of 8 rows: between 2 % faster and 3 % slower, not there.)
-__device__ __forceinline__ void first_if_behind(uint32_t done, uint32_t all)
+// Thirty products 2.5 % on average, none of them 1 % slower; classes at equal distances 2 %.  (Panels of 8 rows: between 2 % faster and 3 % slower, not there.)
+__device__ __forceinline__ void first_if_behind(uint32_t left, uint32_t all)
 {
-    const uint32_t left = all - done;
     if (left * 2u > all) __builtin_amdgcn_s_setprio(3);
     else if (left * 4u > all) __builtin_amdgcn_s_setprio(2);
     else if (left * 8u > all) __builtin_amdgcn_s_setprio(1);
@@ -225,6 +225,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
     const uint32_t *off_p = args.offsets + (size_t)panel * (n_steps + 1);
     const uint32_t N = (uint32_t)args.N;
     const uint32_t count = n_steps > (uint32_t)wave ? (n_steps - (uint32_t)wave + W - 1) / W : 0u;  // steps of this wave
+    const uint32_t most = (n_steps + W - 1) / W;                                                                    // of any
 
     acc_t acc[NB];
 #pragma unroll
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
         if constexpr (STAGED) fetch_b(0);
         else fetch_rows((uint32_t)wave, 0);
         for (uint32_t i = 0; i < count; ++i) {
-            first_if_behind(i, count);
+            first_if_behind(count - i, most);
             // ---- this step's entries (and rows of B) go to the wave's slot: every entry to its
             //      place in the expanded block, which is all zeros at this point
             const uint32_t n = n_next;
@@ -471,6 +472,7 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
     const uint32_t *off_p = args.offsets + (size_t)panel * (n_steps + 1);
     const uint32_t N = (uint32_t)args.N;
     const uint32_t count = n_steps > (uint32_t)wave ? (n_steps - (uint32_t)wave + W - 1) / W : 0u;  // steps of this wave
+    const uint32_t most = (n_steps + W - 1) / W;                                                                    // of any
 
     f32x16 acc[NB], cor[NB];  // sums of h h; of the other products
 #pragma unroll
@@ -594,7 +596,7 @@ template <int RUNS, int NB> __global__ __launch_bounds__(64 * split_waves(NB), s
 #pragma unroll
                 for (int u = 0; u < STAGES; ++u) {
                     if (u == 1 && i + 1 >= last) break;
-                    first_if_behind(i + (uint32_t)u, count);
+                    first_if_behind(count - i - (uint32_t)u, most);
                     // the step's block has arrived: younger are the other stage's and 16 loads of B
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 1) * AL + 16) : "memory");
                     scatter(u);
