@@ -649,13 +649,13 @@ template <int U, int S, int VW, int DMAX, bool WIDE> hipError_t launch_depth(con
 // the ends of the short windows (4096 x 4096, 95 % pruned, 128 columns: 18.0 us with two in flight, 17.4 with
 // one; 22 even and uneven matrices 2 to 12 % faster).  A unit held to two workgroups (lds_pad) has not enough
 // waves for that and keeps two, and so do 64-bit addresses and a caller who asks for more.
-template <int U, int D2, int D4, int D8> hipError_t launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream)
+template <int U, int D2, int D4, int D8> void launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream, hipError_t &ok)
 {
     switch (slices) {
-    case 2: return wide ? launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream);
-    case 4: return wide ? launch_depth<U, 4, 4, D4, true>(a, depth, stream) : launch_depth<U, 4, 4, D4, false>(a, depth, stream);
-    case 8: return wide ? launch_depth<U, 8, 4, D8, true>(a, depth, stream) : launch_depth<U, 8, 4, D8, false>(a, depth, stream);
-    default: return wide ? launch_depth<U, 1, 1, 3, true>(a, depth, stream) : launch_depth<U, 1, 1, 3, false>(a, depth, stream);
+    case 2: ok = wide ? launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream); break;
+    case 4: ok = wide ? launch_depth<U, 4, 4, D4, true>(a, depth, stream) : launch_depth<U, 4, 4, D4, false>(a, depth, stream); break;
+    case 8: ok = wide ? launch_depth<U, 8, 4, D8, true>(a, depth, stream) : launch_depth<U, 8, 4, D8, false>(a, depth, stream); break;
+    default: ok = wide ? launch_depth<U, 1, 1, 3, true>(a, depth, stream) : launch_depth<U, 1, 1, 3, false>(a, depth, stream); break;
     }
 }
 
@@ -688,35 +688,35 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
         dealt.n_dealt = 0;
         return spmm_launch_chunks(dealt, ufi, ufk, slices, wide, depth, stream);
     }
-    hipError_t e = hipErrorInvalidValue;
+    hipError_t ok = hipErrorInvalidValue;
     if (ufk != UFK) {
         if (!wide) {
             switch (ufi) {
-            case 8: e = launch_narrow<8, 2>(a, ufk, slices, stream); break;
-            case 4: e = launch_narrow<4, 2>(a, ufk, slices, stream); break;
-            case 2: e = launch_narrow<2, 2>(a, ufk, slices, stream); break;
-            case 1: e = launch_narrow<1, 2>(a, ufk, slices, stream); break;
+            case 8: ok = launch_narrow<8, 2>(a, ufk, slices, stream); break;
+            case 4: ok = launch_narrow<4, 2>(a, ufk, slices, stream); break;
+            case 2: ok = launch_narrow<2, 2>(a, ufk, slices, stream); break;
+            case 1: ok = launch_narrow<1, 2>(a, ufk, slices, stream); break;
             }
         }
     } else if (ufi == 1 && slices == 2 && !wide && (depth > 1 || (depth == 0 && a.lds_pad > 0))) {
-        e = launch_depth<1, 2, 4, 2, false>(a, depth, stream);
+        ok = launch_depth<1, 2, 4, 2, false>(a, depth, stream);
     } else {
         switch (ufi) {
-        case 8: e = launch_slices<8, 2, 3, 4>(a, slices, wide, depth, stream); break;
-        case 4: e = launch_slices<4, 2, 3, 4>(a, slices, wide, depth, stream); break;
-        case 2: e = launch_slices<2, 2, 2, 6>(a, slices, wide, depth, stream); break;
-        case 1: e = launch_slices<1, 1, 2, 8>(a, slices, wide, depth, stream); break;
+        case 8: launch_slices<8, 2, 3, 4>(a, slices, wide, depth, stream, ok); break;
+        case 4: launch_slices<4, 2, 3, 4>(a, slices, wide, depth, stream, ok); break;
+        case 2: launch_slices<2, 2, 2, 6>(a, slices, wide, depth, stream, ok); break;
+        case 1: launch_slices<1, 1, 2, 8>(a, slices, wide, depth, stream, ok); break;
         }
     }
-    if (e == hipSuccess && a.n_cross > 0)
-        e = launch_kernel(spmm_cross_combine_kernel, dim3((unsigned)a.n_cross, (unsigned)a.n_tiles), 256, 0, (hipStream_t)stream, a.cross_table, a.cross_sums,
+    if (ok == hipSuccess && a.n_cross > 0)
+        ok = launch_kernel(spmm_cross_combine_kernel, dim3((unsigned)a.n_cross, (unsigned)a.n_tiles), 256, 0, (hipStream_t)stream, a.cross_table, a.cross_sums,
                           a.n_cross_slots, (int32_t)ufi, a.C, a.ldc, a.width, a.tile_cols);
-    if (e == hipSuccess && a.k_slices > 1) {
+    if (ok == hipSuccess && a.k_slices > 1) {
         const uint64_t threads = (uint64_t)a.M * (uint64_t)((a.width + 3) / 4);
-        e = launch_kernel(spmm_kslice_combine_kernel, dim3((unsigned)((threads + 255) / 256)), 256, 0, (hipStream_t)stream, a.C, a.k_slices,
+        ok = launch_kernel(spmm_kslice_combine_kernel, dim3((unsigned)((threads + 255) / 256)), 256, 0, (hipStream_t)stream, a.C, a.k_slices,
                           (uint32_t)a.slice_rows, a.ldc, a.C_out, a.ldc_out, (uint32_t)a.M, a.width);
     }
-    return (int)e;
+    return (int)ok;
 }
 
 // Scratch memory that exists without any allocation call: a device array of the library's
