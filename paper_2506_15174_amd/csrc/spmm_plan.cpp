@@ -315,6 +315,23 @@ struct Emitter {
         n_enum += count;
     }
 
+    // What panel() emits for n entries of a panel of one row: one pattern, so chunk after chunk in the order of the columns.
+    // (Taking them one by one through merged, sorted and split copies, as rows of taller panels go, took most of a creation: 4800 x
+    // 1373, 4 % kept, 6 columns, 3.0 ms, now 1.1; 984 x 1322, 2.5 %, 18 columns 0.54 and 0.31.)
+    void row(const int32_t *col, const float *val, int64_t n)
+    {
+        const int64_t chunks = n > 0 ? (n + UFK - 1) / UFK : 1, last = (chunks - 1) * UFK;
+        const size_t h0 = hdr.size(), c0 = cols.size(), v0 = vals.size();
+        hdr.resize(h0 + (size_t)chunks, 1u | (uint32_t)UFK << HDR_COUNT_SHIFT);
+        hdr.back() = (n > 0 ? 1u : 0u) | (uint32_t)(n - last) << HDR_COUNT_SHIFT | HDR_END_PANEL;
+        cols.resize(c0 + (size_t)(chunks * UFK), n > 0 ? (uint32_t)col[n - 1] : 0u);
+        vals.resize(v0 + (size_t)(n > 0 ? chunks * UFK : 0), 0u);
+        if (n == 0) return;
+        std::memcpy(cols.data() + c0, col, (size_t)n * 4);
+        std::memcpy(vals.data() + v0, val, (size_t)n * 4);
+        n_enum += n;
+    }
+
     // Emits the chunks of one panel (or one piece of a panel) whose entries are
     // ordered so that equal patterns are adjacent: first the full chunks of every
     // pattern, then the leftovers (fewer than ufk entries per pattern), packed ufk
@@ -441,6 +458,8 @@ int worker_count(int64_t nnz, int32_t asked)
     if (hw > 0) n = std::min<int64_t>(n, hw);
     return (int)n;
 }
+
+constexpr int64_t FEW_ENTRIES = (int64_t)1 << 20;
 
 // Runs job(first row, last row, share) over `threads` contiguous shares of the rows with about
 // equally many entries each.  The jobs must not throw.
@@ -761,8 +780,9 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     if (nnz > 0 && (!col_idx || !vals)) return ST_INVALID_ARG;
 
     try {
-        const int threads = worker_count(nnz, opts.threads);
-        if (!opts.schedule_only && !columns_ok(K, row_ptr, col_idx, M, threads)) return ST_INVALID_CSR;
+        int threads = worker_count(nnz, opts.threads);
+        // A look at a million columns takes a thread as long as others take to start.
+        if (!opts.schedule_only && !columns_ok(K, row_ptr, col_idx, M, opts.threads < 1 && nnz < FEW_ENTRIES ? 1 : threads)) return ST_INVALID_CSR;
         out = HostPlan();
         out.M = M;
         out.K = K;
@@ -814,6 +834,9 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
             const bool as_sorted = opts.sort_rows > 0 || (opts.sort_rows == 0 && skewed);
             ufi = as_sorted ? choose_ufi_skewed(KS, nnz, max_row, opts.n_hint, cross) : choose_ufi(M, KS, nnz, opts.n_hint);
         }
+        // single rows are copied, not merged: 2 to 8 threads take 1.2 to 1.5 times as long as one on 140 000 to 400 000 entries, 0.8 of
+        // the time on 1.3 million
+        if (opts.threads < 1 && ufi == 1 && nnz < FEW_ENTRIES) threads = 1;
         // single rows share nothing: sorting them would only scatter the rows of C
         const bool sorted = opts.sort_rows > 0 || (opts.sort_rows == 0 && skewed && ufi > 1);
         // row_order[i]: the matrix row that row i of a slice stands for (sorted plans only)
@@ -913,6 +936,49 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
                 for (int64_t p = first_panel; p < last_panel; ++p) {
                     const int64_t r0 = p * UFI, r1 = std::min<int64_t>(MP, r0 + UFI);
                     const int rows = (int)(r1 - r0);
+                    if (UFI == 1) {
+                        const int64_t m = mrow(r0), a = m < 0 ? 0 : row_ptr[m];
+                        int64_t n = m < 0 ? 0 : row_ptr[m + 1] - a;
+                        const int32_t *col = col_idx + a;
+                        const float *val = vals + a;
+                        bool in_order = true;
+                        for (int64_t q = 1; q < n; ++q) in_order &= col[q] >= col[q - 1];
+                        if (!in_order) {  // stable, as below
+                            order.resize((size_t)n);
+                            std::iota(order.begin(), order.end(), 0);
+                            std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return col[x] < col[y]; });
+                            ccol[0].resize((size_t)n);
+                            cval[0].resize((size_t)n);
+                            for (int64_t q = 0; q < n; ++q) {
+                                ccol[0][(size_t)q] = col[order[(size_t)q]];
+                                cval[0][(size_t)q] = val[order[(size_t)q]];
+                            }
+                            col = ccol[0].data();
+                            val = cval[0].data();
+                        }
+                        if (NS > 1) {  // this slice's columns
+                            const int64_t sl = r0 / MS;
+                            const int32_t *lo = std::lower_bound(col, col + n, (int32_t)std::min<int64_t>(sl * KS, INT32_MAX));
+                            const int32_t *hi = std::lower_bound(lo, col + n, (int32_t)std::min<int64_t>((sl + 1) * KS, INT32_MAX));
+                            val += lo - col;
+                            n = hi - lo;
+                            col = lo;
+                        }
+                        if (!split) {
+                            em.row(col, val, n);
+                            continue;
+                        }
+                        for (int64_t s = gi; s <= g_last; ++s) {
+                            Group &gs = groups[(size_t)s];
+                            const int64_t from = gs.nnz_begin - g0.nnz_begin;
+                            gs.chunk0 = (int64_t)em.hdr.size();
+                            gs.words0 = (int64_t)em.vals.size();
+                            em.row(col + from, val + from, gs.nnz_end - gs.nnz_begin);
+                            gs.n_chunks = (int64_t)em.hdr.size() - gs.chunk0;
+                            gs.n_words = (int64_t)em.vals.size() - gs.words0;
+                        }
+                        continue;
+                    }
                     // canonical rows: stable order by column (duplicates keep stored order)
                     for (int r = 0; r < rows; ++r) {
                         const int64_t m = mrow(r0 + r);
