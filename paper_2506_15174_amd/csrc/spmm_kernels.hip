@@ -348,8 +348,11 @@ spmm_chunks_kernel(const chunk_args args)
     // leftover chunks); the 24-bit multiply of the narrow path ignores it anyway.
     auto col_index = [&](uint32_t word) -> uint32_t { return WIDE ? (word & col_mask) : word; };
 
-    // Lanes beyond the tile width compute on the tile's first columns and store
+    // Lanes beyond the tile width compute on its last columns and store
     // nothing: no divergent control flow in the hot loop, no out-of-range access.
+    // (On its first columns they touch a cache line away from their neighbours' once more: 11461 x 2261, 95 % lognormal, 36
+    // columns 16.2 -> 14.5 us, 705 x 9728, 90 %, 102 columns 22.4 -> 21.9; 36 products 1.5 % on average, 1 % slower at worst.
+    // With those lanes switched off: between 6 % slower and 5 % faster.)
     // The last active lane may own fewer than VW columns: it loads past the end of
     // its rows of B (the next row, or zeros past the end of B through the buffer
     // descriptor's range check) and stores only its own columns.
@@ -362,7 +365,7 @@ spmm_chunks_kernel(const chunk_args args)
         cword_t *wins = (cword_t *)(wins_g) + it[IT_WIN0];
         const uint32_t *stream = stream_g + (size_t)it[IT_STREAM0];
         const uint32_t ld_bytes = (uint32_t)ldn * 4u;
-        const uint32_t lane_off = active ? (uint32_t)(sl * VW * 4) : 0u;
+        const uint32_t lane_off = (uint32_t)((active ? sl : (width - 1) / VW) * VW * 4);
         const uint32_t slot0 = (uint32_t)(slice * Q);  // this slice's first column slot
         BSource<WIDE> src;
         src.init(B, b_bytes);
