@@ -25,10 +25,12 @@ struct strip_args {
     const float *B;
     float *C;
     uint64_t b_bytes;   // bytes of B
-    uint64_t n_places;  // strips of all groups
-    uint64_t first;     // the launch's first
+    // Strips of all groups (of which a C that fits the device's memory has fewer than 2^30: a place holds 512 bytes of it in
+    // bands, and there are 2048 or one per strip without); the launch's first.
+    uint32_t n_places, first;
     int32_t K, N, bands, band_rows;
-    uint32_t n_units, n_groups, n_strips;
+    uint32_t n_units, n_groups, n_strips, set;  // set: strips that come first, of all groups (strips_of_set)
+    uint32_t share;                             // places of an XCD in this launch
 };
 
 // v of lane l ^ 1, l ^ 2, l ^ 4 or l ^ 8
@@ -91,10 +93,16 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
 {
     extern __shared__ __attribute__((aligned(32))) char lds[];  // (whole rows: the halves of one differ in a bit of the address)
     // Workgroups are dealt to the eight XCDs in turn: each takes an eighth of the places, next to each other, so that the strips of
-    // a group, which read the same entries, share an L2.
-    const uint64_t place = args.first + blockIdx.x % 8u * (gridDim.x / 8u) + blockIdx.x / 8u;
+    // a group, which read the same entries, share an L2, and in two sets (strips_of_set) half of the XCDs fetch half of B.
+    // (The arguments all at once: in rounds, each where it is needed, the last one's wait would come behind the unit's place.)
+    asm volatile("" ::"s"(args.units), "s"(args.B), "s"(args.b_bytes), "s"(args.n_places), "s"(args.first), "s"(args.K), "s"(args.N), "s"(args.bands), "s"(args.band_rows),
+                 "s"(args.n_units), "s"(args.n_groups), "s"(args.n_strips), "s"(args.set), "s"(args.share));
+    const uint32_t place = args.first + blockIdx.x % 8u * args.share + blockIdx.x / 8u;
     if (place >= args.n_places) return;
-    const uint32_t group = (uint32_t)(place / args.n_strips), strip = (uint32_t)(place % args.n_strips);
+    const uint32_t first_set = args.n_groups * args.set;
+    const bool second = place >= first_set;
+    const uint32_t at = second ? place - first_set : place, width = second ? args.n_strips - args.set : args.set;
+    const uint32_t group = at / width, strip = (second ? args.set : 0u) + at % width;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
     constexpr int AHEAD = 3;  // groups of a unit in registers: the one at work and the next two
@@ -763,6 +771,22 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     return hipSuccess;
 }
 
+// Strips of the first of two sets, or all.  In one set every XCD fetches all of B into its L2, one fourth of a line per strip,
+// before its workgroups multiply, and an eighth of the entries; in two sets, one set's places before the other's, half of B and a quarter of the
+// entries.  That pays where the entries are few beside B and the sets share no line.  us in one set and in two, plans and B in turn:
+//   entries / B   0.7   1200 x 4800, 90 %, 256 columns   18.8 and 18.0     4096 x 4096, 97 %, 256 columns    16.7 and 15.9
+//                 2     8192 x 8192, 98 %, 128           23.2 and 22.2     4096 x 8192, 97 %, 128            20.8 and 19.7
+//                 2.6   4096 x 4096, 95 %, 128           12.9 and 12.4     4096 x 16384, 95 %, 128           43.7 and 42.1
+//                 6     5000 x 4000, Zipf, 128           21.1 both
+//                 11    8968 x 2473, 92 %, 96            14.0 and 14.2     4096 x 4096, 80 %, 64 (14)        16.4 and 16.6
+// Rows that are not whole lines: 2 % slower to 1 % faster (110 to 250 columns).  Sets of 40 columns and fewer: up to 14 % slower.
+uint32_t strips_of_set(const StripPlan &p, int64_t K, int32_t N)
+{
+    const int64_t strips = ((int64_t)N + STRIP_COLS - 1) / STRIP_COLS, half = ((strips + 1) / 2 + 3) / 4 * 4;  // (four strips: a line)
+    const double entries = (double)p.steps * (STRIP_GROUP_BYTES / STRIP_STEPS), b = 4.0 * (double)K * (double)N;
+    return (uint32_t)(N % 32 == 0 && strips >= 16 && entries < 8.0 * b ? half : strips);
+}
+
 }  // namespace
 
 int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N, float *C, void *stream)
@@ -772,16 +796,17 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
     if (strips <= StripPlan::KNOWN) groups = p.groups[strips];
     else strip_time(p, K, N, &groups);
     strip_args a{reinterpret_cast<const char *>(p.d_stream), reinterpret_cast<const u32x2 *>(p.d_units), p.d_rows(), B, C, (uint64_t)K * (uint64_t)N * 4u, 0, 0,
-                 (int32_t)K, N, p.bands, p.band_rows, (uint32_t)p.n_units, (uint32_t)groups, (uint32_t)strips};
-    a.n_places = (uint64_t)a.n_groups * a.n_strips;
+                 (int32_t)K, N, p.bands, p.band_rows, (uint32_t)p.n_units, (uint32_t)groups, (uint32_t)strips, strips_of_set(p, K, N), 0};
+    a.n_places = a.n_groups * a.n_strips;
     const bool wide = (uint64_t)N * 4u * 32u >= (1ull << 32);
     const auto kernel = p.bands > 1 ? (wide ? spmm_strips_kernel<true, true> : spmm_strips_kernel<true, false>)
                                     : (wide ? spmm_strips_kernel<false, true> : spmm_strips_kernel<false, false>);
     // HIP refuses a grid of 2^32 threads or more
-    const uint64_t most = ((1ull << 32) - 1) / (64 * STRIP_WAVES) / 8 * 8;
-    for (uint64_t first = 0; first < a.n_places; first += most) {
+    const uint32_t most = (uint32_t)(((1ull << 32) - 1) / (64 * STRIP_WAVES) / 8 * 8);
+    for (uint32_t first = 0; first < a.n_places; first += most) {
         a.first = first;
-        const unsigned blocks = (unsigned)((std::min(a.n_places - first, most) + 7) / 8) * 8u;
+        a.share = (std::min(a.n_places - first, most) + 7) / 8;
+        const unsigned blocks = a.share * 8u;
         const hipError_t e = launch_kernel(kernel, dim3(blocks), 64 * STRIP_WAVES, (unsigned)(p.band_rows + 1) * STRIP_ROW_BYTES, (hipStream_t)stream, a);
         if (e != hipSuccess) return (int)e;
     }
