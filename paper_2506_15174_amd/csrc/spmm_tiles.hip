@@ -36,6 +36,7 @@ struct tile_args {
     int32_t n_panels, n_steps, n_tiles, M, K, N;
     uint32_t first;     // the launch's first place among all column tiles of all panels
     float largest;      // size of A's largest value (spmm_split_tiles_kernel)
+    uint32_t set;       // column tiles that come first, of all panels (panels of 16 rows; tiles_of_set)
 };
 
 template <int NB> struct BVec;
@@ -213,7 +214,19 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
     constexpr int LDS_WORDS = W * SLOT > RED ? W * SLOT : RED;
     __shared__ __attribute__((aligned(16))) float lds[LDS_WORDS];
 
-    const uint32_t id = place_in_matrix(args.first), nt = id % (uint32_t)args.n_tiles, panel = id / (uint32_t)args.n_tiles;
+    uint32_t id = place_in_matrix(args.first), tiles = (uint32_t)args.n_tiles, nt0 = 0;
+    if constexpr (R == 16) {
+        const uint32_t first_set = (uint32_t)args.n_panels * args.set;
+        if (__builtin_expect(id >= first_set, 0)) {
+            nt0 = args.set;
+            if (nt0 == tiles) return;
+            id -= first_set;
+            tiles -= nt0;
+        } else {
+            tiles = args.set;
+        }
+    }
+    const uint32_t nt = nt0 + id % tiles, panel = id / tiles;
     if (panel >= (uint32_t)args.n_panels) return;
     const uint32_t n0 = nt * (uint32_t)NT;
 
@@ -358,9 +371,25 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
     store_sum<R, NB, W>(args, lds, panel, n0, wave, lane, [](uint32_t, const f32x4 &) {});
 }
 
-template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> hipError_t launch(tile_args &a, hipStream_t s)
+// Column tiles of the first of two sets, whole lines of B, or all.  In one set every XCD fetches all of B into its L2 before its
+// workgroups multiply, and an eighth of the blocks; in two, one set's places before the other's, half of B and a quarter of the blocks.  That
+// pays where the blocks are few beside B and rows are whole lines.  Panels of 16 rows, plans and B in turn, in one set and in two, us:
+//   entries / B   0.6   256 x 2048, 70 %, 192 columns  7.06 and 6.73     300 x 6000, 80 % lognormal, 160  13.4 and 12.9
+//                 0.9   512 x 2048, 70 %, 256          9.48 and 9.23     512 x 4096, 85 %, 128            10.1 and 10.0
+//                 1.2   512 x 2048, 80 %, 128          6.68 and 5.99
+//                 3.8   1024 x 2048, 70 %, 128         9.12 and 9.11     (32 rows: 4096 x 1024, 70 %, 128, 15: 12.2 and 12.4)
+// Rows that are not whole lines: 512 x 2048, 75 %, 100 columns 6.69 and 7.00.
+template <int R, int NB> uint32_t tiles_of_set(const tile_args &a, bool few_entries)
+{
+    constexpr uint32_t LINE = NB * R < 32 ? 32 / (NB * R) : 1;
+    const uint32_t tiles = (uint32_t)a.n_tiles, half = ((tiles + 1) / 2 + LINE - 1) / LINE * LINE;
+    return few_entries && half < tiles ? half : tiles;
+}
+
+template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> hipError_t launch(tile_args &a, hipStream_t s, bool few_entries = false)
 {
     a.n_tiles = (int32_t)(((int64_t)a.N + NB * R - 1) / (NB * R));
+    a.set = tiles_of_set<R, NB>(a, few_entries);
     return launch_places(spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>, a, 64 * W, s);
 }
 
@@ -1359,7 +1388,7 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream)
 {
     tile_args a{p.d_stream, p.d_offsets, B, C, (uint64_t)K * (uint64_t)N * 4u, (int32_t)p.n_panels, (int32_t)p.n_steps, 1,
-                (int32_t)M, (int32_t)K, N, 0, p.largest};
+                (int32_t)M, (int32_t)K, N, 0, p.largest, 0};
     hipStream_t s = (hipStream_t)stream;
     const int64_t step_bytes = (int64_t)TILE_OPERANDS * 64 / p.rows * 4 * N;  // rows of B a step touches
     if (step_bytes >= ((int64_t)1 << 32))
@@ -1372,12 +1401,13 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
     }
     int NB = 1;
     spmm_tiles_time(p.rows, M, K, N, 0.0, 0.0, &NB);
+    const bool few_entries = N % 32 == 0 && 4.0 * (double)p.stream_words < 1.5 * (double)a.b_bytes;
     switch (p.rows * 8 + NB) {
     case 32 * 8 + 4: return (int)(p.exact_parts ? launch_split<4>(a, p.loads, s) : launch<32, 4, 8, false, 2>(a, s));
     case 32 * 8 + 2: return (int)(p.n_steps <= FEW_STEPS || !p.exact_parts ? launch<32, 2, 16, false, 4>(a, s) : launch_split<2>(a, p.loads, s));
     case 32 * 8 + 1: return (int)launch<32, 1, 16, true, 4>(a, s);
-    case 16 * 8 + 4: return (int)launch<16, 4, 8, false, 2>(a, s);
-    case 16 * 8 + 2: return (int)launch<16, 2, 8, true, 2>(a, s);
-    default: return (int)launch<16, 1, 16, true, 4>(a, s);
+    case 16 * 8 + 4: return (int)launch<16, 4, 8, false, 2>(a, s, few_entries);
+    case 16 * 8 + 2: return (int)launch<16, 2, 8, true, 2>(a, s, few_entries);
+    default: return (int)launch<16, 1, 16, true, 4>(a, s, few_entries);
     }
 }
