@@ -46,6 +46,7 @@ struct spmm_plan {
     int32_t heavy = 0;        // the first blocks that are heavier than most (heavy_blocks)
     uint32_t lds_pad = 0;     // extra LDS per workgroup that keeps a third one off a compute unit (hold_to_two)
     int32_t n_dealt = 0;      // blocks behind the plan's own in d_items, dealt to the compute units (deal_blocks)
+    bool halved = false;      // 97 to 128 columns are two tiles of 64 (better_halved)
 };
 
 namespace {
@@ -160,6 +161,34 @@ std::vector<uint32_t> deal_blocks(const HostPlan &h, int per_unit)
         else for (size_t w = 0; w < (size_t)WAVES_PER_WG; ++w) items[at + w * ITEM_WORDS + IT_FLAGS] = FLAG_IDLE;
     }
     return items;
+}
+
+// Whether 97 to 128 columns are multiplied earlier in two tiles of 64 than in one.  A launch of up to 512 blocks ends with
+// its fullest compute unit, and two tiles, the blocks in turn, leave that one half a block where it had a whole one; they read the plan
+// twice and have twice the starts and ends, about 0.3 us.  `dealt`: the blocks as a launch of one tile gets them, if not in the plan's order.
+// Loads in chunks, as in deal_blocks (one is 64 cycles of the vector L1).  us in one tile and in two, plans and B in turn, and what the fullest unit is spared:
+//   1103 x 7373, 99 %, Zipf, 97 columns        34.4 and 19.0   248 of 511     506 x 902, 94 %, Zipf, 97              5.75 and 4.41   64 of 127
+//   300 x 4096, 90 % lognormal, 128            11.0 and 7.1     65 of 192     512 x 2048, 90 % lognormal, 128        6.08 and 5.51   36 of 125
+//   2048 x 2048, 98 %, Zipf, 128                8.6 and 6.5     68 of 192     365 x 2494, 98 % lognormal, 128        3.34 and 3.10   20 of 40
+//   512 x 512, 80 %, 128                       3.62 and 3.97    12 of 63      424 x 2254, 94 %, 100                  4.02 and 4.79   -5 of 63
+//   512 x 2048, 90 %, 128                      5.02 and 5.10     4 of 69      6837 x 1529, 99 %, Zipf, 97 (1131 blocks)  6.3 and 9.2  21 of 168
+// Of 35 such products the 17 of up to 512 blocks that are spared 20 are faster, of the others four.
+bool better_halved(const HostPlan &h, const std::vector<uint32_t> &dealt)
+{
+    constexpr int64_t UNITS = 256, STARTING = 8;
+    if (h.ufk != UFK || h.n_blocks > 2 * UNITS || h.k_slices > 1 || h.n_cross > 0) return false;
+    auto fullest = [](const std::vector<uint32_t> &items, int64_t tiles) {
+        std::vector<int64_t> load((size_t)UNITS, 0);
+        const int64_t blocks = (int64_t)(items.size() / ((size_t)WAVES_PER_WG * ITEM_WORDS));
+        for (int64_t at = 0; at < blocks * tiles; ++at) {
+            int64_t chunks = 0;
+            for (int w = 0; w < WAVES_PER_WG; ++w) chunks += items[(size_t)((at / tiles * WAVES_PER_WG + w) * ITEM_WORDS + IT_NCHUNKS)];
+            if (chunks > 0) load[(size_t)(at % UNITS)] += chunks + STARTING;
+        }
+        return *std::max_element(load.begin(), load.end()) / tiles;
+    };
+    const int64_t one = fullest(dealt.empty() ? h.items : dealt, 1), spared = one - fullest(h.items, 2);
+    return spared >= 20 && spared * 6 >= one;
 }
 
 spmm_status_t hip_fail()
@@ -351,6 +380,7 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
             const int slices = h.ufk == 16 ? 8 : h.ufk == 32 ? 16 : h.ufk == 64 ? 32 : io.n_hint <= 0 || io.n_hint > 64 ? 2 : io.n_hint > 32 ? 4 : 8;
             std::vector<uint32_t> dealt = deal_blocks(h, workgroups_per_unit(slices, h.ufi, h.ufk, false));
             p->n_dealt = (int32_t)(dealt.size() / ((size_t)WAVES_PER_WG * ITEM_WORDS));
+            p->halved = better_halved(h, dealt);
             if (p->n_dealt > 0) dealt.insert(dealt.begin(), h.items.begin(), h.items.end());
             const std::vector<uint32_t> &items = p->n_dealt > 0 ? dealt : h.items;
             if (st == SPMM_OK) st = upload(&p->d_items, items.data(), items.size() * 4, p->device_bytes);
@@ -493,6 +523,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     // (0.75 to 1.24 of the time).
     const bool three_tiles = !sliced && !wide && h.ufk == UFK && N > 160 && N <= 192 &&
                              (h.ufi > 1 || (N % 32 == 0 && plan->heavy == 0) || h.nnz < ((int64_t)1 << 19));
+    const bool two_tiles = plan->halved && !wide && N > 96 && N <= 128;
     // Column tiles of one width share a launch (front_blocks: in which order; a
     // tile begins while the previous one drains); a narrower rest takes a launch of its own.
     // Plans made for narrow B (chunks wider than 8 columns) run every N on their own narrow tiles.
@@ -506,7 +537,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
             slices = 1;
             return 64;
         }
-        slices = left > 64 ? (narrow_tiles || three_tiles ? 4 : 2) : left > 32 ? 4 : 8;
+        slices = left > 64 ? (narrow_tiles || three_tiles || two_tiles ? 4 : 2) : left > 32 ? 4 : 8;
         return 256 / slices;
     };
     int32_t j0 = 0;
