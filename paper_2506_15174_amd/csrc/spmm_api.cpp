@@ -172,7 +172,8 @@ std::vector<uint32_t> deal_blocks(const HostPlan &h, int per_unit)
 //   2048 x 2048, 98 %, Zipf, 128                8.6 and 6.5     68 of 192     365 x 2494, 98 % lognormal, 128        3.34 and 3.10   20 of 40
 //   512 x 512, 80 %, 128                       3.62 and 3.97    12 of 63      424 x 2254, 94 %, 100                  4.02 and 4.79   -5 of 63
 //   512 x 2048, 90 %, 128                      5.02 and 5.10     4 of 69      6837 x 1529, 99 %, Zipf, 97 (1131 blocks)  6.3 and 9.2  21 of 168
-// Of 35 such products the 17 of up to 512 blocks that are spared 20 are faster, of the others four.
+// Of 35 such products the 16 of up to 512 blocks that are spared 20 are faster, of the others four; of 22 others that it takes 20,
+// the other two 0.4 and 1.5 % slower.
 bool better_halved(const HostPlan &h, const std::vector<uint32_t> &dealt)
 {
     constexpr int64_t UNITS = 256, STARTING = 8;

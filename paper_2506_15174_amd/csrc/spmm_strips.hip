@@ -78,7 +78,7 @@ __device__ __forceinline__ float add_half(float v)
 // vector L1 fetches a line of 128 bytes for 32, 2 cycles, so 4096 rows take 3.6 us.
 //
 // Three plans in turn (and one back to back), on chunks and on strips:
-//   4096 x 4096, 95 % pruned, 128 columns                     17.6 (16.1) -> 13.1 us (11.2)
+//   4096 x 4096, 95 % pruned, 128 columns                     17.6 (16.1) -> 12.4 us (11.1)
 //   3001 x 2511, 85 % in lognormal rows, 200 columns          37.4 (35.3) -> 17.8 (17.0)
 //   8968 x 2473, 92 %, 96 columns                             41.3 (39.2) -> 14.0 (13.2)
 //
