@@ -46,7 +46,7 @@ struct spmm_plan {
     int32_t heavy = 0;        // the first blocks that are heavier than most (heavy_blocks)
     uint32_t lds_pad = 0;     // extra LDS per workgroup that keeps a third one off a compute unit (hold_to_two)
     int32_t n_dealt = 0;      // blocks behind the plan's own in d_items, dealt to the compute units (deal_blocks)
-    bool halved = false;      // 97 to 128 columns are two tiles of 64 (better_halved)
+    int64_t spared = 0;       // chunks that two column tiles instead of one spare the fullest compute unit (spared_by_halves)
 };
 
 namespace {
@@ -163,8 +163,8 @@ std::vector<uint32_t> deal_blocks(const HostPlan &h, int per_unit)
     return items;
 }
 
-// Whether 97 to 128 columns are multiplied earlier in two tiles of 64 than in one.  A launch of up to 512 blocks ends with
-// its fullest compute unit, and two tiles, the blocks in turn, leave that one half a block where it had a whole one; they read the plan
+// What two column tiles of half the width spare the fullest compute unit of a launch; 0 where that is less than a sixth of its load.  A
+// launch of up to 512 blocks ends with that unit, and two tiles, the blocks in turn, leave that one half a block where it had a whole one; they read the plan
 // twice and have twice the starts and ends, about 0.3 us.  `dealt`: the blocks as a launch of one tile gets them, if not in the plan's order.
 // Loads in chunks, as in deal_blocks (one is 64 cycles of the vector L1).  us in one tile and in two, plans and B in turn, and what the fullest unit is spared:
 //   1103 x 7373, 99 %, Zipf, 97 columns        34.4 and 19.0   248 of 511     506 x 902, 94 %, Zipf, 97              5.75 and 4.41   64 of 127
@@ -174,10 +174,16 @@ std::vector<uint32_t> deal_blocks(const HostPlan &h, int per_unit)
 //   512 x 2048, 90 %, 128                      5.02 and 5.10     4 of 69      6837 x 1529, 99 %, Zipf, 97 (1131 blocks)  6.3 and 9.2  21 of 168
 // Of 35 such products the 16 of up to 512 blocks that are spared 20 are faster, of the others four; of 22 others that it takes 20,
 // the other two 0.4 and 1.5 % slower.
-bool better_halved(const HostPlan &h, const std::vector<uint32_t> &dealt)
+//
+// A chunk's rows of B in tiles of 64 and 32 columns take half the time, and four slices and eight more of the rest:
+//   566 x 14392, 98 %, Zipf, 64 columns        47.6 and 26.3   904 of 1808    1256 x 5508, 98 %, Zipf, 56            18.0 and 12.6  320 of 656
+//   958 x 3397, 98 %, Zipf, 48                 6.51 and 6.15   124 of 264     1971 x 3239, 98 %, Zipf, 64            6.77 and 6.64  120 of 280
+//   541 x 8687, 90 % lognormal, 56             14.0 and 14.2   110 of 413     992 x 1742, 98 %, Zipf, 48             4.09 and 4.25   44 of 104
+constexpr int64_t SPARED_128 = 20, SPARED_64 = 120;
+int64_t spared_by_halves(const HostPlan &h, const std::vector<uint32_t> &dealt)
 {
     constexpr int64_t UNITS = 256, STARTING = 8;
-    if (h.ufk != UFK || h.n_blocks > 2 * UNITS || h.k_slices > 1 || h.n_cross > 0) return false;
+    if (h.ufk != UFK || h.n_blocks > 2 * UNITS || h.k_slices > 1 || h.n_cross > 0) return 0;
     auto fullest = [](const std::vector<uint32_t> &items, int64_t tiles) {
         std::vector<int64_t> load((size_t)UNITS, 0);
         const int64_t blocks = (int64_t)(items.size() / ((size_t)WAVES_PER_WG * ITEM_WORDS));
@@ -189,7 +195,7 @@ bool better_halved(const HostPlan &h, const std::vector<uint32_t> &dealt)
         return *std::max_element(load.begin(), load.end()) / tiles;
     };
     const int64_t one = fullest(dealt.empty() ? h.items : dealt, 1), spared = one - fullest(h.items, 2);
-    return spared >= 20 && spared * 6 >= one;
+    return spared * 6 >= one ? spared : 0;
 }
 
 spmm_status_t hip_fail()
@@ -381,7 +387,7 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
             const int slices = h.ufk == 16 ? 8 : h.ufk == 32 ? 16 : h.ufk == 64 ? 32 : io.n_hint <= 0 || io.n_hint > 64 ? 2 : io.n_hint > 32 ? 4 : 8;
             std::vector<uint32_t> dealt = deal_blocks(h, workgroups_per_unit(slices, h.ufi, h.ufk, false));
             p->n_dealt = (int32_t)(dealt.size() / ((size_t)WAVES_PER_WG * ITEM_WORDS));
-            p->halved = better_halved(h, dealt);
+            p->spared = spared_by_halves(h, dealt);
             if (p->n_dealt > 0) dealt.insert(dealt.begin(), h.items.begin(), h.items.end());
             const std::vector<uint32_t> &items = p->n_dealt > 0 ? dealt : h.items;
             if (st == SPMM_OK) st = upload(&p->d_items, items.data(), items.size() * 4, p->device_bytes);
@@ -524,7 +530,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     // (0.75 to 1.24 of the time).
     const bool three_tiles = !sliced && !wide && h.ufk == UFK && N > 160 && N <= 192 &&
                              (h.ufi > 1 || (N % 32 == 0 && plan->heavy == 0) || h.nnz < ((int64_t)1 << 19));
-    const bool two_tiles = plan->halved && !wide && N > 96 && N <= 128;
+    const bool two_tiles = !wide && ((N > 96 && N <= 128 && plan->spared >= SPARED_128) || (N > 40 && N <= 64 && plan->spared >= SPARED_64));
     // Column tiles of one width share a launch (front_blocks: in which order; a
     // tile begins while the previous one drains); a narrower rest takes a launch of its own.
     // Plans made for narrow B (chunks wider than 8 columns) run every N on their own narrow tiles.
@@ -538,7 +544,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
             slices = 1;
             return 64;
         }
-        slices = left > 64 ? (narrow_tiles || three_tiles || two_tiles ? 4 : 2) : left > 32 ? 4 : 8;
+        slices = left > 64 ? (narrow_tiles || three_tiles || two_tiles ? 4 : 2) : left > 32 && !(two_tiles && N <= 64) ? 4 : 8;
         return 256 / slices;
     };
     int32_t j0 = 0;
