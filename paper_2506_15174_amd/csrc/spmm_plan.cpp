@@ -492,6 +492,19 @@ bool columns_ok(int64_t K, const int32_t *row_ptr, const int32_t *col_idx, int64
     return std::count(bad.begin(), bad.end(), 0) == (ptrdiff_t)bad.size();
 }
 
+// Entries of the rows whose columns do not ascend.
+int64_t entries_out_of_order(const int32_t *row_ptr, const int32_t *col_idx, int64_t M)
+{
+    int64_t entries = 0;
+    for (int64_t i = 0; i < M; ++i) {
+        const int64_t a = row_ptr[i], b = row_ptr[i + 1];
+        bool ascend = true;
+        for (int64_t q = a + 1; q < b; ++q) ascend &= col_idx[q] >= col_idx[q - 1];
+        if (!ascend) entries += b - a;
+    }
+    return entries;
+}
+
 // Cuts the groups (creation order) into at most `want` contiguous ranges of about
 // equal numbers of entries; a cut never falls between the pieces of one panel.
 // Returns the range boundaries, first 0 and last groups.size().
@@ -834,9 +847,12 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
             const bool as_sorted = opts.sort_rows > 0 || (opts.sort_rows == 0 && skewed);
             ufi = as_sorted ? choose_ufi_skewed(KS, nnz, max_row, opts.n_hint, cross) : choose_ufi(M, KS, nnz, opts.n_hint);
         }
-        // single rows are copied, not merged: 2 to 8 threads take 1.2 to 1.5 times as long as one on 140 000 to 400 000 entries, 0.8 of
-        // the time on 1.3 million
-        if (opts.threads < 1 && ufi == 1 && nnz < FEW_ENTRIES) threads = 1;
+        // Single rows are copied, not merged: 2 to 8 threads take 1.2 to 1.5 times as long as one on 140 000 to 400 000 entries, 0.8 of
+        // the time on 1.3 million.  Rows out of order are sorted first, 50 ns an entry: a thread for every 2^14 of theirs.  On one thread
+        // and so, 8 cores, ms: 1024 x 4096 at 90 % 23.8 and 6.2 with all rows out of order, 9.4 and 3.3 with three of ten, 3.0 and 2.6 with one of
+        // twenty; 2048 x 4096 at 90 % 48.2 and 9.4, 18.8 and 5.3, 6.9 and 5.1; 900 x 3000 at 95 % 7.1 and 4.9, 2.9 and 2.4, 1.3 and 1.3.
+        if (opts.threads < 1 && ufi == 1 && nnz < FEW_ENTRIES && !opts.schedule_only)
+            threads = (int)std::min<int64_t>(threads, std::max<int64_t>(1, entries_out_of_order(row_ptr, col_idx, M) >> 14));
         // single rows share nothing: sorting them would only scatter the rows of C
         const bool sorted = opts.sort_rows > 0 || (opts.sort_rows == 0 && skewed && ufi > 1);
         // row_order[i]: the matrix row that row i of a slice stands for (sorted plans only)

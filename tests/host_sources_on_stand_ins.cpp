@@ -4,14 +4,19 @@
 //   choices    which matrices are left to chunks that strips would take by the lengths of their rows
 //   launches   what spmm_execute hands to the launcher
 //   places     what the workgroups of a launch compute
+//   threads    how many threads a creation starts
+#include <dlfcn.h>
 #include <hip/hip_runtime_api.h>
+#include <pthread.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "spmm.h"
@@ -38,6 +43,18 @@ void operator delete(void *p) noexcept
     std::free(p);
 }
 void operator delete(void *p, size_t) noexcept { operator delete(p); }
+
+// ---- threads: counted
+
+static std::atomic<long> threads_started{0};
+
+extern "C" int pthread_create(pthread_t *thread, const pthread_attr_t *attr, void *(*start)(void *), void *arg)
+{
+    typedef int (*function)(pthread_t *, const pthread_attr_t *, void *(*)(void *), void *);
+    static const function real = reinterpret_cast<function>(dlsym(RTLD_NEXT, "pthread_create"));
+    ++threads_started;
+    return real(thread, attr, start, arg);
+}
 
 // ---- device memory
 
@@ -454,6 +471,45 @@ static void places()
     REQUIRE(none > 0 && some > 0 && whole > 0);
 }
 
+// Plans of single rows with fewer than 2^20 entries are made by one thread where the columns ascend, and by several where many
+// rows have to be sorted first; the plans are the same.
+static void threads()
+{
+    csr ordered = spread(4096, 0.0, 1024, 0.1);
+    for (size_t q = 0; q < ordered.vals.size(); ++q) ordered.vals[q] = (float)q;
+    REQUIRE(ordered.vals.size() > (size_t)1 << 18 && ordered.vals.size() < (size_t)1 << 20);
+    if (std::thread::hardware_concurrency() < 2) return;
+    std::vector<uint32_t> arrays[3];
+    long started[3];
+    for (int k = 0; k < 3; ++k) {  // rows turned around: none, the first ten, all
+        csr a = ordered;
+        for (int64_t i = 0; i < (k == 0 ? 0 : k == 1 ? 10 : a.M); ++i) {
+            std::reverse(a.col_idx.begin() + a.row_ptr[(size_t)i], a.col_idx.begin() + a.row_ptr[(size_t)i + 1]);
+            std::reverse(a.vals.begin() + a.row_ptr[(size_t)i], a.vals.begin() + a.row_ptr[(size_t)i + 1]);
+        }
+        spmm_options_t o;
+        std::memset(&o, 0, sizeof o);
+        o.host_only = 1;
+        o.n_hint = 64;
+        spmm_plan_t *p = nullptr;
+        spmm_plan_info_t info;
+        const long before = threads_started;
+        REQUIRE(create(a, o, &p) == SPMM_OK && spmm_plan_describe(p, &info) == SPMM_OK && info.ufi == 1);
+        started[k] = threads_started - before;
+        for (int which : {SPMM_ARRAY_HDR, SPMM_ARRAY_STREAM, SPMM_ARRAY_WINS, SPMM_ARRAY_ITEMS}) {
+            int64_t n = 0;
+            REQUIRE(spmm_plan_get_array(p, which, nullptr, 0, &n) == SPMM_OK);
+            const size_t at = arrays[k].size();
+            arrays[k].resize(at + (size_t)n);
+            REQUIRE(spmm_plan_get_array(p, which, arrays[k].data() + at, n, nullptr) == SPMM_OK);
+        }
+        REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
+    }
+    std::printf("threads started: %ld, %ld and %ld\n", started[0], started[1], started[2]);
+    REQUIRE(started[0] == 0 && started[1] == 0 && started[2] > 0);
+    REQUIRE(arrays[0] == arrays[1] && arrays[0] == arrays[2]);
+}
+
 int main(int argc, char **argv)
 {
     const char *what = argc > 1 ? argv[1] : "";
@@ -461,6 +517,7 @@ int main(int argc, char **argv)
     else if (!std::strcmp(what, "choices")) choices();
     else if (!std::strcmp(what, "launches")) held_to_two();
     else if (!std::strcmp(what, "places")) places();
+    else if (!std::strcmp(what, "threads")) threads();
     else return 2;
     std::printf("ok\n");
     return 0;

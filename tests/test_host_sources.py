@@ -40,3 +40,7 @@ def test_compute_units_held_to_two_workgroups(program):
 
 def test_every_block_of_every_column_tile_once(program):
     passes(program, "places")
+
+
+def test_rows_out_of_order_are_sorted_by_several_threads(program):
+    passes(program, "threads")
