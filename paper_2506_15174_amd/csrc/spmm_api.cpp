@@ -46,7 +46,8 @@ struct spmm_plan {
     int32_t heavy = 0;        // the first blocks that are heavier than most (heavy_blocks)
     uint32_t lds_pad = 0;     // extra LDS per workgroup that keeps a third one off a compute unit (hold_to_two)
     int32_t n_dealt = 0;      // blocks behind the plan's own in d_items, dealt to the compute units (deal_blocks)
-    int64_t spared = 0;       // chunks that two column tiles instead of one spare the fullest compute unit (spared_by_halves)
+    // Whether 41 to 64, 97 to 119 and 120 to 128 columns run as two column tiles (spared_by_two_tiles)
+    bool halved_64 = false, halved_119 = false, halved_128 = false;
 };
 
 namespace {
@@ -163,39 +164,53 @@ std::vector<uint32_t> deal_blocks(const HostPlan &h, int per_unit)
     return items;
 }
 
-// What two column tiles of half the width spare the fullest compute unit of a launch; 0 where that is less than a sixth of its load.  A
-// launch of up to 512 blocks ends with that unit, and two tiles, the blocks in turn, leave that one half a block where it had a whole one; they read the plan
-// twice and have twice the starts and ends, about 0.3 us.  `dealt`: the blocks as a launch of one tile gets them, if not in the plan's order.
-// Loads in chunks, as in deal_blocks (one is 64 cycles of the vector L1).  us in one tile and in two, plans and B in turn, and what the fullest unit is spared:
+// What two column tiles spare the fullest compute unit of a launch of N columns in one tile of 64 or 128, in chunks (one is 64 cycles of
+// the vector L1); 0 where that is not worth it.
+//
+// A launch of up to 512 blocks ends with its fullest unit.  Of up to 128 blocks a block's two tiles, each about half of its time, go to two units of
+// which one would be idle; of more, even ones too, a unit with a block more than another or a heavy one gets half a block there.  Against that, two
+// tiles read the plan twice and have twice the starts and ends, about 0.3 us, and where rows of B are no whole lines they fetch more lines.
+// The loads of both launches are counted in the order in which their workgroups start (front_blocks: block by block from 120 columns on, below at most
+// the heavy ones or 128 first); blocks as in deal_blocks.  us in one tile and in two, plans and B in turn, and what the fullest unit is spared:
 //   1103 x 7373, 99 %, Zipf, 97 columns        34.4 and 19.0   248 of 511     506 x 902, 94 %, Zipf, 97              5.75 and 4.41   64 of 127
 //   300 x 4096, 90 % lognormal, 128            11.0 and 7.1     65 of 192     512 x 2048, 90 % lognormal, 128        6.08 and 5.51   36 of 125
 //   2048 x 2048, 98 %, Zipf, 128                8.6 and 6.5     68 of 192     365 x 2494, 98 % lognormal, 128        3.34 and 3.10   20 of 40
 //   512 x 512, 80 %, 128                       3.62 and 3.97    12 of 63      424 x 2254, 94 %, 100                  4.02 and 4.79   -5 of 63
 //   512 x 2048, 90 %, 128                      5.02 and 5.10     4 of 69      6837 x 1529, 99 %, Zipf, 97 (1131 blocks)  6.3 and 9.2  21 of 168
-// Of 35 such products the 16 of up to 512 blocks that are spared 20 are faster, of the others four; of 22 others that it takes 20,
-// the other two 0.4 and 1.5 % slower.
-//
 // A chunk's rows of B in tiles of 64 and 32 columns take half the time, and four slices and eight more of the rest:
 //   566 x 14392, 98 %, Zipf, 64 columns        47.6 and 26.3   904 of 1808    1256 x 5508, 98 %, Zipf, 56            18.0 and 12.6  320 of 656
 //   958 x 3397, 98 %, Zipf, 48                 6.51 and 6.15   124 of 264     1971 x 3239, 98 %, Zipf, 64            6.77 and 6.64  120 of 280
 //   541 x 8687, 90 % lognormal, 56             14.0 and 14.2   110 of 413     992 x 1742, 98 %, Zipf, 48             4.09 and 4.25   44 of 104
-constexpr int64_t SPARED_128 = 20, SPARED_64 = 120;
-int64_t spared_by_halves(const HostPlan &h, const std::vector<uint32_t> &dealt)
+// 183 chunk plans of 64 to 4096 rows, Zipf, lognormal and even: at 120 to 128 columns 28 are taken (20 chunks, a sixth of the load), 1.21 times as fast on
+// average and 1 % slower at worst; at 97 to 119 39, 1.16 times and 1 % at worst; at 41 to 64 (120 chunks) 33, 1.19 times and none slower.  Taller panels, whose chunks are
+// multiplied by more rows, below 120 columns only for a quarter: 657 x 7119, 95 % lognormal, 119 columns 13.2 and 14.4 (46 of 265), 815 x 3535,
+// 96 %, 119, 8.1 and 8.6 (31 of 163).  With the loads counted as if all launches went block by block 14 of 54 at 97 to 119 columns were slower, up to 11 %.
+int64_t spared_by_two_tiles(const HostPlan &h, const std::vector<uint32_t> &dealt, int32_t heavy, int32_t N)
 {
     constexpr int64_t UNITS = 256, STARTING = 8;
     if (h.ufk != UFK || h.n_blocks > 2 * UNITS || h.k_slices > 1 || h.n_cross > 0) return 0;
-    auto fullest = [](const std::vector<uint32_t> &items, int64_t tiles) {
+    constexpr size_t WORDS = (size_t)WAVES_PER_WG * ITEM_WORDS;
+    spmm_launch_args a;
+    a.width = N;
+    a.heavy = heavy;
+    auto fullest = [&](const std::vector<uint32_t> &items, int32_t tiles, int32_t tile_cols) {
+        a.n_blocks = (int32_t)(items.size() / WORDS);
+        a.n_tiles = tiles;
+        a.tile_cols = tile_cols;
+        const launch_shape shape{(uint32_t)a.n_blocks, (uint32_t)tiles, front_blocks(a)};
         std::vector<int64_t> load((size_t)UNITS, 0);
-        const int64_t blocks = (int64_t)(items.size() / ((size_t)WAVES_PER_WG * ITEM_WORDS));
-        for (int64_t at = 0; at < blocks * tiles; ++at) {
-            int64_t chunks = 0;
-            for (int w = 0; w < WAVES_PER_WG; ++w) chunks += items[(size_t)((at / tiles * WAVES_PER_WG + w) * ITEM_WORDS + IT_NCHUNKS)];
-            if (chunks > 0) load[(size_t)(at % UNITS)] += chunks + STARTING;
-        }
+        for (uint32_t y = 0; y < shape.n_tiles; ++y)
+            for (uint32_t x = 0; x < shape.n_blocks; ++x) {
+                const uint32_t *block = items.data() + place_of(shape, launch_group{x, y}).block * WORDS;
+                int64_t chunks = 0;
+                for (int w = 0; w < WAVES_PER_WG; ++w) chunks += block[w * ITEM_WORDS + IT_NCHUNKS];
+                if (chunks > 0) load[(y * shape.n_blocks + x) % (uint32_t)UNITS] += chunks + STARTING;
+            }
         return *std::max_element(load.begin(), load.end()) / tiles;
     };
-    const int64_t one = fullest(dealt.empty() ? h.items : dealt, 1), spared = one - fullest(h.items, 2);
-    return spared * 6 >= one ? spared : 0;
+    const int32_t half = N > 64 ? 64 : 32;
+    const int64_t one = fullest(dealt.empty() ? h.items : dealt, 1, 2 * half), spared = one - fullest(h.items, 2, half);
+    return spared >= (N > 64 ? 20 : 120) && spared * (h.ufi > 1 && N < 120 ? 4 : 6) >= one ? spared : 0;
 }
 
 spmm_status_t hip_fail()
@@ -387,7 +402,9 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
             const int slices = h.ufk == 16 ? 8 : h.ufk == 32 ? 16 : h.ufk == 64 ? 32 : io.n_hint <= 0 || io.n_hint > 64 ? 2 : io.n_hint > 32 ? 4 : 8;
             std::vector<uint32_t> dealt = deal_blocks(h, workgroups_per_unit(slices, h.ufi, h.ufk, false));
             p->n_dealt = (int32_t)(dealt.size() / ((size_t)WAVES_PER_WG * ITEM_WORDS));
-            p->spared = spared_by_halves(h, dealt);
+            p->halved_64 = spared_by_two_tiles(h, dealt, p->heavy, 64) > 0;
+            p->halved_119 = spared_by_two_tiles(h, dealt, p->heavy, 119) > 0;
+            p->halved_128 = spared_by_two_tiles(h, dealt, p->heavy, 128) > 0;
             if (p->n_dealt > 0) dealt.insert(dealt.begin(), h.items.begin(), h.items.end());
             const std::vector<uint32_t> &items = p->n_dealt > 0 ? dealt : h.items;
             if (st == SPMM_OK) st = upload(&p->d_items, items.data(), items.size() * 4, p->device_bytes);
@@ -530,7 +547,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     // (0.75 to 1.24 of the time).
     const bool three_tiles = !sliced && !wide && h.ufk == UFK && N > 160 && N <= 192 &&
                              (h.ufi > 1 || (N % 32 == 0 && plan->heavy == 0) || h.nnz < ((int64_t)1 << 19));
-    const bool two_tiles = !wide && ((N > 96 && N <= 128 && plan->spared >= SPARED_128) || (N > 40 && N <= 64 && plan->spared >= SPARED_64));
+    const bool two_tiles = !wide && (N > 96 ? N < 120 ? plan->halved_119 : N <= 128 && plan->halved_128 : N > 40 && N <= 64 && plan->halved_64);
     // Column tiles of one width share a launch (front_blocks: in which order; a
     // tile begins while the previous one drains); a narrower rest takes a launch of its own.
     // Plans made for narrow B (chunks wider than 8 columns) run every N on their own narrow tiles.

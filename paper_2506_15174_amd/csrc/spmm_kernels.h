@@ -86,6 +86,13 @@ struct spmm_launch_args {
 struct place {
     uint32_t block, tile;
 };
+// A launch and a workgroup of it for place_of on the host; a kernel hands over its arguments and blockIdx.
+struct launch_shape {
+    uint32_t n_blocks, n_tiles, front;
+};
+struct launch_group {
+    uint32_t x, y;
+};
 #ifdef __HIPCC__
 #define SPMM_DEVICE __device__ __forceinline__
 #else

@@ -413,20 +413,13 @@ static void held_to_two()
     REQUIRE(launches(spread(512, 0.5), 64, &info)[0].lds_pad == 0 && info.n_blocks <= 512);
 }
 
-struct launch_shape {
-    uint32_t n_blocks, n_tiles, front;
-};
-struct workgroup {
-    uint32_t x, y;
-};
-
 // Every block of every tile exactly once: the first `front` blocks of all tiles, block by block, then the others tile by tile.
 static void places_of(uint32_t n_blocks, uint32_t n_tiles, uint32_t front)
 {
     uint32_t block = 0, tile = 0;  // expected
     for (uint32_t y = 0; y < n_tiles; ++y)
         for (uint32_t x = 0; x < n_blocks; ++x) {
-            const place p = place_of(launch_shape{n_blocks, n_tiles, front}, workgroup{x, y});
+            const place p = place_of(launch_shape{n_blocks, n_tiles, front}, launch_group{x, y});
             REQUIRE(p.block == block && p.tile == tile);
             if (block < front) {
                 if (++tile == n_tiles) {
@@ -450,7 +443,7 @@ static void places()
     // the largest launches: workgroups of 256 threads, fewer than 2^32 of these in a row of the grid
     const uint32_t most = (1u << 24) - 1;
     const launch_shape wide{most, 256, 1}, whole_front{most, 8, most};
-    const place first = place_of(wide, workgroup{0, 0}), last = place_of(wide, workgroup{most - 1, 255}), end = place_of(whole_front, workgroup{most - 1, 7});
+    const place first = place_of(wide, launch_group{0, 0}), last = place_of(wide, launch_group{most - 1, 255}), end = place_of(whole_front, launch_group{most - 1, 7});
     REQUIRE(first.block == 0 && first.tile == 0 && last.block == most - 1 && last.tile == 255 && end.block == most - 1 && end.tile == 7);
     // the rule's choices, at the edges of its widths, for plans of few and many, even and uneven blocks
     uint32_t whole = 0, some = 0, none = 0;
