@@ -224,7 +224,6 @@ def kernel_shape(N, ufi, K=0, ufk=8, k_slices=1):
     if ufk != 8:
         S = {16: 8, 32: 16}.get(ufk, 64 if N <= 4 else 32)
         return "S=%d,VW=4,D=2,UFK=%d" % (S, ufk)
-    # (a plan of single rows that holds compute units to two workgroups keeps D=2)
     depth = {8: (2, 3, 4), 4: (2, 3, 4), 2: (2, 2, 6), 1: (1, 2, 8)}[ufi]
     if k_slices == 1 and tiles_of_64(N, K):
         return "S=4,VW=4,D=%d, tiles of 64 columns" % depth[1]

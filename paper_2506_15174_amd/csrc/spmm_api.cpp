@@ -44,7 +44,6 @@ struct spmm_plan {
     int depth = 0;            // spmm_options_t.depth: pipeline depth asked for (0 = per-instance default)
     bool probe = false;       // spmm_options_t.probe: loads-only launches (measurement)
     int32_t heavy = 0;        // the first blocks that are heavier than most (heavy_blocks)
-    uint32_t lds_pad = 0;     // extra LDS per workgroup that keeps a third one off a compute unit (hold_to_two)
     int32_t n_dealt = 0;      // blocks behind the plan's own in d_items, dealt to the compute units (deal_blocks)
     // Whether 41 to 64, 97 to 119 and 120 to 128 columns run as two column tiles (spared_by_two_tiles)
     bool halved_64 = false, halved_119 = false, halved_128 = false;
@@ -71,33 +70,6 @@ int32_t heavy_blocks(const HostPlan &h)
     return (int32_t)last;
 }
 
-// Whether to hold a compute unit to two workgroups.  The workgroups come heaviest first.  While all of
-// them fit the chip at once the device deals them out in turn, so with a few more than 512 the heaviest
-// units, which hold the first and the 257th, get the 513th as well; held to two per unit, those few wait
-// for the first one with room, a lightly loaded one.  (1024 x 4096 with lognormal rows, 90 % pruned, 64
-// columns, 559 workgroups: 9.9 -> 8.2 us.)  Fewer waves hide less latency, and those last workgroups start
-// late, so the cap is for plans where the most loaded unit gets at least 14 % less to do and a unit's mean load
-// shrinks by 24 chunks or more.  Timed with and without it, 360 random plans of 513 to 768 workgroups: the 23
-// that this takes run 6 % faster on average (20 % to two of 10 and 13 % slower); the other plans of single rows,
-// held all the same, would be 3 % slower, and so would the ten of taller panels that it would take, whose
-// registers leave less room for a third workgroup to begin with.  (A launch of dealt blocks does without.)
-bool hold_to_two(const HostPlan &h)
-{
-    constexpr int64_t UNITS = 256;
-    const int64_t n = h.n_blocks;
-    if (h.ufi != 1 || n <= 2 * UNITS || n > 2 * UNITS + UNITS / 2) return false;
-    auto weight = [&](int64_t block) { return block_weight(h, block); };
-    std::vector<int64_t> held((size_t)UNITS, 0);
-    for (int64_t b = 0; b < 2 * UNITS; ++b) held[(size_t)(b % UNITS)] += weight(b);
-    std::vector<int64_t> dealt = held;
-    for (int64_t b = 2 * UNITS; b < n; ++b) {
-        dealt[(size_t)(b % UNITS)] += weight(b);
-        *std::min_element(held.begin(), held.end()) += weight(b);
-    }
-    const double ratio = (double)*std::max_element(held.begin(), held.end()) / (double)std::max<int64_t>(1, *std::max_element(dealt.begin(), dealt.end()));
-    return ratio <= 0.86 && (double)h.n_chunks / UNITS * (1.0 - ratio) >= 24.0;
-}
-
 // The blocks in the order in which compute units are loaded evenly; empty where the order they have does that.
 //
 // While all workgroups of a launch fit the chip the device deals them out in turn: block b goes to the unit of block
@@ -108,7 +80,7 @@ bool hold_to_two(const HostPlan &h)
 // A gather is bound by the unit's vector L1, so a unit's time is the sum of its blocks' chunks; a block's start and end
 // count as STARTING chunks.  A plan whose fullest unit gains less than 3 % keeps its order.
 //
-// In the plan's own order (the first and third held to two workgroups, hold_to_two) and dealt, lognormal rows:
+// In the plan's own order (the first and third with room for two workgroups on a unit, by LDS that they did not use) and dealt, lognormal rows:
 //   1024 x 4096, 90 % pruned, 64 columns, 560 blocks     8.8 -> 7.5 us
 //   1024 x 2048, 90 %, 64 columns, 286 blocks            6.5 -> 5.1
 //   1536 x 6144, 95 %, 64 columns, 646 blocks            9.7 -> 7.6
@@ -408,7 +380,6 @@ spmm_status_t create(plan_owner &plan, int64_t M, int64_t K, const int32_t *row_
             if (p->n_dealt > 0) dealt.insert(dealt.begin(), h.items.begin(), h.items.end());
             const std::vector<uint32_t> &items = p->n_dealt > 0 ? dealt : h.items;
             if (st == SPMM_OK) st = upload(&p->d_items, items.data(), items.size() * 4, p->device_bytes);
-            if (h.k_slices == 1 && win_words(h.ufk) == WIN_WORDS && hold_to_two(h)) p->lds_pad = 48u << 10;  // 32 KiB and these: half of a unit's LDS
         }
         if (st != SPMM_OK) return st;
         p->on_device = true;
@@ -593,7 +564,7 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
         a.width = cols;
         a.tile_cols = tile;
         a.n_tiles = n_tiles;
-        a.lds_pad = tile_pad == 0 && n_tiles == 1 ? plan->lds_pad : tile_pad;
+        a.lds_pad = tile_pad;
         const bool dealt = n_tiles == 1 && tile_pad == 0 && plan->n_dealt <= 256 * workgroups_per_unit(slices, h.ufi, h.ufk, wide);
         a.dealt = plan->d_items + (size_t)h.n_blocks * WAVES_PER_WG * ITEM_WORDS;
         a.n_dealt = dealt ? plan->n_dealt : 0;

@@ -53,7 +53,7 @@ struct spmm_launch_args {
     const uint32_t *rowmap = nullptr; // DEVICE row of C per row of the plan, or null (same rows)
     int32_t n_blocks;       // workgroups to launch
     // The same descriptors in the order in which compute units are loaded evenly, idle blocks among them (deal_blocks), for a
-    // launch of one column tile; it needs no lds_pad.  None: 0.
+    // launch of one column tile.  None: 0.
     const uint32_t *dealt = nullptr;
     int32_t n_dealt = 0;
     const float *B;         // DEVICE first column of the launch's first column tile

@@ -658,8 +658,7 @@ template <int U, int S, int VW, int DMAX, bool WIDE> hipError_t launch_depth(con
 // in flight for the same number of requests.  Single rows in two slices make four loads per chunk, and
 // up to 32 waves per compute unit keep the gather busy by themselves: looking a chunk ahead only costs work at
 // the ends of the short windows (4096 x 4096, 95 % pruned, 128 columns: 18.0 us with two in flight, 17.4 with
-// one; 22 even and uneven matrices 2 to 12 % faster).  A unit held to two workgroups (lds_pad) has not enough
-// waves for that and keeps two, and so do 64-bit addresses and a caller who asks for more.
+// one; 22 even and uneven matrices 2 to 12 % faster).  64-bit addresses keep two, and so does a caller who asks for more.
 template <int U, int D2, int D4, int D8> void launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream, hipError_t &ok)
 {
     switch (slices) {
@@ -695,7 +694,6 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
         spmm_launch_args dealt = a;
         dealt.items = a.dealt;
         dealt.n_blocks = a.n_dealt;
-        dealt.lds_pad = 0;
         dealt.n_dealt = 0;
         return spmm_launch_chunks(dealt, ufi, ufk, slices, wide, depth, stream);
     }
@@ -709,7 +707,7 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
             case 1: ok = launch_narrow<1, 2>(a, ufk, slices, stream); break;
             }
         }
-    } else if (ufi == 1 && slices == 2 && !wide && (depth > 1 || (depth == 0 && a.lds_pad > 0))) {
+    } else if (ufi == 1 && slices == 2 && !wide && depth > 1) {
         ok = launch_depth<1, 2, 4, 2, false>(a, depth, stream);
     } else {
         switch (ufi) {

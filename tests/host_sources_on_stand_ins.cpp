@@ -285,7 +285,7 @@ static void failures()
             REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
         }
     }
-    {   // a compute unit held to two workgroups (more than 512 of them)
+    {   // blocks dealt to the compute units (more than 512 of them)
         const csr uneven = matrix(1090, 2048, 16, 40);
         std::memset(&o, 0, sizeof o);
         o.threads = 1;
@@ -298,7 +298,7 @@ static void failures()
         std::printf("%lld workgroups\n", (long long)info.n_blocks);
         REQUIRE(info.n_blocks > 512 && info.n_blocks <= 640);
         REQUIRE(spmm_plan_destroy(p) == SPMM_OK);
-        fail_in_turn("held to two", uneven, o);
+        fail_in_turn("dealt", uneven, o);
     }
     {   // several threads: their handles and their states are allocations too
         std::memset(&o, 0, sizeof o);
@@ -394,23 +394,23 @@ static std::vector<spmm_launch_args> launches(const csr &a, int N, spmm_plan_inf
     return launched;
 }
 
-// Compute units are held to two workgroups (extra LDS) where a few more than 512 workgroups of uneven rows
-// would overload the units that get three; not for even rows or taller panels, not for other numbers of
-// workgroups, and not where several column tiles share the launch.
-static void held_to_two()
+// A few more than 512 workgroups of uneven rows, which would overload the units that get three, are dealt by weight; not even
+// rows, and not where several column tiles share the launch.  Compute units are held to two workgroups (extra LDS) for tiles
+// of 64 columns that fill an L2 only.
+static void dealt_or_held()
 {
     spmm_plan_info_t info;
     for (int N : {64, 100, 128}) {
         const std::vector<spmm_launch_args> uneven = launches(spread(4096, 0.5), N, &info);
         REQUIRE(info.ufi == 1 && info.n_blocks > 512 && info.n_blocks <= 640);
-        REQUIRE(uneven.size() == 1 && uneven[0].n_tiles == 1 && uneven[0].lds_pad == 48u << 10);
+        REQUIRE(uneven.size() == 1 && uneven[0].n_tiles == 1 && uneven[0].n_dealt > 512 && uneven[0].lds_pad == 0);
     }
     const std::vector<spmm_launch_args> two_tiles = launches(spread(4096, 0.5), 256, &info);
-    REQUIRE(two_tiles.size() == 1 && two_tiles[0].n_tiles == 2 && two_tiles[0].lds_pad == 0);
-    REQUIRE(launches(spread(4096, 0.0), 64, &info)[0].lds_pad == 0);
-    REQUIRE(launches(spread(1147, 0.5, 1230, 0.35), 64, &info)[0].lds_pad == 0);
-    REQUIRE(info.ufi == 2 && info.n_blocks > 512 && info.n_blocks <= 640);
-    REQUIRE(launches(spread(512, 0.5), 64, &info)[0].lds_pad == 0 && info.n_blocks <= 512);
+    REQUIRE(two_tiles.size() == 1 && two_tiles[0].n_tiles == 2 && two_tiles[0].n_dealt == 0 && two_tiles[0].lds_pad == 0);
+    const std::vector<spmm_launch_args> even = launches(matrix(1024, 4096, 10, 0), 64, &info);
+    REQUIRE(even[0].n_dealt == 0 && even[0].lds_pad == 0);
+    const std::vector<spmm_launch_args> filled = launches(spread(16384, 0.0, 300, 0.02), 128, &info);
+    REQUIRE(filled.size() == 1 && filled[0].n_tiles == 2 && filled[0].tile_cols == 64 && filled[0].lds_pad == 24u << 10);
 }
 
 // Every block of every tile exactly once: the first `front` blocks of all tiles, block by block, then the others tile by tile.
@@ -508,7 +508,7 @@ int main(int argc, char **argv)
     const char *what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "failures")) failures();
     else if (!std::strcmp(what, "choices")) choices();
-    else if (!std::strcmp(what, "launches")) held_to_two();
+    else if (!std::strcmp(what, "launches")) dealt_or_held();
     else if (!std::strcmp(what, "places")) places();
     else if (!std::strcmp(what, "threads")) threads();
     else return 2;

@@ -34,7 +34,7 @@ def test_which_path_is_chosen(program):
     passes(program, "choices")
 
 
-def test_compute_units_held_to_two_workgroups(program):
+def test_blocks_are_dealt_or_compute_units_held_to_two_workgroups(program):
     passes(program, "launches")
 
 
