@@ -17,7 +17,7 @@ TORCH_EXT_SOURCE = "spmm_torch.cpp"
 TORCH_EXT_PATH = os.path.join(LIB_DIR, "_spmm_torch.so")
 
 SOURCES = ["spmm_kernels.hip", "spmm_tiles.hip", "spmm_strips.hip", "spmm_plan.cpp", "spmm_api.cpp"]
-HEADERS = ["spmm_format.h", "spmm_kernels.h", "spmm_plan.h", "spmm_tiles.h", "spmm_strips.h", "spmm_strips_build.h", "spmm_upload.h", "spmm_launch.h"]
+HEADERS = ["spmm_format.h", "spmm_kernels.h", "spmm_plan.h", "spmm_tiles.h", "spmm_strips.h", "spmm_strips_build.h", "spmm_upload.h", "spmm_launch.h", "spmm_places.h"]
 
 
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")

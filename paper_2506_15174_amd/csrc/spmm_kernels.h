@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "spmm_format.h"
+#include "spmm_places.h"
 
 // Waves per SIMD the register budget of an instance is sized for.  Narrow slices
 // keep few B rows in flight per wave and walk a long dependent chain per chunk
@@ -93,11 +94,6 @@ struct launch_shape {
 struct launch_group {
     uint32_t x, y;
 };
-#ifdef __HIPCC__
-#define SPMM_DEVICE __device__ __forceinline__
-#else
-#define SPMM_DEVICE inline
-#endif
 template <typename args_t, typename at_t> SPMM_DEVICE place place_of(const args_t &args, const at_t &group)
 {
     if (__builtin_expect(args.front == 0, 1)) return place{group.x, group.y};  // (one tile: without a taken branch)

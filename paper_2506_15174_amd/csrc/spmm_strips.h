@@ -91,6 +91,9 @@ int spmm_strips_build_on_device(int64_t M, int64_t K, const int32_t *row_ptr, co
                                 strips::start &begun, StripPlan &out);
 void spmm_strips_release(StripPlan &p);  // however it was built
 
+// Strips of the first of the two sets in which a product's come, half of the XCDs fetching each; all: one set.
+extern "C" uint32_t spmm_strips_of_set(int64_t steps, int64_t K, int32_t N);
+
 // Enqueues C <- A x B.  Returns the hipError_t of the launch as int.
 int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N, float *C, void *stream);
 

@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "spmm_launch.h"
+#include "spmm_places.h"
 #include "spmm_strips_build.h"
 #include "spmm_upload.h"
 
@@ -29,7 +30,7 @@ struct strip_args {
     // bands, and there are 2048 or one per strip without); the launch's first.
     uint32_t n_places, first;
     int32_t K, N, bands, band_rows;
-    uint32_t n_units, n_groups, n_strips, set;  // set: strips that come first, of all groups (strips_of_set)
+    uint32_t n_units, n_groups, n_strips, set;  // set: strips that come first, of all groups (spmm_strips_of_set)
     uint32_t share;                             // places of an XCD in this launch
 };
 
@@ -93,16 +94,14 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
 {
     extern __shared__ __attribute__((aligned(32))) char lds[];  // (whole rows: the halves of one differ in a bit of the address)
     // Workgroups are dealt to the eight XCDs in turn: each takes an eighth of the places, next to each other, so that the strips of
-    // a group, which read the same entries, share an L2, and in two sets (strips_of_set) half of the XCDs fetch half of B.
+    // a group, which read the same entries, share an L2, and in two sets (spmm_strips_of_set) half of the XCDs fetch half of B.
     // (The arguments all at once: in rounds, each where it is needed, the last one's wait would come behind the unit's place.)
     asm volatile("" ::"s"(args.units), "s"(args.B), "s"(args.b_bytes), "s"(args.n_places), "s"(args.first), "s"(args.K), "s"(args.N), "s"(args.bands), "s"(args.band_rows),
                  "s"(args.n_units), "s"(args.n_groups), "s"(args.n_strips), "s"(args.set), "s"(args.share));
     const uint32_t place = args.first + blockIdx.x % 8u * args.share + blockIdx.x / 8u;
     if (place >= args.n_places) return;
-    const uint32_t first_set = args.n_groups * args.set;
-    const bool second = place >= first_set;
-    const uint32_t at = second ? place - first_set : place, width = second ? args.n_strips - args.set : args.set;
-    const uint32_t group = at / width, strip = (second ? args.set : 0u) + at % width;
+    const set_place at = place_in_sets(place, args.n_groups, args.n_strips, args.set);
+    const uint32_t group = at.row, strip = at.column;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = (int)(threadIdx.x & 63);
     constexpr int AHEAD = 3;  // groups of a unit in registers: the one at work and the next two
@@ -771,6 +770,8 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
     return hipSuccess;
 }
 
+}  // namespace
+
 // Strips of the first of two sets, or all.  In one set every XCD fetches all of B into its L2, one fourth of a line per strip,
 // before its workgroups multiply, and an eighth of the entries; in two sets, one set's places before the other's, half of B and a quarter of the
 // entries.  That pays where the entries are few beside B and the sets share no line.  us in one set and in two, plans and B in turn:
@@ -780,14 +781,12 @@ hipError_t build(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
 //                 6     5000 x 4000, Zipf, 128           21.1 both
 //                 11    8968 x 2473, 92 %, 96            14.0 and 14.2     4096 x 4096, 80 %, 64 (14)        16.4 and 16.6
 // Rows that are not whole lines: 2 % slower to 1 % faster (110 to 250 columns).  Sets of 40 columns and fewer: up to 14 % slower.
-uint32_t strips_of_set(const StripPlan &p, int64_t K, int32_t N)
+uint32_t spmm_strips_of_set(int64_t steps, int64_t K, int32_t N)
 {
     const int64_t strips = ((int64_t)N + STRIP_COLS - 1) / STRIP_COLS, half = ((strips + 1) / 2 + 3) / 4 * 4;  // (four strips: a line)
-    const double entries = (double)p.steps * (STRIP_GROUP_BYTES / STRIP_STEPS), b = 4.0 * (double)K * (double)N;
+    const double entries = (double)steps * (STRIP_GROUP_BYTES / STRIP_STEPS), b = 4.0 * (double)K * (double)N;
     return (uint32_t)(N % 32 == 0 && strips >= 16 && entries < 8.0 * b ? half : strips);
 }
-
-}  // namespace
 
 int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N, float *C, void *stream)
 {
@@ -796,7 +795,7 @@ int spmm_strips_execute(const StripPlan &p, int64_t K, const float *B, int32_t N
     if (strips <= StripPlan::KNOWN) groups = p.groups[strips];
     else strip_time(p, K, N, &groups);
     strip_args a{reinterpret_cast<const char *>(p.d_stream), reinterpret_cast<const u32x2 *>(p.d_units), p.d_rows(), B, C, (uint64_t)K * (uint64_t)N * 4u, 0, 0,
-                 (int32_t)K, N, p.bands, p.band_rows, (uint32_t)p.n_units, (uint32_t)groups, (uint32_t)strips, strips_of_set(p, K, N), 0};
+                 (int32_t)K, N, p.bands, p.band_rows, (uint32_t)p.n_units, (uint32_t)groups, (uint32_t)strips, spmm_strips_of_set(p.steps, K, N), 0};
     a.n_places = a.n_groups * a.n_strips;
     const bool wide = (uint64_t)N * 4u * 32u >= (1ull << 32);
     const auto kernel = p.bands > 1 ? (wide ? spmm_strips_kernel<true, true> : spmm_strips_kernel<true, false>)

@@ -45,6 +45,10 @@ void spmm_tiles_release(TilePlan &p);
 // (1, 2 or 4) it runs with.  density = share of the entries kept, peak = the largest such share of a panel.
 extern "C" double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density, double peak, int *NB);
 
+// Column tiles of the first of the two sets in which those of panels of 16 rows come, half of the XCDs fetching each; all:
+// one set.  stream_words: of the plan.
+extern "C" uint32_t spmm_tiles_of_set(int rows, int64_t M, int64_t K, int32_t N, int64_t stream_words);
+
 // Enqueues C <- A x B.  Returns the hipError_t of the launch as int.
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream);
 

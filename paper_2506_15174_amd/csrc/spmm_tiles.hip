@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "spmm_launch.h"
+#include "spmm_places.h"
 #include "spmm_tiles.h"
 #include "spmm_upload.h"
 
@@ -214,19 +215,10 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
     constexpr int LDS_WORDS = W * SLOT > RED ? W * SLOT : RED;
     __shared__ __attribute__((aligned(16))) float lds[LDS_WORDS];
 
-    uint32_t id = place_in_matrix(args.first), tiles = (uint32_t)args.n_tiles, nt0 = 0;
-    if constexpr (R == 16) {
-        const uint32_t first_set = (uint32_t)args.n_panels * args.set;
-        if (__builtin_expect(id >= first_set, 0)) {
-            nt0 = args.set;
-            if (nt0 == tiles) return;
-            id -= first_set;
-            tiles -= nt0;
-        } else {
-            tiles = args.set;
-        }
-    }
-    const uint32_t nt = nt0 + id % tiles, panel = id / tiles;
+    const uint32_t id = place_in_matrix(args.first);
+    const set_place at = R == 16 ? place_in_sets(id, (uint32_t)args.n_panels, (uint32_t)args.n_tiles, args.set)
+                                 : set_place{id / (uint32_t)args.n_tiles, id % (uint32_t)args.n_tiles};
+    const uint32_t panel = at.row, nt = at.column;
     if (panel >= (uint32_t)args.n_panels) return;
     const uint32_t n0 = nt * (uint32_t)NT;
 
@@ -379,17 +371,16 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
 //                 1.2   512 x 2048, 80 %, 128          6.68 and 5.99
 //                 3.8   1024 x 2048, 70 %, 128         9.12 and 9.11     (32 rows: 4096 x 1024, 70 %, 128, 15: 12.2 and 12.4)
 // Rows that are not whole lines: 512 x 2048, 75 %, 100 columns 6.69 and 7.00.
-template <int R, int NB> uint32_t tiles_of_set(const tile_args &a, bool few_entries)
+uint32_t tiles_of_set(int tile_cols, uint32_t tiles, int64_t K, int32_t N, int64_t stream_words)
 {
-    constexpr uint32_t LINE = NB * R < 32 ? 32 / (NB * R) : 1;
-    const uint32_t tiles = (uint32_t)a.n_tiles, half = ((tiles + 1) / 2 + LINE - 1) / LINE * LINE;
-    return few_entries && half < tiles ? half : tiles;
+    const uint32_t line = tile_cols < 32 ? 32 / (uint32_t)tile_cols : 1, half = ((tiles + 1) / 2 + line - 1) / line * line;
+    return N % 32 == 0 && 4.0 * (double)stream_words < 1.5 * 4.0 * (double)K * (double)N && half < tiles ? half : tiles;
 }
 
-template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> hipError_t launch(tile_args &a, hipStream_t s, bool few_entries = false)
+template <int R, int NB, int W, bool STAGED, int MINW, bool WIDE = false> hipError_t launch(tile_args &a, hipStream_t s, int64_t stream_words = INT64_MAX)
 {
     a.n_tiles = (int32_t)(((int64_t)a.N + NB * R - 1) / (NB * R));
-    a.set = tiles_of_set<R, NB>(a, few_entries);
+    a.set = tiles_of_set(NB * R, (uint32_t)a.n_tiles, a.K, a.N, stream_words);
     return launch_places(spmm_tiles_kernel<R, NB, W, STAGED, WIDE, MINW>, a, 64 * W, s);
 }
 
@@ -1385,6 +1376,15 @@ double spmm_tiles_time(int rows, int64_t M, int64_t K, int64_t N, double density
     return best;
 }
 
+uint32_t spmm_tiles_of_set(int rows, int64_t M, int64_t K, int32_t N, int64_t stream_words)
+{
+    int NB = 1;
+    spmm_tiles_time(rows, M, K, N, 0.0, 0.0, &NB);
+    const uint32_t tiles = (uint32_t)(((int64_t)N + NB * rows - 1) / (NB * rows));
+    const bool wide = (int64_t)TILE_OPERANDS * 64 / rows * 4 * N >= ((int64_t)1 << 32);
+    return rows == 16 && !wide ? tiles_of_set(NB * rows, tiles, K, N, stream_words) : tiles;
+}
+
 int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, int32_t N, float *C, void *stream)
 {
     tile_args a{p.d_stream, p.d_offsets, B, C, (uint64_t)K * (uint64_t)N * 4u, (int32_t)p.n_panels, (int32_t)p.n_steps, 1,
@@ -1401,13 +1401,12 @@ int spmm_tiles_execute(const TilePlan &p, int64_t M, int64_t K, const float *B, 
     }
     int NB = 1;
     spmm_tiles_time(p.rows, M, K, N, 0.0, 0.0, &NB);
-    const bool few_entries = N % 32 == 0 && 4.0 * (double)p.stream_words < 1.5 * (double)a.b_bytes;
     switch (p.rows * 8 + NB) {
     case 32 * 8 + 4: return (int)(p.exact_parts ? launch_split<4>(a, p.loads, s) : launch<32, 4, 8, false, 2>(a, s));
     case 32 * 8 + 2: return (int)(p.n_steps <= FEW_STEPS || !p.exact_parts ? launch<32, 2, 16, false, 4>(a, s) : launch_split<2>(a, p.loads, s));
     case 32 * 8 + 1: return (int)launch<32, 1, 16, true, 4>(a, s);
-    case 16 * 8 + 4: return (int)launch<16, 4, 8, false, 2>(a, s, few_entries);
-    case 16 * 8 + 2: return (int)launch<16, 2, 8, true, 2>(a, s, few_entries);
-    default: return (int)launch<16, 1, 16, true, 4>(a, s, few_entries);
+    case 16 * 8 + 4: return (int)launch<16, 4, 8, false, 2>(a, s, p.stream_words);
+    case 16 * 8 + 2: return (int)launch<16, 2, 8, true, 2>(a, s, p.stream_words);
+    default: return (int)launch<16, 1, 16, true, 4>(a, s, p.stream_words);
     }
 }

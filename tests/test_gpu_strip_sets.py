@@ -1,5 +1,7 @@
 """Strips in two sets, each fetched by half of the XCDs: every strip of every group of rows is computed once, at sets of equal
 and of different sizes, in one band and in several, in one round of workgroups and in more."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -20,7 +22,12 @@ def test_whole_numbers_are_exact(M, K, density, N):
     csr = gen.csr_from_dense(W)
     B = rng.integers(-4, 5, (K, N)).astype(np.float32)
     plan = spmm.plan_create(csr.M, csr.K, csr.row_ptr, csr.col_idx, csr.vals, n_hint=128, strips=1)
-    assert plan.describe()["strip_units"] > 0
+    info = plan.describe()
+    assert info["strip_units"] > 0
+    f = spmm.load().spmm_strips_of_set
+    f.restype, f.argtypes = ctypes.c_uint32, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int32]
+    first = {128: 8, 160: 12, 192: 12, 256: 16, 288: 20, 2080: 132}.get(N, (N + 7) // 8)
+    assert f(info["n_enum"] // 64, K, N) == first
     full = torch.full((M + 2, N), float("nan"), device="cuda")
     for _ in range(2):
         plan.execute(torch.from_numpy(B).cuda(), full[1:M + 1])
