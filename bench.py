@@ -213,11 +213,21 @@ def tiles_of_64(N, K):
     return N > 64 and K * 512 > 4 << 20 and K * 256 <= 4 << 20
 
 
-def kernel_shape(N, ufi, K=0, ufk=8, k_slices=1):
+def column_tiles(plan, N):
+    """Column tiles of the (first) launch on N columns of a plan on chunks, and the columns of one."""
+    import ctypes
+    import paper_2506_15174_amd as spmm
+    f, cols = spmm.load().spmm_chunk_tiles, ctypes.c_int32(0)
+    f.restype, f.argtypes = ctypes.c_int32, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p]
+    return f(plan.handle, N, ctypes.byref(cols)), cols.value
+
+
+def kernel_shape(N, ufi, K=0, ufk=8, k_slices=1, tile_cols=0):
     """Template arguments of the instance spmm_execute launches for a tile of N columns
     (N a multiple of 4, at most 128) of a plan with panels of `ufi` rows and chunks of
     `ufk` columns: slices per wave, floats per lane, pipeline depth (the tables of
-    spmm_launch_chunks).  When 128 columns of B exceed one L2 and 64 fit
+    spmm_launch_chunks).  `tile_cols`: columns of a tile where the library says (column_tiles) that the product runs as
+    two of half the width, which depends on the rows' lengths.  When 128 columns of B exceed one L2 and 64 fit
     (8192 < K <= 16384) the product runs as two tiles of 64 columns, unless the plan is cut
     into column ranges (k_slices > 1), which runs full tiles.  Plans made for narrow B (ufk
     16 / 32 / 64) run on 8 / 16 / 32 or 64 slices."""
@@ -225,8 +235,10 @@ def kernel_shape(N, ufi, K=0, ufk=8, k_slices=1):
         S = {16: 8, 32: 16}.get(ufk, 64 if N <= 4 else 32)
         return "S=%d,VW=4,D=2,UFK=%d" % (S, ufk)
     depth = {8: (2, 3, 4), 4: (2, 3, 4), 2: (2, 2, 6), 1: (1, 2, 8)}[ufi]
-    if k_slices == 1 and tiles_of_64(N, K):
+    if k_slices == 1 and (tiles_of_64(N, K) or (tile_cols == 64 and N > 64)):
         return "S=4,VW=4,D=%d, tiles of 64 columns" % depth[1]
+    if tile_cols == 32 and N > 32:
+        return "S=8,VW=4,D=%d, tiles of 32 columns" % depth[2]
     if N > 64:
         return "S=2,VW=4,D=%d%s" % (depth[0], ", %d column ranges" % k_slices if k_slices > 1 else "")
     if N > 32:
@@ -736,7 +748,8 @@ def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, pla
         groups = split_groups(info["tile_rows"], csr.M, csr.K, N)
         kernel, launches = tile_kernel(info["tile_rows"], groups), 1
     else:
-        shape = kernel_shape(N, info["ufi"], csr.K, info["ufk"], info["k_slices"])
+        tiles, tile_cols = column_tiles(plan, N)
+        shape = kernel_shape(N, info["ufi"], csr.K, info["ufk"], info["k_slices"], tile_cols)
         kernel, launches = "spmm_chunks_kernel<UFI=%d,%s>" % (info["ufi"], shape), 1 + (info["n_cross"] > 0) + (info["k_slices"] > 1)
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 5), "traffic": traffic, "traffic_source": prov,
@@ -763,7 +776,6 @@ def kernel_report(torch, csr, plan, info, B, C, N, workload_key, samples=20, pla
     # rows (S rows of B per load); the ceiling is the rate the gather microbenchmark
     # reaches on distinct rows of an L2-resident B.
     S = int(shape.split(",")[0][2:])
-    tiles = 2 if (info["ufk"] == 8 and info["k_slices"] == 1 and tiles_of_64(N, csr.K)) else 1
     wave_loads = info["n_chunks"] * info["ufk"] // S * tiles
     roofline["gather"] = {"wave_loads_per_launch": wave_loads,
                           "g_wave_loads_per_s": round(wave_loads / (avg_ms * 1e-3) / 1e9, 2),

@@ -450,6 +450,69 @@ spmm_status_t(spmm_plan_create_ex)(spmm_plan_t **plan, int64_t M, int64_t K, con
 
 namespace {
 
+// How a plan's chunks take N columns of B.
+struct column_tiles {
+    bool wide, quads, sliced, narrow_tiles, three_tiles, two_tiles;
+    int ufk;
+    int32_t N;
+
+    column_tiles(const spmm_plan &plan, int32_t n) : ufk(plan.host.ufk), N(n)
+    {
+        const HostPlan &h = plan.host;
+        const uint64_t b_total = (uint64_t)h.K * (uint64_t)N * 4u;
+        // Narrow addressing: 32-bit byte offsets into B formed by a 24 x 24-bit multiply.
+        const bool narrow_ok = b_total <= 0xFFFFFFFFull && h.K < (1 << 24) && (uint64_t)N * 4u < (1u << 24);
+        wide = !narrow_ok || (plan.force_wide && b_total > 0);
+        // Four columns per lane: 16-byte loads and stores at 4-byte alignment are legal, and a
+        // last lane with fewer than four columns reads past the end of its rows of B, which is
+        // safe through the buffer descriptor of the narrow addressing only (range-checked).
+        quads = !wide || N % 4 == 0;
+        sliced = h.k_slices > 1;
+        // A 128-column tile of B that exceeds one L2 (4 MiB) while a 64-column tile fits: two
+        // narrower tiles read the plan twice but keep their rows of B L2-resident (measured on a
+        // 16384-column matrix of 13 M nonzeros: 275 against 295 us).
+        // (A plan cut along K binds every slice of B to the L2s of its own XCDs instead and runs full tiles.)
+        narrow_tiles = !sliced && (int64_t)h.K * 512 > ((int64_t)4 << 20) && (int64_t)h.K * 256 <= ((int64_t)4 << 20);
+        // 161 to 192 columns are three tiles of 64 in one launch: as 128 and 64 the launch of the wide tile drains
+        // before that of the rest begins.  24 even and uneven matrices at 161, 176, 188 and 192 columns: 13 to 18 % faster on
+        // average, 2 % slower at worst (24 others 12 to 17 and 6 %).  Single
+        // rows share no load, and a row of B that begins inside of a cache line takes one line in three more than its
+        // columns in tiles of 64, one in five in tiles of 128: from 2^19 entries on even ones are up to 11 % slower then, uneven ones
+        // between 14 % faster and 9 % slower; below, up to twice as fast.
+        // 129 to 160 columns, 128 and a tile of 32, stay: as three tiles of 64 the 24 matrices are 5 % slower on average at 130 columns, 1 % at 144 and 3 % faster at 160
+        // (0.75 to 1.24 of the time).
+        three_tiles = !sliced && !wide && ufk == UFK && N > 160 && N <= 192 && (h.ufi > 1 || (N % 32 == 0 && plan.heavy == 0) || h.nnz < ((int64_t)1 << 19));
+        two_tiles = !wide && (N > 96 ? N < 120 ? plan.halved_119 : N <= 128 && plan.halved_128 : N > 40 && N <= 64 && plan.halved_64);
+    }
+    // Columns of a tile where `left` are to be computed, and its slices.
+    int32_t tile_for(int32_t left, int &slices) const
+    {
+        if (ufk != UFK) {
+            slices = ufk == 16 ? 8 : ufk == 32 ? 16 : left > 4 ? 32 : 64;
+            return 256 / slices;
+        }
+        if (!quads) {
+            slices = 1;
+            return 64;
+        }
+        slices = left > 64 ? (narrow_tiles || three_tiles || two_tiles ? 4 : 2) : left > 32 && !(two_tiles && N <= 64) ? 4 : 8;
+        return 256 / slices;
+    }
+    // The next launch of those: its tiles, their columns (the last may have fewer) and slices, and the columns of all.
+    int32_t launch(int32_t left, int32_t &tile, int32_t &cols, int &slices) const
+    {
+        tile = tile_for(left, slices);
+        const int32_t n_tiles = left / tile;
+        cols = n_tiles * tile;
+        int rest_slices = 0;
+        if (n_tiles == 0 || (left > cols && tile_for(left - cols, rest_slices) == tile)) {
+            cols = left;  // the narrower last tile runs on the same kernel
+            return n_tiles + 1;
+        }
+        return n_tiles;
+    }
+};
+
 // cross_sums: scratch for the sums of panels cut across workgroups, with room for
 // cross_tiles column tiles of one launch (unused by plans without such panels)
 spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, float *C, void *stream,
@@ -470,14 +533,9 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     if (plan->strips.n_units > 0) return spmm_strips_execute(plan->strips, h.K, B, N, C, stream) == 0 ? SPMM_OK : hip_fail();
     if (plan->tiles.rows > 0) return spmm_tiles_execute(plan->tiles, h.M, h.K, B, N, C, stream) == 0 ? SPMM_OK : hip_fail();
 
+    const column_tiles tiling(*plan, N);
+    const bool wide = tiling.wide, sliced = tiling.sliced;
     const uint64_t b_total = (uint64_t)h.K * (uint64_t)N * 4u;
-    // Narrow addressing: 32-bit byte offsets into B formed by a 24 x 24-bit multiply.
-    const bool narrow_ok = b_total <= 0xFFFFFFFFull && h.K < (1 << 24) && (uint64_t)N * 4u < (1u << 24);
-    const bool wide = !narrow_ok || (plan->force_wide && b_total > 0);
-    // Four columns per lane: 16-byte loads and stores at 4-byte alignment are legal, and a
-    // last lane with fewer than four columns reads past the end of its rows of B, which is
-    // safe through the buffer descriptor of the narrow addressing only (range-checked).
-    const bool quads = !wide || N % 4 == 0;
     spmm_launch_args a;
     a.stream = plan->d_stream;
     a.wins = plan->d_wins;
@@ -486,7 +544,6 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     a.n_blocks = (int32_t)h.n_blocks;
     a.ldn = N;
     a.ldc = N;
-    const bool sliced = h.k_slices > 1;
     a.k_slices = h.k_slices;
     a.slice_rows = h.slice_rows;
     a.M = h.M;
@@ -500,53 +557,19 @@ spmm_status_t execute_with(const spmm_plan_t *plan, const float *B, int32_t N, f
     if (plan->probe && (wide || h.ufk > 16)) return SPMM_ERR_UNSUPPORTED;
     // the scratch of panels cut across workgroups holds so many column tiles of one launch
     const int32_t max_tiles = sliced ? 1 : h.n_cross_slots > 0 ? cross_tiles : 65535;
-    // A 128-column tile of B that exceeds one L2 (4 MiB) while a 64-column tile fits: two
-    // narrower tiles read the plan twice but keep their rows of B L2-resident (measured on a
-    // 16384-column matrix of 13 M nonzeros: 275 against 295 us).
-    // (A plan cut along K binds every slice of B to the L2s of its own XCDs instead and runs full tiles.)
-    const bool narrow_tiles = !sliced && (int64_t)h.K * 512 > ((int64_t)4 << 20) && (int64_t)h.K * 256 <= ((int64_t)4 << 20);
     // A tile of 64 columns where 128 exceed the L2 fills it: two workgroups per CU instead of three keep the
-    // rows of B that concurrently running waves sweep inside it (same matrix: 262 against 275 us).
-    const uint32_t tile_pad = narrow_tiles ? 24u << 10 : 0u;
-    // 161 to 192 columns are three tiles of 64 in one launch: as 128 and 64 the launch of the wide tile drains
-    // before that of the rest begins.  24 even and uneven matrices at 161, 176, 188 and 192 columns: 13 to 18 % faster on
-    // average, 2 % slower at worst (24 others 12 to 17 and 6 %).  Single
-    // rows share no load, and a row of B that begins inside of a cache line takes one line in three more than its
-    // columns in tiles of 64, one in five in tiles of 128: from 2^19 entries on even ones are up to 11 % slower then, uneven ones
-    // between 14 % faster and 9 % slower; below, up to twice as fast.
-    // 129 to 160 columns, 128 and a tile of 32, stay: as three tiles of 64 the 24 matrices are 5 % slower on average at 130 columns, 1 % at 144 and 3 % faster at 160
-    // (0.75 to 1.24 of the time).
-    const bool three_tiles = !sliced && !wide && h.ufk == UFK && N > 160 && N <= 192 &&
-                             (h.ufi > 1 || (N % 32 == 0 && plan->heavy == 0) || h.nnz < ((int64_t)1 << 19));
-    const bool two_tiles = !wide && (N > 96 ? N < 120 ? plan->halved_119 : N <= 128 && plan->halved_128 : N > 40 && N <= 64 && plan->halved_64);
+    // rows of B that concurrently running waves sweep inside it (16384 columns, 13 M nonzeros: 262 against 275 us).
+    const uint32_t tile_pad = tiling.narrow_tiles ? 24u << 10 : 0u;
     // Column tiles of one width share a launch (front_blocks: in which order; a
     // tile begins while the previous one drains); a narrower rest takes a launch of its own.
     // Plans made for narrow B (chunks wider than 8 columns) run every N on their own narrow tiles.
     if (h.ufk != UFK && wide) return SPMM_ERR_UNSUPPORTED;
-    auto tile_for = [&](int32_t left, int &slices) -> int32_t {
-        if (h.ufk != UFK) {
-            slices = h.ufk == 16 ? 8 : h.ufk == 32 ? 16 : left > 4 ? 32 : 64;
-            return 256 / slices;
-        }
-        if (!quads) {
-            slices = 1;
-            return 64;
-        }
-        slices = left > 64 ? (narrow_tiles || three_tiles || two_tiles ? 4 : 2) : left > 32 && !(two_tiles && N <= 64) ? 4 : 8;
-        return 256 / slices;
-    };
     int32_t j0 = 0;
     while (j0 < N) {
         // a plan cut along K takes the columns in batches its slices' buffer holds
         const int32_t left = sliced && N - j0 > KSLICE_COLS ? KSLICE_COLS : N - j0;
         int slices = 0;
-        const int32_t tile = tile_for(left, slices);
-        int32_t n_tiles = left / tile, cols = n_tiles * tile;
-        int rest_slices = 0;
-        if (n_tiles == 0 || (left > cols && tile_for(left - cols, rest_slices) == tile)) {
-            n_tiles += 1;  // the narrower last tile runs on the same kernel
-            cols = left;
-        }
+        int32_t tile = 0, cols = 0, n_tiles = tiling.launch(left, tile, cols, slices);
         if (n_tiles > max_tiles) {  // grid limit, or the scratch's; the loop takes the rest
             n_tiles = max_tiles;
             cols = n_tiles * tile;
@@ -706,6 +729,19 @@ int64_t spmm_strips_words(const spmm_plan_t *plan, uint32_t *out, int64_t cap, i
         (hipMemcpy(out, p.d_units, front * 4, hipMemcpyDeviceToHost) != hipSuccess || hipMemcpy(out + front, p.d_stream, behind * 4, hipMemcpyDeviceToHost) != hipSuccess))
         return -1;
     return (int64_t)(front + behind);
+}
+
+// For the tests and the benchmark: the column tiles of the first launch on N columns of a plan on chunks, and the columns of one; 0
+// on tiles and strips.
+int32_t spmm_chunk_tiles(const spmm_plan_t *plan, int32_t N, int32_t *tile_cols)
+{
+    if (!plan || !plan->on_device || !plan->on_chunks() || N < 1) return 0;
+    int32_t tile = 0, cols = 0;
+    int slices = 0;
+    const column_tiles tiling(*plan, N);
+    const int32_t n = tiling.launch(tiling.sliced ? std::min(N, KSLICE_COLS) : N, tile, cols, slices);
+    if (tile_cols) *tile_cols = tile;
+    return n;
 }
 
 const char *spmm_status_string(spmm_status_t status)

@@ -4,11 +4,15 @@
 #include "host_sources_on_stand_ins.cpp"
 #undef main
 
+extern "C" int32_t spmm_chunk_tiles(const spmm_plan_t *plan, int32_t N, int32_t *tile_cols);
+
 static std::vector<spmm_launch_args> on_columns(const spmm_plan_t *p, int N)
 {
     static float word;  // B and C are only passed on
     launched.clear();
     REQUIRE(spmm_execute(p, &word, N, &word, nullptr) == SPMM_OK && !launched.empty());
+    int32_t tile_cols = 0;
+    REQUIRE(spmm_chunk_tiles(p, N, &tile_cols) == launched[0].n_tiles && tile_cols == launched[0].tile_cols);
     return launched;
 }
 

@@ -27,6 +27,10 @@ def test_kernel_label_follows_the_launch_table():
         assert bench.kernel_shape(32, ufi) == "S=8,VW=4,D=%d" % d8
         # 128 columns of a 16384-row B exceed one L2, 64 fit: tiles of 64
         assert bench.kernel_shape(128, ufi, 16384).startswith("S=4,VW=4,D=%d" % d4)
+        # as two tiles of half the width
+        assert bench.kernel_shape(128, ufi, tile_cols=64) == "S=4,VW=4,D=%d, tiles of 64 columns" % d4
+        assert bench.kernel_shape(64, ufi, tile_cols=32) == "S=8,VW=4,D=%d, tiles of 32 columns" % d8
+        assert bench.kernel_shape(128, ufi, tile_cols=128) == "S=2,VW=4,D=%d" % d2
     # plans made for narrow B: chunks of 16 / 32 / 64 columns on 8 / 16 / 32 or 64 slices, depth by height
     narrow = {int(u): int(d) for u, d in re.findall(r"case (\d): ok = launch_narrow<\d, (\d)>\(", src)}
     assert sorted(narrow) == [1, 2, 4, 8]
