@@ -39,6 +39,26 @@ constexpr int waves_per_simd(int S, int UFI, int UFKT, bool WIDE)
     return WIDE ? (narrow > 4 ? narrow - 2 : 2) : narrow;
 }
 
+// Chunks of B rows that a wave of an instance has in flight: the shallowest pipeline that keeps the
+// loads flowing (see waves_per_simd); one column slot per slice (8 slices) needs more chunks
+// in flight for the same number of requests.  Single rows in two slices make four loads per chunk, and
+// up to 32 waves per compute unit keep the gather busy by themselves: looking a chunk ahead only costs work at
+// the ends of the short windows (4096 x 4096, 95 % pruned, 128 columns: 18.0 us with two in flight, 17.4 with
+// one; 22 even and uneven matrices 2 to 12 % faster).  64-bit addresses keep two, and so does a caller who asks for more.
+// Plans made for narrow B, two: a wave has five to thirty of their wide chunks, and every further one in flight lengthens the start of
+// its window (8192 x 8192, 98 % pruned, 32 columns: 9.5 us with four, 9.0 with three, 8.6 with two; 40 of
+// 48 plans of one to eight rows are fastest with two or, by less than 2 %, three).
+constexpr int chunk_depth(int UFI, int UFKT, int S)
+{
+    return UFKT > spmm_fmt::UFK ? 2
+           : S == 1             ? 3
+           : S == 2             ? (UFI == 1 ? 1 : 2)
+           : S == 4             ? (UFI >= 4 ? 3 : 2)
+           : UFI >= 4           ? 4
+           : UFI == 2           ? 6
+                                : 8;
+}
+
 // Workgroups of an instance that share a compute unit: by its registers, and by 160 KiB of LDS.
 constexpr int workgroups_per_unit(int S, int UFI, int UFKT, bool WIDE)
 {
@@ -136,6 +156,9 @@ inline uint32_t front_blocks(const spmm_launch_args &a)
 // ufk = columns per chunk of the plan: 8, or 16 / 32 / 64 with slices = 8 / 16 / 32 or 64 (tiles
 // of 32 / 16 / 8 or 4 columns; 32-bit addressing and the tuned depth only).
 int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, bool wide, int depth, void *stream);
+
+// The tuned depth of such a launch, for the tests (chunk_depth).
+extern "C" int spmm_chunk_depth(int ufi, int ufk, int slices);
 
 // Size of the library's statically allocated device scratch (one copy per device, held
 // until the process ends).

@@ -653,30 +653,26 @@ template <int U, int S, int VW, int DMAX, bool WIDE> hipError_t launch_depth(con
     return launch_instance<U, S, VW, DMAX, WIDE>(a, stream);
 }
 
-// Pipeline depths per height (D2, D4, D8 for 2, 4, 8 slices): the shallowest that keeps the
-// loads flowing (see waves_per_simd); one column slot per slice (8 slices) needs more chunks
-// in flight for the same number of requests.  Single rows in two slices make four loads per chunk, and
-// up to 32 waves per compute unit keep the gather busy by themselves: looking a chunk ahead only costs work at
-// the ends of the short windows (4096 x 4096, 95 % pruned, 128 columns: 18.0 us with two in flight, 17.4 with
-// one; 22 even and uneven matrices 2 to 12 % faster).  64-bit addresses keep two, and so does a caller who asks for more.
-template <int U, int D2, int D4, int D8> void launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream, hipError_t &ok)
+template <int U> hipError_t launch_slices(const spmm_launch_args &a, int slices, bool wide, int depth, void *stream)
 {
+    constexpr int D2 = chunk_depth(U, UFK, 2), D4 = chunk_depth(U, UFK, 4), D8 = chunk_depth(U, UFK, 8), D1 = chunk_depth(U, UFK, 1);
     switch (slices) {
-    case 2: ok = wide ? launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream); break;
-    case 4: ok = wide ? launch_depth<U, 4, 4, D4, true>(a, depth, stream) : launch_depth<U, 4, 4, D4, false>(a, depth, stream); break;
-    case 8: ok = wide ? launch_depth<U, 8, 4, D8, true>(a, depth, stream) : launch_depth<U, 8, 4, D8, false>(a, depth, stream); break;
-    default: ok = wide ? launch_depth<U, 1, 1, 3, true>(a, depth, stream) : launch_depth<U, 1, 1, 3, false>(a, depth, stream); break;
+    case 2:
+        if (D2 == 1 && !wide && depth > 1) return launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), false>(a, depth, stream);
+        return wide ? launch_depth<U, 2, 4, (D2 > 1 ? D2 : 2), true>(a, depth, stream) : launch_depth<U, 2, 4, D2, false>(a, depth, stream);
+    case 4: return wide ? launch_depth<U, 4, 4, D4, true>(a, depth, stream) : launch_depth<U, 4, 4, D4, false>(a, depth, stream);
+    case 8: return wide ? launch_depth<U, 8, 4, D8, true>(a, depth, stream) : launch_depth<U, 8, 4, D8, false>(a, depth, stream);
+    default: return wide ? launch_depth<U, 1, 1, D1, true>(a, depth, stream) : launch_depth<U, 1, 1, D1, false>(a, depth, stream);
     }
 }
 
 // Plans made for narrow B (chunks of 16, 32 or 64 columns): one instance per height and chunk
 // width pair, 32-bit addressing only.  slices: 8 (tile of 32 columns, chunks of 16), 16 (16
-// columns, chunks of 32), 32 or 64 (8 or 4 columns, chunks of 64).  Two chunks in flight: a wave
-// has five to thirty of these wide chunks, and every further one in flight lengthens the start of
-// its window (8192 x 8192, 98 % pruned, 32 columns: 9.5 us with four, 9.0 with three, 8.6 with two; 40 of
-// 48 plans of one to eight rows are fastest with two or, by less than 2 %, three).
-template <int U, int D> hipError_t launch_narrow(const spmm_launch_args &a, int ufk, int slices, void *stream)
+// columns, chunks of 32), 32 or 64 (8 or 4 columns, chunks of 64).
+template <int U> hipError_t launch_narrow(const spmm_launch_args &a, int ufk, int slices, void *stream)
 {
+    constexpr int D = chunk_depth(U, 16, 8);
+    static_assert(D == chunk_depth(U, 32, 16) && D == chunk_depth(U, 64, 32) && D == chunk_depth(U, 64, 64), "one depth for all of them");
     if (a.probe && ufk == 16 && slices == 8) return launch_instance<U, 8, 4, D, false, 16, true>(a, stream);
     if (ufk == 16 && slices == 8) return launch_instance<U, 8, 4, D, false, 16>(a, stream);
     if (ufk == 32 && slices == 16) return launch_instance<U, 16, 4, D, false, 32>(a, stream);
@@ -698,24 +694,16 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
         return spmm_launch_chunks(dealt, ufi, ufk, slices, wide, depth, stream);
     }
     hipError_t ok = hipErrorInvalidValue;
-    if (ufk != UFK) {
-        if (!wide) {
-            switch (ufi) {
-            case 8: ok = launch_narrow<8, 2>(a, ufk, slices, stream); break;
-            case 4: ok = launch_narrow<4, 2>(a, ufk, slices, stream); break;
-            case 2: ok = launch_narrow<2, 2>(a, ufk, slices, stream); break;
-            case 1: ok = launch_narrow<1, 2>(a, ufk, slices, stream); break;
-            }
-        }
-    } else if (ufi == 1 && slices == 2 && !wide && depth > 1) {
-        ok = launch_depth<1, 2, 4, 2, false>(a, depth, stream);
-    } else {
-        switch (ufi) {
-        case 8: launch_slices<8, 2, 3, 4>(a, slices, wide, depth, stream, ok); break;
-        case 4: launch_slices<4, 2, 3, 4>(a, slices, wide, depth, stream, ok); break;
-        case 2: launch_slices<2, 2, 2, 6>(a, slices, wide, depth, stream, ok); break;
-        case 1: launch_slices<1, 1, 2, 8>(a, slices, wide, depth, stream, ok); break;
-        }
+    if (ufk == UFK) {
+        if (ufi == 8) ok = launch_slices<8>(a, slices, wide, depth, stream);
+        if (ufi == 4) ok = launch_slices<4>(a, slices, wide, depth, stream);
+        if (ufi == 2) ok = launch_slices<2>(a, slices, wide, depth, stream);
+        if (ufi == 1) ok = launch_slices<1>(a, slices, wide, depth, stream);
+    } else if (!wide) {
+        if (ufi == 8) ok = launch_narrow<8>(a, ufk, slices, stream);
+        if (ufi == 4) ok = launch_narrow<4>(a, ufk, slices, stream);
+        if (ufi == 2) ok = launch_narrow<2>(a, ufk, slices, stream);
+        if (ufi == 1) ok = launch_narrow<1>(a, ufk, slices, stream);
     }
     if (ok == hipSuccess && a.n_cross > 0)
         ok = launch_kernel(spmm_cross_combine_kernel, dim3((unsigned)a.n_cross, (unsigned)a.n_tiles), 256, 0, (hipStream_t)stream, a.cross_table, a.cross_sums,
@@ -727,6 +715,8 @@ int spmm_launch_chunks(const spmm_launch_args &a, int ufi, int ufk, int slices, 
     }
     return (int)ok;
 }
+
+int spmm_chunk_depth(int ufi, int ufk, int slices) { return chunk_depth(ufi, ufk, slices); }
 
 // Scratch memory that exists without any allocation call: a device array of the library's
 // code object, for callers of spmm_execute_static.  In host code the array's name is only a

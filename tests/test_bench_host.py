@@ -1,11 +1,11 @@
 """Host-side checks of bench.py: the byte model, the kernel label it prints against the
-launch table of the kernels' source, and the refusal of more than one GPU."""
+launch table of the library, and the refusal of more than one GPU."""
 import os
-import re
 import subprocess
 import sys
 
 import bench
+import paper_2506_15174_amd as spmm
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -17,10 +17,8 @@ def test_algorithmic_bytes_model():
 
 
 def test_kernel_label_follows_the_launch_table():
-    src = open(os.path.join(ROOT, "paper_2506_15174_amd", "csrc", "spmm_kernels.hip")).read()
-    table = {int(u): (int(d2), int(d4), int(d8))
-             for u, d2, d4, d8 in re.findall(r"case (\d): launch_slices<\d, (\d), (\d), (\d)>\(", src)}
-    assert sorted(table) == [1, 2, 4, 8]
+    depth = spmm.load().spmm_chunk_depth
+    table = {ufi: tuple(depth(ufi, 8, slices) for slices in (2, 4, 8)) for ufi in (1, 2, 4, 8)}
     for ufi, (d2, d4, d8) in table.items():
         assert bench.kernel_shape(128, ufi) == "S=2,VW=4,D=%d" % d2
         assert bench.kernel_shape(64, ufi) == "S=4,VW=4,D=%d" % d4
@@ -32,8 +30,7 @@ def test_kernel_label_follows_the_launch_table():
         assert bench.kernel_shape(64, ufi, tile_cols=32) == "S=8,VW=4,D=%d, tiles of 32 columns" % d8
         assert bench.kernel_shape(128, ufi, tile_cols=128) == "S=2,VW=4,D=%d" % d2
     # plans made for narrow B: chunks of 16 / 32 / 64 columns on 8 / 16 / 32 or 64 slices, depth by height
-    narrow = {int(u): int(d) for u, d in re.findall(r"case (\d): ok = launch_narrow<\d, (\d)>\(", src)}
-    assert sorted(narrow) == [1, 2, 4, 8]
+    narrow = {ufi: depth(ufi, 16, 8) for ufi in (1, 2, 4, 8)}
     for ufi, d in narrow.items():
         assert bench.kernel_shape(32, ufi, ufk=16) == "S=8,VW=4,D=%d,UFK=16" % d
         assert bench.kernel_shape(16, ufi, ufk=32) == "S=16,VW=4,D=%d,UFK=32" % d
@@ -93,7 +90,6 @@ def test_build_refuses_kernel_instances_that_spill():
 
 def test_facts_of_a_plan_on_tiles():
     """Of a plan on tiles the benchmark prints the tiles' facts and none of the chunk schedule that it does not use."""
-    import paper_2506_15174_amd as spmm
     info = spmm.plan_create(3, 4, [0, 2, 2, 3], [0, 3, 1], [1.0, 2.0, 3.0], host_only=True).describe()
     assert bench.schedule_of(info, bench.PLAN_KEYS) == {k: info[k] for k in bench.PLAN_KEYS}
     on_tiles = bench.schedule_of(dict(info, tile_rows=16), bench.PLAN_KEYS)
