@@ -78,6 +78,48 @@ def check_no_spills(remarks):
     return seen
 
 
+def check_waits_at_barriers(assembly):
+    """A kernel that waits for all loads but the youngest n before a barrier (`s_waitcnt vmcnt(n) lgkmcnt(0)`, `s_barrier`) has
+    loads to LDS in flight that other waves read behind it: on every way to the wait at least n plain loads must come after the last of those, or
+    the barrier lets a stale row through.  Walks the compiler's assembly back from every such wait; returns how many there are, raises where an order is another."""
+    import re
+    label = re.compile(r"^(\S+):")
+    lines = [ln.split(";")[0].strip() for ln in assembly.splitlines()]
+    lines = [ln for ln in lines if ln and (not ln.startswith(".") or label.match(ln))]
+    at = {label.match(ln).group(1): i for i, ln in enumerate(lines) if label.match(ln)}
+    to = {}
+    for i, ln in enumerate(lines):
+        m = re.match(r"s_c?branch\S*\s+(\S+)", ln)
+        if m and m.group(1) in at:
+            to.setdefault(at[m.group(1)], []).append(i)
+    checked = 0
+    for i, ln in enumerate(lines[:-1]):
+        m = re.match(r"s_waitcnt vmcnt\((\d+)\) lgkmcnt\(0\)$", ln)
+        if not m or m.group(1) == "0" or lines[i + 1] != "s_barrier":
+            continue
+        checked += 1
+        todo, seen = [(i, int(m.group(1)))], set()
+        while todo:
+            j, left = todo.pop()
+            if left == 0 or (j, left) in seen:
+                continue
+            seen.add((j, left))
+            before = list(to.get(j, []))
+            if j > 0 and not re.match(r"s_branch|s_endpgm|s_setpc", lines[j - 1]):
+                before.append(j - 1)
+            for k in before:
+                op = lines[k]
+                if re.match(r"s_waitcnt.*vmcnt\(0\)", op):
+                    continue  # nothing older is in flight
+                if re.match(r"(buffer|global|flat|scratch)_", op):
+                    if not re.match(r"(buffer|global)_load", op) or op.endswith(" lds") or "_load_lds" in op:
+                        raise RuntimeError("a barrier waits for all but %s loads, and %d before it is `%s`" % (m.group(1), int(m.group(1)) - left + 1, op))
+                    todo.append((k, left - 1))
+                else:
+                    todo.append((k, left))
+    return checked
+
+
 def build(verbose=False):
     """Compile every source for gfx950 and link the shared library.
 
@@ -105,6 +147,16 @@ def build(verbose=False):
             n = check_no_spills(remarks)
             if verbose:
                 print("%s: %d kernel instances, none uses scratch memory" % (s, n))
+        if s == "spmm_strips.hip":
+            listing = obj[:-2] + ".s"
+            _run(cmd + common + ["-S", "--cuda-device-only", os.path.join(CSRC, s), "-o", listing], False)
+            with open(listing) as f:
+                n = check_waits_at_barriers(f.read())
+            os.remove(listing)
+            if n < 4:
+                raise RuntimeError("%s: of the barriers behind a strip's copy, one in each kernel, %d were found" % (s, n))
+            if verbose:
+                print("%s: %d barriers that loads may cross, none of them to LDS" % (s, n))
         objects.append(obj)
     _run([hipcc, "-shared", "-fPIC"] + objects +
          ["-L", os.path.join(ROCM, "lib"), "-lamdhip64", "-pthread", "-o", LIB_PATH], verbose)

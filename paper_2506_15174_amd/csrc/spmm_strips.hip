@@ -175,6 +175,7 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
             const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(stream), (short)0, (int)(groups * STRIP_GROUP_BYTES), 0x00020000);
             f32x4 values[AHEAD];
             u32x2 places[AHEAD];
+            constexpr int LOADS = 2;               // of a fetch
             auto fetch = [&](int k, uint32_t g) {  // nothing past the unit
                 values[k] = __builtin_bit_cast(f32x4, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(r, lane * 16, (int)(g * STRIP_GROUP_BYTES), 0));
                 places[k] = __builtin_amdgcn_raw_buffer_load_b64(r, 1024 + lane * 8, (int)(g * STRIP_GROUP_BYTES), 0);
@@ -192,8 +193,9 @@ template <bool BANDS, bool WIDE> __global__ __launch_bounds__(64 * STRIP_WAVES, 
                 copy_band((uint32_t)band);
                 __syncthreads();
             } else if (!copied) {
-                // all loads but the four of the entries, which a barrier of the compiler's would wait for too
-                asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                // All loads but those of the two fetches, which a barrier of the compiler's would wait for too: the copy's are older than
+                // theirs, and none is younger (the build looks whether the compiler kept it so: check_waits_at_barriers).
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * LOADS) : "memory");
             }
             copied = true;
             if (!BANDS || band + 1 == bands) word = args.rows[(size_t)(any ? unit : 0u) * 64u + (uint32_t)lane];

@@ -88,6 +88,40 @@ def test_build_refuses_kernel_instances_that_spill():
         build.check_no_spills("")
 
 
+def test_build_refuses_a_barrier_that_a_load_to_lds_may_cross():
+    """The build walks the compiler's assembly back from the barrier behind a strip's copy: the loads that may cross it are the
+    entries', on every way."""
+    import pytest
+    from paper_2506_15174_amd import build
+    ok = """
+kernel:
+        s_cbranch_scc1 .LBB0_2
+.LBB0_1:                                ; %copy
+        buffer_load_dwordx4 v2, s[0:3], 0 offen lds
+        s_cbranch_scc1 .LBB0_1
+.LBB0_2:
+        buffer_load_dwordx4 v[4:7], v3, s[4:7], 0 offen
+        buffer_load_dwordx2 v[8:9], v3, s[4:7], 0 offen
+        s_cbranch_vccz .LBB0_4
+        s_waitcnt vmcnt(2) lgkmcnt(0)
+        s_barrier
+.LBB0_4:
+        s_endpgm
+"""
+    entry = "        buffer_load_dwordx2 v[8:9], v3, s[4:7], 0 offen\n"
+    copy = "        buffer_load_dwordx4 v2, s[0:3], 0 offen lds\n"
+    assert build.check_waits_at_barriers(ok) == 1
+    assert build.check_waits_at_barriers(ok.replace("vmcnt(2)", "vmcnt(0)")) == 0  # the compiler's own
+    for bad in (ok.replace(entry, ""),                                                      # one load fewer
+                ok.replace(entry, copy + entry), ok.replace(entry, entry + copy),           # the copy between them, and after
+                ok.replace(entry, entry + "        global_store_dword v1, v2, s[0:1]\n"),   # counted with the loads, in no order with them
+                ok.replace(".LBB0_2:", "        s_cbranch_vccz .LBB0_3\n.LBB0_2:").replace(entry, ".LBB0_3:\n" + entry)):  # a way past one of them
+        with pytest.raises(RuntimeError, match="all but 2 loads"):
+            build.check_waits_at_barriers(bad)
+    waited = ok.replace(entry, "        s_waitcnt vmcnt(0)\n" + entry)
+    assert build.check_waits_at_barriers(waited) == 1  # one load in flight, and nothing older
+
+
 def test_facts_of_a_plan_on_tiles():
     """Of a plan on tiles the benchmark prints the tiles' facts and none of the chunk schedule that it does not use."""
     info = spmm.plan_create(3, 4, [0, 2, 2, 3], [0, 3, 1], [1.0, 2.0, 3.0], host_only=True).describe()
