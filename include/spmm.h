@@ -104,7 +104,8 @@ typedef struct {
     int32_t force_wide;    /* nonzero: spmm_execute uses the 64-bit addressing kernels also where B
                               is small enough for 32-bit offsets (lets small inputs exercise them) */
     int32_t threads;       /* host threads of the inspector, 1..64 (0 = one per 2^16 entries,
-                              at most 16 and at most the machine's; the plan does not depend on it) */
+                              at most 16 and at most the machine's; for panels of single rows below 2^20 entries
+                              one per 2^14 entries of rows whose columns do not ascend; the plan does not depend on it) */
     int32_t depth;         /* chunks of B rows a wave keeps in flight (the software pipeline's depth,
                               the paper's unroll(k, UFk) axis of Figure 2): 1, 2, 3, 4 or 8;
                               0 = the depth tuned per kernel instance.  A depth the register budget

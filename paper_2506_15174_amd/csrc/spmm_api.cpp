@@ -80,13 +80,13 @@ int32_t heavy_blocks(const HostPlan &h)
 // A gather is bound by the unit's vector L1, so a unit's time is the sum of its blocks' chunks; a block's start and end
 // count as STARTING chunks.  A plan whose fullest unit gains less than 3 % keeps its order.
 //
-// In the plan's own order (the first and third with room for two workgroups on a unit, by LDS that they did not use) and dealt, lognormal rows:
-//   1024 x 4096, 90 % pruned, 64 columns, 560 blocks     8.8 -> 7.5 us
-//   1024 x 2048, 90 %, 64 columns, 286 blocks            6.5 -> 5.1
-//   1536 x 6144, 95 %, 64 columns, 646 blocks            9.7 -> 7.6
-//   700 x 5000, 90 %, 100 columns, 323 of two rows      14.7 -> 11.2
-//   2048 x 4096, 90 %, 32 columns, 932 blocks            8.2 -> 7.1
-//   5000 x 2000, 97 %, 128 columns, 704 blocks           9.0 -> 8.2
+// In the plan's own order and dealt, lognormal rows, three plans and B in turn, us:
+//   1024 x 4096, 90 % pruned, 64 columns, 552 blocks    10.0 -> 8.0
+//   1024 x 2048, 90 %, 64 columns, 283 blocks            6.1 -> 5.2
+//   1536 x 6144, 95 %, 64 columns, 644 blocks           10.3 -> 8.9
+//   700 x 5000, 90 %, 100 columns, 321 of two rows      14.8 -> 13.1
+//   2048 x 4096, 90 %, 32 columns, about 1000 blocks     8.6 -> 8.1
+//   5000 x 2000, 97 %, 128 columns, 703 blocks           9.5 -> 8.8
 // Twenty even, lognormal and Zipf matrices 8 % on average, none slower.  More blocks than the chip holds go to whichever unit is done first,
 // and several column tiles have an order of their own (front_blocks).
 std::vector<uint32_t> deal_blocks(const HostPlan &h, int per_unit)

@@ -9,21 +9,16 @@
 #include "spmm_format.h"
 #include "spmm_places.h"
 
-// Waves per SIMD the register budget of an instance is sized for.  Narrow slices
-// keep few B rows in flight per wave and walk a long dependent chain per chunk
-// (header, row branches, LDS reads), so they need more resident waves to cover
-// it: 8 (64 VGPRs) with eight slices, 6 (80 VGPRs) with four, 4 (128 VGPRs)
-// with two.  The eight-row tile alone is 32 registers: 4 waves whatever the slices
-// (sized for 6, the eight-slice instance spilled 68 registers and ran 10-28 % slower).
 // Waves per SIMD an instance is compiled for (its register budget: 512 / waves).  Measured on
 // the pruned-layer shapes with every depth forced: past two or three chunks in flight a deeper
 // pipeline buys nothing (the memory path, not the number of requests a wave has outstanding,
 // paces the gather), while every further resident wave hides more of the chunk's dependent
 // chain (header, row branches, value reads).  So each instance takes the shallowest pipeline
-// that keeps the loads flowing and the occupancy its tile allows: eight-row tiles 4 waves
-// (6 on four slices), four-row tiles 4 waves on two slices and 8 otherwise, shorter tiles 6 to
+// that keeps the loads flowing and the occupancy its tile allows: eight-row tiles, 32 registers by themselves, 4 waves
+// (6 on four slices; on eight, sized for 6, 68 registers spilled and it ran 10-28 % slower), four-row tiles 4 waves on two slices and 8 otherwise, shorter tiles 6 to
 // 8.  Wider chunks (UFKT > 8) give a slice two column slots per chunk: 8 waves (6 with eight
-// rows); windows of 2048 words (UFKT >= 32) cap a compute unit at two workgroups.
+// rows) on 16 columns, where 6 (4) are as fast but for the blocks that may be dealt (workgroups_per_unit; single rows at 18 to 32 columns, in
+// us: 2048 x 4096, 90 % lognormal, 8.6 -> 8.0, 11461 x 2261, 95 %, 11.4 -> 11.2, ten others within 1.5 %); windows of 2048 words (UFKT >= 32) cap a compute unit at two workgroups.
 // Every budget is one the instance fits without spilling (the build checks it): a spilled
 // register could be the destination of a B row still in flight.  64-bit addressing costs a
 // register more per column slot, so those instances get the budget of two waves fewer.

@@ -371,6 +371,7 @@ __global__ __launch_bounds__(64 * W, MINW) void spmm_tiles_kernel(const tile_arg
 //                 1.2   512 x 2048, 80 %, 128          6.68 and 5.99
 //                 3.8   1024 x 2048, 70 %, 128         9.12 and 9.11     (32 rows: 4096 x 1024, 70 %, 128, 15: 12.2 and 12.4)
 // Rows that are not whole lines: 512 x 2048, 75 %, 100 columns 6.69 and 7.00.
+// 11 random products that it takes 2.5 % faster on average, 1 % slower at worst; 49 others 0.93 to 1.06 times as fast in two sets, 0.99 on average.
 uint32_t tiles_of_set(int tile_cols, uint32_t tiles, int64_t K, int32_t N, int64_t stream_words)
 {
     const uint32_t line = tile_cols < 32 ? 32 / (uint32_t)tile_cols : 1, half = ((tiles + 1) / 2 + line - 1) / line * line;
