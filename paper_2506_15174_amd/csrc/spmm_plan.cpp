@@ -851,8 +851,12 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
         // the time on 1.3 million.  Rows out of order are sorted first, 50 ns an entry: a thread for every 2^14 of theirs.  On one thread
         // and so, 8 cores, ms: 1024 x 4096 at 90 % 23.8 and 6.2 with all rows out of order, 9.4 and 3.3 with three of ten, 3.0 and 2.6 with one of
         // twenty; 2048 x 4096 at 90 % 48.2 and 9.4, 18.8 and 5.3, 6.9 and 5.1; 900 x 3000 at 95 % 7.1 and 4.9, 2.9 and 2.4, 1.3 and 1.3.
-        if (opts.threads < 1 && ufi == 1 && nnz < FEW_ENTRIES && !opts.schedule_only)
-            threads = (int)std::min<int64_t>(threads, std::max<int64_t>(1, entries_out_of_order(row_ptr, col_idx, M) >> 14));
+        bool ascending = false;  // known to
+        if (opts.threads < 1 && ufi == 1 && nnz < FEW_ENTRIES && !opts.schedule_only) {
+            const int64_t to_sort = entries_out_of_order(row_ptr, col_idx, M);
+            ascending = to_sort == 0;
+            threads = (int)std::min<int64_t>(threads, std::max<int64_t>(1, to_sort >> 14));
+        }
         // single rows share nothing: sorting them would only scatter the rows of C
         const bool sorted = opts.sort_rows > 0 || (opts.sort_rows == 0 && skewed && ufi > 1);
         // row_order[i]: the matrix row that row i of a slice stands for (sorted plans only)
@@ -958,7 +962,8 @@ int spmm_inspect(int64_t M, int64_t K, const int32_t *row_ptr, const int32_t *co
                         const int32_t *col = col_idx + a;
                         const float *val = vals + a;
                         bool in_order = true;
-                        for (int64_t q = 1; q < n; ++q) in_order &= col[q] >= col[q - 1];
+                        if (!ascending)
+                            for (int64_t q = 1; q < n; ++q) in_order &= col[q] >= col[q - 1];
                         if (!in_order) {  // stable, as below
                             order.resize((size_t)n);
                             std::iota(order.begin(), order.end(), 0);
