@@ -467,7 +467,8 @@ def _ladder_matrices(gen):
 def run_ablation(args):
     """The ingredients of the method switched on one by one on 30 sweep matrices (paper
     Section 4.3, Figure 7: baseline -> + enumeration -> + coarsening), as geometric-mean
-    GFLOP/s per column count:
+    GFLOP/s per column count (every rung up to +ranges runs on chunks, with its blocks dealt to the
+    compute units by weight and its columns in two tiles where a plan gets that: no option turns it off):
       rows        one wave per row, rows never cut, no B row requested before the
                   previous chunk is multiplied (the paper's Figure 1a mapping with this
                   kernel's chunked B loads)
